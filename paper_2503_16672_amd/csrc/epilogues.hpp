@@ -1,5 +1,7 @@
 // Epilogues of the GEMM core: what happens to a lane's 4x4x16 accumulators.
-// A lane owns rows m_lane + 16*mi + v (64 consecutive) and columns n_lane + ni (4 consecutive).
+// A lane owns rows m_lane + 16*mi + v (16 MI consecutive) and columns n_lane + ni (NI consecutive), MI x NI = 4 x 4 for the 256 x 256
+// block tile and less for the smaller ones.  Where a lane holds less than a whole piece of a panel form (64 features), it starts
+// m_lane % 64 features into it.
 #pragma once
 #include "gemm_core.hpp"
 #include "launch.hpp"
@@ -17,57 +19,97 @@ __device__ __forceinline__ void tele_add2(unsigned long long* tele, uint32_t pac
   }
 }
 
-// A per-feature fp32 vector (bias, weight scale) over the lane's 64 features m_lane .. m_lane + 63, loaded once with
-// 16-byte loads and shared by the lane's 4 tokens; `fill` everywhere if the vector is absent.
-struct LaneVec64 {
-  f32x4 v[16];
+// A per-feature fp32 vector (bias, weight scale) over the lane's 16 MI features from m_lane on, loaded once with
+// 16-byte loads and shared by the lane's tokens; `fill` everywhere if the vector is absent.
+template <int MI>
+struct LaneVec {
+  f32x4 v[4 * MI];
   __device__ __forceinline__ void load(const float* p, int m_lane, float fill) {
 #pragma unroll
-    for (int i = 0; i < 16; i++) v[i] = f32x4{fill, fill, fill, fill};
+    for (int i = 0; i < 4 * MI; i++) v[i] = f32x4{fill, fill, fill, fill};
     if (p) {
 #pragma unroll
-      for (int i = 0; i < 16; i++) v[i] = *reinterpret_cast<const f32x4*>(p + m_lane + 4 * i);
+      for (int i = 0; i < 4 * MI; i++) v[i] = *reinterpret_cast<const f32x4*>(p + m_lane + 4 * i);
     }
   }
   __device__ __forceinline__ float at(int i) const { return v[i >> 2][i & 3]; }   // feature m_lane + i
 };
 
-// The lane's 64 entries m_lane .. m_lane + 63 of a row map, loaded with 16-byte loads (the map and m_lane are 16-byte aligned).
-struct LaneIdx64 {
-  i32x4 v[16];
+// The lane's 16 MI entries of a row map from m_lane on, loaded with 16-byte loads (the map and m_lane are 16-byte aligned).
+template <int MI>
+struct LaneIdx {
+  i32x4 v[4 * MI];
   __device__ __forceinline__ void load(const int* p, int m_lane) {
 #pragma unroll
-    for (int i = 0; i < 16; i++) v[i] = *reinterpret_cast<const i32x4*>(p + m_lane + 4 * i);
+    for (int i = 0; i < 4 * MI; i++) v[i] = *reinterpret_cast<const i32x4*>(p + m_lane + 4 * i);
   }
   __device__ __forceinline__ int at(int i) const { return v[i >> 2][i & 3]; }
 };
 
-// What the backward epilogues read back of the forward's saved activation, for the lane's 4 tokens x 64 features, requested in one
+// The 4 MI nibbles of a lane's groups (MI 16-bit words, low group first) to and from the metadata bytes.
+template <int MI> __device__ __forceinline__ void st_nibbles(uint8_t* p, const uint32_t (&nib)[2]) {
+  if constexpr (MI == 4) *reinterpret_cast<u32x2*>(p) = u32x2{nib[0], nib[1]};
+  else if constexpr (MI == 2) *reinterpret_cast<uint32_t*>(p) = nib[0];
+  else *reinterpret_cast<uint16_t*>(p) = (uint16_t)nib[0];
+}
+template <int MI> __device__ __forceinline__ u32x2 ld_nibbles(const uint8_t* p) {
+  if constexpr (MI == 4) return *reinterpret_cast<const u32x2*>(p);
+  else if constexpr (MI == 2) return u32x2{*reinterpret_cast<const uint32_t*>(p), 0u};
+  else return u32x2{*reinterpret_cast<const uint16_t*>(p), 0u};
+}
+
+// NI consecutive bf16 results of one row, rounded and stored in one go
+template <int NI> __device__ __forceinline__ void st_cols(__bf16* p, const float (&x)[NI]) {
+  if constexpr (NI == 4) *reinterpret_cast<u32x2*>(p) = u32x2{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3])};
+  else if constexpr (NI == 2) *reinterpret_cast<uint32_t*>(p) = pack_bf16x2(x[0], x[1]);
+  else *p = (__bf16)x[0];
+}
+// byte b of NI words, stored as NI consecutive bytes
+template <int NI> __device__ __forceinline__ void st_bytes(uint8_t* p, const uint32_t (&w)[NI], int b) {
+  uint32_t o = 0u;
+#pragma unroll
+  for (int i = 0; i < NI; i++) o |= ((w[i] >> (8 * b)) & 0xFFu) << (8 * i);
+  if constexpr (NI == 4) *reinterpret_cast<uint32_t*>(p) = o;
+  else if constexpr (NI == 2) *reinterpret_cast<uint16_t*>(p) = (uint16_t)o;
+  else *p = (uint8_t)o;
+}
+// 2 MI words (8 MI bytes) of e4m3 codes
+template <int MI> __device__ __forceinline__ void st_codes(uint8_t* p, const uint32_t (&q)[2 * MI]) {
+  if constexpr (MI == 1) *reinterpret_cast<u32x2*>(p) = u32x2{q[0], q[1]};
+  else {
+#pragma unroll
+    for (int i = 0; i < MI / 2; i++) *reinterpret_cast<u32x4*>(p + 16 * i) = u32x4{q[4 * i], q[4 * i + 1], q[4 * i + 2], q[4 * i + 3]};
+  }
+}
+
+// What the backward epilogues read back of the forward's saved activation, for the lane's tokens x features, requested in one
 // go before any arithmetic or store: a load placed inside the loops is followed by stores through pointers the compiler must assume
 // may alias, so each one waited out a full memory round trip by itself (16 of them in the 2:4 epilogue, 32 in the dense one -- the
 // latter had made the dense dH kernel 0.4 ms slower than the GEMM alone).
-// 2:4: one 64-byte piece of kept values + 8 metadata bytes per token (bf16 panel form).
+// 2:4: one 64-byte piece (or part) of kept values + its metadata bytes per token (bf16 panel form).
+template <int MI, int NI>
 struct LaneSaved24 {
-  u32x4 h[4][4];   // [ni][mi]: the kept values of groups 4 mi .. 4 mi + 3
-  u32x2 mt[4];
+  u32x4 h[NI][MI];   // [ni][mi]: the kept values of groups 4 mi .. 4 mi + 3
+  u32x2 mt[NI];
   __device__ __forceinline__ void load(const __bf16* Hc, const uint8_t* meta, int F, int m_lane, int n_lane) {
 #pragma unroll
-    for (int ni = 0; ni < 4; ni++) {
+    for (int ni = 0; ni < NI; ni++) {
       size_t piece = a24_piece(n_lane + ni, m_lane >> 6, F >> 6);
-      mt[ni] = *reinterpret_cast<const u32x2*>(meta + piece * 8);
+      mt[ni] = ld_nibbles<MI>(meta + piece * 8 + ((m_lane & 63) >> 3));
 #pragma unroll
-      for (int mi = 0; mi < 4; mi++) h[ni][mi] = *reinterpret_cast<const u32x4*>(Hc + piece * 32 + 8 * mi);
+      for (int mi = 0; mi < MI; mi++) h[ni][mi] = *reinterpret_cast<const u32x4*>(Hc + piece * 32 + ((m_lane & 63) >> 1) + 8 * mi);
     }
   }
 };
 // dense: the bf16 activation in dense panel form (64-byte pieces of 32 features), 16 features per (mi, ni).
+template <int MI, int NI>
 struct LaneSavedDense {
-  u32x4 h[4][4][2];   // [mi][ni][q]: features 16 mi + 8 q .. + 7 of token ni
+  u32x4 h[MI][NI][2];   // [mi][ni][q]: features 16 mi + 8 q .. + 7 of token ni
   __device__ __forceinline__ void load(const __bf16* H, int F, int m_lane, int n_lane) {
 #pragma unroll
-    for (int mi = 0; mi < 4; mi++)
+    for (int mi = 0; mi < MI; mi++)
 #pragma unroll
-      for (int ni = 0; ni < 4; ni++) {
+      for (int ni = 0; ni < NI; ni++) {
         int f = m_lane + 16 * mi;
         const __bf16* p = H + a24_piece(n_lane + ni, f >> 5, F >> 5) * 32 + (f & 31);
         h[mi][ni][0] = *reinterpret_cast<const u32x4*>(p);
@@ -79,62 +121,64 @@ struct LaneSavedDense {
 // C[m][n], n contiguous: 4 consecutive columns per lane and row -> one 8-byte store per row.
 struct EpiRowMajor {
   struct Args { __bf16* C; int ldc; };
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[4][4], int m_lane, int n_lane) {
+  template <int MI, int NI>
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
 #pragma unroll
-    for (int mi = 0; mi < 4; mi++)
+    for (int mi = 0; mi < MI; mi++)
 #pragma unroll
       for (int v = 0; v < 16; v++) {
-        u32x2 o;
-        o[0] = pack_bf16x2(acc[mi][0][v], acc[mi][1][v]);
-        o[1] = pack_bf16x2(acc[mi][2][v], acc[mi][3][v]);
-        *reinterpret_cast<u32x2*>(e.C + (size_t)(m_lane + 16 * mi + v) * e.ldc + n_lane) = o;
+        float o[NI];
+#pragma unroll
+        for (int ni = 0; ni < NI; ni++) o[ni] = acc[mi][ni][v];
+        st_cols<NI>(e.C + (size_t)(m_lane + 16 * mi + v) * e.ldc + n_lane, o);
       }
   }
 };
 
-// Transposing store of a wave's 128 (m) x 128 (n) part of the tile, out[n][m] with m contiguous, through LDS.  A lane owns 64
-// consecutive m of 4 columns n, i.e. whole 128-byte runs of 4 output rows, but one store instruction of the wave would put 64
-// 16-byte pieces into 64 different lines (32 instructions, 2048 line transactions a wave; on the short-K weight-gradient GEMMs that
-// alone made the transposing kernels 15 % slower than the row-major ones).  So the packed pieces first go to a wave-private 32
-// KiB image [n][m] in the operand ring, which is free by then (row n, 16-byte piece c at piece position c ^ ((n >> 2) & 15), so
-// that the 16 lanes an LDS instruction serves together hit 16 different positions both ways), and leave as 32 instructions that
-// write 4 rows x 256 contiguous bytes each: 8 lines an instruction.
+// Transposing store of a wave's 32 MI (m) x 32 NI (n) part of the tile, out[n][m] with m contiguous, through LDS.  With the 256 x 256
+// tile a lane owns 64 consecutive m of 4 columns n, i.e. whole 128-byte runs of 4 output rows, but one store instruction of the wave
+// would put 64 16-byte pieces into 64 different lines (32 instructions, 2048 line transactions a wave; on the short-K
+// weight-gradient GEMMs that alone made the transposing kernels 15 % slower than the row-major ones).  So the packed pieces first
+// go to a wave-private image [n][m] in the operand ring, which is free by then (rows of 4 MI pieces; row n, 16-byte piece c at
+// piece position c ^ (n / NI), so that the 16 lanes an LDS instruction serves together hit different positions both ways),
+// and leave as instructions that write whole rows of the image: 256 contiguous bytes each with MI = 4.
+template <int MI, int NI>
 struct ColMajorStage {
-  static constexpr int WAVE_BYTES = 128 * 256;
-  // piece `c` (0..15: m_local / 8) of row 4 rho + ni
-  static __device__ __forceinline__ void put(char* wbuf, int rho, int ni, int c, u32x4 v) {
-    *reinterpret_cast<u32x4*>(wbuf + (4 * rho + ni) * 256 + ((c ^ (rho & 15)) << 4)) = v;
-  }
+  static constexpr int PIECES = 4 * MI, ROWS = 32 * NI;
+  static __device__ __forceinline__ int at(int r, int c) { return (r * PIECES + (c ^ ((r / NI) & (PIECES - 1)))) << 4; }
+  // piece `c` (m_local / 8) of row NI rho + ni
+  static __device__ __forceinline__ void put(char* wbuf, int rho, int ni, int c, u32x4 v) { *reinterpret_cast<u32x4*>(wbuf + at(NI * rho + ni, c)) = v; }
   // out = the wave's corner &C[n_wave][m_wave]
   static __device__ __forceinline__ void flush(const char* wbuf, __bf16* out, int ldc) {
-    const int lane = threadIdx.x & 63, c = lane & 15, sub = lane >> 4;
+    const int lane = threadIdx.x & 63, c = lane & (PIECES - 1), sub = lane / PIECES;
+    constexpr int PER = 64 / PIECES;   // rows per store instruction
 #pragma unroll
-    for (int j = 0; j < 32; j++) {
-      const int r = 4 * j + sub;
-      u32x4 v = *reinterpret_cast<const u32x4*>(wbuf + r * 256 + ((c ^ (j & 15)) << 4));
-      *reinterpret_cast<u32x4*>(out + (size_t)r * ldc + 8 * c) = v;
+    for (int j = 0; j < ROWS / PER; j++) {
+      const int r = PER * j + sub;
+      *reinterpret_cast<u32x4*>(out + (size_t)r * ldc + 8 * c) = *reinterpret_cast<const u32x4*>(wbuf + at(r, c));
     }
   }
 };
 
-// C stored transposed, out[n][m] with m contiguous (staged through LDS, see ColMajorStage; wbuf = the wave's 32 KiB).
+// C stored transposed, out[n][m] with m contiguous (staged through LDS, see ColMajorStage).
 struct EpiColMajor {
   static constexpr bool STAGED = true;
   struct Args { __bf16* C; int ldc; };
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[4][4], int m_lane, int n_lane, char* wbuf) {
+  template <int MI, int NI>
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane, char* wbuf) {
     const int lane = threadIdx.x & 63, rho = lane & 31, h = lane >> 5;
 #pragma unroll
-    for (int ni = 0; ni < 4; ni++)
+    for (int ni = 0; ni < NI; ni++)
 #pragma unroll
-      for (int mi = 0; mi < 4; mi++)
+      for (int mi = 0; mi < MI; mi++)
 #pragma unroll
         for (int q = 0; q < 2; q++) {
           u32x4 o;
 #pragma unroll
           for (int d = 0; d < 4; d++) o[d] = pack_bf16x2(acc[mi][ni][8 * q + 2 * d], acc[mi][ni][8 * q + 2 * d + 1]);
-          ColMajorStage::put(wbuf, rho, ni, 8 * h + 2 * mi + q, o);
+          ColMajorStage<MI, NI>::put(wbuf, rho, ni, 2 * MI * h + 2 * mi + q, o);
         }
-    ColMajorStage::flush(wbuf, e.C + (size_t)(n_lane - 4 * rho) * e.ldc + (m_lane - 64 * h), e.ldc);
+    ColMajorStage<MI, NI>::flush(wbuf, e.C + (size_t)(n_lane - NI * rho) * e.ldc + (m_lane - 16 * MI * h), e.ldc);
   }
 };
 
@@ -147,14 +191,15 @@ struct EpiColMajor {
 template <bool STATS>
 struct EpiRelu2T {
   struct Args { __bf16* H; __bf16* Ht; const float* b1; int F; int T; unsigned long long* tele; };
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[4][4], int m_lane, int n_lane) {
+  template <int MI, int NI>
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
     uint32_t nonzero = 0u;   // of this lane's 256 activations
-    LaneVec64 lb;
+    LaneVec<MI> lb;
     lb.load(e.b1, m_lane, 0.f);
 #pragma unroll
-    for (int mi = 0; mi < 4; mi++) {
+    for (int mi = 0; mi < MI; mi++) {
 #pragma unroll
-      for (int ni = 0; ni < 4; ni++) {
+      for (int ni = 0; ni < NI; ni++) {
 #pragma unroll
         for (int v = 0; v < 16; v++) {
           float r = fmaxf(acc[mi][ni][v] + lb.at(16 * mi + v), 0.f);
@@ -176,10 +221,10 @@ struct EpiRelu2T {
       if (e.Ht) {
 #pragma unroll
         for (int v = 0; v < 16; v++) {
-          u32x2 o;
-          o[0] = pack_bf16x2(acc[mi][0][v], acc[mi][1][v]);
-          o[1] = pack_bf16x2(acc[mi][2][v], acc[mi][3][v]);
-          *reinterpret_cast<u32x2*>(e.Ht + a24_piece(m_lane + 16 * mi + v, n_lane >> 5, e.T >> 5) * 32 + (n_lane & 31)) = o;
+          float o[NI];
+#pragma unroll
+          for (int ni = 0; ni < NI; ni++) o[ni] = acc[mi][ni][v];
+          st_cols<NI>(e.Ht + a24_piece(m_lane + 16 * mi + v, n_lane >> 5, e.T >> 5) * 32 + (n_lane & 31), o);
         }
       }
     }
@@ -191,30 +236,32 @@ struct EpiRelu2T {
 using EpiRelu2 = EpiRelu2T<false>;
 
 // Per-feature non-zero counts of the activation epilogues (Sec. 2, "Optimization 1": the column-level sparsity the first GEMM's
-// epilogue can compute for free).  A lane counts its 4 tokens in 8-bit fields, 4 features per register: the packed pair of
+// epilogue can compute for free).  A lane counts its tokens in 8-bit fields, 4 features per register: the packed pair of
 // features 16 mi + 2 d and + 1 goes to fields (2 d) % 4 and (2 d + 1) % 4 of register 4 mi + d / 2.
-__device__ __forceinline__ void nnz_count(uint32_t (&cnt)[16], uint32_t hpk, int mi, int d) {
+template <int MI>
+__device__ __forceinline__ void nnz_count(uint32_t (&cnt)[4 * MI], uint32_t hpk, int mi, int d) {
   uint32_t lo = min(hpk & 0xFFFFu, 1u), hi = min(hpk >> 16, 1u);
   cnt[4 * mi + (d >> 1)] += (lo << (16 * (d & 1))) + (hi << (16 * (d & 1) + 8));
 }
-// The 32 lanes that hold the same 64 features add their fields up with a butterfly (<= 128 per field); lane r then adds the
-// totals of features r and r + 32 to nnz [F] with atomics (the caller zeroes it).
-__device__ __forceinline__ void nnz_flush(uint32_t (&cnt)[16], uint32_t* nnz, int m_lane) {
+// The 32 lanes that hold the same 16 MI features add their fields up with a butterfly (<= 128 per field); lane r then adds the
+// totals of features r and (MI = 4) r + 32 to nnz [F] with atomics (the caller zeroes it).
+template <int MI>
+__device__ __forceinline__ void nnz_flush(uint32_t (&cnt)[4 * MI], uint32_t* nnz, int m_lane) {
   int lane = threadIdx.x & 63;
 #pragma unroll
-  for (int i = 0; i < 16; i++)
+  for (int i = 0; i < 4 * MI; i++)
 #pragma unroll
     for (int sft = 1; sft < 32; sft <<= 1) cnt[i] += (uint32_t)__shfl_xor((int)cnt[i], sft, 64);
   int r = lane & 31;
-  uint32_t w0 = 0u, w1 = 0u;
 #pragma unroll
-  for (int i = 0; i < 8; i++) {
-    w0 = (r >> 2) == i ? cnt[i] : w0;
-    w1 = (r >> 2) == i ? cnt[8 + i] : w1;
+  for (int b = 0; b < 4 * MI; b += 8) {   // registers b .. b + 7: features 4 b .. 4 b + 31
+    uint32_t w = 0u;
+#pragma unroll
+    for (int i = 0; i < 8; i++)
+      if (b + i < 4 * MI) w = (r >> 2) == i ? cnt[b + i] : w;
+    uint32_t c = (w >> (8 * (r & 3))) & 0xFFu;
+    if (c) atomicAdd(nnz + m_lane + 4 * b + r, c);
   }
-  uint32_t c0 = (w0 >> (8 * (r & 3))) & 0xFFu, c1 = (w1 >> (8 * (r & 3))) & 0xFFu;
-  if (c0) atomicAdd(nnz + m_lane + r, c0);
-  if (c1) atomicAdd(nnz + m_lane + 32 + r, c1);
 }
 
 // Fused up-projection epilogue of the 2:4 FFN (Sec. 2: activation, then sparsification, in one pass):
@@ -234,20 +281,21 @@ __device__ __forceinline__ void nnz_flush(uint32_t (&cnt)[16], uint32_t* nnz, in
 template <bool STATS>
 struct EpiPrune24T {
   struct Args { __bf16* Hc; uint8_t* meta; __bf16* Hdbg; const float* b1; int F; uint32_t* nnz; unsigned long long* tele; };
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[4][4], int m_lane, int n_lane) {
-    uint32_t cnt[16];
+  template <int MI, int NI>
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+    uint32_t cnt[4 * MI];
     uint32_t kept = 0u;   // non-zero values among the lane's 128 stored ones
 #pragma unroll
-    for (int i = 0; i < 16; i++) cnt[i] = 0u;
-    LaneVec64 lb;
+    for (int i = 0; i < 4 * MI; i++) cnt[i] = 0u;
+    LaneVec<MI> lb;
     lb.load(e.b1, m_lane, 0.f);
 #pragma unroll
-    for (int ni = 0; ni < 4; ni++) {
+    for (int ni = 0; ni < NI; ni++) {
       size_t t = (size_t)(n_lane + ni);
-      uint32_t vals[16];
+      uint32_t vals[4 * MI];
       uint32_t nib[2] = {0u, 0u};
 #pragma unroll
-      for (int mi = 0; mi < 4; mi++) {
+      for (int mi = 0; mi < MI; mi++) {
         uint32_t hpk[8];
 #pragma unroll
         for (int d = 0; d < 8; d++) {
@@ -255,7 +303,7 @@ struct EpiPrune24T {
           float r0 = fmaxf(acc[mi][ni][2 * d] + b0, 0.f);
           float r1 = fmaxf(acc[mi][ni][2 * d + 1] + b1v, 0.f);
           hpk[d] = pack_bf16x2(r0 * r0, r1 * r1);
-          if constexpr (STATS) nnz_count(cnt, hpk[d], mi, d);
+          if constexpr (STATS) nnz_count<MI>(cnt, hpk[d], mi, d);
         }
         if (e.Hdbg) {
           __bf16* row = e.Hdbg + t * e.F + m_lane + 16 * mi;
@@ -274,22 +322,22 @@ struct EpiPrune24T {
         }
       }
       size_t piece = a24_piece((int)t, m_lane >> 6, e.F >> 6);
-      __bf16* hrow = e.Hc + piece * 32;
+      __bf16* hrow = e.Hc + piece * 32 + ((m_lane & 63) >> 1);
 #pragma unroll
-      for (int q = 0; q < 4; q++)
+      for (int q = 0; q < MI; q++)
         *reinterpret_cast<u32x4*>(hrow + 8 * q) = u32x4{vals[4 * q], vals[4 * q + 1], vals[4 * q + 2], vals[4 * q + 3]};
-      *reinterpret_cast<u32x2*>(e.meta + piece * 8) = u32x2{nib[0], nib[1]};
+      st_nibbles<MI>(e.meta + piece * 8 + ((m_lane & 63) >> 3), nib);
     }
     if constexpr (STATS) {
       if (e.tele) {
         // the lane's own non-zero count is the sum of its fields (at most 4 each); with the kept count, over the wave
         uint32_t tot = 0u;
 #pragma unroll
-        for (int i = 0; i < 16; i++) tot += (cnt[i] & 0xFFu) + ((cnt[i] >> 8) & 0xFFu) + ((cnt[i] >> 16) & 0xFFu) + (cnt[i] >> 24);
+        for (int i = 0; i < 4 * MI; i++) tot += (cnt[i] & 0xFFu) + ((cnt[i] >> 8) & 0xFFu) + ((cnt[i] >> 16) & 0xFFu) + (cnt[i] >> 24);
         tele_add2(e.tele, tot | (kept << 16), TELE_NONZERO, TELE_KEPT_TOK, blockIdx.x + (threadIdx.x >> 6));
       }
     }
-    if constexpr (STATS) if (e.nnz) nnz_flush(cnt, e.nnz, m_lane);
+    if constexpr (STATS) if (e.nnz) nnz_flush<MI>(cnt, e.nnz, m_lane);
   }
 };
 using EpiPrune24 = EpiPrune24T<false>;   // without the statistic (a compile-time switch: the plain kernel carries no trace of it)
@@ -298,17 +346,18 @@ using EpiPrune24 = EpiPrune24T<false>;   // without the statistic (a compile-tim
 // GEMMs work on a permutation of the hidden features and write each row back to its feature).
 struct EpiRowMajorMapped {
   struct Args { __bf16* C; int ldc; const int* rowmap; };
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[4][4], int m_lane, int n_lane) {
-    LaneIdx64 rows;
+  template <int MI, int NI>
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+    LaneIdx<MI> rows;
     rows.load(e.rowmap, m_lane);
 #pragma unroll
-    for (int mi = 0; mi < 4; mi++)
+    for (int mi = 0; mi < MI; mi++)
 #pragma unroll
       for (int v = 0; v < 16; v++) {
-        u32x2 o;
-        o[0] = pack_bf16x2(acc[mi][0][v], acc[mi][1][v]);
-        o[1] = pack_bf16x2(acc[mi][2][v], acc[mi][3][v]);
-        *reinterpret_cast<u32x2*>(e.C + (size_t)rows.at(16 * mi + v) * e.ldc + n_lane) = o;
+        float o[NI];
+#pragma unroll
+        for (int ni = 0; ni < NI; ni++) o[ni] = acc[mi][ni][v];
+        st_cols<NI>(e.C + (size_t)rows.at(16 * mi + v) * e.ldc + n_lane, o);
       }
   }
 };
@@ -319,13 +368,14 @@ struct EpiRowMajorMapped {
 // H, dZ and dZt are all in dense panel form.
 struct EpiDRelu {
   struct Args { const __bf16* H; __bf16* dZ; __bf16* dZt; int F; int T; };
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[4][4], int m_lane, int n_lane) {
-    LaneSavedDense sv;
+  template <int MI, int NI>
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+    LaneSavedDense<MI, NI> sv;
     sv.load(e.H, e.F, m_lane, n_lane);
 #pragma unroll
-    for (int mi = 0; mi < 4; mi++) {
+    for (int mi = 0; mi < MI; mi++) {
 #pragma unroll
-      for (int ni = 0; ni < 4; ni++) {
+      for (int ni = 0; ni < NI; ni++) {
         int f = m_lane + 16 * mi;
         size_t o = a24_piece(n_lane + ni, f >> 5, e.F >> 5) * 32 + (f & 31);
 #pragma unroll
@@ -346,10 +396,10 @@ struct EpiDRelu {
       if (e.dZt) {
 #pragma unroll
         for (int v = 0; v < 16; v++) {
-          u32x2 o;
-          o[0] = pack_bf16x2(acc[mi][0][v], acc[mi][1][v]);
-          o[1] = pack_bf16x2(acc[mi][2][v], acc[mi][3][v]);
-          *reinterpret_cast<u32x2*>(e.dZt + a24_piece(m_lane + 16 * mi + v, n_lane >> 5, e.T >> 5) * 32 + (n_lane & 31)) = o;
+          float o[NI];
+#pragma unroll
+          for (int ni = 0; ni < NI; ni++) o[ni] = acc[mi][ni][v];
+          st_cols<NI>(e.dZt + a24_piece(m_lane + 16 * mi + v, n_lane >> 5, e.T >> 5) * 32 + (n_lane & 31), o);
         }
       }
     }
@@ -361,17 +411,18 @@ struct EpiDRelu {
 // the forward's metadata: dZc [T][F/2].  Hc, meta and dZc are in panel form: one piece per lane and token.
 struct EpiDGather {
   struct Args { const __bf16* Hc; const uint8_t* meta; __bf16* dZc; int F; };
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[4][4], int m_lane, int n_lane) {
-    LaneSaved24 sv;
+  template <int MI, int NI>
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+    LaneSaved24<MI, NI> sv;
     sv.load(e.Hc, e.meta, e.F, m_lane, n_lane);
 #pragma unroll
-    for (int ni = 0; ni < 4; ni++) {
+    for (int ni = 0; ni < NI; ni++) {
       size_t t = (size_t)(n_lane + ni);
       size_t piece = a24_piece((int)t, m_lane >> 6, e.F >> 6);
       const u32x2 mt = sv.mt[ni];
-      __bf16* zrow = e.dZc + piece * 32;
+      __bf16* zrow = e.dZc + piece * 32 + ((m_lane & 63) >> 1);
 #pragma unroll
-      for (int mi = 0; mi < 4; mi++) {
+      for (int mi = 0; mi < MI; mi++) {
         const u32x4 h = sv.h[ni][mi];
         u32x4 z;
 #pragma unroll
@@ -414,17 +465,18 @@ __device__ __forceinline__ uint32_t cvt_e4m3x2(float lo, float hi, uint32_t old,
 //   significant bits, too few for 2 sqrt(h)).
 struct EpiPrune24F8 {
   struct Args { uint8_t* Hc8; uint8_t* meta; __bf16* Hdbg; const float* b1; int F; float zscale; float sh; __bf16* Hc16; uint8_t* meta16; };
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[4][4], int m_lane, int n_lane) {
-    LaneVec64 lb;
+  template <int MI, int NI>
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+    LaneVec<MI> lb;
     lb.load(e.b1, m_lane, 0.f);
 #pragma unroll
-    for (int ni = 0; ni < 4; ni++) {
+    for (int ni = 0; ni < NI; ni++) {
       size_t t = (size_t)(n_lane + ni);
-      uint32_t q8[8];
+      uint32_t q8[2 * MI];
       uint32_t nib[2] = {0u, 0u};
       size_t piece16 = a24_piece((int)t, m_lane >> 6, e.F >> 6);
 #pragma unroll
-      for (int mi = 0; mi < 4; mi++) {
+      for (int mi = 0; mi < MI; mi++) {
         uint32_t hpk[8];
 #pragma unroll
         for (int d = 0; d < 8; d++) {
@@ -447,19 +499,16 @@ struct EpiPrune24F8 {
           int gi = 4 * mi + a;
           float v0 = bf16_lo_to_f32(pair) / e.sh;
           float v1 = bf16_hi_to_f32(pair) / e.sh;
-          // group gi's two stored bytes are bytes 2 gi, 2 gi + 1 of the lane's 32
+          // group gi's two stored bytes are bytes 2 gi, 2 gi + 1 of the lane's 8 MI
           q8[gi >> 1] = cvt_e4m3x2(v0, v1, (gi & 1) ? q8[gi >> 1] : 0u, (gi & 1) != 0);
           nib[gi >> 3] |= n4 << (4 * (gi & 7));
         }
-        if (e.Hc16) *reinterpret_cast<u32x4*>(e.Hc16 + piece16 * 32 + 8 * mi) = u32x4{pairs[0], pairs[1], pairs[2], pairs[3]};
+        if (e.Hc16) *reinterpret_cast<u32x4*>(e.Hc16 + piece16 * 32 + ((m_lane & 63) >> 1) + 8 * mi) = u32x4{pairs[0], pairs[1], pairs[2], pairs[3]};
       }
       size_t piece = a24_piece((int)t, m_lane >> 7, e.F >> 7);
-      int half = (m_lane >> 6) & 1;
-      uint8_t* hrow = e.Hc8 + piece * 64 + 32 * half;
-      *reinterpret_cast<u32x4*>(hrow) = u32x4{q8[0], q8[1], q8[2], q8[3]};
-      *reinterpret_cast<u32x4*>(hrow + 16) = u32x4{q8[4], q8[5], q8[6], q8[7]};
-      *reinterpret_cast<u32x2*>(e.meta + piece * 16 + 8 * half) = u32x2{nib[0], nib[1]};
-      if (e.Hc16) *reinterpret_cast<u32x2*>(e.meta16 + piece16 * 8) = u32x2{nib[0], nib[1]};
+      st_codes<MI>(e.Hc8 + piece * 64 + ((m_lane & 127) >> 1), q8);
+      st_nibbles<MI>(e.meta + piece * 16 + ((m_lane & 127) >> 3), nib);
+      if (e.Hc16) st_nibbles<MI>(e.meta16 + piece16 * 8 + ((m_lane & 63) >> 3), nib);
     }
   }
 };
@@ -471,16 +520,17 @@ struct EpiPrune24F8 {
 // the fp8 panel form (the operand of the sparse dX GEMM).
 struct EpiDGatherF8 {
   struct Args { const __bf16* Hc16; const uint8_t* meta16; uint8_t* dZc8; int F; float scale; float sdz; };
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[4][4], int m_lane, int n_lane) {
-    LaneSaved24 sv;
+  template <int MI, int NI>
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+    LaneSaved24<MI, NI> sv;
     sv.load(e.Hc16, e.meta16, e.F, m_lane, n_lane);
 #pragma unroll
-    for (int ni = 0; ni < 4; ni++) {
+    for (int ni = 0; ni < NI; ni++) {
       size_t t = (size_t)(n_lane + ni);
       const u32x2 mt = sv.mt[ni];
-      uint32_t q8[8];
+      uint32_t q8[2 * MI];
 #pragma unroll
-      for (int mi = 0; mi < 4; mi++) {
+      for (int mi = 0; mi < MI; mi++) {
         const u32x4 h = sv.h[ni][mi];
 #pragma unroll
         for (int a = 0; a < 4; a++) {
@@ -497,9 +547,7 @@ struct EpiDGatherF8 {
         }
       }
       size_t piece = a24_piece((int)t, m_lane >> 7, e.F >> 7);
-      uint8_t* zrow = e.dZc8 + piece * 64 + 32 * ((m_lane >> 6) & 1);
-      *reinterpret_cast<u32x4*>(zrow) = u32x4{q8[0], q8[1], q8[2], q8[3]};
-      *reinterpret_cast<u32x4*>(zrow + 16) = u32x4{q8[4], q8[5], q8[6], q8[7]};
+      st_codes<MI>(e.dZc8 + piece * 64 + ((m_lane & 127) >> 1), q8);
     }
   }
 };
@@ -508,20 +556,21 @@ struct EpiDGatherF8 {
 struct EpiColMajorScaled {
   static constexpr bool STAGED = true;
   struct Args { __bf16* C; int ldc; float scale; };
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[4][4], int m_lane, int n_lane, char* wbuf) {
+  template <int MI, int NI>
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane, char* wbuf) {
     const int lane = threadIdx.x & 63, rho = lane & 31, h = lane >> 5;
 #pragma unroll
-    for (int ni = 0; ni < 4; ni++)
+    for (int ni = 0; ni < NI; ni++)
 #pragma unroll
-      for (int mi = 0; mi < 4; mi++)
+      for (int mi = 0; mi < MI; mi++)
 #pragma unroll
         for (int q = 0; q < 2; q++) {
           u32x4 o;
 #pragma unroll
           for (int d = 0; d < 4; d++) o[d] = pack_bf16x2(acc[mi][ni][8 * q + 2 * d] * e.scale, acc[mi][ni][8 * q + 2 * d + 1] * e.scale);
-          ColMajorStage::put(wbuf, rho, ni, 8 * h + 2 * mi + q, o);
+          ColMajorStage<MI, NI>::put(wbuf, rho, ni, 2 * MI * h + 2 * mi + q, o);
         }
-    ColMajorStage::flush(wbuf, e.C + (size_t)(n_lane - 4 * rho) * e.ldc + (m_lane - 64 * h), e.ldc);
+    ColMajorStage<MI, NI>::flush(wbuf, e.C + (size_t)(n_lane - NI * rho) * e.ldc + (m_lane - 16 * MI * h), e.ldc);
   }
 };
 
@@ -536,22 +585,23 @@ struct EpiColMajorScaled {
 template <bool STATS>
 struct EpiPrune24RwT {
   struct Args { __bf16* Hc; uint8_t* meta; __bf16* Hdbg; const float* b1; int F; const float* sx; const float* sw1; uint32_t* rowmax; uint32_t* nnz; };
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[4][4], int m_lane, int n_lane) {
-    uint32_t cnt[16];
+  template <int MI, int NI>
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+    uint32_t cnt[4 * MI];
 #pragma unroll
-    for (int i = 0; i < 16; i++) cnt[i] = 0u;
-    LaneVec64 lb, lw;
+    for (int i = 0; i < 4 * MI; i++) cnt[i] = 0u;
+    LaneVec<MI> lb, lw;
     lb.load(e.b1, m_lane, 0.f);
     lw.load(e.sw1, m_lane, 1.f);
 #pragma unroll
-    for (int ni = 0; ni < 4; ni++) {
+    for (int ni = 0; ni < NI; ni++) {
       size_t t = (size_t)(n_lane + ni);
       const float sxt = e.sx[t];
-      uint32_t vals[16];
+      uint32_t vals[4 * MI];
       uint32_t nib[2] = {0u, 0u};
       uint32_t mx = 0u;
 #pragma unroll
-      for (int mi = 0; mi < 4; mi++) {
+      for (int mi = 0; mi < MI; mi++) {
         uint32_t hpk[8];
 #pragma unroll
         for (int d = 0; d < 8; d++) {
@@ -560,7 +610,7 @@ struct EpiPrune24RwT {
           float r1 = fmaxf(acc[mi][ni][2 * d + 1] * (sxt * lw.at(16 * mi + 2 * d + 1)) + b1v, 0.f);
           hpk[d] = pack_bf16x2(r0 * r0, r1 * r1);
           mx = max(mx, max(hpk[d] & 0xFFFFu, hpk[d] >> 16));
-          if constexpr (STATS) nnz_count(cnt, hpk[d], mi, d);
+          if constexpr (STATS) nnz_count<MI>(cnt, hpk[d], mi, d);
         }
         if (e.Hdbg) {
           __bf16* row = e.Hdbg + t * e.F + m_lane + 16 * mi;
@@ -577,14 +627,14 @@ struct EpiPrune24RwT {
         }
       }
       size_t piece = a24_piece((int)t, m_lane >> 6, e.F >> 6);
-      __bf16* hrow = e.Hc + piece * 32;
+      __bf16* hrow = e.Hc + piece * 32 + ((m_lane & 63) >> 1);
 #pragma unroll
-      for (int q = 0; q < 4; q++)
+      for (int q = 0; q < MI; q++)
         *reinterpret_cast<u32x4*>(hrow + 8 * q) = u32x4{vals[4 * q], vals[4 * q + 1], vals[4 * q + 2], vals[4 * q + 3]};
-      *reinterpret_cast<u32x2*>(e.meta + piece * 8) = u32x2{nib[0], nib[1]};
+      st_nibbles<MI>(e.meta + piece * 8 + ((m_lane & 63) >> 3), nib);
       if (mx) atomicMax(e.rowmax + t, mx);
     }
-    if constexpr (STATS) nnz_flush(cnt, e.nnz, m_lane);
+    if constexpr (STATS) nnz_flush<MI>(cnt, e.nnz, m_lane);
   }
 };
 using EpiPrune24Rw = EpiPrune24RwT<false>;
@@ -597,18 +647,19 @@ using EpiPrune24Rw = EpiPrune24RwT<false>;
 // backward quantises per hidden feature for its dW2 GEMM.
 struct EpiRelu2Rw {
   struct Args { __bf16* H16; const float* b1; int F; const float* sx; const float* sw1; uint32_t* rowmax; __bf16* Ht16; int T; };
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[4][4], int m_lane, int n_lane) {
-    LaneVec64 lb, lw;
+  template <int MI, int NI>
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+    LaneVec<MI> lb, lw;
     lb.load(e.b1, m_lane, 0.f);
     lw.load(e.sw1, m_lane, 1.f);
-    uint32_t mx[4] = {0u, 0u, 0u, 0u};
-    float sxt[4];
+    uint32_t mx[NI] = {};
+    float sxt[NI];
 #pragma unroll
-    for (int ni = 0; ni < 4; ni++) sxt[ni] = e.sx[n_lane + ni];
+    for (int ni = 0; ni < NI; ni++) sxt[ni] = e.sx[n_lane + ni];
 #pragma unroll
-    for (int mi = 0; mi < 4; mi++) {
+    for (int mi = 0; mi < MI; mi++) {
 #pragma unroll
-      for (int ni = 0; ni < 4; ni++) {
+      for (int ni = 0; ni < NI; ni++) {
         const int t = n_lane + ni;
         int f = m_lane + 16 * mi;
         __bf16* row = e.H16 + a24_piece(t, f >> 5, e.F >> 5) * 32 + (f & 31);
@@ -631,15 +682,15 @@ struct EpiRelu2Rw {
       if (e.Ht16) {
 #pragma unroll
         for (int v = 0; v < 16; v++) {
-          u32x2 o;
-          o[0] = pack_bf16x2(acc[mi][0][v], acc[mi][1][v]);
-          o[1] = pack_bf16x2(acc[mi][2][v], acc[mi][3][v]);
-          *reinterpret_cast<u32x2*>(e.Ht16 + a24_piece(m_lane + 16 * mi + v, n_lane >> 5, e.T >> 5) * 32 + (n_lane & 31)) = o;
+          float o[NI];
+#pragma unroll
+          for (int ni = 0; ni < NI; ni++) o[ni] = acc[mi][ni][v];
+          st_cols<NI>(e.Ht16 + a24_piece(m_lane + 16 * mi + v, n_lane >> 5, e.T >> 5) * 32 + (n_lane & 31), o);
         }
       }
     }
 #pragma unroll
-    for (int ni = 0; ni < 4; ni++) if (mx[ni]) atomicMax(e.rowmax + n_lane + ni, mx[ni]);
+    for (int ni = 0; ni < NI; ni++) if (mx[ni]) atomicMax(e.rowmax + n_lane + ni, mx[ni]);
   }
 };
 
@@ -649,19 +700,20 @@ struct EpiRelu2Rw {
 // streaming kernels then quantise per token and per hidden feature; rowmax[t] is raised to the largest magnitude word of the row.
 struct EpiDReluRw {
   struct Args { const __bf16* H16; __bf16* dZ16; __bf16* dZt16; int F; int T; const float* rs; const float* cs; uint32_t* rowmax; };
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[4][4], int m_lane, int n_lane) {
-    LaneVec64 lr;
+  template <int MI, int NI>
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+    LaneVec<MI> lr;
     lr.load(e.rs, m_lane, 1.f);
-    uint32_t mx[4] = {0u, 0u, 0u, 0u};
-    float cs[4];
+    uint32_t mx[NI] = {};
+    float cs[NI];
 #pragma unroll
-    for (int ni = 0; ni < 4; ni++) cs[ni] = e.cs[n_lane + ni];
-    LaneSavedDense sv;
+    for (int ni = 0; ni < NI; ni++) cs[ni] = e.cs[n_lane + ni];
+    LaneSavedDense<MI, NI> sv;
     sv.load(e.H16, e.F, m_lane, n_lane);
 #pragma unroll
-    for (int mi = 0; mi < 4; mi++) {
+    for (int mi = 0; mi < MI; mi++) {
 #pragma unroll
-      for (int ni = 0; ni < 4; ni++) {
+      for (int ni = 0; ni < NI; ni++) {
         int f = m_lane + 16 * mi;
         size_t o = a24_piece(n_lane + ni, f >> 5, e.F >> 5) * 32 + (f & 31);
 #pragma unroll
@@ -683,33 +735,36 @@ struct EpiDReluRw {
       }
 #pragma unroll
       for (int v = 0; v < 16; v++) {
-        u32x2 o;
-        o[0] = pack_bf16x2(acc[mi][0][v], acc[mi][1][v]);
-        o[1] = pack_bf16x2(acc[mi][2][v], acc[mi][3][v]);
-        *reinterpret_cast<u32x2*>(e.dZt16 + a24_piece(m_lane + 16 * mi + v, n_lane >> 5, e.T >> 5) * 32 + (n_lane & 31)) = o;
+        float o[NI];
+#pragma unroll
+        for (int ni = 0; ni < NI; ni++) o[ni] = acc[mi][ni][v];
+        st_cols<NI>(e.dZt16 + a24_piece(m_lane + 16 * mi + v, n_lane >> 5, e.T >> 5) * 32 + (n_lane & 31), o);
       }
     }
 #pragma unroll
-    for (int ni = 0; ni < 4; ni++) if (mx[ni]) atomicMax(e.rowmax + n_lane + ni, mx[ni]);
+    for (int ni = 0; ni < NI; ni++) if (mx[ni]) atomicMax(e.rowmax + n_lane + ni, mx[ni]);
   }
 };
 
 // C[m][n] = bf16(acc * rs[m] * cs[n]), n contiguous (row-wise-scaled fp8 down-projection: rs = sh per token, cs = sw2).
 struct EpiRowMajorRowCol {
   struct Args { __bf16* C; int ldc; const float* rs; const float* cs; };
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[4][4], int m_lane, int n_lane) {
-    const f32x4 cs = *reinterpret_cast<const f32x4*>(e.cs + n_lane);
-    LaneVec64 lr;                                  // the lane's 64 row scales: 16 loads of 16 bytes, not 64 of 4
+  template <int MI, int NI>
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+    float cs[NI];
+#pragma unroll
+    for (int ni = 0; ni < NI; ni++) cs[ni] = e.cs[n_lane + ni];
+    LaneVec<MI> lr;                                  // the lane's 64 row scales: 16 loads of 16 bytes, not 64 of 4
     lr.load(e.rs, m_lane, 1.f);
 #pragma unroll
-    for (int mi = 0; mi < 4; mi++)
+    for (int mi = 0; mi < MI; mi++)
 #pragma unroll
       for (int v = 0; v < 16; v++) {
         const float r = lr.at(16 * mi + v);
-        u32x2 o;
-        o[0] = pack_bf16x2(acc[mi][0][v] * r * cs[0], acc[mi][1][v] * r * cs[1]);
-        o[1] = pack_bf16x2(acc[mi][2][v] * r * cs[2], acc[mi][3][v] * r * cs[3]);
-        *reinterpret_cast<u32x2*>(e.C + (size_t)(m_lane + 16 * mi + v) * e.ldc + n_lane) = o;
+        float o[NI];
+#pragma unroll
+        for (int ni = 0; ni < NI; ni++) o[ni] = acc[mi][ni][v] * r * cs[ni];
+        st_cols<NI>(e.C + (size_t)(m_lane + 16 * mi + v) * e.ldc + n_lane, o);
       }
   }
 };
@@ -718,21 +773,24 @@ struct EpiRowMajorRowCol {
 // of the permuted feature space, rs their scales in that order; each row goes back to its feature).
 struct EpiRowMajorRowColMapped {
   struct Args { __bf16* C; int ldc; const float* rs; const float* cs; const int* rowmap; };
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[4][4], int m_lane, int n_lane) {
-    const f32x4 cs = *reinterpret_cast<const f32x4*>(e.cs + n_lane);
-    LaneVec64 lr;
+  template <int MI, int NI>
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+    float cs[NI];
+#pragma unroll
+    for (int ni = 0; ni < NI; ni++) cs[ni] = e.cs[n_lane + ni];
+    LaneVec<MI> lr;
     lr.load(e.rs, m_lane, 1.f);
-    LaneIdx64 rows;
+    LaneIdx<MI> rows;
     rows.load(e.rowmap, m_lane);
 #pragma unroll
-    for (int mi = 0; mi < 4; mi++)
+    for (int mi = 0; mi < MI; mi++)
 #pragma unroll
       for (int v = 0; v < 16; v++) {
         const float r = lr.at(16 * mi + v);
-        u32x2 o;
-        o[0] = pack_bf16x2(acc[mi][0][v] * r * cs[0], acc[mi][1][v] * r * cs[1]);
-        o[1] = pack_bf16x2(acc[mi][2][v] * r * cs[2], acc[mi][3][v] * r * cs[3]);
-        *reinterpret_cast<u32x2*>(e.C + (size_t)rows.at(16 * mi + v) * e.ldc + n_lane) = o;
+        float o[NI];
+#pragma unroll
+        for (int ni = 0; ni < NI; ni++) o[ni] = acc[mi][ni][v] * r * cs[ni];
+        st_cols<NI>(e.C + (size_t)rows.at(16 * mi + v) * e.ldc + n_lane, o);
       }
   }
 };
@@ -742,15 +800,16 @@ struct EpiRowMajorRowColMapped {
 struct EpiColMajorRowCol {
   static constexpr bool STAGED = true;
   struct Args { __bf16* C; int ldc; const float* rs; const float* cs; };
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[4][4], int m_lane, int n_lane, char* wbuf) {
+  template <int MI, int NI>
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane, char* wbuf) {
     const int lane = threadIdx.x & 63, rho = lane & 31, h = lane >> 5;
-    LaneVec64 lr;
+    LaneVec<MI> lr;
     lr.load(e.rs, m_lane, 1.f);
 #pragma unroll
-    for (int ni = 0; ni < 4; ni++) {
+    for (int ni = 0; ni < NI; ni++) {
       const float cs = e.cs[n_lane + ni];
 #pragma unroll
-      for (int mi = 0; mi < 4; mi++)
+      for (int mi = 0; mi < MI; mi++)
 #pragma unroll
         for (int q = 0; q < 2; q++) {
           u32x4 o;
@@ -759,10 +818,10 @@ struct EpiColMajorRowCol {
             int i = 16 * mi + 8 * q + 2 * d;
             o[d] = pack_bf16x2(acc[mi][ni][8 * q + 2 * d] * lr.at(i) * cs, acc[mi][ni][8 * q + 2 * d + 1] * lr.at(i + 1) * cs);
           }
-          ColMajorStage::put(wbuf, rho, ni, 8 * h + 2 * mi + q, o);
+          ColMajorStage<MI, NI>::put(wbuf, rho, ni, 2 * MI * h + 2 * mi + q, o);
         }
     }
-    ColMajorStage::flush(wbuf, e.C + (size_t)(n_lane - 4 * rho) * e.ldc + (m_lane - 64 * h), e.ldc);
+    ColMajorStage<MI, NI>::flush(wbuf, e.C + (size_t)(n_lane - NI * rho) * e.ldc + (m_lane - 16 * MI * h), e.ldc);
   }
 };
 
@@ -775,24 +834,25 @@ struct EpiColMajorRowCol {
 // rowmax[t] to the largest magnitude word of its part of the row; a streaming kernel then quantises with rowmax[t] / 448.
 struct EpiDGatherRw {
   struct Args { const __bf16* Hc16; const uint8_t* meta16; __bf16* dZc16; int F; const float* rs; const float* cs; uint32_t* rowmax; };
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[4][4], int m_lane, int n_lane) {
-    LaneVec64 lr;
+  template <int MI, int NI>
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+    LaneVec<MI> lr;
     lr.load(e.rs, m_lane, 1.f);
-    LaneSaved24 sv;
+    LaneSaved24<MI, NI> sv;
     sv.load(e.Hc16, e.meta16, e.F, m_lane, n_lane);
-    float csv[4];
+    float csv[NI];
 #pragma unroll
-    for (int ni = 0; ni < 4; ni++) csv[ni] = e.cs[n_lane + ni];
+    for (int ni = 0; ni < NI; ni++) csv[ni] = e.cs[n_lane + ni];
 #pragma unroll
-    for (int ni = 0; ni < 4; ni++) {
+    for (int ni = 0; ni < NI; ni++) {
       size_t t = (size_t)(n_lane + ni);
       const float cs = csv[ni];
       size_t piece = a24_piece((int)t, m_lane >> 6, e.F >> 6);
       const u32x2 mt = sv.mt[ni];
-      __bf16* zrow = e.dZc16 + piece * 32;
+      __bf16* zrow = e.dZc16 + piece * 32 + ((m_lane & 63) >> 1);
       uint32_t mx = 0u;
 #pragma unroll
-      for (int mi = 0; mi < 4; mi++) {
+      for (int mi = 0; mi < MI; mi++) {
         const u32x4 h = sv.h[ni][mi];
         u32x4 z;
 #pragma unroll
@@ -823,15 +883,16 @@ struct EpiDGatherRw {
 // reduces over tokens (dense fp8 panel form).
 struct EpiRelu2F8 {
   struct Args { uint8_t* H8; const float* b1; int F; float zscale; float sh; __bf16* H16; uint8_t* H8t; int T; };
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[4][4], int m_lane, int n_lane) {
-    LaneVec64 lb;
+  template <int MI, int NI>
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+    LaneVec<MI> lb;
     lb.load(e.b1, m_lane, 0.f);
-    uint32_t qs[4][16];   // the lane's codes: [token][4 features per word]
+    uint32_t qs[NI][4 * MI];   // the lane's codes: [token][4 features per word]
 #pragma unroll
-    for (int ni = 0; ni < 4; ni++) {
-      uint8_t* row = e.H8 + a24_piece(n_lane + ni, m_lane >> 6, e.F >> 6) * 64;   // a lane's 64 features: one piece
+    for (int ni = 0; ni < NI; ni++) {
+      uint8_t* row = e.H8 + a24_piece(n_lane + ni, m_lane >> 6, e.F >> 6) * 64 + (m_lane & 63);
 #pragma unroll
-      for (int mi = 0; mi < 4; mi++) {
+      for (int mi = 0; mi < MI; mi++) {
         uint32_t q[4], hp[8];
 #pragma unroll
         for (int d = 0; d < 8; d++) {
@@ -853,14 +914,15 @@ struct EpiRelu2F8 {
       }
     }
     if (e.H8t) {
-      // feature m_lane + 4 w + b: its codes of the lane's 4 consecutive tokens -> one 4-byte store
+      // feature m_lane + 4 w + b: its codes of the lane's NI consecutive tokens -> one store
 #pragma unroll
-      for (int w = 0; w < 16; w++)
+      for (int w = 0; w < 4 * MI; w++)
 #pragma unroll
         for (int b = 0; b < 4; b++) {
-          uint32_t o = ((qs[0][w] >> (8 * b)) & 0xFFu) | (((qs[1][w] >> (8 * b)) & 0xFFu) << 8) | (((qs[2][w] >> (8 * b)) & 0xFFu) << 16) |
-                       (((qs[3][w] >> (8 * b)) & 0xFFu) << 24);
-          *reinterpret_cast<uint32_t*>(e.H8t + a24_piece(m_lane + 4 * w + b, n_lane >> 6, e.T >> 6) * 64 + (n_lane & 63)) = o;
+          uint32_t t[NI];
+#pragma unroll
+          for (int ni = 0; ni < NI; ni++) t[ni] = qs[ni][w];
+          st_bytes<NI>(e.H8t + a24_piece(m_lane + 4 * w + b, n_lane >> 6, e.T >> 6) * 64 + (n_lane & 63), t, b);
         }
     }
   }
@@ -871,15 +933,16 @@ struct EpiRelu2F8 {
 // operand of the dX GEMM and the [F][T] operand of the dW1 GEMM (dense fp8 panel forms).
 struct EpiDReluF8 {
   struct Args { const __bf16* H16; uint8_t* dZ8; uint8_t* dZ8t; int F; int T; float scale; float sdz; };
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[4][4], int m_lane, int n_lane) {
-    uint32_t qs[4][16];
-    LaneSavedDense sv;
+  template <int MI, int NI>
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+    uint32_t qs[NI][4 * MI];
+    LaneSavedDense<MI, NI> sv;
     sv.load(e.H16, e.F, m_lane, n_lane);
 #pragma unroll
-    for (int ni = 0; ni < 4; ni++) {
-      uint8_t* row = e.dZ8 + a24_piece(n_lane + ni, m_lane >> 6, e.F >> 6) * 64;
+    for (int ni = 0; ni < NI; ni++) {
+      uint8_t* row = e.dZ8 + a24_piece(n_lane + ni, m_lane >> 6, e.F >> 6) * 64 + (m_lane & 63);
 #pragma unroll
-      for (int mi = 0; mi < 4; mi++) {
+      for (int mi = 0; mi < MI; mi++) {
         uint32_t q[4];
 #pragma unroll
         for (int hq = 0; hq < 2; hq++) {
@@ -899,12 +962,13 @@ struct EpiDReluF8 {
       }
     }
 #pragma unroll
-    for (int w = 0; w < 16; w++)
+    for (int w = 0; w < 4 * MI; w++)
 #pragma unroll
       for (int b = 0; b < 4; b++) {
-        uint32_t o = ((qs[0][w] >> (8 * b)) & 0xFFu) | (((qs[1][w] >> (8 * b)) & 0xFFu) << 8) | (((qs[2][w] >> (8 * b)) & 0xFFu) << 16) |
-                     (((qs[3][w] >> (8 * b)) & 0xFFu) << 24);
-        *reinterpret_cast<uint32_t*>(e.dZ8t + a24_piece(m_lane + 4 * w + b, n_lane >> 6, e.T >> 6) * 64 + (n_lane & 63)) = o;
+        uint32_t t[NI];
+#pragma unroll
+        for (int ni = 0; ni < NI; ni++) t[ni] = qs[ni][w];
+        st_bytes<NI>(e.dZ8t + a24_piece(m_lane + 4 * w + b, n_lane >> 6, e.T >> 6) * 64 + (n_lane & 63), t, b);
       }
   }
 };
@@ -912,15 +976,16 @@ struct EpiDReluF8 {
 // C[m][n] = bf16(scale * acc), n contiguous (fp8 down-projection: scale = sh * sw2).
 struct EpiRowMajorScaled {
   struct Args { __bf16* C; int ldc; float scale; };
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[4][4], int m_lane, int n_lane) {
+  template <int MI, int NI>
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
 #pragma unroll
-    for (int mi = 0; mi < 4; mi++)
+    for (int mi = 0; mi < MI; mi++)
 #pragma unroll
       for (int v = 0; v < 16; v++) {
-        u32x2 o;
-        o[0] = pack_bf16x2(acc[mi][0][v] * e.scale, acc[mi][1][v] * e.scale);
-        o[1] = pack_bf16x2(acc[mi][2][v] * e.scale, acc[mi][3][v] * e.scale);
-        *reinterpret_cast<u32x2*>(e.C + (size_t)(m_lane + 16 * mi + v) * e.ldc + n_lane) = o;
+        float o[NI];
+#pragma unroll
+        for (int ni = 0; ni < NI; ni++) o[ni] = acc[mi][ni][v] * e.scale;
+        st_cols<NI>(e.C + (size_t)(m_lane + 16 * mi + v) * e.ldc + n_lane, o);
       }
   }
 };

@@ -1,9 +1,12 @@
 // MFMA / sparse-MFMA GEMM core for gfx950 (CDNA4), bf16 operands, fp32 accumulation.
 //
 // One kernel template computes C[m][n] = sum_k A[m][k] * B[n][k]; both operands are K-contiguous in memory
-// (operands that are not are transposed once by a streaming kernel, see k_stream.hip).  Block tile 256x256, four
-// wavefronts (2x2), each owning a 128x128 wave tile = 4x4 MFMA tiles of 32x32: 256 accumulator registers per lane,
-// pinned to the AGPR file.
+// (operands that are not are transposed once by a streaming kernel, see k_stream.hip).  Four wavefronts (2x2), each owning a
+// wave tile of MI x NI MFMA tiles of 32x32, so a block tile is 64 MI x 64 NI.  Block tile 256x256 (MI = NI = 4: 256 accumulator
+// registers per lane, pinned to the AGPR file) is the one that streams the fewest operand bytes per matrix op and carries the
+// large problems; 256x128, 128x128, 128x64 and 64x64 take the shapes whose 256x256 tiles would leave CUs idle (pick_tile in
+// launch_impl.hpp).  What follows describes the 256x256 tile; the smaller ones have the same LDS rows, swizzles and lane layouts.
+// An output element sums the same k in the same order in every tile, so the results are the same bit for bit.
 //
 //   A dense  : [M][K]                         -> v_mfma_f32_32x32x16_bf16
 //   A sparse : 2:4-compressed [M][K/2] + metadata [M][K/8] -> v_smfmac_f32_32x32x32_bf16
@@ -110,31 +113,47 @@ __host__ __device__ __forceinline__ size_t a24_piece(int r, int kp, int npanels)
   return ((size_t)(r >> 8) * npanels + kp) * 256 + (r & 255);
 }
 
+// Ring depth (stages) of each tile.  256 x 256 fills the LDS by itself.  The smaller tiles keep their ring under half of the LDS where three
+// stages fit, so that a second workgroup shares the CU and fills this one's barrier and epilogue gaps: a deeper ring with one workgroup
+// is 10-25 % slower once a CU has two tiles to do (sparse 128 x 128, T = 4096, D = 2048, F = 8192: 103 us against 113) and no faster
+// when it has one.  Sparse 256 x 128 has room for two stages a workgroup only, and those expose the memory latency (112 us; 81 us with
+// four stages and the CU to itself).
+constexpr int ring_depth(bool sparse, bool f8, int mi, int ni) {
+  return mi * ni == 16 ? (sparse ? 3 : 4) : mi * ni == 8 ? (sparse || f8 ? 4 : 3) : mi * ni == 4 ? (sparse ? 3 : 4) : mi * ni == 2 ? 4 : 6;
+}
+
 // Stage geometry.  Everything is laid out in bytes, and an fp8 kernel has exactly the byte geometry of its bf16
 // counterpart with twice the k per byte: the LDS tiles, swizzles, DMA plan and fragment addresses are shared.
-template <bool SPARSE, bool F8 = false>
+template <bool SPARSE, bool F8 = false, int MI = 4, int NI = 4>
 struct Geo {
+  static constexpr int BM = 64 * MI, BN = 64 * NI;        // block tile: 2 x 2 waves of 32 MI x 32 NI
   static constexpr int ESIZE = F8 ? 1 : 2;
   static constexpr int BK = (SPARSE ? 128 : 64) / ESIZE;  // dense k per stage (B rows of 128 / 64 bytes)
-  static constexpr int A_BYTES = 256 * 64;               // 64-byte rows: dense k, or the stored values of twice as many k
+  static constexpr int A_BYTES = BM * 64;                // 64-byte rows: dense k, or the stored values of twice as many k
   static constexpr int META_ROW = SPARSE ? (F8 ? 16 : 8) : 0;   // metadata bytes per row and stage (4 bits per group of 4 k)
-  static constexpr int META_BYTES = 256 * META_ROW;
+  static constexpr int META_BYTES = BM * META_ROW;
   static constexpr int B_ROW = SPARSE ? 128 : 64;
-  static constexpr int B_BYTES = 256 * B_ROW;
+  static constexpr int B_BYTES = BN * B_ROW;
   static constexpr int META_OFF = A_BYTES;
   static constexpr int B_OFF = A_BYTES + META_BYTES;
   static constexpr int STAGE = A_BYTES + META_BYTES + B_BYTES;
-  static constexpr int NB = SPARSE ? 3 : 4;              // ring depth
+  static constexpr int NB = ring_depth(SPARSE, F8, MI, NI);
   static constexpr int LDS_TOTAL = NB * STAGE;
-  static constexpr int NM = SPARSE ? (F8 ? 1 : 2) : 0;   // metadata DMA instructions per wave and stage
-  static constexpr int NDMA = SPARSE ? 4 + NM + 8 : 4 + 4;  // DMA instructions per wave and stage
+  static constexpr int PER_CU = LDS_TOTAL <= 80 * 1024 ? 2 : 1;   // workgroups a CU is meant to hold (bounds the registers)
+  // metadata DMA instructions per wave and stage (where a tile has less metadata than the four waves fetch, waves fetch the
+  // same bytes to the same place: every wave then has the same count of instructions in flight)
+  static constexpr int NM = SPARSE ? (F8 || MI < 4 ? 1 : 2) : 0;
+  static constexpr int NDMA = MI + NM + (SPARSE ? 2 * NI : NI);  // DMA instructions per wave and stage
 };
 
-// LDS row -> row of the 256-row block tile (inverse of the permutation described above)
+// LDS row -> row of the block tile (inverse of the permutation described above; in general wave-tile row 16 MI hc + 16 mi + v
+// belongs to lane half hc, M-tile mi, register v, and wave-tile column NI c + ni to lane column c, N-tile ni)
+template <int MI>
 __device__ __forceinline__ int unperm_m(int p) {
-  return (p & 128) | (((p >> 2) & 1) << 6) | (((p >> 5) & 3) << 4) | (((p >> 3) & 3) << 2) | (p & 3);
+  return (p & ~(32 * MI - 1)) | (((p >> 2) & 1) * (16 * MI)) | (((p >> 5) & (MI - 1)) << 4) | (((p >> 3) & 3) << 2) | (p & 3);
 }
-__device__ __forceinline__ int unperm_n(int p) { return (p & 128) | ((p & 31) << 2) | ((p >> 5) & 3); }
+template <int NI>
+__device__ __forceinline__ int unperm_n(int p) { return (p & ~(32 * NI - 1)) | ((p & 31) * NI) | ((p >> 5) & (NI - 1)); }
 // 16-byte chunk swizzles.  A 16-byte-per-lane LDS read of a wavefront is served 16 lanes per clock, and the lanes
 // that share a clock are not consecutive: {0-3, 20-23} and {4-7, 16-19} each pair up with {8-11, 28-31} or
 // {12-15, 24-27} (likewise +32); they must hit 16 different 16-byte slots of the 256-byte bank row (measured on
@@ -163,13 +182,14 @@ __device__ __forceinline__ void wait_lgkmcnt0() { __builtin_amdgcn_s_waitcnt(0xC
 // ------------------------------------------------------------------------------------------------
 // global -> LDS DMA plan of one wave
 // ------------------------------------------------------------------------------------------------
-template <bool SPARSE, bool F8 = false, int PROBE = 0>
+template <bool SPARSE, bool F8 = false, int PROBE = 0, int MI = 4, int NI = 4>
 struct Dma {
-  using G = Geo<SPARSE, F8>;
+  using G = Geo<SPARSE, F8, MI, NI>;
+  static constexpr int NVB = SPARSE ? 2 * NI : NI;
   const char* a;      // block's first A row (uniform)
   const char* am;     // metadata
   const char* b;
-  uint32_t va[4], vm[2], vb[SPARSE ? 8 : 4];   // per-lane byte offsets from the uniform bases
+  uint32_t va[MI], vm[2], vb[NVB];   // per-lane byte offsets from the uniform bases
   uint32_t a_stage, m_stage, b_stage;          // bytes from one stage to the next in the A values / metadata / B stream
   int wave;
 
@@ -178,43 +198,42 @@ struct Dma {
     wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t b_row = (uint32_t)g.K * G::ESIZE;                 // bytes per B row in memory
     const uint32_t a_row = SPARSE ? b_row / 2 : b_row;               // bytes per A row (stored values only if sparse)
-    a = static_cast<const char*>(g.A) + (size_t)m0 * a_row;
-    b = static_cast<const char*>(g.B) + (g.b_rowmap ? (size_t)0 : (size_t)n0 * b_row);
-    am = SPARSE ? reinterpret_cast<const char*>(g.Ameta) + (size_t)m0 * (g.K / 8) : nullptr;
-    // a block tile's 256 rows occupy the same byte range in both forms; only the order of the pieces inside differs
-    const bool panel = g.a_panel != 0;
+    // 256 rows occupy the same byte range in both forms; only the order of the pieces inside differs.  A tile of fewer rows
+    // starts m0 % 256 (n0 % 256) rows into such a block.
+    const bool panel = g.a_panel != 0, bp = g.b_panel != 0;
     const uint32_t a_pitch = panel ? 64u : a_row, m_pitch = panel ? (uint32_t)G::META_ROW : (uint32_t)(g.K / 8);
+    const int mb = m0 & ~255, ma = m0 & 255, nb = bp ? n0 & ~255 : n0, na = bp ? n0 & 255 : 0;
+    a = static_cast<const char*>(g.A) + (size_t)mb * a_row + (size_t)ma * a_pitch;
+    b = static_cast<const char*>(g.B) + (g.b_rowmap ? (size_t)0 : (size_t)nb * b_row);
+    am = SPARSE ? reinterpret_cast<const char*>(g.Ameta) + (size_t)mb * (g.K / 8) + (size_t)ma * m_pitch : nullptr;
     a_stage = panel ? 256u * 64u : 64u;
     m_stage = panel ? 256u * G::META_ROW : (uint32_t)G::META_ROW;
-    const bool bp = g.b_panel != 0;
     b_stage = bp ? 256u * (uint32_t)G::B_ROW : (uint32_t)G::B_ROW;
 #pragma unroll
-    for (int j = 0; j < 4; j++) {
-      int p = 64 * wave + 16 * j + (lane >> 2);
+    for (int j = 0; j < MI; j++) {
+      int p = 16 * (MI * wave + j) + (lane >> 2);
       int c = (lane & 3) ^ swz4(p);
-      va[j] = (uint32_t)unperm_m(p) * a_pitch + c * 16;
-      if constexpr (!SPARSE) {
-        if (bp) vb[j] = (uint32_t)p * 64u + c * 16;     // LDS row p is piece p of the block's 16 KiB run
-        else vb[j] = (g.b_rowmap ? (uint32_t)g.b_rowmap[n0 + unperm_n(p)] : (uint32_t)unperm_n(p)) * b_row + c * 16;
-      }
+      va[j] = (uint32_t)unperm_m<MI>(p) * a_pitch + c * 16;
+    }
+#pragma unroll
+    for (int j = 0; j < NVB; j++) {
+      // dense: 64-byte rows, 16 an instruction; sparse: 128-byte rows, 8 an instruction
+      int p = SPARSE ? 8 * (NVB * wave + j) + (lane >> 3) : 16 * (NVB * wave + j) + (lane >> 2);
+      int c = SPARSE ? (lane & 7) ^ swz8(p) : (lane & 3) ^ swz4(p);
+      // panel: with NI = 4 LDS row p is piece p of the block's run; a sparse row's 128 bytes are two 64-byte pieces in
+      // consecutive 16 KiB runs
+      if (bp) vb[j] = (uint32_t)(c >> 2) * (256u * 64u) + (uint32_t)(NI == 4 ? p : b_panel_pos(na + unperm_n<NI>(p))) * 64u + (c & 3) * 16;
+      else vb[j] = (g.b_rowmap ? (uint32_t)g.b_rowmap[n0 + unperm_n<NI>(p)] : (uint32_t)unperm_n<NI>(p)) * b_row + c * 16;
     }
     if constexpr (SPARSE) {
-#pragma unroll
-      for (int j = 0; j < 8; j++) {
-        int p = 64 * wave + 8 * j + (lane >> 3);
-        int c = (lane & 7) ^ swz8(p);
-        // panel: the row's 128 bytes are two 64-byte pieces in consecutive 16 KiB runs
-        if (bp) vb[j] = (uint32_t)(c >> 2) * (256u * 64u) + (uint32_t)p * 64u + (c & 3) * 16;
-        else vb[j] = (g.b_rowmap ? (uint32_t)g.b_rowmap[n0 + unperm_n(p)] : (uint32_t)unperm_n(p)) * b_row + c * 16;
-      }
+      vm[1] = 0;
       if constexpr (F8) {
-        vm[0] = (uint32_t)unperm_m(64 * wave + lane) * m_pitch;      // one row's 16 metadata bytes per lane
-        vm[1] = 0;
+        vm[0] = (uint32_t)unperm_m<MI>(64 * (wave % MI) + lane) * m_pitch;      // one row's 16 metadata bytes per lane
       } else {
 #pragma unroll
-        for (int j = 0; j < 2; j++) {
-          int d = 64 * (2 * wave + j) + lane;
-          vm[j] = (uint32_t)unperm_m(d >> 1) * m_pitch + 4 * (d & 1);
+        for (int j = 0; j < G::NM; j++) {
+          int d = 64 * ((G::NM * wave + j) % (2 * MI)) + lane;
+          vm[j] = (uint32_t)unperm_m<MI>(d >> 1) * m_pitch + 4 * (d & 1);
         }
       }
     }
@@ -228,20 +247,17 @@ struct Dma {
     // The stage's uniform base goes through an opaque scalar register pair, so that the compiler keeps it apart from the
     // lane's 32-bit offset and picks the instruction's scalar-base + 32-bit-offset form: no 64-bit vector add per
     // instruction, one address register per instruction instead of two.
-    if constexpr (J < 4) {
-      __builtin_amdgcn_global_load_lds((glb_char*)(sbase(a, kt, a_stage) + voff(va[J])), (lds_char*)(buf + (4 * wave + J) * 1024), 16, 0, 0);
-    } else if constexpr (!SPARSE) {
-      constexpr int j = J - 4;
-      __builtin_amdgcn_global_load_lds((glb_char*)(sbase(b, kt, b_stage) + voff(vb[j])), (lds_char*)(buf + G::B_OFF + (4 * wave + j) * 1024), 16, 0, 0);
-    } else if constexpr (J < 4 + G::NM) {
-      constexpr int j = J - 4;
+    if constexpr (J < MI) {
+      __builtin_amdgcn_global_load_lds((glb_char*)(sbase(a, kt, a_stage) + voff(va[J])), (lds_char*)(buf + (MI * wave + J) * 1024), 16, 0, 0);
+    } else if constexpr (J < MI + G::NM) {
+      constexpr int j = J - MI;
       if constexpr (F8)
-        __builtin_amdgcn_global_load_lds((glb_char*)(sbase(am, kt, m_stage) + voff(vm[0])), (lds_char*)(buf + G::META_OFF + wave * 1024), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds((glb_char*)(sbase(am, kt, m_stage) + voff(vm[0])), (lds_char*)(buf + G::META_OFF + (wave % MI) * 1024), 16, 0, 0);
       else
-        __builtin_amdgcn_global_load_lds((glb_char*)(sbase(am, kt, m_stage) + voff(vm[j])), (lds_char*)(buf + G::META_OFF + (2 * wave + j) * 256), 4, 0, 0);
+        __builtin_amdgcn_global_load_lds((glb_char*)(sbase(am, kt, m_stage) + voff(vm[j])), (lds_char*)(buf + G::META_OFF + ((G::NM * wave + j) % (2 * MI)) * 256), 4, 0, 0);
     } else {
-      constexpr int j = J - 4 - G::NM;
-      __builtin_amdgcn_global_load_lds((glb_char*)(sbase(b, kt, b_stage) + voff(vb[j])), (lds_char*)(buf + G::B_OFF + (8 * wave + j) * 1024), 16, 0, 0);
+      constexpr int j = J - MI - G::NM;
+      __builtin_amdgcn_global_load_lds((glb_char*)(sbase(b, kt, b_stage) + voff(vb[j])), (lds_char*)(buf + G::B_OFF + (NVB * wave + j) * 1024), 16, 0, 0);
     }
   }
   static __device__ __forceinline__ const char* sbase(const char* base, int kt, uint32_t stage) {
@@ -263,29 +279,28 @@ struct Dma {
 struct LaneCtx {
   int rho, h;       // lane & 31, lane >> 5
   int wy, wx;       // wave row / column inside the block tile
-  int a_row64;      // byte offset of LDS row (wy*128 + rho) with 64-byte rows
-  int b_row64;      // (wx*128 + rho) * 64
-  int b_row128;     // (wx*128 + rho) * 128
-  int sw4;          // swz4 of the lane's row (the same for all four 32-row tiles)
+  int a_row;        // LDS row of the lane in the wave's first 32 rows of A
+  int b_row;        // ... of B
+  int sw4;          // swz4 of the lane's row (the same for every 32-row tile)
   int sw8;          // swz8 of the lane's B row for even ni (odd ni: ^4)
 };
 
-// Dense: K step S (0,1) of the 32-wide stage; fragment I < 4 -> a[I], else b[I-4]
+// Dense: K step S (0,1) of the 64-byte stage rows; fragment I < MI -> a[I], else b[I-MI]
+template <int MI, int NI>
 struct FragD {
-  bf16x8 a[4], b[4];
+  bf16x8 a[MI], b[NI];
 };
-template <int S, int I, int PROBE = 0>
-__device__ __forceinline__ void load_frag_dense1(const char* buf, const LaneCtx& L, FragD& f) {
+template <class G, int S, int I, int PROBE, int MI, int NI>
+__device__ __forceinline__ void load_frag_dense1(const char* buf, const LaneCtx& L, FragD<MI, NI>& f) {
   if constexpr ((PROBE & PROBE_NO_FRAG) != 0) return;
-  constexpr int i = I & 3;
   int c = ((2 * S + L.h) ^ L.sw4) << 4;
-  if constexpr (I < 4) f.a[i] = *reinterpret_cast<const bf16x8*>(buf + L.a_row64 + i * (32 * 64) + c);
-  else f.b[i] = *reinterpret_cast<const bf16x8*>(buf + Geo<false>::B_OFF + L.b_row64 + i * (32 * 64) + c);
+  if constexpr (I < MI) f.a[I] = *reinterpret_cast<const bf16x8*>(buf + L.a_row * 64 + I * (32 * 64) + c);
+  else f.b[I - MI] = *reinterpret_cast<const bf16x8*>(buf + G::B_OFF + L.b_row * 64 + (I - MI) * (32 * 64) + c);
 }
-template <int M, int PROBE = 0>
-__device__ __forceinline__ void mfma_dense1(const FragD& f, f32x16 (&acc)[4][4]) {
+template <int M, int PROBE, int MI, int NI>
+__device__ __forceinline__ void mfma_dense1(const FragD<MI, NI>& f, f32x16 (&acc)[MI][NI]) {
   if constexpr ((PROBE & PROBE_NO_MFMA) != 0) return;
-  constexpr int mi = M >> 2, ni = M & 3;
+  constexpr int mi = M / NI, ni = M % NI;
   acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[mi], f.b[ni], acc[mi][ni], 0, 0, 0);
 }
 // fp8 e4m3, v_mfma_f32_32x32x64_f8f6f4: 32 operand bytes per lane, paired byte by byte between A and B (measured:
@@ -297,34 +312,42 @@ __device__ __forceinline__ i32x8 cat16(const bf16x8& lo, const bf16x8& hi) {
   i32x4 l = __builtin_bit_cast(i32x4, lo), h = __builtin_bit_cast(i32x4, hi);
   return __builtin_shufflevector(l, h, 0, 1, 2, 3, 4, 5, 6, 7);
 }
-template <int M, int PROBE = 0>
-__device__ __forceinline__ void mfma_dense_f8(const FragD& f0, const FragD& f1, f32x16 (&acc)[4][4]) {
+// The 256 x 256 tile's form is written as inline assembly with the accumulator tied in place: through the builtin the compiler gives this
+// instruction a destination different from its accumulator input, which with all 256 accumulation registers in
+// use spills accumulators to scratch memory on every op.  Default modifiers = both operands e4m3, unscaled.
+// No software wait states are needed there: consecutive ops use different accumulators, and the same one is only
+// touched again 16 ops later.
+__device__ __forceinline__ void mfma_f8_pinned(const i32x8& a, const i32x8& b, f32x16& c) {
+  asm volatile("v_mfma_f32_32x32x64_f8f6f4 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+}
+// The smaller tiles have registers to spare, and their accumulators come round again within a few ops: the builtin, whose
+// hazards the compiler handles (formats 0 = e4m3; scale operands 0 = the unscaled instruction).
+__device__ __forceinline__ void mfma_f8(const i32x8& a, const i32x8& b, f32x16& c) {
+  c = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, 0, 0, 0);
+}
+template <int M, int PROBE, int MI, int NI>
+__device__ __forceinline__ void mfma_dense_f8(const FragD<MI, NI>& f0, const FragD<MI, NI>& f1, f32x16 (&acc)[MI][NI]) {
   if constexpr ((PROBE & PROBE_NO_MFMA) != 0) return;
-  constexpr int mi = M >> 2, ni = M & 3;
-  // Written as inline assembly with the accumulator tied in place: through the builtin the compiler gives this
-  // instruction a destination different from its accumulator input, which with all 256 accumulation registers in
-  // use spills accumulators to scratch memory on every op.  Default modifiers = both operands e4m3, unscaled.
-  // No software wait states are needed here: consecutive ops use different accumulators, and the same one is only
-  // touched again 16 ops later.
-  asm volatile("v_mfma_f32_32x32x64_f8f6f4 %0, %1, %2, %0"
-               : "+a"(acc[mi][ni])
-               : "v"(cat16(f0.a[mi], f1.a[mi])), "v"(cat16(f0.b[ni], f1.b[ni])));
+  constexpr int mi = M / NI, ni = M % NI;
+  if constexpr (MI * NI == 16) mfma_f8_pinned(cat16(f0.a[mi], f1.a[mi]), cat16(f0.b[ni], f1.b[ni]), acc[mi][ni]);
+  else mfma_f8(cat16(f0.a[mi], f1.a[mi]), cat16(f0.b[ni], f1.b[ni]), acc[mi][ni]);
 }
 
 // Sparse: the stage's K window of 64 = four 16-wide windows w.  Instruction S (0,1) gives lane half q the window
 // 2q+S, so a lane's two instructions use 32 consecutive stored-value bytes and one 32-bit metadata word (ABID = S
 // picks the half).  B lane half h then needs, for instruction S, the 8-k chunks 2S+h (registers 0..7) and 4+2S+h
 // (registers 8..15).
+template <int MI, int NI>
 struct FragS {
-  bf16x8 a[4];
-  bf16x8 blo[4], bhi[4];
+  bf16x8 a[MI];
+  bf16x8 blo[NI], bhi[NI];
 };
 // Metadata of a lane for the stage's two instructions: bf16 one 32-bit word (16 bits per instruction, picked by
 // ABID); fp8 (twice the groups per stored byte) two words, one per instruction.
 template <bool F8> struct IdxWords { uint32_t w[F8 ? 2 : 1]; };
-template <bool F8, int I>
-__device__ __forceinline__ void load_idx_sparse1(const char* buf, const LaneCtx& L, IdxWords<F8> (&idx)[4]) {
-  const char* p = buf + Geo<true, F8>::META_OFF + (L.wy * 128 + L.rho + 32 * I) * Geo<true, F8>::META_ROW;
+template <class G, bool F8, int I, int MI>
+__device__ __forceinline__ void load_idx_sparse1(const char* buf, const LaneCtx& L, IdxWords<F8> (&idx)[MI]) {
+  const char* p = buf + G::META_OFF + (L.a_row + 32 * I) * G::META_ROW;
   if constexpr (F8) {
     u32x2 v = *reinterpret_cast<const u32x2*>(p + 8 * L.h);
     idx[I].w[0] = v[0]; idx[I].w[1] = v[1];
@@ -332,26 +355,26 @@ __device__ __forceinline__ void load_idx_sparse1(const char* buf, const LaneCtx&
     idx[I].w[0] = *reinterpret_cast<const uint32_t*>(p + 4 * L.h);
   }
 }
-// fragment I of instruction S: I < 4 -> a[I]; 4..7 -> low half of b[I-4]; 8..11 -> high half of b[I-8]
-template <bool F8, int S, int I, int PROBE = 0>
-__device__ __forceinline__ void load_frag_sparse1(const char* buf, const LaneCtx& L, FragS& f) {
+// fragment I of instruction S: I < MI -> a[I]; the next NI -> low halves of b; the last NI -> high halves of b
+template <class G, int S, int I, int PROBE, int MI, int NI>
+__device__ __forceinline__ void load_frag_sparse1(const char* buf, const LaneCtx& L, FragS<MI, NI>& f) {
   if constexpr ((PROBE & PROBE_NO_FRAG) != 0) return;
-  constexpr int i = I & 3;
-  if constexpr (I < 4) {
-    f.a[i] = *reinterpret_cast<const bf16x8*>(buf + L.a_row64 + i * (32 * 64) + (((2 * L.h + S) ^ L.sw4) << 4));
+  if constexpr (I < MI) {
+    f.a[I] = *reinterpret_cast<const bf16x8*>(buf + L.a_row * 64 + I * (32 * 64) + (((2 * L.h + S) ^ L.sw4) << 4));
   } else {
+    constexpr int i = (I - MI) % NI;
     int sw = L.sw8 ^ ((i & 1) << 2);
-    const char* row = buf + Geo<true, F8>::B_OFF + L.b_row128 + i * (32 * 128);
-    if constexpr (I < 8) f.blo[i] = *reinterpret_cast<const bf16x8*>(row + (((2 * S + L.h) ^ sw) << 4));
+    const char* row = buf + G::B_OFF + L.b_row * 128 + i * (32 * 128);
+    if constexpr (I < MI + NI) f.blo[i] = *reinterpret_cast<const bf16x8*>(row + (((2 * S + L.h) ^ sw) << 4));
     else f.bhi[i] = *reinterpret_cast<const bf16x8*>(row + (((4 + 2 * S + L.h) ^ sw) << 4));
   }
 }
 // fp8: v_smfmac_f32_32x32x64_fp8_fp8 has, byte for byte, the operand layout of the bf16 instruction (measured): A 16
 // stored bytes of the lane half's window, B the two 16-byte chunks, and a full 32-bit index word per instruction.
-template <bool F8, int S, int M, int PROBE = 0>
-__device__ __forceinline__ void mfma_sparse1(const FragS& f, const IdxWords<F8> (&idx)[4], f32x16 (&acc)[4][4]) {
+template <bool F8, int S, int M, int PROBE, int MI, int NI>
+__device__ __forceinline__ void mfma_sparse1(const FragS<MI, NI>& f, const IdxWords<F8> (&idx)[MI], f32x16 (&acc)[MI][NI]) {
   if constexpr ((PROBE & PROBE_NO_MFMA) != 0) return;
-  constexpr int mi = M >> 2, ni = M & 3;
+  constexpr int mi = M / NI, ni = M % NI;
   if constexpr (F8) {
     acc[mi][ni] = __builtin_amdgcn_smfmac_f32_32x32x64_fp8_fp8(__builtin_bit_cast(i32x4, f.a[mi]), cat16(f.blo[ni], f.bhi[ni]), acc[mi][ni],
                                                                (int)idx[mi].w[S], 0, 0);
@@ -403,13 +426,13 @@ __device__ __forceinline__ void tile_coords(int ntm, int ntn, int pid, int& tm, 
   tn = in / gsz;
 }
 
-// an epilogue that declares `static constexpr bool STAGED` takes a fifth argument: 32 KiB of LDS private to the wave
+// an epilogue that declares `static constexpr bool STAGED` takes a fifth argument: LDS private to the wave for its part of the result in bf16
 template <class E, class = void> struct epi_is_staged : std::false_type {};
 template <class E> struct epi_is_staged<E, std::void_t<decltype(E::STAGED)>> : std::true_type {};
 
-// Epilogue concept:  struct E { struct Args {...}; static __device__ void run(const Args&, acc, m_lane, n_lane); }
-//   m_lane = global row of acc[0][*][0] for this lane (its 64 rows are m_lane + 16*mi + v),
-//   n_lane = global column of acc[*][0][*] (its 4 columns are n_lane + ni).
+// Epilogue concept:  struct E { struct Args {...}; template <int MI, int NI> static __device__ void run(const Args&, acc, m_lane, n_lane); }
+//   m_lane = global row of acc[0][*][0] for this lane (its 16 MI rows are m_lane + 16*mi + v),
+//   n_lane = global column of acc[*][0][*] (its NI columns are n_lane + ni).
 // One block tile of one GEMM: tile number `pid` of g (workgroup-uniform), LDS ring at `smem`.
 // Pacing of the DMA issue.  The four waves run in step, one per SIMD, and share one address unit that takes about
 // 14 cycles per 16-byte-a-lane DMA instruction; a matrix-op slot is 32 cycles.  When every wave hands over a DMA
@@ -433,27 +456,37 @@ constexpr int dma_on_step0(int M) {
   return (M % 2 == 0 && M / 2 < NDMA - H1) ? H1 + M / 2 : -1;
 }
 
-template <bool SPARSE, class Epi, bool F8 = false, int PROBE = 0>
+// The smaller tiles (several workgroups a CU, whose issue gaps fill each other) spread N memory instructions over the slots of a K
+// step by whole runs: slot M carries instructions [M * per, M * per + per).
+template <int N, int SLOTS, int M, class F>
+__device__ __forceinline__ void ride(F&& f) {
+  constexpr int per = (N + SLOTS - 1) / SLOTS, lo = M * per < N ? M * per : N, hi = (M + 1) * per < N ? (M + 1) * per : N;
+  static_for<hi - lo>([&](auto i) { f(std::integral_constant<int, lo + decltype(i)::value>{}); });
+}
+
+template <bool SPARSE, class Epi, bool F8 = false, int PROBE = 0, int MI = 4, int NI = 4>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi::Args& ea, char* smem, int pid, int pid_end = 0, int pid_step = 0) {
-  using G = Geo<SPARSE, F8>;
+  using G = Geo<SPARSE, F8, MI, NI>;
+  constexpr bool BIG = MI * NI == 16;       // the 256 x 256 tile: accumulators pinned, memory instructions paced slot by slot
+  constexpr int NMF = MI * NI;              // matrix ops (slots) per K step
+  constexpr int FRAG_SLOTS = BIG ? 16 : (NMF + 1) / 2;   // slots of a K step that carry fragment reads (BIG: one a slot from the first on)
   constexpr int NB = G::NB, NDMA = G::NDMA - ((SPARSE && (PROBE & PROBE_FILL_LESS)) ? 3 : 0);
   constexpr bool PERSIST = (PROBE & PROBE_PERSIST) != 0;
 
   int tid = threadIdx.x;
   int lane = tid & 63, wave = tid >> 6;
   int tm, tn;
-  tile_coords<PROBE>(g.M / TILE_M, g.N / TILE_N, pid, tm, tn);
-  int m0 = tm * TILE_M, n0 = tn * TILE_N;
+  tile_coords<PROBE>(g.M / G::BM, g.N / G::BN, pid, tm, tn);
+  int m0 = tm * G::BM, n0 = tn * G::BN;
 
   LaneCtx L;
   L.rho = lane & 31; L.h = lane >> 5; L.wy = wave >> 1; L.wx = wave & 1;
-  L.a_row64 = (L.wy * 128 + L.rho) * 64;
-  L.b_row64 = (L.wx * 128 + L.rho) * 64;
-  L.b_row128 = (L.wx * 128 + L.rho) * 128;
+  L.a_row = L.wy * (32 * MI) + L.rho;
+  L.b_row = L.wx * (32 * NI) + L.rho;
   L.sw4 = swz4(L.rho);
-  L.sw8 = (L.rho & 7) ^ (L.rho >> 3);
+  L.sw8 = swz8(L.b_row);
 
-  Dma<SPARSE, F8, PROBE> dma;
+  Dma<SPARSE, F8, PROBE, MI, NI> dma;
   dma.init(g, m0, n0, tid);
 
   const int nk = g.K / G::BK;
@@ -463,19 +496,21 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
   bool first = true;
 
   for (;;) {   // one pass per tile (PERSIST: several tiles per workgroup)
-  f32x16 acc[4][4];
+  f32x16 acc[MI][NI];
 #pragma unroll
-  for (int i = 0; i < 4; i++)
+  for (int i = 0; i < MI; i++)
 #pragma unroll
-    for (int j = 0; j < 4; j++)
+    for (int j = 0; j < NI; j++)
 #pragma unroll
       for (int v = 0; v < 16; v++) acc[i][j][v] = 0.f;
   // Pin the accumulators to the accumulation register file: an empty asm with an AGPR constraint gives their
   // live ranges the AGPR class, so the 256 arch VGPRs stay free for fragments and addresses.
+  if constexpr (BIG) {
 #pragma unroll
-  for (int i = 0; i < 4; i++)
+    for (int i = 0; i < MI; i++)
 #pragma unroll
-    for (int j = 0; j < 4; j++) asm volatile("" : "+a"(acc[i][j]));
+      for (int j = 0; j < NI; j++) asm volatile("" : "+a"(acc[i][j]));
+  }
 
   // a later tile's prologue went out before the previous epilogue, whose stores count in the same counter and complete in no
   // fixed order with the loads: wait for all of it
@@ -487,22 +522,23 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
   // MODE 1: tail -- nothing left to issue, wait for everything outstanding before the barrier
   // MODE 2: last stage -- no barrier, no next fragments
   if constexpr (SPARSE) {
-    FragS f0, f1;
-    IdxWords<F8> idx[4];
-    static_for<4>([&](auto I) { load_idx_sparse1<F8, I>(smem, L, idx); });
-    static_for<12>([&](auto I) { load_frag_sparse1<F8, 0, I, PROBE>(smem, L, f0); });
+    FragS<MI, NI> f0, f1;
+    constexpr int NF = MI + 2 * NI;
+    IdxWords<F8> idx[MI];
+    static_for<MI>([&](auto I) { load_idx_sparse1<G, F8, I>(smem, L, idx); });
+    static_for<NF>([&](auto I) { load_frag_sparse1<G, 0, I, PROBE>(smem, L, f0); });
     // sparse: spread the DMA of a stage over two K steps (see dma_on_step1) when there is a steady state at all
-    constexpr bool PACED = (PROBE & PROBE_UNPACED) == 0;
+    constexpr bool PACED = BIG && (PROBE & PROBE_UNPACED) == 0;
     auto stage = [&](int kt, char* cur, char* nxt, char* prv, auto mode, auto spread) {
       constexpr int MODE = decltype(mode)::value;
       constexpr bool SPREAD0 = decltype(spread)::value != 0;   // this stage's first K step carries the rest of stage kt-1+NB
-      IdxWords<F8> idx_n[4] = {};
+      IdxWords<F8> idx_n[MI] = {};
       FFN24_FENCE();
-      static_for<16>([&](auto M) {
+      static_for<NMF>([&](auto M) {
         mfma_sparse1<F8, 0, M, PROBE>(f0, idx, acc);
         constexpr int J0 = dma_on_step0<NDMA, PACED, PACED>(M);
         if constexpr (SPREAD0 && J0 >= 0) dma.template issue<(J0 >= 0 ? J0 : 0)>(kt - 1 + NB, prv);
-        if constexpr (M < 12) load_frag_sparse1<F8, 1, M, PROBE>(cur, L, f1);
+        ride<NF, FRAG_SLOTS, M>([&](auto I) { load_frag_sparse1<G, 1, I, PROBE>(cur, L, f1); });
         FFN24_FENCE();
       });
       if constexpr (MODE != 2) {
@@ -513,18 +549,22 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
         __builtin_amdgcn_s_barrier();
       }
       FFN24_FENCE();
-      static_for<16>([&](auto M) {
+      static_for<NMF>([&](auto M) {
         mfma_sparse1<F8, 1, M, PROBE>(f1, idx, acc);
-        constexpr int J1 = dma_on_step1<NDMA, PACED, PACED>(M);
-        if constexpr (MODE == 0 && J1 >= 0) dma.template issue<(J1 >= 0 ? J1 : 0)>(kt + NB, cur);
+        if constexpr (BIG) {
+          constexpr int J1 = dma_on_step1<NDMA, PACED, PACED>(M);
+          if constexpr (MODE == 0 && J1 >= 0) dma.template issue<(J1 >= 0 ? J1 : 0)>(kt + NB, cur);
+        } else {
+          if constexpr (MODE == 0) ride<NDMA, NMF, M>([&](auto J) { dma.template issue<J>(kt + NB, cur); });
+        }
         if constexpr (MODE != 2) {
-          if constexpr (M < 4) load_idx_sparse1<F8, M>(nxt, L, idx_n);
-          if constexpr (M < 12) load_frag_sparse1<F8, 0, M, PROBE>(nxt, L, f0);
+          if constexpr (M < MI) load_idx_sparse1<G, F8, M>(nxt, L, idx_n);
+          ride<NF, FRAG_SLOTS, M>([&](auto I) { load_frag_sparse1<G, 0, I, PROBE>(nxt, L, f0); });
         }
         FFN24_FENCE();
       });
 #pragma unroll
-      for (int i = 0; i < 4; i++) idx[i] = idx_n[i];
+      for (int i = 0; i < MI; i++) idx[i] = idx_n[i];
     };
     int slot = 0;
     auto advance = [&](int kt, auto mode, auto spread) {
@@ -549,19 +589,21 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
     // Dense fp8: a stage is ONE K step of 16 matrix ops (64 cycles each).  The fragments of the whole next stage and
     // the DMA of the stage that reuses this stage's buffer (its fragments are already in registers) ride on them;
     // one barrier at the end of the stage.  Two fragment sets alternate.
-    FragD fr[2][2];
-    static_for<8>([&](auto I) { load_frag_dense1<0, I, PROBE>(smem, L, fr[0][0]); });
-    static_for<8>([&](auto I) { load_frag_dense1<1, I, PROBE>(smem, L, fr[0][1]); });
+    FragD<MI, NI> fr[2][2];
+    constexpr int NF = MI + NI;
+    static_assert(NB % 2 == 0, "the stages are walked in pairs");
+    static_for<NF>([&](auto I) { load_frag_dense1<G, 0, I, PROBE>(smem, L, fr[0][0]); });
+    static_for<NF>([&](auto I) { load_frag_dense1<G, 1, I, PROBE>(smem, L, fr[0][1]); });
     auto stage = [&](int kt, char* cur, char* nxt, auto par, auto mode) {
       constexpr int P = decltype(par)::value, MODE = decltype(mode)::value;
       FFN24_FENCE();
-      static_for<16>([&](auto M) {
+      static_for<NMF>([&](auto M) {
         mfma_dense_f8<M, PROBE>(fr[P][0], fr[P][1], acc);
-        if constexpr (MODE == 0 && M < NDMA) dma.template issue<M>(kt + NB, cur);
-        if constexpr (MODE != 2) {
-          if constexpr (M < 8) load_frag_dense1<0, M, PROBE>(nxt, L, fr[P ^ 1][0]);
-          else load_frag_dense1<1, M - 8, PROBE>(nxt, L, fr[P ^ 1][1]);
-        }
+        if constexpr (MODE == 0) ride<NDMA, (BIG ? NDMA : NMF), M>([&](auto J) { dma.template issue<J>(kt + NB, cur); });
+        if constexpr (MODE != 2) ride<2 * NF, NMF, M>([&](auto I) {
+          if constexpr (I < NF) load_frag_dense1<G, 0, I, PROBE>(nxt, L, fr[P ^ 1][0]);
+          else load_frag_dense1<G, 1, I - NF, PROBE>(nxt, L, fr[P ^ 1][1]);
+        });
         FFN24_FENCE();
       });
       if constexpr (MODE != 2) {
@@ -590,18 +632,19 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
     using M0 = std::integral_constant<int, 0>; using M1 = std::integral_constant<int, 1>; using M2 = std::integral_constant<int, 2>;
     int kt = 0;
     for (; kt < nk - NB; kt += 2) { advance(kt, P0{}, M0{}); advance(kt + 1, P1{}, M0{}); }
-    if (nk >= NB) { advance(kt, P0{}, M1{}); advance(kt + 1, P1{}, M1{}); kt += 2; }
+    for (; kt < nk - 2; kt += 2) { advance(kt, P0{}, M1{}); advance(kt + 1, P1{}, M1{}); }
     advance(kt, P0{}, M1{});
     advance(kt + 1, P1{}, M2{});
   } else {
-    FragD f0, f1;
-    static_for<8>([&](auto I) { load_frag_dense1<0, I, PROBE>(smem, L, f0); });
+    FragD<MI, NI> f0, f1;
+    constexpr int NF = MI + NI;
+    static_for<NF>([&](auto I) { load_frag_dense1<G, 0, I, PROBE>(smem, L, f0); });
     auto stage = [&](int kt, char* cur, char* nxt, auto mode) {
       constexpr int MODE = decltype(mode)::value;
       FFN24_FENCE();
-      static_for<16>([&](auto M) {
+      static_for<NMF>([&](auto M) {
         mfma_dense1<M, PROBE>(f0, acc);
-        if constexpr (M < 8) load_frag_dense1<1, M, PROBE>(cur, L, f1);
+        ride<NF, FRAG_SLOTS, M>([&](auto I) { load_frag_dense1<G, 1, I, PROBE>(cur, L, f1); });
         FFN24_FENCE();
       });
       if constexpr (MODE != 2) {
@@ -610,11 +653,15 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
         __builtin_amdgcn_s_barrier();
       }
       FFN24_FENCE();
-      static_for<16>([&](auto M) {
+      static_for<NMF>([&](auto M) {
         mfma_dense1<M, PROBE>(f1, acc);
-        constexpr int J1 = dma_on_step1<NDMA, false, (PROBE & PROBE_UNPACED) == 0>(M);
-        if constexpr (MODE == 0 && J1 >= 0) dma.template issue<(J1 >= 0 ? J1 : 0)>(kt + NB, cur);
-        if constexpr (MODE != 2 && M < 8) load_frag_dense1<0, M, PROBE>(nxt, L, f0);
+        if constexpr (BIG) {
+          constexpr int J1 = dma_on_step1<NDMA, false, (PROBE & PROBE_UNPACED) == 0>(M);
+          if constexpr (MODE == 0 && J1 >= 0) dma.template issue<(J1 >= 0 ? J1 : 0)>(kt + NB, cur);
+        } else {
+          if constexpr (MODE == 0) ride<NDMA, NMF, M>([&](auto J) { dma.template issue<J>(kt + NB, cur); });
+        }
+        if constexpr (MODE != 2) ride<NF, FRAG_SLOTS, M>([&](auto I) { load_frag_dense1<G, 0, I, PROBE>(nxt, L, f0); });
         FFN24_FENCE();
       });
     };
@@ -630,7 +677,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
     advance(kt, std::integral_constant<int, 2>{});
   }
 
-  if constexpr (F8 && !SPARSE) {
+  if constexpr (F8 && !SPARSE && BIG) {
     // the dense fp8 ops are inline assembly, which the compiler's hazard handling does not see: let the last ones
     // (16 passes each) drain before the epilogue reads the accumulators
     asm volatile("s_nop 15\n s_nop 15\n s_nop 15\n s_nop 15\n s_nop 15" ::: "memory");
@@ -641,8 +688,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
 #pragma unroll
       for (int j = 0; j < 4; j++) asm volatile("" : "+a"(acc[i][j]));
   }
-  int m_lane = m0 + L.wy * 128 + 64 * L.h;
-  int n_lane = n0 + L.wx * 128 + 4 * L.rho;
+  int m_lane = m0 + L.wy * (32 * MI) + (16 * MI) * L.h;
+  int n_lane = n0 + L.wx * (32 * NI) + NI * L.rho;
   if constexpr (PERSIST) {
     pid += pid_step;
     const bool more = pid < pid_end;
@@ -650,22 +697,23 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
       // every wave has read its last fragments: the ring is free for the next tile's first stages, which then land while
       // the epilogue runs
       __builtin_amdgcn_s_barrier();
-      tile_coords<PROBE>(g.M / TILE_M, g.N / TILE_N, pid, tm, tn);
-      m0 = tm * TILE_M; n0 = tn * TILE_N;
+      tile_coords<PROBE>(g.M / G::BM, g.N / G::BN, pid, tm, tn);
+      m0 = tm * G::BM; n0 = tn * G::BN;
       dma.init(g, m0, n0, tid);
       for (int s = 0; s < npro; s++) static_for<NDMA>([&](auto J) { dma.template issue<J>(s, smem + s * G::STAGE); });
     }
-    Epi::run(ea, acc, m_lane, n_lane);
+    Epi::template run<MI, NI>(ea, acc, m_lane, n_lane);
     if (!more) break;
     first = false;
   } else {
     if constexpr (epi_is_staged<Epi>::value) {
       // the epilogue stages its stores through the operand ring: every wave must have read its last fragments first
-      static_assert(G::LDS_TOTAL >= GEMM_THREADS / 64 * 128 * 256, "a 32 KiB staging area per wave");
+      constexpr int WAVE_BYTES = (32 * NI) * (64 * MI);   // the wave's part of the result in bf16
+      static_assert(G::LDS_TOTAL >= GEMM_THREADS / 64 * WAVE_BYTES, "a staging area per wave");
       __builtin_amdgcn_s_barrier();
-      Epi::run(ea, acc, m_lane, n_lane, smem + wave * (128 * 256));
+      Epi::template run<MI, NI>(ea, acc, m_lane, n_lane, smem + wave * WAVE_BYTES);
     } else {
-      Epi::run(ea, acc, m_lane, n_lane);
+      Epi::template run<MI, NI>(ea, acc, m_lane, n_lane);
     }
     break;
   }
@@ -688,12 +736,12 @@ struct ClkSample {
   }
 };
 
-template <bool SPARSE, class Epi, bool F8 = false, int PROBE = 0>
-__global__ void __launch_bounds__(GEMM_THREADS) gemm_kernel(GemmArgs g, typename Epi::Args ea) {
+template <bool SPARSE, class Epi, bool F8 = false, int PROBE = 0, int MI = 4, int NI = 4>
+__global__ void __launch_bounds__(GEMM_THREADS, (Geo<SPARSE, F8, MI, NI>::PER_CU)) gemm_kernel(GemmArgs g, typename Epi::Args ea) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   ClkSample cs;
   cs.begin(g);
-  gemm_tile<SPARSE, Epi, F8, PROBE>(g, ea, smem, blockIdx.x, (g.M / TILE_M) * (g.N / TILE_N), gridDim.x);
+  gemm_tile<SPARSE, Epi, F8, PROBE, MI, NI>(g, ea, smem, blockIdx.x, (g.M / TILE_M) * (g.N / TILE_N), gridDim.x);
   cs.end(g);
 }
 
@@ -702,15 +750,15 @@ __global__ void __launch_bounds__(GEMM_THREADS) gemm_kernel(GemmArgs g, typename
 // "Optimization 1": a 2:4 GEMM over most hidden features plus a dense one over the few that are not sparse enough):
 // alone, the small dense GEMM would occupy a fraction of the CUs for as long as a full round of tiles.  The dense
 // tiles, which take longer, come first.
-template <class Epi, bool F8 = false>
-__global__ void __launch_bounds__(GEMM_THREADS) gemm_pair_kernel(GemmArgs gd, typename Epi::Args ead, int nd_tiles,
+template <class Epi, bool F8 = false, int MI = 4, int NI = 4>
+__global__ void __launch_bounds__(GEMM_THREADS, (Geo<true, F8, MI, NI>::PER_CU)) gemm_pair_kernel(GemmArgs gd, typename Epi::Args ead, int nd_tiles,
                                                                   GemmArgs gs, typename Epi::Args eas) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int pid = blockIdx.x;
   ClkSample cs;
   cs.begin(gs);
-  if (pid < nd_tiles) gemm_tile<false, Epi, F8>(gd, ead, smem, pid);
-  else gemm_tile<true, Epi, F8>(gs, eas, smem, pid - nd_tiles);
+  if (pid < nd_tiles) gemm_tile<false, Epi, F8, 0, MI, NI>(gd, ead, smem, pid);
+  else gemm_tile<true, Epi, F8, 0, MI, NI>(gs, eas, smem, pid - nd_tiles);
   cs.end(gs);
 }
 

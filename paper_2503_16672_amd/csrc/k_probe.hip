@@ -117,22 +117,22 @@ double median_of(std::vector<float>& v) {
 }
 
 template <bool SPARSE, int PROBE>
-int run_gemm_variant(const GemmArgs& g, __bf16* C, int reps, double* ms_median, double* mhz) {
+int run_gemm_variant(const GemmArgs& g_in, __bf16* C, int reps, double* ms_median, double* mhz) {
   DevBuf clk;
   if (clk.alloc(16 * CLK_SLOTS)) return 1;
   if (hipMemset(clk.p, 0, 16 * CLK_SLOTS) != hipSuccess) return 1;
+  GemmArgs g = g_in;
+  g.clk = static_cast<unsigned long long*>(clk.p);
   EpiRowMajor::Args ea{C, g.N};
   std::vector<hipEvent_t> ev(reps + 1);
   for (auto& e : ev) if (hipEventCreate(&e) != hipSuccess) return 1;
-  tl_gemm_clk = static_cast<unsigned long long*>(clk.p);
   int rc = 0;
-  for (int i = 0; i < 3 && !rc; i++) rc = launch_gemm<SPARSE, EpiRowMajor, false, PROBE>(g, ea, nullptr);
+  for (int i = 0; i < 3 && !rc; i++) rc = launch_tile<SPARSE, EpiRowMajor, false, PROBE, 4, 4>(g, ea, nullptr);
   if (!rc) rc = hipEventRecord(ev[0], nullptr) != hipSuccess;
   for (int i = 0; i < reps && !rc; i++) {
-    rc = launch_gemm<SPARSE, EpiRowMajor, false, PROBE>(g, ea, nullptr);
+    rc = launch_tile<SPARSE, EpiRowMajor, false, PROBE, 4, 4>(g, ea, nullptr);
     if (!rc) rc = hipEventRecord(ev[i + 1], nullptr) != hipSuccess;
   }
-  tl_gemm_clk = nullptr;
   if (!rc) rc = hipEventSynchronize(ev[reps]) != hipSuccess;
   std::vector<float> ms(reps, 0.f);
   for (int i = 0; i < reps && !rc; i++) rc = hipEventElapsedTime(&ms[i], ev[i], ev[i + 1]) != hipSuccess;
