@@ -542,7 +542,7 @@ int sparsify24_featurewise(const void* Hc, const uint8_t* meta, const void* dZc,
   if ((dZc == nullptr) != (dZc_t == nullptr)) return FFN24_ERR_NULL;
   if (misaligned(Hc) || misaligned(meta) || misaligned(Hc_t) || misaligned(meta_t) || misaligned(dZc) || misaligned(dZc_t))
     return FFN24_ERR_ALIGN;
-  return launch_featurewise24(Hc, meta, dZc, (int)T, (int)F, Hc_t, meta_t, dZc_t, 0, nullptr, static_cast<hipStream_t>(stream)) ? FFN24_ERR_HIP : FFN24_OK;
+  return launch_featurewise24_rows(Hc, meta, dZc, (int)T, (int)F, Hc_t, meta_t, dZc_t, static_cast<hipStream_t>(stream)) ? FFN24_ERR_HIP : FFN24_OK;
 }
 
 int spmm24(const void* values, const uint8_t* meta, const void* Bt, int64_t M, int64_t N, int64_t K, void* C, void* stream) {
@@ -760,7 +760,7 @@ int ffn24_bwd(ffn24_ctx* c, const void* dY, void* dX, void* dW1, void* dW2, void
     { Timed t(c, K_TR_DW1, s); if (t.done(launch_transpose(c->dW1t, F, D, dW1, 0, nullptr, 0, nullptr, s))) return FFN24_ERR_HIP; }
     return FFN24_OK;
   }
-  { Timed t(c, K_FW, s);  if (t.done(launch_featurewise24(c->Hc, c->meta, c->dZc, T, F, c->Hc_t, c->meta_t, c->dZc_t, 1, c->tele, s))) return FFN24_ERR_HIP; }
+  { Timed t(c, K_FW, s);  if (t.done(launch_featurewise24(c->Hc, c->meta, c->dZc, T, F, c->Hc_t, c->meta_t, c->dZc_t, c->tele, s))) return FFN24_ERR_HIP; }
   if (c->tele && (rc = tele_snapshot(c, 1, s))) return rc;
   { Timed t(c, K_TR_ACT, s);
     int rc1 = launch_transpose(dY, T, D, c->dYt, 2, nullptr, 0, perm, s);

@@ -124,17 +124,16 @@ int launch_sparsify24(const void* H, int64_t rows, int64_t cols, void* vals, uin
 // Input: token-wise compressed Hc [T][F/2] + meta [T][F/8], and optionally dZc [T][F/2] with the same metadata.
 // Output: for every feature, groups of 4 consecutive tokens of the pruned activation keep their top-2:
 //   Hc_t [F][T/2], meta_t [F][T/8], and dZc_t [F][T/2] = dZ at the positions picked for H.
+// Inputs and outputs in the panel form of gemm_core.hpp (a caller's row-major tensors: featurewise24_rows_kernel below).
 // One workgroup handles 64 tokens x 64 features: decompress into LDS, then each work item takes one feature
-// and 8 consecutive tokens (two groups).  PANEL: inputs and outputs are in the panel form of gemm_core.hpp (the
-// workgroup's input is then one contiguous 4 KiB run per tensor and it writes one contiguous 4 KiB run; 128-token tiles, with
-// twice the LDS per workgroup and half the workgroups per CU, ran at 5.0 instead of 5.9 TB/s); otherwise
-// row-major, where a feature row's outputs are written 64 bytes at a time.
+// and 8 consecutive tokens (two groups).  The workgroup's input is one contiguous 4 KiB run per tensor and it writes one contiguous
+// 4 KiB run; 128-token tiles, with twice the LDS per workgroup and half the workgroups per CU, ran at 5.0 instead of 5.9 TB/s.
 constexpr int FW_TOK = 64, FW_FEAT = 64, FW_LD = FW_FEAT + 2;
 
-// SPLIT (Sec. 2, "Optimization 1"; panel form only): feature f becomes row row_of_feat[f] of the outputs; rows below
+// SPLIT (Sec. 2, "Optimization 1"): feature f becomes row row_of_feat[f] of the outputs; rows below
 // n_sparse are 2:4-compressed along tokens as above, the others -- the least sparse features -- are written out
 // uncompressed, as rows [row - n_sparse] of the dense operands Hdn_t, dZdn_t [n_dense][T] (dense panel form).
-template <bool PANEL, bool SPLIT = false>
+template <bool SPLIT>
 __global__ void __launch_bounds__(256) featurewise24_kernel(const uint16_t* __restrict__ Hc, const uint8_t* __restrict__ meta,
                                                             const uint16_t* __restrict__ dZc, int T, int F,
                                                             uint16_t* __restrict__ Hc_t, uint8_t* __restrict__ meta_t,
@@ -152,15 +151,8 @@ __global__ void __launch_bounds__(256) featurewise24_kernel(const uint16_t* __re
     int item = tid + 256 * i;
     int tok = item >> 2, ch = item & 3;
     int t = t0 + tok;
-    size_t vo, mo;   // offsets of this item's 8 stored values (in elements) and of its 2 metadata bytes
-    if constexpr (PANEL) {
-      size_t piece = a24_piece(t, f0 >> 6, F >> 6);
-      vo = piece * 32 + 8 * ch;
-      mo = piece * 8 + 2 * ch;
-    } else {
-      vo = (size_t)t * (F / 2) + f0 / 2 + 8 * ch;
-      mo = (size_t)t * (F / 8) + f0 / 8 + 2 * ch;
-    }
+    // offsets of this item's 8 stored values (in elements) and of its 2 metadata bytes
+    const size_t piece = a24_piece(t, f0 >> 6, F >> 6), vo = piece * 32 + 8 * ch, mo = piece * 8 + 2 * ch;
     u32x4 hv = ld_stream(reinterpret_cast<const u32x4*>(Hc + vo));
     u32x4 zv = {0u, 0u, 0u, 0u};
     if (has_z) zv = ld_stream(reinterpret_cast<const u32x4*>(dZc + vo));
@@ -188,9 +180,7 @@ __global__ void __launch_bounds__(256) featurewise24_kernel(const uint16_t* __re
 #pragma unroll
   for (int i = 0; i < FW_TOK / 32; i++) {
     int item = tid + 256 * i;
-    int oct, f;
-    if constexpr (PANEL) { oct = (item & 7) | ((item >> 9) << 3); f = (item >> 3) & 63; }
-    else { oct = item % (FW_TOK / 8); f = item / (FW_TOK / 8); }
+    const int oct = (item & 7) | ((item >> 9) << 3), f = (item >> 3) & 63;
     uint32_t h[8], z[8];
 #pragma unroll
     for (int j = 0; j < 8; j++) {
@@ -232,16 +222,7 @@ __global__ void __launch_bounds__(256) featurewise24_kernel(const uint16_t* __re
       uint32_t zb = i1 == 3 ? z[4 * g + 3] : (i1 == 2 ? z[4 * g + 2] : z[4 * g + 1]);
       zp[g] = za | (zb << 16);
     }
-    size_t vo, mo;
-    if constexpr (PANEL) {
-      size_t piece = a24_piece(orow, (t0 + 8 * oct) >> 6, T >> 6);
-      vo = piece * 32 + 4 * (oct & 7);
-      mo = piece * 8 + (oct & 7);
-    } else {
-      size_t frow = (size_t)(f0 + f);
-      vo = frow * (T / 2) + (t0 + 8 * oct) / 2;
-      mo = frow * (T / 8) + t0 / 8 + oct;
-    }
+    const size_t piece = a24_piece(orow, (t0 + 8 * oct) >> 6, T >> 6), vo = piece * 32 + 4 * (oct & 7), mo = piece * 8 + (oct & 7);
     st_stream(reinterpret_cast<u32x2*>(Hc_t + vo), u32x2{hp[0], hp[1]});
     if (has_z) st_stream(reinterpret_cast<u32x2*>(dZc_t + vo), u32x2{zp[0], zp[1]});
     st_stream(meta_t + mo, (uint8_t)(nb[0] | (nb[1] << 4)));
@@ -294,11 +275,110 @@ int launch_tele_sum(const unsigned long long* tele, long long elements, long lon
   return (int)hipGetLastError();
 }
 
+// The same for a caller's row-major tensors (T a multiple of 128, F of 64).  What bounds it is HBM, so both sides move whole lines.  A
+// workgroup takes 128 tokens x 256 features; a lane owns one group of 4 features and reads its 4-byte pair of each of its wave's
+// 32 tokens, so a wave's load is 256 contiguous bytes of a token row, all 64 of them are in flight before the first is used, and
+// nothing has to be spread out in LDS first.  A lane then holds 8 consecutive tokens (two groups) of 4 features at a time; the picked
+// values go to an LDS image of the transposed rows (H first, dZ after it through the same space) and leave as whole lines, 128 bytes
+// of a feature row.  In the image the rows of features 4 l + j stand at j * 64 + l: a wave's 8-byte writes then step through
+// consecutive rows, whose pitch keeps them on different banks.  Each XCD takes a contiguous run of the tiles, features fastest: a token
+// row's metadata line serves four neighbouring tiles and should be fetched by one L2.
+// Measured at 8064 x 8256 / 16384 x 16384 (with dZ): 67 us = 4.2 TB/s / 230 us = 5.0 TB/s; tiles dealt round-robin over the XCDs 69 / 259-307
+// us; 64-token tiles 81 / 373 us, 32-token tiles 207 / 1005 us (half and quarter lines out); three workgroups a CU 135 / 538 us (spills).
+// 64 x 64 tiles spread out in LDS, which read and wrote half lines and 8-byte metadata pieces, took 160 us = 1.8 TB/s.
+constexpr int FWR_CH = 4, FWR_TOK = 32 * FWR_CH;   // chunks of 8 tokens per wave, tokens per workgroup
+__global__ void __launch_bounds__(256, 2) featurewise24_rows_kernel(const uint32_t* __restrict__ Hc, const uint8_t* __restrict__ meta,
+                                                                    const uint32_t* __restrict__ dZc, int T, int F, uint8_t* __restrict__ Hc_t,
+                                                                    uint8_t* __restrict__ meta_t, uint8_t* __restrict__ dZc_t) {
+  constexpr int CH = FWR_CH, TOK = FWR_TOK, ROWB = TOK, PITCH = ROWB + 16;   // bytes of stored values per transposed row; LDS pitch
+  __shared__ __attribute__((aligned(16))) uint8_t sV[256 * PITCH];
+  __shared__ __attribute__((aligned(16))) uint32_t sM[256 * CH];             // 4 CH metadata bytes per feature, CH of each wave
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // workgroup id -> tile: ids go round-robin over the 8 XCDs; XCD x takes the tiles from x (n / 8) + min(x, n % 8) on
+  const unsigned nf = gridDim.x, n = nf * gridDim.y, bid = blockIdx.x + nf * blockIdx.y, xcd = bid & 7;
+  const unsigned tile = xcd * (n >> 3) + min(xcd, n & 7) + (bid >> 3);
+  const int f0 = (int)(tile % nf) * 256, t0 = (int)(tile / nf) * TOK;
+  const int G = F >> 2;                                           // groups (4-byte pairs) per token row
+  const int g = min((f0 >> 2) + lane, G - 1);                     // lanes beyond the last group repeat it; nothing of theirs is stored
+  const bool has_z = dZc != nullptr;
+  const size_t tw = (size_t)(t0 + 8 * CH * wave);
+  uint32_t h[8 * CH], z[8 * CH], m[8 * CH];
+#pragma unroll
+  for (int i = 0; i < 8 * CH; i++) {
+    h[i] = ld_stream(Hc + (tw + i) * G + g);
+    m[i] = meta[(tw + i) * (G >> 1) + (g >> 1)];
+    z[i] = has_z ? ld_stream(dZc + (tw + i) * G + g) : 0u;
+  }
+  uint32_t zo[CH][4][2];
+  uint32_t mo[4] = {0u, 0u, 0u, 0u};                              // the wave's CH metadata bytes of the lane's 4 features
+#pragma unroll
+  for (int c = 0; c < CH; c++) {
+    uint32_t ho[4][2];
+#pragma unroll
+    for (int q = 0; q < 2; q++) {                                 // group of 4 tokens
+      uint64_t hw[4], zw[4];                                      // a token's 4 features, 16 bits each
+#pragma unroll
+      for (int t = 0; t < 4; t++) {
+        const int i = 8 * c + 4 * q + t;
+        const uint32_t nib = m[i] >> (4 * (g & 1)), s0 = (nib & 3u) << 4, s1 = (nib & 12u) << 2;
+        hw[t] = ((uint64_t)(h[i] & 0xFFFFu) << s0) | ((uint64_t)(h[i] >> 16) << s1);
+        zw[t] = ((uint64_t)(z[i] & 0xFFFFu) << s0) | ((uint64_t)(z[i] >> 16) << s1);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        uint32_t w[4], x[4];
+#pragma unroll
+        for (int t = 0; t < 4; t++) { w[t] = (uint32_t)(hw[t] >> (16 * j)) & 0xFFFFu; x[t] = (uint32_t)(zw[t] >> (16 * j)) & 0xFFFFu; }
+        const uint32_t nb = pick24_words(w[0], w[1], w[2], w[3], ho[j][q]);
+        const uint32_t i0 = nb & 3u, i1 = nb >> 2;
+        const uint32_t za = i0 == 0 ? x[0] : (i0 == 1 ? x[1] : x[2]), zb = i1 == 3 ? x[3] : (i1 == 2 ? x[2] : x[1]);
+        zo[c][j][q] = za | (zb << 16);
+        mo[j] |= nb << (8 * c + 4 * q);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; j++) *reinterpret_cast<u32x2*>(sV + (64 * j + lane) * PITCH + 8 * (CH * wave + c)) = u32x2{ho[j][0], ho[j][1]};
+  }
+#pragma unroll
+  for (int j = 0; j < 4; j++) {
+    static_assert(CH == 4, "a wave's metadata bytes of a feature are one word");
+    sM[(64 * j + lane) * CH + wave] = mo[j];
+  }
+  __syncthreads();
+  constexpr int PIECES = ROWB / 16;                               // 16-byte pieces of a row
+  auto flush = [&](uint8_t* out) {
+#pragma unroll
+    for (int i = 0; i < PIECES; i++) {
+      const int item = tid + 256 * i, r = item / PIECES, pc = item % PIECES, f = f0 + 4 * (r & 63) + (r >> 6);
+      if (f < F) st_stream(reinterpret_cast<u32x4*>(out + (size_t)f * T + t0 + 16 * pc), *reinterpret_cast<const u32x4*>(sV + r * PITCH + 16 * pc));
+    }
+  };
+  flush(Hc_t);
+  {
+    const int f = f0 + 4 * (tid & 63) + (tid >> 6);
+    uint8_t* out = meta_t + (size_t)f * (T >> 3) + (t0 >> 3);
+    if (f < F) *reinterpret_cast<u32x4*>(out) = *reinterpret_cast<const u32x4*>(sM + tid * CH);
+  }
+  if (!has_z) return;                                             // (a kernel argument: all work items or none)
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < CH; c++)
+#pragma unroll
+    for (int j = 0; j < 4; j++) *reinterpret_cast<u32x2*>(sV + (64 * j + lane) * PITCH + 8 * (CH * wave + c)) = u32x2{zo[c][j][0], zo[c][j][1]};
+  __syncthreads();
+  flush(dZc_t);
+}
+
+int launch_featurewise24_rows(const void* Hc, const uint8_t* meta, const void* dZc, int T, int F, void* Hc_t, uint8_t* meta_t, void* dZc_t, hipStream_t s) {
+  hipLaunchKernelGGL(featurewise24_rows_kernel, dim3((F + 255) / 256, T / FWR_TOK), dim3(256), 0, s, static_cast<const uint32_t*>(Hc), meta, static_cast<const uint32_t*>(dZc),
+                     T, F, static_cast<uint8_t*>(Hc_t), meta_t, static_cast<uint8_t*>(dZc_t));
+  return (int)hipGetLastError();
+}
+
 int launch_featurewise24(const void* Hc, const uint8_t* meta, const void* dZc, int T, int F,
-                         void* Hc_t, uint8_t* meta_t, void* dZc_t, int panel, unsigned long long* tele, hipStream_t s) {
+                         void* Hc_t, uint8_t* meta_t, void* dZc_t, unsigned long long* tele, hipStream_t s) {
   dim3 grid(F / FW_FEAT, T / FW_TOK);
-  auto kern = panel ? featurewise24_kernel<true> : featurewise24_kernel<false>;
-  hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, static_cast<const uint16_t*>(Hc), meta,
+  hipLaunchKernelGGL(featurewise24_kernel<false>, grid, dim3(256), 0, s, static_cast<const uint16_t*>(Hc), meta,
                      static_cast<const uint16_t*>(dZc), T, F, static_cast<uint16_t*>(Hc_t), meta_t, static_cast<uint16_t*>(dZc_t),
                      nullptr, 0, nullptr, nullptr, tele, nullptr, nullptr);
   return (int)hipGetLastError();
@@ -308,7 +388,7 @@ int launch_featurewise24(const void* Hc, const uint8_t* meta, const void* dZc, i
 int launch_featurewise24_rowmax(const void* Hc, const uint8_t* meta, const void* dZc, int T, int F, void* Hc_t, uint8_t* meta_t, void* dZc_t,
                                 uint32_t* hmax, uint32_t* zmax, hipStream_t s) {
   dim3 grid(F / FW_FEAT, T / FW_TOK);
-  hipLaunchKernelGGL(featurewise24_kernel<true>, grid, dim3(256), 0, s, static_cast<const uint16_t*>(Hc), meta,
+  hipLaunchKernelGGL(featurewise24_kernel<false>, grid, dim3(256), 0, s, static_cast<const uint16_t*>(Hc), meta,
                      static_cast<const uint16_t*>(dZc), T, F, static_cast<uint16_t*>(Hc_t), meta_t, static_cast<uint16_t*>(dZc_t),
                      nullptr, 0, nullptr, nullptr, nullptr, hmax, zmax);
   return (int)hipGetLastError();
@@ -318,7 +398,7 @@ int launch_featurewise24_split(const void* Hc, const uint8_t* meta, const void* 
                                void* Hc_t, uint8_t* meta_t, void* dZc_t, void* Hdn_t, void* dZdn_t, unsigned long long* tele,
                                uint32_t* hmax, uint32_t* zmax, hipStream_t s) {
   dim3 grid(F / FW_FEAT, T / FW_TOK);
-  hipLaunchKernelGGL((featurewise24_kernel<true, true>), grid, dim3(256), 0, s, static_cast<const uint16_t*>(Hc), meta,
+  hipLaunchKernelGGL(featurewise24_kernel<true>, grid, dim3(256), 0, s, static_cast<const uint16_t*>(Hc), meta,
                      static_cast<const uint16_t*>(dZc), T, F, static_cast<uint16_t*>(Hc_t), meta_t, static_cast<uint16_t*>(dZc_t),
                      row_of_feat, n_sparse, static_cast<uint16_t*>(Hdn_t), static_cast<uint16_t*>(dZdn_t), tele, hmax, zmax);
   return (int)hipGetLastError();

@@ -155,9 +155,10 @@ int launch_sparsify24(const void* H, int64_t rows, int64_t cols, void* vals, uin
 int launch_sparsify24_quant(const void* H, int64_t rows, int64_t cols, float scale, void* vals8, uint8_t* meta, hipStream_t s);
 // e4m3 in and out, pick on the code bytes; cols % 16 == 0
 int launch_sparsify24_bytes(const void* H8, int64_t rows, int64_t cols, void* vals8, uint8_t* meta, hipStream_t s);
-// panel: inputs and outputs are in panel form (the library's own buffers) instead of row-major
+// inputs and outputs in panel form (the library's own buffers); _rows: row-major (a caller's), T % 128 == 0, F % 64 == 0
 int launch_featurewise24(const void* Hc, const uint8_t* meta, const void* dZc, int T, int F,
-                         void* Hc_t, uint8_t* meta_t, void* dZc_t, int panel, unsigned long long* tele, hipStream_t s);
+                         void* Hc_t, uint8_t* meta_t, void* dZc_t, unsigned long long* tele, hipStream_t s);
+int launch_featurewise24_rows(const void* Hc, const uint8_t* meta, const void* dZc, int T, int F, void* Hc_t, uint8_t* meta_t, void* dZc_t, hipStream_t s);
 // out[0] = elements, out[1..3] = the sums of the telemetry slots (non-zero, kept token-wise, kept feature-wise), out[4] = path
 int launch_tele_sum(const unsigned long long* tele, long long elements, long long path, long long* out, hipStream_t s);
 // panel form -> row-major copy of a compressed operand: rows x npanels pieces of `piece_bytes` (64 values / 8 or 16 metadata)

@@ -134,3 +134,21 @@ def test_tiles_telemetry_counts(F24):
         assert n["kept_tokenwise"] == int((P.words_of(ctx.saved("Hc")) != 0).sum())
         assert n["kept_featurewise"] == int((P.words_of(ctx.saved("Hc_t")) != 0).sum())
         ctx.close()
+
+
+@pytest.mark.parametrize("T,Fh,with_dz", [(128, 64, True), (128, 192, True), (256, 256, False), (384, 320, True), (1152, 1088, True), (2048, 4160, False)])
+def test_featurewise_rows_edges(F24, T, Fh, with_dz):
+    """Row-major feature-wise re-compression at the edges of its 128 x 256 tiles (feature counts that fill a quarter, three quarters, one and a
+    quarter of a tile; tile counts that are no multiple of the XCDs), signed values, with and without dZ: bit for bit against the oracle."""
+    print(f"featurewise rows T={T} F={Fh} dZ={with_dz}", flush=True)
+    rng = np.random.default_rng(T + Fh)
+    H = rng.normal(size=(T, Fh)).astype(np.float32) * (rng.random((T, Fh)) < 0.3)
+    Z = rng.normal(size=(T, Fh)).astype(np.float32)
+    v, m = O.sparsify24(O.f32_to_bf16_bits(H))
+    zc = O.compress_with_meta(O.f32_to_bf16_bits(Z), m)
+    v_ref, m_ref = O.sparsify24(np.ascontiguousarray(O.decompress24(v, m).T))
+    z_ref = O.compress_with_meta(np.ascontiguousarray(O.decompress24(zc, m).T), m_ref)
+    hv, mt, zt = F24.sparsify24_featurewise(P.dev_bf16_from_words(v), torch.from_numpy(m).cuda(), P.dev_bf16_from_words(zc) if with_dz else None)
+    torch.cuda.synchronize()
+    assert np.array_equal(mt.cpu().numpy(), m_ref) and np.array_equal(P.words_of(hv), v_ref)
+    assert (zt is None) if not with_dz else np.array_equal(P.words_of(zt), z_ref)
