@@ -122,7 +122,7 @@ FFN24_API int ffn24_set_row_scales(ffn24_ctx* ctx, const float* sx, const float*
  * memory, cols a multiple of 8.  axis 1: one scale per row, scales[r] = max_c |X[r][c]| / 448 (1 if the row is all zero);
  * axis 0: one scale per column, scales[c] = max_r |X[r][c]| / 448.  codes[r][c] = e4m3(X[r][c] / scale), round to nearest even
  * (nothing saturates: the largest entry of every row / column maps to 448).  codes: rows x cols bytes, row-major; scales: fp32,
- * [rows] or [cols] (with axis 0 the buffer also holds intermediate values until the call's last kernel has run).  These are the
+ * [rows] or [cols] (with axis 0 the codes buffer holds intermediate values until the call's last kernel has run).  These are the
  * (codes, scales) pairs that ffn24_set_row_scales / ffn24_fwd and ffn24_bwd_rowwise take, made from the caller's bf16 tensors:
  * X per row, W1 and W2 per column for the forward; dY per row and per column, X per column, W2 and W1 per row for the backward.
  * Empty matrices are a no-op.  FFN24_ERR_SHAPE for another axis or cols % 8 != 0. */

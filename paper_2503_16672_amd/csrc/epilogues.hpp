@@ -456,6 +456,23 @@ __device__ __forceinline__ uint32_t cvt_e4m3x2(float lo, float hi, uint32_t old,
                    : (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(lo, hi, (int)old, false);
 }
 
+// Correctly rounded division by a scale that divides many values: with r the correctly rounded reciprocal of s and q = RN(a r), the
+// remainder a - q s is exact in one fused multiply-add and RN(q + remainder * r) is RN(a / s) (Markstein's theorem).  Five operations a
+// value instead of the ten of the division sequence, and the same codes as with an IEEE division: q is clamped to +-2^20 first,
+// beyond the largest code by far, so that a quotient that overflows (or an infinity) keeps its sign instead of turning into a NaN, and
+// copysign keeps the sign of a zero.  The theorem wants no underflow on the way: ok() admits scales for which a remainder can
+// underflow only where |a / s| is below 2^-20, which every e4m3 rounding takes to zero.
+struct ExactDiv {
+  float s, r;
+  __device__ __forceinline__ ExactDiv() {}
+  __device__ __forceinline__ explicit ExactDiv(float scale) : s(scale), r(1.f / scale) {}
+  __device__ __forceinline__ bool ok() const { return s >= 0x1p-60f && s <= 0x1p60f; }
+  __device__ __forceinline__ float operator()(float a) const {
+    const float q = __builtin_amdgcn_fmed3f(a * r, -0x1p20f, 0x1p20f);
+    return __builtin_copysignf(__builtin_fmaf(__builtin_fmaf(-q, s, a), r, q), a);
+  }
+};
+
 // fp8 up-projection: z = zscale * acc + b1 (zscale = sx * sw1); h = bf16(max(0, z)^2); the keep-2-of-4 pick is made on
 // the bf16 words exactly as in EpiPrune24; the kept values are then quantised, e4m3(h / sh).
 //   Hc8, meta: panel form of the fp8 operand: piece = 64 stored bytes + 16 metadata bytes for 128 features of a token;

@@ -952,95 +952,200 @@ int launch_quantise_rows(const void* Hc16, const uint8_t* meta16, const uint32_t
 // Row-wise / column-wise e4m3 quantisation of a bf16 matrix X [R][C] (the operands a caller hands to the row-wise-scaled
 // GEMMs; Sec. 2 of the paper: FP8 row-wise scaling).  scale = (largest magnitude of the row or column) / 448, 1 if that is
 // zero; codes = e4m3(x / scale), row-major [R][C].
-// Per row: one wave per row, two passes over the row (the second one finds it in the caches).
+
+// largest magnitudes of a bf16 vector, lane by lane of its 16-bit halves (sign cleared, as unsigned integers)
+typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
+__device__ __forceinline__ u16x8 max_mag(u16x8 m, u32x4 v) {
+  return __builtin_elementwise_max(m, __builtin_bit_cast(u16x8, v & u32x4{0x7FFF7FFFu, 0x7FFF7FFFu, 0x7FFF7FFFu, 0x7FFF7FFFu}));
+}
+__device__ __forceinline__ float scale_of_max(uint32_t word) {
+  const float mx = __builtin_bit_cast(float, word << 16);
+  return mx > 0.f ? mx / 448.f : 1.f;
+}
+
+// 8 bf16 values -> 8 codes, value j divided by d[j] (or all by the one divider)
+template <int N>
+__device__ __forceinline__ u32x2 quantise8(u32x4 v, const ExactDiv (&d)[N]) {
+  uint32_t q[2];
+#pragma unroll
+  for (int i = 0; i < 2; i++) {
+    const int j = 4 * i;
+    q[i] = cvt_e4m3x2(d[j % N](bf16_lo_to_f32(v[2 * i])), d[(j + 1) % N](bf16_hi_to_f32(v[2 * i])), 0u, false);
+    q[i] = cvt_e4m3x2(d[(j + 2) % N](bf16_lo_to_f32(v[2 * i + 1])), d[(j + 3) % N](bf16_hi_to_f32(v[2 * i + 1])), q[i], true);
+  }
+  return u32x2{q[0], q[1]};
+}
+// the same with the division instruction sequence, for scales that ExactDiv does not take
+template <int N>
+__device__ __forceinline__ u32x2 quantise8_ieee(u32x4 v, const ExactDiv (&d)[N]) {
+  uint32_t q[2];
+#pragma unroll
+  for (int i = 0; i < 2; i++) {
+    const int j = 4 * i;
+    q[i] = cvt_e4m3x2(bf16_lo_to_f32(v[2 * i]) / d[j % N].s, bf16_hi_to_f32(v[2 * i]) / d[(j + 1) % N].s, 0u, false);
+    q[i] = cvt_e4m3x2(bf16_lo_to_f32(v[2 * i + 1]) / d[(j + 2) % N].s, bf16_hi_to_f32(v[2 * i + 1]) / d[(j + 3) % N].s, q[i], true);
+  }
+  return u32x2{q[0], q[1]};
+}
+
+// Per row, the whole row held in registers between the maximum and the quantisation: LANES work items per row (a wave, or the workgroup
+// for rows beyond 4096 values), up to NV 16-byte pieces each, all requested before the first is used.
+template <int LANES, int NV>
 __global__ void __launch_bounds__(256) quantise_bf16_rows_kernel(const u32x4* __restrict__ X, int64_t R, int C8, u32x2* __restrict__ codes,
                                                                  float* __restrict__ scales) {
+  const int t = threadIdx.x & (LANES - 1);
+  const int64_t r = (int64_t)blockIdx.x * (256 / LANES) + threadIdx.x / LANES;
+  if (r >= R) return;                                  // (whole waves; with LANES = 256 there is one row per workgroup)
+  const u32x4* row = X + r * C8;
+  u32x4 v[NV];
+#pragma unroll
+  for (int i = 0; i < NV; i++) {
+    const int c = t + LANES * i;
+    v[i] = c < C8 ? ld_stream(row + c) : u32x4{0u, 0u, 0u, 0u};
+  }
+  u16x8 mv = {};
+#pragma unroll
+  for (int i = 0; i < NV; i++) mv = max_mag(mv, v[i]);
+  uint32_t m = 0u;
+#pragma unroll
+  for (int j = 0; j < 8; j++) m = max(m, (uint32_t)mv[j]);
+#pragma unroll
+  for (int sft = 1; sft < 64; sft <<= 1) m = max(m, (uint32_t)__shfl_xor((int)m, sft, 64));
+  if constexpr (LANES == 256) {
+    __shared__ uint32_t sm[4];
+    if ((t & 63) == 0) sm[t >> 6] = m;
+    __syncthreads();
+    m = max(max(sm[0], sm[1]), max(sm[2], sm[3]));
+  }
+  const float s = scale_of_max(m);
+  if (t == 0) scales[r] = s;
+  const ExactDiv d[1] = {ExactDiv(s)};
+  u32x2* out = codes + r * C8;
+  const bool ok = d[0].ok();
+#pragma unroll
+  for (int i = 0; i < NV; i++) {
+    const int c = t + LANES * i;
+    if (c < C8) st_stream(out + c, ok ? quantise8(v[i], d) : quantise8_ieee(v[i], d));
+  }
+}
+
+// Rows too long for the registers: one wave per row, two passes over it (the second one finds it in the caches).
+__global__ void __launch_bounds__(256) quantise_bf16_long_rows_kernel(const u32x4* __restrict__ X, int64_t R, int C8, u32x2* __restrict__ codes,
+                                                                      float* __restrict__ scales) {
   const int lane = threadIdx.x & 63;
   const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (r >= R) return;
   const u32x4* row = X + r * C8;
+  u16x8 mv = {};
+  for (int c = lane; c < C8; c += 64) mv = max_mag(mv, row[c]);
   uint32_t m = 0u;
-  for (int c = lane; c < C8; c += 64) {
-    u32x4 v = row[c];
 #pragma unroll
-    for (int d = 0; d < 4; d++) m = max(m, max(v[d] & 0x7FFFu, (v[d] >> 16) & 0x7FFFu));
-  }
+  for (int j = 0; j < 8; j++) m = max(m, (uint32_t)mv[j]);
 #pragma unroll
   for (int sft = 1; sft < 64; sft <<= 1) m = max(m, (uint32_t)__shfl_xor((int)m, sft, 64));
-  const float mx = __builtin_bit_cast(float, m << 16);
-  const float s = mx > 0.f ? mx / 448.f : 1.f;
+  const float s = scale_of_max(m);
   if (lane == 0) scales[r] = s;
+  const ExactDiv d[1] = {ExactDiv(s)};
   u32x2* out = codes + r * C8;
-  for (int c = lane; c < C8; c += 64) {
-    u32x4 v = row[c];
-    uint32_t q0 = cvt_e4m3x2(bf16_lo_to_f32(v[0]) / s, bf16_hi_to_f32(v[0]) / s, 0u, false);
-    q0 = cvt_e4m3x2(bf16_lo_to_f32(v[1]) / s, bf16_hi_to_f32(v[1]) / s, q0, true);
-    uint32_t q1 = cvt_e4m3x2(bf16_lo_to_f32(v[2]) / s, bf16_hi_to_f32(v[2]) / s, 0u, false);
-    q1 = cvt_e4m3x2(bf16_lo_to_f32(v[3]) / s, bf16_hi_to_f32(v[3]) / s, q1, true);
-    st_stream(out + c, u32x2{q0, q1});
+  for (int c = lane; c < C8; c += 64) st_stream(out + c, d[0].ok() ? quantise8(row[c], d) : quantise8_ieee(row[c], d));
+}
+
+// Per column, three kernels: (1) the largest magnitude words of every column over slabs of rows, (2) their maximum over the slabs and the
+// scale, (3) the codes.  A workgroup of (1) and (3) covers 64 pieces of 8 columns x 4 interleaved row groups, so that a wave's load is
+// 1024 contiguous bytes of a row and QC_UNROLL rows are in flight per work item.  The slab maxima [slab][C] (16-bit words) stand in the
+// codes buffer, which (3) overwrites afterwards: 2 C ceil(R / QC_ROWS) bytes of its R C.  With a single slab (1) writes the scales.
+constexpr int QC_UNROLL = 16, QC_ROWS = 4 * QC_UNROLL, QC_SLABS = 256;
+
+__global__ void __launch_bounds__(256) colmax_bf16_kernel(const u32x4* __restrict__ X, int64_t R, int C8, int64_t slab_rows, u16x8* __restrict__ part,
+                                                          float* __restrict__ scales) {
+  __shared__ u16x8 sm[4][64];
+  const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
+  const int c = blockIdx.x * 64 + lane;
+  const int64_t r0 = (int64_t)blockIdx.y * slab_rows, r1 = r0 + slab_rows < R ? r0 + slab_rows : R;
+  u16x8 m = {};
+  if (c < C8) {
+    for (int64_t rb = r0 + grp; rb < r1; rb += QC_ROWS) {
+      u32x4 v[QC_UNROLL];
+#pragma unroll
+      for (int i = 0; i < QC_UNROLL; i++) {
+        const int64_t r = rb + 4 * i;
+        v[i] = X[(r < r1 ? r : rb) * C8 + c];          // past the slab's end: its first row again
+      }
+#pragma unroll
+      for (int i = 0; i < QC_UNROLL; i++) m = max_mag(m, v[i]);
+    }
+  }
+  sm[grp][lane] = m;
+  __syncthreads();
+  if (grp != 0 || c >= C8) return;
+  m = __builtin_elementwise_max(__builtin_elementwise_max(m, sm[1][lane]), __builtin_elementwise_max(sm[2][lane], sm[3][lane]));
+  if (part) part[(size_t)blockIdx.y * C8 + c] = m;
+  else {
+#pragma unroll
+    for (int j = 0; j < 8; j++) scales[8 * c + j] = scale_of_max(m[j]);
   }
 }
 
-// Per column, step 1: cmax[c] (zeroed by the caller) is raised to the largest magnitude word of column c.  A work item takes 8
-// consecutive columns of a slab of QC_ROWS rows.
-constexpr int QC_ROWS = 64;
-__global__ void __launch_bounds__(256) colmax_bf16_kernel(const u32x4* __restrict__ X, int64_t R, int C8, uint32_t* __restrict__ cmax) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= C8) return;
-  const int64_t r0 = (int64_t)blockIdx.y * QC_ROWS, r1 = r0 + QC_ROWS < R ? r0 + QC_ROWS : R;
-  uint32_t m[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
-  for (int64_t r = r0; r < r1; r++) {
-    u32x4 v = ld_stream(X + r * C8 + c);
+// (2): 16 pieces of 8 columns x 16 groups of slabs per workgroup
+__global__ void __launch_bounds__(256) col_scales_kernel(const u16x8* __restrict__ part, int C8, int slabs, float* __restrict__ scales) {
+  __shared__ u16x8 sm[16][16];
+  const int ci = threadIdx.x & 15, grp = threadIdx.x >> 4, c = blockIdx.x * 16 + ci;
+  u16x8 m = {};
+  if (c < C8)
+    for (int k = grp; k < slabs; k += 16) m = __builtin_elementwise_max(m, part[(size_t)k * C8 + c]);
+  sm[grp][ci] = m;
+  __syncthreads();
+  if (threadIdx.x >= 128) return;
+  const int col = threadIdx.x;                          // 16 pieces x 8 columns
+  if (blockIdx.x * 128 + col >= 8 * C8) return;
+  uint32_t w = 0u;
 #pragma unroll
-    for (int d = 0; d < 4; d++) { m[2 * d] = max(m[2 * d], v[d] & 0x7FFFu); m[2 * d + 1] = max(m[2 * d + 1], (v[d] >> 16) & 0x7FFFu); }
-  }
-#pragma unroll
-  for (int j = 0; j < 8; j++) if (m[j]) atomicMax(cmax + 8 * c + j, m[j]);
+  for (int k = 0; k < 16; k++) w = max(w, (uint32_t)reinterpret_cast<const uint16_t*>(&sm[k][col >> 3])[col & 7]);
+  scales[blockIdx.x * 128 + col] = scale_of_max(w);
 }
-// step 2: codes with the scales taken from the column maxima
-__global__ void __launch_bounds__(256) quantise_bf16_cols_kernel(const u32x4* __restrict__ X, int64_t R, int C8, const u32x4* __restrict__ cmax,
+
+__global__ void __launch_bounds__(256) quantise_bf16_cols_kernel(const u32x4* __restrict__ X, int64_t R, int C8, const float* __restrict__ scales,
                                                                  u32x2* __restrict__ codes) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= C8) return;
-  const int64_t r0 = (int64_t)blockIdx.y * QC_ROWS, r1 = r0 + QC_ROWS < R ? r0 + QC_ROWS : R;
-  float s[8];
-  u32x4 ma = cmax[2 * c], mb = cmax[2 * c + 1];
+  const unsigned nc = (unsigned)((C8 + 63) / 64);      // (one grid dimension: rows / QC_ROWS may pass the limit of the second)
+  const int c = (int)(blockIdx.x % nc) * 64 + (threadIdx.x & 63);
+  const int64_t rb = (int64_t)(blockIdx.x / nc) * QC_ROWS + (threadIdx.x >> 6);
+  if (c >= C8 || rb >= R) return;
+  u32x4 v[QC_UNROLL];
 #pragma unroll
-  for (int j = 0; j < 8; j++) {
-    float mx = __builtin_bit_cast(float, (j < 4 ? ma[j] : mb[j - 4]) << 16);
-    s[j] = mx > 0.f ? mx / 448.f : 1.f;
+  for (int i = 0; i < QC_UNROLL; i++) {
+    const int64_t r = rb + 4 * i;
+    v[i] = ld_stream(X + (r < R ? r : rb) * C8 + c);
   }
-  for (int64_t r = r0; r < r1; r++) {
-    u32x4 v = ld_stream(X + r * C8 + c);
-    uint32_t q0 = cvt_e4m3x2(bf16_lo_to_f32(v[0]) / s[0], bf16_hi_to_f32(v[0]) / s[1], 0u, false);
-    q0 = cvt_e4m3x2(bf16_lo_to_f32(v[1]) / s[2], bf16_hi_to_f32(v[1]) / s[3], q0, true);
-    uint32_t q1 = cvt_e4m3x2(bf16_lo_to_f32(v[2]) / s[4], bf16_hi_to_f32(v[2]) / s[5], 0u, false);
-    q1 = cvt_e4m3x2(bf16_lo_to_f32(v[3]) / s[6], bf16_hi_to_f32(v[3]) / s[7], q1, true);
-    st_stream(codes + r * C8 + c, u32x2{q0, q1});
+  ExactDiv d[8];
+  bool ok = true;
+#pragma unroll
+  for (int j = 0; j < 8; j++) { d[j] = ExactDiv(scales[8 * c + j]); ok = ok && d[j].ok(); }
+#pragma unroll
+  for (int i = 0; i < QC_UNROLL; i++) {
+    const int64_t r = rb + 4 * i;
+    if (r < R) st_stream(codes + r * C8 + c, ok ? quantise8(v[i], d) : quantise8_ieee(v[i], d));
   }
-}
-// step 3: the column maxima (bf16 words) become the scales, in place
-__global__ void __launch_bounds__(256) scales_from_max_kernel(uint32_t* __restrict__ cmax, int C) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= C) return;
-  const float mx = __builtin_bit_cast(float, cmax[c] << 16);
-  cmax[c] = __builtin_bit_cast(uint32_t, mx > 0.f ? mx / 448.f : 1.f);
 }
 
 int launch_quantise_bf16(const void* X, int64_t R, int64_t C, int axis, void* codes, float* scales, hipStream_t s) {
   const int C8 = (int)(C / 8);
+  const u32x4* x = static_cast<const u32x4*>(X);
+  u32x2* out = static_cast<u32x2*>(codes);
   if (axis == 1) {
-    hipLaunchKernelGGL(quantise_bf16_rows_kernel, dim3((unsigned)((R + 3) / 4)), dim3(256), 0, s, static_cast<const u32x4*>(X), R, C8,
-                       static_cast<u32x2*>(codes), scales);
+    auto kern = C8 <= 64 * 2 ? quantise_bf16_rows_kernel<64, 2> : C8 <= 64 * 8 ? quantise_bf16_rows_kernel<64, 8>
+              : C8 <= 256 * 8 ? quantise_bf16_rows_kernel<256, 8> : quantise_bf16_long_rows_kernel;
+    const int per = C8 > 64 * 8 && C8 <= 256 * 8 ? 1 : 4;   // rows per workgroup
+    hipLaunchKernelGGL(kern, dim3((unsigned)((R + per - 1) / per)), dim3(256), 0, s, x, R, C8, out, scales);
     return (int)hipGetLastError();
   }
-  uint32_t* cmax = reinterpret_cast<uint32_t*>(scales);
-  if (int rc = launch_zero32(cmax, (size_t)C, s)) return rc;
-  dim3 grid((unsigned)((C8 + 255) / 256), (unsigned)((R + QC_ROWS - 1) / QC_ROWS));
-  hipLaunchKernelGGL(colmax_bf16_kernel, grid, dim3(256), 0, s, static_cast<const u32x4*>(X), R, C8, cmax);
-  hipLaunchKernelGGL(quantise_bf16_cols_kernel, grid, dim3(256), 0, s, static_cast<const u32x4*>(X), R, C8, reinterpret_cast<const u32x4*>(cmax),
-                     static_cast<u32x2*>(codes));
-  hipLaunchKernelGGL(scales_from_max_kernel, dim3((unsigned)((C + 255) / 256)), dim3(256), 0, s, cmax, (int)C);
+  // at most QC_SLABS slabs, each a whole number of QC_ROWS rows
+  const int64_t slab_rows = ((R + QC_SLABS - 1) / QC_SLABS + QC_ROWS - 1) / QC_ROWS * QC_ROWS;
+  const int slabs = (int)((R + slab_rows - 1) / slab_rows);
+  u16x8* part = slabs > 1 ? static_cast<u16x8*>(codes) : nullptr;
+  const unsigned nc = (unsigned)((C8 + 63) / 64);
+  hipLaunchKernelGGL(colmax_bf16_kernel, dim3(nc, (unsigned)slabs), dim3(256), 0, s, x, R, C8, slab_rows, part, scales);
+  if (part) hipLaunchKernelGGL(col_scales_kernel, dim3((unsigned)((C8 + 15) / 16)), dim3(256), 0, s, part, C8, slabs, scales);
+  hipLaunchKernelGGL(quantise_bf16_cols_kernel, dim3(nc * (unsigned)((R + QC_ROWS - 1) / QC_ROWS)), dim3(256), 0, s, x, R, C8, scales, out);
   return (int)hipGetLastError();
 }
 

@@ -152,3 +152,35 @@ def test_featurewise_rows_edges(F24, T, Fh, with_dz):
     torch.cuda.synchronize()
     assert np.array_equal(mt.cpu().numpy(), m_ref) and np.array_equal(P.words_of(hv), v_ref)
     assert (zt is None) if not with_dz else np.array_equal(P.words_of(zt), z_ref)
+
+
+@pytest.mark.parametrize("R,C", [(1, 16), (2, 504), (3, 1032), (63, 520), (64, 512), (65, 1024), (130, 4096), (37, 4104), (9, 16384), (5, 16392), (16385, 16)])
+def test_quantise_e4m3_edges(F24, R, C):
+    """Every row width class (two, eight pieces a lane, a workgroup a row, too long for the registers), row counts at the edges of the
+    column kernels' slabs (one slab, a partial one, more than 256 x 64 rows), scales from denormal to near the largest, zeros of both
+    signs, infinities and NaNs: codes and scales bit for bit those of an IEEE division."""
+    print(f"quantise_e4m3 edges R={R} C={C}", flush=True)
+    rng = np.random.default_rng(R * 7 + C)
+    x = rng.standard_normal((R, C)).astype(np.float32)
+    x *= np.exp2(rng.integers(-3, 4, size=(R, 1)) * 40.0).astype(np.float32)        # 2^-120 .. 2^120
+    x[rng.random((R, C)) < 0.2] = -0.0
+    if R > 2:
+        x[1] *= 0.0
+        x[2] = np.exp2(-130.0) * rng.integers(-3, 4, size=C)
+    words = O.f32_to_bf16_bits(x)
+    if R > 4:
+        words[3, 0] = 0x7F80
+        words[4, :2] = (0xFF80, 0x7FC0)
+    w = torch.from_numpy(words.view(np.int16).copy()).view(torch.bfloat16)
+    xf = w.float()
+    for axis in (1, 0):
+        mag = torch.from_numpy((words & 0x7FFF).astype(np.int32)).amax(dim=axis)      # the largest magnitude word, NaNs above infinity
+        amax = (mag << 16).view(torch.float32)
+        s = torch.where(amax > 0, amax / 448.0, torch.ones_like(amax))
+        q = (xf / (s[:, None] if axis == 1 else s[None, :])).numpy()
+        q = np.where(np.isnan(q), np.float32(-448.0), q)                               # what the saturation makes of a NaN
+        ref = O.f32_to_e4m3_bits(np.clip(q, -448.0, 448.0))
+        codes, scales = F24.quantise_e4m3(w.cuda(), axis)
+        torch.cuda.synchronize()
+        assert torch.equal(scales.cpu(), s)
+        assert np.array_equal(codes.cpu().numpy(), ref)
