@@ -457,19 +457,25 @@ __device__ __forceinline__ uint32_t cvt_e4m3x2(float lo, float hi, uint32_t old,
 }
 
 // Correctly rounded division by a scale that divides many values: with r the correctly rounded reciprocal of s and q = RN(a r), the
-// remainder a - q s is exact in one fused multiply-add and RN(q + remainder * r) is RN(a / s) (Markstein's theorem).  Five operations a
-// value instead of the ten of the division sequence, and the same codes as with an IEEE division: q is clamped to +-2^20 first,
-// beyond the largest code by far, so that a quotient that overflows (or an infinity) keeps its sign instead of turning into a NaN, and
-// copysign keeps the sign of a zero.  The theorem wants no underflow on the way: ok() admits scales for which a remainder can
-// underflow only where |a / s| is below 2^-20, which every e4m3 rounding takes to zero.
+// remainder a - q s is exact in one fused multiply-add and RN(q + remainder * r) is RN(a / s) (Markstein's theorem).  Six operations a
+// value instead of the ten of the division sequence, and the same e4m3 codes as with an IEEE division for every pair of operands:
+//   - q is clamped to +-2^20 first, beyond the largest code by far, so that a quotient that overflows (or an infinity) keeps its sign
+//     instead of turning into a NaN; copysign keeps the sign of a zero;
+//   - the theorem wants no underflow on the way: both operands are multiplied by a power of two p that keeps s within 2^+-60, so a
+//     remainder can underflow only where |a / s| is below 2^-20, which every rounding to e4m3 takes to zero;
+//   - an infinite scale becomes p = 0, s = 1: finite values give their zero, infinite ones NaN.
 struct ExactDiv {
-  float s, r;
+  float p, s, r;
   __device__ __forceinline__ ExactDiv() {}
-  __device__ __forceinline__ explicit ExactDiv(float scale) : s(scale), r(1.f / scale) {}
-  __device__ __forceinline__ bool ok() const { return s >= 0x1p-60f && s <= 0x1p60f; }
+  __device__ __forceinline__ explicit ExactDiv(float scale) {
+    const bool inf = scale > 0x1.fffffep127f;
+    p = inf ? 0.f : scale > 0x1p60f ? 0x1p-100f : scale < 0x1p-60f ? 0x1p100f : 1.f;
+    s = inf ? 1.f : scale * p;
+    r = 1.f / s;
+  }
   __device__ __forceinline__ float operator()(float a) const {
-    const float q = __builtin_amdgcn_fmed3f(a * r, -0x1p20f, 0x1p20f);
-    return __builtin_copysignf(__builtin_fmaf(__builtin_fmaf(-q, s, a), r, q), a);
+    const float ap = a * p, q = __builtin_amdgcn_fmed3f(ap * r, -0x1p20f, 0x1p20f);
+    return __builtin_copysignf(__builtin_fmaf(__builtin_fmaf(-q, s, ap), r, q), a);
   }
 };
 
@@ -486,6 +492,7 @@ struct EpiPrune24F8 {
   static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
     LaneVec<MI> lb;
     lb.load(e.b1, m_lane, 0.f);
+    const ExactDiv by_sh(e.sh);
 #pragma unroll
     for (int ni = 0; ni < NI; ni++) {
       size_t t = (size_t)(n_lane + ni);
@@ -514,8 +521,8 @@ struct EpiPrune24F8 {
           uint32_t n4 = pick24_packed(hpk[2 * a], hpk[2 * a + 1], pair);
           pairs[a] = pair;
           int gi = 4 * mi + a;
-          float v0 = bf16_lo_to_f32(pair) / e.sh;
-          float v1 = bf16_hi_to_f32(pair) / e.sh;
+          float v0 = by_sh(bf16_lo_to_f32(pair));
+          float v1 = by_sh(bf16_hi_to_f32(pair));
           // group gi's two stored bytes are bytes 2 gi, 2 gi + 1 of the lane's 8 MI
           q8[gi >> 1] = cvt_e4m3x2(v0, v1, (gi & 1) ? q8[gi >> 1] : 0u, (gi & 1) != 0);
           nib[gi >> 3] |= n4 << (4 * (gi & 7));
@@ -541,6 +548,7 @@ struct EpiDGatherF8 {
   static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
     LaneSaved24<MI, NI> sv;
     sv.load(e.Hc16, e.meta16, e.F, m_lane, n_lane);
+    const ExactDiv by_sdz(e.sdz);
 #pragma unroll
     for (int ni = 0; ni < NI; ni++) {
       size_t t = (size_t)(n_lane + ni);
@@ -559,7 +567,7 @@ struct EpiDGatherF8 {
           float s1 = i1 == 3 ? x3 : (i1 == 2 ? x2 : x1);
           float g0 = 2.f * __builtin_amdgcn_sqrtf(bf16_lo_to_f32(h[a]));
           float g1 = 2.f * __builtin_amdgcn_sqrtf(bf16_hi_to_f32(h[a]));
-          float v0 = (s0 * e.scale * g0) / e.sdz, v1 = (s1 * e.scale * g1) / e.sdz;
+          float v0 = by_sdz(s0 * e.scale * g0), v1 = by_sdz(s1 * e.scale * g1);
           q8[gi >> 1] = cvt_e4m3x2(v0, v1, (gi & 1) ? q8[gi >> 1] : 0u, (gi & 1) != 0);
         }
       }
@@ -905,6 +913,7 @@ struct EpiRelu2F8 {
     LaneVec<MI> lb;
     lb.load(e.b1, m_lane, 0.f);
     uint32_t qs[NI][4 * MI];   // the lane's codes: [token][4 features per word]
+    const ExactDiv by_sh(e.sh);
 #pragma unroll
     for (int ni = 0; ni < NI; ni++) {
       uint8_t* row = e.H8 + a24_piece(n_lane + ni, m_lane >> 6, e.F >> 6) * 64 + (m_lane & 63);
@@ -917,7 +926,7 @@ struct EpiRelu2F8 {
           float r0 = fmaxf(acc[mi][ni][2 * d] * e.zscale + b0, 0.f);
           float r1 = fmaxf(acc[mi][ni][2 * d + 1] * e.zscale + b1v, 0.f);
           hp[d] = pack_bf16x2(r0 * r0, r1 * r1);
-          q[d >> 1] = cvt_e4m3x2(bf16_lo_to_f32(hp[d]) / e.sh, bf16_hi_to_f32(hp[d]) / e.sh, (d & 1) ? q[d >> 1] : 0u, (d & 1) != 0);
+          q[d >> 1] = cvt_e4m3x2(by_sh(bf16_lo_to_f32(hp[d])), by_sh(bf16_hi_to_f32(hp[d])), (d & 1) ? q[d >> 1] : 0u, (d & 1) != 0);
         }
         *reinterpret_cast<u32x4*>(row + 16 * mi) = u32x4{q[0], q[1], q[2], q[3]};
         if (e.H16) {
@@ -953,6 +962,7 @@ struct EpiDReluF8 {
   template <int MI, int NI>
   static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
     uint32_t qs[NI][4 * MI];
+    const ExactDiv by_sdz(e.sdz);
     LaneSavedDense<MI, NI> sv;
     sv.load(e.H16, e.F, m_lane, n_lane);
 #pragma unroll
@@ -968,7 +978,7 @@ struct EpiDReluF8 {
           for (int d = 0; d < 4; d++) {
             float g0 = 2.f * __builtin_amdgcn_sqrtf(bf16_lo_to_f32(h[d]));
             float g1 = 2.f * __builtin_amdgcn_sqrtf(bf16_hi_to_f32(h[d]));
-            float v0 = (acc[mi][ni][8 * hq + 2 * d] * e.scale * g0) / e.sdz, v1 = (acc[mi][ni][8 * hq + 2 * d + 1] * e.scale * g1) / e.sdz;
+            float v0 = by_sdz(acc[mi][ni][8 * hq + 2 * d] * e.scale * g0), v1 = by_sdz(acc[mi][ni][8 * hq + 2 * d + 1] * e.scale * g1);
             int dd = 4 * hq + d;
             q[dd >> 1] = cvt_e4m3x2(v0, v1, (dd & 1) ? q[dd >> 1] : 0u, (dd & 1) != 0);
           }

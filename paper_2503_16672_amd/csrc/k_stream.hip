@@ -47,19 +47,42 @@ __global__ void __launch_bounds__(256) sparsify24_kernel(const u32x4* __restrict
   }
 }
 
+// largest magnitudes of a bf16 vector, lane by lane of its 16-bit halves (sign cleared, as unsigned integers)
+typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
+__device__ __forceinline__ u16x8 max_mag(u16x8 m, u32x4 v) {
+  return __builtin_elementwise_max(m, __builtin_bit_cast(u16x8, v & u32x4{0x7FFF7FFFu, 0x7FFF7FFFu, 0x7FFF7FFFu, 0x7FFF7FFFu}));
+}
+__device__ __forceinline__ float scale_of_max(uint32_t word) {
+  const float mx = __builtin_bit_cast(float, word << 16);
+  return mx > 0.f ? mx / 448.f : 1.f;
+}
+
+// 8 bf16 values -> 8 codes, value j divided by d[j] (or all by the one divider)
+template <int N>
+__device__ __forceinline__ u32x2 quantise8(u32x4 v, const ExactDiv (&d)[N]) {
+  uint32_t q[2];
+#pragma unroll
+  for (int i = 0; i < 2; i++) {
+    const int j = 4 * i;
+    q[i] = cvt_e4m3x2(d[j % N](bf16_lo_to_f32(v[2 * i])), d[(j + 1) % N](bf16_hi_to_f32(v[2 * i])), 0u, false);
+    q[i] = cvt_e4m3x2(d[(j + 2) % N](bf16_lo_to_f32(v[2 * i + 1])), d[(j + 3) % N](bf16_hi_to_f32(v[2 * i + 1])), q[i], true);
+  }
+  return u32x2{q[0], q[1]};
+}
 // Standalone activation-side kernel of Sec. 2 (sparsification and FP8 quantisation in one pass): the pick is made on the
 // bf16 words exactly as above, the two kept values of each group are then quantised, e4m3(kept / scale), saturating.
 // Per work item 8 elements: one 16-byte load, 4 code bytes, one metadata byte (2.625 bytes per element in all).
 __global__ void __launch_bounds__(256) sparsify24_quant_kernel(const u32x4* __restrict__ in, int64_t n_oct, float scale,
                                                                uint32_t* __restrict__ vals8, uint8_t* __restrict__ meta) {
+  const ExactDiv by_scale(scale);
   int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; o < n_oct; o += stride) {
     u32x4 v = ld_stream(in + o);
     uint32_t p0, p1;
     uint32_t n0 = pick24_words(v[0] & 0xFFFFu, v[0] >> 16, v[1] & 0xFFFFu, v[1] >> 16, p0);
     uint32_t n1 = pick24_words(v[2] & 0xFFFFu, v[2] >> 16, v[3] & 0xFFFFu, v[3] >> 16, p1);
-    uint32_t q = cvt_e4m3x2(bf16_lo_to_f32(p0) / scale, bf16_hi_to_f32(p0) / scale, 0u, false);
-    q = cvt_e4m3x2(bf16_lo_to_f32(p1) / scale, bf16_hi_to_f32(p1) / scale, q, true);
+    uint32_t q = cvt_e4m3x2(by_scale(bf16_lo_to_f32(p0)), by_scale(bf16_hi_to_f32(p0)), 0u, false);
+    q = cvt_e4m3x2(by_scale(bf16_lo_to_f32(p1)), by_scale(bf16_hi_to_f32(p1)), q, true);
     st_stream(vals8 + o, q);
     st_stream(meta + o, (uint8_t)(n0 | (n1 << 4)));
   }
@@ -843,9 +866,9 @@ __global__ void __launch_bounds__(256) quantise_rows_kernel(const u32x4* __restr
     int tl = (int)(i & 255);
     size_t blk = i >> 8;
     int j = (int)(blk % np8), t = (int)(blk / np8) * 256 + tl;
-    float mxv = __builtin_bit_cast(float, rowmax[t] << 16);
-    float s = mxv > 0.f ? mxv / 448.f : 1.f;
+    const float s = scale_of_max(rowmax[t]);
     if (j == 0) sh[t] = s;
+    const ExactDiv d[1] = {ExactDiv(s)};
     u32x4 out[4];
     u32x2 mo[2];
 #pragma unroll
@@ -854,13 +877,9 @@ __global__ void __launch_bounds__(256) quantise_rows_kernel(const u32x4* __restr
       mo[hlf] = meta16[pin];
 #pragma unroll
       for (int c = 0; c < 4; c++) {
-        u32x4 v = Hc16[pin * 4 + c];                      // 8 bf16 values -> 8 codes = 2 dwords
-        uint32_t q0 = cvt_e4m3x2(bf16_lo_to_f32(v[0]) / s, bf16_hi_to_f32(v[0]) / s, 0u, false);
-        q0 = cvt_e4m3x2(bf16_lo_to_f32(v[1]) / s, bf16_hi_to_f32(v[1]) / s, q0, true);
-        uint32_t q1 = cvt_e4m3x2(bf16_lo_to_f32(v[2]) / s, bf16_hi_to_f32(v[2]) / s, 0u, false);
-        q1 = cvt_e4m3x2(bf16_lo_to_f32(v[3]) / s, bf16_hi_to_f32(v[3]) / s, q1, true);
-        out[2 * hlf + (c >> 1)][2 * (c & 1)] = q0;
-        out[2 * hlf + (c >> 1)][2 * (c & 1) + 1] = q1;
+        const u32x2 q = quantise8(Hc16[pin * 4 + c], d);  // 8 bf16 values -> 8 codes = 2 dwords
+        out[2 * hlf + (c >> 1)][2 * (c & 1)] = q[0];
+        out[2 * hlf + (c >> 1)][2 * (c & 1) + 1] = q[1];
       }
     }
 #pragma unroll
@@ -880,23 +899,16 @@ __global__ void __launch_bounds__(256) quantise_rows_dense_kernel(const u32x4* _
     int tl = (int)(i & 255);
     size_t blk = i >> 8;
     int j = (int)(blk % np8), t = (int)(blk / np8) * 256 + tl;
-    float mxv = __builtin_bit_cast(float, rowmax[t] << 16);
-    float s = mxv > 0.f ? mxv / 448.f : 1.f;
+    const float s = scale_of_max(rowmax[t]);
     if (j == 0) sh[t] = s;
+    const ExactDiv div[1] = {ExactDiv(s)};
 #pragma unroll
     for (int hlf = 0; hlf < 2; hlf++) {
       size_t pin = a24_piece(t, 2 * j + hlf, F >> 5);
 #pragma unroll
       for (int c = 0; c < 2; c++) {                       // 16 bf16 values -> 16 codes
-        u32x4 v0 = H16[pin * 4 + 2 * c], v1 = H16[pin * 4 + 2 * c + 1];
-        u32x4 o;
-#pragma unroll
-        for (int d = 0; d < 2; d++) {
-          uint32_t q = cvt_e4m3x2(bf16_lo_to_f32(v0[2 * d]) / s, bf16_hi_to_f32(v0[2 * d]) / s, 0u, false);
-          o[d] = cvt_e4m3x2(bf16_lo_to_f32(v0[2 * d + 1]) / s, bf16_hi_to_f32(v0[2 * d + 1]) / s, q, true);
-          q = cvt_e4m3x2(bf16_lo_to_f32(v1[2 * d]) / s, bf16_hi_to_f32(v1[2 * d]) / s, 0u, false);
-          o[2 + d] = cvt_e4m3x2(bf16_lo_to_f32(v1[2 * d + 1]) / s, bf16_hi_to_f32(v1[2 * d + 1]) / s, q, true);
-        }
+        const u32x2 lo = quantise8(H16[pin * 4 + 2 * c], div), hi = quantise8(H16[pin * 4 + 2 * c + 1], div);
+        const u32x4 o = {lo[0], lo[1], hi[0], hi[1]};
         H8[i * 4 + 2 * hlf + c] = o;
       }
     }
@@ -953,41 +965,6 @@ int launch_quantise_rows(const void* Hc16, const uint8_t* meta16, const uint32_t
 // GEMMs; Sec. 2 of the paper: FP8 row-wise scaling).  scale = (largest magnitude of the row or column) / 448, 1 if that is
 // zero; codes = e4m3(x / scale), row-major [R][C].
 
-// largest magnitudes of a bf16 vector, lane by lane of its 16-bit halves (sign cleared, as unsigned integers)
-typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
-__device__ __forceinline__ u16x8 max_mag(u16x8 m, u32x4 v) {
-  return __builtin_elementwise_max(m, __builtin_bit_cast(u16x8, v & u32x4{0x7FFF7FFFu, 0x7FFF7FFFu, 0x7FFF7FFFu, 0x7FFF7FFFu}));
-}
-__device__ __forceinline__ float scale_of_max(uint32_t word) {
-  const float mx = __builtin_bit_cast(float, word << 16);
-  return mx > 0.f ? mx / 448.f : 1.f;
-}
-
-// 8 bf16 values -> 8 codes, value j divided by d[j] (or all by the one divider)
-template <int N>
-__device__ __forceinline__ u32x2 quantise8(u32x4 v, const ExactDiv (&d)[N]) {
-  uint32_t q[2];
-#pragma unroll
-  for (int i = 0; i < 2; i++) {
-    const int j = 4 * i;
-    q[i] = cvt_e4m3x2(d[j % N](bf16_lo_to_f32(v[2 * i])), d[(j + 1) % N](bf16_hi_to_f32(v[2 * i])), 0u, false);
-    q[i] = cvt_e4m3x2(d[(j + 2) % N](bf16_lo_to_f32(v[2 * i + 1])), d[(j + 3) % N](bf16_hi_to_f32(v[2 * i + 1])), q[i], true);
-  }
-  return u32x2{q[0], q[1]};
-}
-// the same with the division instruction sequence, for scales that ExactDiv does not take
-template <int N>
-__device__ __forceinline__ u32x2 quantise8_ieee(u32x4 v, const ExactDiv (&d)[N]) {
-  uint32_t q[2];
-#pragma unroll
-  for (int i = 0; i < 2; i++) {
-    const int j = 4 * i;
-    q[i] = cvt_e4m3x2(bf16_lo_to_f32(v[2 * i]) / d[j % N].s, bf16_hi_to_f32(v[2 * i]) / d[(j + 1) % N].s, 0u, false);
-    q[i] = cvt_e4m3x2(bf16_lo_to_f32(v[2 * i + 1]) / d[(j + 2) % N].s, bf16_hi_to_f32(v[2 * i + 1]) / d[(j + 3) % N].s, q[i], true);
-  }
-  return u32x2{q[0], q[1]};
-}
-
 // Per row, the whole row held in registers between the maximum and the quantisation: LANES work items per row (a wave, or the workgroup
 // for rows beyond 4096 values), up to NV 16-byte pieces each, all requested before the first is used.
 template <int LANES, int NV>
@@ -1021,11 +998,10 @@ __global__ void __launch_bounds__(256) quantise_bf16_rows_kernel(const u32x4* __
   if (t == 0) scales[r] = s;
   const ExactDiv d[1] = {ExactDiv(s)};
   u32x2* out = codes + r * C8;
-  const bool ok = d[0].ok();
 #pragma unroll
   for (int i = 0; i < NV; i++) {
     const int c = t + LANES * i;
-    if (c < C8) st_stream(out + c, ok ? quantise8(v[i], d) : quantise8_ieee(v[i], d));
+    if (c < C8) st_stream(out + c, quantise8(v[i], d));
   }
 }
 
@@ -1047,7 +1023,7 @@ __global__ void __launch_bounds__(256) quantise_bf16_long_rows_kernel(const u32x
   if (lane == 0) scales[r] = s;
   const ExactDiv d[1] = {ExactDiv(s)};
   u32x2* out = codes + r * C8;
-  for (int c = lane; c < C8; c += 64) st_stream(out + c, d[0].ok() ? quantise8(row[c], d) : quantise8_ieee(row[c], d));
+  for (int c = lane; c < C8; c += 64) st_stream(out + c, quantise8(row[c], d));
 }
 
 // Per column, three kernels: (1) the largest magnitude words of every column over slabs of rows, (2) their maximum over the slabs and the
@@ -1117,13 +1093,12 @@ __global__ void __launch_bounds__(256) quantise_bf16_cols_kernel(const u32x4* __
     v[i] = ld_stream(X + (r < R ? r : rb) * C8 + c);
   }
   ExactDiv d[8];
-  bool ok = true;
 #pragma unroll
-  for (int j = 0; j < 8; j++) { d[j] = ExactDiv(scales[8 * c + j]); ok = ok && d[j].ok(); }
+  for (int j = 0; j < 8; j++) d[j] = ExactDiv(scales[8 * c + j]);
 #pragma unroll
   for (int i = 0; i < QC_UNROLL; i++) {
     const int64_t r = rb + 4 * i;
-    if (r < R) st_stream(codes + r * C8 + c, ok ? quantise8(v[i], d) : quantise8_ieee(v[i], d));
+    if (r < R) st_stream(codes + r * C8 + c, quantise8(v[i], d));
   }
 }
 
