@@ -599,6 +599,25 @@ struct EpiColMajorScaled {
   }
 };
 
+// Row maxima of a launch: rowmax[t] is raised to the largest bf16 magnitude word of row t.  A token row spans F / (16 MI) lanes of the
+// launch, and one atomic for each of them was the larger part of the row-wise epilogues (T = F = 8192: a million atomics, 15 us of the
+// dH GEMM's 157 with 256 x 256 tiles and 40 of 167 with 256 x 128).  So the two lane halves, which hold the same tokens, are
+// combined first, and what is already there is looked at before: the values are requested when the epilogue starts, and an atomic
+// goes out only where it would raise one -- about ln(n) of n contributions.  A value that is out of date is lower and only costs an
+// atomic.
+template <int NI>
+struct RowMax {
+  uint32_t seen[NI];
+  __device__ __forceinline__ void load(const uint32_t* rowmax, int n_lane) {
+#pragma unroll
+    for (int ni = 0; ni < NI; ni++) seen[ni] = __hip_atomic_load(rowmax + n_lane + ni, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ void raise(uint32_t* rowmax, int n_lane, int ni, uint32_t mx) const {
+    mx = max(mx, (uint32_t)__shfl_xor((int)mx, 32, 64));
+    if ((threadIdx.x & 32) == 0 && mx > seen[ni]) atomicMax(rowmax + n_lane + ni, mx);
+  }
+};
+
 // fp8 up-projection with ROW-WISE scaling (the paper's precision recipe, Sec. 2: "FP8 rowwise scaling"): the
 // activation operand carries one scale per token, the weight one per output channel:
 //   z = sx[t] sw1[f] acc + b1[f];  h = bf16(max(0, z)^2);  keep-2-of-4 as in EpiPrune24.
@@ -615,6 +634,8 @@ struct EpiPrune24RwT {
     uint32_t cnt[4 * MI];
 #pragma unroll
     for (int i = 0; i < 4 * MI; i++) cnt[i] = 0u;
+    RowMax<NI> rm;
+    rm.load(e.rowmax, n_lane);
     LaneVec<MI> lb, lw;
     lb.load(e.b1, m_lane, 0.f);
     lw.load(e.sw1, m_lane, 1.f);
@@ -657,7 +678,7 @@ struct EpiPrune24RwT {
       for (int q = 0; q < MI; q++)
         *reinterpret_cast<u32x4*>(hrow + 8 * q) = u32x4{vals[4 * q], vals[4 * q + 1], vals[4 * q + 2], vals[4 * q + 3]};
       st_nibbles<MI>(e.meta + piece * 8 + ((m_lane & 63) >> 3), nib);
-      if (mx) atomicMax(e.rowmax + t, mx);
+      rm.raise(e.rowmax, n_lane, ni, mx);
     }
     if constexpr (STATS) nnz_flush<MI>(cnt, e.nnz, m_lane);
   }
@@ -674,6 +695,8 @@ struct EpiRelu2Rw {
   struct Args { __bf16* H16; const float* b1; int F; const float* sx; const float* sw1; uint32_t* rowmax; __bf16* Ht16; int T; };
   template <int MI, int NI>
   static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+    RowMax<NI> rm;
+    rm.load(e.rowmax, n_lane);
     LaneVec<MI> lb, lw;
     lb.load(e.b1, m_lane, 0.f);
     lw.load(e.sw1, m_lane, 1.f);
@@ -715,7 +738,7 @@ struct EpiRelu2Rw {
       }
     }
 #pragma unroll
-    for (int ni = 0; ni < NI; ni++) if (mx[ni]) atomicMax(e.rowmax + n_lane + ni, mx[ni]);
+    for (int ni = 0; ni < NI; ni++) rm.raise(e.rowmax, n_lane, ni, mx[ni]);
   }
 };
 
@@ -727,6 +750,8 @@ struct EpiDReluRw {
   struct Args { const __bf16* H16; __bf16* dZ16; __bf16* dZt16; int F; int T; const float* rs; const float* cs; uint32_t* rowmax; };
   template <int MI, int NI>
   static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+    RowMax<NI> rm;
+    rm.load(e.rowmax, n_lane);
     LaneVec<MI> lr;
     lr.load(e.rs, m_lane, 1.f);
     uint32_t mx[NI] = {};
@@ -767,7 +792,7 @@ struct EpiDReluRw {
       }
     }
 #pragma unroll
-    for (int ni = 0; ni < NI; ni++) if (mx[ni]) atomicMax(e.rowmax + n_lane + ni, mx[ni]);
+    for (int ni = 0; ni < NI; ni++) rm.raise(e.rowmax, n_lane, ni, mx[ni]);
   }
 };
 
@@ -861,6 +886,8 @@ struct EpiDGatherRw {
   struct Args { const __bf16* Hc16; const uint8_t* meta16; __bf16* dZc16; int F; const float* rs; const float* cs; uint32_t* rowmax; };
   template <int MI, int NI>
   static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+    RowMax<NI> rm;
+    rm.load(e.rowmax, n_lane);
     LaneVec<MI> lr;
     lr.load(e.rs, m_lane, 1.f);
     LaneSaved24<MI, NI> sv;
@@ -896,7 +923,7 @@ struct EpiDGatherRw {
         }
         *reinterpret_cast<u32x4*>(zrow + 8 * mi) = z;
       }
-      if (mx) atomicMax(e.rowmax + t, mx);
+      rm.raise(e.rowmax, n_lane, ni, mx);
     }
   }
 };

@@ -119,7 +119,7 @@ __host__ __device__ __forceinline__ size_t a24_piece(int r, int kp, int npanels)
 // when it has one.  Sparse 256 x 128 has room for two stages a workgroup only, and those expose the memory latency (112 us; 81 us with
 // four stages and the CU to itself).
 constexpr int ring_depth(bool sparse, bool f8, int mi, int ni) {
-  return mi * ni == 16 ? (sparse ? 3 : 4) : mi * ni == 8 ? (sparse || f8 ? 4 : 3) : mi * ni == 4 ? (sparse ? 3 : 4) : mi * ni == 2 ? 4 : 6;
+  return mi * ni == 16 ? (sparse ? 3 : 4) : mi * ni == 8 ? (sparse ? 4 : 3) : mi * ni == 4 ? (sparse ? 3 : 4) : mi * ni == 2 ? 4 : 6;
 }
 
 // Stage geometry.  Everything is laid out in bytes, and an fp8 kernel has exactly the byte geometry of its bf16
@@ -591,7 +591,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
     // one barrier at the end of the stage.  Two fragment sets alternate.
     FragD<MI, NI> fr[2][2];
     constexpr int NF = MI + NI;
-    static_assert(NB % 2 == 0, "the stages are walked in pairs");
     static_for<NF>([&](auto I) { load_frag_dense1<G, 0, I, PROBE>(smem, L, fr[0][0]); });
     static_for<NF>([&](auto I) { load_frag_dense1<G, 1, I, PROBE>(smem, L, fr[0][1]); });
     auto stage = [&](int kt, char* cur, char* nxt, auto par, auto mode) {
@@ -631,7 +630,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
     using P0 = std::integral_constant<int, 0>; using P1 = std::integral_constant<int, 1>;
     using M0 = std::integral_constant<int, 0>; using M1 = std::integral_constant<int, 1>; using M2 = std::integral_constant<int, 2>;
     int kt = 0;
-    for (; kt < nk - NB; kt += 2) { advance(kt, P0{}, M0{}); advance(kt + 1, P1{}, M0{}); }
+    for (; kt + 1 < nk - NB; kt += 2) { advance(kt, P0{}, M0{}); advance(kt + 1, P1{}, M0{}); }
+    if (NB % 2 != 0 && kt < nk - NB) { advance(kt, P0{}, M0{}); advance(kt + 1, P1{}, M1{}); kt += 2; }
     for (; kt < nk - 2; kt += 2) { advance(kt, P0{}, M1{}); advance(kt + 1, P1{}, M1{}); }
     advance(kt, P0{}, M1{});
     advance(kt + 1, P1{}, M2{});

@@ -15,7 +15,7 @@ namespace ffn24 {
 // up-projection T 1280 D 768 F 3072 29 -> 15 (128 x 128).  A stage of an fp8 kernel holds twice the k in the same bytes and time.
 struct TileCost { int mi, ni, per_k, fixed; };   // 0.1 ns per (bf16) k; ns per tile
 constexpr TileCost TILES_SPARSE[] = {{4, 4, 140, 6000}, {4, 2, 92, 5000}, {2, 2, 57, 3000}, {2, 1, 39, 2000}, {1, 1, 26, 1500}};
-constexpr TileCost TILES_DENSE[] = {{4, 4, 205, 19000}, {4, 2, 125, 8000}, {2, 2, 74, 3500}, {2, 1, 52, 2000}, {1, 1, 34, 1000}};
+constexpr TileCost TILES_DENSE[] = {{4, 4, 205, 19000}, {4, 2, 125, 5000}, {2, 2, 74, 2500}, {2, 1, 52, 2000}, {1, 1, 34, 1000}};
 constexpr int NUM_TILES = 5;   // the two tables list the same tiles
 constexpr long long CHIP_CUS = 256;
 
