@@ -849,70 +849,32 @@ int launch_featurewise24_f8(const void* Hc8, const uint8_t* meta, const void* dZ
   return (int)hipGetLastError();
 }
 
-// Row-wise fp8 quantisation of the compressed activation (Sec. 2 describes one kernel for activation, sparsification
+// Row-wise fp8 quantisation of an operand in panel form (Sec. 2 describes one kernel for activation, sparsification
 // and FP8 quantisation; here only the last step is left to a kernel of its own, because the scale of a token row,
 // sh[t] = (largest activation of the row) / 448, is known only once the whole row exists).
-// Input: bf16 kept values + metadata in the bf16 panel form (64-byte / 8-byte pieces per 64 features);
-// output: e4m3 codes + metadata in the fp8 panel form (64-byte / 16-byte pieces per 128 features), and sh [T].
-// One work item per (token, 128 features): two input pieces -> one output piece.
-__global__ void __launch_bounds__(256) quantise_rows_kernel(const u32x4* __restrict__ Hc16, const u32x2* __restrict__ meta16,
-                                                            const uint32_t* __restrict__ rowmax, int T, int F,
-                                                            u32x4* __restrict__ Hc8, u32x4* __restrict__ meta8, float* __restrict__ sh) {
-  const int np8 = F >> 7;                                 // output pieces per token
-  size_t n = (size_t)T * np8;
-  size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-    // item order = output piece order: ((t / 256) * np8 + j) * 256 + t % 256
-    int tl = (int)(i & 255);
-    size_t blk = i >> 8;
-    int j = (int)(blk % np8), t = (int)(blk / np8) * 256 + tl;
-    const float s = scale_of_max(rowmax[t]);
-    if (j == 0) sh[t] = s;
-    const ExactDiv d[1] = {ExactDiv(s)};
-    u32x4 out[4];
-    u32x2 mo[2];
-#pragma unroll
-    for (int hlf = 0; hlf < 2; hlf++) {
-      size_t pin = a24_piece(t, 2 * j + hlf, F >> 6);
-      mo[hlf] = meta16[pin];
-#pragma unroll
-      for (int c = 0; c < 4; c++) {
-        const u32x2 q = quantise8(Hc16[pin * 4 + c], d);  // 8 bf16 values -> 8 codes = 2 dwords
-        out[2 * hlf + (c >> 1)][2 * (c & 1)] = q[0];
-        out[2 * hlf + (c >> 1)][2 * (c & 1) + 1] = q[1];
-      }
-    }
-#pragma unroll
-    for (int c = 0; c < 4; c++) Hc8[i * 4 + c] = out[c];
-    meta8[i] = u32x4{mo[0][0], mo[0][1], mo[1][0], mo[1][1]};
-  }
-}
-
-// The same for the dense baseline: bf16 [T][F] in dense panel form (64-byte pieces of 32 features) -> e4m3 [T][F] in the
-// dense fp8 panel form (64-byte pieces of 64 features).  One work item per (token, 64 features).
-__global__ void __launch_bounds__(256) quantise_rows_dense_kernel(const u32x4* __restrict__ H16, const uint32_t* __restrict__ rowmax,
-                                                                  int T, int F, u32x4* __restrict__ H8, float* __restrict__ sh) {
-  const int np8 = F >> 6;                                 // output pieces per token
-  size_t n = (size_t)T * np8;
-  size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-    int tl = (int)(i & 255);
-    size_t blk = i >> 8;
-    int j = (int)(blk % np8), t = (int)(blk / np8) * 256 + tl;
-    const float s = scale_of_max(rowmax[t]);
-    if (j == 0) sh[t] = s;
-    const ExactDiv div[1] = {ExactDiv(s)};
-#pragma unroll
-    for (int hlf = 0; hlf < 2; hlf++) {
-      size_t pin = a24_piece(t, 2 * j + hlf, F >> 5);
-#pragma unroll
-      for (int c = 0; c < 2; c++) {                       // 16 bf16 values -> 16 codes
-        const u32x2 lo = quantise8(H16[pin * 4 + 2 * c], div), hi = quantise8(H16[pin * 4 + 2 * c + 1], div);
-        const u32x4 o = {lo[0], lo[1], hi[0], hi[1]};
-        H8[i * 4 + 2 * hlf + c] = o;
-      }
-    }
-  }
+// Compressed (META): bf16 kept values + metadata, 64-byte / 8-byte pieces per 64 features, become e4m3 codes + metadata, 64-byte /
+// 16-byte pieces per 128 features.  Dense: bf16 pieces of 32 features become e4m3 pieces of 64.  Either way two input pieces of a
+// row, one panel (256 pieces) apart, make one output piece, and sh [T] is written.
+// HBM-bound (3.375 bytes per stored value compressed, 3 dense).  Four neighbouring lanes take a row's piece, 16 bytes each, so that
+// a wave reads whole contiguous kilobytes; a lane's 8 codes of either input piece are exchanged with its neighbour's, so that each
+// stores 16 bytes and the wave a contiguous kilobyte again.  One output piece per lane and workgroups in memory order (a
+// quarter of a block of 256 rows each, then the next panel).  The stores are plain: the next kernel reads the codes.
+template <bool META>
+__global__ void __launch_bounds__(256) quantise_rows_kernel(const u32x4* __restrict__ H16, const u32x2* __restrict__ meta16,
+                                                            const uint32_t* __restrict__ rowmax, int np8, u32x4* __restrict__ H8,
+                                                            u32x2* __restrict__ meta8, float* __restrict__ sh) {
+  const int c = threadIdx.x & 3, j = blockIdx.x >> 2, t = blockIdx.y * 256 + 64 * (blockIdx.x & 3) + (threadIdx.x >> 2);
+  const size_t pin = a24_piece(t, 2 * j, 2 * np8), pout = a24_piece(t, j, np8);
+  const u32x4 v0 = ld_stream(H16 + pin * 4 + c), v1 = ld_stream(H16 + (pin + 256) * 4 + c);
+  if (META && c < 2) meta8[pout * 2 + c] = ld_stream(meta16 + pin + 256 * c);
+  const float s = scale_of_max(rowmax[t]);
+  if (j == 0 && c == 0) sh[t] = s;
+  const ExactDiv d[1] = {ExactDiv(s)};
+  const u32x2 q0 = quantise8(v0, d), q1 = quantise8(v1, d);
+  const bool odd = c & 1;                              // even lanes store of the first input piece, odd ones of the second
+  const u32x2 keep = odd ? q1 : q0, send = odd ? q0 : q1;
+  const uint32_t r0 = (uint32_t)__shfl_xor((int)send[0], 1, 64), r1 = (uint32_t)__shfl_xor((int)send[1], 1, 64);
+  H8[pout * 4 + 2 * odd + (c >> 1)] = odd ? u32x4{r0, r1, keep[0], keep[1]} : u32x4{keep[0], keep[1], r0, r1};
 }
 
 // Largest magnitude word of every row of a bf16 matrix [R][C] in dense panel form (64-byte pieces of 32 k): rmax[r] is raised
@@ -943,21 +905,19 @@ int launch_rowmax_dense(const void* X16, int R, int C, uint32_t* rmax, hipStream
 }
 
 int launch_quantise_rows_dense(const void* H16, const uint32_t* rowmax, int T, int F, void* H8, float* sh, hipStream_t s) {
-  size_t n = (size_t)T * (F >> 6);
-  size_t blocks = (n + 255) / 256;
-  if (blocks > 256 * 64) blocks = 256 * 64;   // (here the grid-stride walk with plain accesses is the faster shape: 4.8 against 3.0 TB/s)
-  hipLaunchKernelGGL(quantise_rows_dense_kernel, dim3((unsigned)blocks), dim3(256), 0, s, static_cast<const u32x4*>(H16), rowmax, T, F,
-                     static_cast<u32x4*>(H8), sh);
+  const int np8 = F >> 6;
+  hipLaunchKernelGGL(quantise_rows_kernel<false>, dim3((unsigned)(4 * np8), (unsigned)(T / 256)), dim3(256), 0, s,
+                     static_cast<const u32x4*>(H16), static_cast<const u32x2*>(nullptr), rowmax, np8, static_cast<u32x4*>(H8),
+                     static_cast<u32x2*>(nullptr), sh);
   return (int)hipGetLastError();
 }
 
 int launch_quantise_rows(const void* Hc16, const uint8_t* meta16, const uint32_t* rowmax, int T, int F, void* Hc8, uint8_t* meta8, float* sh,
                          hipStream_t s) {
-  size_t n = (size_t)T * (F >> 7);
-  size_t blocks = (n + 255) / 256;
-  if (blocks > 256 * 64) blocks = 256 * 64;
-  hipLaunchKernelGGL(quantise_rows_kernel, dim3((unsigned)blocks), dim3(256), 0, s, static_cast<const u32x4*>(Hc16),
-                     reinterpret_cast<const u32x2*>(meta16), rowmax, T, F, static_cast<u32x4*>(Hc8), reinterpret_cast<u32x4*>(meta8), sh);
+  const int np8 = F >> 7;
+  hipLaunchKernelGGL(quantise_rows_kernel<true>, dim3((unsigned)(4 * np8), (unsigned)(T / 256)), dim3(256), 0, s,
+                     static_cast<const u32x4*>(Hc16), reinterpret_cast<const u32x2*>(meta16), rowmax, np8, static_cast<u32x4*>(Hc8),
+                     reinterpret_cast<u32x2*>(meta8), sh);
   return (int)hipGetLastError();
 }
 
