@@ -138,15 +138,7 @@ int tele_snapshot(ffn24_ctx* c, long long path, hipStream_t s) {
 int weight_pass(ffn24_ctx* c, const void* W1, const void* W2, hipStream_t s) {
   int D = (int)c->D, F = (int)c->F;
   Timed t(c, K_TR_W, s);
-  int rc1;
-  if (c->f8) {
-    rc1 = launch_transpose8(W1, D, F, c->W1t, 1, c->W1p, 1, s);
-    if (!rc1) rc1 = launch_transpose8(W2, F, D, c->W2t, 2, c->W2p, 0, s);
-  } else {
-    rc1 = launch_transpose(W1, D, F, c->W1t, 1, c->W1p, 1, nullptr, s);
-    if (!rc1) rc1 = launch_transpose(W2, F, D, c->W2t, 2, c->W2p, 0, nullptr, s);
-  }
-  return t.done(rc1) ? FFN24_ERR_HIP : FFN24_OK;
+  return t.done((c->f8 ? launch_transpose8_weights : launch_transpose_weights)(W1, W2, D, F, c->W1t, c->W1p, c->W2t, c->W2p, s)) ? FFN24_ERR_HIP : FFN24_OK;
 }
 
 // Weights of a forward call: both given (run the weight pass; prepared copies are gone after it), or both NULL (use
@@ -634,8 +626,7 @@ int ffn24_fwd_static(const void* X, const void* W1, const float* b1, const void*
   unsigned char* W2t = W1t + 2 * df;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int Ti = (int)T, Di = (int)D, Fi = (int)F;
-  if (launch_transpose(W1, Di, Fi, W1t, 1, nullptr, 0, nullptr, s)) return FFN24_ERR_HIP;
-  if (launch_transpose(W2, Fi, Di, W2t, 2, nullptr, 0, nullptr, s)) return FFN24_ERR_HIP;
+  if (launch_transpose_weights(W1, W2, Di, Fi, W1t, nullptr, W2t, nullptr, s)) return FFN24_ERR_HIP;
   if (launch_up_prune24(W1t, X, b1, Ti, Di, Fi, Hc, meta, nullptr, nullptr, nullptr, nullptr, s)) return FFN24_ERR_HIP;
   if (launch_sp_rowmajor(Hc, meta, 1, W2t, 1, Ti, Di, Fi, Y, s)) return FFN24_ERR_HIP;
   return FFN24_OK;
@@ -684,13 +675,12 @@ int ffn24_bwd_rowwise(ffn24_ctx* c, const ffn24_rowwise_bwd_operands* op, void* 
       if (!rc1) rc1 = launch_quantise_rows_dense(c->Hdn_t, c->hmax + ns, nd, T, c->Hdn8_t, c->sh_f + ns, s);
       if (t.done(rc1 ? rc1 : launch_quantise_rows_dense(c->dZdn_t, c->zmax + ns, nd, T, c->dZdn8_t, c->sdz_f + ns, s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_TR_ACT, s);
-      int rc1 = launch_transpose8_rows(op->dY8c, T, D, c->dYt, 2, perm, s);
-      if (t.done(rc1 ? rc1 : launch_transpose8_rows(op->X8c, T, D, c->Xt, 2, perm, s))) return FFN24_ERR_HIP; }
+      if (t.done(launch_transpose8_acts(op->dY8c, op->X8c, T, D, c->dYt, nullptr, c->Xt, perm, s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_DW2, s);
       if (t.done(launch_split_wgrad_f8_rowwise(c->Hc_t, c->meta_t, ns, c->Hdn8_t, nd, c->dYt, D, T, c->sh_f, op->sdy_d, dW2, D, c->feat_of_row, s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_DW1, s);
       if (t.done(launch_split_wgrad_f8_rowwise(c->dZc_t, c->meta_t, ns, c->dZdn8_t, nd, c->Xt, D, T, c->sdz_f, op->sx_d, c->dW1t, D, c->feat_of_row, s))) return FFN24_ERR_HIP; }
-    { Timed t(c, K_TR_DW1, s); if (t.done(launch_transpose(c->dW1t, F, D, dW1, 0, nullptr, 0, nullptr, s))) return FFN24_ERR_HIP; }
+    { Timed t(c, K_TR_DW1, s); if (t.done(launch_transpose(c->dW1t, F, D, dW1, s))) return FFN24_ERR_HIP; }
     return FFN24_OK;
   }
   { Timed t(c, K_FW, s);
@@ -699,8 +689,7 @@ int ffn24_bwd_rowwise(ffn24_ctx* c, const ffn24_rowwise_bwd_operands* op, void* 
     int rc1 = launch_quantise_rows(c->Hct16, c->meta_t16, c->hmax, F, T, c->Hc_t, c->meta_t, c->sh_f, s);
     if (t.done(rc1 ? rc1 : launch_quantise_rows(c->dZct16, c->meta_t16, c->zmax, F, T, c->dZc_t, c->meta_t, c->sdz_f, s))) return FFN24_ERR_HIP; }
   { Timed t(c, K_TR_ACT, s);
-    int rc1 = launch_transpose8_rows(op->dY8c, T, D, c->dYt, 2, perm, s);
-    if (t.done(rc1 ? rc1 : launch_transpose8_rows(op->X8c, T, D, c->Xt, 2, perm, s))) return FFN24_ERR_HIP; }
+    if (t.done(launch_transpose8_acts(op->dY8c, op->X8c, T, D, c->dYt, nullptr, c->Xt, perm, s))) return FFN24_ERR_HIP; }
   { Timed t(c, K_DW2, s);
     if (t.done(launch_sp_rowmajor_f8_rowwise(c->Hc_t, c->meta_t, c->dYt, 1, F, D, T, c->sh_f, op->sdy_d, dW2, s))) return FFN24_ERR_HIP; }
   { Timed t(c, K_DW1, s);
@@ -721,8 +710,7 @@ int ffn24_bwd(ffn24_ctx* c, const void* dY, void* dX, void* dW1, void* dW2, void
   if (c->f8) {
     // fp8 backward (per-tensor scales): every GEMM operand is e4m3, the gradients come out in bf16
     { Timed t(c, K_TR_ACT, s);   // dY^T for the dW2 GEMM first: the same pass leaves dY8 in panel form for the dH GEMM
-      int rc1 = launch_transpose8(dY, T, D, c->dYt, 2, c->dYp8, 1, s);
-      if (t.done(rc1 ? rc1 : launch_transpose8(c->X, T, D, c->Xt, 2, nullptr, 0, s))) return FFN24_ERR_HIP; }
+      if (t.done(launch_transpose8_acts(dY, c->X, T, D, c->dYt, c->dYp8, c->Xt, nullptr, s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_DH, s);
       if (t.done(launch_dh_gather_f8(c->W2p, c->dYp8, c->Hc16, c->meta16, T, D, F, c->sdy * c->sw2, c->sdz, c->dZc, s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_DX, s);
@@ -753,18 +741,16 @@ int ffn24_bwd(ffn24_ctx* c, const void* dY, void* dX, void* dW1, void* dW2, void
         return FFN24_ERR_HIP; }
     if (c->tele && (rc = tele_snapshot(c, 1, s))) return rc;
     { Timed t(c, K_TR_ACT, s);
-      int rc1 = launch_transpose(dY, T, D, c->dYt, 2, nullptr, 0, perm, s);
-      if (t.done(rc1 ? rc1 : launch_transpose(c->X, T, D, c->Xt, 2, nullptr, 0, perm, s))) return FFN24_ERR_HIP; }
+      if (t.done(launch_transpose_acts(dY, c->X, T, D, c->dYt, c->Xt, perm, s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_DW2, s); if (t.done(launch_split_wgrad(c->Hc_t, c->meta_t, ns, c->Hdn_t, nd, c->dYt, D, T, dW2, D, c->feat_of_row, s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_DW1, s); if (t.done(launch_split_wgrad(c->dZc_t, c->meta_t, ns, c->dZdn_t, nd, c->Xt, D, T, c->dW1t, D, c->feat_of_row, s))) return FFN24_ERR_HIP; }
-    { Timed t(c, K_TR_DW1, s); if (t.done(launch_transpose(c->dW1t, F, D, dW1, 0, nullptr, 0, nullptr, s))) return FFN24_ERR_HIP; }
+    { Timed t(c, K_TR_DW1, s); if (t.done(launch_transpose(c->dW1t, F, D, dW1, s))) return FFN24_ERR_HIP; }
     return FFN24_OK;
   }
   { Timed t(c, K_FW, s);  if (t.done(launch_featurewise24(c->Hc, c->meta, c->dZc, T, F, c->Hc_t, c->meta_t, c->dZc_t, c->tele, s))) return FFN24_ERR_HIP; }
   if (c->tele && (rc = tele_snapshot(c, 1, s))) return rc;
   { Timed t(c, K_TR_ACT, s);
-    int rc1 = launch_transpose(dY, T, D, c->dYt, 2, nullptr, 0, perm, s);
-    if (t.done(rc1 ? rc1 : launch_transpose(c->X, T, D, c->Xt, 2, nullptr, 0, perm, s))) return FFN24_ERR_HIP; }
+    if (t.done(launch_transpose_acts(dY, c->X, T, D, c->dYt, c->Xt, perm, s))) return FFN24_ERR_HIP; }
   { Timed t(c, K_DW2, s); if (t.done(launch_sp_rowmajor(c->Hc_t, c->meta_t, 1, c->dYt, 1, F, D, T, dW2, s))) return FFN24_ERR_HIP; }
   { Timed t(c, K_DW1, s); if (t.done(launch_sp_colmajor(c->dZc_t, c->meta_t, 1, c->Xt, 1, F, D, T, dW1, s))) return FFN24_ERR_HIP; }
   return FFN24_OK;
@@ -841,8 +827,7 @@ int ffn_bwd_rowwise(ffn24_ctx* c, const ffn24_rowwise_bwd_operands* op, void* dX
     if (!rc1) rc1 = launch_quantise_rows_dense(c->Hdt16, c->hmax, F, T, c->Hd_t, c->sh_f, s);
     if (t.done(rc1 ? rc1 : launch_quantise_rows_dense(c->dZdt16, c->zmax, F, T, c->dZd_t, c->sdz_f, s))) return FFN24_ERR_HIP; }
   { Timed t(c, K_TR_ACT, s);
-    int rc1 = launch_transpose8(op->dY8c, T, D, c->dYt, 2, nullptr, 0, s);
-    if (t.done(rc1 ? rc1 : launch_transpose8(op->X8c, T, D, c->Xt, 2, nullptr, 0, s))) return FFN24_ERR_HIP; }
+    if (t.done(launch_transpose8_acts(op->dY8c, op->X8c, T, D, c->dYt, nullptr, c->Xt, nullptr, s))) return FFN24_ERR_HIP; }
   { Timed t(c, KD_DW2, s);
     if (t.done(launch_dense_rowmajor_f8_rowwise(c->Hd_t, c->dYt, 1, F, D, T, c->sh_f, op->sdy_d, dW2, s))) return FFN24_ERR_HIP; }
   { Timed t(c, KD_DW1, s);
@@ -862,8 +847,7 @@ int ffn_bwd(ffn24_ctx* c, const void* dY, void* dX, void* dW1, void* dW2, void* 
   int T = (int)c->T, D = (int)c->D, F = (int)c->F;
   if (c->f8) {
     { Timed t(c, K_TR_ACT, s);
-      int rc1 = launch_transpose8(dY, T, D, c->dYt, 2, c->dYp8, 1, s);
-      if (t.done(rc1 ? rc1 : launch_transpose8(c->X, T, D, c->Xt, 2, nullptr, 0, s))) return FFN24_ERR_HIP; }
+      if (t.done(launch_transpose8_acts(dY, c->X, T, D, c->dYt, c->dYp8, c->Xt, nullptr, s))) return FFN24_ERR_HIP; }
     { Timed t(c, KD_DH, s);
       if (t.done(launch_dh_drelu_f8(c->W2p, c->dYp8, c->Hd16, T, D, F, c->sdy * c->sw2, c->sdz, c->dZd, c->dZd_t, s))) return FFN24_ERR_HIP; }
     { Timed t(c, KD_DX, s);
@@ -877,8 +861,7 @@ int ffn_bwd(ffn24_ctx* c, const void* dY, void* dX, void* dW1, void* dW2, void* 
   { Timed t(c, KD_DH, s);  if (t.done(launch_dh_drelu(c->W2p, dY, c->Hd, T, D, F, c->dZd, c->dZd_t, s))) return FFN24_ERR_HIP; }
   { Timed t(c, KD_DX, s);  if (t.done(launch_dense_rowmajor(c->dZd, 1, c->W1p, 1, T, D, F, dX, s))) return FFN24_ERR_HIP; }
   { Timed t(c, K_TR_ACT, s);
-    int rc1 = launch_transpose(dY, T, D, c->dYt, 2, nullptr, 0, nullptr, s);
-    if (t.done(rc1 ? rc1 : launch_transpose(c->X, T, D, c->Xt, 2, nullptr, 0, nullptr, s))) return FFN24_ERR_HIP; }
+    if (t.done(launch_transpose_acts(dY, c->X, T, D, c->dYt, c->Xt, nullptr, s))) return FFN24_ERR_HIP; }
   { Timed t(c, KD_DW2, s); if (t.done(launch_dense_rowmajor(c->Hd_t, 1, c->dYt, 1, F, D, T, dW2, s))) return FFN24_ERR_HIP; }
   { Timed t(c, KD_DW1, s); if (t.done(launch_dense_colmajor(c->dZd_t, 1, c->Xt, 1, F, D, T, dW1, s))) return FFN24_ERR_HIP; }
   return FFN24_OK;

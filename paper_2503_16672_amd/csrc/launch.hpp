@@ -163,16 +163,17 @@ int launch_featurewise24_rows(const void* Hc, const uint8_t* meta, const void* d
 int launch_tele_sum(const unsigned long long* tele, long long elements, long long path, long long* out, hipStream_t s);
 // panel form -> row-major copy of a compressed operand: rows x npanels pieces of `piece_bytes` (64 values / 8 or 16 metadata)
 int launch_unpanel(const void* src, int rows, int npanels, int piece_bytes, void* dst, hipStream_t s);
-// in [R][C] -> out [C][R] (R % 64 == 0, C % 128 == 0); out_form: 0 row-major, 1 dense panel form (A operands), 2 B panel form
-// (gemm_core.hpp; both then need C % 256 == 0);
-// in_panel (may be NULL): also a panel-form copy of `in` itself (then R % 256 == 0), in the B form if in_panel_b
-// in_rowmap (may be NULL): row r of the input is taken from memory row in_rowmap[r]
-int launch_transpose(const void* in, int R, int C, void* out, int out_form, void* in_panel, int in_panel_b, const int* in_rowmap, hipStream_t s);
-// the same for 1-byte elements (fp8): in [R][C] -> out [C][R] (R % 64 == 0, C % 256 == 0); panel forms: 64-byte pieces of 64 k
-// in_panel (may be NULL): also a panel-form copy of `in` itself (R % 256 == 0, C % 64 == 0), in the B form if in_panel_b
-int launch_transpose8(const void* in, int R, int C, void* out, int out_form, void* in_panel, int in_panel_b, hipStream_t s);
-// the same without the panel copy, input row r taken from memory row in_rowmap[r] (may be NULL)
-int launch_transpose8_rows(const void* in, int R, int C, void* out, int out_form, const int* in_rowmap, hipStream_t s);
+// transposes, in [R][C] -> out [C][R] (R % 64 == 0, C % 128 == 0; 1-byte elements, transpose8: C % 256 == 0), two to a launch:
+//   plain: row-major out
+//   weights: W1 [D][F] -> W1t in dense panel form (A operand) and, W1p given, W1 itself in B panel form; W2 [F][D] -> W2t in B panel
+//   form and, W2p given, W2 itself in dense panel form (all sizes multiples of 256)
+//   acts: dY, X [T][D] -> dYt, Xt in B panel form, row r taken from memory row rowmap[r] (may be NULL); bytes: dYp given, also dY
+//   itself in B panel form
+int launch_transpose(const void* in, int R, int C, void* out, hipStream_t s);
+int launch_transpose_weights(const void* W1, const void* W2, int D, int F, void* W1t, void* W1p, void* W2t, void* W2p, hipStream_t s);
+int launch_transpose_acts(const void* dY, const void* X, int T, int D, void* dYt, void* Xt, const int* rowmap, hipStream_t s);
+int launch_transpose8_weights(const void* W1, const void* W2, int D, int F, void* W1t, void* W1p, void* W2t, void* W2p, hipStream_t s);
+int launch_transpose8_acts(const void* dY, const void* X, int T, int D, void* dYt, void* dYp, void* Xt, const int* rowmap, hipStream_t s);
 // dst[i] = src[map[i]], i < n
 int launch_gather_f32(const float* src, const int* map, int n, float* dst, hipStream_t s);
 
