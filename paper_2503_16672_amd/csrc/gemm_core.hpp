@@ -762,6 +762,31 @@ __global__ void __launch_bounds__(GEMM_THREADS, (Geo<true, F8, MI, NI>::PER_CU))
   cs.end(gs);
 }
 
+// Two GEMMs of one kind and size in one launch, each with its own epilogue: workgroups [0, n_first) take the tiles of the first.  The two
+// weight gradients of a step run like this where one of them alone would leave CUs idle.  One main loop serves both; EpiB is a staged
+// epilogue (transposing store), EpiA a plain one.
+template <class EpiA, class EpiB>
+struct EpiDuo {
+  static constexpr bool STAGED = true;
+  struct Args { typename EpiA::Args a; typename EpiB::Args b; bool second; };
+  template <int MI, int NI>
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane, char* wbuf) {
+    if (e.second) EpiB::template run<MI, NI>(e.b, acc, m_lane, n_lane, wbuf);
+    else EpiA::template run<MI, NI>(e.a, acc, m_lane, n_lane);
+  }
+};
+template <bool SPARSE, class EpiA, class EpiB, bool F8, int MI, int NI>
+__global__ void __launch_bounds__(GEMM_THREADS, (Geo<SPARSE, F8, MI, NI>::PER_CU)) gemm_duo_kernel(GemmArgs ga, typename EpiA::Args ea, int n_first,
+                                                                                                  GemmArgs gb, typename EpiB::Args eb) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const int bid = blockIdx.x;
+  const bool second = bid >= n_first;
+  GemmArgs g = ga;                       // (same M, N, K and operand forms)
+  if (second) { g.A = gb.A; g.Ameta = gb.Ameta; g.B = gb.B; }
+  const typename EpiDuo<EpiA, EpiB>::Args e{ea, eb, second};
+  gemm_tile<SPARSE, EpiDuo<EpiA, EpiB>, F8, 0, MI, NI>(g, e, smem, second ? bid - n_first : bid);
+}
+
 // ------------------------------------------------------------------------------------------------
 // small device helpers shared by the epilogues
 // ------------------------------------------------------------------------------------------------

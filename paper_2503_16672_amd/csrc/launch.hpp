@@ -74,6 +74,14 @@ int launch_split_partition(const uint32_t* nnz, int F, int n_dense, int max_coun
 int launch_featurewise24_split(const void* Hc, const uint8_t* meta, const void* dZc, int T, int F, const int* row_of_feat, int n_sparse,
                                void* Hc_t, uint8_t* meta_t, void* dZc_t, void* Hdn_t, void* dZdn_t, unsigned long long* tele,
                                uint32_t* hmax, uint32_t* zmax, hipStream_t s);
+// both weight gradients of a step, in one launch where that helps: dW2 [F][D] and dW1 [D][F] from the transposed activation H and dZ Z
+// (2:4 along tokens with one metadata tensor, or dense: meta NULL), dYt and Xt; everything in panel form; fp8: a scale each, or
+// a scale per row and per column each
+int launch_wgrad(const void* H, const void* Z, const uint8_t* meta, const void* dYt, const void* Xt, int F, int D, int T, void* dW2, void* dW1, hipStream_t s);
+int launch_wgrad_f8(const void* H, const void* Z, const uint8_t* meta, const void* dYt, const void* Xt, int F, int D, int T, float scale2, float scale1,
+                    void* dW2, void* dW1, hipStream_t s);
+int launch_wgrad_f8_rowwise(const void* H, const void* Z, const uint8_t* meta, const void* dYt, const void* Xt, int F, int D, int T, const float* rs2,
+                            const float* cs2, const float* rs1, const float* cs1, void* dW2, void* dW1, hipStream_t s);
 // dense GEMMs: A [M][K] (a_panel: in dense panel form), B [N][K]
 int launch_dense_rowmajor(const void* A, int a_panel, const void* B, int b_panel, int M, int N, int K, void* C, hipStream_t s);
 int launch_dense_colmajor(const void* A, int a_panel, const void* B, int b_panel, int M, int N, int K, void* Ct, hipStream_t s);

@@ -22,12 +22,12 @@ constexpr long long CHIP_CUS = 256;
 inline long long tile_time(const TileCost& t, int K, bool f8) { return (long long)(f8 ? K / 2 : K) * t.per_k / 10 + t.fixed; }
 inline long long tile_count(const TileCost& t, int M, int N) { return (long long)(M / (64 * t.mi)) * (N / (64 * t.ni)); }
 
-inline int pick_tile(bool sparse, bool f8, int M, int N, int K) {
+inline int pick_tile(bool sparse, bool f8, int M, int N, int K, int gemms = 1) {   // gemms: that many of this size share the launch
   int best = 0;
   long long best_time = 0;
   for (int i = 0; i < NUM_TILES; i++) {
     const TileCost& t = sparse ? TILES_SPARSE[i] : TILES_DENSE[i];
-    const long long time = (tile_count(t, M, N) + CHIP_CUS - 1) / CHIP_CUS * tile_time(t, K, f8);
+    const long long time = (gemms * tile_count(t, M, N) + CHIP_CUS - 1) / CHIP_CUS * tile_time(t, K, f8);
     if (i == 0 || time * 100 < best_time * 97) { best = i; best_time = time; }
   }
   return best;
@@ -74,6 +74,35 @@ static int launch_gemm(const GemmArgs& g_in, const typename Epi::Args& ea, hipSt
     case 2: return launch_tile<SPARSE, Epi, F8, 0, 2, 2>(g, ea, s);
     case 3: return launch_tile<SPARSE, Epi, F8, 0, 2, 1>(g, ea, s);
     default: return launch_tile<SPARSE, Epi, F8, 0, 1, 1>(g, ea, s);
+  }
+}
+
+template <bool SPARSE, class EpiA, class EpiB, bool F8, int MI, int NI>
+static int launch_duo_tile(const GemmArgs& ga, const typename EpiA::Args& ea, const GemmArgs& gb, const typename EpiB::Args& eb, hipStream_t s) {
+  using G = Geo<SPARSE, F8, MI, NI>;
+  auto kern = gemm_duo_kernel<SPARSE, EpiA, EpiB, F8, MI, NI>;
+  static std::atomic<bool> configured[MAX_DEVICES] = {};
+  if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), G::LDS_TOTAL, configured)) return rc;
+  const int n = (ga.M / G::BM) * (ga.N / G::BN);
+  hipLaunchKernelGGL(kern, dim3(2 * n), dim3(GEMM_THREADS), G::LDS_TOTAL, s, ga, ea, n, gb, eb);
+  return (int)hipGetLastError();
+}
+
+// Two GEMMs of the same M, N, K and operand forms (gemm_duo_kernel), with the tile that suits both together.  Where that is the 256 x 256
+// tile and each of them fills the chip by itself, there is nothing to gain and they go out one after the other.
+template <bool SPARSE, class EpiA, class EpiB, bool F8 = false>
+static int launch_gemm_duo(const GemmArgs& ga, const typename EpiA::Args& ea, const GemmArgs& gb, const typename EpiB::Args& eb, hipStream_t s) {
+  const int tile = pick_tile(SPARSE, F8, ga.M, ga.N, ga.K, 2);
+  if (tile == 0 && tile_count(TILES_SPARSE[0], ga.M, ga.N) % CHIP_CUS == 0) {
+    const int rc = launch_gemm<SPARSE, EpiA, F8>(ga, ea, s);
+    return rc ? rc : launch_gemm<SPARSE, EpiB, F8>(gb, eb, s);
+  }
+  switch (tile) {
+    case 0: return launch_duo_tile<SPARSE, EpiA, EpiB, F8, 4, 4>(ga, ea, gb, eb, s);
+    case 1: return launch_duo_tile<SPARSE, EpiA, EpiB, F8, 4, 2>(ga, ea, gb, eb, s);
+    case 2: return launch_duo_tile<SPARSE, EpiA, EpiB, F8, 2, 2>(ga, ea, gb, eb, s);
+    case 3: return launch_duo_tile<SPARSE, EpiA, EpiB, F8, 2, 1>(ga, ea, gb, eb, s);
+    default: return launch_duo_tile<SPARSE, EpiA, EpiB, F8, 1, 1>(ga, ea, gb, eb, s);
   }
 }
 
