@@ -558,15 +558,17 @@ int ffn24_fwd(ffn24_ctx* c, const void* X, const void* W1, const float* b1, cons
   if ((rc = resolve_weights(c, W1, W2, s))) return rc;
   if (c->f8 && (c->flags & FFN24_ROWWISE)) {
     // row-wise scaling: up-projection (bf16 kept values + row maxima), row-wise quantisation, scaled sparse GEMM
-    if (launch_zero32(c->rowmax, (size_t)T, s)) return FFN24_ERR_HIP;
     uint32_t* nnz = (c->flags & FFN24_SPLIT) && c->n_dense > 0 ? c->nnz : nullptr;
-    if (nnz && launch_zero32(nnz, (size_t)F, s)) return FFN24_ERR_HIP;
+    PaneliseJobs pre;
+    pre.add_zero(c->rowmax, T);
+    if (nnz) pre.add_zero(nnz, F);
     // token permutation: position p inside the FFN holds token perm[p] -- its row of X8 is gathered by the pass that brings X8
     // into panel form, its scale by a small kernel; everything in between lives in FFN order, and Y's rows go back to their tokens
     const int* perm = c->perm_on ? c->perm : nullptr;
     const float* sx = c->rsx;
-    if (perm) { if (launch_gather_f32(c->rsx, perm, T, c->sx_p, s)) return FFN24_ERR_HIP; sx = c->sx_p; }
-    { Timed t(c, K_PANEL_X, s); if (t.done(launch_panelise8_rows(X, T, D, c->Xp8, 1, perm, s))) return FFN24_ERR_HIP; }
+    if (perm) { pre.set_gather(c->rsx, perm, T, c->sx_p); sx = c->sx_p; }
+    pre.add_copy(X, T, D, c->Xp8, 1, perm);
+    { Timed t(c, K_PANEL_X, s); if (t.done(launch_panelise8(pre, s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_UP, s);
       if (t.done(launch_up_prune24_f8_rowwise(c->W1t, c->Xp8, b1, T, D, F, sx, c->rsw1, c->Hc16, c->meta16, c->Hdbg, c->rowmax, nnz, s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_QUANT, s);
@@ -580,7 +582,9 @@ int ffn24_fwd(ffn24_ctx* c, const void* X, const void* W1, const float* b1, cons
   }
   if (c->f8) {
     const bool train = (c->flags & FFN24_TRAINING) != 0;
-    { Timed t(c, K_PANEL_X, s); if (t.done(launch_panelise8(X, T, D, c->Xp8, 1, s))) return FFN24_ERR_HIP; }
+    PaneliseJobs pre;
+    pre.add_copy(X, T, D, c->Xp8, 1, nullptr);
+    { Timed t(c, K_PANEL_X, s); if (t.done(launch_panelise8(pre, s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_UP, s);
       if (t.done(launch_up_prune24_f8(c->W1t, c->Xp8, b1, T, D, F, c->sx * c->sw1, c->sh, c->Hc, c->meta, c->Hdbg, train ? c->Hc16 : nullptr,
                                       train ? c->meta16 : nullptr, s))) return FFN24_ERR_HIP; }
@@ -646,12 +650,13 @@ int ffn24_bwd_rowwise(ffn24_ctx* c, const ffn24_rowwise_bwd_operands* op, void* 
   // where it lies (measured: no slower than from a panel-form copy, and the copy costs 0.1 ms)
   // dY8r likewise (the B operand of the dense dH GEMM, 64 bytes of every row a stage), with the rows of a token permutation gathered
   const int* perm = c->perm_on ? c->perm : nullptr;
-  { Timed t(c, K_PANEL_W, s);
-    int rc1 = launch_panelise8(op->W2_8r, F, D, c->W2rp, 0, s);
-    if (t.done(rc1 ? rc1 : launch_panelise8_rows(op->dY8r, T, D, c->dYp8, 1, perm, s))) return FFN24_ERR_HIP; }
-  if (launch_zero32(c->rowmax_dz, (size_t)T, s) || launch_zero32(c->hmax, (size_t)F, s) || launch_zero32(c->zmax, (size_t)F, s)) return FFN24_ERR_HIP;
+  PaneliseJobs pre;
+  pre.add_copy(op->W2_8r, F, D, c->W2rp, 0, nullptr);
+  pre.add_copy(op->dY8r, T, D, c->dYp8, 1, perm);
+  pre.add_zero(c->rowmax_dz, T); pre.add_zero(c->hmax, F); pre.add_zero(c->zmax, F);
   const float* sdy_t = op->sdy_t;                     // as in the forward: the scales of the gathered rows, and dX's rows scattered back
-  if (perm) { if (launch_gather_f32(op->sdy_t, perm, T, c->sdy_p, s)) return FFN24_ERR_HIP; sdy_t = c->sdy_p; }
+  if (perm) { pre.set_gather(op->sdy_t, perm, T, c->sdy_p); sdy_t = c->sdy_p; }
+  { Timed t(c, K_PANEL_W, s); if (t.done(launch_panelise8(pre, s))) return FFN24_ERR_HIP; }
   { Timed t(c, K_DH, s);
     if (t.done(launch_dh_gather_f8_rowwise(c->W2rp, c->dYp8, c->Hc16, c->meta16, T, D, F, op->sw2_f, sdy_t, c->dZc16, c->rowmax_dz, s))) return FFN24_ERR_HIP; }
   { Timed t(c, K_QUANT_DZ, s);
@@ -774,8 +779,10 @@ int ffn_fwd(ffn24_ctx* c, const void* X, const void* W1, const float* b1, const 
   if ((rc = resolve_weights(c, W1, W2, s))) return rc;
   if (c->f8 && (c->flags & FFN24_ROWWISE)) {
     // dense baseline with row-wise scales: up-projection (bf16 activations + row maxima), row-wise quantisation, dense GEMM
-    if (launch_zero32(c->rowmax, (size_t)T, s)) return FFN24_ERR_HIP;
-    { Timed t(c, K_PANEL_X, s); if (t.done(launch_panelise8(X, T, D, c->Xp8, 1, s))) return FFN24_ERR_HIP; }
+    PaneliseJobs pre;
+    pre.add_zero(c->rowmax, T);
+    pre.add_copy(X, T, D, c->Xp8, 1, nullptr);
+    { Timed t(c, K_PANEL_X, s); if (t.done(launch_panelise8(pre, s))) return FFN24_ERR_HIP; }
     { Timed t(c, KD_UP, s);
       if (t.done(launch_up_relu2_f8_rowwise(c->W1t, c->Xp8, b1, T, D, F, c->rsx, c->rsw1, c->Hd16, c->rowmax, c->Hdt16, s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_QUANT, s);
@@ -787,7 +794,9 @@ int ffn_fwd(ffn24_ctx* c, const void* X, const void* W1, const float* b1, const 
   }
   if (c->f8) {
     const bool train = (c->flags & FFN24_TRAINING) != 0;
-    { Timed t(c, K_PANEL_X, s); if (t.done(launch_panelise8(X, T, D, c->Xp8, 1, s))) return FFN24_ERR_HIP; }
+    PaneliseJobs pre;
+    pre.add_copy(X, T, D, c->Xp8, 1, nullptr);
+    { Timed t(c, K_PANEL_X, s); if (t.done(launch_panelise8(pre, s))) return FFN24_ERR_HIP; }
     { Timed t(c, KD_UP, s);
       if (t.done(launch_up_relu2_f8(c->W1t, c->Xp8, b1, T, D, F, c->sx * c->sw1, c->sh, c->Hd, train ? c->Hd16 : nullptr, train ? c->Hd_t : nullptr, s)))
         return FFN24_ERR_HIP; }
@@ -813,11 +822,12 @@ int ffn_bwd_rowwise(ffn24_ctx* c, const ffn24_rowwise_bwd_operands* op, void* dX
   if (rc) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
   int T = (int)c->T, D = (int)c->D, F = (int)c->F;
-  { Timed t(c, K_PANEL_W, s);
-    int rc1 = launch_panelise8(op->W2_8r, F, D, c->W2rp, 0, s);
-    if (!rc1) rc1 = launch_panelise8(op->W1_8c, D, F, c->W1cp, 1, s);      // (the dense dX GEMM does lose with its B operand row-major: 1.28 -> 1.43 ms)
-    if (t.done(rc1 ? rc1 : launch_panelise8(op->dY8r, T, D, c->dYp8, 1, s))) return FFN24_ERR_HIP; }
-  if (launch_zero32(c->rowmax_dz, (size_t)T, s) || launch_zero32(c->hmax, (size_t)F, s) || launch_zero32(c->zmax, (size_t)F, s)) return FFN24_ERR_HIP;
+  PaneliseJobs pre;
+  pre.add_copy(op->W2_8r, F, D, c->W2rp, 0, nullptr);
+  pre.add_copy(op->W1_8c, D, F, c->W1cp, 1, nullptr);      // (the dense dX GEMM does lose with its B operand row-major: 1.28 -> 1.43 ms)
+  pre.add_copy(op->dY8r, T, D, c->dYp8, 1, nullptr);
+  pre.add_zero(c->rowmax_dz, T); pre.add_zero(c->hmax, F); pre.add_zero(c->zmax, F);
+  { Timed t(c, K_PANEL_W, s); if (t.done(launch_panelise8(pre, s))) return FFN24_ERR_HIP; }
   { Timed t(c, KD_DH, s);
     if (t.done(launch_dh_drelu_f8_rowwise(c->W2rp, c->dYp8, c->Hd16, T, D, F, op->sw2_f, op->sdy_t, c->dZd16, c->dZdt16, c->rowmax_dz, s))) return FFN24_ERR_HIP; }
   { Timed t(c, K_QUANT_DZ, s);

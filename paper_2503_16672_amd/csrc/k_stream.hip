@@ -765,40 +765,47 @@ int launch_transpose8_acts(const void* dY, const void* X, int T, int D, void* dY
   return (int)hipGetLastError();
 }
 
-// dst[i] = src[map[i]]: a per-token scale vector brought into the order of a token permutation
-__global__ void __launch_bounds__(256) gather_f32_kernel(const float* __restrict__ src, const int* __restrict__ map, int n, float* __restrict__ dst) {
-  int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < n) dst[i] = src[map[i]];
+// What an fp8 forward or backward needs done before its first GEMM, in one launch (each of these passes by itself is about as long as its
+// launch: T = 8192 D = 2048 F = 8192, token permutation and split, 4 + 6 launches of 4.7-9 us became 2):
+//   copies: byte matrices [R][C] (row-major, C a multiple of 64) into the dense fp8 panel form (64-byte pieces of 64 k, K = C) as A
+//     operands take it, or, b_form, into the B panel form (rows of every block of 256 in LDS order); row r is taken from memory row
+//     rowmap[r] if one is given (token permutation); 16 bytes per work item;
+//   zero: 32-bit words cleared (row maxima, counts);
+//   gather: dst[i] = src[map[i]], a per-token scale vector brought into the order of a token permutation.
+__global__ void __launch_bounds__(256) panelise8_kernel(PaneliseJobs jobs) {
+  unsigned bid = blockIdx.x;
+#pragma unroll
+  for (int j = 0; j < PaneliseJobs::COPIES; j++) {
+    const PaneliseJobs::Copy& cp = jobs.copy[j];
+    if (bid < cp.blocks) {
+      const int per_row = cp.C >> 4;
+      const size_t i = (size_t)bid * 256 + threadIdx.x;
+      if (i >= (size_t)cp.R * per_row) return;
+      const int r = (int)(i / per_row), cq = (int)(i % per_row), c = cq << 4;
+      const int prow = cp.b_form ? b_panel_pos(r) : r;
+      const size_t src = cp.rowmap ? (size_t)cp.rowmap[r] * per_row + cq : i;
+      st_stream(reinterpret_cast<u32x4*>(static_cast<uint8_t*>(cp.out) + a24_piece(prow, c >> 6, cp.C >> 6) * 64 + (c & 63)),
+                ld_stream(static_cast<const u32x4*>(cp.in) + src));
+      return;
+    }
+    bid -= cp.blocks;
+  }
+  int i = (int)(bid * 256 + threadIdx.x);
+#pragma unroll
+  for (int j = 0; j < PaneliseJobs::ZEROS; j++) {
+    if (i < jobs.zero_n[j]) { jobs.zero[j][i] = 0u; return; }
+    i -= jobs.zero_n[j];
+  }
+  if (i < jobs.gather_n) jobs.gather_dst[i] = jobs.gather_src[jobs.gather_map[i]];
 }
 
-int launch_gather_f32(const float* src, const int* map, int n, float* dst, hipStream_t s) {
-  hipLaunchKernelGGL(gather_f32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, src, map, n, dst);
+int launch_panelise8(const PaneliseJobs& jobs, hipStream_t s) {
+  unsigned blocks = 0;
+  int side = jobs.gather_n;
+  for (const auto& c : jobs.copy) blocks += c.blocks;
+  for (int n : jobs.zero_n) side += n;
+  hipLaunchKernelGGL(panelise8_kernel, dim3(blocks + (unsigned)((side + 255) / 256)), dim3(256), 0, s, jobs);
   return (int)hipGetLastError();
-}
-
-// A byte matrix [R][C] (row-major, C a multiple of 64) copied into the dense fp8 panel form (64-byte pieces of 64 k, K = C) as
-// A operands take it, or, b_form, into the B panel form (rows of every block of 256 in LDS order).  16 bytes per work item.
-// in_rowmap (optional): row r is taken from memory row in_rowmap[r] (token permutation).
-__global__ void __launch_bounds__(256) panelise8_kernel(const u32x4* __restrict__ in, int R, int C, uint8_t* __restrict__ out, int b_form,
-                                                        const int* __restrict__ in_rowmap) {
-  const int per_row = C >> 4;
-  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (size_t)R * per_row) return;
-  int r = (int)(i / per_row), cq = (int)(i % per_row), c = cq << 4;
-  int prow = b_form ? b_panel_pos(r) : r;
-  size_t src = in_rowmap ? (size_t)in_rowmap[r] * per_row + cq : i;
-  st_stream(reinterpret_cast<u32x4*>(out + a24_piece(prow, c >> 6, C >> 6) * 64 + (c & 63)), ld_stream(in + src));
-}
-
-int launch_panelise8_rows(const void* in, int R, int C, void* out, int b_form, const int* in_rowmap, hipStream_t s) {
-  size_t n = (size_t)R * (C >> 4);
-  hipLaunchKernelGGL(panelise8_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, static_cast<const u32x4*>(in), R, C,
-                     static_cast<uint8_t*>(out), b_form, in_rowmap);
-  return (int)hipGetLastError();
-}
-
-int launch_panelise8(const void* in, int R, int C, void* out, int b_form, hipStream_t s) {
-  return launch_panelise8_rows(in, R, C, out, b_form, nullptr, s);
 }
 
 // Feature-wise 2:4 on top of the token-wise mask for the fp8 operands (Sec. 2, last paragraph; the FP8 side of the fused

@@ -148,12 +148,8 @@ int launch_sp_colmajor_f8_rowwise(const void* vals8, const uint8_t* meta, const 
 // stored magnitude word of each output row
 int launch_featurewise24_rowmax(const void* Hc, const uint8_t* meta, const void* dZc, int T, int F, void* Hc_t, uint8_t* meta_t, void* dZc_t,
                                 uint32_t* hmax, uint32_t* zmax, hipStream_t s);
-// byte matrix [R][C] (C % 64 == 0, R % 256 == 0) -> dense fp8 panel form, or the B panel form if b_form
-int launch_panelise8(const void* in, int R, int C, void* out, int b_form, hipStream_t s);
-// the same with row r taken from memory row in_rowmap[r] (may be NULL)
-int launch_panelise8_rows(const void* in, int R, int C, void* out, int b_form, const int* in_rowmap, hipStream_t s);
 // bf16 X [R][C] (C % 8 == 0) -> e4m3 codes [R][C] and one scale per row (axis 1, scales [R]) or per column (axis 0, scales [C]; the
-// buffer also holds the column maxima while the call runs)
+// codes buffer holds the slabs' column maxima in between)
 int launch_quantise_bf16(const void* X, int64_t R, int64_t C, int axis, void* codes, float* scales, hipStream_t s);
 // streaming kernels
 // p[0..n) = 0 (a kernel, not a memset node)
@@ -171,6 +167,23 @@ int launch_featurewise24_rows(const void* Hc, const uint8_t* meta, const void* d
 int launch_tele_sum(const unsigned long long* tele, long long elements, long long path, long long* out, hipStream_t s);
 // panel form -> row-major copy of a compressed operand: rows x npanels pieces of `piece_bytes` (64 values / 8 or 16 metadata)
 int launch_unpanel(const void* src, int rows, int npanels, int piece_bytes, void* dst, hipStream_t s);
+// what an fp8 forward or backward needs before its first GEMM, in one launch (panelise8_kernel): up to three byte matrices copied into panel
+// form, up to three word arrays cleared, one scale vector gathered
+struct PaneliseJobs {
+  static constexpr int COPIES = 3, ZEROS = 3;
+  struct Copy { const void* in; int R, C; void* out; int b_form; const int* rowmap; unsigned blocks; } copy[COPIES] = {};
+  uint32_t* zero[ZEROS] = {};
+  int zero_n[ZEROS] = {};
+  const float* gather_src = nullptr; const int* gather_map = nullptr; float* gather_dst = nullptr; int gather_n = 0;
+  int copies = 0, zeros = 0;   // (host side: slots in use)
+  // R x C bytes, C % 64 == 0, R % 256 == 0
+  void add_copy(const void* in, int R, int C, void* out, int b_form, const int* rowmap) {
+    copy[copies++] = Copy{in, R, C, out, b_form, rowmap, (unsigned)(((size_t)R * (C >> 4) + 255) / 256)};
+  }
+  void add_zero(uint32_t* p, int n) { zero[zeros] = p; zero_n[zeros++] = n; }
+  void set_gather(const float* src, const int* map, int n, float* dst) { gather_src = src; gather_map = map; gather_n = n; gather_dst = dst; }
+};
+int launch_panelise8(const PaneliseJobs& jobs, hipStream_t s);
 // transposes, in [R][C] -> out [C][R] (R % 64 == 0, C % 128 == 0; 1-byte elements, transpose8: C % 256 == 0), two to a launch:
 //   plain: row-major out
 //   weights: W1 [D][F] -> W1t in dense panel form (A operand) and, W1p given, W1 itself in B panel form; W2 [F][D] -> W2t in B panel
@@ -182,8 +195,6 @@ int launch_transpose_weights(const void* W1, const void* W2, int D, int F, void*
 int launch_transpose_acts(const void* dY, const void* X, int T, int D, void* dYt, void* Xt, const int* rowmap, hipStream_t s);
 int launch_transpose8_weights(const void* W1, const void* W2, int D, int F, void* W1t, void* W1p, void* W2t, void* W2p, hipStream_t s);
 int launch_transpose8_acts(const void* dY, const void* X, int T, int D, void* dYt, void* dYp, void* Xt, const int* rowmap, hipStream_t s);
-// dst[i] = src[map[i]], i < n
-int launch_gather_f32(const float* src, const int* map, int n, float* dst, hipStream_t s);
 
 // ------------------------------------------------------------------------------------------------
 // measurement probes (k_probe.hip); they allocate their own buffers and wait for their own work
