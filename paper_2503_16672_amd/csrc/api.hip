@@ -681,10 +681,15 @@ int ffn24_bwd_rowwise(ffn24_ctx* c, const ffn24_rowwise_bwd_operands* op, void* 
       if (t.done(rc1 ? rc1 : launch_quantise_rows_dense(c->dZdn_t, c->zmax + ns, nd, T, c->dZdn8_t, c->sdz_f + ns, s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_TR_ACT, s);
       if (t.done(launch_transpose8_acts(op->dY8c, op->X8c, T, D, c->dYt, nullptr, c->Xt, perm, s))) return FFN24_ERR_HIP; }
+    if (!c->profiling) {   // (profiling times the two by themselves)
+      if (launch_split_wgrads_f8_rowwise(c->Hc_t, c->dZc_t, c->meta_t, ns, c->Hdn8_t, c->dZdn8_t, nd, c->dYt, c->Xt, D, T, c->sh_f, op->sdy_d, c->sdz_f, op->sx_d,
+                                         dW2, c->dW1t, D, c->feat_of_row, s)) return FFN24_ERR_HIP;
+    } else {
     { Timed t(c, K_DW2, s);
       if (t.done(launch_split_wgrad_f8_rowwise(c->Hc_t, c->meta_t, ns, c->Hdn8_t, nd, c->dYt, D, T, c->sh_f, op->sdy_d, dW2, D, c->feat_of_row, s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_DW1, s);
       if (t.done(launch_split_wgrad_f8_rowwise(c->dZc_t, c->meta_t, ns, c->dZdn8_t, nd, c->Xt, D, T, c->sdz_f, op->sx_d, c->dW1t, D, c->feat_of_row, s))) return FFN24_ERR_HIP; }
+    }
     { Timed t(c, K_TR_DW1, s); if (t.done(launch_transpose(c->dW1t, F, D, dW1, s))) return FFN24_ERR_HIP; }
     return FFN24_OK;
   }
@@ -749,8 +754,12 @@ int ffn24_bwd(ffn24_ctx* c, const void* dY, void* dX, void* dW1, void* dW2, void
     if (c->tele && (rc = tele_snapshot(c, 1, s))) return rc;
     { Timed t(c, K_TR_ACT, s);
       if (t.done(launch_transpose_acts(dY, c->X, T, D, c->dYt, c->Xt, perm, s))) return FFN24_ERR_HIP; }
+    if (!c->profiling) {
+      if (launch_split_wgrads(c->Hc_t, c->dZc_t, c->meta_t, ns, c->Hdn_t, c->dZdn_t, nd, c->dYt, c->Xt, D, T, dW2, c->dW1t, D, c->feat_of_row, s)) return FFN24_ERR_HIP;
+    } else {
     { Timed t(c, K_DW2, s); if (t.done(launch_split_wgrad(c->Hc_t, c->meta_t, ns, c->Hdn_t, nd, c->dYt, D, T, dW2, D, c->feat_of_row, s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_DW1, s); if (t.done(launch_split_wgrad(c->dZc_t, c->meta_t, ns, c->dZdn_t, nd, c->Xt, D, T, c->dW1t, D, c->feat_of_row, s))) return FFN24_ERR_HIP; }
+    }
     { Timed t(c, K_TR_DW1, s); if (t.done(launch_transpose(c->dW1t, F, D, dW1, s))) return FFN24_ERR_HIP; }
     return FFN24_OK;
   }

@@ -745,21 +745,35 @@ __global__ void __launch_bounds__(GEMM_THREADS, (Geo<SPARSE, F8, MI, NI>::PER_CU
   cs.end(g);
 }
 
-// Two GEMMs in one launch: the first `nd_tiles` workgroups compute the tiles of a dense GEMM gd, the others those of
-// a sparse GEMM gs (same epilogue type, separate arguments).  The split weight-gradient GEMMs use it (Sec. 2,
-// "Optimization 1": a 2:4 GEMM over most hidden features plus a dense one over the few that are not sparse enough):
-// alone, the small dense GEMM would occupy a fraction of the CUs for as long as a full round of tiles.  The dense
-// tiles, which take longer, come first.
+// A dense and a sparse GEMM (same epilogue type, separate arguments, same N and K) in one launch, for one weight gradient or for both
+// (`sets` = 2).  The split weight-gradient GEMMs use it (Sec. 2, "Optimization 1": a 2:4 GEMM over most hidden features plus a dense one
+// over the few that are not sparse enough): alone, the small dense GEMM would occupy a fraction of the CUs for as long as a full round
+// of tiles.  The dense tiles, which take longer, come first, those of both sets before any sparse one: with one set a launch, a
+// shape whose sparse tiles take just one round waited twice for its dense tiles (fp8, T = F = 8192, D = 2048, 512 dense features: 2 x
+// 93-97 us; both sets in one launch: 178 us).
+template <class Epi>
+struct PairSet { GemmArgs gd; typename Epi::Args ed; GemmArgs gs; typename Epi::Args es; };
+
 template <class Epi, bool F8 = false, int MI = 4, int NI = 4>
-__global__ void __launch_bounds__(GEMM_THREADS, (Geo<true, F8, MI, NI>::PER_CU)) gemm_pair_kernel(GemmArgs gd, typename Epi::Args ead, int nd_tiles,
-                                                                  GemmArgs gs, typename Epi::Args eas) {
+__global__ void __launch_bounds__(GEMM_THREADS, (Geo<true, F8, MI, NI>::PER_CU)) gemm_pair_kernel(PairSet<Epi> a, PairSet<Epi> b, int sets, int nd_tiles,
+                                                                                                 int ns_tiles) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  const int pid = blockIdx.x;
+  int pid = blockIdx.x;
   ClkSample cs;
-  cs.begin(gs);
-  if (pid < nd_tiles) gemm_tile<false, Epi, F8, 0, MI, NI>(gd, ead, smem, pid);
-  else gemm_tile<true, Epi, F8, 0, MI, NI>(gs, eas, smem, pid - nd_tiles);
-  cs.end(gs);
+  cs.begin(a.gs);
+  if (pid < sets * nd_tiles) {
+    GemmArgs g = a.gd;                   // (the sets differ in their operands only)
+    typename Epi::Args e = a.ed;
+    if (pid >= nd_tiles) { pid -= nd_tiles; g.A = b.gd.A; g.B = b.gd.B; e = b.ed; }
+    gemm_tile<false, Epi, F8, 0, MI, NI>(g, e, smem, pid);
+  } else {
+    pid -= sets * nd_tiles;
+    GemmArgs g = a.gs;
+    typename Epi::Args e = a.es;
+    if (pid >= ns_tiles) { pid -= ns_tiles; g.A = b.gs.A; g.Ameta = b.gs.Ameta; g.B = b.gs.B; e = b.es; }
+    gemm_tile<true, Epi, F8, 0, MI, NI>(g, e, smem, pid);
+  }
+  cs.end(a.gs);
 }
 
 // Two GEMMs of one kind and size in one launch, each with its own epilogue: workgroups [0, n_first) take the tiles of the first.  The two

@@ -23,13 +23,23 @@ int launch_sp_rowmajor_f8_rowwise_mapped(const void* vals8, const uint8_t* meta,
   return launch_gemm<true, EpiRowMajorRowColMapped, true>(g, ea, s);
 }
 
+static PairSet<EpiRowMajorRowColMapped> split_set(const void* vals8, const uint8_t* meta, int ns, const void* Ad8, int nd, const void* B8, int N, int K,
+                                                  const float* rs, const float* cs, void* C, int ldc, const int* rowmap) {
+  return {GemmArgs{Ad8, nullptr, B8, nd, N, K, 1, nullptr, 1}, {static_cast<__bf16*>(C), ldc, rs + ns, cs, rowmap + ns},
+          GemmArgs{vals8, meta, B8, ns, N, K, 1, nullptr, 1}, {static_cast<__bf16*>(C), ldc, rs, cs, rowmap}};
+}
+
 int launch_split_wgrad_f8_rowwise(const void* vals8, const uint8_t* meta, int ns, const void* Ad8, int nd, const void* B8, int N, int K,
                                   const float* rs, const float* cs, void* C, int ldc, const int* rowmap, hipStream_t s) {
-  GemmArgs gs{vals8, meta, B8, ns, N, K, 1, nullptr, 1};
-  GemmArgs gd{Ad8, nullptr, B8, nd, N, K, 1, nullptr, 1};
-  EpiRowMajorRowColMapped::Args eas{static_cast<__bf16*>(C), ldc, rs, cs, rowmap};
-  EpiRowMajorRowColMapped::Args ead{static_cast<__bf16*>(C), ldc, rs + ns, cs, rowmap + ns};
-  return launch_gemm_pair<EpiRowMajorRowColMapped, true>(gd, ead, gs, eas, s);
+  const PairSet<EpiRowMajorRowColMapped> a = split_set(vals8, meta, ns, Ad8, nd, B8, N, K, rs, cs, C, ldc, rowmap);
+  return launch_gemm_pair<EpiRowMajorRowColMapped, true>(a, a, 1, s);
+}
+
+int launch_split_wgrads_f8_rowwise(const void* H, const void* Z, const uint8_t* meta, int ns, const void* Hd, const void* Zd, int nd, const void* dYt,
+                                   const void* Xt, int N, int K, const float* rs2, const float* cs2, const float* rs1, const float* cs1, void* dW2, void* dW1t,
+                                   int ldc, const int* rowmap, hipStream_t s) {
+  return launch_gemm_pair<EpiRowMajorRowColMapped, true>(split_set(H, meta, ns, Hd, nd, dYt, N, K, rs2, cs2, dW2, ldc, rowmap),
+                                                         split_set(Z, meta, ns, Zd, nd, Xt, N, K, rs1, cs1, dW1t, ldc, rowmap), 2, s);
 }
 
 int launch_up_relu2_f8_rowwise(const void* W1t8, const void* X8, const float* b1, int T, int D, int F, const float* sx, const float* sw1,

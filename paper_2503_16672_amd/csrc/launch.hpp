@@ -64,6 +64,12 @@ int launch_dh_drelu(const void* W2, const void* dY, const void* H, int T, int D,
 // [ns, ns + nd) from the dense GEMM over Ad [nd][K], both against B [N][K] (B panel form), one launch; row m goes to C[rowmap[m]][*]
 int launch_split_wgrad(const void* vals, const uint8_t* meta, int ns, const void* Ad, int nd, const void* B, int N, int K,
                        void* C, int ldc, const int* rowmap, hipStream_t s);
+// both weight gradients of a split step in one launch: dW2 from (H, Hd) and dYt, dW1 (as [F][D] rows, dW1t) from (Z, Zd) and Xt
+int launch_split_wgrads(const void* H, const void* Z, const uint8_t* meta, int ns, const void* Hd, const void* Zd, int nd, const void* dYt, const void* Xt, int N,
+                        int K, void* dW2, void* dW1t, int ldc, const int* rowmap, hipStream_t s);
+int launch_split_wgrads_f8_rowwise(const void* H, const void* Z, const uint8_t* meta, int ns, const void* Hd, const void* Zd, int nd, const void* dYt,
+                                   const void* Xt, int N, int K, const float* rs2, const float* cs2, const float* rs1, const float* cs1, void* dW2, void* dW1t,
+                                   int ldc, const int* rowmap, hipStream_t s);
 // feature partition for the split (one workgroup): the n_dense features with the largest counts (ties: lower index)
 // become rows [F - n_dense, F) of the split operands, the others rows [0, F - n_dense), both in ascending feature order
 // (max_count: an upper bound of every count, the number of tokens)

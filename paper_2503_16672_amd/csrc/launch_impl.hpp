@@ -37,11 +37,11 @@ inline int pick_tile(bool sparse, bool f8, int M, int N, int K, int gemms = 1) {
 // the dense ones take by themselves (their epilogue is a plain store here, not one of the fused ones the dense table is priced for).
 // The two parts make the estimate rougher, so a smaller tile has to promise 10 % (fp8, T 8192 D 2048 F 8192, 512 dense features:
 // 98.4 us with 256 x 256 and 99.0 with 256 x 128, which the estimate puts 7 % ahead).
-inline int pick_pair_tile(bool f8, int Md, int Ms, int N, int K) {
+inline int pick_pair_tile(bool f8, int Md, int Ms, int N, int K, int sets) {
   int best = 0;
   long long best_time = 0;
   for (int i = 0; i < NUM_TILES; i++) {
-    const long long nd = tile_count(TILES_DENSE[i], Md, N), ns = tile_count(TILES_SPARSE[i], Ms, N);
+    const long long nd = sets * tile_count(TILES_DENSE[i], Md, N), ns = sets * tile_count(TILES_SPARSE[i], Ms, N);
     const long long ts = tile_time(TILES_SPARSE[i], K, f8), td = tile_time(TILES_DENSE[i], K, f8) - TILES_DENSE[i].fixed + TILES_SPARSE[i].fixed;
     long long time = (nd + ns + CHIP_CUS - 1) / CHIP_CUS * ts;
     const long long dense = (nd + CHIP_CUS - 1) / CHIP_CUS * td, even = (nd * td + ns * ts) / CHIP_CUS;
@@ -107,29 +107,29 @@ static int launch_gemm_duo(const GemmArgs& ga, const typename EpiA::Args& ea, co
 }
 
 template <class Epi, bool F8, int MI, int NI>
-static int launch_pair_tile(const GemmArgs& gd, const typename Epi::Args& ead, const GemmArgs& gs, const typename Epi::Args& eas, hipStream_t s) {
+static int launch_pair_tile(const PairSet<Epi>& a, const PairSet<Epi>& b, int sets, hipStream_t s) {
   using GS = Geo<true, F8, MI, NI>;
   using GD = Geo<false, F8, MI, NI>;
   auto kern = gemm_pair_kernel<Epi, F8, MI, NI>;
   constexpr int lds = GS::LDS_TOTAL > GD::LDS_TOTAL ? GS::LDS_TOTAL : GD::LDS_TOTAL;
   static std::atomic<bool> configured[MAX_DEVICES] = {};
   if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds, configured)) return rc;
-  int nd_tiles = (gd.M / GD::BM) * (gd.N / GD::BN), ns_tiles = (gs.M / GS::BM) * (gs.N / GS::BN);
-  hipLaunchKernelGGL(kern, dim3(nd_tiles + ns_tiles), dim3(GEMM_THREADS), lds, s, gd, ead, nd_tiles, gs, eas);
+  const int nd = (a.gd.M / GD::BM) * (a.gd.N / GD::BN), ns = (a.gs.M / GS::BM) * (a.gs.N / GS::BN);
+  hipLaunchKernelGGL(kern, dim3(sets * (nd + ns)), dim3(GEMM_THREADS), lds, s, a, b, sets, nd, ns);
   return (int)hipGetLastError();
 }
 
-// dense GEMM gd and sparse GEMM gs in one launch (gemm_pair_kernel)
+// a dense and a sparse GEMM in one launch (gemm_pair_kernel), or two such sets of the same sizes; b is read with sets == 2 only
 template <class Epi, bool F8 = false>
-static int launch_gemm_pair(const GemmArgs& gd, const typename Epi::Args& ead, const GemmArgs& gs_in, const typename Epi::Args& eas, hipStream_t s) {
-  GemmArgs gs = gs_in;
-  gs.clk = tl_gemm_clk;
-  switch (pick_pair_tile(F8, gd.M, gs.M, gs.N, gs.K)) {
-    case 0: return launch_pair_tile<Epi, F8, 4, 4>(gd, ead, gs, eas, s);
-    case 1: return launch_pair_tile<Epi, F8, 4, 2>(gd, ead, gs, eas, s);
-    case 2: return launch_pair_tile<Epi, F8, 2, 2>(gd, ead, gs, eas, s);
-    case 3: return launch_pair_tile<Epi, F8, 2, 1>(gd, ead, gs, eas, s);
-    default: return launch_pair_tile<Epi, F8, 1, 1>(gd, ead, gs, eas, s);
+static int launch_gemm_pair(const PairSet<Epi>& a_in, const PairSet<Epi>& b, int sets, hipStream_t s) {
+  PairSet<Epi> a = a_in;
+  a.gs.clk = tl_gemm_clk;
+  switch (pick_pair_tile(F8, a.gd.M, a.gs.M, a.gs.N, a.gs.K, sets)) {
+    case 0: return launch_pair_tile<Epi, F8, 4, 4>(a, b, sets, s);
+    case 1: return launch_pair_tile<Epi, F8, 4, 2>(a, b, sets, s);
+    case 2: return launch_pair_tile<Epi, F8, 2, 2>(a, b, sets, s);
+    case 3: return launch_pair_tile<Epi, F8, 2, 1>(a, b, sets, s);
+    default: return launch_pair_tile<Epi, F8, 1, 1>(a, b, sets, s);
   }
 }
 
