@@ -428,89 +428,89 @@ int launch_featurewise24_split(const void* Hc, const uint8_t* meta, const void* 
 }
 
 // Feature partition of the split weight-gradient GEMMs (Sec. 2, "Optimization 1", where the paper sorts the features by their statistic).
-// Only the set matters, so no sort: the threshold count c* = the smallest c with #{nnz > c} <= n_dense is found by
-// bisection over the counts (which sit in LDS); every feature above it is dense, and of those equal to it the first
-// (n_dense - #above) by index.  Sparse features become rows 0 .. F - n_dense - 1, dense ones the rows after, both in
-// ascending feature order.  One workgroup of 1024; F <= 2^20 (beyond 32768 features the counts stay in global memory).
+// Only the set matters, so no sort: the threshold count c* = the smallest c with #{nnz > c} <= n_dense is found with a histogram of
+// the counts' top 11 bits, summed from the top, and one of the remaining bits inside the bin that c* falls into; every feature above
+// c* is dense, and of those equal to it the first (n_dense - #above) by index.  Sparse features become rows 0 .. F - n_dense - 1,
+// dense ones the rows after, both in ascending feature order.  One workgroup of 1024; F <= 2^20 (beyond 32768 features the counts
+// stay in global memory).  What bounds it is the chain of block-wide steps, each a few hundred cycles whatever it adds up: three or
+// four here against one for each bit of the token count and three more when c* was found by bisection (F = 8192, T = 8192: 23.7 us
+// with bisection, 14.6 now).
 // In LDS count f sits at word f + f / 32: the ranking passes give every thread a run of consecutive features, and without the
 // padding the lanes' runs would start a multiple of 32 words apart, all in two banks.  The rows are first written over the counts
 // in LDS and leave in feature order, so that the stores to row_of_feat are whole lines and those to feat_of_row nearly so.
-constexpr int PART_LDS_FEATS = 32768;
+constexpr int PART_LDS_FEATS = 32768, PART_BINS = 2048;   // one workgroup of 1024: two bins a thread
 __device__ __forceinline__ int part_slot(int f) { return f + (f >> 5); }
 
 template <bool IN_LDS>
 __global__ void __launch_bounds__(1024) split_partition_kernel(const uint32_t* __restrict__ nnz_g, int F, int n_dense, uint32_t max_count,
                                                                int* __restrict__ row_of_feat, int* __restrict__ feat_of_row) {
   extern __shared__ uint32_t s_nnz[];                // F counts if they fit
-  __shared__ int s_part[16];
-  __shared__ int s_total;
+  __shared__ uint32_t s_part[16];
+  __shared__ int s_bin, s_above;
+  __shared__ uint32_t s_hist[PART_BINS];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   constexpr bool in_lds = IN_LDS;
-  if (in_lds) for (int f = tid; f < F; f += 1024) s_nnz[part_slot(f)] = nnz_g[f];
-  __syncthreads();
-  auto nnz = [&](int f) { return in_lds ? s_nnz[part_slot(f)] : nnz_g[f]; };
-  // block-wide sum, and exclusive prefix over threads, of one int per thread (wave shuffles + 16 partials in LDS)
-  auto block_scan = [&](int v, int& total) {
-    int incl = v;
+  if (in_lds) for (int f = tid; f < F; f += 1024) s_nnz[part_slot(f)] = min(nnz_g[f], max_count);
+  auto nnz = [&](int f) { return in_lds ? s_nnz[part_slot(f)] : min(nnz_g[f], max_count); };   // every count indexes the histogram
+  // block-wide exclusive prefix over threads of one word per thread (wave shuffles + 16 partials in LDS)
+  auto block_scan = [&](uint32_t v) {
+    uint32_t incl = v;
 #pragma unroll
     for (int st = 1; st < 64; st <<= 1) {
-      int o = __shfl_up(incl, st, 64);
+      const uint32_t o = (uint32_t)__shfl_up((int)incl, st, 64);
       if (lane >= st) incl += o;
     }
     if (lane == 63) s_part[wave] = incl;
     __syncthreads();
-    if (tid == 0) {
-      int run = 0;
-      for (int w = 0; w < 16; w++) { int x = s_part[w]; s_part[w] = run; run += x; }
-      s_total = run;
-    }
-    __syncthreads();
-    int excl = s_part[wave] + incl - v;
-    total = s_total;
-    __syncthreads();
-    return excl;
-  };
-  // block-wide sum alone (the bisection needs no prefix): wave shuffles, 16 partials in LDS that every thread adds up itself
-  auto block_sum = [&](int v) {
+    uint32_t before = 0u;
 #pragma unroll
-    for (int st = 1; st < 64; st <<= 1) v += __shfl_xor(v, st, 64);
-    if (lane == 0) s_part[wave] = v;
+    for (int w = 0; w < 16; w++) before += w < wave ? s_part[w] : 0u;
     __syncthreads();
-    int total = 0;
-#pragma unroll
-    for (int w = 0; w < 16; w++) total += s_part[w];
-    __syncthreads();
-    return total;
+    return before + incl - v;
   };
-  // bisection: invariant #{nnz > hi} <= n_dense and (lo == -1 or #{nnz > lo} > n_dense); strided accesses here
-  int lo = -1, hi = (int)max_count;              // no count exceeds max_count (the number of tokens, at most 2^20)
-  while (hi - lo > 1) {
-    int mid = (lo + hi) >> 1;
-    int c = 0;
-    for (int f = tid; f < F; f += 1024) c += (int)nnz(f) > mid;
-    if (block_sum(c) <= n_dense) hi = mid; else lo = mid;
+  // the bin in which the number of features above it passes n_dense, with `base` of them above all bins, and how many are above the bin:
+  // thread t adds up bins 2047 - 2 t and 2046 - 2 t, and exactly one thread finds it (more than n_dense features in all)
+  auto find_bin = [&](int base, int& bin, int& above) {
+    __syncthreads();
+    const int top = PART_BINS - 1 - 2 * tid, h0 = (int)s_hist[top], h1 = (int)s_hist[top - 1];
+    const int a0 = base + (int)block_scan((uint32_t)(h0 + h1)), a1 = a0 + h0;
+    if (a0 <= n_dense && a1 > n_dense) { s_bin = top; s_above = a0; }
+    if (a1 <= n_dense && a1 + h1 > n_dense) { s_bin = top - 1; s_above = a1; }
+    __syncthreads();
+    bin = s_bin; above = s_above;
+  };
+  // no count exceeds max_count (the number of tokens, at most 2^20), so at most 10 bits are left below the first histogram
+  const int bits = 32 - __clz((int)max_count), shift = bits > 11 ? bits - 11 : 0;
+  s_hist[tid] = s_hist[tid + 1024] = 0u;
+  __syncthreads();
+  for (int f = tid; f < F; f += 1024) atomicAdd(&s_hist[nnz(f) >> shift], 1u);
+  int bin, n_above;
+  find_bin(0, bin, n_above);
+  uint32_t cstar = (uint32_t)bin;
+  if (shift) {
+    s_hist[tid] = s_hist[tid + 1024] = 0u;
+    __syncthreads();
+    for (int f = tid; f < F; f += 1024) if ((int)(nnz(f) >> shift) == bin) atomicAdd(&s_hist[nnz(f) & ((1u << shift) - 1u)], 1u);
+    int low;
+    find_bin(n_above, low, n_above);
+    cstar = ((uint32_t)bin << shift) | (uint32_t)low;
   }
-  const uint32_t cstar = (uint32_t)hi;
   // consecutive features per thread from here on, so that ranks follow the feature index
   const int per = (F + 1023) / 1024;
   const int f_lo = min(tid * per, F), f_hi = min(f_lo + per, F);
   int above = 0, equal = 0;
   for (int f = f_lo; f < f_hi; f++) { above += nnz(f) > cstar; equal += nnz(f) == cstar; }
-  int n_above, n_equal;
-  block_scan(above, n_above);
   const int take_eq = n_dense - n_above;             // how many of the features equal to c* become dense (by index)
-  const int eq_before = block_scan(equal, n_equal);
-  int dense_here = 0;
-  {
-    int e = eq_before;
-    for (int f = f_lo; f < f_hi; f++) {
-      bool d = nnz(f) > cstar || (nnz(f) == cstar && e < take_eq);
-      e += nnz(f) == cstar;
-      dense_here += d;
-    }
+  int eq_before, above_before;
+  if constexpr (in_lds) {                            // at most 32768 features: both prefixes fit one word
+    static_assert(PART_LDS_FEATS < 65536, "two 16-bit prefixes");
+    const uint32_t both = block_scan((uint32_t)above | ((uint32_t)equal << 16));
+    above_before = (int)(both & 0xFFFFu); eq_before = (int)(both >> 16);
+  } else {
+    above_before = (int)block_scan((uint32_t)above);
+    eq_before = (int)block_scan((uint32_t)equal);
   }
-  int n_d;
-  const int d_before = block_scan(dense_here, n_d);
+  const int d_before = above_before + min(eq_before, take_eq);
   const int n_sparse = F - n_dense;
   int e = eq_before, dpos = d_before;
   for (int f = f_lo; f < f_hi; f++) {

@@ -120,6 +120,29 @@ def test_tiles_split(F24, T, D, Fh):
     P._check_split(F24, T, D, Fh, "per_feature", T + D + Fh, 256)
 
 
+@pytest.mark.parametrize("T,Fh,n_dense", [(256, 1024, 256), (2048, 2048, 512), (16384, 1280, 256)])
+def test_split_partition_counts_with_ties(F24, T, Fh, n_dense):
+    """The partition on counts that need one and both levels of its histogram, with every count shared by several features and with one
+    count for all of them: the oracle's set, exactly (ties by feature index)."""
+    g = torch.Generator().manual_seed(T + Fh)
+    X = torch.randn(T, 256, generator=g).bfloat16().cuda()
+    W1 = torch.randn(256, Fh // 8, generator=g).mul(1 / 16).repeat(1, 8).bfloat16().cuda()
+    b1 = torch.linspace(-2, 2, Fh // 8).repeat(8).cuda()
+    W2 = torch.randn(Fh, 256, generator=g).bfloat16().cuda()
+    for bias in (b1, torch.full_like(b1, -1e4), torch.full_like(b1, 1e4)):
+        print(f"split partition T={T} F={Fh} dense {n_dense} bias {float(bias[0])}", flush=True)
+        ctx = F24.Context(T, 256, Fh, F24.FFN24_TRAINING | F24.FFN24_SPLIT)
+        ctx.set_split(n_dense)
+        ctx.ffn24_fwd(X, W1, bias, W2)
+        ctx.ffn24_bwd(X)
+        torch.cuda.synchronize()
+        nnz = ctx.saved("nnz").cpu().numpy().astype(np.int64)
+        assert len(np.unique(nnz)) <= Fh // 8
+        dense = O.split_features(nnz, n_dense)
+        assert np.array_equal(ctx.saved("feat_of_row").cpu().numpy(), np.concatenate([np.flatnonzero(~dense), np.flatnonzero(dense)]))
+        ctx.close()
+
+
 def test_tiles_telemetry_counts(F24):
     """Counting epilogues on the smaller tiles: the counts equal those of the tensors the GPU stored."""
     for T, D, Fh in SHAPES[:3]:
