@@ -5,6 +5,7 @@
 #pragma once
 #include "gemm_core.hpp"
 #include "launch.hpp"
+#include "tile_rule.hpp"
 
 namespace ffn24 {
 
@@ -487,6 +488,7 @@ struct ExactDiv {
 //   bf16 panel form -- what the backward takes the activation's derivative from (the e4m3 code of h keeps 4
 //   significant bits, too few for 2 sqrt(h)).
 struct EpiPrune24F8 {
+  static constexpr EpiCost COST = EPI_FP8;
   struct Args { uint8_t* Hc8; uint8_t* meta; __bf16* Hdbg; const float* b1; int F; float zscale; float sh; __bf16* Hc16; uint8_t* meta16; };
   template <int MI, int NI>
   static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
@@ -543,6 +545,7 @@ struct EpiPrune24F8 {
 // form); the result is quantised, e4m3(dZ / sdz) (saturating), and stored compressed with the forward's metadata in
 // the fp8 panel form (the operand of the sparse dX GEMM).
 struct EpiDGatherF8 {
+  static constexpr EpiCost COST = EPI_FP8;
   struct Args { const __bf16* Hc16; const uint8_t* meta16; uint8_t* dZc8; int F; float scale; float sdz; };
   template <int MI, int NI>
   static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
@@ -628,6 +631,7 @@ struct RowMax {
 // STATS: also the per-feature non-zero counts of the activation before pruning, into nnz [F] (as in EpiPrune24T).
 template <bool STATS>
 struct EpiPrune24RwT {
+  static constexpr EpiCost COST = EPI_FP8;
   struct Args { __bf16* Hc; uint8_t* meta; __bf16* Hdbg; const float* b1; int F; const float* sx; const float* sw1; uint32_t* rowmax; uint32_t* nnz; };
   template <int MI, int NI>
   static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
@@ -692,6 +696,7 @@ using EpiPrune24Rw = EpiPrune24RwT<false>;
 // Ht16 (optional, a training context): the same values once more as the bf16 [F][T] operand (dense panel form, K = T) that the
 // backward quantises per hidden feature for its dW2 GEMM.
 struct EpiRelu2Rw {
+  static constexpr EpiCost COST = EPI_FP8_SPILLS;
   struct Args { __bf16* H16; const float* b1; int F; const float* sx; const float* sw1; uint32_t* rowmax; __bf16* Ht16; int T; };
   template <int MI, int NI>
   static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
@@ -747,6 +752,7 @@ struct EpiRelu2Rw {
 // bf16 panel form), at every position.  Stored in bf16 twice, as the [T][F] and the [F][T] operand (dense panel forms) that
 // streaming kernels then quantise per token and per hidden feature; rowmax[t] is raised to the largest magnitude word of the row.
 struct EpiDReluRw {
+  static constexpr EpiCost COST = EPI_FP8;
   struct Args { const __bf16* H16; __bf16* dZ16; __bf16* dZt16; int F; int T; const float* rs; const float* cs; uint32_t* rowmax; };
   template <int MI, int NI>
   static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
@@ -883,6 +889,7 @@ struct EpiColMajorRowCol {
 // -- so it is written as bf16, compressed with the forward's metadata (dZc16, bf16 panel form), and every lane raises
 // rowmax[t] to the largest magnitude word of its part of the row; a streaming kernel then quantises with rowmax[t] / 448.
 struct EpiDGatherRw {
+  static constexpr EpiCost COST = EPI_FP8;
   struct Args { const __bf16* Hc16; const uint8_t* meta16; __bf16* dZc16; int F; const float* rs; const float* cs; uint32_t* rowmax; };
   template <int MI, int NI>
   static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
@@ -934,6 +941,7 @@ struct EpiDGatherRw {
 // backward takes the derivative from it) and the codes once more as the [F][T] operand of the weight-gradient GEMM that
 // reduces over tokens (dense fp8 panel form).
 struct EpiRelu2F8 {
+  static constexpr EpiCost COST = EPI_FP8;
   struct Args { uint8_t* H8; const float* b1; int F; float zscale; float sh; __bf16* H16; uint8_t* H8t; int T; };
   template <int MI, int NI>
   static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
@@ -985,6 +993,7 @@ struct EpiRelu2F8 {
 // the bf16 activation the dense forward saved (H16, dense bf16 panel form); stored as e4m3(dZ / sdz) twice: the [T][F]
 // operand of the dX GEMM and the [F][T] operand of the dW1 GEMM (dense fp8 panel forms).
 struct EpiDReluF8 {
+  static constexpr EpiCost COST = EPI_FP8;
   struct Args { const __bf16* H16; uint8_t* dZ8; uint8_t* dZ8t; int F; int T; float scale; float sdz; };
   template <int MI, int NI>
   static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {

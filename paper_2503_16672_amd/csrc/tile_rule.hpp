@@ -1,0 +1,64 @@
+// Which block tile a GEMM takes (host code, no HIP: the rule compiles by itself).
+#pragma once
+
+namespace ffn24 {
+
+// The 256 x 256 tile does the least operand traffic per matrix op, but a shape with fewer than 256 of them leaves CUs idle and one
+// with, say, 300 makes half of them do two while the others wait; the smaller tiles cost more per output element and spread better.
+// The rule estimates, for every tile, (tiles a CU gets, rounded up) x (K x time per k + time of fill and epilogue) and takes the least,
+// preferring the larger tile within 3 %.  A stage of an fp8 kernel holds twice the k in the same bytes and time.
+// The constants are effective ones: fitted to whole steps in a sustained loop on one MI355X (a round of 256 x 256 tiles runs at the power
+// limit there, and a last round that leaves CUs idle at a higher clock, which single launches do not show), with one GEMM at a time taken
+// off the 256 x 256 tile, over 136 shapes: T 256-16384, D 256-5632, F 1024-16384, 0.08 to 6.8 rounds of 256 x 256 tiles in the up-projection,
+// bf16 and both fp8 recipes, 2:4 and dense.  Against the library without smaller tiles, 278 of 279 steps and forwards at 40 shapes that were
+// not fitted (0.03 to 8 rounds, seven kinds) take at most 0.8 % longer, and the mean is 1.34 x faster.  What it avoids: a bf16 step at T 2304
+// D 4864 F 15616 (2.1 rounds) is 2-3 % longer with 256 x 128 up-projection and dH than with 256 x 256.
+struct TileCost { int mi, ni, per_k, fixed; };   // 0.1 ns per (bf16) k; ns per tile
+constexpr TileCost TILES_SPARSE[] = {{4, 4, 140, 6000}, {4, 2, 92, 5000}, {2, 2, 57, 3000}, {2, 1, 39, 2000}, {1, 1, 26, 1500}};
+constexpr TileCost TILES_DENSE[] = {{4, 4, 205, 19000}, {4, 2, 132, 5000}, {2, 2, 84, 1750}, {2, 1, 52, 2000}, {1, 1, 34, 1000}};
+constexpr int NUM_TILES = 5;   // the two tables list the same tiles
+constexpr long long CHIP_CUS = 256;
+
+// What an epilogue adds to the fill and store of the two largest dense tiles (ns).  The fp8 epilogues scale or quantise every value beside
+// 256 accumulators, and half the reduction time covers it less; the dense row-wise one spills 44 registers on the 256 x 128 tile, which
+// made that tile 4-15 us dearer than 256 x 256 at 1.8-2.6 rounds.
+struct EpiCost { int t256x256, t256x128; };
+constexpr EpiCost EPI_PLAIN = {0, 0}, EPI_FP8 = {3000, 0}, EPI_FP8_SPILLS = {3000, 8000};
+
+inline long long tile_time(const TileCost& t, int K, bool f8) { return (long long)(f8 ? K / 2 : K) * t.per_k / 10 + t.fixed; }
+inline long long tile_count(const TileCost& t, int M, int N) { return (long long)(M / (64 * t.mi)) * (N / (64 * t.ni)); }
+
+inline int pick_tile(bool sparse, bool f8, EpiCost epi, int M, int N, int K, int gemms = 1) {   // gemms: that many of this size share the launch
+  int best = 0;
+  long long best_time = 0;
+  for (int i = 0; i < NUM_TILES; i++) {
+    const TileCost& t = sparse ? TILES_SPARSE[i] : TILES_DENSE[i];
+    const long long one = tile_time(t, K, f8) + (i == 0 ? epi.t256x256 : i == 1 ? epi.t256x128 : 0);
+    const long long time = (gemms * tile_count(t, M, N) + CHIP_CUS - 1) / CHIP_CUS * one;
+    if (i == 0 || time * 100 < best_time * 97) { best = i; best_time = time; }
+  }
+  return best;
+}
+
+// The same for a dense and a sparse GEMM in one launch (same N and K, the dense tiles first), `sets` times: all tiles over the CUs, but no
+// less than the dense ones take by themselves (their epilogue is a plain store, and their tiles share CUs with sparse ones instead of
+// running in full rounds: the time per k of single launches).  The two parts make the estimate rougher, so a
+// smaller tile has to promise 10 % (fp8, T 8192 D 2048 F 8192, 512 dense features: 98.4 us with 256 x 256 and 99.0 with 256 x 128, which
+// the estimate puts 7 % ahead).
+constexpr int PAIR_DENSE_PER_K[] = {205, 125, 74, 52, 34};
+inline int pick_pair_tile(bool f8, int Md, int Ms, int N, int K, int sets) {
+  int best = 0;
+  long long best_time = 0;
+  for (int i = 0; i < NUM_TILES; i++) {
+    const long long nd = sets * tile_count(TILES_DENSE[i], Md, N), ns = sets * tile_count(TILES_SPARSE[i], Ms, N);
+    const long long ts = tile_time(TILES_SPARSE[i], K, f8), td = tile_time({0, 0, PAIR_DENSE_PER_K[i], TILES_SPARSE[i].fixed}, K, f8);
+    long long time = (nd + ns + CHIP_CUS - 1) / CHIP_CUS * ts;
+    const long long dense = (nd + CHIP_CUS - 1) / CHIP_CUS * td, even = (nd * td + ns * ts) / CHIP_CUS;
+    time = time > dense ? time : dense;
+    time = time > even ? time : even;
+    if (i == 0 || time * 100 < best_time * 90) { best = i; best_time = time; }
+  }
+  return best;
+}
+
+}  // namespace ffn24
