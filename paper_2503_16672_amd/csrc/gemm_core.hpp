@@ -396,8 +396,11 @@ __device__ __forceinline__ void mfma_sparse1(const FragS<MI, NI>& f, const IdxWo
 // the others find in the memory-side cache.  Measured against one 8 x 4 patch per XCD with all XCDs side by side
 // along M (every round then streams the whole A operand): 3.5 % on the sparse GEMMs, nothing on the dense ones.
 // Tile-rows beyond the last whole round (ntm not a multiple of 32: the sparse part of a split weight gradient) and shapes whose
-// tile-columns the grid does not divide fall back to bands of 8 tile-rows, each XCD a contiguous run of tiles.
-template <int PROBE = 0>
+// tile-columns the grid does not divide fall back to bands of 8 tile-rows, each XCD a contiguous run of tiles: of 4 tile-rows if a tile
+// is twice as tall as wide (256 x 128, 128 x 64), so that an XCD's 32 tiles still cover a square of the result (a bf16 step at T 4864 D 3328
+// F 7680, dense GEMMs on 256 x 128: 1115 -> 1092 us, 1099 with 256 x 256; T 11008 D 1536 F 5120 dense 989 -> 971).  The rounds keep
+// their patch of 8 x 4 tiles for it: 4 x 8 costs 1.5 % at T 4096 D 2048 F 8192.
+template <int PROBE = 0, bool TALL = false>
 __device__ __forceinline__ void tile_coords(int ntm, int ntn, int pid, int& tm, int& tn) {
   // XCD grid, patch shape; GX * GY = 8 XCDs, PM * PN = 32 CUs
   constexpr int GX = (PROBE & PROBE_WALK_8x1) ? 8 : 4, GY = 8 / GX;
@@ -416,7 +419,7 @@ __device__ __forceinline__ void tile_coords(int ntm, int ntn, int pid, int& tm, 
   ntm -= tm0;
   int nb = ntm * ntn;
   if ((nb & 7) == 0) pid = (pid & 7) * (nb >> 3) + (pid >> 3);
-  const int GROUP = 8;
+  const int GROUP = TALL ? 4 : 8;
   int per_group = GROUP * ntn;
   int gid = pid / per_group;
   int first = gid * GROUP;
@@ -476,7 +479,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
   int tid = threadIdx.x;
   int lane = tid & 63, wave = tid >> 6;
   int tm, tn;
-  tile_coords<PROBE>(g.M / G::BM, g.N / G::BN, pid, tm, tn);
+  tile_coords<PROBE, MI == 2 * NI>(g.M / G::BM, g.N / G::BN, pid, tm, tn);
   int m0 = tm * G::BM, n0 = tn * G::BN;
 
   LaneCtx L;
@@ -697,7 +700,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
       // every wave has read its last fragments: the ring is free for the next tile's first stages, which then land while
       // the epilogue runs
       __builtin_amdgcn_s_barrier();
-      tile_coords<PROBE>(g.M / G::BM, g.N / G::BN, pid, tm, tn);
+      tile_coords<PROBE, MI == 2 * NI>(g.M / G::BM, g.N / G::BN, pid, tm, tn);
       m0 = tm * G::BM; n0 = tn * G::BN;
       dma.init(g, m0, n0, tid);
       for (int s = 0; s < npro; s++) static_for<NDMA>([&](auto J) { dma.template issue<J>(s, smem + s * G::STAGE); });
