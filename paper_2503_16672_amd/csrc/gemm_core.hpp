@@ -150,10 +150,10 @@ struct Geo {
 // belongs to lane half hc, M-tile mi, register v, and wave-tile column NI c + ni to lane column c, N-tile ni)
 template <int MI>
 __device__ __forceinline__ int unperm_m(int p) {
-  return (p & ~(32 * MI - 1)) | (((p >> 2) & 1) * (16 * MI)) | (((p >> 5) & (MI - 1)) << 4) | (((p >> 3) & 3) << 2) | (p & 3);
+  return (p & (32 * MI)) | (((p >> 2) & 1) * (16 * MI)) | (((p >> 5) & (MI - 1)) << 4) | (((p >> 3) & 3) << 2) | (p & 3);
 }
 template <int NI>
-__device__ __forceinline__ int unperm_n(int p) { return (p & ~(32 * NI - 1)) | ((p & 31) * NI) | ((p >> 5) & (NI - 1)); }
+__device__ __forceinline__ int unperm_n(int p) { return (p & (32 * NI)) | ((p & 31) * NI) | ((p >> 5) & (NI - 1)); }
 // 16-byte chunk swizzles.  A 16-byte-per-lane LDS read of a wavefront is served 16 lanes per clock, and the lanes
 // that share a clock are not consecutive: {0-3, 20-23} and {4-7, 16-19} each pair up with {8-11, 28-31} or
 // {12-15, 24-27} (likewise +32); they must hit 16 different 16-byte slots of the 256-byte bank row (measured on
@@ -202,10 +202,14 @@ struct Dma {
     // starts m0 % 256 (n0 % 256) rows into such a block.
     const bool panel = g.a_panel != 0, bp = g.b_panel != 0;
     const uint32_t a_pitch = panel ? 64u : a_row, m_pitch = panel ? (uint32_t)G::META_ROW : (uint32_t)(g.K / 8);
-    const int mb = m0 & ~255, ma = m0 & 255, nb = bp ? n0 & ~255 : n0, na = bp ? n0 & 255 : 0;
-    a = static_cast<const char*>(g.A) + (size_t)mb * a_row + (size_t)ma * a_pitch;
+    const int ma = MI == 4 ? 0 : m0 & 255, mb = m0 - ma, na = NI == 4 || !bp ? 0 : n0 & 255, nb = n0 - na;
+    a = static_cast<const char*>(g.A) + (size_t)mb * a_row;
+    am = SPARSE ? reinterpret_cast<const char*>(g.Ameta) + (size_t)mb * (g.K / 8) : nullptr;
+    if constexpr (MI < 4) {
+      a += (size_t)ma * a_pitch;
+      if constexpr (SPARSE) am += (size_t)ma * m_pitch;
+    }
     b = static_cast<const char*>(g.B) + (g.b_rowmap ? (size_t)0 : (size_t)nb * b_row);
-    am = SPARSE ? reinterpret_cast<const char*>(g.Ameta) + (size_t)mb * (g.K / 8) + (size_t)ma * m_pitch : nullptr;
     a_stage = panel ? 256u * 64u : 64u;
     m_stage = panel ? 256u * G::META_ROW : (uint32_t)G::META_ROW;
     b_stage = bp ? 256u * (uint32_t)G::B_ROW : (uint32_t)G::B_ROW;
@@ -279,8 +283,9 @@ struct Dma {
 struct LaneCtx {
   int rho, h;       // lane & 31, lane >> 5
   int wy, wx;       // wave row / column inside the block tile
-  int a_row;        // LDS row of the lane in the wave's first 32 rows of A
-  int b_row;        // ... of B
+  int a_row64;      // byte offset of the lane's LDS row among the wave's first 32 rows of A (64-byte rows)
+  int b_row64;      // ... of B, 64-byte rows
+  int b_row128;     // ... of B, 128-byte rows
   int sw4;          // swz4 of the lane's row (the same for every 32-row tile)
   int sw8;          // swz8 of the lane's B row for even ni (odd ni: ^4)
 };
@@ -294,8 +299,8 @@ template <class G, int S, int I, int PROBE, int MI, int NI>
 __device__ __forceinline__ void load_frag_dense1(const char* buf, const LaneCtx& L, FragD<MI, NI>& f) {
   if constexpr ((PROBE & PROBE_NO_FRAG) != 0) return;
   int c = ((2 * S + L.h) ^ L.sw4) << 4;
-  if constexpr (I < MI) f.a[I] = *reinterpret_cast<const bf16x8*>(buf + L.a_row * 64 + I * (32 * 64) + c);
-  else f.b[I - MI] = *reinterpret_cast<const bf16x8*>(buf + G::B_OFF + L.b_row * 64 + (I - MI) * (32 * 64) + c);
+  if constexpr (I < MI) f.a[I] = *reinterpret_cast<const bf16x8*>(buf + L.a_row64 + I * (32 * 64) + c);
+  else f.b[I - MI] = *reinterpret_cast<const bf16x8*>(buf + G::B_OFF + L.b_row64 + (I - MI) * (32 * 64) + c);
 }
 template <int M, int PROBE, int MI, int NI>
 __device__ __forceinline__ void mfma_dense1(const FragD<MI, NI>& f, f32x16 (&acc)[MI][NI]) {
@@ -347,7 +352,7 @@ struct FragS {
 template <bool F8> struct IdxWords { uint32_t w[F8 ? 2 : 1]; };
 template <class G, bool F8, int I, int MI>
 __device__ __forceinline__ void load_idx_sparse1(const char* buf, const LaneCtx& L, IdxWords<F8> (&idx)[MI]) {
-  const char* p = buf + G::META_OFF + (L.a_row + 32 * I) * G::META_ROW;
+  const char* p = buf + G::META_OFF + (L.wy * (32 * MI) + L.rho + 32 * I) * G::META_ROW;
   if constexpr (F8) {
     u32x2 v = *reinterpret_cast<const u32x2*>(p + 8 * L.h);
     idx[I].w[0] = v[0]; idx[I].w[1] = v[1];
@@ -360,11 +365,11 @@ template <class G, int S, int I, int PROBE, int MI, int NI>
 __device__ __forceinline__ void load_frag_sparse1(const char* buf, const LaneCtx& L, FragS<MI, NI>& f) {
   if constexpr ((PROBE & PROBE_NO_FRAG) != 0) return;
   if constexpr (I < MI) {
-    f.a[I] = *reinterpret_cast<const bf16x8*>(buf + L.a_row * 64 + I * (32 * 64) + (((2 * L.h + S) ^ L.sw4) << 4));
+    f.a[I] = *reinterpret_cast<const bf16x8*>(buf + L.a_row64 + I * (32 * 64) + (((2 * L.h + S) ^ L.sw4) << 4));
   } else {
     constexpr int i = (I - MI) % NI;
     int sw = L.sw8 ^ ((i & 1) << 2);
-    const char* row = buf + G::B_OFF + L.b_row * 128 + i * (32 * 128);
+    const char* row = buf + G::B_OFF + L.b_row128 + i * (32 * 128);
     if constexpr (I < MI + NI) f.blo[i] = *reinterpret_cast<const bf16x8*>(row + (((2 * S + L.h) ^ sw) << 4));
     else f.bhi[i] = *reinterpret_cast<const bf16x8*>(row + (((4 + 2 * S + L.h) ^ sw) << 4));
   }
@@ -484,10 +489,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
 
   LaneCtx L;
   L.rho = lane & 31; L.h = lane >> 5; L.wy = wave >> 1; L.wx = wave & 1;
-  L.a_row = L.wy * (32 * MI) + L.rho;
-  L.b_row = L.wx * (32 * NI) + L.rho;
+  L.a_row64 = (L.wy * (32 * MI) + L.rho) * 64;
+  L.b_row64 = (L.wx * (32 * NI) + L.rho) * 64;
+  L.b_row128 = (L.wx * (32 * NI) + L.rho) * 128;
   L.sw4 = swz4(L.rho);
-  L.sw8 = swz8(L.b_row);
+  L.sw8 = NI == 1 ? swz8(L.wx * 32 + L.rho) : swz8(L.rho);   // (from NI = 2 on the wave column moves the row by a multiple of 64, which the swizzle does not see)
 
   Dma<SPARSE, F8, PROBE, MI, NI> dma;
   dma.init(g, m0, n0, tid);
