@@ -52,8 +52,8 @@ template <bool SPARSE, class EpiA, class EpiB, bool F8 = false>
 static int launch_gemm_duo(const GemmArgs& ga, const typename EpiA::Args& ea, const GemmArgs& gb, const typename EpiB::Args& eb, hipStream_t s) {
   const int tile = pick_tile(SPARSE, F8, EPI_PLAIN, ga.M, ga.N, ga.K, 2);
   if (tile == 0 && tile_count(TILES_SPARSE[0], ga.M, ga.N) % CHIP_CUS == 0) {
-    const int rc = launch_gemm<SPARSE, EpiA, F8>(ga, ea, s);
-    return rc ? rc : launch_gemm<SPARSE, EpiB, F8>(gb, eb, s);
+    const int rc = launch_tile<SPARSE, EpiA, F8, 0, 4, 4>(ga, ea, s);   // (the tile one of them takes alone, too)
+    return rc ? rc : launch_tile<SPARSE, EpiB, F8, 0, 4, 4>(gb, eb, s);
   }
   switch (tile) {
     case 0: return launch_duo_tile<SPARSE, EpiA, EpiB, F8, 4, 4>(ga, ea, gb, eb, s);

@@ -64,3 +64,26 @@ def picks(tmp_path_factory):
 @pytest.mark.parametrize("i", range(len(MEASURED)), ids=["-".join(str(x) for x in q) for q, _ in MEASURED])
 def test_tile_of_measured_shapes(picks, i):
     assert picks[i] in MEASURED[i][1]
+
+
+def test_two_full_gemms_take_the_large_tile_alone_too(tmp_path):
+    """Where two GEMMs together take the 256 x 256 tile and each fills whole rounds with it, they are launched apart with that tile: one of
+    them by itself has to pick it as well."""
+    if not shutil.which("g++"):
+        pytest.skip("no host compiler")
+    (tmp_path / "main.cpp").write_text("""
+#include "%s"
+using namespace ffn24;
+int main() {
+  int seen = 0;
+  for (int sparse = 0; sparse < 2; sparse++) for (int f8 = 0; f8 < 2; f8++)
+    for (int M = 256; M <= 32768; M += 256) for (int N = 256; N <= 8192; N += 256) for (int K = 256; K <= 16384; K += 768) {
+      if (tile_count(TILES_SPARSE[0], M, N) %% CHIP_CUS || pick_tile(sparse, f8, EPI_PLAIN, M, N, K, 2) != 0) continue;
+      seen++;
+      if (pick_tile(sparse, f8, EPI_PLAIN, M, N, K, 1) != 0) return 1;
+    }
+  return seen ? 0 : 2;
+}
+""" % RULE)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-o", str(tmp_path / "main"), str(tmp_path / "main.cpp")], check=True)
+    assert subprocess.run([str(tmp_path / "main")]).returncode == 0
