@@ -46,12 +46,12 @@ static int launch_duo_tile(const GemmArgs& ga, const typename EpiA::Args& ea, co
   return (int)hipGetLastError();
 }
 
-// Two GEMMs of the same M, N, K and operand forms (gemm_duo_kernel), with the tile that suits both together.  Where that is the 256 x 256
-// tile and each of them fills the chip by itself, there is nothing to gain and they go out one after the other.
+// Two GEMMs of the same M, N, K and operand forms (gemm_duo_kernel), with the tile that suits both together.
 template <bool SPARSE, class EpiA, class EpiB, bool F8 = false>
 static int launch_gemm_duo(const GemmArgs& ga, const typename EpiA::Args& ea, const GemmArgs& gb, const typename EpiB::Args& eb, hipStream_t s) {
   const int tile = pick_tile(SPARSE, F8, EPI_PLAIN, ga.M, ga.N, ga.K, 2);
-  if (tile == 0 && tile_count(TILES_SPARSE[0], ga.M, ga.N) % CHIP_CUS == 0) {
+  const long long n = tile_count(TILES_SPARSE[0], ga.M, ga.N);
+  if (tile == 0 && (n % CHIP_CUS == 0 || apart_is_better(F8, n, ga.K, 1))) {   // (whole rounds each: nothing to share)
     const int rc = launch_tile<SPARSE, EpiA, F8, 0, 4, 4>(ga, ea, s);   // (the tile one of them takes alone, too)
     return rc ? rc : launch_tile<SPARSE, EpiB, F8, 0, 4, 4>(gb, eb, s);
   }
@@ -80,6 +80,10 @@ static int launch_pair_tile(const PairSet<Epi>& a, const PairSet<Epi>& b, int se
 // a dense and a sparse GEMM in one launch (gemm_pair_kernel), or two such sets of the same sizes; b is read with sets == 2 only
 template <class Epi, bool F8 = false>
 static int launch_gemm_pair(const PairSet<Epi>& a_in, const PairSet<Epi>& b, int sets, hipStream_t s) {
+  if (sets == 2 && apart_is_better(F8, tile_count(TILES_DENSE[0], a_in.gd.M + a_in.gs.M, a_in.gs.N), a_in.gs.K, 2)) {
+    const int rc = launch_gemm_pair<Epi, F8>(a_in, a_in, 1, s);
+    return rc ? rc : launch_gemm_pair<Epi, F8>(b, b, 1, s);
+  }
   PairSet<Epi> a = a_in;
   a.gs.clk = tl_gemm_clk;
   switch (pick_pair_tile(F8, a.gd.M, a.gs.M, a.gs.N, a.gs.K, sets)) {

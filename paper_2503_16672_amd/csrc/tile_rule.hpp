@@ -40,7 +40,18 @@ inline int pick_tile(bool sparse, bool f8, EpiCost epi, int M, int N, int K, int
   return best;
 }
 
-// The same for a dense and a sparse GEMM in one launch (same N and K, the dense tiles first), `sets` times: all tiles over the CUs, but no
+// Two launches of n 256 x 256 tiles each (a weight gradient; with the split the dense and the sparse tiles of one) that could be one go out
+// one after the other where sharing saves no round of the chip and the reduction is long: the other's operands then no longer share the
+// L2 with the first's for as long as the launches overlap, and the gap between them is short beside them.  Measured, together -> apart:
+// K = T = 6912, 3.8 rounds each: bf16 step 3539 -> 3512 us, split 3655 -> 3616; K 3584, 2.6 rounds: 1384 -> 1367; K 7680, 1.6 rounds, fp8
+// row-wise: 1046 -> 1032.  Short reductions like one launch (K 256-2048, 1.9-3.8 rounds: 0.5-2.5 % of a step), fp8 up to K 5888.  With
+// the split whole rounds of tiles are together too: its dense tiles outlast their round (K 4096, 2 rounds: 1117 us, 1138 apart).
+inline bool apart_is_better(bool f8, long long n, int K, int min_rounds) {
+  const long long one = (n + CHIP_CUS - 1) / CHIP_CUS, both = (2 * n + CHIP_CUS - 1) / CHIP_CUS;
+  return n >= min_rounds * CHIP_CUS && n % CHIP_CUS != 0 && both == 2 * one && (f8 ? K : 2 * K) >= 6144;
+}
+
+// The tile of a dense and a sparse GEMM in one launch (same N and K, the dense tiles first), `sets` times: all tiles over the CUs, but no
 // less than the dense ones take by themselves (their epilogue is a plain store, and their tiles share CUs with sparse ones instead of
 // running in full rounds: the time per k of single launches).  The two parts make the estimate rougher, so a
 // smaller tile has to promise 10 % (fp8, T 8192 D 2048 F 8192, 512 dense features: 98.4 us with 256 x 256 and 99.0 with 256 x 128, which

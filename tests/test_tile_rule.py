@@ -87,3 +87,24 @@ int main() {
 """ % RULE)
     subprocess.run(["g++", "-std=c++17", "-O1", "-o", str(tmp_path / "main"), str(tmp_path / "main.cpp")], check=True)
     assert subprocess.run([str(tmp_path / "main")]).returncode == 0
+
+
+# fp8, 256 x 256 tiles of one launch, K, least rounds of one -> apart
+TOGETHER = [
+    ((0, 966, 6912, 1), 1), ((0, 966, 6912, 2), 1), ((0, 658, 3584, 1), 1), ((0, 720, 3584, 2), 1), ((1, 406, 7680, 1), 1),
+    ((0, 512, 4096, 2), 0), ((0, 256, 8192, 2), 0), ((0, 1024, 16384, 2), 0),      # whole rounds
+    ((0, 928, 1280, 2), 0), ((0, 980, 2048, 1), 0), ((1, 398, 5120, 1), 0),        # short reductions
+    ((0, 532, 5888, 2), 0), ((0, 1029, 8704, 1), 0),                               # a round saved together
+    ((0, 189, 8192, 1), 0),                                                        # less than a round each
+]
+
+
+def test_launches_apart(tmp_path):
+    if not shutil.which("g++"):
+        pytest.skip("no host compiler")
+    (tmp_path / "main.cpp").write_text('#include "%s"\n#include <cstdio>\nint main() { int f, n, K, r; while (std::scanf("%%d %%d %%d %%d", &f, &n, &K, &r) == 4) '
+                                       'std::printf("%%d\\n", ffn24::apart_is_better(f, n, K, r)); }\n' % RULE)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-o", str(tmp_path / "main"), str(tmp_path / "main.cpp")], check=True)
+    text = "\n".join(" ".join(str(x) for x in q) for q, _ in TOGETHER)
+    got = subprocess.run([str(tmp_path / "main")], input=text, capture_output=True, text=True, check=True).stdout.split()
+    assert [int(x) for x in got] == [a for _, a in TOGETHER]
