@@ -329,8 +329,10 @@ FFN24_API int ffn24_copy_saved(ffn24_ctx* ctx, int which, void* dst, int64_t dst
  * dW1 into [D][F] after a split (with a split, 5 and 6 are the combined sparse + dense launches of dW2 and dW1),
  * 17 the row-wise fp8 quantisation kernel of a forward, 18 the one of dZ in ffn24_bwd_rowwise, 19 its two quantisations of the
  * transposed operands, 20 its re-arrangement of the caller's W2_8r and dY8r (ffn_bwd_rowwise: also W1_8c) into the forms the GEMMs stream, 21 the same for
- * X8 in the forward of an fp8 context.  Returns FFN24_ERR_STATE if that kernel has not run
- * with profiling on. */
+ * X8 in the forward of an fp8 context (20 and 21 with the clears and gathers that share their launch).  Returns
+ * FFN24_ERR_STATE if that kernel has not run with profiling on.
+ * Profiling gives every weight gradient a launch of its own, so that 5 and 6 (11 and 12) can be told apart; without it the two share
+ * one wherever that is faster.  The results are the same bits; the sum of the kernel times is then more than an unprofiled step's. */
 FFN24_API int ffn24_set_profiling(ffn24_ctx* ctx, int on);
 FFN24_API int ffn24_kernel_ms(ffn24_ctx* ctx, int kernel, float* ms);
 /* The shader clock (MHz) GEMM kernel `kernel` of the most recent profiled call really ran at: the first 64 workgroups
