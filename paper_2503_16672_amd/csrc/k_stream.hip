@@ -975,7 +975,7 @@ template <int LANES, int NV>
 __global__ void __launch_bounds__(256) quantise_bf16_rows_kernel(const u32x4* __restrict__ X, int64_t R, int C8, u32x2* __restrict__ codes,
                                                                  float* __restrict__ scales) {
   const int t = threadIdx.x & (LANES - 1);
-  const int64_t r = (int64_t)blockIdx.x * (256 / LANES) + threadIdx.x / LANES;
+  const int64_t r = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * (256 / LANES) + threadIdx.x / LANES;
   if (r >= R) return;                                  // (whole waves; with LANES = 256 there is one row per workgroup)
   const u32x4* row = X + r * C8;
   u32x4 v[NV];
@@ -1114,7 +1114,9 @@ int launch_quantise_bf16(const void* X, int64_t R, int64_t C, int axis, void* co
     auto kern = C8 <= 64 * 2 ? quantise_bf16_rows_kernel<64, 2> : C8 <= 64 * 8 ? quantise_bf16_rows_kernel<64, 8>
               : C8 <= 256 * 8 ? quantise_bf16_rows_kernel<256, 8> : quantise_bf16_long_rows_kernel;
     const int per = C8 > 64 * 8 && C8 <= 256 * 8 ? 1 : 4;   // rows per workgroup
-    hipLaunchKernelGGL(kern, dim3((unsigned)((R + per - 1) / per)), dim3(256), 0, s, x, R, C8, out, scales);
+    // 2^24 rows, the most there can be, of a workgroup each are 2^32 work items, one more than a grid dimension may have: two halves then
+    const int64_t groups = (R + per - 1) / per, most = 1 << 23;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(groups < most ? groups : most), (unsigned)((groups + most - 1) / most)), dim3(256), 0, s, x, R, C8, out, scales);
     return (int)hipGetLastError();
   }
   // at most QC_SLABS slabs, each a whole number of QC_ROWS rows
