@@ -3,6 +3,7 @@
 // operand into K-contiguous form.
 #include "epilogues.hpp"
 #include "launch.hpp"
+#include "tile_rule.hpp"
 
 namespace ffn24 {
 
@@ -147,16 +148,17 @@ int launch_sparsify24(const void* H, int64_t rows, int64_t cols, void* vals, uin
 // Input: token-wise compressed Hc [T][F/2] + meta [T][F/8], and optionally dZc [T][F/2] with the same metadata.
 // Output: for every feature, groups of 4 consecutive tokens of the pruned activation keep their top-2:
 //   Hc_t [F][T/2], meta_t [F][T/8], and dZc_t [F][T/2] = dZ at the positions picked for H.
-// Inputs and outputs in the panel form of gemm_core.hpp (a caller's row-major tensors: featurewise24_rows_kernel below).
+// Inputs and outputs in the panel form of gemm_core.hpp (a caller's row-major tensors: PANEL = false and featurewise24_rows_kernel below).
 // One workgroup handles 64 tokens x 64 features: decompress into LDS, then each work item takes one feature
 // and 8 consecutive tokens (two groups).  The workgroup's input is one contiguous 4 KiB run per tensor and it writes one contiguous
 // 4 KiB run; 128-token tiles, with twice the LDS per workgroup and half the workgroups per CU, ran at 5.0 instead of 5.9 TB/s.
 constexpr int FW_TOK = 64, FW_FEAT = 64, FW_LD = FW_FEAT + 2;
 
-// SPLIT (Sec. 2, "Optimization 1"): feature f becomes row row_of_feat[f] of the outputs; rows below
+// PANEL: in the panel form; otherwise row-major, for matrices too small for featurewise24_rows_kernel's tiles to fill the chip.
+// SPLIT (Sec. 2, "Optimization 1"; panel form only): feature f becomes row row_of_feat[f] of the outputs; rows below
 // n_sparse are 2:4-compressed along tokens as above, the others -- the least sparse features -- are written out
 // uncompressed, as rows [row - n_sparse] of the dense operands Hdn_t, dZdn_t [n_dense][T] (dense panel form).
-template <bool SPLIT>
+template <bool PANEL, bool SPLIT = false>
 __global__ void __launch_bounds__(256) featurewise24_kernel(const uint16_t* __restrict__ Hc, const uint8_t* __restrict__ meta,
                                                             const uint16_t* __restrict__ dZc, int T, int F,
                                                             uint16_t* __restrict__ Hc_t, uint8_t* __restrict__ meta_t,
@@ -175,7 +177,7 @@ __global__ void __launch_bounds__(256) featurewise24_kernel(const uint16_t* __re
     int tok = item >> 2, ch = item & 3;
     int t = t0 + tok;
     // offsets of this item's 8 stored values (in elements) and of its 2 metadata bytes
-    const size_t piece = a24_piece(t, f0 >> 6, F >> 6), vo = piece * 32 + 8 * ch, mo = piece * 8 + 2 * ch;
+    const size_t piece = PANEL ? a24_piece(t, f0 >> 6, F >> 6) : (size_t)t * (F >> 6) + (f0 >> 6), vo = piece * 32 + 8 * ch, mo = piece * 8 + 2 * ch;
     u32x4 hv = ld_stream(reinterpret_cast<const u32x4*>(Hc + vo));
     u32x4 zv = {0u, 0u, 0u, 0u};
     if (has_z) zv = ld_stream(reinterpret_cast<const u32x4*>(dZc + vo));
@@ -245,7 +247,8 @@ __global__ void __launch_bounds__(256) featurewise24_kernel(const uint16_t* __re
       uint32_t zb = i1 == 3 ? z[4 * g + 3] : (i1 == 2 ? z[4 * g + 2] : z[4 * g + 1]);
       zp[g] = za | (zb << 16);
     }
-    const size_t piece = a24_piece(orow, (t0 + 8 * oct) >> 6, T >> 6), vo = piece * 32 + 4 * (oct & 7), mo = piece * 8 + (oct & 7);
+    const size_t piece = PANEL ? a24_piece(orow, (t0 + 8 * oct) >> 6, T >> 6) : (size_t)orow * (T >> 6) + ((t0 + 8 * oct) >> 6);
+    const size_t vo = piece * 32 + 4 * (oct & 7), mo = piece * 8 + (oct & 7);
     st_stream(reinterpret_cast<u32x2*>(Hc_t + vo), u32x2{hp[0], hp[1]});
     if (has_z) st_stream(reinterpret_cast<u32x2*>(dZc_t + vo), u32x2{zp[0], zp[1]});
     st_stream(meta_t + mo, (uint8_t)(nb[0] | (nb[1] << 4)));
@@ -308,7 +311,8 @@ int launch_tele_sum(const unsigned long long* tele, long long elements, long lon
 // row's metadata line serves four neighbouring tiles and should be fetched by one L2.
 // Measured at 8064 x 8256 / 16384 x 16384 (with dZ): 67 us = 4.2 TB/s / 230 us = 5.0 TB/s; tiles dealt round-robin over the XCDs 69 / 259-307
 // us; 64-token tiles 81 / 373 us, 32-token tiles 207 / 1005 us (half and quarter lines out); three workgroups a CU 135 / 538 us (spills).
-// 64 x 64 tiles spread out in LDS, which read and wrote half lines and 8-byte metadata pieces, took 160 us = 1.8 TB/s.
+// 64 x 64 tiles spread out in LDS (featurewise24_kernel<false>), which read and write half lines and 8-byte metadata pieces, take 160 us =
+// 1.8 TB/s, but fill the chip from eight times fewer elements on: small matrices take them (featurewise_small).
 constexpr int FWR_CH = 4, FWR_TOK = 32 * FWR_CH;   // chunks of 8 tokens per wave, tokens per workgroup
 __global__ void __launch_bounds__(256, 2) featurewise24_rows_kernel(const uint32_t* __restrict__ Hc, const uint8_t* __restrict__ meta,
                                                                     const uint32_t* __restrict__ dZc, int T, int F, uint8_t* __restrict__ Hc_t,
@@ -393,6 +397,12 @@ __global__ void __launch_bounds__(256, 2) featurewise24_rows_kernel(const uint32
 }
 
 int launch_featurewise24_rows(const void* Hc, const uint8_t* meta, const void* dZc, int T, int F, void* Hc_t, uint8_t* meta_t, void* dZc_t, hipStream_t s) {
+  if (featurewise_small(T, F)) {
+    hipLaunchKernelGGL(featurewise24_kernel<false>, dim3(F / FW_FEAT, T / FW_TOK), dim3(256), 0, s, static_cast<const uint16_t*>(Hc), meta,
+                       static_cast<const uint16_t*>(dZc), T, F, static_cast<uint16_t*>(Hc_t), meta_t, static_cast<uint16_t*>(dZc_t),
+                       nullptr, 0, nullptr, nullptr, nullptr, nullptr, nullptr);
+    return (int)hipGetLastError();
+  }
   hipLaunchKernelGGL(featurewise24_rows_kernel, dim3((F + 255) / 256, T / FWR_TOK), dim3(256), 0, s, static_cast<const uint32_t*>(Hc), meta, static_cast<const uint32_t*>(dZc),
                      T, F, static_cast<uint8_t*>(Hc_t), meta_t, static_cast<uint8_t*>(dZc_t));
   return (int)hipGetLastError();
@@ -401,7 +411,7 @@ int launch_featurewise24_rows(const void* Hc, const uint8_t* meta, const void* d
 int launch_featurewise24(const void* Hc, const uint8_t* meta, const void* dZc, int T, int F,
                          void* Hc_t, uint8_t* meta_t, void* dZc_t, unsigned long long* tele, hipStream_t s) {
   dim3 grid(F / FW_FEAT, T / FW_TOK);
-  hipLaunchKernelGGL(featurewise24_kernel<false>, grid, dim3(256), 0, s, static_cast<const uint16_t*>(Hc), meta,
+  hipLaunchKernelGGL(featurewise24_kernel<true>, grid, dim3(256), 0, s, static_cast<const uint16_t*>(Hc), meta,
                      static_cast<const uint16_t*>(dZc), T, F, static_cast<uint16_t*>(Hc_t), meta_t, static_cast<uint16_t*>(dZc_t),
                      nullptr, 0, nullptr, nullptr, tele, nullptr, nullptr);
   return (int)hipGetLastError();
@@ -411,7 +421,7 @@ int launch_featurewise24(const void* Hc, const uint8_t* meta, const void* dZc, i
 int launch_featurewise24_rowmax(const void* Hc, const uint8_t* meta, const void* dZc, int T, int F, void* Hc_t, uint8_t* meta_t, void* dZc_t,
                                 uint32_t* hmax, uint32_t* zmax, hipStream_t s) {
   dim3 grid(F / FW_FEAT, T / FW_TOK);
-  hipLaunchKernelGGL(featurewise24_kernel<false>, grid, dim3(256), 0, s, static_cast<const uint16_t*>(Hc), meta,
+  hipLaunchKernelGGL(featurewise24_kernel<true>, grid, dim3(256), 0, s, static_cast<const uint16_t*>(Hc), meta,
                      static_cast<const uint16_t*>(dZc), T, F, static_cast<uint16_t*>(Hc_t), meta_t, static_cast<uint16_t*>(dZc_t),
                      nullptr, 0, nullptr, nullptr, nullptr, hmax, zmax);
   return (int)hipGetLastError();
@@ -421,7 +431,7 @@ int launch_featurewise24_split(const void* Hc, const uint8_t* meta, const void* 
                                void* Hc_t, uint8_t* meta_t, void* dZc_t, void* Hdn_t, void* dZdn_t, unsigned long long* tele,
                                uint32_t* hmax, uint32_t* zmax, hipStream_t s) {
   dim3 grid(F / FW_FEAT, T / FW_TOK);
-  hipLaunchKernelGGL(featurewise24_kernel<true>, grid, dim3(256), 0, s, static_cast<const uint16_t*>(Hc), meta,
+  hipLaunchKernelGGL((featurewise24_kernel<true, true>), grid, dim3(256), 0, s, static_cast<const uint16_t*>(Hc), meta,
                      static_cast<const uint16_t*>(dZc), T, F, static_cast<uint16_t*>(Hc_t), meta_t, static_cast<uint16_t*>(dZc_t),
                      row_of_feat, n_sparse, static_cast<uint16_t*>(Hdn_t), static_cast<uint16_t*>(dZdn_t), tele, hmax, zmax);
   return (int)hipGetLastError();

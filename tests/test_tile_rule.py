@@ -1,4 +1,4 @@
-"""The rule that picks a GEMM's block tile (csrc/tile_rule.hpp), compiled for the host: on shapes timed with every tile in whole steps, in a
+"""The rules that pick a tile (csrc/tile_rule.hpp), compiled for the host.  A GEMM's block tile: on shapes timed with every tile in whole steps, in a
 sustained loop, it does not take one that was clearly slower than another: 0.4 % of a step and more, where the step's times differ by 0.2-0.3 %."""
 import shutil
 import subprocess
@@ -108,3 +108,14 @@ def test_launches_apart(tmp_path):
     text = "\n".join(" ".join(str(x) for x in q) for q, _ in TOGETHER)
     got = subprocess.run([str(tmp_path / "main")], input=text, capture_output=True, text=True, check=True).stdout.split()
     assert [int(x) for x in got] == [a for _, a in TOGETHER]
+
+
+def test_featurewise_tile_of_measured_shapes(tmp_path):
+    if not shutil.which("g++"):
+        pytest.skip("no host compiler")
+    small = [(128, 64), (128, 16384), (16384, 64), (2560, 768), (1280, 1216), (2048, 2048)]            # 64 x 64 tiles 1.2-2.5 x faster
+    large = [(5248, 896), (1792, 3712), (512, 12288), (10112, 768), (16384, 512), (8064, 8256), (1 << 20, 1 << 20)]   # 128 x 256 tiles 1.1-2.8 x
+    checks = " && ".join([f"featurewise_small({a}, {b})" for a, b in small] + [f"!featurewise_small({a}, {b})" for a, b in large])
+    (tmp_path / "main.cpp").write_text('#include "%s"\nusing namespace ffn24;\nint main() { return %s ? 0 : 1; }\n' % (RULE, checks))
+    subprocess.run(["g++", "-std=c++17", "-o", str(tmp_path / "main"), str(tmp_path / "main.cpp")], check=True)
+    assert subprocess.run([str(tmp_path / "main")]).returncode == 0
