@@ -563,7 +563,7 @@ int ffn24_fwd(ffn24_ctx* c, const void* X, const void* W1, const float* b1, cons
     pre.add_zero(c->rowmax, T);
     if (nnz) pre.add_zero(nnz, F);
     // token permutation: position p inside the FFN holds token perm[p] -- its row of X8 is gathered by the pass that brings X8
-    // into panel form, its scale by a small kernel; everything in between lives in FFN order, and Y's rows go back to their tokens
+    // into panel form, its scale by the same launch; everything in between lives in FFN order, and Y's rows go back to their tokens
     const int* perm = c->perm_on ? c->perm : nullptr;
     const float* sx = c->rsx;
     if (perm) { pre.set_gather(c->rsx, perm, T, c->sx_p); sx = c->sx_p; }

@@ -605,9 +605,10 @@ struct EpiColMajorScaled {
 // Row maxima of a launch: rowmax[t] is raised to the largest bf16 magnitude word of row t.  A token row spans F / (16 MI) lanes of the
 // launch, and one atomic for each of them was the larger part of the row-wise epilogues (T = F = 8192: a million atomics, 15 us of the
 // dH GEMM's 157 with 256 x 256 tiles and 40 of 167 with 256 x 128).  So the two lane halves, which hold the same tokens, are
-// combined first, and what is already there is looked at before: the values are requested when the epilogue starts, and an atomic
-// goes out only where it would raise one -- about ln(n) of n contributions.  A value that is out of date is lower and only costs an
-// atomic.
+// combined first, which halves them, and what is already there is looked at before: the values are requested when the epilogue starts,
+// and an atomic goes out only where it would raise one.  That spares the later rounds of a launch and most of a tile that starts late;
+// tiles of one round that finish together all see the cleared value and all send theirs.  A value that is out of date is lower and
+// only costs an atomic.
 template <int NI>
 struct RowMax {
   uint32_t seen[NI];
@@ -625,8 +626,8 @@ struct RowMax {
 // activation operand carries one scale per token, the weight one per output channel:
 //   z = sx[t] sw1[f] acc + b1[f];  h = bf16(max(0, z)^2);  keep-2-of-4 as in EpiPrune24.
 // The kept values cannot be quantised here -- their scale is the maximum of the whole token row, which spans many
-// block tiles -- so they are written as bf16 in the bf16 panel form (Hc, meta), and every lane raises rowmax[t] (bf16
-// word of the largest activation, non-negative, so integer order = value order) with one atomic per token.
+// block tiles -- so they are written as bf16 in the bf16 panel form (Hc, meta), and rowmax[t] (bf16
+// word of the largest activation, non-negative, so integer order = value order) is raised with atomics (RowMax).
 // A streaming kernel then quantises with sh[t] = rowmax[t] / 448 (k_stream.hip).
 // STATS: also the per-feature non-zero counts of the activation before pruning, into nnz [F] (as in EpiPrune24T).
 template <bool STATS>
@@ -886,8 +887,8 @@ struct EpiColMajorRowCol {
 // 4 tokens; dH = rs[f] cs[t] acc (rs = the scale of each hidden feature's row of W2, cs = the scale of each token's row of dY);
 // on the positions the forward kept dZ = dH * 2 sqrt(h), h the bf16 kept value the forward saved (Hc16, meta16: bf16 panel form).
 // Like the activation in the row-wise forward, dZ cannot be quantised here -- the scale of a token row spans many block tiles
-// -- so it is written as bf16, compressed with the forward's metadata (dZc16, bf16 panel form), and every lane raises
-// rowmax[t] to the largest magnitude word of its part of the row; a streaming kernel then quantises with rowmax[t] / 448.
+// -- so it is written as bf16, compressed with the forward's metadata (dZc16, bf16 panel form), and rowmax[t] is
+// raised to the largest magnitude word of the row (RowMax); a streaming kernel then quantises with rowmax[t] / 448.
 struct EpiDGatherRw {
   static constexpr EpiCost COST = EPI_FP8;
   struct Args { const __bf16* Hc16; const uint8_t* meta16; __bf16* dZc16; int F; const float* rs; const float* cs; uint32_t* rowmax; };
