@@ -5,7 +5,7 @@
 // wave tile of MI x NI MFMA tiles of 32x32, so a block tile is 64 MI x 64 NI.  Block tile 256x256 (MI = NI = 4: 256 accumulator
 // registers per lane, pinned to the AGPR file) is the one that streams the fewest operand bytes per matrix op and carries the
 // large problems; 256x128, 128x128, 128x64 and 64x64 take the shapes whose 256x256 tiles would leave CUs idle (pick_tile in
-// launch_impl.hpp).  What follows describes the 256x256 tile; the smaller ones have the same LDS rows, swizzles and lane layouts.
+// tile_rule.hpp).  What follows describes the 256x256 tile; the smaller ones have the same LDS rows, swizzles and lane layouts.
 // An output element sums the same k in the same order in every tile, so the results are the same bit for bit.
 //
 //   A dense  : [M][K]                         -> v_mfma_f32_32x32x16_bf16

@@ -1,4 +1,4 @@
-"""Every block tile of the GEMM kernel, at sizes whose shape takes it (pick_tile in launch_impl.hpp): integer products exactly, and the
+"""Every block tile of the GEMM kernel, at sizes whose shape takes it (pick_tile in tile_rule.hpp): integer products exactly, and the
 fused epilogues against the oracle with the checks and bars of test_gpu_parity (bf16), or bit for bit against the same step in larger
 tiles (fp8).
 
