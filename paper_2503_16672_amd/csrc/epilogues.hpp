@@ -236,14 +236,83 @@ struct EpiRelu2T {
 };
 using EpiRelu2 = EpiRelu2T<false>;
 
-// Per-feature non-zero counts of the activation epilogues (Sec. 2, "Optimization 1": the column-level sparsity the first GEMM's
-// epilogue can compute for free).  A lane counts its tokens in 8-bit fields, 4 features per register: the packed pair of
-// features 16 mi + 2 d and + 1 goes to fields (2 d) % 4 and (2 d + 1) % 4 of register 4 mi + d / 2.
-template <int MI>
-__device__ __forceinline__ void nnz_count(uint32_t (&cnt)[4 * MI], uint32_t hpk, int mi, int d) {
-  uint32_t lo = min(hpk & 0xFFFFu, 1u), hi = min(hpk >> 16, 1u);
-  cnt[4 * mi + (d >> 1)] += (lo << (16 * (d & 1))) + (hi << (16 * (d & 1) + 8));
+// Two 2:4 groups at a time, one in each half of a word (pick24_two).  With two or more columns a lane pairs the same group of two
+// neighbouring tokens; with one (NI = 1) it pairs groups a and a + 2 of the token.  Entry v of a word's low half is feature 16 mi + v of
+// token ni, of its high half the same feature of token ni + 1, or (NI = 1) feature 16 mi + v + 8 of the one token.
+// TwoTokens: what 16 features (an M-tile's) make of two tokens (NI = 1: of one, and index 1 is not used).
+template <int NI>
+struct TwoTokens {
+  static constexpr int TOK = NI > 1 ? 2 : 1, ROWS = NI > 1 ? 16 : 8;   // tokens a word holds; words of an M-tile
+  using Words = uint32_t[ROWS];
+  u32x4 vals[TOK];                   // kept pairs in position order
+  uint32_t nib[TOK];                 // their metadata, 16 bits
+  __device__ __forceinline__ void pick(const Words& h) {
+    uint32_t w = 0u;
+#pragma unroll
+    for (int a = 0; a < ROWS / 4; a++) {
+      const Pick24x2 p = pick24_two(h[4 * a], h[4 * a + 1], h[4 * a + 2], h[4 * a + 3]);
+      w = put_nibbles(w, p, a);
+      const uint32_t lo = __builtin_amdgcn_perm(p.second, p.first, 0x05040100u), hi = __builtin_amdgcn_perm(p.second, p.first, 0x07060302u);
+      vals[0][a] = lo;
+      if constexpr (NI > 1) vals[1][a] = hi; else vals[0][a + 2] = hi;
+    }
+    if constexpr (NI > 1) { nib[0] = w & 0xFFFFu; nib[1] = w >> 16; }
+    else nib[0] = (w & 0xFFu) | ((w >> 8) & 0xFF00u);
+  }
+};
+// A lane's rounded activations of two tokens (or one) for M-tile mi, in the order TwoTokens takes them; z(mi, ni, v) = the pre-activation
+template <int NI, class Z>
+__device__ __forceinline__ void relu2_words(typename TwoTokens<NI>::Words& h, int mi, int ni, Z&& z) {
+#pragma unroll
+  for (int v = 0; v < TwoTokens<NI>::ROWS; v++) {
+    const float r0 = fmaxf(z(mi, ni, v), 0.f), r1 = fmaxf(NI > 1 ? z(mi, ni + 1, v) : z(mi, ni, v + 8), 0.f);
+    h[v] = pack_bf16x2(r0 * r0, r1 * r1);
+  }
 }
+// The same words as rows of 16 features, row-major (parity checks)
+template <int NI>
+__device__ __forceinline__ void st_debug(__bf16* row, int F, const typename TwoTokens<NI>::Words& h) {
+#pragma unroll
+  for (int half = 0; half < 2; half++) {
+    const uint32_t sel = half ? 0x07060302u : 0x05040100u;
+#pragma unroll
+    for (int q = 0; q < TwoTokens<NI>::ROWS / 8; q++) {
+      u32x4 o;
+#pragma unroll
+      for (int d = 0; d < 4; d++) o[d] = __builtin_amdgcn_perm(h[8 * q + 2 * d + 1], h[8 * q + 2 * d], sel);
+      *reinterpret_cast<u32x4*>(row + (NI > 1 ? (size_t)half * F + 8 * q : 8 * half)) = o;
+    }
+  }
+}
+
+// Per-feature non-zero counts of the activation epilogues (Sec. 2, "Optimization 1": the column-level sparsity the first GEMM's
+// epilogue can compute for free).  A lane first counts in 8-bit fields as the words come, one word for 2 v and 2 v + 1 of an
+// M-tile: bytes 0, 1 from the low halves, bytes 2, 3 from the high halves; nnz_fold brings that into 4 features a register, feature f of
+// the lane in field f % 4 of register f / 4.
+template <int MI, int NI> struct NnzCount {
+  static constexpr int ROWS = TwoTokens<NI>::ROWS;
+  uint32_t c[MI * ROWS / 2];
+  __device__ __forceinline__ NnzCount() {
+#pragma unroll
+    for (int i = 0; i < MI * ROWS / 2; i++) c[i] = 0u;
+  }
+  __device__ __forceinline__ void add(int mi, const uint32_t (&h)[ROWS]) {
+#pragma unroll
+    for (int v = 0; v < ROWS; v += 2) c[(mi * ROWS + v) / 2] += pk_min16(h[v], 0x00010001u) + (pk_min16(h[v + 1], 0x00010001u) << 8);
+  }
+  __device__ __forceinline__ void fold(uint32_t (&cnt)[4 * MI]) const {
+#pragma unroll
+    for (int i = 0; i < 4 * MI; i++) {
+      if constexpr (NI > 1) {                            // both halves are tokens of the same two features
+        const uint32_t a = c[2 * i] + (c[2 * i] >> 16), b = c[2 * i + 1] + (c[2 * i + 1] >> 16);
+        cnt[i] = __builtin_amdgcn_perm(b, a, 0x05040100u);
+      } else {                                           // the high halves are features 8 further on
+        const int mi = i / 4, j = i % 4, w = mi * 4 + 2 * (j & 1);
+        cnt[i] = __builtin_amdgcn_perm(c[w + 1], c[w], j < 2 ? 0x05040100u : 0x07060302u);
+      }
+    }
+  }
+};
 // The 32 lanes that hold the same 16 MI features add their fields up with a butterfly (<= 128 per field); lane r then adds the
 // totals of features r and (MI = 4) r + 32 to nnz [F] with atomics (the caller zeroes it).
 template <int MI>
@@ -284,61 +353,47 @@ struct EpiPrune24T {
   struct Args { __bf16* Hc; uint8_t* meta; __bf16* Hdbg; const float* b1; int F; uint32_t* nnz; unsigned long long* tele; };
   template <int MI, int NI>
   static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
-    uint32_t cnt[4 * MI];
-    uint32_t kept = 0u;   // non-zero values among the lane's 128 stored ones
-#pragma unroll
-    for (int i = 0; i < 4 * MI; i++) cnt[i] = 0u;
+    constexpr int TOK = TwoTokens<NI>::TOK;
+    NnzCount<MI, NI> nz;
+    uint32_t kept = 0u;   // non-zero values among the lane's stored ones, first and second of a pair apart (16-bit fields)
     LaneVec<MI> lb;
     lb.load(e.b1, m_lane, 0.f);
 #pragma unroll
-    for (int ni = 0; ni < NI; ni++) {
-      size_t t = (size_t)(n_lane + ni);
-      uint32_t vals[4 * MI];
-      uint32_t nib[2] = {0u, 0u};
+    for (int ni = 0; ni < NI; ni += TOK) {
+      uint32_t nib[TOK][2] = {};
 #pragma unroll
       for (int mi = 0; mi < MI; mi++) {
-        uint32_t hpk[8];
+        TwoTokens<NI> tt;
+        typename TwoTokens<NI>::Words h;
+        relu2_words<NI>(h, mi, ni, [&](int i, int n, int v) { return acc[i][n][v] + lb.at(16 * i + v); });
+        if constexpr (STATS) nz.add(mi, h);
+        if (e.Hdbg) st_debug<NI>(e.Hdbg + (size_t)(n_lane + ni) * e.F + m_lane + 16 * mi, e.F, h);
+        tt.pick(h);
 #pragma unroll
-        for (int d = 0; d < 8; d++) {
-          float b0 = lb.at(16 * mi + 2 * d), b1v = lb.at(16 * mi + 2 * d + 1);
-          float r0 = fmaxf(acc[mi][ni][2 * d] + b0, 0.f);
-          float r1 = fmaxf(acc[mi][ni][2 * d + 1] + b1v, 0.f);
-          hpk[d] = pack_bf16x2(r0 * r0, r1 * r1);
-          if constexpr (STATS) nnz_count<MI>(cnt, hpk[d], mi, d);
-        }
-        if (e.Hdbg) {
-          __bf16* row = e.Hdbg + t * e.F + m_lane + 16 * mi;
-          *reinterpret_cast<u32x4*>(row) = u32x4{hpk[0], hpk[1], hpk[2], hpk[3]};
-          *reinterpret_cast<u32x4*>(row + 8) = u32x4{hpk[4], hpk[5], hpk[6], hpk[7]};
-        }
+        for (int t = 0; t < TOK; t++) {
+          *reinterpret_cast<u32x4*>(e.Hc + a24_piece(n_lane + ni + t, m_lane >> 6, e.F >> 6) * 32 + ((m_lane & 63) >> 1) + 8 * mi) = tt.vals[t];
+          nib[t][mi >> 1] |= tt.nib[t] << (16 * (mi & 1));
+          if constexpr (STATS) {
 #pragma unroll
-        for (int a = 0; a < 4; a++) {
-          // h >= 0, so the storage word is its own magnitude
-          uint32_t pair;
-          uint32_t n4 = pick24_packed(hpk[2 * a], hpk[2 * a + 1], pair);
-          int gi = 4 * mi + a;
-          vals[gi] = pair;
-          nib[gi >> 3] |= n4 << (4 * (gi & 7));
-          if constexpr (STATS) kept += min(pair & 0xFFFFu, 1u) + min(pair >> 16, 1u);
+            for (int i = 0; i < 4; i++) kept += pk_min16(tt.vals[t][i], 0x00010001u);
+          }
         }
       }
-      size_t piece = a24_piece((int)t, m_lane >> 6, e.F >> 6);
-      __bf16* hrow = e.Hc + piece * 32 + ((m_lane & 63) >> 1);
 #pragma unroll
-      for (int q = 0; q < MI; q++)
-        *reinterpret_cast<u32x4*>(hrow + 8 * q) = u32x4{vals[4 * q], vals[4 * q + 1], vals[4 * q + 2], vals[4 * q + 3]};
-      st_nibbles<MI>(e.meta + piece * 8 + ((m_lane & 63) >> 3), nib);
+      for (int t = 0; t < TOK; t++) st_nibbles<MI>(e.meta + a24_piece(n_lane + ni + t, m_lane >> 6, e.F >> 6) * 8 + ((m_lane & 63) >> 3), nib[t]);
     }
     if constexpr (STATS) {
+      uint32_t cnt[4 * MI];
+      nz.fold(cnt);
       if (e.tele) {
         // the lane's own non-zero count is the sum of its fields (at most 4 each); with the kept count, over the wave
         uint32_t tot = 0u;
 #pragma unroll
         for (int i = 0; i < 4 * MI; i++) tot += (cnt[i] & 0xFFu) + ((cnt[i] >> 8) & 0xFFu) + ((cnt[i] >> 16) & 0xFFu) + (cnt[i] >> 24);
-        tele_add2(e.tele, tot | (kept << 16), TELE_NONZERO, TELE_KEPT_TOK, blockIdx.x + (threadIdx.x >> 6));
+        tele_add2(e.tele, tot | (((kept & 0xFFFFu) + (kept >> 16)) << 16), TELE_NONZERO, TELE_KEPT_TOK, blockIdx.x + (threadIdx.x >> 6));
       }
+      if (e.nnz) nnz_flush<MI>(cnt, e.nnz, m_lane);
     }
-    if constexpr (STATS) if (e.nnz) nnz_flush<MI>(cnt, e.nnz, m_lane);
   }
 };
 using EpiPrune24 = EpiPrune24T<false>;   // without the statistic (a compile-time switch: the plain kernel carries no trace of it)
@@ -492,49 +547,40 @@ struct EpiPrune24F8 {
   struct Args { uint8_t* Hc8; uint8_t* meta; __bf16* Hdbg; const float* b1; int F; float zscale; float sh; __bf16* Hc16; uint8_t* meta16; };
   template <int MI, int NI>
   static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+    constexpr int TOK = TwoTokens<NI>::TOK;
     LaneVec<MI> lb;
     lb.load(e.b1, m_lane, 0.f);
     const ExactDiv by_sh(e.sh);
 #pragma unroll
-    for (int ni = 0; ni < NI; ni++) {
-      size_t t = (size_t)(n_lane + ni);
-      uint32_t q8[2 * MI];
-      uint32_t nib[2] = {0u, 0u};
-      size_t piece16 = a24_piece((int)t, m_lane >> 6, e.F >> 6);
+    for (int ni = 0; ni < NI; ni += TOK) {
+      uint32_t nib[TOK][2] = {}, q8[TOK][2 * MI];
 #pragma unroll
       for (int mi = 0; mi < MI; mi++) {
-        uint32_t hpk[8];
+        TwoTokens<NI> tt;
+        typename TwoTokens<NI>::Words h;
+        relu2_words<NI>(h, mi, ni, [&](int i, int n, int v) { return acc[i][n][v] * e.zscale + lb.at(16 * i + v); });
+        if (e.Hdbg) st_debug<NI>(e.Hdbg + (size_t)(n_lane + ni) * e.F + m_lane + 16 * mi, e.F, h);
+        tt.pick(h);
 #pragma unroll
-        for (int d = 0; d < 8; d++) {
-          float b0 = lb.at(16 * mi + 2 * d), b1v = lb.at(16 * mi + 2 * d + 1);
-          float r0 = fmaxf(acc[mi][ni][2 * d] * e.zscale + b0, 0.f);
-          float r1 = fmaxf(acc[mi][ni][2 * d + 1] * e.zscale + b1v, 0.f);
-          hpk[d] = pack_bf16x2(r0 * r0, r1 * r1);
-        }
-        if (e.Hdbg) {
-          __bf16* row = e.Hdbg + t * e.F + m_lane + 16 * mi;
-          *reinterpret_cast<u32x4*>(row) = u32x4{hpk[0], hpk[1], hpk[2], hpk[3]};
-          *reinterpret_cast<u32x4*>(row + 8) = u32x4{hpk[4], hpk[5], hpk[6], hpk[7]};
-        }
-        uint32_t pairs[4];
+        for (int t = 0; t < TOK; t++) {
+          nib[t][mi >> 1] |= tt.nib[t] << (16 * (mi & 1));
 #pragma unroll
-        for (int a = 0; a < 4; a++) {
-          uint32_t pair;
-          uint32_t n4 = pick24_packed(hpk[2 * a], hpk[2 * a + 1], pair);
-          pairs[a] = pair;
-          int gi = 4 * mi + a;
-          float v0 = by_sh(bf16_lo_to_f32(pair));
-          float v1 = by_sh(bf16_hi_to_f32(pair));
-          // group gi's two stored bytes are bytes 2 gi, 2 gi + 1 of the lane's 8 MI
-          q8[gi >> 1] = cvt_e4m3x2(v0, v1, (gi & 1) ? q8[gi >> 1] : 0u, (gi & 1) != 0);
-          nib[gi >> 3] |= n4 << (4 * (gi & 7));
+          for (int a = 0; a < 4; a++) {
+            // group 4 mi + a's two stored bytes are bytes 8 mi + 2 a and + 1 of the lane's 8 MI
+            const float v0 = by_sh(bf16_lo_to_f32(tt.vals[t][a])), v1 = by_sh(bf16_hi_to_f32(tt.vals[t][a]));
+            uint32_t& q = q8[t][2 * mi + (a >> 1)];
+            q = cvt_e4m3x2(v0, v1, (a & 1) ? q : 0u, (a & 1) != 0);
+          }
+          if (e.Hc16) *reinterpret_cast<u32x4*>(e.Hc16 + a24_piece(n_lane + ni + t, m_lane >> 6, e.F >> 6) * 32 + ((m_lane & 63) >> 1) + 8 * mi) = tt.vals[t];
         }
-        if (e.Hc16) *reinterpret_cast<u32x4*>(e.Hc16 + piece16 * 32 + ((m_lane & 63) >> 1) + 8 * mi) = u32x4{pairs[0], pairs[1], pairs[2], pairs[3]};
       }
-      size_t piece = a24_piece((int)t, m_lane >> 7, e.F >> 7);
-      st_codes<MI>(e.Hc8 + piece * 64 + ((m_lane & 127) >> 1), q8);
-      st_nibbles<MI>(e.meta + piece * 16 + ((m_lane & 127) >> 3), nib);
-      if (e.Hc16) st_nibbles<MI>(e.meta16 + piece16 * 8 + ((m_lane & 63) >> 3), nib);
+#pragma unroll
+      for (int t = 0; t < TOK; t++) {
+        const size_t piece = a24_piece(n_lane + ni + t, m_lane >> 7, e.F >> 7);
+        st_codes<MI>(e.Hc8 + piece * 64 + ((m_lane & 127) >> 1), q8[t]);
+        st_nibbles<MI>(e.meta + piece * 16 + ((m_lane & 127) >> 3), nib[t]);
+        if (e.Hc16) st_nibbles<MI>(e.meta16 + a24_piece(n_lane + ni + t, m_lane >> 6, e.F >> 6) * 8 + ((m_lane & 63) >> 3), nib[t]);
+      }
     }
   }
 };
@@ -636,56 +682,54 @@ struct EpiPrune24RwT {
   struct Args { __bf16* Hc; uint8_t* meta; __bf16* Hdbg; const float* b1; int F; const float* sx; const float* sw1; uint32_t* rowmax; uint32_t* nnz; };
   template <int MI, int NI>
   static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
-    uint32_t cnt[4 * MI];
-#pragma unroll
-    for (int i = 0; i < 4 * MI; i++) cnt[i] = 0u;
+    constexpr int TOK = TwoTokens<NI>::TOK;
+    NnzCount<MI, NI> nz;
     RowMax<NI> rm;
     rm.load(e.rowmax, n_lane);
-    LaneVec<MI> lb, lw;
-    lb.load(e.b1, m_lane, 0.f);
-    lw.load(e.sw1, m_lane, 1.f);
+    float sxt[NI];
 #pragma unroll
-    for (int ni = 0; ni < NI; ni++) {
-      size_t t = (size_t)(n_lane + ni);
-      const float sxt = e.sx[t];
-      uint32_t vals[4 * MI];
-      uint32_t nib[2] = {0u, 0u};
-      uint32_t mx = 0u;
+    for (int ni = 0; ni < NI; ni++) sxt[ni] = e.sx[n_lane + ni];
+    // M-tile by M-tile, each with its 16 features' biases and scales (asked for one M-tile ahead): all 64 of both beside the accumulators
+    // spilled 17-26 registers with 256 x 128 tiles
+    LaneVec<1> lb[2], lw[2];
+    lb[0].load(e.b1, m_lane, 0.f);
+    lw[0].load(e.sw1, m_lane, 1.f);
+    uint32_t mx[(NI + 1) / 2] = {}, nib[NI][2] = {};     // mx: of each half
 #pragma unroll
-      for (int mi = 0; mi < MI; mi++) {
-        uint32_t hpk[8];
+    for (int mi = 0; mi < MI; mi++) {
+      if (mi + 1 < MI) {
+        lb[(mi + 1) & 1].load(e.b1, m_lane + 16 * (mi + 1), 0.f);
+        lw[(mi + 1) & 1].load(e.sw1, m_lane + 16 * (mi + 1), 1.f);
+      }
 #pragma unroll
-        for (int d = 0; d < 8; d++) {
-          float b0 = lb.at(16 * mi + 2 * d), b1v = lb.at(16 * mi + 2 * d + 1);
-          float r0 = fmaxf(acc[mi][ni][2 * d] * (sxt * lw.at(16 * mi + 2 * d)) + b0, 0.f);
-          float r1 = fmaxf(acc[mi][ni][2 * d + 1] * (sxt * lw.at(16 * mi + 2 * d + 1)) + b1v, 0.f);
-          hpk[d] = pack_bf16x2(r0 * r0, r1 * r1);
-          mx = max(mx, max(hpk[d] & 0xFFFFu, hpk[d] >> 16));
-          if constexpr (STATS) nnz_count<MI>(cnt, hpk[d], mi, d);
-        }
-        if (e.Hdbg) {
-          __bf16* row = e.Hdbg + t * e.F + m_lane + 16 * mi;
-          *reinterpret_cast<u32x4*>(row) = u32x4{hpk[0], hpk[1], hpk[2], hpk[3]};
-          *reinterpret_cast<u32x4*>(row + 8) = u32x4{hpk[4], hpk[5], hpk[6], hpk[7]};
-        }
+      for (int ni = 0; ni < NI; ni += TOK) {
+        TwoTokens<NI> tt;
+        typename TwoTokens<NI>::Words h;
+        relu2_words<NI>(h, mi, ni, [&](int i, int n, int v) { return acc[i][n][v] * (sxt[n] * lw[i & 1].at(v)) + lb[i & 1].at(v); });
 #pragma unroll
-        for (int a = 0; a < 4; a++) {
-          uint32_t pair;
-          uint32_t n4 = pick24_packed(hpk[2 * a], hpk[2 * a + 1], pair);
-          int gi = 4 * mi + a;
-          vals[gi] = pair;
-          nib[gi >> 3] |= n4 << (4 * (gi & 7));
+        for (int v = 0; v < TwoTokens<NI>::ROWS; v++) mx[ni / 2] = pk_max16(mx[ni / 2], h[v]);
+        if constexpr (STATS) nz.add(mi, h);
+        if (e.Hdbg) st_debug<NI>(e.Hdbg + (size_t)(n_lane + ni) * e.F + m_lane + 16 * mi, e.F, h);
+        tt.pick(h);
+#pragma unroll
+        for (int t = 0; t < TOK; t++) {
+          *reinterpret_cast<u32x4*>(e.Hc + a24_piece(n_lane + ni + t, m_lane >> 6, e.F >> 6) * 32 + ((m_lane & 63) >> 1) + 8 * mi) = tt.vals[t];
+          nib[ni + t][mi >> 1] |= tt.nib[t] << (16 * (mi & 1));
         }
       }
-      size_t piece = a24_piece((int)t, m_lane >> 6, e.F >> 6);
-      __bf16* hrow = e.Hc + piece * 32 + ((m_lane & 63) >> 1);
-#pragma unroll
-      for (int q = 0; q < MI; q++)
-        *reinterpret_cast<u32x4*>(hrow + 8 * q) = u32x4{vals[4 * q], vals[4 * q + 1], vals[4 * q + 2], vals[4 * q + 3]};
-      st_nibbles<MI>(e.meta + piece * 8 + ((m_lane & 63) >> 3), nib);
-      rm.raise(e.rowmax, n_lane, ni, mx);
+      FFN24_FENCE();
     }
-    if constexpr (STATS) nnz_flush<MI>(cnt, e.nnz, m_lane);
+#pragma unroll
+    for (int ni = 0; ni < NI; ni++) {
+      st_nibbles<MI>(e.meta + a24_piece(n_lane + ni, m_lane >> 6, e.F >> 6) * 8 + ((m_lane & 63) >> 3), nib[ni]);
+      if constexpr (NI > 1) rm.raise(e.rowmax, n_lane, ni, ni & 1 ? mx[ni / 2] >> 16 : mx[ni / 2] & 0xFFFFu);
+      else rm.raise(e.rowmax, n_lane, ni, max(mx[0] & 0xFFFFu, mx[0] >> 16));
+    }
+    if constexpr (STATS) {
+      uint32_t cnt[4 * MI];
+      nz.fold(cnt);
+      nnz_flush<MI>(cnt, e.nnz, m_lane);
+    }
   }
 };
 using EpiPrune24Rw = EpiPrune24RwT<false>;

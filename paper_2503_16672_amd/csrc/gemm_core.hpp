@@ -841,21 +841,43 @@ __device__ __forceinline__ uint32_t pick24_keys(uint32_t k0, uint32_t k1, uint32
   return (cmax | (cmin << 2)) ^ 15u;
 }
 
-// The same pick for a group of non-negative values that arrive packed, lo = h0 | h1 << 16 and hi = h2 | h3 << 16 (the
-// activation epilogues): with the value in the upper half, key_i = h_i << 16 | (3 - i) takes one instruction each, and
-// the kept pair, in position order, is one byte permute of the two winning keys.
-__device__ __forceinline__ uint32_t pick24_packed(uint32_t lo, uint32_t hi, uint32_t& pair) {
-  uint32_t k0 = (lo << 16) | 3u, k1 = (lo & 0xFFFF0000u) | 2u, k2 = (hi << 16) | 1u, k3 = hi & 0xFFFF0000u;
-  uint32_t a = max(k0, k1), b = min(k0, k1), c = max(k2, k3), d = min(k2, k3);
-  uint32_t top = max(a, c);
-  uint32_t e = max(b, d);
-  uint32_t second = max(min(a, c), min(max(a, c), e));
-  uint32_t ct = top & 3u, cs = second & 3u;
-  bool top_first = ct > cs;
-  uint32_t kf = top_first ? top : second, ks = top_first ? second : top;
-  pair = __builtin_amdgcn_perm(ks, kf, 0x07060302u);           // kf's upper half below ks's upper half
-  uint32_t cmax = max(ct, cs), cmin = min(ct, cs);
-  return (cmax | (cmin << 2)) ^ 15u;
+// The pick for two groups at a time (the activation epilogues): p_i holds entry i of one group in its low half and entry i of another in
+// its high half, non-negative bf16 words (15 bits, so that 16-bit differences keep their sign and integer order is value order).  No key
+// with the position in it is needed: with a = max, b = min of entries 0, 1 and c, d those of 2, 3, both of the first pair stay
+// iff b >= c, both of the second iff d > a, and otherwise the larger of each pair, the earlier one if they are equal (ties go to the
+// lower index throughout).  All of it is packed 16-bit and bitwise arithmetic: 28 instructions for two groups and their
+// metadata against 44 with one group at a time and 32-bit keys, in an epilogue that overlaps with nothing.  T = F = 8192, D = 2048: bf16
+// up-projection 223 -> 221 us, row-wise fp8 with the per-feature counts, 256 x 128 tiles, 146 -> 128 (133 -> 123 without).
+// first, second: the kept entries in position order; bits: the nibble i0 | i1 << 2 of each half as four masks.
+struct Pick24x2 { uint32_t first, second, bit[4]; };
+typedef int16_t i16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ i16x2 as_i16x2(uint32_t w) { return __builtin_bit_cast(i16x2, w); }
+__device__ __forceinline__ uint32_t pk_max16(uint32_t a, uint32_t b) { return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(as_i16x2(a), as_i16x2(b))); }
+__device__ __forceinline__ uint32_t pk_min16(uint32_t a, uint32_t b) { return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(as_i16x2(a), as_i16x2(b))); }
+__device__ __forceinline__ uint32_t pk_less16(uint32_t a, uint32_t b) {   // all ones in the halves where a < b
+  uint32_t m = __builtin_bit_cast(uint32_t, (i16x2)((as_i16x2(a) - as_i16x2(b)) >> (i16x2)(15)));
+  asm("" : "+v"(m));   // opaque: the compiler would turn the masks back into a compare and a select for each half
+  return m;
+}
+__device__ __forceinline__ Pick24x2 pick24_two(uint32_t p0, uint32_t p1, uint32_t p2, uint32_t p3) {
+  const uint32_t a = pk_max16(p0, p1), b = pk_min16(p0, p1), c = pk_max16(p2, p3), d = pk_min16(p2, p3);
+  const uint32_t some = pk_less16(b, c);         // not both of the first pair
+  const uint32_t late = pk_less16(a, d);         // both of the second pair (then `some` is set too)
+  const uint32_t e = pk_less16(p0, p1), f = pk_less16(p2, p3);
+  Pick24x2 r;
+  r.first = (late & p2) | (~late & ((some & a) | (~some & p0)));
+  r.second = (some & ((late & p3) | (~late & c))) | (~some & p1);
+  r.bit[0] = e & some & ~late;
+  r.bit[1] = late;
+  r.bit[2] = ~some | late | f;
+  r.bit[3] = some;
+  return r;
+}
+// the nibbles of a pick at bits 4 k of both halves of w
+__device__ __forceinline__ uint32_t put_nibbles(uint32_t w, const Pick24x2& p, int k) {
+#pragma unroll
+  for (int i = 0; i < 4; i++) w |= p.bit[i] & (0x00010001u << (4 * k + i));
+  return w;
 }
 
 }  // namespace ffn24
