@@ -119,8 +119,16 @@ __host__ __device__ __forceinline__ size_t a24_piece(int r, int kp, int npanels)
 // when it has one.  Sparse 256 x 128 has room for two stages a workgroup only, and those expose the memory latency (112 us; 81 us with
 // four stages and the CU to itself).
 constexpr int ring_depth(bool sparse, bool f8, int mi, int ni) {
-  return mi * ni == 16 ? (sparse ? 3 : 4) : mi * ni == 8 ? (sparse ? 4 : 3) : mi * ni == 4 ? (sparse ? 3 : 4) : mi * ni == 2 ? 4 : 6;
+  return mi * ni == 16 ? (sparse ? 3 : 4) : mi * ni == 8 ? (sparse ? 4 : 3) : mi * ni == 4 ? (sparse ? 3 : 4) : mi * ni == 2 || !sparse ? 4 : 6;
 }
+// A dense 64 x 64 stage holds twice the k, in rows of 128 bytes: half the waits and barriers, and a row-major operand is read in whole
+// lines (1024 x 1024, one tile a CU: K 1024 7.1 -> 6.0 us, K 4096 19.8 -> 15.0, with a row-major B too; two tiles a CU 8.1 -> 7.4, 25 -> 25, row-major
+// 30 -> 26).  With larger tiles it leaves no room for a second workgroup on the CU: 128 x 64 10.7 -> 12.6 with two tiles.
+constexpr bool wide_stage(int mi, int ni) { return mi * ni == 1; }
+// The main loop that reads the fragments of a whole stage ahead (gemm_tile): not for the 256 x 256 tiles, whose registers are full, nor
+// dense 256 x 128, which would spill 18 registers beside a second workgroup, nor sparse 128 x 128, where one tile a CU is bound
+// by the operand stream already (K 4096 22.8 -> 23.9 us, 8192 41.9 -> 42.7; K 1024 9.7 -> 9.0).
+constexpr bool whole_stage_ahead(bool sparse, int mi, int ni) { return sparse ? mi * ni <= 2 || mi * ni == 8 : mi * ni <= 4; }
 
 // Stage geometry.  Everything is laid out in bytes, and an fp8 kernel has exactly the byte geometry of its bf16
 // counterpart with twice the k per byte: the LDS tiles, swizzles, DMA plan and fragment addresses are shared.
@@ -128,11 +136,13 @@ template <bool SPARSE, bool F8 = false, int MI = 4, int NI = 4>
 struct Geo {
   static constexpr int BM = 64 * MI, BN = 64 * NI;        // block tile: 2 x 2 waves of 32 MI x 32 NI
   static constexpr int ESIZE = F8 ? 1 : 2;
-  static constexpr int BK = (SPARSE ? 128 : 64) / ESIZE;  // dense k per stage (B rows of 128 / 64 bytes)
-  static constexpr int A_BYTES = BM * 64;                // 64-byte rows: dense k, or the stored values of twice as many k
+  static constexpr bool WIDE = !SPARSE && wide_stage(MI, NI);
+  static constexpr int A_ROW = WIDE ? 128 : 64;          // dense k, or the stored values of twice as many k
+  static constexpr int B_ROW = SPARSE || WIDE ? 128 : 64;
+  static constexpr int BK = B_ROW / ESIZE;               // dense k per stage
+  static constexpr int A_BYTES = BM * A_ROW;
   static constexpr int META_ROW = SPARSE ? (F8 ? 16 : 8) : 0;   // metadata bytes per row and stage (4 bits per group of 4 k)
   static constexpr int META_BYTES = BM * META_ROW;
-  static constexpr int B_ROW = SPARSE ? 128 : 64;
   static constexpr int B_BYTES = BN * B_ROW;
   static constexpr int META_OFF = A_BYTES;
   static constexpr int B_OFF = A_BYTES + META_BYTES;
@@ -143,7 +153,8 @@ struct Geo {
   // metadata DMA instructions per wave and stage (where a tile has less metadata than the four waves fetch, waves fetch the
   // same bytes to the same place: every wave then has the same count of instructions in flight)
   static constexpr int NM = SPARSE ? (F8 || MI < 4 ? 1 : 2) : 0;
-  static constexpr int NDMA = MI + NM + (SPARSE ? 2 * NI : NI);  // DMA instructions per wave and stage
+  static constexpr int NA = MI * (A_ROW / 64), NVB = NI * (B_ROW / 64);   // ... of the A values and of B
+  static constexpr int NDMA = NA + NM + NVB;             // DMA instructions per wave and stage
 };
 
 // LDS row -> row of the block tile (inverse of the permutation described above; in general wave-tile row 16 MI hc + 16 mi + v
@@ -185,11 +196,11 @@ __device__ __forceinline__ void wait_lgkmcnt0() { __builtin_amdgcn_s_waitcnt(0xC
 template <bool SPARSE, bool F8 = false, int PROBE = 0, int MI = 4, int NI = 4>
 struct Dma {
   using G = Geo<SPARSE, F8, MI, NI>;
-  static constexpr int NVB = SPARSE ? 2 * NI : NI;
+  static constexpr int NA = G::NA, NVB = G::NVB;
   const char* a;      // block's first A row (uniform)
   const char* am;     // metadata
   const char* b;
-  uint32_t va[MI], vm[2], vb[NVB];   // per-lane byte offsets from the uniform bases
+  uint32_t va[NA], vm[2], vb[NVB];   // per-lane byte offsets from the uniform bases
   uint32_t a_stage, m_stage, b_stage;          // bytes from one stage to the next in the A values / metadata / B stream
   int wave;
 
@@ -210,22 +221,22 @@ struct Dma {
       if constexpr (SPARSE) am += (size_t)ma * m_pitch;
     }
     b = static_cast<const char*>(g.B) + (g.b_rowmap ? (size_t)0 : (size_t)nb * b_row);
-    a_stage = panel ? 256u * 64u : 64u;
+    a_stage = panel ? 256u * (uint32_t)G::A_ROW : (uint32_t)G::A_ROW;
     m_stage = panel ? 256u * G::META_ROW : (uint32_t)G::META_ROW;
     b_stage = bp ? 256u * (uint32_t)G::B_ROW : (uint32_t)G::B_ROW;
 #pragma unroll
-    for (int j = 0; j < MI; j++) {
-      int p = 16 * (MI * wave + j) + (lane >> 2);
-      int c = (lane & 3) ^ swz4(p);
-      va[j] = (uint32_t)unperm_m<MI>(p) * a_pitch + c * 16;
+    for (int j = 0; j < NA; j++) {
+      // 64-byte rows, 16 an instruction; 128-byte rows, 8 an instruction, of which the panel form has two 64-byte pieces in
+      // consecutive 16 KiB runs
+      const int p = G::WIDE ? 8 * (NA * wave + j) + (lane >> 3) : 16 * (NA * wave + j) + (lane >> 2);
+      const int c = G::WIDE ? (lane & 7) ^ swz8(p) : (lane & 3) ^ swz4(p);
+      va[j] = (uint32_t)unperm_m<MI>(p) * a_pitch + (G::WIDE && panel ? (uint32_t)(c >> 2) * (256u * 64u) + (c & 3) * 16 : (uint32_t)c * 16);
     }
 #pragma unroll
     for (int j = 0; j < NVB; j++) {
-      // dense: 64-byte rows, 16 an instruction; sparse: 128-byte rows, 8 an instruction
-      int p = SPARSE ? 8 * (NVB * wave + j) + (lane >> 3) : 16 * (NVB * wave + j) + (lane >> 2);
-      int c = SPARSE ? (lane & 7) ^ swz8(p) : (lane & 3) ^ swz4(p);
-      // panel: with NI = 4 LDS row p is piece p of the block's run; a sparse row's 128 bytes are two 64-byte pieces in
-      // consecutive 16 KiB runs
+      int p = G::B_ROW == 128 ? 8 * (NVB * wave + j) + (lane >> 3) : 16 * (NVB * wave + j) + (lane >> 2);
+      int c = G::B_ROW == 128 ? (lane & 7) ^ swz8(p) : (lane & 3) ^ swz4(p);
+      // panel: with NI = 4 LDS row p is piece p of the block's run
       if (bp) vb[j] = (uint32_t)(c >> 2) * (256u * 64u) + (uint32_t)(NI == 4 ? p : b_panel_pos(na + unperm_n<NI>(p))) * 64u + (c & 3) * 16;
       else vb[j] = (g.b_rowmap ? (uint32_t)g.b_rowmap[n0 + unperm_n<NI>(p)] : (uint32_t)unperm_n<NI>(p)) * b_row + c * 16;
     }
@@ -251,16 +262,16 @@ struct Dma {
     // The stage's uniform base goes through an opaque scalar register pair, so that the compiler keeps it apart from the
     // lane's 32-bit offset and picks the instruction's scalar-base + 32-bit-offset form: no 64-bit vector add per
     // instruction, one address register per instruction instead of two.
-    if constexpr (J < MI) {
-      __builtin_amdgcn_global_load_lds((glb_char*)(sbase(a, kt, a_stage) + voff(va[J])), (lds_char*)(buf + (MI * wave + J) * 1024), 16, 0, 0);
-    } else if constexpr (J < MI + G::NM) {
-      constexpr int j = J - MI;
+    if constexpr (J < NA) {
+      __builtin_amdgcn_global_load_lds((glb_char*)(sbase(a, kt, a_stage) + voff(va[J])), (lds_char*)(buf + (NA * wave + J) * 1024), 16, 0, 0);
+    } else if constexpr (J < NA + G::NM) {
+      constexpr int j = J - NA;
       if constexpr (F8)
         __builtin_amdgcn_global_load_lds((glb_char*)(sbase(am, kt, m_stage) + voff(vm[0])), (lds_char*)(buf + G::META_OFF + (wave % MI) * 1024), 16, 0, 0);
       else
         __builtin_amdgcn_global_load_lds((glb_char*)(sbase(am, kt, m_stage) + voff(vm[j])), (lds_char*)(buf + G::META_OFF + ((G::NM * wave + j) % (2 * MI)) * 256), 4, 0, 0);
     } else {
-      constexpr int j = J - MI - G::NM;
+      constexpr int j = J - NA - G::NM;
       __builtin_amdgcn_global_load_lds((glb_char*)(sbase(b, kt, b_stage) + voff(vb[j])), (lds_char*)(buf + G::B_OFF + (NVB * wave + j) * 1024), 16, 0, 0);
     }
   }
@@ -285,9 +296,11 @@ struct LaneCtx {
   int wy, wx;       // wave row / column inside the block tile
   int a_row64;      // byte offset of the lane's LDS row among the wave's first 32 rows of A (64-byte rows)
   int b_row64;      // ... of B, 64-byte rows
+  int a_row128;     // ... of A, 128-byte rows
   int b_row128;     // ... of B, 128-byte rows
   int sw4;          // swz4 of the lane's row (the same for every 32-row tile)
   int sw8;          // swz8 of the lane's B row for even ni (odd ni: ^4)
+  int sw8a;         // swz8 of the lane's A row for even mi (odd mi: ^4)
 };
 
 // Dense: K step S (0,1) of the 64-byte stage rows; fragment I < MI -> a[I], else b[I-MI]
@@ -298,6 +311,13 @@ struct FragD {
 template <class G, int S, int I, int PROBE, int MI, int NI>
 __device__ __forceinline__ void load_frag_dense1(const char* buf, const LaneCtx& L, FragD<MI, NI>& f) {
   if constexpr ((PROBE & PROBE_NO_FRAG) != 0) return;
+  if constexpr (G::WIDE) {
+    constexpr int i = I < MI ? I : I - MI;
+    const int c = ((2 * S + L.h) ^ (I < MI ? L.sw8a : L.sw8) ^ ((i & 1) << 2)) << 4;
+    if constexpr (I < MI) f.a[I] = *reinterpret_cast<const bf16x8*>(buf + L.a_row128 + i * (32 * 128) + c);
+    else f.b[I - MI] = *reinterpret_cast<const bf16x8*>(buf + G::B_OFF + L.b_row128 + i * (32 * 128) + c);
+    return;
+  }
   int c = ((2 * S + L.h) ^ L.sw4) << 4;
   if constexpr (I < MI) f.a[I] = *reinterpret_cast<const bf16x8*>(buf + L.a_row64 + I * (32 * 64) + c);
   else f.b[I - MI] = *reinterpret_cast<const bf16x8*>(buf + G::B_OFF + L.b_row64 + (I - MI) * (32 * 64) + c);
@@ -388,6 +408,37 @@ __device__ __forceinline__ void mfma_sparse1(const FragS<MI, NI>& f, const IdxWo
     acc[mi][ni] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(f.a[mi], b, acc[mi][ni], (int)idx[mi].w[0], 0, S);
   }
 }
+
+// What a wave of the smaller tiles holds of one whole stage: the fragments (and metadata) as READS LDS reads, consumed by OPS matrix ops
+// that come in the order of k.
+template <bool SPARSE, bool F8, int MI, int NI>
+struct StageRegs {                           // dense: chunk pairs q of 32 bytes of k, one K step each (fp8: two a step)
+  static constexpr int PAIRS = wide_stage(MI, NI) ? 4 : 2, NF = MI + NI;
+  static constexpr int READS = PAIRS * NF, OPS = MI * NI * PAIRS / (F8 ? 2 : 1);
+  static constexpr int READ_SLOTS = OPS > 1 ? OPS / 2 : 1;
+  FragD<MI, NI> f[PAIRS];
+  template <class G, int I, int PROBE> __device__ __forceinline__ void read(const char* buf, const LaneCtx& L) { load_frag_dense1<G, I / NF, I % NF, PROBE>(buf, L, f[I / NF]); }
+  template <int M, int PROBE> __device__ __forceinline__ void op(f32x16 (&acc)[MI][NI]) const {
+    constexpr int s = M / (MI * NI), m = M % (MI * NI);
+    if constexpr (F8) mfma_dense_f8<m, PROBE>(f[2 * s], f[2 * s + 1], acc);
+    else mfma_dense1<m, PROBE>(f[s], acc);
+  }
+};
+template <bool F8, int MI, int NI>
+struct StageRegs<true, F8, MI, NI> {
+  static constexpr int NF = MI + 2 * NI;
+  static constexpr int READS = MI + 2 * NF, OPS = 2 * MI * NI;
+  static constexpr int READ_SLOTS = OPS / 2;
+  FragS<MI, NI> f[2];
+  IdxWords<F8> idx[MI];
+  template <class G, int I, int PROBE> __device__ __forceinline__ void read(const char* buf, const LaneCtx& L) {
+    if constexpr (I < MI) load_idx_sparse1<G, F8, I>(buf, L, idx);
+    else load_frag_sparse1<G, (I - MI) / NF, (I - MI) % NF, PROBE>(buf, L, f[(I - MI) / NF]);
+  }
+  template <int M, int PROBE> __device__ __forceinline__ void op(f32x16 (&acc)[MI][NI]) const {
+    mfma_sparse1<F8, M / (MI * NI), M % (MI * NI), PROBE>(f[M / (MI * NI)], idx, acc);
+  }
+};
 
 // ------------------------------------------------------------------------------------------------
 // the kernel
@@ -491,9 +542,12 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
   L.rho = lane & 31; L.h = lane >> 5; L.wy = wave >> 1; L.wx = wave & 1;
   L.a_row64 = (L.wy * (32 * MI) + L.rho) * 64;
   L.b_row64 = (L.wx * (32 * NI) + L.rho) * 64;
+  L.a_row128 = (L.wy * (32 * MI) + L.rho) * 128;
   L.b_row128 = (L.wx * (32 * NI) + L.rho) * 128;
   L.sw4 = swz4(L.rho);
-  L.sw8 = NI == 1 ? swz8(L.wx * 32 + L.rho) : swz8(L.rho);   // (from NI = 2 on the wave column moves the row by a multiple of 64, which the swizzle does not see)
+  // (from NI = 2, MI = 2 on the wave column, wave row moves the row by a multiple of 64, which the swizzle does not see)
+  L.sw8 = NI == 1 ? swz8(L.wx * 32 + L.rho) : swz8(L.rho);
+  L.sw8a = MI == 1 ? swz8(L.wy * 32 + L.rho) : swz8(L.rho);
 
   Dma<SPARSE, F8, PROBE, MI, NI> dma;
   dma.init(g, m0, n0, tid);
@@ -530,7 +584,62 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
   // MODE 0: steady state -- after the barrier the stage kt+NB is issued into the buffer this stage frees
   // MODE 1: tail -- nothing left to issue, wait for everything outstanding before the barrier
   // MODE 2: last stage -- no barrier, no next fragments
-  if constexpr (SPARSE) {
+  if constexpr (whole_stage_ahead(SPARSE, MI, NI)) {
+    // A smaller tile has few matrix ops a stage, so what a wave waits for itself counts: reading the second K step's fragments, the
+    // barrier and reading the next stage's first ones were one chain of 360 cycles a stage of the sparse 64 x 64 tile, beside the 350
+    // its operands take to arrive, and the two added up to 500.  Here the fragments of the WHOLE next stage are read while this
+    // stage's ops run (two register sets), with one wait and one barrier a stage, and the DMA of the stage that reuses this
+    // stage's buffer, whose fragments are in registers, rides along.  One tile a CU, K 4096: sparse 64 x 64 15.0 -> 13.0 us, 128 x 64 16.6
+    // -> 15.2, 256 x 128 37.0 -> 35.8; dense 64 x 64 see wide_stage, 128 x 128 29.8 -> 29.6.  What bounds them now is the operand stream.
+    StageRegs<SPARSE, F8, MI, NI> r0, r1;
+    using SR = StageRegs<SPARSE, F8, MI, NI>;
+    auto stage = [&](int kt, char* cur, char* nxt, const SR& now, SR& next, auto mode, auto left) {
+      constexpr int MODE = decltype(mode)::value, LEFT = decltype(left)::value;
+      FFN24_FENCE();
+      static_for<SR::OPS>([&](auto M) {
+        now.template op<M, PROBE>(acc);
+        if constexpr (MODE != 2) ride<SR::READS, SR::READ_SLOTS, M>([&](auto I) { next.template read<G, I, PROBE>(nxt, L); });
+        // (from 4 matrix ops a K step on, behind the fragment reads: 256 x 128 36.5 -> 35.8 us, dense 128 x 128 11.2 -> 10.6; 128 x 64 15.2 -> 15.7)
+        constexpr int FIRST = NMF >= 4 ? SR::OPS / 2 : 0;
+        if constexpr (MODE == 0 && M >= FIRST) ride<NDMA, SR::OPS - FIRST, M - FIRST>([&](auto J) { dma.template issue<J>(kt + NB, cur); });
+        FFN24_FENCE();
+      });
+      if constexpr (MODE != 2 && LEFT >= 0) {
+        wait_vmcnt<(LEFT > 0 ? LEFT : 0) * NDMA>();   // LEFT: the stages behind stage kt + 2, which the next stage reads, that may be in flight
+        wait_lgkmcnt0();
+        __builtin_amdgcn_s_barrier();
+      }
+      FFN24_FENCE();
+    };
+    using I0 = std::integral_constant<int, 0>; using I1 = std::integral_constant<int, 1>; using I2 = std::integral_constant<int, 2>;
+    int slot = 0;
+    auto advance = [&](int kt, const SR& now, SR& next, auto mode, auto left) {
+      int ns = slot + 1 == NB ? 0 : slot + 1;
+      stage(kt, smem + slot * G::STAGE, smem + ns * G::STAGE, now, next, mode, left);
+      slot = ns;
+    };
+    static_for<SR::READS>([&](auto I) { r0.template read<G, I, PROBE>(smem, L); });
+    if (npro == NB) wait_vmcnt<(NB - 2) * NDMA>(); else wait_vmcnt<0>();   // stage 1, which stage 0 reads
+    wait_lgkmcnt0();
+    __builtin_amdgcn_s_barrier();
+    FFN24_FENCE();
+    int kt = 0;
+    if (nk >= NB) {
+      const int n0 = nk - NB;            // stages that have a stage to ask for
+      using INB = std::integral_constant<int, NB - 2>;
+      for (; kt + 1 < n0; kt += 2) { advance(kt, r0, r1, I0{}, INB{}); advance(kt + 1, r1, r0, I0{}, INB{}); }
+      if (kt < n0) { advance(kt, r0, r1, I0{}, INB{}); kt++; r0 = r1; }
+      static_for<NB>([&](auto i) {
+        constexpr int I = decltype(i)::value;
+        using Mode = std::integral_constant<int, (I == NB - 1 ? 2 : 1)>;
+        using Left = std::integral_constant<int, (I == NB - 2 ? -1 : (NB - 3 - I))>;   // (the last stage reads nothing: no barrier before it)
+        if constexpr (I % 2 == 0) advance(kt + I, r0, r1, Mode{}, Left{}); else advance(kt + I, r1, r0, Mode{}, Left{});
+      });
+    } else {                             // shorter than the ring: everything has landed
+      for (; kt < nk - 1; kt++) { advance(kt, r0, r1, I1{}, I0{}); r0 = r1; }
+      advance(kt, r0, r1, I2{}, I0{});
+    }
+  } else if constexpr (SPARSE) {
     FragS<MI, NI> f0, f1;
     constexpr int NF = MI + 2 * NI;
     IdxWords<F8> idx[MI];
