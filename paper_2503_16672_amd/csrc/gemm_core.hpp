@@ -303,6 +303,22 @@ struct LaneCtx {
   int sw8a;         // swz8 of the lane's A row for even mi (odd mi: ^4)
 };
 
+template <int MI, int NI>
+__device__ __forceinline__ LaneCtx lane_ctx(int tid) {
+  const int lane = tid & 63, wave = tid >> 6;
+  LaneCtx L;
+  L.rho = lane & 31; L.h = lane >> 5; L.wy = wave >> 1; L.wx = wave & 1;
+  L.a_row64 = (L.wy * (32 * MI) + L.rho) * 64;
+  L.b_row64 = (L.wx * (32 * NI) + L.rho) * 64;
+  L.a_row128 = (L.wy * (32 * MI) + L.rho) * 128;
+  L.b_row128 = (L.wx * (32 * NI) + L.rho) * 128;
+  L.sw4 = swz4(L.rho);
+  // (from NI = 2, MI = 2 on the wave column, wave row moves the row by a multiple of 64, which the swizzle does not see)
+  L.sw8 = NI == 1 ? swz8(L.wx * 32 + L.rho) : swz8(L.rho);
+  L.sw8a = MI == 1 ? swz8(L.wy * 32 + L.rho) : swz8(L.rho);
+  return L;
+}
+
 // Dense: K step S (0,1) of the 64-byte stage rows; fragment I < MI -> a[I], else b[I-MI]
 template <int MI, int NI>
 struct FragD {
@@ -538,16 +554,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
   tile_coords<PROBE, MI == 2 * NI>(g.M / G::BM, g.N / G::BN, pid, tm, tn);
   int m0 = tm * G::BM, n0 = tn * G::BN;
 
-  LaneCtx L;
-  L.rho = lane & 31; L.h = lane >> 5; L.wy = wave >> 1; L.wx = wave & 1;
-  L.a_row64 = (L.wy * (32 * MI) + L.rho) * 64;
-  L.b_row64 = (L.wx * (32 * NI) + L.rho) * 64;
-  L.a_row128 = (L.wy * (32 * MI) + L.rho) * 128;
-  L.b_row128 = (L.wx * (32 * NI) + L.rho) * 128;
-  L.sw4 = swz4(L.rho);
-  // (from NI = 2, MI = 2 on the wave column, wave row moves the row by a multiple of 64, which the swizzle does not see)
-  L.sw8 = NI == 1 ? swz8(L.wx * 32 + L.rho) : swz8(L.rho);
-  L.sw8a = MI == 1 ? swz8(L.wy * 32 + L.rho) : swz8(L.rho);
+  const LaneCtx L = lane_ctx<MI, NI>(tid);
 
   Dma<SPARSE, F8, PROBE, MI, NI> dma;
   dma.init(g, m0, n0, tid);
@@ -917,6 +924,177 @@ __global__ void __launch_bounds__(GEMM_THREADS, (Geo<SPARSE, F8, MI, NI>::PER_CU
   if (second) { g.A = gb.A; g.Ameta = gb.Ameta; g.B = gb.B; }
   const typename EpiDuo<EpiA, EpiB>::Args e{ea, eb, second};
   gemm_tile<SPARSE, EpiDuo<EpiA, EpiB>, F8, 0, MI, NI>(g, e, smem, second ? bid - n_first : bid);
+}
+
+// ------------------------------------------------------------------------------------------------
+// the sparse GEMM on a caller's row-major operands (spmm24)
+// ------------------------------------------------------------------------------------------------
+// Row-major, the 64 k of a stage are 64 bytes of an A row, half a line, and 8 bytes of metadata: 256 and 64 requests of the 128 x 64 tile's 320
+// a stage are for pieces of a line, and a CU's global->LDS stream takes about three cycles a request whatever its size (the main loop above
+// spent 53.2 of its 54.5 us at M 2048 N 1024 K 8256 waiting for it, now 37.6 in all; in panel form the same stream takes 25.7).  So a ring slot here holds
+// 128 k: whole lines of A, 16 bytes of metadata a row, and B as two halves of 64 k in the layout of the loop above.  The halves are
+// walked with two register sets, each read while the other's matrix ops run; one wait and one barrier for both.  K need not be a
+// multiple of 128: lanes that would pass the end of a row fetch its last bytes again, and the last half is not walked.  Every
+// second row of A then starts in the middle of a line.  SHIFT (taken then by the 128 x 64 tile, which has four slots): a slot holds those rows' 128 bytes
+// from 64 before, so that they are whole lines too, their two halves stand the other way round, and the second half
+// of what the others have in slot kt is the first of slot kt + 1 (K 8256, 128 x 64: 39.7 us, 43.9 without, 34.4 with K 8192; with 128 x 128,
+// whose three slots leave no time for it, 65 against 53).
+template <int MI, int NI>
+struct GeoRows {
+  static constexpr int BM = 64 * MI, BN = 64 * NI, BK = 128;
+  static constexpr int A_BYTES = BM * 128, META_BYTES = BM * 16, B_HALF = BN * 128;
+  static constexpr int META_OFF = A_BYTES, B_OFF = A_BYTES + META_BYTES, STAGE = B_OFF + 2 * B_HALF;
+  static constexpr int NB = MI * NI == 8 ? 2 : MI * NI == 2 ? 4 : 3;    // slots: what the LDS holds, of the smallest tile what half of it holds
+  static constexpr int LDS_TOTAL = NB * STAGE, PER_CU = LDS_TOTAL <= 80 * 1024 ? 2 : 1;
+  static constexpr int NA = 2 * MI, NM = MI, NVB = 4 * NI, NDMA = NA + NM + NVB;   // DMA instructions per wave and slot
+};
+
+template <int MI, int NI, bool SHIFT>
+struct DmaRows {
+  using G = GeoRows<MI, NI>;
+  const char *a, *am, *b;
+  uint32_t ra[G::NA], rm[G::NM], rb[G::NVB];        // the lane's row, as a byte offset from the uniform bases
+  uint32_t la, lm, lb;                              // the last place inside a row that a fetch may start at
+  int wave;
+  __device__ __forceinline__ void init(const GemmArgs& g, int m0, int n0, int tid) {
+    const int lane = tid & 63;
+    wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t a_row = (uint32_t)g.K, m_row = (uint32_t)g.K / 8, b_row = 2 * (uint32_t)g.K;
+    a = static_cast<const char*>(g.A) + (size_t)m0 * a_row;
+    am = reinterpret_cast<const char*>(g.Ameta) + (size_t)m0 * m_row;
+    b = static_cast<const char*>(g.B) + (size_t)n0 * b_row;
+    la = a_row - 16; lm = m_row - 4; lb = b_row - 16;
+    // 8 rows of 128 bytes an instruction
+#pragma unroll
+    for (int j = 0; j < G::NA; j++) ra[j] = (uint32_t)unperm_m<MI>(8 * (G::NA * wave + j) + (lane >> 3)) * a_row;
+    // 16 rows of 16 bytes, a dword a lane
+#pragma unroll
+    for (int j = 0; j < G::NM; j++) rm[j] = (uint32_t)unperm_m<MI>(16 * (G::NM * wave + j) + (lane >> 2)) * m_row;
+    // the two halves of B lie one after the other; 8 rows of 128 bytes an instruction
+#pragma unroll
+    for (int j = 0; j < G::NVB; j++) rb[j] = (uint32_t)unperm_n<NI>((8 * (G::NVB * wave + j) + (lane >> 3)) & (G::BN - 1)) * b_row;
+  }
+  template <int J>
+  __device__ __forceinline__ void issue(int kt, char* buf) const {
+    const int lane = threadIdx.x & 63;
+    if constexpr (J < G::NA) {
+      const int p = 8 * (G::NA * wave + J) + (lane >> 3);
+      const int at = kt * 128 + (((lane & 7) ^ swz8(p)) << 4) - (SHIFT ? (p & 1) << 6 : 0);   // (unperm_m keeps the low bits: odd rows)
+      const uint32_t in = (uint32_t)min(max(at, 0), (int)la);
+      __builtin_amdgcn_global_load_lds((glb_char*)(a + (ra[J] + in)), (lds_char*)(buf + (G::NA * wave + J) * 1024), 16, 0, 0);
+    } else if constexpr (J < G::NA + G::NM) {
+      constexpr int j = J - G::NA;
+      const uint32_t in = min((uint32_t)kt * 16u + 4u * (lane & 3), lm);
+      __builtin_amdgcn_global_load_lds((glb_char*)(am + (rm[j] + in)), (lds_char*)(buf + G::META_OFF + (G::NM * wave + j) * 256), 4, 0, 0);
+    } else {
+      constexpr int j = J - G::NA - G::NM;
+      const int q = 8 * (G::NVB * wave + j), p = (q + (lane >> 3)) & (G::BN - 1);   // (an instruction's 8 rows lie in one half)
+      const uint32_t in = min((uint32_t)kt * 256u + (q >= G::BN ? 128u : 0u) + (uint32_t)(((lane & 7) ^ swz8(p)) << 4), lb);
+      __builtin_amdgcn_global_load_lds((glb_char*)(b + (rb[j] + in)), (lds_char*)(buf + G::B_OFF + (G::NVB * wave + j) * 1024), 16, 0, 0);
+    }
+  }
+};
+
+// read I of half HALF of the slot at buf (the order of StageRegs<true>: metadata, then the fragments of either K step); abuf: the slot that
+// holds this lane's A rows
+template <int MI, int NI, int HALF, int I>
+__device__ __forceinline__ void read_rows(const char* buf, const char* abuf, const LaneCtx& L, StageRegs<true, false, MI, NI>& r) {
+  using G = GeoRows<MI, NI>;
+  constexpr int NF = MI + 2 * NI;
+  if constexpr (I < MI) {
+    r.idx[I].w[0] = *reinterpret_cast<const uint32_t*>(buf + G::META_OFF + (L.wy * (32 * MI) + L.rho + 32 * I) * 16 + 8 * HALF + 4 * L.h);
+  } else {
+    constexpr int S = (I - MI) / NF, i = (I - MI) % NF;
+    FragS<MI, NI>& f = r.f[S];
+    if constexpr (i < MI) {
+      f.a[i] = *reinterpret_cast<const bf16x8*>(abuf + L.a_row128 + i * (32 * 128) + (((4 * HALF + 2 * L.h + S) ^ L.sw8a ^ ((i & 1) << 2)) << 4));
+    } else {
+      constexpr int n = (i - MI) % NI;
+      const int sw = L.sw8 ^ ((n & 1) << 2);
+      const char* row = buf + G::B_OFF + HALF * G::B_HALF + L.b_row128 + n * (32 * 128);
+      if constexpr (i < MI + NI) f.blo[n] = *reinterpret_cast<const bf16x8*>(row + (((2 * S + L.h) ^ sw) << 4));
+      else f.bhi[n] = *reinterpret_cast<const bf16x8*>(row + (((4 + 2 * S + L.h) ^ sw) << 4));
+    }
+  }
+}
+
+template <class Epi, int MI, int NI, bool SHIFT>
+__global__ void __launch_bounds__(GEMM_THREADS, (GeoRows<MI, NI>::PER_CU)) gemm_rows_kernel(GemmArgs g, typename Epi::Args ea) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  using G = GeoRows<MI, NI>;
+  using SR = StageRegs<true, false, MI, NI>;
+  constexpr int NB = G::NB, NDMA = G::NDMA;
+  constexpr int AHEAD = SHIFT ? 2 : 1;               // slots beyond the present one that must have landed when its second half begins
+  static_assert(NB > AHEAD, "a slot is asked for after that");
+  const int tid = threadIdx.x;
+  int tm, tn;
+  tile_coords<0, MI == 2 * NI>(g.M / G::BM, g.N / G::BN, blockIdx.x, tm, tn);
+  const int m0 = tm * G::BM, n0 = tn * G::BN;
+  LaneCtx L = lane_ctx<MI, NI>(tid);
+  const bool shifted = SHIFT && (L.rho & 1);
+  if (shifted) L.sw8a ^= 4;                          // the halves the other way round
+  DmaRows<MI, NI, SHIFT> dma;
+  dma.init(g, m0, n0, tid);
+  const int nk = (g.K + G::BK - 1) / G::BK;
+  const bool odd = (g.K & 64) != 0;                  // the last slot's second half does not exist
+  const int npro = nk < NB ? nk : NB;
+  for (int s = 0; s < npro; s++) static_for<NDMA>([&](auto J) { dma.template issue<J>(s, smem + s * G::STAGE); });
+  f32x16 acc[MI][NI];
+#pragma unroll
+  for (int i = 0; i < MI; i++)
+#pragma unroll
+    for (int j = 0; j < NI; j++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) acc[i][j][v] = 0.f;
+  if (npro == NB) wait_vmcnt<(NB - AHEAD) * NDMA>(); else wait_vmcnt<0>();
+  __builtin_amdgcn_s_barrier();
+  FFN24_FENCE();
+  SR r0, r1;
+  static_for<SR::READS>([&](auto I) { read_rows<MI, NI, 0, I>(smem, smem, L, r0); });
+  // first half of a slot; the second half's fragments are read meanwhile
+  auto first = [&](const char* cur, const char* nxt) {
+    const char* abuf = shifted ? nxt : cur;
+    static_for<SR::OPS>([&](auto M) {
+      r0.template op<M, 0>(acc);
+      ride<SR::READS, SR::READ_SLOTS, M>([&](auto I) { read_rows<MI, NI, 1, I>(cur, abuf, L, r1); });
+      FFN24_FENCE();
+    });
+  };
+  // second half; the next slot's first fragments are read and, ISSUE, the slot kt + NB asked for into this slot, which every wave has read
+  auto second = [&](int kt, char* cur, const char* nxt, auto issue, auto more) {
+    constexpr bool ISSUE = decltype(issue)::value, MORE = decltype(more)::value;
+    static_for<SR::OPS>([&](auto M) {
+      r1.template op<M, 0>(acc);
+      if constexpr (MORE) ride<SR::READS, SR::READ_SLOTS, M>([&](auto I) { read_rows<MI, NI, 0, I>(nxt, nxt, L, r0); });
+      if constexpr (ISSUE) ride<NDMA, SR::OPS, M>([&](auto J) { dma.template issue<J>(kt + NB, cur); });
+      FFN24_FENCE();
+    });
+  };
+  using Yes = std::true_type; using No = std::false_type;
+  int slot = 0;
+  auto advance = [&](int kt, auto issue, auto left) {
+    constexpr int LEFT = decltype(left)::value;
+    const int ns = slot + 1 == NB ? 0 : slot + 1;
+    char *cur = smem + slot * G::STAGE, *nxt = smem + ns * G::STAGE;
+    FFN24_FENCE();
+    first(cur, nxt);
+    wait_vmcnt<(LEFT > 0 ? LEFT : 0) * NDMA>();      // slot kt + AHEAD has landed; LEFT later ones may be in flight
+    wait_lgkmcnt0();
+    __builtin_amdgcn_s_barrier();
+    FFN24_FENCE();
+    second(kt, cur, nxt, issue, Yes{});
+    slot = ns;
+  };
+  int kt = 0;
+  if (nk >= NB) {
+    for (; kt < nk - NB; kt++) advance(kt, Yes{}, std::integral_constant<int, NB - 1 - AHEAD>{});
+    static_for<NB - 1>([&](auto i) { advance(kt + decltype(i)::value, No{}, std::integral_constant<int, NB - 1 - AHEAD - decltype(i)::value>{}); });
+  } else {
+    for (; kt < nk - 1; kt++) advance(kt, No{}, std::integral_constant<int, 0>{});
+  }
+  first(smem + slot * G::STAGE, smem + slot * G::STAGE);   // (reads a second half even where there is none: nothing is made of it)
+  if (!odd) second(0, smem, smem, No{}, No{});
+  Epi::template run<MI, NI>(ea, acc, m0 + L.wy * (32 * MI) + (16 * MI) * L.h, n0 + L.wx * (32 * NI) + NI * L.rho);
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -18,6 +18,7 @@ int launch_up_prune24(const void* W1t, const void* X, const float* b1, int T, in
 int launch_sp_rowmajor(const void* vals, const uint8_t* meta, int a_panel, const void* B, int b_panel, int M, int N, int K, void* C, hipStream_t s) {
   GemmArgs g{vals, meta, B, M, N, K, a_panel, nullptr, b_panel};
   EpiRowMajor::Args ea{static_cast<__bf16*>(C), N};
+  if (!a_panel && !b_panel && K >= ROWS_MIN_K) return launch_gemm_rows<EpiRowMajor>(g, ea, s);
   return launch_gemm<true, EpiRowMajor>(g, ea, s);
 }
 

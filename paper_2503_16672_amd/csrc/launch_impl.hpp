@@ -35,6 +35,28 @@ static int launch_gemm(const GemmArgs& g_in, const typename Epi::Args& ea, hipSt
   }
 }
 
+template <class Epi, int MI, int NI, bool SHIFT>
+static int launch_rows_tile(const GemmArgs& g, const typename Epi::Args& ea, hipStream_t s) {
+  using G = GeoRows<MI, NI>;
+  auto kern = gemm_rows_kernel<Epi, MI, NI, SHIFT>;
+  static std::atomic<bool> configured[MAX_DEVICES] = {};
+  if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), G::LDS_TOTAL, configured)) return rc;
+  hipLaunchKernelGGL(kern, dim3((g.M / G::BM) * (g.N / G::BN)), dim3(GEMM_THREADS), G::LDS_TOTAL, s, g, ea);
+  return (int)hipGetLastError();
+}
+
+// A 2:4 operand and a dense one as a caller has them, row-major (gemm_rows_kernel), bf16.
+template <class Epi>
+static int launch_gemm_rows(const GemmArgs& g, const typename Epi::Args& ea, hipStream_t s) {
+  switch (pick_tile(true, false, EPI_PLAIN, g.M, g.N, g.K, 1, true)) {
+    case 0: return launch_tile<true, Epi, false, 0, 4, 4>(g, ea, s);
+    case 1: return launch_rows_tile<Epi, 4, 2, false>(g, ea, s);
+    case 2: return launch_rows_tile<Epi, 2, 2, false>(g, ea, s);
+    case 3: return g.K % 128 ? launch_rows_tile<Epi, 2, 1, true>(g, ea, s) : launch_rows_tile<Epi, 2, 1, false>(g, ea, s);
+    default: return launch_rows_tile<Epi, 1, 1, false>(g, ea, s);
+  }
+}
+
 template <bool SPARSE, class EpiA, class EpiB, bool F8, int MI, int NI>
 static int launch_duo_tile(const GemmArgs& ga, const typename EpiA::Args& ea, const GemmArgs& gb, const typename EpiB::Args& eb, hipStream_t s) {
   using G = Geo<SPARSE, F8, MI, NI>;

@@ -16,7 +16,7 @@ namespace ffn24 {
 struct TileCost { int mi, ni, per_k, fixed; };   // 0.1 ns per (bf16) k; ns per tile
 constexpr TileCost TILES_SPARSE[] = {{4, 4, 140, 6000}, {4, 2, 92, 5000}, {2, 2, 57, 3000}, {2, 1, 39, 2000}, {1, 1, 26, 1500}};
 constexpr TileCost TILES_DENSE[] = {{4, 4, 205, 19000}, {4, 2, 132, 5000}, {2, 2, 84, 1750}, {2, 1, 52, 2000}, {1, 1, 34, 1000}};
-constexpr int NUM_TILES = 5;   // the two tables list the same tiles
+constexpr int NUM_TILES = 5;   // the tables list the same tiles
 constexpr long long CHIP_CUS = 256;
 
 // What an epilogue adds to the fill and store of the two largest dense tiles (ns).  The fp8 epilogues scale or quantise every value beside
@@ -25,14 +25,23 @@ constexpr long long CHIP_CUS = 256;
 struct EpiCost { int t256x256, t256x128; };
 constexpr EpiCost EPI_PLAIN = {0, 0}, EPI_FP8 = {3000, 0}, EPI_FP8_SPILLS = {3000, 8000};
 
+// The same for a caller's row-major 2:4 operand (spmm24) with K >= ROWS_MIN_K, single launches: 256 x 256 with the main loop of the panel forms,
+// the others with gemm_rows_kernel, whose slots take whole lines of the rows and do not fit the LDS with 256 x 256.  Fitted to 70 shapes (M 256-8192, N
+// 256-4096, K 256-16384): of those with K >= ROWS_MIN_K each takes the fastest of the five.  M 8192 N 2048 K 4096: 256 x 256 71 us, 256 x 128
+// 88; M 4096 N 2048 K 4096: 45 with 256 x 128, 56 with 128 x 128 and with 256 x 256; M 2048 N 2048 K 4096: 28 with 128 x 128, 37 with 128 x 64.
+// Shorter reductions keep the kernels of the panel forms and their rule: with few slots there is little to gain (M N 1024 K 832: 5.2 -> 4.8 us)
+// and the larger slots leave one workgroup on a CU where two ran (M 8192 N 4096 K 512, 128 x 128: 33 -> 41 us).
+constexpr int ROWS_MIN_K = 2048;
+constexpr TileCost TILES_ROWS[] = {{4, 4, 155, 5000}, {4, 2, 105, 3700}, {2, 2, 62, 2000}, {2, 1, 39, 2100}, {1, 1, 28, 400}};
+
 inline long long tile_time(const TileCost& t, int K, bool f8) { return (long long)(f8 ? K / 2 : K) * t.per_k / 10 + t.fixed; }
 inline long long tile_count(const TileCost& t, int M, int N) { return (long long)(M / (64 * t.mi)) * (N / (64 * t.ni)); }
 
-inline int pick_tile(bool sparse, bool f8, EpiCost epi, int M, int N, int K, int gemms = 1) {   // gemms: that many of this size share the launch
+inline int pick_tile(bool sparse, bool f8, EpiCost epi, int M, int N, int K, int gemms = 1, bool rows = false) {   // gemms: that many of this size share the launch
   int best = 0;
   long long best_time = 0;
   for (int i = 0; i < NUM_TILES; i++) {
-    const TileCost& t = sparse ? TILES_SPARSE[i] : TILES_DENSE[i];
+    const TileCost& t = rows ? TILES_ROWS[i] : sparse ? TILES_SPARSE[i] : TILES_DENSE[i];
     const long long one = tile_time(t, K, f8) + (i == 0 ? epi.t256x256 : i == 1 ? epi.t256x128 : 0);
     const long long time = (gemms * tile_count(t, M, N) + CHIP_CUS - 1) / CHIP_CUS * one;
     if (i == 0 || time * 100 < best_time * 97) { best = i; best_time = time; }
