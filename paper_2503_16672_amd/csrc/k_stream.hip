@@ -149,10 +149,27 @@ int launch_sparsify24(const void* H, int64_t rows, int64_t cols, void* vals, uin
 // Output: for every feature, groups of 4 consecutive tokens of the pruned activation keep their top-2:
 //   Hc_t [F][T/2], meta_t [F][T/8], and dZc_t [F][T/2] = dZ at the positions picked for H.
 // Inputs and outputs in the panel form of gemm_core.hpp (a caller's row-major tensors: PANEL = false and featurewise24_rows_kernel below).
-// One workgroup handles 64 tokens x 64 features: decompress into LDS, then each work item takes one feature
-// and 8 consecutive tokens (two groups).  The workgroup's input is one contiguous 4 KiB run per tensor and it writes one contiguous
-// 4 KiB run; 128-token tiles, with twice the LDS per workgroup and half the workgroups per CU, ran at 5.0 instead of 5.9 TB/s.
-constexpr int FW_TOK = 64, FW_FEAT = 64, FW_LD = FW_FEAT + 2;
+// One workgroup handles 64 tokens x 64 features at a time: decompress into LDS, then each work item takes two features and 8 consecutive
+// tokens (two groups each).  A tile's input is one contiguous 4 KiB run per tensor and it writes one contiguous 4 KiB run; 128-token
+// tiles, with twice the LDS per workgroup and half the workgroups per CU, ran at 5.0 instead of 5.9 TB/s.  Words are pairs of features
+// throughout, f in the low half and f + 8 in the high half, so that the decompression and the pick are packed and bitwise arithmetic on
+// two groups, LDS is accessed by whole dwords (a pitch of 33: a wave's reads, 8 words of 8 token octets, fall into 64 different banks),
+// and a wave's stores cover 8 consecutive features at a time.
+// A workgroup walks `tiles` tiles of 64 tokens, the next one's input on its way while this one is worked on, and raises the row maxima
+// once: with one tile a workgroup two million atomics went out at T = F = 8192.  What bounds it is HBM; feature by feature and tile by tile
+// it took 82.9 us there with the maxima and a split, now 56.6 = 5.0 TB/s; without them, T = F = 16384, 206 -> 192 = 5.9 TB/s; T 1280 F 3072
+// 5.7 -> 4.5.
+constexpr int FW_TOK = 64, FW_FEAT = 64, FW_LDW = FW_FEAT / 2 + 1, FW_TILES = 4;
+
+// all ones in the halves of the mask where bit b of the half is set
+__device__ __forceinline__ uint32_t half_mask(uint32_t w, int b) {
+  uint32_t m = __builtin_bit_cast(uint32_t, (i16x2)((i16x2)(as_i16x2(w) << (i16x2)(15 - b)) >> (i16x2)(15)));
+  asm("" : "+v"(m));   // (opaque, as in pk_less16)
+  return m;
+}
+__device__ __forceinline__ uint32_t sel(uint32_t mask, uint32_t a, uint32_t b) { return (mask & a) | (~mask & b); }
+__device__ __forceinline__ uint32_t halves_lo(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }   // a's low half, b's above it
+__device__ __forceinline__ uint32_t halves_hi(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
 
 // PANEL: in the panel form; otherwise row-major, for matrices too small for featurewise24_rows_kernel's tiles to fill the chip.
 // SPLIT (Sec. 2, "Optimization 1"; panel form only): feature f becomes row row_of_feat[f] of the outputs; rows below
@@ -160,115 +177,134 @@ constexpr int FW_TOK = 64, FW_FEAT = 64, FW_LD = FW_FEAT + 2;
 // uncompressed, as rows [row - n_sparse] of the dense operands Hdn_t, dZdn_t [n_dense][T] (dense panel form).
 template <bool PANEL, bool SPLIT = false>
 __global__ void __launch_bounds__(256) featurewise24_kernel(const uint16_t* __restrict__ Hc, const uint8_t* __restrict__ meta,
-                                                            const uint16_t* __restrict__ dZc, int T, int F,
+                                                            const uint16_t* __restrict__ dZc, int T, int F, int tiles,
                                                             uint16_t* __restrict__ Hc_t, uint8_t* __restrict__ meta_t,
                                                             uint16_t* __restrict__ dZc_t, const int* __restrict__ row_of_feat,
                                                             int n_sparse, uint16_t* __restrict__ Hdn_t, uint16_t* __restrict__ dZdn_t,
                                                             unsigned long long* __restrict__ tele, uint32_t* __restrict__ hmax,
                                                             uint32_t* __restrict__ zmax) {
-  __shared__ uint16_t sH[FW_TOK * FW_LD];
-  __shared__ uint16_t sZ[FW_TOK * FW_LD];
-  int f0 = blockIdx.x * FW_FEAT, t0 = blockIdx.y * FW_TOK;
-  int tid = threadIdx.x;
-  bool has_z = dZc != nullptr;
-#pragma unroll
-  for (int i = 0; i < FW_TOK / 64; i++) {
-    int item = tid + 256 * i;
-    int tok = item >> 2, ch = item & 3;
-    int t = t0 + tok;
+  __shared__ uint32_t sH[FW_TOK * FW_LDW];
+  __shared__ uint32_t sZ[FW_TOK * FW_LDW];
+  const int f0 = blockIdx.x * FW_FEAT, t_first = blockIdx.y * FW_TOK * tiles;
+  const int tid = threadIdx.x;
+  const bool has_z = dZc != nullptr;
+  const int tok = tid >> 2, ch = tid & 3;            // in: 16 features of a token
+  const int oct = tid & 7, word = tid >> 3;          // out: 8 tokens of features fa and fa + 8
+  const int fa = ((word >> 3) << 4) | (word & 7);
+  u32x4 hv, zv = {0u, 0u, 0u, 0u};
+  uint32_t mv;
+  auto request = [&](int t0) {
     // offsets of this item's 8 stored values (in elements) and of its 2 metadata bytes
+    const int t = t0 + tok;
     const size_t piece = PANEL ? a24_piece(t, f0 >> 6, F >> 6) : (size_t)t * (F >> 6) + (f0 >> 6), vo = piece * 32 + 8 * ch, mo = piece * 8 + 2 * ch;
-    u32x4 hv = ld_stream(reinterpret_cast<const u32x4*>(Hc + vo));
-    u32x4 zv = {0u, 0u, 0u, 0u};
+    hv = ld_stream(reinterpret_cast<const u32x4*>(Hc + vo));
     if (has_z) zv = ld_stream(reinterpret_cast<const u32x4*>(dZc + vo));
-    uint32_t m16 = ld_stream(reinterpret_cast<const uint16_t*>(meta + mo));
+    mv = ld_stream(reinterpret_cast<const uint16_t*>(meta + mo));
+  };
+  request(t_first);
+  int orow[2];
+  uint32_t dense = 0u;                               // SPLIT: the halves whose feature is written out uncompressed
 #pragma unroll
-    for (int g = 0; g < 4; g++) {
-      uint32_t nib = (m16 >> (4 * g)) & 15u;
-      uint32_t i0 = nib & 3u, i1 = nib >> 2;
-      uint32_t h_lo = hv[g] & 0xFFFFu, h_hi = hv[g] >> 16, z_lo = zv[g] & 0xFFFFu, z_hi = zv[g] >> 16;
-      uint32_t hw[4], zw[4];
-#pragma unroll
-      for (uint32_t j = 0; j < 4; j++) {
-        hw[j] = (i0 == j) ? h_lo : ((i1 == j) ? h_hi : 0u);
-        zw[j] = (i0 == j) ? z_lo : ((i1 == j) ? z_hi : 0u);
-      }
-      int o = tok * FW_LD + 16 * ch + 4 * g;   // even: 4-byte aligned
-      *reinterpret_cast<uint32_t*>(&sH[o]) = hw[0] | (hw[1] << 16);
-      *reinterpret_cast<uint32_t*>(&sH[o + 2]) = hw[2] | (hw[3] << 16);
-      *reinterpret_cast<uint32_t*>(&sZ[o]) = zw[0] | (zw[1] << 16);
-      *reinterpret_cast<uint32_t*>(&sZ[o + 2]) = zw[2] | (zw[3] << 16);
-    }
+  for (int b = 0; b < 2; b++) {
+    orow[b] = SPLIT ? row_of_feat[f0 + fa + 8 * b] : f0 + fa + 8 * b;
+    if (SPLIT && orow[b] >= n_sparse) dense |= 0xFFFFu << (16 * b);
   }
-  __syncthreads();
-  uint32_t kept = 0u;   // non-zero activations this work item writes out (at most 32)
+  uint32_t kept = 0u, mh = 0u, mz = 0u;              // non-zero activations this work item writes out; its largest magnitudes (of either half)
+  for (int it = 0; it < tiles; it++) {
+    const int t0 = t_first + FW_TOK * it;
+    const uint32_t mm = (mv & 0xFFu) | ((mv & 0xFF00u) << 8);   // nibbles of groups 0, 1 below, of groups 2, 3 in the high half
 #pragma unroll
-  for (int i = 0; i < FW_TOK / 32; i++) {
-    int item = tid + 256 * i;
-    const int oct = (item & 7) | ((item >> 9) << 3), f = (item >> 3) & 63;
+    for (int g = 0; g < 2; g++) {                    // groups g and g + 2
+      const uint32_t b0 = half_mask(mm, 4 * g), b1 = half_mask(mm, 4 * g + 1), b2 = half_mask(mm, 4 * g + 2), b3 = half_mask(mm, 4 * g + 3);
+      const uint32_t at0[4] = {~b0 & ~b1, b0 & ~b1, ~b0 & b1, b0 & b1}, at1[4] = {~b2 & ~b3, b2 & ~b3, ~b2 & b3, b2 & b3};
+      const uint32_t h0 = halves_lo(hv[g], hv[g + 2]), h1 = halves_hi(hv[g], hv[g + 2]), z0 = halves_lo(zv[g], zv[g + 2]), z1 = halves_hi(zv[g], zv[g + 2]);
+      const int o = tok * FW_LDW + 8 * ch + 4 * g;
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        sH[o + j] = sel(at0[j], h0, h1 & at1[j]);
+        if (has_z) sZ[o + j] = sel(at0[j], z0, z1 & at1[j]);
+      }
+    }
+    __syncthreads();
+    if (it + 1 < tiles) request(t0 + FW_TOK);
     uint32_t h[8], z[8];
 #pragma unroll
     for (int j = 0; j < 8; j++) {
-      h[j] = sH[(8 * oct + j) * FW_LD + f];
-      z[j] = sZ[(8 * oct + j) * FW_LD + f];
+      h[j] = sH[(8 * oct + j) * FW_LDW + word];
+      z[j] = has_z ? sZ[(8 * oct + j) * FW_LDW + word] : 0u;
     }
-    int orow = f0 + f;
-    if constexpr (SPLIT) {
-      orow = row_of_feat[f0 + f];
-      if (orow >= n_sparse) {   // dense feature: its 8 tokens as they are (already token-wise pruned)
-        size_t o = a24_piece(orow - n_sparse, (t0 + 8 * oct) >> 5, T >> 5) * 32 + ((t0 + 8 * oct) & 31);
-        *reinterpret_cast<u32x4*>(Hdn_t + o) = u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
-        if (has_z) *reinterpret_cast<u32x4*>(dZdn_t + o) = u32x4{z[0] | (z[1] << 16), z[2] | (z[3] << 16), z[4] | (z[5] << 16), z[6] | (z[7] << 16)};
-#pragma unroll
-        for (int j = 0; j < 8; j++) kept += min(h[j], 1u);
-        if (hmax) {   // as below: the eight work items of a feature are neighbouring lanes and take this branch together
-          uint32_t mh = 0u, mz = 0u;
-#pragma unroll
-          for (int j = 0; j < 8; j++) { mh = max(mh, h[j]); mz = max(mz, z[j] & 0x7FFFu); }
-#pragma unroll
-          for (int sft = 1; sft < 8; sft <<= 1) {
-            mh = max(mh, (uint32_t)__shfl_xor((int)mh, sft, 64));
-            mz = max(mz, (uint32_t)__shfl_xor((int)mz, sft, 64));
-          }
-          if ((tid & 7) == 0) {
-            if (mh) atomicMax(hmax + orow, mh);
-            if (mz && has_z) atomicMax(zmax + orow, mz);
-          }
-        }
-        continue;
-      }
-    }
-    uint32_t hp[2], zp[2], nb[2];
+    if (it + 1 < tiles) __syncthreads();             // the next tile may overwrite the image
+    uint32_t hp[2][2], zp[2][2], nib = 0u;           // [feature][group]
+    uint32_t zall = 0u;
 #pragma unroll
     for (int g = 0; g < 2; g++) {
-      nb[g] = pick24_words(h[4 * g], h[4 * g + 1], h[4 * g + 2], h[4 * g + 3], hp[g]);
-      uint32_t i0 = nb[g] & 3u, i1 = nb[g] >> 2;
-      uint32_t za = i0 == 0 ? z[4 * g] : (i0 == 1 ? z[4 * g + 1] : z[4 * g + 2]);
-      uint32_t zb = i1 == 3 ? z[4 * g + 3] : (i1 == 2 ? z[4 * g + 2] : z[4 * g + 1]);
-      zp[g] = za | (zb << 16);
-    }
-    const size_t piece = PANEL ? a24_piece(orow, (t0 + 8 * oct) >> 6, T >> 6) : (size_t)orow * (T >> 6) + ((t0 + 8 * oct) >> 6);
-    const size_t vo = piece * 32 + 4 * (oct & 7), mo = piece * 8 + (oct & 7);
-    st_stream(reinterpret_cast<u32x2*>(Hc_t + vo), u32x2{hp[0], hp[1]});
-    if (has_z) st_stream(reinterpret_cast<u32x2*>(dZc_t + vo), u32x2{zp[0], zp[1]});
-    st_stream(meta_t + mo, (uint8_t)(nb[0] | (nb[1] << 4)));
-    if (hmax) {
-      // largest stored magnitude word of this feature's row, for a row-wise quantisation that follows (the eight work items of
-      // a feature are neighbouring lanes: one atomic per feature, tensor and workgroup)
-      static_assert(FW_TOK == 64, "the eight items of a feature are the lanes tid & 7");
-      uint32_t mh = max(max(hp[0] & 0xFFFFu, hp[0] >> 16), max(hp[1] & 0xFFFFu, hp[1] >> 16));
-      uint32_t mz = max(max(zp[0] & 0x7FFFu, (zp[0] >> 16) & 0x7FFFu), max(zp[1] & 0x7FFFu, (zp[1] >> 16) & 0x7FFFu));
+      uint32_t m[4];
 #pragma unroll
-      for (int sft = 1; sft < 8; sft <<= 1) {
-        mh = max(mh, (uint32_t)__shfl_xor((int)mh, sft, 64));
-        mz = max(mz, (uint32_t)__shfl_xor((int)mz, sft, 64));
+      for (int j = 0; j < 4; j++) m[j] = h[4 * g + j] & 0x7FFF7FFFu;   // the pick is by magnitude
+      const Pick24x2 p = pick24_two(m[0], m[1], m[2], m[3]);
+      const uint32_t second0 = p.bit[0] /* i0 == 1 */, third0 = p.bit[1], last1 = p.bit[2] & p.bit[3], not_first1 = p.bit[3];
+      const uint32_t *a = h + 4 * g, *c = z + 4 * g;
+      const uint32_t hf = sel(third0, a[2], sel(second0, a[1], a[0])), hs = sel(not_first1, sel(last1, a[3], a[2]), a[1]);
+      const uint32_t zf = sel(third0, c[2], sel(second0, c[1], c[0])), zs = sel(not_first1, sel(last1, c[3], c[2]), c[1]);
+      hp[0][g] = halves_lo(hf, hs); hp[1][g] = halves_hi(hf, hs);
+      zp[0][g] = halves_lo(zf, zs); zp[1][g] = halves_hi(zf, zs);
+      nib = put_nibbles(nib, p, g);
+      if (hmax) {
+        mh = pk_max16(mh, pk_max16(pk_max16(m[0], m[1]), pk_max16(m[2], m[3])));   // (the largest of a group is always kept)
+        mz = pk_max16(mz, SPLIT ? ~dense & pk_max16(zf & 0x7FFF7FFFu, zs & 0x7FFF7FFFu) : pk_max16(zf & 0x7FFF7FFFu, zs & 0x7FFF7FFFu));
+        if constexpr (SPLIT) {
+#pragma unroll
+          for (int j = 0; j < 4; j++) zall = pk_max16(zall, c[j] & 0x7FFF7FFFu);
+        }
       }
-      if ((tid & 7) == 0) {
-        if (mh) atomicMax(hmax + orow, mh);
-        if (mz && has_z) atomicMax(zmax + orow, mz);
+      if (tele) {
+        uint32_t n = pk_min16(hf & 0x7FFF7FFFu, 0x00010001u) + pk_min16(hs & 0x7FFF7FFFu, 0x00010001u);
+        if constexpr (SPLIT) {
+          uint32_t all = 0u;
+#pragma unroll
+          for (int j = 0; j < 4; j++) all += pk_min16(m[j], 0x00010001u);
+          n = sel(dense, all, n);
+        }
+        kept += (n & 0xFFFFu) + (n >> 16);
       }
     }
-    kept += min(hp[0] & 0xFFFFu, 1u) + min(hp[0] >> 16, 1u) + min(hp[1] & 0xFFFFu, 1u) + min(hp[1] >> 16, 1u);
+    if (SPLIT) mz = pk_max16(mz, dense & zall);
+    const int t = t0 + 8 * oct;
+#pragma unroll
+    for (int b = 0; b < 2; b++) {
+      if (SPLIT && orow[b] >= n_sparse) {            // dense feature: its 8 tokens as they are (already token-wise pruned)
+        const size_t o = a24_piece(orow[b] - n_sparse, t >> 5, T >> 5) * 32 + (t & 31);
+        u32x4 x, y;
+#pragma unroll
+        for (int d = 0; d < 4; d++) {
+          x[d] = b ? halves_hi(h[2 * d], h[2 * d + 1]) : halves_lo(h[2 * d], h[2 * d + 1]);
+          y[d] = b ? halves_hi(z[2 * d], z[2 * d + 1]) : halves_lo(z[2 * d], z[2 * d + 1]);
+        }
+        *reinterpret_cast<u32x4*>(Hdn_t + o) = x;
+        if (has_z) *reinterpret_cast<u32x4*>(dZdn_t + o) = y;
+        continue;
+      }
+      const size_t piece = PANEL ? a24_piece(orow[b], t >> 6, T >> 6) : (size_t)orow[b] * (T >> 6) + (t >> 6);
+      const size_t vo = piece * 32 + 4 * oct, mo = piece * 8 + oct;
+      st_stream(reinterpret_cast<u32x2*>(Hc_t + vo), u32x2{hp[b][0], hp[b][1]});
+      if (has_z) st_stream(reinterpret_cast<u32x2*>(dZc_t + vo), u32x2{zp[b][0], zp[b][1]});
+      st_stream(meta_t + mo, (uint8_t)(b ? nib >> 16 : nib));
+    }
+  }
+  if (hmax) {
+    // largest stored magnitude word of a feature's row, for a row-wise quantisation that follows (the eight work items of two features
+    // are neighbouring lanes: one atomic per feature, tensor and workgroup)
+#pragma unroll
+    for (int sft = 1; sft < 8; sft <<= 1) {
+      mh = pk_max16(mh, (uint32_t)__shfl_xor((int)mh, sft, 64));
+      mz = pk_max16(mz, (uint32_t)__shfl_xor((int)mz, sft, 64));
+    }
+    if (oct < 2) {                                   // lane 0 of the eight raises the one feature's, lane 1 the other's
+      const uint32_t a = oct ? mh >> 16 : mh & 0xFFFFu, c = oct ? mz >> 16 : mz & 0xFFFFu;
+      const int r = oct ? orow[1] : orow[0];
+      if (a) atomicMax(hmax + r, a);
+      if (c && has_z) atomicMax(zmax + r, c);
+    }
   }
   // what the weight-gradient GEMMs still see of the activation (Sec. 2: the second, feature-wise drop): one atomic
   // per workgroup (tele is a kernel argument, so the barrier is reached by all or none)
@@ -283,6 +319,9 @@ __global__ void __launch_bounds__(256) featurewise24_kernel(const uint16_t* __re
                 (unsigned long long)(s_kept[0] + s_kept[1] + s_kept[2] + s_kept[3]));
   }
 }
+
+// Tiles of 64 tokens a workgroup of the panel form walks (T a multiple of 256): four where that leaves several workgroups a CU.
+static int fw_tiles(int T, int F) { return (long long)(F / FW_FEAT) * (T / (FW_TOK * FW_TILES)) >= 1024 ? FW_TILES : 1; }
 
 // out[0] = elements, out[1 + k] = the sum of the slots of quantity k, out[4] = path: what a telemetry snapshot holds
 __global__ void __launch_bounds__(64) tele_sum_kernel(const unsigned long long* __restrict__ tele, long long elements, long long path,
@@ -399,7 +438,7 @@ __global__ void __launch_bounds__(256, 2) featurewise24_rows_kernel(const uint32
 int launch_featurewise24_rows(const void* Hc, const uint8_t* meta, const void* dZc, int T, int F, void* Hc_t, uint8_t* meta_t, void* dZc_t, hipStream_t s) {
   if (featurewise_small(T, F)) {
     hipLaunchKernelGGL(featurewise24_kernel<false>, dim3(F / FW_FEAT, T / FW_TOK), dim3(256), 0, s, static_cast<const uint16_t*>(Hc), meta,
-                       static_cast<const uint16_t*>(dZc), T, F, static_cast<uint16_t*>(Hc_t), meta_t, static_cast<uint16_t*>(dZc_t),
+                       static_cast<const uint16_t*>(dZc), T, F, 1, static_cast<uint16_t*>(Hc_t), meta_t, static_cast<uint16_t*>(dZc_t),
                        nullptr, 0, nullptr, nullptr, nullptr, nullptr, nullptr);
     return (int)hipGetLastError();
   }
@@ -410,9 +449,10 @@ int launch_featurewise24_rows(const void* Hc, const uint8_t* meta, const void* d
 
 int launch_featurewise24(const void* Hc, const uint8_t* meta, const void* dZc, int T, int F,
                          void* Hc_t, uint8_t* meta_t, void* dZc_t, unsigned long long* tele, hipStream_t s) {
-  dim3 grid(F / FW_FEAT, T / FW_TOK);
+  const int tiles = fw_tiles(T, F);
+  dim3 grid(F / FW_FEAT, T / (FW_TOK * tiles));
   hipLaunchKernelGGL(featurewise24_kernel<true>, grid, dim3(256), 0, s, static_cast<const uint16_t*>(Hc), meta,
-                     static_cast<const uint16_t*>(dZc), T, F, static_cast<uint16_t*>(Hc_t), meta_t, static_cast<uint16_t*>(dZc_t),
+                     static_cast<const uint16_t*>(dZc), T, F, tiles, static_cast<uint16_t*>(Hc_t), meta_t, static_cast<uint16_t*>(dZc_t),
                      nullptr, 0, nullptr, nullptr, tele, nullptr, nullptr);
   return (int)hipGetLastError();
 }
@@ -420,9 +460,10 @@ int launch_featurewise24(const void* Hc, const uint8_t* meta, const void* dZc, i
 // the same (panel form) with the largest stored magnitude word of every output row: hmax, zmax [F], zeroed by the caller
 int launch_featurewise24_rowmax(const void* Hc, const uint8_t* meta, const void* dZc, int T, int F, void* Hc_t, uint8_t* meta_t, void* dZc_t,
                                 uint32_t* hmax, uint32_t* zmax, hipStream_t s) {
-  dim3 grid(F / FW_FEAT, T / FW_TOK);
+  const int tiles = fw_tiles(T, F);
+  dim3 grid(F / FW_FEAT, T / (FW_TOK * tiles));
   hipLaunchKernelGGL(featurewise24_kernel<true>, grid, dim3(256), 0, s, static_cast<const uint16_t*>(Hc), meta,
-                     static_cast<const uint16_t*>(dZc), T, F, static_cast<uint16_t*>(Hc_t), meta_t, static_cast<uint16_t*>(dZc_t),
+                     static_cast<const uint16_t*>(dZc), T, F, tiles, static_cast<uint16_t*>(Hc_t), meta_t, static_cast<uint16_t*>(dZc_t),
                      nullptr, 0, nullptr, nullptr, nullptr, hmax, zmax);
   return (int)hipGetLastError();
 }
@@ -430,9 +471,10 @@ int launch_featurewise24_rowmax(const void* Hc, const uint8_t* meta, const void*
 int launch_featurewise24_split(const void* Hc, const uint8_t* meta, const void* dZc, int T, int F, const int* row_of_feat, int n_sparse,
                                void* Hc_t, uint8_t* meta_t, void* dZc_t, void* Hdn_t, void* dZdn_t, unsigned long long* tele,
                                uint32_t* hmax, uint32_t* zmax, hipStream_t s) {
-  dim3 grid(F / FW_FEAT, T / FW_TOK);
+  const int tiles = fw_tiles(T, F);
+  dim3 grid(F / FW_FEAT, T / (FW_TOK * tiles));
   hipLaunchKernelGGL((featurewise24_kernel<true, true>), grid, dim3(256), 0, s, static_cast<const uint16_t*>(Hc), meta,
-                     static_cast<const uint16_t*>(dZc), T, F, static_cast<uint16_t*>(Hc_t), meta_t, static_cast<uint16_t*>(dZc_t),
+                     static_cast<const uint16_t*>(dZc), T, F, tiles, static_cast<uint16_t*>(Hc_t), meta_t, static_cast<uint16_t*>(dZc_t),
                      row_of_feat, n_sparse, static_cast<uint16_t*>(Hdn_t), static_cast<uint16_t*>(dZdn_t), tele, hmax, zmax);
   return (int)hipGetLastError();
 }

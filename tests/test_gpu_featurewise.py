@@ -27,3 +27,20 @@ def test_featurewise_rows_tiles(F24, T, Fh, with_dz):
         assert np.array_equal(P.words_of(zt), O.compress_with_meta(np.ascontiguousarray(O.decompress24(zc, m).T), m_ref))
     else:
         assert zt is None
+
+
+@pytest.mark.parametrize("T,Fh", [(256, 512), (1280, 3072), (4096, 4096), (8192, 2304)])   # one and four tiles of tokens a workgroup
+def test_featurewise_of_a_context_equals_the_row_major_one(F24, T, Fh):
+    """The context's own re-compression (panel form) against the public one, which the oracle checks above, on the tensors it started from."""
+    print(f"featurewise context T={T} F={Fh}", flush=True)
+    D = 256
+    g = torch.Generator(device="cuda").manual_seed(T + Fh)
+    new = lambda *s: torch.randn(s, device="cuda", generator=g).to(torch.bfloat16)
+    ctx = F24.Context(T, D, Fh, F24.FFN24_TRAINING | F24.FFN24_TELEMETRY)
+    ctx.ffn24_fwd(new(T, D), new(D, Fh), torch.full((Fh,), -16.0, device="cuda"), new(Fh, D))
+    ctx.ffn24_bwd(new(T, D))
+    hv, mt, zt = F24.sparsify24_featurewise(ctx.saved("Hc"), ctx.saved("meta"), ctx.saved("dZc"))
+    torch.cuda.synchronize()
+    assert torch.equal(ctx.saved("meta_t"), mt)
+    assert torch.equal(ctx.saved("Hc_t").view(torch.int16), hv.view(torch.int16)) and torch.equal(ctx.saved("dZc_t").view(torch.int16), zt.view(torch.int16))
+    assert ctx.telemetry()["kept_featurewise"] == int((hv != 0).sum())
