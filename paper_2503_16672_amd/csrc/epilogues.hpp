@@ -83,22 +83,78 @@ template <int MI> __device__ __forceinline__ void st_codes(uint8_t* p, const uin
   }
 }
 
+// A wave's part of a compressed operand in the bf16 panel form (MI = 4: a lane's 64 features of a token are one 64-byte piece, the two
+// lane halves two panels), through LDS.  A store instruction of a lane's own pieces would put 64 16-byte parts into 64 different lines, 16 times
+// over with 4 columns; the wave's tokens are neighbours, so what it owns of a panel is one contiguous run of 2 NI KiB.  The pieces go to
+// a wave-private image in the operand ring (free by then) and leave, or come in, as whole kilobytes: LDS rows are 256 bytes = 4 tokens, and
+// 16-byte place s of row r holds the run's s ^ (r & 15), so that the lanes of an LDS instruction meet in no bank either way.
+// 256 x 128 tiles, D 2048: row-wise fp8 dH at T = F = 8192 129 -> 120 us, its up-projection 124 -> 119; bf16 at T 4096 F 8192 dH 120 -> 115.5, up-projection
+// 119.5 -> 117.  256 x 256, T = F = 8192: bf16 dH 227.5 -> 225.7, row-wise fp8 140 -> 133, the up-projections within 1 %.
+template <int NI>
+struct PanelStage {
+  static constexpr int HALF = 32 * NI * 64;          // a panel's run: bytes of 32 NI tokens
+  static __device__ __forceinline__ char* at(char* wbuf, int tok, int c) {   // 16-byte part c of token tok of the lane's panel
+    const int r = tok >> 2;
+    return wbuf + ((threadIdx.x & 32) ? HALF : 0) + r * 256 + ((((tok & 3) * 4 + c) ^ (r & 15)) << 4);
+  }
+  // the wave's first piece of the lower panel, and the bytes from there to the other panel's
+  static __device__ __forceinline__ size_t first(int m_lane, int n_lane, int F) {
+    const int lane = threadIdx.x & 63;
+    return a24_piece(n_lane - NI * (lane & 31), (m_lane >> 6) - (lane >> 5), F >> 6) * 64;
+  }
+  static constexpr size_t PANEL = 256 * 64;
+  static __device__ __forceinline__ void flush(const char* wbuf, char* out) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int j = 0; j < 4 * NI; j++) {
+      const int q = j % (2 * NI), r = 4 * q + (lane >> 4);
+      *reinterpret_cast<u32x4*>(out + (j / (2 * NI)) * PANEL + q * 1024 + 16 * lane) =
+          *reinterpret_cast<const u32x4*>(wbuf + (j / (2 * NI)) * HALF + r * 256 + (((lane & 15) ^ (r & 15)) << 4));
+    }
+  }
+  // by DMA: the caller waits for vmcnt(0) before the first `at`
+  static __device__ __forceinline__ void fetch(char* wbuf, const char* in) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int j = 0; j < 4 * NI; j++) {
+      const int q = j % (2 * NI), r = 4 * q + (lane >> 4);
+      __builtin_amdgcn_global_load_lds((glb_char*)(in + (j / (2 * NI)) * PANEL + r * 256 + (((lane & 15) ^ (r & 15)) << 4)), (lds_char*)(wbuf + j * 1024), 16, 0, 0);
+    }
+  }
+};
+
 // What the backward epilogues read back of the forward's saved activation, for the lane's tokens x features, requested in one
 // go before any arithmetic or store: a load placed inside the loops is followed by stores through pointers the compiler must assume
 // may alias, so each one waited out a full memory round trip by itself (16 of them in the 2:4 epilogue, 32 in the dense one -- the
 // latter had made the dense dH kernel 0.4 ms slower than the GEMM alone).
 // 2:4: one 64-byte piece (or part) of kept values + its metadata bytes per token (bf16 panel form).
+// MI = 4: the kept values come through LDS (PanelStage) and are read from there token by token, `wbuf` staying the place a result of the same
+// form may be put to piece by piece.
 template <int MI, int NI>
 struct LaneSaved24 {
-  u32x4 h[NI][MI];   // [ni][mi]: the kept values of groups 4 mi .. 4 mi + 3
+  u32x4 h[MI == 4 ? 1 : NI][MI];   // [ni][mi]: the kept values of groups 4 mi .. 4 mi + 3
   u32x2 mt[NI];
-  __device__ __forceinline__ void load(const __bf16* Hc, const uint8_t* meta, int F, int m_lane, int n_lane) {
+  char* wbuf;
+  __device__ __forceinline__ u32x4 kept(int ni, int mi) const {
+    if constexpr (MI == 4) return *reinterpret_cast<const u32x4*>(PanelStage<NI>::at(wbuf, NI * (threadIdx.x & 31) + ni, mi));
+    else return h[ni][mi];
+  }
+  __device__ __forceinline__ void load(const __bf16* Hc, const uint8_t* meta, int F, int m_lane, int n_lane, char* buf) {
+    wbuf = buf;
+    if constexpr (MI == 4) {
+      PanelStage<NI>::fetch(wbuf, reinterpret_cast<const char*>(Hc) + PanelStage<NI>::first(m_lane, n_lane, F));
+#pragma unroll
+      for (int ni = 0; ni < NI; ni++) mt[ni] = ld_nibbles<MI>(meta + a24_piece(n_lane + ni, m_lane >> 6, F >> 6) * 8);
+      wait_vmcnt<0>();
+      asm volatile("" ::: "memory");                 // (the compiler does not see the DMA write what `kept` reads)
+      return;
+    }
 #pragma unroll
     for (int ni = 0; ni < NI; ni++) {
       size_t piece = a24_piece(n_lane + ni, m_lane >> 6, F >> 6);
       mt[ni] = ld_nibbles<MI>(meta + piece * 8 + ((m_lane & 63) >> 3));
 #pragma unroll
-      for (int mi = 0; mi < MI; mi++) h[ni][mi] = *reinterpret_cast<const u32x4*>(Hc + piece * 32 + ((m_lane & 63) >> 1) + 8 * mi);
+      for (int mi = 0; mi < MI; mi++) h[MI == 4 ? 0 : ni][mi] = *reinterpret_cast<const u32x4*>(Hc + piece * 32 + ((m_lane & 63) >> 1) + 8 * mi);
     }
   }
 };
@@ -350,9 +406,10 @@ __device__ __forceinline__ void nnz_flush(uint32_t (&cnt)[4 * MI], uint32_t* nnz
 //   (Sec. 2, first paragraph: the share of non-zeros that 2:4 drops), one pair of atomics per wave.
 template <bool STATS>
 struct EpiPrune24T {
+  static constexpr bool STAGED = true;
   struct Args { __bf16* Hc; uint8_t* meta; __bf16* Hdbg; const float* b1; int F; uint32_t* nnz; unsigned long long* tele; };
   template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane, char* wbuf) {
     constexpr int TOK = TwoTokens<NI>::TOK;
     NnzCount<MI, NI> nz;
     uint32_t kept = 0u;   // non-zero values among the lane's stored ones, first and second of a pair apart (16-bit fields)
@@ -371,7 +428,8 @@ struct EpiPrune24T {
         tt.pick(h);
 #pragma unroll
         for (int t = 0; t < TOK; t++) {
-          *reinterpret_cast<u32x4*>(e.Hc + a24_piece(n_lane + ni + t, m_lane >> 6, e.F >> 6) * 32 + ((m_lane & 63) >> 1) + 8 * mi) = tt.vals[t];
+          if constexpr (MI == 4) *reinterpret_cast<u32x4*>(PanelStage<NI>::at(wbuf, NI * (threadIdx.x & 31) + ni + t, mi)) = tt.vals[t];
+          else *reinterpret_cast<u32x4*>(e.Hc + a24_piece(n_lane + ni + t, m_lane >> 6, e.F >> 6) * 32 + ((m_lane & 63) >> 1) + 8 * mi) = tt.vals[t];
           nib[t][mi >> 1] |= tt.nib[t] << (16 * (mi & 1));
           if constexpr (STATS) {
 #pragma unroll
@@ -382,6 +440,7 @@ struct EpiPrune24T {
 #pragma unroll
       for (int t = 0; t < TOK; t++) st_nibbles<MI>(e.meta + a24_piece(n_lane + ni + t, m_lane >> 6, e.F >> 6) * 8 + ((m_lane & 63) >> 3), nib[t]);
     }
+    if constexpr (MI == 4) PanelStage<NI>::flush(wbuf, reinterpret_cast<char*>(e.Hc) + PanelStage<NI>::first(m_lane, n_lane, e.F));
     if constexpr (STATS) {
       uint32_t cnt[4 * MI];
       nz.fold(cnt);
@@ -466,11 +525,12 @@ struct EpiDRelu {
 // the forward kept, dZ = dH * 2 sqrt(h); elsewhere dZ = 0 and nothing is stored.  Output is compressed with
 // the forward's metadata: dZc [T][F/2].  Hc, meta and dZc are in panel form: one piece per lane and token.
 struct EpiDGather {
+  static constexpr bool STAGED = true;
   struct Args { const __bf16* Hc; const uint8_t* meta; __bf16* dZc; int F; };
   template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane, char* wbuf) {
     LaneSaved24<MI, NI> sv;
-    sv.load(e.Hc, e.meta, e.F, m_lane, n_lane);
+    sv.load(e.Hc, e.meta, e.F, m_lane, n_lane, wbuf);
 #pragma unroll
     for (int ni = 0; ni < NI; ni++) {
       size_t t = (size_t)(n_lane + ni);
@@ -479,7 +539,7 @@ struct EpiDGather {
       __bf16* zrow = e.dZc + piece * 32 + ((m_lane & 63) >> 1);
 #pragma unroll
       for (int mi = 0; mi < MI; mi++) {
-        const u32x4 h = sv.h[ni][mi];
+        const u32x4 h = sv.kept(ni, mi);
         u32x4 z;
 #pragma unroll
         for (int a = 0; a < 4; a++) {
@@ -493,9 +553,11 @@ struct EpiDGather {
           float g1 = 2.f * __builtin_amdgcn_sqrtf(bf16_hi_to_f32(h[a]));
           z[a] = pack_bf16x2(s0 * g0, s1 * g1);
         }
-        *reinterpret_cast<u32x4*>(zrow + 8 * mi) = z;
+        if constexpr (MI == 4) *reinterpret_cast<u32x4*>(PanelStage<NI>::at(wbuf, NI * (threadIdx.x & 31) + ni, mi)) = z;
+        else *reinterpret_cast<u32x4*>(zrow + 8 * mi) = z;
       }
     }
+    if constexpr (MI == 4) PanelStage<NI>::flush(wbuf, reinterpret_cast<char*>(e.dZc) + PanelStage<NI>::first(m_lane, n_lane, e.F));
   }
 };
 
@@ -591,12 +653,13 @@ struct EpiPrune24F8 {
 // form); the result is quantised, e4m3(dZ / sdz) (saturating), and stored compressed with the forward's metadata in
 // the fp8 panel form (the operand of the sparse dX GEMM).
 struct EpiDGatherF8 {
+  static constexpr bool STAGED = true;
   static constexpr EpiCost COST = EPI_FP8;
   struct Args { const __bf16* Hc16; const uint8_t* meta16; uint8_t* dZc8; int F; float scale; float sdz; };
   template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane, char* wbuf) {
     LaneSaved24<MI, NI> sv;
-    sv.load(e.Hc16, e.meta16, e.F, m_lane, n_lane);
+    sv.load(e.Hc16, e.meta16, e.F, m_lane, n_lane, wbuf);
     const ExactDiv by_sdz(e.sdz);
 #pragma unroll
     for (int ni = 0; ni < NI; ni++) {
@@ -605,7 +668,7 @@ struct EpiDGatherF8 {
       uint32_t q8[2 * MI];
 #pragma unroll
       for (int mi = 0; mi < MI; mi++) {
-        const u32x4 h = sv.h[ni][mi];
+        const u32x4 h = sv.kept(ni, mi);
 #pragma unroll
         for (int a = 0; a < 4; a++) {
           int gi = 4 * mi + a;
@@ -679,9 +742,10 @@ struct RowMax {
 template <bool STATS>
 struct EpiPrune24RwT {
   static constexpr EpiCost COST = EPI_FP8;
+  static constexpr bool STAGED = true;
   struct Args { __bf16* Hc; uint8_t* meta; __bf16* Hdbg; const float* b1; int F; const float* sx; const float* sw1; uint32_t* rowmax; uint32_t* nnz; };
   template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane, char* wbuf) {
     constexpr int TOK = TwoTokens<NI>::TOK;
     NnzCount<MI, NI> nz;
     RowMax<NI> rm;
@@ -713,12 +777,14 @@ struct EpiPrune24RwT {
         tt.pick(h);
 #pragma unroll
         for (int t = 0; t < TOK; t++) {
-          *reinterpret_cast<u32x4*>(e.Hc + a24_piece(n_lane + ni + t, m_lane >> 6, e.F >> 6) * 32 + ((m_lane & 63) >> 1) + 8 * mi) = tt.vals[t];
+          if constexpr (MI == 4) *reinterpret_cast<u32x4*>(PanelStage<NI>::at(wbuf, NI * (threadIdx.x & 31) + ni + t, mi)) = tt.vals[t];
+          else *reinterpret_cast<u32x4*>(e.Hc + a24_piece(n_lane + ni + t, m_lane >> 6, e.F >> 6) * 32 + ((m_lane & 63) >> 1) + 8 * mi) = tt.vals[t];
           nib[ni + t][mi >> 1] |= tt.nib[t] << (16 * (mi & 1));
         }
       }
       FFN24_FENCE();
     }
+    if constexpr (MI == 4) PanelStage<NI>::flush(wbuf, reinterpret_cast<char*>(e.Hc) + PanelStage<NI>::first(m_lane, n_lane, e.F));
 #pragma unroll
     for (int ni = 0; ni < NI; ni++) {
       st_nibbles<MI>(e.meta + a24_piece(n_lane + ni, m_lane >> 6, e.F >> 6) * 8 + ((m_lane & 63) >> 3), nib[ni]);
@@ -934,16 +1000,17 @@ struct EpiColMajorRowCol {
 // -- so it is written as bf16, compressed with the forward's metadata (dZc16, bf16 panel form), and rowmax[t] is
 // raised to the largest magnitude word of the row (RowMax); a streaming kernel then quantises with rowmax[t] / 448.
 struct EpiDGatherRw {
+  static constexpr bool STAGED = true;
   static constexpr EpiCost COST = EPI_FP8;
   struct Args { const __bf16* Hc16; const uint8_t* meta16; __bf16* dZc16; int F; const float* rs; const float* cs; uint32_t* rowmax; };
   template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane, char* wbuf) {
     RowMax<NI> rm;
     rm.load(e.rowmax, n_lane);
     LaneVec<MI> lr;
     lr.load(e.rs, m_lane, 1.f);
     LaneSaved24<MI, NI> sv;
-    sv.load(e.Hc16, e.meta16, e.F, m_lane, n_lane);
+    sv.load(e.Hc16, e.meta16, e.F, m_lane, n_lane, wbuf);
     float csv[NI];
 #pragma unroll
     for (int ni = 0; ni < NI; ni++) csv[ni] = e.cs[n_lane + ni];
@@ -957,7 +1024,7 @@ struct EpiDGatherRw {
       uint32_t mx = 0u;
 #pragma unroll
       for (int mi = 0; mi < MI; mi++) {
-        const u32x4 h = sv.h[ni][mi];
+        const u32x4 h = sv.kept(ni, mi);
         u32x4 z;
 #pragma unroll
         for (int a = 0; a < 4; a++) {
@@ -973,10 +1040,12 @@ struct EpiDGatherRw {
           z[a] = pack_bf16x2(s0 * g0, s1 * g1);
           mx = max(mx, max(z[a] & 0x7FFFu, (z[a] >> 16) & 0x7FFFu));
         }
-        *reinterpret_cast<u32x4*>(zrow + 8 * mi) = z;
+        if constexpr (MI == 4) *reinterpret_cast<u32x4*>(PanelStage<NI>::at(wbuf, NI * (threadIdx.x & 31) + ni, mi)) = z;
+        else *reinterpret_cast<u32x4*>(zrow + 8 * mi) = z;
       }
       rm.raise(e.rowmax, n_lane, ni, mx);
     }
+    if constexpr (MI == 4) PanelStage<NI>::flush(wbuf, reinterpret_cast<char*>(e.dZc16) + PanelStage<NI>::first(m_lane, n_lane, e.F));
   }
 };
 
