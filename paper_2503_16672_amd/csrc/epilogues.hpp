@@ -83,40 +83,42 @@ template <int MI> __device__ __forceinline__ void st_codes(uint8_t* p, const uin
   }
 }
 
-// A wave's part of a compressed operand in the bf16 panel form (MI = 4: a lane's 64 features of a token are one 64-byte piece, the two
-// lane halves two panels), through LDS.  A store instruction of a lane's own pieces would put 64 16-byte parts into 64 different lines, 16 times
+// A wave's part of an operand in a bf16 panel form (MI = 4: a lane's 64 features of a token are one 64-byte piece, or two of a dense operand, the
+// two lane halves two panels, or four), through LDS.  A store instruction of a lane's own pieces would put 64 16-byte parts into 64 different lines, 16 times
 // over with 4 columns; the wave's tokens are neighbours, so what it owns of a panel is one contiguous run of 2 NI KiB.  The pieces go to
 // a wave-private image in the operand ring (free by then) and leave, or come in, as whole kilobytes: LDS rows are 256 bytes = 4 tokens, and
 // 16-byte place s of row r holds the run's s ^ (r & 15), so that the lanes of an LDS instruction meet in no bank either way.
 // 256 x 128 tiles, D 2048: row-wise fp8 dH at T = F = 8192 129 -> 120 us, its up-projection 124 -> 119; bf16 at T 4096 F 8192 dH 120 -> 115.5, up-projection
 // 119.5 -> 117.  256 x 256, T = F = 8192: bf16 dH 227.5 -> 225.7, row-wise fp8 140 -> 133, the up-projections within 1 %.
-template <int NI>
+// Dense form: a bf16 dense step at T 4096 D 2048 F 8192 762 -> 751 us (up-projection and dH 157 -> 142 each in a kernel trace).
+// P: panels of a lane half (1: the 2:4 form, 64 features of 32 kept values each; 2: the dense form, 32 features each).
+template <int NI, int P = 1>
 struct PanelStage {
-  static constexpr int HALF = 32 * NI * 64;          // a panel's run: bytes of 32 NI tokens
-  static __device__ __forceinline__ char* at(char* wbuf, int tok, int c) {   // 16-byte part c of token tok of the lane's panel
+  static constexpr int RUN = 32 * NI * 64;           // a panel's run: bytes of 32 NI tokens
+  static constexpr size_t PANEL = 256 * 64;          // from one panel's pieces to the next one's in memory
+  static __device__ __forceinline__ char* at(char* wbuf, int tok, int c, int panel = 0) {   // 16-byte part c of token tok of the lane's panel
     const int r = tok >> 2;
-    return wbuf + ((threadIdx.x & 32) ? HALF : 0) + r * 256 + ((((tok & 3) * 4 + c) ^ (r & 15)) << 4);
+    return wbuf + (((threadIdx.x & 32) ? P : 0) + panel) * RUN + r * 256 + ((((tok & 3) * 4 + c) ^ (r & 15)) << 4);
   }
-  // the wave's first piece of the lower panel, and the bytes from there to the other panel's
+  // the wave's first piece of its lowest panel
   static __device__ __forceinline__ size_t first(int m_lane, int n_lane, int F) {
     const int lane = threadIdx.x & 63;
-    return a24_piece(n_lane - NI * (lane & 31), (m_lane >> 6) - (lane >> 5), F >> 6) * 64;
+    return a24_piece(n_lane - NI * (lane & 31), ((m_lane >> 6) - (lane >> 5)) * P, F / (64 / P)) * 64;
   }
-  static constexpr size_t PANEL = 256 * 64;
   static __device__ __forceinline__ void flush(const char* wbuf, char* out) {
     const int lane = threadIdx.x & 63;
 #pragma unroll
-    for (int j = 0; j < 4 * NI; j++) {
+    for (int j = 0; j < 4 * P * NI; j++) {
       const int q = j % (2 * NI), r = 4 * q + (lane >> 4);
       *reinterpret_cast<u32x4*>(out + (j / (2 * NI)) * PANEL + q * 1024 + 16 * lane) =
-          *reinterpret_cast<const u32x4*>(wbuf + (j / (2 * NI)) * HALF + r * 256 + (((lane & 15) ^ (r & 15)) << 4));
+          *reinterpret_cast<const u32x4*>(wbuf + (j / (2 * NI)) * RUN + r * 256 + (((lane & 15) ^ (r & 15)) << 4));
     }
   }
   // by DMA: the caller waits for vmcnt(0) before the first `at`
   static __device__ __forceinline__ void fetch(char* wbuf, const char* in) {
     const int lane = threadIdx.x & 63;
 #pragma unroll
-    for (int j = 0; j < 4 * NI; j++) {
+    for (int j = 0; j < 4 * P * NI; j++) {
       const int q = j % (2 * NI), r = 4 * q + (lane >> 4);
       __builtin_amdgcn_global_load_lds((glb_char*)(in + (j / (2 * NI)) * PANEL + r * 256 + (((lane & 15) ^ (r & 15)) << 4)), (lds_char*)(wbuf + j * 1024), 16, 0, 0);
     }
@@ -247,9 +249,10 @@ struct EpiColMajor {
 // dense path reports while 2:4 is still switched off (Sec. 2, last paragraph: the dense warm-up).
 template <bool STATS>
 struct EpiRelu2T {
+  static constexpr bool STAGED = true;
   struct Args { __bf16* H; __bf16* Ht; const float* b1; int F; int T; unsigned long long* tele; };
   template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane, char* wbuf) {
     uint32_t nonzero = 0u;   // of this lane's 256 activations
     LaneVec<MI> lb;
     lb.load(e.b1, m_lane, 0.f);
@@ -272,7 +275,8 @@ struct EpiRelu2T {
             o[d] = pack_bf16x2(acc[mi][ni][8 * q + 2 * d], acc[mi][ni][8 * q + 2 * d + 1]);
             if constexpr (STATS) nonzero += min(o[d] & 0xFFFFu, 1u) + min(o[d] >> 16, 1u);
           }
-          *reinterpret_cast<u32x4*>(row + 8 * q) = o;
+          if constexpr (MI == 4) *reinterpret_cast<u32x4*>(PanelStage<NI, 2>::at(wbuf, NI * (threadIdx.x & 31) + ni, 2 * (mi & 1) + q, mi >> 1)) = o;
+          else *reinterpret_cast<u32x4*>(row + 8 * q) = o;
         }
       }
       if (e.Ht) {
@@ -285,6 +289,7 @@ struct EpiRelu2T {
         }
       }
     }
+    if constexpr (MI == 4) PanelStage<NI, 2>::flush(wbuf, reinterpret_cast<char*>(e.H) + PanelStage<NI, 2>::first(m_lane, n_lane, e.F));
     if constexpr (STATS) {
       if (e.tele) tele_add2(e.tele, nonzero, TELE_NONZERO, -1, blockIdx.x + (threadIdx.x >> 6));
     }
@@ -482,11 +487,17 @@ struct EpiRowMajorMapped {
 // Stored as a [T][F] operand and, for the weight-gradient GEMM that reduces over tokens, also as an [F][T] operand;
 // H, dZ and dZt are all in dense panel form.
 struct EpiDRelu {
+  static constexpr bool STAGED = true;
   struct Args { const __bf16* H; __bf16* dZ; __bf16* dZt; int F; int T; };
   template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
-    LaneSavedDense<MI, NI> sv;
-    sv.load(e.H, e.F, m_lane, n_lane);
+  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane, char* wbuf) {
+    LaneSavedDense<MI == 4 ? 1 : MI, NI> sv;         // (MI = 4: through LDS, like the result)
+    const size_t run = MI == 4 ? PanelStage<NI, 2>::first(m_lane, n_lane, e.F) : 0;
+    if constexpr (MI == 4) {
+      PanelStage<NI, 2>::fetch(wbuf, reinterpret_cast<const char*>(e.H) + run);
+      wait_vmcnt<0>();
+      asm volatile("" ::: "memory");                 // (the compiler does not see the DMA write what is read below)
+    } else sv.load(e.H, e.F, m_lane, n_lane);
 #pragma unroll
     for (int mi = 0; mi < MI; mi++) {
 #pragma unroll
@@ -495,7 +506,12 @@ struct EpiDRelu {
         size_t o = a24_piece(n_lane + ni, f >> 5, e.F >> 5) * 32 + (f & 31);
 #pragma unroll
         for (int q = 0; q < 2; q++) {
-          const u32x4 h = sv.h[mi][ni][q];
+          char* place = nullptr;
+          u32x4 h;
+          if constexpr (MI == 4) {
+            place = PanelStage<NI, 2>::at(wbuf, NI * (threadIdx.x & 31) + ni, 2 * (mi & 1) + q, mi >> 1);
+            h = *reinterpret_cast<const u32x4*>(place);
+          } else h = sv.h[mi][ni][q];
           u32x4 r;
 #pragma unroll
           for (int d = 0; d < 4; d++) {
@@ -505,7 +521,8 @@ struct EpiDRelu {
             acc[mi][ni][8 * q + 2 * d + 1] *= g1;
             r[d] = pack_bf16x2(acc[mi][ni][8 * q + 2 * d], acc[mi][ni][8 * q + 2 * d + 1]);
           }
-          *reinterpret_cast<u32x4*>(e.dZ + o + 8 * q) = r;
+          if constexpr (MI == 4) *reinterpret_cast<u32x4*>(place) = r;
+          else *reinterpret_cast<u32x4*>(e.dZ + o + 8 * q) = r;
         }
       }
       if (e.dZt) {
@@ -518,6 +535,7 @@ struct EpiDRelu {
         }
       }
     }
+    if constexpr (MI == 4) PanelStage<NI, 2>::flush(wbuf, reinterpret_cast<char*>(e.dZ) + run);
   }
 };
 
