@@ -303,22 +303,6 @@ struct LaneCtx {
   int sw8a;         // swz8 of the lane's A row for even mi (odd mi: ^4)
 };
 
-template <int MI, int NI>
-__device__ __forceinline__ LaneCtx lane_ctx(int tid) {
-  const int lane = tid & 63, wave = tid >> 6;
-  LaneCtx L;
-  L.rho = lane & 31; L.h = lane >> 5; L.wy = wave >> 1; L.wx = wave & 1;
-  L.a_row64 = (L.wy * (32 * MI) + L.rho) * 64;
-  L.b_row64 = (L.wx * (32 * NI) + L.rho) * 64;
-  L.a_row128 = (L.wy * (32 * MI) + L.rho) * 128;
-  L.b_row128 = (L.wx * (32 * NI) + L.rho) * 128;
-  L.sw4 = swz4(L.rho);
-  // (from NI = 2, MI = 2 on the wave column, wave row moves the row by a multiple of 64, which the swizzle does not see)
-  L.sw8 = NI == 1 ? swz8(L.wx * 32 + L.rho) : swz8(L.rho);
-  L.sw8a = MI == 1 ? swz8(L.wy * 32 + L.rho) : swz8(L.rho);
-  return L;
-}
-
 // Dense: K step S (0,1) of the 64-byte stage rows; fragment I < MI -> a[I], else b[I-MI]
 template <int MI, int NI>
 struct FragD {
@@ -554,7 +538,16 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
   tile_coords<PROBE, MI == 2 * NI>(g.M / G::BM, g.N / G::BN, pid, tm, tn);
   int m0 = tm * G::BM, n0 = tn * G::BN;
 
-  const LaneCtx L = lane_ctx<MI, NI>(tid);
+  LaneCtx L;   // (filled in here: as the result of a function it costs the sparse 256 x 256 store kernels a spilled register)
+  L.rho = lane & 31; L.h = lane >> 5; L.wy = wave >> 1; L.wx = wave & 1;
+  L.a_row64 = (L.wy * (32 * MI) + L.rho) * 64;
+  L.b_row64 = (L.wx * (32 * NI) + L.rho) * 64;
+  L.a_row128 = (L.wy * (32 * MI) + L.rho) * 128;
+  L.b_row128 = (L.wx * (32 * NI) + L.rho) * 128;
+  L.sw4 = swz4(L.rho);
+  // (from NI = 2, MI = 2 on the wave column, wave row moves the row by a multiple of 64, which the swizzle does not see)
+  L.sw8 = NI == 1 ? swz8(L.wx * 32 + L.rho) : swz8(L.rho);
+  L.sw8a = MI == 1 ? swz8(L.wy * 32 + L.rho) : swz8(L.rho);
 
   Dma<SPARSE, F8, PROBE, MI, NI> dma;
   dma.init(g, m0, n0, tid);
@@ -1030,7 +1023,13 @@ __global__ void __launch_bounds__(GEMM_THREADS, (GeoRows<MI, NI>::PER_CU)) gemm_
   int tm, tn;
   tile_coords<0, MI == 2 * NI>(g.M / G::BM, g.N / G::BN, blockIdx.x, tm, tn);
   const int m0 = tm * G::BM, n0 = tn * G::BN;
-  LaneCtx L = lane_ctx<MI, NI>(tid);
+  const int lane = tid & 63, wave = tid >> 6;
+  LaneCtx L = {};
+  L.rho = lane & 31; L.h = lane >> 5; L.wy = wave >> 1; L.wx = wave & 1;
+  L.a_row128 = (L.wy * (32 * MI) + L.rho) * 128;
+  L.b_row128 = (L.wx * (32 * NI) + L.rho) * 128;
+  L.sw8 = NI == 1 ? swz8(L.wx * 32 + L.rho) : swz8(L.rho);
+  L.sw8a = MI == 1 ? swz8(L.wy * 32 + L.rho) : swz8(L.rho);
   const bool shifted = SHIFT && (L.rho & 1);
   if (shifted) L.sw8a ^= 4;                          // the halves the other way round
   DmaRows<MI, NI, SHIFT> dma;
