@@ -83,6 +83,10 @@ template <int MI> __device__ __forceinline__ void st_codes(uint8_t* p, const uin
   }
 }
 
+// x is computed here.  What an epilogue collects tile by tile and uses at its end (row maxima, counts, metadata) the compiler would move
+// there, with all the words it is made of kept until then: 200 of them beside the accumulators, 7-9 registers spilled with 256 x 256 tiles.
+__device__ __forceinline__ void keep_here(uint32_t& x) { asm volatile("" : "+v"(x)); }
+
 // A wave's part of an operand in a bf16 panel form (MI = 4: a lane's 64 features of a token are one 64-byte piece, or two of a dense operand, the
 // two lane halves two panels, or four), through LDS.  A store instruction of a lane's own pieces would put 64 16-byte parts into 64 different lines, 16 times
 // over with 4 columns; the wave's tokens are neighbours, so what it owns of a panel is one contiguous run of 2 NI KiB.  The pieces go to
@@ -359,7 +363,10 @@ template <int MI, int NI> struct NnzCount {
   }
   __device__ __forceinline__ void add(int mi, const uint32_t (&h)[ROWS]) {
 #pragma unroll
-    for (int v = 0; v < ROWS; v += 2) c[(mi * ROWS + v) / 2] += pk_min16(h[v], 0x00010001u) + (pk_min16(h[v + 1], 0x00010001u) << 8);
+    for (int v = 0; v < ROWS; v += 2) {
+      c[(mi * ROWS + v) / 2] += pk_min16(h[v], 0x00010001u) + (pk_min16(h[v + 1], 0x00010001u) << 8);
+      keep_here(c[(mi * ROWS + v) / 2]);
+    }
   }
   __device__ __forceinline__ void fold(uint32_t (&cnt)[4 * MI]) const {
 #pragma unroll
@@ -798,7 +805,9 @@ struct EpiPrune24RwT {
           if constexpr (MI == 4) *reinterpret_cast<u32x4*>(PanelStage<NI>::at(wbuf, NI * (threadIdx.x & 31) + ni + t, mi)) = tt.vals[t];
           else *reinterpret_cast<u32x4*>(e.Hc + a24_piece(n_lane + ni + t, m_lane >> 6, e.F >> 6) * 32 + ((m_lane & 63) >> 1) + 8 * mi) = tt.vals[t];
           nib[ni + t][mi >> 1] |= tt.nib[t] << (16 * (mi & 1));
+          keep_here(nib[ni + t][mi >> 1]);
         }
+        keep_here(mx[ni / 2]);
       }
       FFN24_FENCE();
     }
