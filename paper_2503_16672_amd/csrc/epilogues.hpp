@@ -352,7 +352,7 @@ __device__ __forceinline__ void st_debug(__bf16* row, int F, const typename TwoT
 
 // Per-feature non-zero counts of the activation epilogues (Sec. 2, "Optimization 1": the column-level sparsity the first GEMM's
 // epilogue can compute for free).  A lane first counts in 8-bit fields as the words come, one word for 2 v and 2 v + 1 of an
-// M-tile: bytes 0, 1 from the low halves, bytes 2, 3 from the high halves; nnz_fold brings that into 4 features a register, feature f of
+// M-tile: bytes 0, 1 from the low halves, bytes 2, 3 from the high halves; fold brings that into 4 features a register, feature f of
 // the lane in field f % 4 of register f / 4.
 template <int MI, int NI> struct NnzCount {
   static constexpr int ROWS = TwoTokens<NI>::ROWS;

@@ -538,7 +538,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
   tile_coords<PROBE, MI == 2 * NI>(g.M / G::BM, g.N / G::BN, pid, tm, tn);
   int m0 = tm * G::BM, n0 = tn * G::BN;
 
-  LaneCtx L;   // (filled in here: as the result of a function it costs the sparse 256 x 256 store kernels a spilled register)
+  // (written out here and in gemm_rows_kernel: from a function, returned or by reference, it costs the sparse 256 x 256 store kernels 1-4
+  // spilled registers)
+  LaneCtx L;
   L.rho = lane & 31; L.h = lane >> 5; L.wy = wave >> 1; L.wx = wave & 1;
   L.a_row64 = (L.wy * (32 * MI) + L.rho) * 64;
   L.b_row64 = (L.wx * (32 * NI) + L.rho) * 64;
@@ -922,16 +924,16 @@ __global__ void __launch_bounds__(GEMM_THREADS, (Geo<SPARSE, F8, MI, NI>::PER_CU
 // ------------------------------------------------------------------------------------------------
 // the sparse GEMM on a caller's row-major operands (spmm24)
 // ------------------------------------------------------------------------------------------------
-// Row-major, the 64 k of a stage are 64 bytes of an A row, half a line, and 8 bytes of metadata: 256 and 64 requests of the 128 x 64 tile's 320
-// a stage are for pieces of a line, and a CU's global->LDS stream takes about three cycles a request whatever its size (the main loop above
+// Row-major, the 64 k of a stage are 64 bytes of an A row, half a line, and 8 bytes of metadata: 256 of the 128 x 64 tile's 320 requests a stage
+// are for pieces of a line, and a CU's global->LDS stream takes about three cycles a request whatever its size (the main loop above
 // spent 53.2 of its 54.5 us at M 2048 N 1024 K 8256 waiting for it, now 37.6 in all; in panel form the same stream takes 25.7).  So a ring slot here holds
 // 128 k: whole lines of A, 16 bytes of metadata a row, and B as two halves of 64 k in the layout of the loop above.  The halves are
 // walked with two register sets, each read while the other's matrix ops run; one wait and one barrier for both.  K need not be a
 // multiple of 128: lanes that would pass the end of a row fetch its last bytes again, and the last half is not walked.  Every
 // second row of A then starts in the middle of a line.  SHIFT (taken then by the 128 x 64 tile, which has four slots): a slot holds those rows' 128 bytes
 // from 64 before, so that they are whole lines too, their two halves stand the other way round, and the second half
-// of what the others have in slot kt is the first of slot kt + 1 (K 8256, 128 x 64: 39.7 us, 43.9 without, 34.4 with K 8192; with 128 x 128,
-// whose three slots leave no time for it, 65 against 53).
+// of what the others have in slot kt is the first of slot kt + 1 (K 8256, 128 x 64: 39.7 us, 43.9 without, 34.4 with K 8192).  Three slots leave
+// no time for it: 128 x 128 at K 8256 65 us against 53 without, 64 x 64 at M N 512 K 2112 8.3 against 7.7 and at K 8256 42.7 against 25.6.
 template <int MI, int NI>
 struct GeoRows {
   static constexpr int BM = 64 * MI, BN = 64 * NI, BK = 128;
@@ -1034,10 +1036,9 @@ __global__ void __launch_bounds__(GEMM_THREADS, (GeoRows<MI, NI>::PER_CU)) gemm_
   if (shifted) L.sw8a ^= 4;                          // the halves the other way round
   DmaRows<MI, NI, SHIFT> dma;
   dma.init(g, m0, n0, tid);
-  const int nk = (g.K + G::BK - 1) / G::BK;
+  const int nk = (g.K + G::BK - 1) / G::BK;         // at least NB (launch_rows_tile)
   const bool odd = (g.K & 64) != 0;                  // the last slot's second half does not exist
-  const int npro = nk < NB ? nk : NB;
-  for (int s = 0; s < npro; s++) static_for<NDMA>([&](auto J) { dma.template issue<J>(s, smem + s * G::STAGE); });
+  for (int s = 0; s < NB; s++) static_for<NDMA>([&](auto J) { dma.template issue<J>(s, smem + s * G::STAGE); });
   f32x16 acc[MI][NI];
 #pragma unroll
   for (int i = 0; i < MI; i++)
@@ -1045,7 +1046,7 @@ __global__ void __launch_bounds__(GEMM_THREADS, (GeoRows<MI, NI>::PER_CU)) gemm_
     for (int j = 0; j < NI; j++)
 #pragma unroll
       for (int v = 0; v < 16; v++) acc[i][j][v] = 0.f;
-  if (npro == NB) wait_vmcnt<(NB - AHEAD) * NDMA>(); else wait_vmcnt<0>();
+  wait_vmcnt<(NB - AHEAD) * NDMA>();
   __builtin_amdgcn_s_barrier();
   FFN24_FENCE();
   SR r0, r1;
@@ -1085,12 +1086,8 @@ __global__ void __launch_bounds__(GEMM_THREADS, (GeoRows<MI, NI>::PER_CU)) gemm_
     slot = ns;
   };
   int kt = 0;
-  if (nk >= NB) {
-    for (; kt < nk - NB; kt++) advance(kt, Yes{}, std::integral_constant<int, NB - 1 - AHEAD>{});
-    static_for<NB - 1>([&](auto i) { advance(kt + decltype(i)::value, No{}, std::integral_constant<int, NB - 1 - AHEAD - decltype(i)::value>{}); });
-  } else {
-    for (; kt < nk - 1; kt++) advance(kt, No{}, std::integral_constant<int, 0>{});
-  }
+  for (; kt < nk - NB; kt++) advance(kt, Yes{}, std::integral_constant<int, NB - 1 - AHEAD>{});
+  static_for<NB - 1>([&](auto i) { advance(kt + decltype(i)::value, No{}, std::integral_constant<int, NB - 1 - AHEAD - decltype(i)::value>{}); });
   first(smem + slot * G::STAGE, smem + slot * G::STAGE);   // (reads a second half even where there is none: nothing is made of it)
   if (!odd) second(0, smem, smem, No{}, No{});
   Epi::template run<MI, NI>(ea, acc, m0 + L.wy * (32 * MI) + (16 * MI) * L.h, n0 + L.wx * (32 * NI) + NI * L.rho);

@@ -38,6 +38,7 @@ static int launch_gemm(const GemmArgs& g_in, const typename Epi::Args& ea, hipSt
 template <class Epi, int MI, int NI, bool SHIFT>
 static int launch_rows_tile(const GemmArgs& g, const typename Epi::Args& ea, hipStream_t s) {
   using G = GeoRows<MI, NI>;
+  static_assert(ROWS_MIN_K / G::BK >= G::NB, "the kernel fills its ring before it starts");
   auto kern = gemm_rows_kernel<Epi, MI, NI, SHIFT>;
   static std::atomic<bool> configured[MAX_DEVICES] = {};
   if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), G::LDS_TOTAL, configured)) return rc;
@@ -45,7 +46,7 @@ static int launch_rows_tile(const GemmArgs& g, const typename Epi::Args& ea, hip
   return (int)hipGetLastError();
 }
 
-// A 2:4 operand and a dense one as a caller has them, row-major (gemm_rows_kernel), bf16.
+// A 2:4 operand and a dense one as a caller has them, row-major (gemm_rows_kernel), bf16, K >= ROWS_MIN_K.
 template <class Epi>
 static int launch_gemm_rows(const GemmArgs& g, const typename Epi::Args& ea, hipStream_t s) {
   switch (pick_tile(true, false, EPI_PLAIN, g.M, g.N, g.K, 1, true)) {
