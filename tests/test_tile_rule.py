@@ -6,6 +6,8 @@ from pathlib import Path
 
 import pytest
 
+from test_gpu_pick import SHAPES as PICK_SHAPES
+
 RULE = Path(__file__).resolve().parents[1] / "paper_2503_16672_amd" / "csrc" / "tile_rule.hpp"
 MAIN = """
 #include "%s"
@@ -57,13 +59,23 @@ def picks(tmp_path_factory):
     d = tmp_path_factory.mktemp("tile_rule")
     (d / "main.cpp").write_text(MAIN % RULE)
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-o", str(d / "main"), str(d / "main.cpp")], check=True)
-    text = "\n".join(" ".join(str(x) for x in q) for q, _ in MEASURED)
-    return [int(x) for x in subprocess.run([str(d / "main")], input=text, capture_output=True, text=True, check=True).stdout.split()]
+
+    def run(queries):
+        text = "\n".join(" ".join(str(x) for x in q) for q in queries)
+        return [int(x) for x in subprocess.run([str(d / "main")], input=text, capture_output=True, text=True, check=True).stdout.split()]
+    return run
 
 
 @pytest.mark.parametrize("i", range(len(MEASURED)), ids=["-".join(str(x) for x in q) for q, _ in MEASURED])
 def test_tile_of_measured_shapes(picks, i):
-    assert picks[i] in MEASURED[i][1]
+    assert picks([MEASURED[i][0]])[0] in MEASURED[i][1]
+
+
+def test_shapes_of_the_pick_tests_take_every_tile(picks):
+    """The GPU test of the pick runs each block tile, of the bf16 and of the row-wise fp8 up-projection."""
+    for f8, epilogue in ((0, "p"), (1, "f")):
+        assert picks([(0, f8, epilogue, Fh, T, D, 1) for T, D, Fh, _ in PICK_SHAPES]) == [tile for *_, tile in PICK_SHAPES]
+    assert {tile for *_, tile in PICK_SHAPES} == set(range(5))
 
 
 def test_two_full_gemms_take_the_large_tile_alone_too(tmp_path):
