@@ -155,10 +155,10 @@ int launch_sparsify24(const void* H, int64_t rows, int64_t cols, void* vals, uin
 // throughout, f in the low half and f + 8 in the high half, so that the decompression and the pick are packed and bitwise arithmetic on
 // two groups, LDS is accessed by whole dwords (a pitch of 33: a wave's reads, 8 words of 8 token octets, fall into 64 different banks),
 // and a wave's stores cover 8 consecutive features at a time.
-// A workgroup walks `tiles` tiles of 64 tokens, the next one's input on its way while this one is worked on, and raises the row maxima
+// A workgroup walks `tiles` tiles of 64 tokens (fw_tiles), the next one's input on its way while this one is worked on, and raises the row maxima
 // once: with one tile a workgroup two million atomics went out at T = F = 8192.  What bounds it is HBM; feature by feature and tile by tile
-// it took 82.9 us there with the maxima and a split, now 56.6 = 5.0 TB/s; without them, T = F = 16384, 206 -> 192 = 5.9 TB/s; T 1280 F 3072
-// 5.7 -> 4.5.
+// it took 82.9 us there with the maxima and a split, now 52-57 = 5.0 TB/s and more; without them, T = F = 16384, 206 -> 193 = 5.9 TB/s; T 1280
+// F 3072 5.7 -> 4.5.
 constexpr int FW_TOK = 64, FW_FEAT = 64, FW_LDW = FW_FEAT / 2 + 1, FW_TILES = 4;
 
 // all ones in the halves of the mask where bit b of the half is set
@@ -320,8 +320,12 @@ __global__ void __launch_bounds__(256) featurewise24_kernel(const uint16_t* __re
   }
 }
 
-// Tiles of 64 tokens a workgroup of the panel form walks (T a multiple of 256): four where that leaves several workgroups a CU.
-static int fw_tiles(int T, int F) { return (long long)(F / FW_FEAT) * (T / (FW_TOK * FW_TILES)) >= 1024 ? FW_TILES : 1; }
+// Tiles of 64 tokens a workgroup of the panel form walks (T a multiple of 256): four with a split and row maxima, whose atomics go to rows all
+// over the matrix, from a workgroup a CU on; one otherwise.  One, four, in a kernel trace (us), T F with split and maxima: 1024 2048 7.1, 9.7; 1280
+// 3072 9.5, 9.6; 2048 2048 10.6, 10.0; 2816 3840 14.7, 13.5; 4096 4096 20.1, 18.4; 8192 2048 29.0, 19.2; 8192 8192 79.6, 51.8.  Maxima without a
+// split: 2048 2048 6.3, 9.6; 4096 4096 15.9, 16.5; 4096 8192 27.1, 28.6; 8192 8192 62.4, 62.2.  Neither: 2048 4096 6.5, 7.7; 4096 4096 12.9,
+// 13.3; 8192 8192 42.8, 44.4; 16384 16384 193, 197; a split or telemetry alone are the same 2-5 % apart.
+static int fw_tiles(int T, int F, bool split_maxima) { return split_maxima && (F / FW_FEAT) * (T / (FW_TOK * FW_TILES)) >= 256 ? FW_TILES : 1; }
 
 // out[0] = elements, out[1 + k] = the sum of the slots of quantity k, out[4] = path: what a telemetry snapshot holds
 __global__ void __launch_bounds__(64) tele_sum_kernel(const unsigned long long* __restrict__ tele, long long elements, long long path,
@@ -350,8 +354,8 @@ int launch_tele_sum(const unsigned long long* tele, long long elements, long lon
 // row's metadata line serves four neighbouring tiles and should be fetched by one L2.
 // Measured at 8064 x 8256 / 16384 x 16384 (with dZ): 67 us = 4.2 TB/s / 230 us = 5.0 TB/s; tiles dealt round-robin over the XCDs 69 / 259-307
 // us; 64-token tiles 81 / 373 us, 32-token tiles 207 / 1005 us (half and quarter lines out); three workgroups a CU 135 / 538 us (spills).
-// 64 x 64 tiles spread out in LDS (featurewise24_kernel<false>), which read and write half lines and 8-byte metadata pieces, take 160 us =
-// 1.8 TB/s, but fill the chip from eight times fewer elements on: small matrices take them (featurewise_small).
+// 64 x 64 tiles spread out in LDS (featurewise24_kernel<false>), which read and write half lines and 8-byte metadata pieces, take 71 us at 8064 x
+// 4160, where these take 38, but fill the chip from eight times fewer elements on: small matrices take them (featurewise_small).
 constexpr int FWR_CH = 4, FWR_TOK = 32 * FWR_CH;   // chunks of 8 tokens per wave, tokens per workgroup
 __global__ void __launch_bounds__(256, 2) featurewise24_rows_kernel(const uint32_t* __restrict__ Hc, const uint8_t* __restrict__ meta,
                                                                     const uint32_t* __restrict__ dZc, int T, int F, uint8_t* __restrict__ Hc_t,
@@ -449,10 +453,9 @@ int launch_featurewise24_rows(const void* Hc, const uint8_t* meta, const void* d
 
 int launch_featurewise24(const void* Hc, const uint8_t* meta, const void* dZc, int T, int F,
                          void* Hc_t, uint8_t* meta_t, void* dZc_t, unsigned long long* tele, hipStream_t s) {
-  const int tiles = fw_tiles(T, F);
-  dim3 grid(F / FW_FEAT, T / (FW_TOK * tiles));
+  dim3 grid(F / FW_FEAT, T / FW_TOK);
   hipLaunchKernelGGL(featurewise24_kernel<true>, grid, dim3(256), 0, s, static_cast<const uint16_t*>(Hc), meta,
-                     static_cast<const uint16_t*>(dZc), T, F, tiles, static_cast<uint16_t*>(Hc_t), meta_t, static_cast<uint16_t*>(dZc_t),
+                     static_cast<const uint16_t*>(dZc), T, F, 1, static_cast<uint16_t*>(Hc_t), meta_t, static_cast<uint16_t*>(dZc_t),
                      nullptr, 0, nullptr, nullptr, tele, nullptr, nullptr);
   return (int)hipGetLastError();
 }
@@ -460,10 +463,9 @@ int launch_featurewise24(const void* Hc, const uint8_t* meta, const void* dZc, i
 // the same (panel form) with the largest stored magnitude word of every output row: hmax, zmax [F], zeroed by the caller
 int launch_featurewise24_rowmax(const void* Hc, const uint8_t* meta, const void* dZc, int T, int F, void* Hc_t, uint8_t* meta_t, void* dZc_t,
                                 uint32_t* hmax, uint32_t* zmax, hipStream_t s) {
-  const int tiles = fw_tiles(T, F);
-  dim3 grid(F / FW_FEAT, T / (FW_TOK * tiles));
+  dim3 grid(F / FW_FEAT, T / FW_TOK);
   hipLaunchKernelGGL(featurewise24_kernel<true>, grid, dim3(256), 0, s, static_cast<const uint16_t*>(Hc), meta,
-                     static_cast<const uint16_t*>(dZc), T, F, tiles, static_cast<uint16_t*>(Hc_t), meta_t, static_cast<uint16_t*>(dZc_t),
+                     static_cast<const uint16_t*>(dZc), T, F, 1, static_cast<uint16_t*>(Hc_t), meta_t, static_cast<uint16_t*>(dZc_t),
                      nullptr, 0, nullptr, nullptr, nullptr, hmax, zmax);
   return (int)hipGetLastError();
 }
@@ -471,7 +473,7 @@ int launch_featurewise24_rowmax(const void* Hc, const uint8_t* meta, const void*
 int launch_featurewise24_split(const void* Hc, const uint8_t* meta, const void* dZc, int T, int F, const int* row_of_feat, int n_sparse,
                                void* Hc_t, uint8_t* meta_t, void* dZc_t, void* Hdn_t, void* dZdn_t, unsigned long long* tele,
                                uint32_t* hmax, uint32_t* zmax, hipStream_t s) {
-  const int tiles = fw_tiles(T, F);
+  const int tiles = fw_tiles(T, F, hmax != nullptr);
   dim3 grid(F / FW_FEAT, T / (FW_TOK * tiles));
   hipLaunchKernelGGL((featurewise24_kernel<true, true>), grid, dim3(256), 0, s, static_cast<const uint16_t*>(Hc), meta,
                      static_cast<const uint16_t*>(dZc), T, F, tiles, static_cast<uint16_t*>(Hc_t), meta_t, static_cast<uint16_t*>(dZc_t),

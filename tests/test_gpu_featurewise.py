@@ -29,7 +29,7 @@ def test_featurewise_rows_tiles(F24, T, Fh, with_dz):
         assert zt is None
 
 
-@pytest.mark.parametrize("T,Fh", [(256, 512), (1280, 3072), (4096, 4096), (8192, 2304)])   # one and four tiles of tokens a workgroup
+@pytest.mark.parametrize("T,Fh", [(256, 512), (1280, 3072), (4096, 4096), (8192, 2304)])
 def test_featurewise_of_a_context_equals_the_row_major_one(F24, T, Fh):
     """The context's own re-compression (panel form) against the public one, which the oracle checks above, on the tensors it started from."""
     print(f"featurewise context T={T} F={Fh}", flush=True)
@@ -44,3 +44,10 @@ def test_featurewise_of_a_context_equals_the_row_major_one(F24, T, Fh):
     assert torch.equal(ctx.saved("meta_t"), mt)
     assert torch.equal(ctx.saved("Hc_t").view(torch.int16), hv.view(torch.int16)) and torch.equal(ctx.saved("dZc_t").view(torch.int16), zt.view(torch.int16))
     assert ctx.telemetry()["kept_featurewise"] == int((hv != 0).sum())
+
+
+@pytest.mark.parametrize("T,Fh", [(1792, 2048), (2048, 2048), (2304, 3072)])   # one tile of tokens a workgroup; four, from 256 workgroups on
+def test_split_with_row_maxima_around_four_tiles(F24, T, Fh):
+    """Every feature's scale and codes of a row-wise step with a split, bit for bit from the context's own tensors (and its weight gradients)."""
+    print(f"featurewise split T={T} F={Fh}", flush=True)
+    P._fp8_rowwise_split_case(F24, T, 256, Fh, "per_feature", seed=T + Fh, n_dense=512)
