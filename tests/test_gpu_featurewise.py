@@ -51,3 +51,22 @@ def test_split_with_row_maxima_around_four_tiles(F24, T, Fh):
     """Every feature's scale and codes of a row-wise step with a split, bit for bit from the context's own tensors (and its weight gradients)."""
     print(f"featurewise split T={T} F={Fh}", flush=True)
     P._fp8_rowwise_split_case(F24, T, 256, Fh, "per_feature", seed=T + Fh, n_dense=512)
+
+
+@pytest.mark.parametrize("T,Fh", [(256, 320), (4352, 1088)])   # 64 x 64 and 128 x 256 tiles
+def test_featurewise_of_nans_and_infinities(F24, T, Fh):
+    """Few words, so that most groups hold equal magnitudes: NaNs of two payloads, infinities and zeros of both signs, the neighbours of
+    infinity.  The pick is by magnitude word, NaNs above infinity; ties go to the earlier token."""
+    print(f"featurewise NaN T={T} F={Fh}", flush=True)
+    rng = np.random.default_rng(T)
+    words = np.array([0x7FC0, 0xFFC0, 0x7F81, 0xFFFF, 0x7F80, 0xFF80, 0x7F7F, 0xFF7F, 0x0000, 0x8000, 0x0001, 0x3F80], np.uint16)
+    H = words[rng.integers(0, len(words), size=(T, Fh))]
+    H[:, ::4] = np.where(rng.random((T, Fh // 4)) < 0.5, 0x7FC0, 0x7F80).astype(np.uint16)
+    Z = rng.integers(0, 1 << 16, size=(T, Fh)).astype(np.uint16)
+    v, m = O.sparsify24(H)
+    zc = O.compress_with_meta(Z, m)
+    v_ref, m_ref = O.sparsify24(np.ascontiguousarray(O.decompress24(v, m).T))
+    z_ref = O.compress_with_meta(np.ascontiguousarray(O.decompress24(zc, m).T), m_ref)
+    hv, mt, zt = F24.sparsify24_featurewise(P.dev_bf16_from_words(v), torch.from_numpy(m).cuda(), P.dev_bf16_from_words(zc))
+    torch.cuda.synchronize()
+    assert np.array_equal(mt.cpu().numpy(), m_ref) and np.array_equal(P.words_of(hv), v_ref) and np.array_equal(P.words_of(zt), z_ref)
