@@ -10,9 +10,13 @@ namespace ffn24 {
 // The constants are effective ones: fitted to whole steps in a sustained loop on one MI355X (a round of 256 x 256 tiles runs at the power
 // limit there, and a last round that leaves CUs idle at a higher clock, which single launches do not show), with one GEMM at a time taken
 // off the 256 x 256 tile, over 136 shapes: T 256-16384, D 256-5632, F 1024-16384, 0.08 to 6.8 rounds of 256 x 256 tiles in the up-projection,
-// bf16 and both fp8 recipes, 2:4 and dense.  Against the library without smaller tiles, 278 of 279 steps and forwards at 40 shapes that were
-// not fitted (0.03 to 8 rounds, seven kinds) take at most 0.8 % longer, and the mean is 1.34 x faster.  What it avoids: a bf16 step at T 2304
-// D 4864 F 15616 (2.1 rounds) is 2-3 % longer with 256 x 128 up-projection and dH than with 256 x 256.
+// bf16 and both fp8 recipes, 2:4 and dense.  The fit is of before the small tiles read a whole stage ahead and the epilogues went through LDS.
+// What it is worth with the present kernels, at 40 other shapes (T 256-14080, D 256-5120, F 1024-16384, 0.03 to 5.5 rounds): of 280 steps
+// and forwards (seven kinds) none takes more than 0.5 % longer than with 256 x 256 tiles throughout, and the mean (geometric) is 1.45 x
+// faster.  GEMM by GEMM, each of the five tiles in whole steps: 78 % of 480 choices cost at most 0.4 % of a step over the best one, 90 % at most
+// 2 %; the worst are 7.2 and 6.0 % (T 1792 D 2304 F 6400, dense and bf16 step: 128 x 128 where 256 x 256 is the better), the others
+// above 3 % mostly small shapes that take a tile one size too large and weight gradients of half a round that are faster on 128 x 128.
+// What the rule avoids: a bf16 step at T 2304 D 4864 F 15616 (2.1 rounds) is 1.8 % longer with 256 x 128 up-projection and dH than with 256 x 256.
 struct TileCost { int mi, ni, per_k, fixed; };   // 0.1 ns per (bf16) k; ns per tile
 constexpr TileCost TILES_SPARSE[] = {{4, 4, 140, 6000}, {4, 2, 92, 5000}, {2, 2, 57, 3000}, {2, 1, 39, 2000}, {1, 1, 26, 1500}};
 constexpr TileCost TILES_DENSE[] = {{4, 4, 205, 19000}, {4, 2, 132, 5000}, {2, 2, 84, 1750}, {2, 1, 52, 2000}, {1, 1, 34, 1000}};
@@ -20,17 +24,20 @@ constexpr int NUM_TILES = 5;   // the tables list the same tiles
 constexpr long long CHIP_CUS = 256;
 
 // What an epilogue adds to the fill and store of the two largest dense tiles (ns).  The fp8 epilogues scale or quantise every value beside
-// 256 accumulators, and half the reduction time covers it less; the dense row-wise one spills 44 registers on the 256 x 128 tile, which
-// made that tile 4-15 us dearer than 256 x 256 at 1.8-2.6 rounds.
+// 256 accumulators, and half the reduction time covers it less.  The dense row-wise one spills 44 registers on the 256 x 128 tile and 22 on the
+// 256 x 256: the two are equal at 1.8-2.6 rounds (544 us either way at T 5888 D 2304 F 5120, 690 and 691 at T 7168 D 2048 F 6144), where
+// the accumulators alone would make 256 x 128 the better.
 struct EpiCost { int t256x256, t256x128; };
 constexpr EpiCost EPI_PLAIN = {0, 0}, EPI_FP8 = {3000, 0}, EPI_FP8_SPILLS = {3000, 8000};
 
 // The same for a caller's row-major 2:4 operand (spmm24) with K >= ROWS_MIN_K, single launches: 256 x 256 with the main loop of the panel forms,
 // the others with gemm_rows_kernel, whose slots take whole lines of the rows and do not fit the LDS with 256 x 256.  Fitted to 70 shapes (M 256-8192, N
-// 256-4096, K 256-16384): of those with K >= ROWS_MIN_K each takes the fastest of the five.  M 8192 N 2048 K 4096: 256 x 256 71 us, 256 x 128
-// 88; M 4096 N 2048 K 4096: 45 with 256 x 128, 56 with 128 x 128 and with 256 x 256; M 2048 N 2048 K 4096: 28 with 128 x 128, 37 with 128 x 64.
-// Shorter reductions keep the kernels of the panel forms and their rule: with few slots there is little to gain (M N 1024 K 832: 5.2 -> 4.8 us)
-// and the larger slots leave one workgroup on a CU where two ran (M 8192 N 4096 K 512, 128 x 128: 33 -> 41 us).
+// 256-4096, K 256-16384).  At 21 other M x N and K 2048-16384, even and odd multiples of 64, the choice is the fastest of the five but for one,
+// 3 % from it, and no slower anywhere than the kernels of the panel forms with their rule: 1.0-1.45 x (K 4096: M N 512 14.8 -> 12.3 us, M 2048 N
+// 1024 26.5 -> 19.2, M N 2048 32.8 -> 27.7, M 4096 N 2048 50.1 -> 44.2; from 130 tiles of 256 x 256 on the same kernel).
+// The line is on the safe side.  Short reductions have little to gain in slots and lose where the larger slots leave one workgroup on a CU
+// that took two (M N 1536 K 256 4.6 -> 5.1 us, M 8192 N 4096 K 512 on 128 x 128 33 -> 42); between K 1024 and 1984 single launches would gain
+// 3-20 % (M 2048 N 1024 K 1536 10.8 -> 9.0), or 0.3-1.5 us, of which a caller that is bound by its launches sees nothing.
 constexpr int ROWS_MIN_K = 2048;
 constexpr TileCost TILES_ROWS[] = {{4, 4, 155, 5000}, {4, 2, 105, 3700}, {2, 2, 62, 2000}, {2, 1, 39, 2100}, {1, 1, 28, 400}};
 
@@ -83,7 +90,7 @@ inline int pick_pair_tile(bool f8, int Md, int Ms, int N, int K, int sets) {
 
 // Row-major feature-wise re-compression (k_stream.hip): 64 x 64 tiles, 3-4 us whatever there is to do, up to 2^22 elements; above, tiles of
 // 128 tokens x 256 features, which move whole lines but keep a workgroup busy for 7.5 us.  Measured, 64 x 64 against 128 x 256, with
-// dZ: 128 x 64 3.2 / 7.5 us, 128 x 16384 5.2 / 8.8, 2048 x 2048 7.4 / 9.2; 5248 x 896 10.3 / 9.2, 1792 x 3712 12.9 / 9.9.
+// dZ: 128 x 64 2.8 / 7.4 us, 128 x 16384 4.6 / 9.3, 1280 x 3200 9.1 / 10.0, 2048 x 2048 7.8 / 9.8; 5248 x 896 10.7 / 9.8, 1792 x 3712 13.1 / 10.3.
 inline bool featurewise_small(long long T, long long F) { return T * F <= 1 << 22; }
 
 }  // namespace ffn24
