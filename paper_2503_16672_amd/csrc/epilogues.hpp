@@ -83,9 +83,11 @@ template <int MI> __device__ __forceinline__ void st_codes(uint8_t* p, const uin
   }
 }
 
-// x is computed here.  What an epilogue collects tile by tile and uses at its end (row maxima, counts, metadata) the compiler would move
-// there, with all the words it is made of kept until then: 200 of them beside the accumulators, 7-9 registers spilled with 256 x 256 tiles.
-__device__ __forceinline__ void keep_here(uint32_t& x) { asm volatile("" : "+v"(x)); }
+// HERE: x is computed here.  What an epilogue collects tile by tile and uses at its end (row maxima, counts, metadata) the compiler otherwise
+// moves there, with all the words it is made of kept until then.  In the row-wise 2:4 epilogue on 256 x 256 tiles that is 200 of them beside
+// the accumulators, and spilled 7-9 registers; where nothing spills it is the better order (row-wise with counts, 256 x 128, T 2048 D
+// 1024 F 4096: 17.4 us, 18.4 with HERE; bf16 with counts 256 x 256 T = F = 8192 242.5, 245).
+template <bool HERE> __device__ __forceinline__ void keep_here(uint32_t& x) { if constexpr (HERE) asm volatile("" : "+v"(x)); }
 
 // A wave's part of an operand in a bf16 panel form (MI = 4: a lane's 64 features of a token are one 64-byte piece, or two of a dense operand, the
 // two lane halves two panels, or four), through LDS.  A store instruction of a lane's own pieces would put 64 16-byte parts into 64 different lines, 16 times
@@ -354,7 +356,7 @@ __device__ __forceinline__ void st_debug(__bf16* row, int F, const typename TwoT
 // epilogue can compute for free).  A lane first counts in 8-bit fields as the words come, one word for 2 v and 2 v + 1 of an
 // M-tile: bytes 0, 1 from the low halves, bytes 2, 3 from the high halves; fold brings that into 4 features a register, feature f of
 // the lane in field f % 4 of register f / 4.
-template <int MI, int NI> struct NnzCount {
+template <int MI, int NI, bool HERE = false> struct NnzCount {
   static constexpr int ROWS = TwoTokens<NI>::ROWS;
   uint32_t c[MI * ROWS / 2];
   __device__ __forceinline__ NnzCount() {
@@ -365,7 +367,7 @@ template <int MI, int NI> struct NnzCount {
 #pragma unroll
     for (int v = 0; v < ROWS; v += 2) {
       c[(mi * ROWS + v) / 2] += pk_min16(h[v], 0x00010001u) + (pk_min16(h[v + 1], 0x00010001u) << 8);
-      keep_here(c[(mi * ROWS + v) / 2]);
+      keep_here<HERE>(c[(mi * ROWS + v) / 2]);
     }
   }
   __device__ __forceinline__ void fold(uint32_t (&cnt)[4 * MI]) const {
@@ -772,7 +774,8 @@ struct EpiPrune24RwT {
   template <int MI, int NI>
   static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane, char* wbuf) {
     constexpr int TOK = TwoTokens<NI>::TOK;
-    NnzCount<MI, NI> nz;
+    constexpr bool HERE = NI == 4;
+    NnzCount<MI, NI, HERE> nz;
     RowMax<NI> rm;
     rm.load(e.rowmax, n_lane);
     float sxt[NI];
@@ -805,9 +808,9 @@ struct EpiPrune24RwT {
           if constexpr (MI == 4) *reinterpret_cast<u32x4*>(PanelStage<NI>::at(wbuf, NI * (threadIdx.x & 31) + ni + t, mi)) = tt.vals[t];
           else *reinterpret_cast<u32x4*>(e.Hc + a24_piece(n_lane + ni + t, m_lane >> 6, e.F >> 6) * 32 + ((m_lane & 63) >> 1) + 8 * mi) = tt.vals[t];
           nib[ni + t][mi >> 1] |= tt.nib[t] << (16 * (mi & 1));
-          keep_here(nib[ni + t][mi >> 1]);
+          keep_here<HERE>(nib[ni + t][mi >> 1]);
         }
-        keep_here(mx[ni / 2]);
+        keep_here<HERE>(mx[ni / 2]);
       }
       FFN24_FENCE();
     }

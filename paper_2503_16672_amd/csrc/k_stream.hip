@@ -157,7 +157,7 @@ int launch_sparsify24(const void* H, int64_t rows, int64_t cols, void* vals, uin
 // and a wave's stores cover 8 consecutive features at a time.
 // A workgroup walks `tiles` tiles of 64 tokens (fw_tiles), the next one's input on its way while this one is worked on, and raises the row maxima
 // once: with one tile a workgroup two million atomics went out at T = F = 8192.  What bounds it is HBM; feature by feature and tile by tile
-// it took 82.9 us there with the maxima and a split, now 52-57 = 5.0 TB/s and more; without them, T = F = 16384, 206 -> 193 = 5.9 TB/s; T 1280
+// it took 82.9 us there with the maxima and a split, now 52-57 = 5.0 TB/s and more; without them, T = F = 16384, 206 -> 180 = 6.3 TB/s; T 1280
 // F 3072 5.7 -> 4.5.
 constexpr int FW_TOK = 64, FW_FEAT = 64, FW_LDW = FW_FEAT / 2 + 1, FW_TILES = 4;
 
@@ -321,10 +321,11 @@ __global__ void __launch_bounds__(256) featurewise24_kernel(const uint16_t* __re
 }
 
 // Tiles of 64 tokens a workgroup of the panel form walks (T a multiple of 256): four with a split and row maxima, whose atomics go to rows all
-// over the matrix, from a workgroup a CU on; one otherwise.  One, four, in a kernel trace (us), T F with split and maxima: 1024 2048 7.1, 9.7; 1280
-// 3072 9.5, 9.6; 2048 2048 10.6, 10.0; 2816 3840 14.7, 13.5; 4096 4096 20.1, 18.4; 8192 2048 29.0, 19.2; 8192 8192 79.6, 51.8.  Maxima without a
-// split: 2048 2048 6.3, 9.6; 4096 4096 15.9, 16.5; 4096 8192 27.1, 28.6; 8192 8192 62.4, 62.2.  Neither: 2048 4096 6.5, 7.7; 4096 4096 12.9,
-// 13.3; 8192 8192 42.8, 44.4; 16384 16384 193, 197; a split or telemetry alone are the same 2-5 % apart.
+// over the matrix, from a workgroup a CU on; one otherwise.  One, four, in a kernel trace of whole steps (us, T F), with split and maxima: 1280
+// 3072 8.8, 9.2; 2048 2048 11.2, 9.7; 2048 4096 13.1, 11.5; 4096 4096 21.0, 18.8; 8192 2048 28.6, 17.8; 8192 8192 80, 61; 16384 8192 158, 111.
+// Maxima without a split: 2048 4096 8.5, 10.6; 8192 2048 19.4, 18.2; 4096 8192 28.4, 29.8; 8192 8192 50.2, 48.7; 16384 8192 112, 115; 16384 16384
+// 198, 214.  Neither: 2048 4096 6.9, 8.1; 4096 8192 23.9, 24.9; 8192 8192 44.5, 47.8; 16384 16384 180, 197 (telemetry 186, 200); a split alone lies
+// within 4 % either way from 2048 4096 on.
 static int fw_tiles(int T, int F, bool split_maxima) { return split_maxima && (F / FW_FEAT) * (T / (FW_TOK * FW_TILES)) >= 256 ? FW_TILES : 1; }
 
 // out[0] = elements, out[1 + k] = the sum of the slots of quantity k, out[4] = path: what a telemetry snapshot holds
