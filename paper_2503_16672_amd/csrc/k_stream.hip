@@ -325,7 +325,8 @@ __global__ void __launch_bounds__(256) featurewise24_kernel(const uint16_t* __re
 // 3072 8.8, 9.2; 2048 2048 11.2, 9.7; 2048 4096 13.1, 11.5; 4096 4096 21.0, 18.8; 8192 2048 28.6, 17.8; 8192 8192 80, 61; 16384 8192 158, 111.
 // Maxima without a split: 2048 4096 8.5, 10.6; 8192 2048 19.4, 18.2; 4096 8192 28.4, 29.8; 8192 8192 50.2, 48.7; 16384 8192 112, 115; 16384 16384
 // 198, 214.  Neither: 2048 4096 6.9, 8.1; 4096 8192 23.9, 24.9; 8192 8192 44.5, 47.8; 16384 16384 180, 197 (telemetry 186, 200); a split alone lies
-// within 4 % either way from 2048 4096 on.
+// within 4 % either way from 2048 4096 on.  The level differs from program to program, for one and four alike: in a loop
+// with a dense step in between, neither at 8192 8192 takes 59 and 60.
 static int fw_tiles(int T, int F, bool split_maxima) { return split_maxima && (F / FW_FEAT) * (T / (FW_TOK * FW_TILES)) >= 256 ? FW_TILES : 1; }
 
 // out[0] = elements, out[1 + k] = the sum of the slots of quantity k, out[4] = path: what a telemetry snapshot holds
