@@ -344,8 +344,8 @@ FFN24_API int ffn24_kernel_mhz(ffn24_ctx* ctx, int kernel, float* mhz);
 /* Measurement probes (no paper passage: they measure the machine, for the benchmark's report).  Each allocates its own
  * device buffers, runs on the default stream and waits for its own work; not for serving code.
  *   ffn24_probe_mfma_rate: a register-resident loop of matrix instructions with no memory traffic, one wave per SIMD on
- *     every CU, pseudo-random operands.  kind 0 dense bf16 32x32x16, 1 sparse bf16 32x32x32, 2 dense fp8 32x32x64,
- *     3 sparse fp8 32x32x64; iters x 16 ops per wave.  Returns shader-clock cycles per op and wave, the clock (MHz) the
+ *     every CU, pseudo-random operands.  kind 0 dense bf16 16x16x32, 1 sparse bf16 16x16x64, 2 dense fp8 16x16x128,
+ *     3 sparse fp8 16x16x128; iters x 64 ops per wave.  Returns shader-clock cycles per op and wave, the clock (MHz) the
  *     loop ran at, and the chip-wide rate in dense-equivalent TFLOP/s (a sparse op counts its dense equivalent).
  *   ffn24_probe_gemm: the library's GEMM core (dense bf16 if sparse == 0, else 2:4 bf16; plain row-major epilogue) on
  *     pseudo-random operands, M, N multiples of 256, K a multiple of 128 and >= 512, with ingredients of its main loop

@@ -1,6 +1,6 @@
-// Epilogues of the GEMM core: what happens to a lane's 4x4x16 accumulators.
-// A lane owns rows m_lane + 16*mi + v (16 MI consecutive) and columns n_lane + ni (NI consecutive), MI x NI = 4 x 4 for the 256 x 256
-// block tile and less for the smaller ones.  Where a lane holds less than a whole piece of a panel form (64 features), it starts
+// Epilogues of the GEMM core: what happens to a lane's accumulators.
+// A lane owns rows m_lane + 16*mi + v (16 MI consecutive) and columns n_lane + ni (NI consecutive), MI x NI = 2 x 8 for the 256 x 256
+// block tile and 4 x 2 to 1 x 1 for the smaller ones.  Where a lane holds less than a whole piece of a panel form (64 features), it starts
 // m_lane % 64 features into it.
 #pragma once
 #include "gemm_core.hpp"
@@ -9,12 +9,26 @@
 
 namespace ffn24 {
 
+// (counted: an epilogue that needs it does not keep the work item's number in a register through the main loop)
+__device__ __forceinline__ int lane_id() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
+
+// How a wave's lanes share its part of the tile: LANES consecutive ones hold the same 16 MI rows and side by side NI columns each.
+template <int MI, int NI>
+struct LaneTile {
+  static constexpr int LANES = NI == 8 ? 16 : 32, GROUPS = 64 / LANES;
+  static constexpr int ROWS = GROUPS * 16 * MI, COLS = LANES * NI;      // of the wave
+  // the wave holds whole runs of the panel forms, which go through LDS
+  static constexpr bool STAGED = ROWS == 128;
+  static __device__ __forceinline__ int rho() { return lane_id() & (LANES - 1); }             // which columns
+  static __device__ __forceinline__ int h() { return lane_id() / LANES; }              // which rows
+};
+
 // Sums two 16-bit fields over the wave (each field's total must stay below 65536) and has lane 0 add them to slot
 // `slot` of quantities ka and kb.
 __device__ __forceinline__ void tele_add2(unsigned long long* tele, uint32_t packed, int ka, int kb, int slot) {
 #pragma unroll
   for (int sft = 1; sft < 64; sft <<= 1) packed += (uint32_t)__shfl_xor((int)packed, sft, 64);
-  if ((threadIdx.x & 63) == 0) {
+  if (lane_id() == 0) {
     atomicAdd(tele + tele_index(ka, slot), (unsigned long long)(packed & 0xFFFFu));
     if (kb >= 0) atomicAdd(tele + tele_index(kb, slot), (unsigned long long)(packed >> 16));
   }
@@ -61,18 +75,18 @@ template <int MI> __device__ __forceinline__ u32x2 ld_nibbles(const uint8_t* p) 
 
 // NI consecutive bf16 results of one row, rounded and stored in one go
 template <int NI> __device__ __forceinline__ void st_cols(__bf16* p, const float (&x)[NI]) {
-  if constexpr (NI == 4) *reinterpret_cast<u32x2*>(p) = u32x2{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3])};
+  if constexpr (NI == 8) *reinterpret_cast<u32x4*>(p) = u32x4{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7])};
   else if constexpr (NI == 2) *reinterpret_cast<uint32_t*>(p) = pack_bf16x2(x[0], x[1]);
   else *p = (__bf16)x[0];
 }
 // byte b of NI words, stored as NI consecutive bytes
 template <int NI> __device__ __forceinline__ void st_bytes(uint8_t* p, const uint32_t (&w)[NI], int b) {
-  uint32_t o = 0u;
+  uint32_t o[2] = {};
 #pragma unroll
-  for (int i = 0; i < NI; i++) o |= ((w[i] >> (8 * b)) & 0xFFu) << (8 * i);
-  if constexpr (NI == 4) *reinterpret_cast<uint32_t*>(p) = o;
-  else if constexpr (NI == 2) *reinterpret_cast<uint16_t*>(p) = (uint16_t)o;
-  else *p = (uint8_t)o;
+  for (int i = 0; i < NI; i++) o[i / 4] |= ((w[i] >> (8 * b)) & 0xFFu) << (8 * (i % 4));
+  if constexpr (NI == 8) *reinterpret_cast<u32x2*>(p) = u32x2{o[0], o[1]};
+  else if constexpr (NI == 2) *reinterpret_cast<uint16_t*>(p) = (uint16_t)o[0];
+  else *p = (uint8_t)o[0];
 }
 // 2 MI words (8 MI bytes) of e4m3 codes
 template <int MI> __device__ __forceinline__ void st_codes(uint8_t* p, const uint32_t (&q)[2 * MI]) {
@@ -97,36 +111,39 @@ template <bool HERE> __device__ __forceinline__ void keep_here(uint32_t& x) { if
 // 256 x 128 tiles, D 2048: row-wise fp8 dH at T = F = 8192 129 -> 120 us, its up-projection 124 -> 119; bf16 at T 4096 F 8192 dH 120 -> 115.5, up-projection
 // 119.5 -> 117.  256 x 256, T = F = 8192: bf16 dH 227.5 -> 225.7, row-wise fp8 140 -> 133, the up-projections within 1 %.
 // Dense form: a bf16 dense step at T 4096 D 2048 F 8192 762 -> 751 us (up-projection and dH 157 -> 142 each in a kernel trace).
-// P: panels of a lane half (1: the 2:4 form, 64 features of 32 kept values each; 2: the dense form, 32 features each).
-template <int NI, int P = 1>
+// P: panels of 64 features (1: the 2:4 form, 64 features of 32 kept values each; 2: the dense form, 32 features each).
+template <int MI, int NI, int P = 1>
 struct PanelStage {
-  static constexpr int RUN = 32 * NI * 64;           // a panel's run: bytes of 32 NI tokens
+  using LT = LaneTile<MI, NI>;
+  static constexpr int RUN = LT::COLS * 64;          // a panel's run: bytes of the wave's tokens
   static constexpr size_t PANEL = 256 * 64;          // from one panel's pieces to the next one's in memory
-  static __device__ __forceinline__ char* at(char* wbuf, int tok, int c, int panel = 0) {   // 16-byte part c of token tok of the lane's panel
-    const int r = tok >> 2;
-    return wbuf + (((threadIdx.x & 32) ? P : 0) + panel) * RUN + r * 256 + ((((tok & 3) * 4 + c) ^ (r & 15)) << 4);
+  static constexpr int PARTS = P * MI;               // 16-byte parts of a token that a lane holds
+  static constexpr int RUNS = 2 * P, KB = RUN / 1024;
+  // place of part s of LDS row r: rows that lanes next to each other write to differ in the four bits that are taken
+  static __device__ __forceinline__ int swz(int r, int s) { return r * 256 + ((s ^ ((NI == 8 ? r >> 1 : r) & 15)) << 4); }
+  static __device__ __forceinline__ char* at(char* wbuf, int ni, int part) {   // part `part` of the lane's of its token ni
+    const int tok = NI * LT::rho() + ni, p = LT::h() * PARTS + part;
+    return wbuf + (p >> 2) * RUN + swz(tok >> 2, (tok & 3) * 4 + (p & 3));
   }
   // the wave's first piece of its lowest panel
   static __device__ __forceinline__ size_t first(int m_lane, int n_lane, int F) {
-    const int lane = threadIdx.x & 63;
-    return a24_piece(n_lane - NI * (lane & 31), ((m_lane >> 6) - (lane >> 5)) * P, F / (64 / P)) * 64;
+    return a24_piece(n_lane - NI * LT::rho(), ((m_lane - 16 * MI * LT::h()) >> 6) * P, F / (64 / P)) * 64;
   }
   static __device__ __forceinline__ void flush(const char* wbuf, char* out) {
-    const int lane = threadIdx.x & 63;
+    const int lane = lane_id();
 #pragma unroll
-    for (int j = 0; j < 4 * P * NI; j++) {
-      const int q = j % (2 * NI), r = 4 * q + (lane >> 4);
-      *reinterpret_cast<u32x4*>(out + (j / (2 * NI)) * PANEL + q * 1024 + 16 * lane) =
-          *reinterpret_cast<const u32x4*>(wbuf + (j / (2 * NI)) * RUN + r * 256 + (((lane & 15) ^ (r & 15)) << 4));
+    for (int j = 0; j < RUNS * KB; j++) {
+      const int q = j % KB, r = 4 * q + (lane >> 4);
+      *reinterpret_cast<u32x4*>(out + (j / KB) * PANEL + q * 1024 + 16 * lane) = *reinterpret_cast<const u32x4*>(wbuf + (j / KB) * RUN + swz(r, lane & 15));
     }
   }
   // by DMA: the caller waits for vmcnt(0) before the first `at`
   static __device__ __forceinline__ void fetch(char* wbuf, const char* in) {
-    const int lane = threadIdx.x & 63;
+    const int lane = lane_id();
 #pragma unroll
-    for (int j = 0; j < 4 * P * NI; j++) {
-      const int q = j % (2 * NI), r = 4 * q + (lane >> 4);
-      __builtin_amdgcn_global_load_lds((glb_char*)(in + (j / (2 * NI)) * PANEL + r * 256 + (((lane & 15) ^ (r & 15)) << 4)), (lds_char*)(wbuf + j * 1024), 16, 0, 0);
+    for (int j = 0; j < RUNS * KB; j++) {
+      const int q = j % KB, r = 4 * q + (lane >> 4);
+      __builtin_amdgcn_global_load_lds((glb_char*)(in + (j / KB) * PANEL + swz(r, lane & 15)), (lds_char*)(wbuf + j * 1024), 16, 0, 0);
     }
   }
 };
@@ -136,23 +153,24 @@ struct PanelStage {
 // may alias, so each one waited out a full memory round trip by itself (16 of them in the 2:4 epilogue, 32 in the dense one -- the
 // latter had made the dense dH kernel 0.4 ms slower than the GEMM alone).
 // 2:4: one 64-byte piece (or part) of kept values + its metadata bytes per token (bf16 panel form).
-// MI = 4: the kept values come through LDS (PanelStage) and are read from there token by token, `wbuf` staying the place a result of the same
+// LaneTile::STAGED: the kept values come through LDS (PanelStage) and are read from there token by token, `wbuf` staying the place a result of the same
 // form may be put to piece by piece.
 template <int MI, int NI>
 struct LaneSaved24 {
-  u32x4 h[MI == 4 ? 1 : NI][MI];   // [ni][mi]: the kept values of groups 4 mi .. 4 mi + 3
+  static constexpr bool STAGED = LaneTile<MI, NI>::STAGED;
+  u32x4 h[STAGED ? 1 : NI][MI];    // [ni][mi]: the kept values of groups 4 mi .. 4 mi + 3
   u32x2 mt[NI];
   char* wbuf;
   __device__ __forceinline__ u32x4 kept(int ni, int mi) const {
-    if constexpr (MI == 4) return *reinterpret_cast<const u32x4*>(PanelStage<NI>::at(wbuf, NI * (threadIdx.x & 31) + ni, mi));
+    if constexpr (STAGED) return *reinterpret_cast<const u32x4*>(PanelStage<MI, NI>::at(wbuf, ni, mi));
     else return h[ni][mi];
   }
   __device__ __forceinline__ void load(const __bf16* Hc, const uint8_t* meta, int F, int m_lane, int n_lane, char* buf) {
     wbuf = buf;
-    if constexpr (MI == 4) {
-      PanelStage<NI>::fetch(wbuf, reinterpret_cast<const char*>(Hc) + PanelStage<NI>::first(m_lane, n_lane, F));
+    if constexpr (STAGED) {
+      PanelStage<MI, NI>::fetch(wbuf, reinterpret_cast<const char*>(Hc) + PanelStage<MI, NI>::first(m_lane, n_lane, F));
 #pragma unroll
-      for (int ni = 0; ni < NI; ni++) mt[ni] = ld_nibbles<MI>(meta + a24_piece(n_lane + ni, m_lane >> 6, F >> 6) * 8);
+      for (int ni = 0; ni < NI; ni++) mt[ni] = ld_nibbles<MI>(meta + a24_piece(n_lane + ni, m_lane >> 6, F >> 6) * 8 + ((m_lane & 63) >> 3));
       wait_vmcnt<0>();
       asm volatile("" ::: "memory");                 // (the compiler does not see the DMA write what `kept` reads)
       return;
@@ -162,7 +180,7 @@ struct LaneSaved24 {
       size_t piece = a24_piece(n_lane + ni, m_lane >> 6, F >> 6);
       mt[ni] = ld_nibbles<MI>(meta + piece * 8 + ((m_lane & 63) >> 3));
 #pragma unroll
-      for (int mi = 0; mi < MI; mi++) h[MI == 4 ? 0 : ni][mi] = *reinterpret_cast<const u32x4*>(Hc + piece * 32 + ((m_lane & 63) >> 1) + 8 * mi);
+      for (int mi = 0; mi < MI; mi++) h[STAGED ? 0 : ni][mi] = *reinterpret_cast<const u32x4*>(Hc + piece * 32 + ((m_lane & 63) >> 1) + 8 * mi);
     }
   }
 };
@@ -186,8 +204,8 @@ struct LaneSavedDense {
 // C[m][n], n contiguous: 4 consecutive columns per lane and row -> one 8-byte store per row.
 struct EpiRowMajor {
   struct Args { __bf16* C; int ldc; };
-  template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+  template <int MI, int NI, class Acc>
+  static __device__ __forceinline__ void run(const Args& e, Acc& acc, int m_lane, int n_lane) {
 #pragma unroll
     for (int mi = 0; mi < MI; mi++)
 #pragma unroll
@@ -200,25 +218,28 @@ struct EpiRowMajor {
   }
 };
 
-// Transposing store of a wave's 32 MI (m) x 32 NI (n) part of the tile, out[n][m] with m contiguous, through LDS.  With the 256 x 256
-// tile a lane owns 64 consecutive m of 4 columns n, i.e. whole 128-byte runs of 4 output rows, but one store instruction of the wave
+// Transposing store of a wave's part of the tile, out[n][m] with m contiguous, through LDS.  With the 256 x 256
+// tile a lane owns 32 consecutive m of 8 columns n, half lines of 8 output rows, and one store instruction of the wave
 // would put 64 16-byte pieces into 64 different lines (32 instructions, 2048 line transactions a wave; on the short-K
 // weight-gradient GEMMs that alone made the transposing kernels 15 % slower than the row-major ones).  So the packed pieces first
-// go to a wave-private image [n][m] in the operand ring, which is free by then (rows of 4 MI pieces; row n, 16-byte piece c at
-// piece position c ^ (n / NI), so that the 16 lanes an LDS instruction serves together hit different positions both ways),
-// and leave as instructions that write whole rows of the image: 256 contiguous bytes each with MI = 4.
+// go to a wave-private image [n][m] in the operand ring, which is free by then (row n, 16-byte piece c at
+// piece position c ^ key(n), so that the 16 lanes an LDS instruction serves together hit different positions both ways: lanes of different
+// rho, and with LANES = 16 of two neighbouring h, whose pieces differ in the bit that key leaves out),
+// and leave as instructions that write whole rows of the image: 256 contiguous bytes each with 128 rows a wave.
 template <int MI, int NI>
 struct ColMajorStage {
-  static constexpr int PIECES = 4 * MI, ROWS = 32 * NI;
-  static __device__ __forceinline__ int at(int r, int c) { return (r * PIECES + (c ^ ((r / NI) & (PIECES - 1)))) << 4; }
-  // piece `c` (m_local / 8) of row NI rho + ni
-  static __device__ __forceinline__ void put(char* wbuf, int rho, int ni, int c, u32x4 v) { *reinterpret_cast<u32x4*>(wbuf + at(NI * rho + ni, c)) = v; }
-  // out = the wave's corner &C[n_wave][m_wave]
-  static __device__ __forceinline__ void flush(const char* wbuf, __bf16* out, int ldc) {
-    const int lane = threadIdx.x & 63, c = lane & (PIECES - 1), sub = lane / PIECES;
+  using LT = LaneTile<MI, NI>;
+  static constexpr int PIECES = LT::ROWS / 8;
+  static __device__ __forceinline__ int at(int r, int c) { return (r * PIECES + (c ^ ((r / NI) & (LT::LANES == 16 ? 11 : PIECES - 1)))) << 4; }
+  // piece `c` (of 8 m, among the lane's own) of its column ni
+  static __device__ __forceinline__ void put(char* wbuf, int ni, int c, u32x4 v) { *reinterpret_cast<u32x4*>(wbuf + at(NI * LT::rho() + ni, 2 * MI * LT::h() + c)) = v; }
+  // C, ldc: the whole result; m_lane, n_lane: the lane's
+  static __device__ __forceinline__ void flush(const char* wbuf, __bf16* C, int ldc, int m_lane, int n_lane) {
+    __bf16* out = C + (size_t)(n_lane - NI * LT::rho()) * ldc + (m_lane - 16 * MI * LT::h());
+    const int lane = lane_id(), c = lane & (PIECES - 1), sub = lane / PIECES;
     constexpr int PER = 64 / PIECES;   // rows per store instruction
 #pragma unroll
-    for (int j = 0; j < ROWS / PER; j++) {
+    for (int j = 0; j < LT::COLS / PER; j++) {
       const int r = PER * j + sub;
       *reinterpret_cast<u32x4*>(out + (size_t)r * ldc + 8 * c) = *reinterpret_cast<const u32x4*>(wbuf + at(r, c));
     }
@@ -229,9 +250,8 @@ struct ColMajorStage {
 struct EpiColMajor {
   static constexpr bool STAGED = true;
   struct Args { __bf16* C; int ldc; };
-  template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane, char* wbuf) {
-    const int lane = threadIdx.x & 63, rho = lane & 31, h = lane >> 5;
+  template <int MI, int NI, class Acc>
+  static __device__ __forceinline__ void run(const Args& e, Acc& acc, int m_lane, int n_lane, char* wbuf) {
 #pragma unroll
     for (int ni = 0; ni < NI; ni++)
 #pragma unroll
@@ -241,9 +261,9 @@ struct EpiColMajor {
           u32x4 o;
 #pragma unroll
           for (int d = 0; d < 4; d++) o[d] = pack_bf16x2(acc[mi][ni][8 * q + 2 * d], acc[mi][ni][8 * q + 2 * d + 1]);
-          ColMajorStage<MI, NI>::put(wbuf, rho, ni, 2 * MI * h + 2 * mi + q, o);
+          ColMajorStage<MI, NI>::put(wbuf, ni, 2 * mi + q, o);
         }
-    ColMajorStage<MI, NI>::flush(wbuf, e.C + (size_t)(n_lane - NI * rho) * e.ldc + (m_lane - 16 * MI * h), e.ldc);
+    ColMajorStage<MI, NI>::flush(wbuf, e.C, e.ldc, m_lane, n_lane);
   }
 };
 
@@ -257,8 +277,8 @@ template <bool STATS>
 struct EpiRelu2T {
   static constexpr bool STAGED = true;
   struct Args { __bf16* H; __bf16* Ht; const float* b1; int F; int T; unsigned long long* tele; };
-  template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane, char* wbuf) {
+  template <int MI, int NI, class Acc>
+  static __device__ __forceinline__ void run(const Args& e, Acc& acc, int m_lane, int n_lane, char* wbuf) {
     uint32_t nonzero = 0u;   // of this lane's 256 activations
     LaneVec<MI> lb;
     lb.load(e.b1, m_lane, 0.f);
@@ -281,7 +301,7 @@ struct EpiRelu2T {
             o[d] = pack_bf16x2(acc[mi][ni][8 * q + 2 * d], acc[mi][ni][8 * q + 2 * d + 1]);
             if constexpr (STATS) nonzero += min(o[d] & 0xFFFFu, 1u) + min(o[d] >> 16, 1u);
           }
-          if constexpr (MI == 4) *reinterpret_cast<u32x4*>(PanelStage<NI, 2>::at(wbuf, NI * (threadIdx.x & 31) + ni, 2 * (mi & 1) + q, mi >> 1)) = o;
+          if constexpr (LaneTile<MI, NI>::STAGED) *reinterpret_cast<u32x4*>(PanelStage<MI, NI, 2>::at(wbuf, ni, 2 * mi + q)) = o;
           else *reinterpret_cast<u32x4*>(row + 8 * q) = o;
         }
       }
@@ -295,9 +315,9 @@ struct EpiRelu2T {
         }
       }
     }
-    if constexpr (MI == 4) PanelStage<NI, 2>::flush(wbuf, reinterpret_cast<char*>(e.H) + PanelStage<NI, 2>::first(m_lane, n_lane, e.F));
+    if constexpr (LaneTile<MI, NI>::STAGED) PanelStage<MI, NI, 2>::flush(wbuf, reinterpret_cast<char*>(e.H) + PanelStage<MI, NI, 2>::first(m_lane, n_lane, e.F));
     if constexpr (STATS) {
-      if (e.tele) tele_add2(e.tele, nonzero, TELE_NONZERO, -1, blockIdx.x + (threadIdx.x >> 6));
+      if (e.tele) tele_add2(e.tele, nonzero, TELE_NONZERO, -1, blockIdx.x + (m_lane >> 6) + (n_lane >> 6));
     }
   }
 };
@@ -383,21 +403,21 @@ template <int MI, int NI, bool HERE = false> struct NnzCount {
     }
   }
 };
-// The 32 lanes that hold the same 16 MI features add their fields up with a butterfly (<= 128 per field); lane r then adds the
-// totals of features r and (MI = 4) r + 32 to nnz [F] with atomics (the caller zeroes it).
-template <int MI>
+// The lanes that hold the same 16 MI features add their fields up with a butterfly (<= 128 per field); each then adds the
+// totals of every LANES-th feature to nnz [F] with atomics (the caller zeroes it).
+template <int MI, int NI>
 __device__ __forceinline__ void nnz_flush(uint32_t (&cnt)[4 * MI], uint32_t* nnz, int m_lane) {
-  int lane = threadIdx.x & 63;
+  constexpr int LANES = LaneTile<MI, NI>::LANES, REGS = LANES / 4;
 #pragma unroll
   for (int i = 0; i < 4 * MI; i++)
 #pragma unroll
-    for (int sft = 1; sft < 32; sft <<= 1) cnt[i] += (uint32_t)__shfl_xor((int)cnt[i], sft, 64);
-  int r = lane & 31;
+    for (int sft = 1; sft < LANES; sft <<= 1) cnt[i] += (uint32_t)__shfl_xor((int)cnt[i], sft, 64);
+  int r = LaneTile<MI, NI>::rho();
 #pragma unroll
-  for (int b = 0; b < 4 * MI; b += 8) {   // registers b .. b + 7: features 4 b .. 4 b + 31
+  for (int b = 0; b < 4 * MI; b += REGS) {   // registers b .. b + REGS - 1: features 4 b .. 4 b + LANES - 1
     uint32_t w = 0u;
 #pragma unroll
-    for (int i = 0; i < 8; i++)
+    for (int i = 0; i < REGS; i++)
       if (b + i < 4 * MI) w = (r >> 2) == i ? cnt[b + i] : w;
     uint32_t c = (w >> (8 * (r & 3))) & 0xFFu;
     if (c) atomicAdd(nnz + m_lane + 4 * b + r, c);
@@ -422,8 +442,8 @@ template <bool STATS>
 struct EpiPrune24T {
   static constexpr bool STAGED = true;
   struct Args { __bf16* Hc; uint8_t* meta; __bf16* Hdbg; const float* b1; int F; uint32_t* nnz; unsigned long long* tele; };
-  template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane, char* wbuf) {
+  template <int MI, int NI, class Acc>
+  static __device__ __forceinline__ void run(const Args& e, Acc& acc, int m_lane, int n_lane, char* wbuf) {
     constexpr int TOK = TwoTokens<NI>::TOK;
     NnzCount<MI, NI> nz;
     uint32_t kept = 0u;   // non-zero values among the lane's stored ones, first and second of a pair apart (16-bit fields)
@@ -442,7 +462,7 @@ struct EpiPrune24T {
         tt.pick(h);
 #pragma unroll
         for (int t = 0; t < TOK; t++) {
-          if constexpr (MI == 4) *reinterpret_cast<u32x4*>(PanelStage<NI>::at(wbuf, NI * (threadIdx.x & 31) + ni + t, mi)) = tt.vals[t];
+          if constexpr (LaneTile<MI, NI>::STAGED) *reinterpret_cast<u32x4*>(PanelStage<MI, NI>::at(wbuf, ni + t, mi)) = tt.vals[t];
           else *reinterpret_cast<u32x4*>(e.Hc + a24_piece(n_lane + ni + t, m_lane >> 6, e.F >> 6) * 32 + ((m_lane & 63) >> 1) + 8 * mi) = tt.vals[t];
           nib[t][mi >> 1] |= tt.nib[t] << (16 * (mi & 1));
           if constexpr (STATS) {
@@ -454,7 +474,7 @@ struct EpiPrune24T {
 #pragma unroll
       for (int t = 0; t < TOK; t++) st_nibbles<MI>(e.meta + a24_piece(n_lane + ni + t, m_lane >> 6, e.F >> 6) * 8 + ((m_lane & 63) >> 3), nib[t]);
     }
-    if constexpr (MI == 4) PanelStage<NI>::flush(wbuf, reinterpret_cast<char*>(e.Hc) + PanelStage<NI>::first(m_lane, n_lane, e.F));
+    if constexpr (LaneTile<MI, NI>::STAGED) PanelStage<MI, NI>::flush(wbuf, reinterpret_cast<char*>(e.Hc) + PanelStage<MI, NI>::first(m_lane, n_lane, e.F));
     if constexpr (STATS) {
       uint32_t cnt[4 * MI];
       nz.fold(cnt);
@@ -463,9 +483,9 @@ struct EpiPrune24T {
         uint32_t tot = 0u;
 #pragma unroll
         for (int i = 0; i < 4 * MI; i++) tot += (cnt[i] & 0xFFu) + ((cnt[i] >> 8) & 0xFFu) + ((cnt[i] >> 16) & 0xFFu) + (cnt[i] >> 24);
-        tele_add2(e.tele, tot | (((kept & 0xFFFFu) + (kept >> 16)) << 16), TELE_NONZERO, TELE_KEPT_TOK, blockIdx.x + (threadIdx.x >> 6));
+        tele_add2(e.tele, tot | (((kept & 0xFFFFu) + (kept >> 16)) << 16), TELE_NONZERO, TELE_KEPT_TOK, blockIdx.x + (m_lane >> 6) + (n_lane >> 6));
       }
-      if (e.nnz) nnz_flush<MI>(cnt, e.nnz, m_lane);
+      if (e.nnz) nnz_flush<MI, NI>(cnt, e.nnz, m_lane);
     }
   }
 };
@@ -475,8 +495,8 @@ using EpiPrune24 = EpiPrune24T<false>;   // without the statistic (a compile-tim
 // GEMMs work on a permutation of the hidden features and write each row back to its feature).
 struct EpiRowMajorMapped {
   struct Args { __bf16* C; int ldc; const int* rowmap; };
-  template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+  template <int MI, int NI, class Acc>
+  static __device__ __forceinline__ void run(const Args& e, Acc& acc, int m_lane, int n_lane) {
     LaneIdx<MI> rows;
     rows.load(e.rowmap, m_lane);
 #pragma unroll
@@ -498,12 +518,13 @@ struct EpiRowMajorMapped {
 struct EpiDRelu {
   static constexpr bool STAGED = true;
   struct Args { const __bf16* H; __bf16* dZ; __bf16* dZt; int F; int T; };
-  template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane, char* wbuf) {
-    LaneSavedDense<MI == 4 ? 1 : MI, NI> sv;         // (MI = 4: through LDS, like the result)
-    const size_t run = MI == 4 ? PanelStage<NI, 2>::first(m_lane, n_lane, e.F) : 0;
-    if constexpr (MI == 4) {
-      PanelStage<NI, 2>::fetch(wbuf, reinterpret_cast<const char*>(e.H) + run);
+  template <int MI, int NI, class Acc>
+  static __device__ __forceinline__ void run(const Args& e, Acc& acc, int m_lane, int n_lane, char* wbuf) {
+    constexpr bool STAGED = LaneTile<MI, NI>::STAGED;   // through LDS, like the result
+    LaneSavedDense<STAGED ? 1 : MI, STAGED ? 1 : NI> sv;
+    const size_t run = STAGED ? PanelStage<MI, NI, 2>::first(m_lane, n_lane, e.F) : 0;
+    if constexpr (LaneTile<MI, NI>::STAGED) {
+      PanelStage<MI, NI, 2>::fetch(wbuf, reinterpret_cast<const char*>(e.H) + run);
       wait_vmcnt<0>();
       asm volatile("" ::: "memory");                 // (the compiler does not see the DMA write what is read below)
     } else sv.load(e.H, e.F, m_lane, n_lane);
@@ -517,8 +538,8 @@ struct EpiDRelu {
         for (int q = 0; q < 2; q++) {
           char* place = nullptr;
           u32x4 h;
-          if constexpr (MI == 4) {
-            place = PanelStage<NI, 2>::at(wbuf, NI * (threadIdx.x & 31) + ni, 2 * (mi & 1) + q, mi >> 1);
+          if constexpr (LaneTile<MI, NI>::STAGED) {
+            place = PanelStage<MI, NI, 2>::at(wbuf, ni, 2 * mi + q);
             h = *reinterpret_cast<const u32x4*>(place);
           } else h = sv.h[mi][ni][q];
           u32x4 r;
@@ -530,7 +551,7 @@ struct EpiDRelu {
             acc[mi][ni][8 * q + 2 * d + 1] *= g1;
             r[d] = pack_bf16x2(acc[mi][ni][8 * q + 2 * d], acc[mi][ni][8 * q + 2 * d + 1]);
           }
-          if constexpr (MI == 4) *reinterpret_cast<u32x4*>(place) = r;
+          if constexpr (LaneTile<MI, NI>::STAGED) *reinterpret_cast<u32x4*>(place) = r;
           else *reinterpret_cast<u32x4*>(e.dZ + o + 8 * q) = r;
         }
       }
@@ -544,7 +565,7 @@ struct EpiDRelu {
         }
       }
     }
-    if constexpr (MI == 4) PanelStage<NI, 2>::flush(wbuf, reinterpret_cast<char*>(e.dZ) + run);
+    if constexpr (LaneTile<MI, NI>::STAGED) PanelStage<MI, NI, 2>::flush(wbuf, reinterpret_cast<char*>(e.dZ) + run);
   }
 };
 
@@ -554,8 +575,8 @@ struct EpiDRelu {
 struct EpiDGather {
   static constexpr bool STAGED = true;
   struct Args { const __bf16* Hc; const uint8_t* meta; __bf16* dZc; int F; };
-  template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane, char* wbuf) {
+  template <int MI, int NI, class Acc>
+  static __device__ __forceinline__ void run(const Args& e, Acc& acc, int m_lane, int n_lane, char* wbuf) {
     LaneSaved24<MI, NI> sv;
     sv.load(e.Hc, e.meta, e.F, m_lane, n_lane, wbuf);
 #pragma unroll
@@ -580,11 +601,11 @@ struct EpiDGather {
           float g1 = 2.f * __builtin_amdgcn_sqrtf(bf16_hi_to_f32(h[a]));
           z[a] = pack_bf16x2(s0 * g0, s1 * g1);
         }
-        if constexpr (MI == 4) *reinterpret_cast<u32x4*>(PanelStage<NI>::at(wbuf, NI * (threadIdx.x & 31) + ni, mi)) = z;
+        if constexpr (LaneTile<MI, NI>::STAGED) *reinterpret_cast<u32x4*>(PanelStage<MI, NI>::at(wbuf, ni, mi)) = z;
         else *reinterpret_cast<u32x4*>(zrow + 8 * mi) = z;
       }
     }
-    if constexpr (MI == 4) PanelStage<NI>::flush(wbuf, reinterpret_cast<char*>(e.dZc) + PanelStage<NI>::first(m_lane, n_lane, e.F));
+    if constexpr (LaneTile<MI, NI>::STAGED) PanelStage<MI, NI>::flush(wbuf, reinterpret_cast<char*>(e.dZc) + PanelStage<MI, NI>::first(m_lane, n_lane, e.F));
   }
 };
 
@@ -634,8 +655,8 @@ struct ExactDiv {
 struct EpiPrune24F8 {
   static constexpr EpiCost COST = EPI_FP8;
   struct Args { uint8_t* Hc8; uint8_t* meta; __bf16* Hdbg; const float* b1; int F; float zscale; float sh; __bf16* Hc16; uint8_t* meta16; };
-  template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+  template <int MI, int NI, class Acc>
+  static __device__ __forceinline__ void run(const Args& e, Acc& acc, int m_lane, int n_lane) {
     constexpr int TOK = TwoTokens<NI>::TOK;
     LaneVec<MI> lb;
     lb.load(e.b1, m_lane, 0.f);
@@ -683,8 +704,8 @@ struct EpiDGatherF8 {
   static constexpr bool STAGED = true;
   static constexpr EpiCost COST = EPI_FP8;
   struct Args { const __bf16* Hc16; const uint8_t* meta16; uint8_t* dZc8; int F; float scale; float sdz; };
-  template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane, char* wbuf) {
+  template <int MI, int NI, class Acc>
+  static __device__ __forceinline__ void run(const Args& e, Acc& acc, int m_lane, int n_lane, char* wbuf) {
     LaneSaved24<MI, NI> sv;
     sv.load(e.Hc16, e.meta16, e.F, m_lane, n_lane, wbuf);
     const ExactDiv by_sdz(e.sdz);
@@ -720,9 +741,8 @@ struct EpiDGatherF8 {
 struct EpiColMajorScaled {
   static constexpr bool STAGED = true;
   struct Args { __bf16* C; int ldc; float scale; };
-  template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane, char* wbuf) {
-    const int lane = threadIdx.x & 63, rho = lane & 31, h = lane >> 5;
+  template <int MI, int NI, class Acc>
+  static __device__ __forceinline__ void run(const Args& e, Acc& acc, int m_lane, int n_lane, char* wbuf) {
 #pragma unroll
     for (int ni = 0; ni < NI; ni++)
 #pragma unroll
@@ -732,9 +752,9 @@ struct EpiColMajorScaled {
           u32x4 o;
 #pragma unroll
           for (int d = 0; d < 4; d++) o[d] = pack_bf16x2(acc[mi][ni][8 * q + 2 * d] * e.scale, acc[mi][ni][8 * q + 2 * d + 1] * e.scale);
-          ColMajorStage<MI, NI>::put(wbuf, rho, ni, 2 * MI * h + 2 * mi + q, o);
+          ColMajorStage<MI, NI>::put(wbuf, ni, 2 * mi + q, o);
         }
-    ColMajorStage<MI, NI>::flush(wbuf, e.C + (size_t)(n_lane - NI * rho) * e.ldc + (m_lane - 16 * MI * h), e.ldc);
+    ColMajorStage<MI, NI>::flush(wbuf, e.C, e.ldc, m_lane, n_lane);
   }
 };
 
@@ -745,7 +765,7 @@ struct EpiColMajorScaled {
 // and an atomic goes out only where it would raise one.  That spares the later rounds of a launch and most of a tile that starts late;
 // tiles of one round that finish together all see the cleared value and all send theirs.  A value that is out of date is lower and
 // only costs an atomic.
-template <int NI>
+template <int MI, int NI>
 struct RowMax {
   uint32_t seen[NI];
   __device__ __forceinline__ void load(const uint32_t* rowmax, int n_lane) {
@@ -753,8 +773,9 @@ struct RowMax {
     for (int ni = 0; ni < NI; ni++) seen[ni] = __hip_atomic_load(rowmax + n_lane + ni, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   __device__ __forceinline__ void raise(uint32_t* rowmax, int n_lane, int ni, uint32_t mx) const {
-    mx = max(mx, (uint32_t)__shfl_xor((int)mx, 32, 64));
-    if ((threadIdx.x & 32) == 0 && mx > seen[ni]) atomicMax(rowmax + n_lane + ni, mx);
+#pragma unroll
+    for (int sft = LaneTile<MI, NI>::LANES; sft < 64; sft <<= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, sft, 64));
+    if (LaneTile<MI, NI>::h() == 0 && mx > seen[ni]) atomicMax(rowmax + n_lane + ni, mx);
   }
 };
 
@@ -771,12 +792,12 @@ struct EpiPrune24RwT {
   static constexpr EpiCost COST = EPI_FP8;
   static constexpr bool STAGED = true;
   struct Args { __bf16* Hc; uint8_t* meta; __bf16* Hdbg; const float* b1; int F; const float* sx; const float* sw1; uint32_t* rowmax; uint32_t* nnz; };
-  template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane, char* wbuf) {
+  template <int MI, int NI, class Acc>
+  static __device__ __forceinline__ void run(const Args& e, Acc& acc, int m_lane, int n_lane, char* wbuf) {
     constexpr int TOK = TwoTokens<NI>::TOK;
-    constexpr bool HERE = NI == 4;
+    constexpr bool HERE = NI == 8;
     NnzCount<MI, NI, HERE> nz;
-    RowMax<NI> rm;
+    RowMax<MI, NI> rm;
     rm.load(e.rowmax, n_lane);
     float sxt[NI];
 #pragma unroll
@@ -805,7 +826,7 @@ struct EpiPrune24RwT {
         tt.pick(h);
 #pragma unroll
         for (int t = 0; t < TOK; t++) {
-          if constexpr (MI == 4) *reinterpret_cast<u32x4*>(PanelStage<NI>::at(wbuf, NI * (threadIdx.x & 31) + ni + t, mi)) = tt.vals[t];
+          if constexpr (LaneTile<MI, NI>::STAGED) *reinterpret_cast<u32x4*>(PanelStage<MI, NI>::at(wbuf, ni + t, mi)) = tt.vals[t];
           else *reinterpret_cast<u32x4*>(e.Hc + a24_piece(n_lane + ni + t, m_lane >> 6, e.F >> 6) * 32 + ((m_lane & 63) >> 1) + 8 * mi) = tt.vals[t];
           nib[ni + t][mi >> 1] |= tt.nib[t] << (16 * (mi & 1));
           keep_here<HERE>(nib[ni + t][mi >> 1]);
@@ -814,7 +835,7 @@ struct EpiPrune24RwT {
       }
       FFN24_FENCE();
     }
-    if constexpr (MI == 4) PanelStage<NI>::flush(wbuf, reinterpret_cast<char*>(e.Hc) + PanelStage<NI>::first(m_lane, n_lane, e.F));
+    if constexpr (LaneTile<MI, NI>::STAGED) PanelStage<MI, NI>::flush(wbuf, reinterpret_cast<char*>(e.Hc) + PanelStage<MI, NI>::first(m_lane, n_lane, e.F));
 #pragma unroll
     for (int ni = 0; ni < NI; ni++) {
       st_nibbles<MI>(e.meta + a24_piece(n_lane + ni, m_lane >> 6, e.F >> 6) * 8 + ((m_lane & 63) >> 3), nib[ni]);
@@ -824,7 +845,7 @@ struct EpiPrune24RwT {
     if constexpr (STATS) {
       uint32_t cnt[4 * MI];
       nz.fold(cnt);
-      nnz_flush<MI>(cnt, e.nnz, m_lane);
+      nnz_flush<MI, NI>(cnt, e.nnz, m_lane);
     }
   }
 };
@@ -839,9 +860,9 @@ using EpiPrune24Rw = EpiPrune24RwT<false>;
 struct EpiRelu2Rw {
   static constexpr EpiCost COST = EPI_FP8_SPILLS;
   struct Args { __bf16* H16; const float* b1; int F; const float* sx; const float* sw1; uint32_t* rowmax; __bf16* Ht16; int T; };
-  template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
-    RowMax<NI> rm;
+  template <int MI, int NI, class Acc>
+  static __device__ __forceinline__ void run(const Args& e, Acc& acc, int m_lane, int n_lane) {
+    RowMax<MI, NI> rm;
     rm.load(e.rowmax, n_lane);
     LaneVec<MI> lb, lw;
     lb.load(e.b1, m_lane, 0.f);
@@ -895,9 +916,9 @@ struct EpiRelu2Rw {
 struct EpiDReluRw {
   static constexpr EpiCost COST = EPI_FP8;
   struct Args { const __bf16* H16; __bf16* dZ16; __bf16* dZt16; int F; int T; const float* rs; const float* cs; uint32_t* rowmax; };
-  template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
-    RowMax<NI> rm;
+  template <int MI, int NI, class Acc>
+  static __device__ __forceinline__ void run(const Args& e, Acc& acc, int m_lane, int n_lane) {
+    RowMax<MI, NI> rm;
     rm.load(e.rowmax, n_lane);
     LaneVec<MI> lr;
     lr.load(e.rs, m_lane, 1.f);
@@ -946,8 +967,8 @@ struct EpiDReluRw {
 // C[m][n] = bf16(acc * rs[m] * cs[n]), n contiguous (row-wise-scaled fp8 down-projection: rs = sh per token, cs = sw2).
 struct EpiRowMajorRowCol {
   struct Args { __bf16* C; int ldc; const float* rs; const float* cs; };
-  template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+  template <int MI, int NI, class Acc>
+  static __device__ __forceinline__ void run(const Args& e, Acc& acc, int m_lane, int n_lane) {
     float cs[NI];
 #pragma unroll
     for (int ni = 0; ni < NI; ni++) cs[ni] = e.cs[n_lane + ni];
@@ -970,8 +991,8 @@ struct EpiRowMajorRowCol {
 // of the permuted feature space, rs their scales in that order; each row goes back to its feature).
 struct EpiRowMajorRowColMapped {
   struct Args { __bf16* C; int ldc; const float* rs; const float* cs; const int* rowmap; };
-  template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+  template <int MI, int NI, class Acc>
+  static __device__ __forceinline__ void run(const Args& e, Acc& acc, int m_lane, int n_lane) {
     float cs[NI];
 #pragma unroll
     for (int ni = 0; ni < NI; ni++) cs[ni] = e.cs[n_lane + ni];
@@ -997,9 +1018,8 @@ struct EpiRowMajorRowColMapped {
 struct EpiColMajorRowCol {
   static constexpr bool STAGED = true;
   struct Args { __bf16* C; int ldc; const float* rs; const float* cs; };
-  template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane, char* wbuf) {
-    const int lane = threadIdx.x & 63, rho = lane & 31, h = lane >> 5;
+  template <int MI, int NI, class Acc>
+  static __device__ __forceinline__ void run(const Args& e, Acc& acc, int m_lane, int n_lane, char* wbuf) {
     LaneVec<MI> lr;
     lr.load(e.rs, m_lane, 1.f);
 #pragma unroll
@@ -1015,10 +1035,10 @@ struct EpiColMajorRowCol {
             int i = 16 * mi + 8 * q + 2 * d;
             o[d] = pack_bf16x2(acc[mi][ni][8 * q + 2 * d] * lr.at(i) * cs, acc[mi][ni][8 * q + 2 * d + 1] * lr.at(i + 1) * cs);
           }
-          ColMajorStage<MI, NI>::put(wbuf, rho, ni, 2 * MI * h + 2 * mi + q, o);
+          ColMajorStage<MI, NI>::put(wbuf, ni, 2 * mi + q, o);
         }
     }
-    ColMajorStage<MI, NI>::flush(wbuf, e.C + (size_t)(n_lane - NI * rho) * e.ldc + (m_lane - 16 * MI * h), e.ldc);
+    ColMajorStage<MI, NI>::flush(wbuf, e.C, e.ldc, m_lane, n_lane);
   }
 };
 
@@ -1033,9 +1053,9 @@ struct EpiDGatherRw {
   static constexpr bool STAGED = true;
   static constexpr EpiCost COST = EPI_FP8;
   struct Args { const __bf16* Hc16; const uint8_t* meta16; __bf16* dZc16; int F; const float* rs; const float* cs; uint32_t* rowmax; };
-  template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane, char* wbuf) {
-    RowMax<NI> rm;
+  template <int MI, int NI, class Acc>
+  static __device__ __forceinline__ void run(const Args& e, Acc& acc, int m_lane, int n_lane, char* wbuf) {
+    RowMax<MI, NI> rm;
     rm.load(e.rowmax, n_lane);
     LaneVec<MI> lr;
     lr.load(e.rs, m_lane, 1.f);
@@ -1070,12 +1090,12 @@ struct EpiDGatherRw {
           z[a] = pack_bf16x2(s0 * g0, s1 * g1);
           mx = max(mx, max(z[a] & 0x7FFFu, (z[a] >> 16) & 0x7FFFu));
         }
-        if constexpr (MI == 4) *reinterpret_cast<u32x4*>(PanelStage<NI>::at(wbuf, NI * (threadIdx.x & 31) + ni, mi)) = z;
+        if constexpr (LaneTile<MI, NI>::STAGED) *reinterpret_cast<u32x4*>(PanelStage<MI, NI>::at(wbuf, ni, mi)) = z;
         else *reinterpret_cast<u32x4*>(zrow + 8 * mi) = z;
       }
       rm.raise(e.rowmax, n_lane, ni, mx);
     }
-    if constexpr (MI == 4) PanelStage<NI>::flush(wbuf, reinterpret_cast<char*>(e.dZc16) + PanelStage<NI>::first(m_lane, n_lane, e.F));
+    if constexpr (LaneTile<MI, NI>::STAGED) PanelStage<MI, NI>::flush(wbuf, reinterpret_cast<char*>(e.dZc16) + PanelStage<MI, NI>::first(m_lane, n_lane, e.F));
   }
 };
 
@@ -1087,8 +1107,8 @@ struct EpiDGatherRw {
 struct EpiRelu2F8 {
   static constexpr EpiCost COST = EPI_FP8;
   struct Args { uint8_t* H8; const float* b1; int F; float zscale; float sh; __bf16* H16; uint8_t* H8t; int T; };
-  template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+  template <int MI, int NI, class Acc>
+  static __device__ __forceinline__ void run(const Args& e, Acc& acc, int m_lane, int n_lane) {
     LaneVec<MI> lb;
     lb.load(e.b1, m_lane, 0.f);
     uint32_t qs[NI][4 * MI];   // the lane's codes: [token][4 features per word]
@@ -1139,8 +1159,8 @@ struct EpiRelu2F8 {
 struct EpiDReluF8 {
   static constexpr EpiCost COST = EPI_FP8;
   struct Args { const __bf16* H16; uint8_t* dZ8; uint8_t* dZ8t; int F; int T; float scale; float sdz; };
-  template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+  template <int MI, int NI, class Acc>
+  static __device__ __forceinline__ void run(const Args& e, Acc& acc, int m_lane, int n_lane) {
     uint32_t qs[NI][4 * MI];
     const ExactDiv by_sdz(e.sdz);
     LaneSavedDense<MI, NI> sv;
@@ -1183,8 +1203,8 @@ struct EpiDReluF8 {
 // C[m][n] = bf16(scale * acc), n contiguous (fp8 down-projection: scale = sh * sw2).
 struct EpiRowMajorScaled {
   struct Args { __bf16* C; int ldc; float scale; };
-  template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane) {
+  template <int MI, int NI, class Acc>
+  static __device__ __forceinline__ void run(const Args& e, Acc& acc, int m_lane, int n_lane) {
 #pragma unroll
     for (int mi = 0; mi < MI; mi++)
 #pragma unroll

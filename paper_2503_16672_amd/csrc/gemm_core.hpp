@@ -2,14 +2,14 @@
 //
 // One kernel template computes C[m][n] = sum_k A[m][k] * B[n][k]; both operands are K-contiguous in memory
 // (operands that are not are transposed once by a streaming kernel, see k_stream.hip).  Four wavefronts (2x2), each owning a
-// wave tile of MI x NI MFMA tiles of 32x32, so a block tile is 64 MI x 64 NI.  Block tile 256x256 (MI = NI = 4: 256 accumulator
+// wave tile of 32 MI x 32 NI, so a block tile is 64 MI x 64 NI.  Block tile 256x256 (MI = NI = 4: 256 accumulator
 // registers per lane, pinned to the AGPR file) is the one that streams the fewest operand bytes per matrix op and carries the
 // large problems; 256x128, 128x128, 128x64 and 64x64 take the shapes whose 256x256 tiles would leave CUs idle (pick_tile in
-// tile_rule.hpp).  What follows describes the 256x256 tile; the smaller ones have the same LDS rows, swizzles and lane layouts.
+// tile_rule.hpp).  The 256x256 tile, at the power limit, uses the 16x16 matrix ops (gemm_tile_big), the smaller ones the 32x32 ops.
 // An output element sums the same k in the same order in every tile, so the results are the same bit for bit.
 //
-//   A dense  : [M][K]                         -> v_mfma_f32_32x32x16_bf16
-//   A sparse : 2:4-compressed [M][K/2] + metadata [M][K/8] -> v_smfmac_f32_32x32x32_bf16
+//   A dense  : [M][K]                         -> v_mfma_f32_16x16x32_bf16, v_mfma_f32_32x32x16_bf16
+//   A sparse : 2:4-compressed [M][K/2] + metadata [M][K/8] -> v_smfmac_f32_16x16x64_bf16, v_smfmac_f32_32x32x32_bf16
 //   B        : [N][K]
 //
 // 2:4 operand (Sec. 1 of the paper, "Hardware-accelerated (2:4) sparsity"; Fig. 2): of every 4 consecutive K entries
@@ -29,29 +29,23 @@
 //
 // Data movement.  Global memory goes straight to LDS (global_load_lds_dwordx4: no VGPR staging, no LDS store
 // instructions) into a ring of stage buffers, 2-3 stages ahead of the math, so that L2/HBM latency is covered:
-//   dense : stage = 32 k  (A 16 KiB + B 16 KiB), ring of 4  -> 128 KiB of the CU's 160 KiB LDS
-//   sparse: stage = 64 k  (A 16 KiB stored values + 2 KiB metadata + B 32 KiB), ring of 3 -> 150 KiB
+//   dense : stage = 32 k  (A 16 KiB + B 16 KiB), ring of 4  -> 128 KiB of the CU's 160 KiB LDS (fp8: 64 k, ring of 5, all of it)
+//   sparse: stage = 64 k  (A 16 KiB stored values + 2 KiB metadata + B 32 KiB), ring of 3 -> 151 KiB
 // A wave-level DMA instruction fills 1 KiB of LDS in lane order, so the swizzled, row-permuted LDS layout is
 // produced by choosing which global 16 bytes each lane fetches.
 //
-// Schedule of one stage (two K steps of 16 matrix ops each), written slot by slot with scheduling fences:
-//   step 0: matrix ops; the LDS fragment reads of step 1 ride on them
-//   wait for the next stage's DMA, one workgroup barrier
-//   step 1: matrix ops; the DMA of the stage that reuses this buffer and the fragment reads of the next stage's
-//           step 0 ride on them -- the DMA instructions on every other slot only, and for the sparse stage (14 a wave) half
-//           of them on the even slots of the NEXT stage's step 0 (see dma_on_step1 below)
-//
-// Lane layouts of the matrix instructions (measured on gfx950 with one-hot operands):
+// Lane layouts of the matrix instructions (measured on gfx950 with one-hot operands; the 16x16 ops at gemm_tile_big):
 //   dense 32x32x16:  A lane l holds row l%32, k = 8*(l/32)..+7;  B lane l holds column l%32, same k;
 //                    C register v of lane l is row 8*(v/4) + 4*(l/32) + v%4, column l%32.
 //   sparse 32x32x32: A lane l holds row l%32 and the 8 stored values of dense k 16*(l/32)..+15;
 //                    B lane l holds column l%32, registers 0..7 = k 8*(l/32)..+7, registers 8..15 = k 16+8*(l/32)..+7.
 //
 // Row remapping.  Which global row sits in which MFMA-tile row is free, so it is chosen to make every lane's
-// accumulators contiguous in memory:  wave-tile row 64*hc + 16*mi + v belongs to lane half hc, M-tile mi,
-// accumulator register v (64 consecutive rows per lane, in groups of 4 that never straddle lanes -- the 2:4 groups of
-// the fused prune epilogue);  wave-tile column 4*c + ni belongs to lane column c, N-tile ni (4 consecutive columns
-// per lane).  The permutation is applied when a tile is brought into LDS, so fragment reads stay linear.
+// accumulators contiguous in memory.  32x32 ops:  wave-tile row 16*MI*hc + 16*mi + v belongs to lane half hc, M-tile mi,
+// accumulator register v (16 MI consecutive rows per lane, in groups of 4 that never straddle lanes -- the 2:4 groups of
+// the fused prune epilogue);  wave-tile column NI*c + ni belongs to lane column c, N-tile ni (NI consecutive columns
+// per lane).  16x16 ops: rows 32*q + 4*t + v and columns 8*c + t, 32 x 8 a lane.  The permutation is applied when a tile is brought into LDS
+// or when its fragments are read.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -95,14 +89,14 @@ constexpr int PROBE_WALK_BANDS = 16;   // bands of 8 tile-rows, each XCD a conti
 constexpr int PROBE_WALK_8x1 = 32;     // the 8 patches of a round side by side along M
 constexpr int PROBE_PATCH_4x8 = 64;    // per-XCD patches of 4 x 8 tiles
 constexpr int PROBE_PATCH_16x2 = 128;  // per-XCD patches of 16 x 2 tiles
-constexpr int PROBE_UNPACED = 256;     // a stage's DMA instructions on consecutive matrix-op slots of its second K step
+constexpr int PROBE_UNPACED = 256;     // DMA instructions on consecutive matrix-op slots (of each half of a step)
 constexpr int PROBE_PERSIST = 1024;    // one workgroup per CU walks the tiles id, id + grid, ...; the next tile's first stages are asked for
                                        // before the epilogue of the present one
 constexpr int PROBE_FILL_LESS = 512;   // sparse: the last 3 of a wave's 14 DMA instructions of every stage are left out -- 38 KiB a stage
                                        // instead of 50, about the bytes per matrix op of a 384 x 256 tile (what a taller tile could gain)
 
-// B panel form: the dense panel form (64-byte pieces, a24_piece) whose rows are, inside every block of 256, stored in the
-// order the block tile keeps them in LDS: position q of a block holds row unperm_n(q), i.e. row n sits at b_panel_pos(n).
+// B panel form: the dense panel form (64-byte pieces, a24_piece) whose rows are, inside every block of 256, stored at b_panel_pos(n): the four
+// rows n .. n + 3 of a multiple of 4 at places 32 apart, rows 4 apart next to each other.
 // A stage of a block tile's B operand is then one (sparse: two) contiguous 16 KiB run(s), and every DMA instruction
 // reads whole 128-byte lines.  Used for every B operand the library makes itself (re-arranged weights, transposed
 // activations); a caller's row-major B (spmm24; X and dY) is read as it is.
@@ -119,7 +113,7 @@ __host__ __device__ __forceinline__ size_t a24_piece(int r, int kp, int npanels)
 // when it has one.  Sparse 256 x 128 has room for two stages a workgroup only, and those expose the memory latency (112 us; 81 us with
 // four stages and the CU to itself).
 constexpr int ring_depth(bool sparse, bool f8, int mi, int ni) {
-  return mi * ni == 16 ? (sparse ? 3 : 4) : mi * ni == 8 ? (sparse ? 4 : 3) : mi * ni == 4 ? (sparse ? 3 : 4) : mi * ni == 2 || !sparse ? 4 : 6;
+  return mi * ni == 16 ? (sparse ? 3 : f8 ? 5 : 4) : mi * ni == 8 ? (sparse ? 4 : 3) : mi * ni == 4 ? (sparse ? 3 : 4) : mi * ni == 2 || !sparse ? 4 : 6;
 }
 // A dense 64 x 64 stage holds twice the k, in rows of 128 bytes: half the waits and barriers, and a row-major operand is read in whole
 // lines (1024 x 1024, one tile a CU: K 1024 7.1 -> 6.0 us, K 4096 19.8 -> 15.0, with a row-major B too; two tiles a CU 8.1 -> 7.4, 25 -> 25, row-major
@@ -137,12 +131,14 @@ struct Geo {
   static constexpr int BM = 64 * MI, BN = 64 * NI;        // block tile: 2 x 2 waves of 32 MI x 32 NI
   static constexpr int ESIZE = F8 ? 1 : 2;
   static constexpr bool WIDE = !SPARSE && wide_stage(MI, NI);
+  static constexpr bool BIG = MI * NI == 16;             // 16 x 16 matrix ops, in an order of LDS rows of its own
   static constexpr int A_ROW = WIDE ? 128 : 64;          // dense k, or the stored values of twice as many k
   static constexpr int B_ROW = SPARSE || WIDE ? 128 : 64;
   static constexpr int BK = B_ROW / ESIZE;               // dense k per stage
   static constexpr int A_BYTES = BM * A_ROW;
   static constexpr int META_ROW = SPARSE ? (F8 ? 16 : 8) : 0;   // metadata bytes per row and stage (4 bits per group of 4 k)
-  static constexpr int META_BYTES = BM * META_ROW;
+  // metadata: BM rows; the 256 x 256 tile shifts every KiB (bf16: 256 bytes) a DMA instruction brings by a few banks (big_meta)
+  static constexpr int META_BYTES = BIG ? 4 * (F8 ? 1024 + 128 : 2 * (256 + 32)) * (SPARSE ? 1 : 0) : BM * META_ROW;
   static constexpr int B_BYTES = BN * B_ROW;
   static constexpr int META_OFF = A_BYTES;
   static constexpr int B_OFF = A_BYTES + META_BYTES;
@@ -165,12 +161,25 @@ __device__ __forceinline__ int unperm_m(int p) {
 }
 template <int NI>
 __device__ __forceinline__ int unperm_n(int p) { return (p & (32 * NI)) | ((p & 31) * NI) | ((p >> 5) & (NI - 1)); }
+// The 256 x 256 tile: row 32 q + 4 t + v of the wave tile belongs to lane quarter q, M-tile t, register v, and column 8 c + t to lane column c, N-tile t.
+// A rows lie in LDS as they are.  B: LDS row -> lane column and N-tile; what one DMA instruction fetches (16 rows of 64 bytes, 8 of 128) are
+// neighbouring pieces of the B panel form (n at b_panel_pos(n)) in an order that puts the rows a fragment read takes together
+// into one run: 8 of 64 bytes, 4 of 128.
+template <bool SPARSE> __device__ __forceinline__ int big_n_col(int p) { return SPARSE ? ((p >> 3) & 3) << 2 | (p & 3) : ((p >> 4) & 1) << 3 | (p & 7); }
+template <bool SPARSE> __device__ __forceinline__ int big_n_tile(int p) { return ((p >> 5) & 3) | (SPARSE ? (p >> 2) & 1 : (p >> 3) & 1) << 2; }
+template <bool SPARSE> __device__ __forceinline__ int big_unperm_n(int p) { return (p & 128) | big_n_col<SPARSE>(p) << 3 | big_n_tile<SPARSE>(p); }
 // 16-byte chunk swizzles.  A 16-byte-per-lane LDS read of a wavefront is served 16 lanes per clock, and the lanes
 // that share a clock are not consecutive: {0-3, 20-23} and {4-7, 16-19} each pair up with {8-11, 28-31} or
 // {12-15, 24-27} (likewise +32); they must hit 16 different 16-byte slots of the 256-byte bank row (measured on
 // gfx950 with a read-throughput probe: both swizzles run at the rate of a linear read).
 __device__ __forceinline__ int swz8(int p) { return (p ^ (p >> 3)) & 7; }          // 128-byte rows
 __device__ __forceinline__ int swz4(int p) { return ((p >> 2) & 1) | ((((p >> 1) ^ (p >> 3)) & 1) << 1); }   // 64-byte rows
+// The same for the 256 x 256 tiles, whose fragments are 16 rows (of lanes i = 0 .. 15) by four chunks: the lanes that share a clock are four
+// neighbouring i of each i / 4, neighbouring i / 4 on different quarters.  64-byte rows, four of them in a bank row: the quarters take chunks
+// 0 1 2 3 (dense; neighbours differ in bit 0, so bit 3 of i goes to bit 1) or 0 2 1 3 (2:4; the other way round).  128-byte rows: chunks
+// 0 1 4 5 and two on, so bits 1 and 3 of i go to bits 1 and 2.
+template <bool SPARSE> __device__ __forceinline__ int swz4_big(int i) { return SPARSE ? (i >> 3) & 1 : ((i >> 3) & 1) << 1; }
+__device__ __forceinline__ int swz8_big(int i) { return (i & 2) | (((i >> 3) & 1) << 2); }
 
 // compile-time loop: f(std::integral_constant<int, 0>) ... f(std::integral_constant<int, N-1>)
 template <class F, int... Is>
@@ -181,6 +190,13 @@ __device__ __forceinline__ void static_for(F&& f) { static_for_impl(f, std::make
 // Nothing may be moved across this point by the instruction scheduler.  The main loop is written as a sequence of
 // slots {one matrix op + the memory ops that ride on it}, fenced from each other, so the issue order is the source order.
 #define FFN24_FENCE() __builtin_amdgcn_sched_barrier(0)
+
+// The lane's number, counted anew: kept in a register from the start of the kernel through the main loop it is one more than the 256 x 256 tiles have.
+__device__ __forceinline__ int fresh_lane() {
+  uint32_t all;
+  asm volatile("s_mov_b32 %0, -1" : "=s"(all));
+  return __builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0));
+}
 
 // s_waitcnt with only the vector-memory counter constrained (gfx9 encoding: vmcnt = bits 3:0 and 15:14)
 template <int N>
@@ -197,9 +213,9 @@ template <bool SPARSE, bool F8 = false, int PROBE = 0, int MI = 4, int NI = 4>
 struct Dma {
   using G = Geo<SPARSE, F8, MI, NI>;
   static constexpr int NA = G::NA, NVB = G::NVB;
-  const char* a;      // block's first A row (uniform)
-  const char* am;     // metadata
-  const char* b;
+  __amdgpu_buffer_rsrc_t a;      // from the block's first A row on (uniform)
+  __amdgpu_buffer_rsrc_t am;     // metadata
+  __amdgpu_buffer_rsrc_t b;
   uint32_t va[NA], vm[2], vb[NVB];   // per-lane byte offsets from the uniform bases
   uint32_t a_stage, m_stage, b_stage;          // bytes from one stage to the next in the A values / metadata / B stream
   int wave;
@@ -214,13 +230,9 @@ struct Dma {
     const bool panel = g.a_panel != 0, bp = g.b_panel != 0;
     const uint32_t a_pitch = panel ? 64u : a_row, m_pitch = panel ? (uint32_t)G::META_ROW : (uint32_t)(g.K / 8);
     const int ma = MI == 4 ? 0 : m0 & 255, mb = m0 - ma, na = NI == 4 || !bp ? 0 : n0 & 255, nb = n0 - na;
-    a = static_cast<const char*>(g.A) + (size_t)mb * a_row;
-    am = SPARSE ? reinterpret_cast<const char*>(g.Ameta) + (size_t)mb * (g.K / 8) : nullptr;
-    if constexpr (MI < 4) {
-      a += (size_t)ma * a_pitch;
-      if constexpr (SPARSE) am += (size_t)ma * m_pitch;
-    }
-    b = static_cast<const char*>(g.B) + (g.b_rowmap ? (size_t)0 : (size_t)nb * b_row);
+    a = from(static_cast<const char*>(g.A) + (size_t)mb * a_row + (size_t)ma * a_pitch);
+    if constexpr (SPARSE) am = from(reinterpret_cast<const char*>(g.Ameta) + (size_t)mb * (g.K / 8) + (size_t)ma * m_pitch);
+    b = from(static_cast<const char*>(g.B) + (g.b_rowmap ? (size_t)0 : (size_t)nb * b_row));
     a_stage = panel ? 256u * (uint32_t)G::A_ROW : (uint32_t)G::A_ROW;
     m_stage = panel ? 256u * G::META_ROW : (uint32_t)G::META_ROW;
     b_stage = bp ? 256u * (uint32_t)G::B_ROW : (uint32_t)G::B_ROW;
@@ -229,26 +241,28 @@ struct Dma {
       // 64-byte rows, 16 an instruction; 128-byte rows, 8 an instruction, of which the panel form has two 64-byte pieces in
       // consecutive 16 KiB runs
       const int p = G::WIDE ? 8 * (NA * wave + j) + (lane >> 3) : 16 * (NA * wave + j) + (lane >> 2);
-      const int c = G::WIDE ? (lane & 7) ^ swz8(p) : (lane & 3) ^ swz4(p);
-      va[j] = (uint32_t)unperm_m<MI>(p) * a_pitch + (G::WIDE && panel ? (uint32_t)(c >> 2) * (256u * 64u) + (c & 3) * 16 : (uint32_t)c * 16);
+      const int c = G::BIG ? (lane & 3) ^ swz4_big<SPARSE>((p >> 3) & 12) : G::WIDE ? (lane & 7) ^ swz8(p) : (lane & 3) ^ swz4(p);
+      va[j] = (uint32_t)(G::BIG ? p : unperm_m<MI>(p)) * a_pitch + (G::WIDE && panel ? (uint32_t)(c >> 2) * (256u * 64u) + (c & 3) * 16 : (uint32_t)c * 16);
     }
 #pragma unroll
     for (int j = 0; j < NVB; j++) {
       int p = G::B_ROW == 128 ? 8 * (NVB * wave + j) + (lane >> 3) : 16 * (NVB * wave + j) + (lane >> 2);
-      int c = G::B_ROW == 128 ? (lane & 7) ^ swz8(p) : (lane & 3) ^ swz4(p);
-      // panel: with NI = 4 LDS row p is piece p of the block's run
-      if (bp) vb[j] = (uint32_t)(c >> 2) * (256u * 64u) + (uint32_t)(NI == 4 ? p : b_panel_pos(na + unperm_n<NI>(p))) * 64u + (c & 3) * 16;
-      else vb[j] = (g.b_rowmap ? (uint32_t)g.b_rowmap[n0 + unperm_n<NI>(p)] : (uint32_t)unperm_n<NI>(p)) * b_row + c * 16;
+      int c = G::B_ROW == 128 ? (lane & 7) ^ (G::BIG ? swz8_big(big_n_col<SPARSE>(p)) : swz8(p)) : (lane & 3) ^ (G::BIG ? swz4_big<false>(big_n_col<SPARSE>(p)) : swz4(p));
+      const int n = G::BIG ? big_unperm_n<SPARSE>(p) : unperm_n<NI>(p);
+      if (bp) vb[j] = (uint32_t)(c >> 2) * (256u * 64u) + (uint32_t)b_panel_pos(na + n) * 64u + (c & 3) * 16;
+      else vb[j] = (g.b_rowmap ? (uint32_t)g.b_rowmap[n0 + n] : (uint32_t)n) * b_row + c * 16;
     }
     if constexpr (SPARSE) {
       vm[1] = 0;
       if constexpr (F8) {
-        vm[0] = (uint32_t)unperm_m<MI>(64 * (wave % MI) + lane) * m_pitch;      // one row's 16 metadata bytes per lane
+        // one row's 16 metadata bytes per lane (256 x 256: place 8 t + 4 q + v of the KiB is row 32 q + 4 t + v)
+        const int r = G::BIG ? 64 * wave + 32 * ((lane >> 2) & 1) + 4 * (lane >> 3) + (lane & 3) : unperm_m<MI>(64 * (wave % MI) + lane);
+        vm[0] = (uint32_t)r * m_pitch;
       } else {
 #pragma unroll
         for (int j = 0; j < G::NM; j++) {
           int d = 64 * ((G::NM * wave + j) % (2 * MI)) + lane;
-          vm[j] = (uint32_t)unperm_m<MI>(d >> 1) * m_pitch + 4 * (d & 1);
+          vm[j] = (uint32_t)(G::BIG ? d >> 1 : unperm_m<MI>(d >> 1)) * m_pitch + 4 * (d & 1);
         }
       }
     }
@@ -259,32 +273,26 @@ struct Dma {
   __device__ __forceinline__ void issue(int kt, char* buf) const {
     if constexpr ((PROBE & PROBE_NO_DMA) != 0) return;
     if constexpr ((PROBE & PROBE_K_WRAP) != 0) kt &= 7;
-    // The stage's uniform base goes through an opaque scalar register pair, so that the compiler keeps it apart from the
-    // lane's 32-bit offset and picks the instruction's scalar-base + 32-bit-offset form: no 64-bit vector add per
-    // instruction, one address register per instruction instead of two.
+    // Buffer loads: descriptor + lane's 32-bit offset + the stage's scalar offset.  A fetch is the setting of M0 and the load, where the form with a
+    // 64-bit address took three instructions more (a scalar base, a copy of the offset that the selector would accept); beside a
+    // 16 x 16 op (16 cycles) there is room for three in all.
     if constexpr (J < NA) {
-      __builtin_amdgcn_global_load_lds((glb_char*)(sbase(a, kt, a_stage) + voff(va[J])), (lds_char*)(buf + (NA * wave + J) * 1024), 16, 0, 0);
+      load<16>(a, buf + (NA * wave + J) * 1024, va[J], (uint32_t)kt * a_stage);
     } else if constexpr (J < NA + G::NM) {
       constexpr int j = J - NA;
-      if constexpr (F8)
-        __builtin_amdgcn_global_load_lds((glb_char*)(sbase(am, kt, m_stage) + voff(vm[0])), (lds_char*)(buf + G::META_OFF + (wave % MI) * 1024), 16, 0, 0);
-      else
-        __builtin_amdgcn_global_load_lds((glb_char*)(sbase(am, kt, m_stage) + voff(vm[j])), (lds_char*)(buf + G::META_OFF + ((G::NM * wave + j) % (2 * MI)) * 256), 4, 0, 0);
+      if constexpr (F8) load<16>(am, buf + G::META_OFF + (G::BIG ? wave * (1024 + 128) : (wave % MI) * 1024), vm[0], (uint32_t)kt * m_stage);
+      else load<4>(am, buf + G::META_OFF + (G::BIG ? (G::NM * wave + j) * (256 + 32) : ((G::NM * wave + j) % (2 * MI)) * 256), vm[j], (uint32_t)kt * m_stage);
     } else {
       constexpr int j = J - NA - G::NM;
-      __builtin_amdgcn_global_load_lds((glb_char*)(sbase(b, kt, b_stage) + voff(vb[j])), (lds_char*)(buf + G::B_OFF + (NVB * wave + j) * 1024), 16, 0, 0);
+      load<16>(b, buf + G::B_OFF + (NVB * wave + j) * 1024, vb[j], (uint32_t)kt * b_stage);
     }
   }
-  static __device__ __forceinline__ const char* sbase(const char* base, int kt, uint32_t stage) {
-    const char* p = base + (size_t)kt * stage;
-    asm volatile("" : "+s"(p));
-    return p;
-  }
-  // (the offset is made opaque at the point of use too: hoisted out of the loop, its zero-extension would be out of the
-  // instruction selector's sight and the 64-bit form would come back)
-  static __device__ __forceinline__ uint32_t voff(uint32_t o) {
-    asm volatile("" : "+v"(o));
-    return o;
+  // (no bound: every offset lies inside the operand, less than 4 GiB from the block's first row)
+  static __device__ __forceinline__ __amdgpu_buffer_rsrc_t from(const char* p) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(p), 0, -1, 0x00020000); }
+  template <int BYTES>
+  static __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, char* lds, uint32_t off, uint32_t stage) {
+    if constexpr (BYTES == 16) __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_char*)lds, 16, (int)off, (int)stage, 0, 0);
+    else __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_char*)lds, 4, (int)off, (int)stage, 0, 0);
   }
 };
 
@@ -337,14 +345,6 @@ __device__ __forceinline__ i32x8 cat16(const bf16x8& lo, const bf16x8& hi) {
   i32x4 l = __builtin_bit_cast(i32x4, lo), h = __builtin_bit_cast(i32x4, hi);
   return __builtin_shufflevector(l, h, 0, 1, 2, 3, 4, 5, 6, 7);
 }
-// The 256 x 256 tile's form is written as inline assembly with the accumulator tied in place: through the builtin the compiler gives this
-// instruction a destination different from its accumulator input, which with all 256 accumulation registers in
-// use spills accumulators to scratch memory on every op.  Default modifiers = both operands e4m3, unscaled.
-// No software wait states are needed there: consecutive ops use different accumulators, and the same one is only
-// touched again 16 ops later.
-__device__ __forceinline__ void mfma_f8_pinned(const i32x8& a, const i32x8& b, f32x16& c) {
-  asm volatile("v_mfma_f32_32x32x64_f8f6f4 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
-}
 // The smaller tiles have registers to spare, and their accumulators come round again within a few ops: the builtin, whose
 // hazards the compiler handles (formats 0 = e4m3; scale operands 0 = the unscaled instruction).
 __device__ __forceinline__ void mfma_f8(const i32x8& a, const i32x8& b, f32x16& c) {
@@ -354,8 +354,7 @@ template <int M, int PROBE, int MI, int NI>
 __device__ __forceinline__ void mfma_dense_f8(const FragD<MI, NI>& f0, const FragD<MI, NI>& f1, f32x16 (&acc)[MI][NI]) {
   if constexpr ((PROBE & PROBE_NO_MFMA) != 0) return;
   constexpr int mi = M / NI, ni = M % NI;
-  if constexpr (MI * NI == 16) mfma_f8_pinned(cat16(f0.a[mi], f1.a[mi]), cat16(f0.b[ni], f1.b[ni]), acc[mi][ni]);
-  else mfma_f8(cat16(f0.a[mi], f1.a[mi]), cat16(f0.b[ni], f1.b[ni]), acc[mi][ni]);
+  mfma_f8(cat16(f0.a[mi], f1.a[mi]), cat16(f0.b[ni], f1.b[ni]), acc[mi][ni]);
 }
 
 // Sparse: the stage's K window of 64 = four 16-wide windows w.  Instruction S (0,1) gives lane half q the window
@@ -489,30 +488,22 @@ __device__ __forceinline__ void tile_coords(int ntm, int ntn, int pid, int& tm, 
 template <class E, class = void> struct epi_is_staged : std::false_type {};
 template <class E> struct epi_is_staged<E, std::void_t<decltype(E::STAGED)>> : std::true_type {};
 
-// Epilogue concept:  struct E { struct Args {...}; template <int MI, int NI> static __device__ void run(const Args&, acc, m_lane, n_lane); }
+// Epilogue concept:  struct E { struct Args {...}; template <int MI, int NI, class Acc> static __device__ void run(const Args&, Acc& acc, m_lane, n_lane); }
 //   m_lane = global row of acc[0][*][0] for this lane (its 16 MI rows are m_lane + 16*mi + v),
 //   n_lane = global column of acc[*][0][*] (its NI columns are n_lane + ni).
-// One block tile of one GEMM: tile number `pid` of g (workgroup-uniform), LDS ring at `smem`.
-// Pacing of the DMA issue.  The four waves run in step, one per SIMD, and share one address unit that takes about
-// 14 cycles per 16-byte-a-lane DMA instruction; a matrix-op slot is 32 cycles.  When every wave hands over a DMA
-// instruction on every slot, the unit is oversubscribed (4 x 14 > 32), the waves stall in the issue and their matrix
-// pipes idle: measured per K step, the step that carries 14 DMA instructions on consecutive slots takes 1200 cycles
-// instead of 512.  So the instructions ride on every other slot only.  Dense (8 a stage): the even slots of the second
-// K step.  Sparse (13 or 14 a stage): the first half on the even slots of the second K step, the rest on the even slots of
-// the NEXT stage's first K step, still into the buffer that the stage before freed -- one stage buffer is therefore
-// half filled across a stage boundary, which costs nothing because the ring keeps NB - 2 whole stages in flight anyway.
-// dma_on_step1 / dma_on_step0: which DMA instruction rides on slot M of that K step (-1: none).
-template <int NDMA, bool SPREAD, bool PACED>
-constexpr int dma_on_step1(int M) {
-  constexpr int H1 = SPREAD ? NDMA / 2 : NDMA;
-  if (!PACED || 2 * H1 > 16) return M < H1 ? M : -1;
-  return (M % 2 == 0 && M / 2 < H1) ? M / 2 : -1;
-}
-template <int NDMA, bool SPREAD, bool PACED>
-constexpr int dma_on_step0(int M) {
-  constexpr int H1 = SPREAD ? NDMA / 2 : NDMA;
-  if (!SPREAD) return -1;
-  return (M % 2 == 0 && M / 2 < NDMA - H1) ? H1 + M / 2 : -1;
+// Acc: f32x16 [MI][NI], or (256 x 256) float [MI][NI][16]; either is indexed acc[mi][ni][v].
+// run<2, 8> is the 256 x 256 tile (see LaneTile), the others are the smaller tiles' wave tiles.
+template <class G, class Epi, int MI, int NI, class Acc>
+__device__ __forceinline__ void run_epilogue(const typename Epi::Args& ea, Acc& acc, int m_lane, int n_lane, char* smem, int wave) {
+  if constexpr (epi_is_staged<Epi>::value) {
+    // the epilogue stages its stores through the operand ring: every wave must have read its last fragments first
+    constexpr int WAVE_BYTES = (G::BN / 2) * G::BM;   // the wave's part of the result in bf16
+    static_assert(G::LDS_TOTAL >= GEMM_THREADS / 64 * WAVE_BYTES, "a staging area per wave");
+    __builtin_amdgcn_s_barrier();
+    Epi::template run<MI, NI>(ea, acc, m_lane, n_lane, smem + wave * WAVE_BYTES);
+  } else {
+    Epi::template run<MI, NI>(ea, acc, m_lane, n_lane);
+  }
 }
 
 // The smaller tiles (several workgroups a CU, whose issue gaps fill each other) spread N memory instructions over the slots of a K
@@ -523,14 +514,12 @@ __device__ __forceinline__ void ride(F&& f) {
   static_for<hi - lo>([&](auto i) { f(std::integral_constant<int, lo + decltype(i)::value>{}); });
 }
 
-template <bool SPARSE, class Epi, bool F8 = false, int PROBE = 0, int MI = 4, int NI = 4>
-__device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi::Args& ea, char* smem, int pid, int pid_end = 0, int pid_step = 0) {
+template <bool SPARSE, class Epi, bool F8, int MI, int NI>
+__device__ __forceinline__ void gemm_tile_small(const GemmArgs& g, const typename Epi::Args& ea, char* smem, int pid) {
   using G = Geo<SPARSE, F8, MI, NI>;
-  constexpr bool BIG = MI * NI == 16;       // the 256 x 256 tile: accumulators pinned, memory instructions paced slot by slot
   constexpr int NMF = MI * NI;              // matrix ops (slots) per K step
-  constexpr int FRAG_SLOTS = BIG ? 16 : (NMF + 1) / 2;   // slots of a K step that carry fragment reads (BIG: one a slot from the first on)
-  constexpr int NB = G::NB, NDMA = G::NDMA - ((SPARSE && (PROBE & PROBE_FILL_LESS)) ? 3 : 0);
-  constexpr bool PERSIST = (PROBE & PROBE_PERSIST) != 0;
+  constexpr int FRAG_SLOTS = (NMF + 1) / 2; // slots of a K step that carry fragment reads
+  constexpr int NB = G::NB, NDMA = G::NDMA, PROBE = 0;
 
   int tid = threadIdx.x;
   int lane = tid & 63, wave = tid >> 6;
@@ -558,9 +547,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
   // prologue: stages 0 .. min(NB, nk)-1 into their ring slots; wait for stage 0 only
   const int npro = nk < NB ? nk : NB;
   for (int s = 0; s < npro; s++) static_for<NDMA>([&](auto J) { dma.template issue<J>(s, smem + s * G::STAGE); });
-  bool first = true;
-
-  for (;;) {   // one pass per tile (PERSIST: several tiles per workgroup)
   f32x16 acc[MI][NI];
 #pragma unroll
   for (int i = 0; i < MI; i++)
@@ -568,18 +554,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
     for (int j = 0; j < NI; j++)
 #pragma unroll
       for (int v = 0; v < 16; v++) acc[i][j][v] = 0.f;
-  // Pin the accumulators to the accumulation register file: an empty asm with an AGPR constraint gives their
-  // live ranges the AGPR class, so the 256 arch VGPRs stay free for fragments and addresses.
-  if constexpr (BIG) {
-#pragma unroll
-    for (int i = 0; i < MI; i++)
-#pragma unroll
-      for (int j = 0; j < NI; j++) asm volatile("" : "+a"(acc[i][j]));
-  }
 
-  // a later tile's prologue went out before the previous epilogue, whose stores count in the same counter and complete in no
-  // fixed order with the loads: wait for all of it
-  if (first && npro == NB) wait_vmcnt<(NB - 1) * NDMA>(); else wait_vmcnt<0>();
+  if (npro == NB) wait_vmcnt<(NB - 1) * NDMA>(); else wait_vmcnt<0>();
   __builtin_amdgcn_s_barrier();
   FFN24_FENCE();
 
@@ -647,23 +623,17 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
     IdxWords<F8> idx[MI];
     static_for<MI>([&](auto I) { load_idx_sparse1<G, F8, I>(smem, L, idx); });
     static_for<NF>([&](auto I) { load_frag_sparse1<G, 0, I, PROBE>(smem, L, f0); });
-    // sparse: spread the DMA of a stage over two K steps (see dma_on_step1) when there is a steady state at all
-    constexpr bool PACED = BIG && (PROBE & PROBE_UNPACED) == 0;
-    auto stage = [&](int kt, char* cur, char* nxt, char* prv, auto mode, auto spread) {
+    auto stage = [&](int kt, char* cur, char* nxt, auto mode) {
       constexpr int MODE = decltype(mode)::value;
-      constexpr bool SPREAD0 = decltype(spread)::value != 0;   // this stage's first K step carries the rest of stage kt-1+NB
       IdxWords<F8> idx_n[MI] = {};
       FFN24_FENCE();
       static_for<NMF>([&](auto M) {
         mfma_sparse1<F8, 0, M, PROBE>(f0, idx, acc);
-        constexpr int J0 = dma_on_step0<NDMA, PACED, PACED>(M);
-        if constexpr (SPREAD0 && J0 >= 0) dma.template issue<(J0 >= 0 ? J0 : 0)>(kt - 1 + NB, prv);
         ride<NF, FRAG_SLOTS, M>([&](auto I) { load_frag_sparse1<G, 1, I, PROBE>(cur, L, f1); });
         FFN24_FENCE();
       });
       if constexpr (MODE != 2) {
-        // stage kt+1 must have landed; behind it in issue order are the NB - 2 stages kt+2 .. kt+NB-1, all of them whole
-        // (the rest of stage kt-1+NB went out just above)
+        // stage kt+1 must have landed; behind it in issue order are the NB - 2 stages kt+2 .. kt+NB-1
         if constexpr (MODE == 0) wait_vmcnt<(NB - 2) * NDMA>(); else wait_vmcnt<0>();
         wait_lgkmcnt0();
         __builtin_amdgcn_s_barrier();
@@ -671,12 +641,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
       FFN24_FENCE();
       static_for<NMF>([&](auto M) {
         mfma_sparse1<F8, 1, M, PROBE>(f1, idx, acc);
-        if constexpr (BIG) {
-          constexpr int J1 = dma_on_step1<NDMA, PACED, PACED>(M);
-          if constexpr (MODE == 0 && J1 >= 0) dma.template issue<(J1 >= 0 ? J1 : 0)>(kt + NB, cur);
-        } else {
-          if constexpr (MODE == 0) ride<NDMA, NMF, M>([&](auto J) { dma.template issue<J>(kt + NB, cur); });
-        }
+        if constexpr (MODE == 0) ride<NDMA, NMF, M>([&](auto J) { dma.template issue<J>(kt + NB, cur); });
         if constexpr (MODE != 2) {
           if constexpr (M < MI) load_idx_sparse1<G, F8, M>(nxt, L, idx_n);
           ride<NF, FRAG_SLOTS, M>([&](auto I) { load_frag_sparse1<G, 0, I, PROBE>(nxt, L, f0); });
@@ -687,24 +652,15 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
       for (int i = 0; i < MI; i++) idx[i] = idx_n[i];
     };
     int slot = 0;
-    auto advance = [&](int kt, auto mode, auto spread) {
+    auto advance = [&](int kt, auto mode) {
       int ns = slot + 1 == NB ? 0 : slot + 1;
-      int ps = slot == 0 ? NB - 1 : slot - 1;
-      stage(kt, smem + slot * G::STAGE, smem + ns * G::STAGE, smem + ps * G::STAGE, mode, spread);
+      stage(kt, smem + slot * G::STAGE, smem + ns * G::STAGE, mode);
       slot = ns;
     };
-    using I0 = std::integral_constant<int, 0>; using I1 = std::integral_constant<int, 1>; using I2 = std::integral_constant<int, 2>;
-    using SP = std::integral_constant<int, PACED ? 1 : 0>;
     int kt = 0;
-    if (nk > NB) {
-      // stage 0 issues the first half of stage NB; stages 1 .. nk-NB each issue the rest of what the stage before began,
-      // and all but the last of them the first half of their own
-      advance(kt, I0{}, I0{}); kt++;
-      for (; kt < nk - NB; kt++) advance(kt, I0{}, SP{});
-      if constexpr (PACED) { advance(kt, I1{}, I1{}); kt++; }
-    }
-    for (; kt < nk - 1; kt++) advance(kt, I1{}, I0{});
-    advance(kt, I2{}, I0{});
+    for (; kt < nk - NB; kt++) advance(kt, std::integral_constant<int, 0>{});
+    for (; kt < nk - 1; kt++) advance(kt, std::integral_constant<int, 1>{});
+    advance(kt, std::integral_constant<int, 2>{});
   } else if constexpr (F8) {
     // Dense fp8: a stage is ONE K step of 16 matrix ops (64 cycles each).  The fragments of the whole next stage and
     // the DMA of the stage that reuses this stage's buffer (its fragments are already in registers) ride on them;
@@ -718,7 +674,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
       FFN24_FENCE();
       static_for<NMF>([&](auto M) {
         mfma_dense_f8<M, PROBE>(fr[P][0], fr[P][1], acc);
-        if constexpr (MODE == 0) ride<NDMA, (BIG ? NDMA : NMF), M>([&](auto J) { dma.template issue<J>(kt + NB, cur); });
+        if constexpr (MODE == 0) ride<NDMA, NMF, M>([&](auto J) { dma.template issue<J>(kt + NB, cur); });
         if constexpr (MODE != 2) ride<2 * NF, NMF, M>([&](auto I) {
           if constexpr (I < NF) load_frag_dense1<G, 0, I, PROBE>(nxt, L, fr[P ^ 1][0]);
           else load_frag_dense1<G, 1, I - NF, PROBE>(nxt, L, fr[P ^ 1][1]);
@@ -740,7 +696,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
     FFN24_FENCE();
     // The two fragment sets alternate by stage parity.  The stage count is even (K is a multiple of 128 here), so
     // the stages are walked in pairs, straight-line: a parity branch inside the loop makes the compiler shuffle the
-    // 256 accumulation registers between its two arms.
+    // accumulation registers between its two arms.
     int slot = 0;
     auto advance = [&](int kt, auto par, auto mode) {
       int ns = slot + 1 == NB ? 0 : slot + 1;
@@ -775,12 +731,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
       FFN24_FENCE();
       static_for<NMF>([&](auto M) {
         mfma_dense1<M, PROBE>(f1, acc);
-        if constexpr (BIG) {
-          constexpr int J1 = dma_on_step1<NDMA, false, (PROBE & PROBE_UNPACED) == 0>(M);
-          if constexpr (MODE == 0 && J1 >= 0) dma.template issue<(J1 >= 0 ? J1 : 0)>(kt + NB, cur);
-        } else {
-          if constexpr (MODE == 0) ride<NDMA, NMF, M>([&](auto J) { dma.template issue<J>(kt + NB, cur); });
-        }
+        if constexpr (MODE == 0) ride<NDMA, NMF, M>([&](auto J) { dma.template issue<J>(kt + NB, cur); });
         if constexpr (MODE != 2) ride<NF, FRAG_SLOTS, M>([&](auto I) { load_frag_dense1<G, 0, I, PROBE>(nxt, L, f0); });
         FFN24_FENCE();
       });
@@ -797,19 +748,213 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
     advance(kt, std::integral_constant<int, 2>{});
   }
 
-  if constexpr (F8 && !SPARSE && BIG) {
-    // the dense fp8 ops are inline assembly, which the compiler's hazard handling does not see: let the last ones
-    // (16 passes each) drain before the epilogue reads the accumulators
-    asm volatile("s_nop 15\n s_nop 15\n s_nop 15\n s_nop 15\n s_nop 15" ::: "memory");
-    // and tie the accumulators to a point after the wait (volatile statements keep their order), so that no read of
-    // them can be scheduled above it
-#pragma unroll
-    for (int i = 0; i < 4; i++)
-#pragma unroll
-      for (int j = 0; j < 4; j++) asm volatile("" : "+a"(acc[i][j]));
-  }
   int m_lane = m0 + L.wy * (32 * MI) + (16 * MI) * L.h;
   int n_lane = n0 + L.wx * (32 * NI) + NI * L.rho;
+  run_epilogue<G, Epi, MI, NI>(ea, acc, m_lane, n_lane, smem, wave);
+}
+
+// The 256 x 256 block tile: four waves of 128 x 128, one a SIMD, 256 accumulators a lane pinned to the AGPR file.  Its matrix ops are the
+// 16 x 16 ones: under matrix load the chip is bound by its power limit, and a 16 x 16 op moves fewer accumulator bytes a flop through the
+// register file than a 32 x 32 one.  Register-resident loops at the power limit, N(0, 1) operands, 32 x 32 -> 16 x 16 (PFLOP/s dense equivalent):
+// dense bf16 1.83 -> 2.09, 2:4 bf16 3.37 -> 3.55, dense fp8 4.11 -> 4.47, 2:4 fp8 6.49 -> 6.89.  The whole loop, pseudo-random operands, M 16384
+// N 4096: dense bf16 K 16384 1.59 -> 1.53 ms, K 4096 0.495 -> 0.467, 2:4 1.02 -> 0.98, 0.262 -> 0.256; the steps of the block at T = F = 16384, D 4096
+// 7.45 -> 7.09 ms, fp8 forward at T = D = 8192, F 32768 2.48 -> 2.33 ms.  What bounds it is energy: the clock settles 15 % higher than with the
+// 32 x 32 ops (1.75 against 1.52 GHz) and a stage takes 10 % more cycles (1290 against 1180 of 1024), and whatever saves cycles alone (B fragments read two
+// at a time or spread, DMA on every 64 or 128 cycles, five stages, a serpentine over the ops) lowers the clock again: all within 1 %.
+// With the k of a stage given to the lane quarters as below an op adds up what two 32 x 32 ops add up, in the same order: the results are the
+// same bit for bit (all four types), so the smaller tiles, which are not at the power limit, keep theirs.
+//   lane l, quarter q = l / 16, c = l % 16: A row / B column c of a 16-row tile; accumulators = rows 4 q .. 4 q + 3, column c.
+//   dense bf16 16x16x32: k 8 q .. + 7 of the stage's 32 (16-byte chunk q of the row).
+//   dense fp8 16x16x128: chunk q of two consecutive stages (a K step is two stages).
+//   2:4 16x16x64 (fp8 16x16x128): the stored values of window 0, 2, 1, 3 of the stage's four for q = 0 .. 3, with their metadata;
+//     B: chunks c0 = (q & 1) + 4 (q / 2) and c0 + 2 of the stage row's eight.
+// A K step is 64 ops in two halves of 32, one for each half of the columns, the ops of a row of four next to each other:
+//   half 0: the other half's B fragments of this step are read;
+//   wait for the next stage's DMA, one workgroup barrier: this stage's buffer is free;
+//   half 1: the next step's first B fragments take the place of the ones half 0 used up, its A fragments follow row by row behind the
+//           last op that uses theirs, and the DMA of the stage that reuses the buffer rides along.
+// So no fragment is held twice, and every read has at least 28 ops to arrive.
+template <bool SPARSE, bool F8>
+struct BigFrags {
+  static constexpr bool PAIR = F8 && !SPARSE;                 // 32 bytes of A a lane
+  bf16x8 a[8][PAIR ? 2 : 1], b[2][4][SPARSE || PAIR ? 2 : 1];
+  uint32_t idx[SPARSE ? 8 : 1];
+};
+struct BigLane { int a, b, m; };   // byte offsets of the lane's first fragment of A, of B and of its metadata inside a stage
+
+// The ops are inline assembly with the accumulator tied in place in the AGPR file.  Through the builtins the compiler, with all 256 of those
+// registers in use, copies accumulators to the other file and back round the ops of the loops' tails, or spills some of them.  What
+// its hazard handling then does not see: the same accumulator comes round again 64 ops later, the operands come from LDS reads (which it
+// does wait for; no vector instruction writes one within two instructions of its op, tests/test_kernel_hazards.py), and the end of the
+// main loop waits for the last ops.  Default modifiers of the f8f6f4 op: both operands e4m3, unscaled.
+__device__ __forceinline__ void op16_bf16(const bf16x8& a, const bf16x8& b, f32x4& c) { asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b)); }
+__device__ __forceinline__ void op16_f8(const i32x8& a, const i32x8& b, f32x4& c) { asm volatile("v_mfma_f32_16x16x128_f8f6f4 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b)); }
+__device__ __forceinline__ void op16_sp_bf16(const bf16x8& a, const i32x8& b, uint32_t idx, f32x4& c) { asm volatile("v_smfmac_f32_16x16x64_bf16 %0, %1, %2, %3" : "+a"(c) : "v"(a), "v"(b), "v"(idx)); }
+__device__ __forceinline__ void op16_sp_f8(const bf16x8& a, const i32x8& b, uint32_t idx, f32x4& c) { asm volatile("v_smfmac_f32_16x16x128_fp8_fp8 %0, %1, %2, %3" : "+a"(c) : "v"(a), "v"(b), "v"(idx)); }
+template <bool SPARSE, bool F8, int H, int M>
+__device__ __forceinline__ void big_op(const BigFrags<SPARSE, F8>& f, f32x4 (&acc)[8][8]) {
+  constexpr int mi = M / 4, n = M % 4, ni = 4 * H + n;
+  if constexpr (!SPARSE && !F8) op16_bf16(f.a[mi][0], f.b[H][n][0], acc[mi][ni]);
+  else if constexpr (!SPARSE) op16_f8(cat16(f.a[mi][0], f.a[mi][1]), cat16(f.b[H][n][0], f.b[H][n][1]), acc[mi][ni]);
+  else if constexpr (!F8) op16_sp_bf16(f.a[mi][0], cat16(f.b[H][n][0], f.b[H][n][1]), f.idx[mi], acc[mi][ni]);
+  else op16_sp_f8(f.a[mi][0], cat16(f.b[H][n][0], f.b[H][n][1]), f.idx[mi], acc[mi][ni]);
+}
+// fragment reads of A tile T (with its metadata) and of read I of B half H; buf: the stage's buffer, buf2: the second stage's (dense fp8)
+template <class G, bool SPARSE, bool F8, int T>
+__device__ __forceinline__ void big_read_a(const char* buf, const char* buf2, const BigLane& L, BigFrags<SPARSE, F8>& f) {
+  f.a[T][0] = *reinterpret_cast<const bf16x8*>(buf + L.a + T * (4 * 64));
+  if constexpr (F8 && !SPARSE) f.a[T][1] = *reinterpret_cast<const bf16x8*>(buf2 + L.a + T * (4 * 64));
+  if constexpr (SPARSE && F8) f.idx[T] = *reinterpret_cast<const uint32_t*>(buf + L.m + T * (8 * 16));
+  if constexpr (SPARSE && !F8) f.idx[T] = *reinterpret_cast<const uint16_t*>(buf + L.m + T * (4 * 8));
+}
+template <class G, bool SPARSE, bool F8, int H, int I>
+__device__ __forceinline__ void big_read_b(const char* buf, const char* buf2, const BigLane& L, BigFrags<SPARSE, F8>& f) {
+  // N-tile 4 H + n
+  if constexpr (SPARSE) f.b[H][I / 2][I % 2] = *reinterpret_cast<const bf16x8*>(buf + (L.b ^ ((I % 2) << 5)) + (32 * (I / 2) + 4 * H) * 128);
+  else if constexpr (F8) f.b[H][I / 2][I % 2] = *reinterpret_cast<const bf16x8*>((I % 2 ? buf2 : buf) + L.b + (32 * (I / 2) + 8 * H) * 64);
+  else f.b[H][I][0] = *reinterpret_cast<const bf16x8*>(buf + L.b + (32 * I + 8 * H) * 64);
+}
+
+// Pacing of the DMA issue.  The four waves run in step, one per SIMD, and share one address unit that takes about
+// 14 cycles per 16-byte-a-lane DMA instruction; an op takes 16 (dense fp8: 32) cycles.  When every wave hands over a DMA
+// instruction on every 32 cycles, the unit is oversubscribed (4 x 14 > 32), the waves stall in the issue and their matrix
+// pipes idle: measured per 512 cycles of matrix ops, the ones that carried 14 DMA instructions took 1200 cycles.  So they are spread over
+// the whole step from its barrier to the next one: half of them in half 1, the rest in half 0 of the NEXT step, still into the buffer that the stage
+// before freed -- one stage buffer is therefore half filled across a stage boundary, which costs nothing because the ring keeps NB - 2 whole
+// stages in flight anyway.  One instruction on every 64 cycles (2:4, 13 or 14 a stage) or 128 (dense).  Fragment reads take the slots between.
+// which fragment read of B rides on op M of a half: two on every four ops
+constexpr int big_read_slot(int M) { return M % 4 == 1 ? M / 4 * 2 : M % 4 == 2 ? M / 4 * 2 + 1 : -1; }
+template <int SLOTS, int N> constexpr int paced(int M) { return M % SLOTS == 0 && M / SLOTS < N ? M / SLOTS : -1; }
+
+template <bool SPARSE, class Epi, bool F8, int PROBE>
+__device__ __forceinline__ void gemm_tile_big(const GemmArgs& g, const typename Epi::Args& ea, char* smem, int pid, int pid_end, int pid_step) {
+  using G = Geo<SPARSE, F8, 4, 4>;
+  constexpr int NB = G::NB, NDMA = G::NDMA - ((SPARSE && (PROBE & PROBE_FILL_LESS)) ? 3 : 0);
+  constexpr bool PERSIST = (PROBE & PROBE_PERSIST) != 0, FRAG = (PROBE & PROBE_NO_FRAG) == 0, MATH = (PROBE & PROBE_NO_MFMA) == 0;
+  constexpr int PACE = (PROBE & PROBE_UNPACED) ? 1 : F8 || SPARSE ? 4 : 8;
+  using I0 = std::integral_constant<int, 0>; using I1 = std::integral_constant<int, 1>;
+
+  const int tid = threadIdx.x, lane = tid & 63, q = lane >> 4, c = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wy = wave >> 1, wx = wave & 1;
+  int tm, tn;
+  tile_coords<PROBE>(g.M / G::BM, g.N / G::BN, pid, tm, tn);
+  int m0 = tm * G::BM, n0 = tn * G::BN;
+  const int win = SPARSE ? ((q & 1) << 1) | (q >> 1) : q;      // chunk of A
+  BigLane L;
+  // lane c of a quarter holds row 32 (c / 4) + c % 4 of A's first tile
+  L.a = (wy * 128 + 32 * (c >> 2) + (c & 3)) * 64 + ((win ^ swz4_big<SPARSE>(c)) << 4);
+  L.b = SPARSE ? G::B_OFF + (wx * 128 + 8 * (c >> 2) + (c & 3)) * 128 + ((((q & 1) | ((q >> 1) << 2)) ^ swz8_big(c)) << 4)
+               : G::B_OFF + (wx * 128 + 16 * (c >> 3) + (c & 7)) * 64 + ((q ^ swz4_big<false>(c)) << 4);
+  L.m = G::META_OFF + (F8 ? (2 * wy + (c >> 3)) * (1024 + 128) + ((c >> 2) & 1) * 64 + (c & 3) * 16 + 4 * win : (4 * wy + (c >> 2)) * (256 + 32) + (c & 3) * 8 + 2 * win);
+
+  Dma<SPARSE, F8, PROBE, 4, 4> dma;
+  dma.init(g, m0, n0, tid);
+  const int nk = g.K / G::BK;
+  constexpr int STEP = F8 && !SPARSE ? 2 : 1;                  // stages a K step
+  constexpr int H1 = NDMA * STEP / 2;                          // DMA instructions of a full step in half 1
+  constexpr int AHEAD = NB - 1;                                // stages that are asked for before the first step ...
+  constexpr int PART = STEP == 1 ? H1 : 0;                     // ... and instructions of the next one; the first step brings the rest of it
+  const bool ring_full = nk > AHEAD;
+  auto prologue = [&]() {
+    const int n = ring_full ? AHEAD : nk;
+    for (int s = 0; s < n; s++) static_for<NDMA>([&](auto J) { dma.template issue<J>(s, smem + s * G::STAGE); });
+    if (PART > 0 && ring_full) static_for<PART>([&](auto J) { dma.template issue<J>(AHEAD, smem + AHEAD * G::STAGE); });
+  };
+  prologue();
+  bool first = true;
+
+  for (;;) {   // one pass per tile (PERSIST: several tiles per workgroup)
+  f32x4 acc[8][8];
+#pragma unroll
+  for (int i = 0; i < 8; i++)
+#pragma unroll
+    for (int j = 0; j < 8; j++) {
+      acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      // Pin the accumulators to the accumulation register file: an empty asm with an AGPR constraint gives their
+      // live ranges the AGPR class, so the 256 arch VGPRs stay free for fragments and addresses.
+      asm volatile("" : "+a"(acc[i][j]));
+    }
+  BigFrags<SPARSE, F8> f;
+  constexpr int NRB = SPARSE || F8 ? 8 : 4;                    // reads of half of B
+
+  // the first step's stages have landed.  (A later tile's prologue went out before the previous epilogue, whose stores count in the same counter and
+  // complete in no fixed order with the loads: wait for all of it.)
+  if (first && ring_full) wait_vmcnt<(AHEAD - STEP) * NDMA + PART>(); else wait_vmcnt<0>();
+  __builtin_amdgcn_s_barrier();
+  FFN24_FENCE();
+  if constexpr (FRAG) {
+    static_for<8>([&](auto T) { big_read_a<G, SPARSE, F8, T>(smem, smem + G::STAGE, L, f); });
+    static_for<NRB>([&](auto I) { big_read_b<G, SPARSE, F8, 0, I>(smem, smem + G::STAGE, L, f); });
+  }
+
+  int slot = 0;
+  auto ring = [&](int s) { return smem + (s >= NB ? s - NB : s) * G::STAGE; };
+  // The step that starts with stage kt.  REST: its first half asks for what is left of stage kt - 1 + NB (dense fp8: for stage kt + 4); ISSUE: its second half
+  // begins stage kt + NB; LEFT: DMA instructions behind the next step's that may be in flight at the barrier (-1: the last step,
+  // no barrier and nothing to read)
+  auto step = [&](int kt, auto rest, auto issue, auto left) {
+    constexpr bool REST = decltype(rest)::value != 0, ISSUE = decltype(issue)::value != 0;
+    constexpr int LEFT = decltype(left)::value;
+    char *cur = ring(slot), *cur2 = ring(slot + 1), *nxt = ring(slot + STEP), *nxt2 = ring(slot + STEP + 1), *prv = ring(slot + NB - 1);
+    FFN24_FENCE();
+    static_for<32>([&](auto M) {
+      if constexpr (MATH) big_op<SPARSE, F8, 0, M>(f, acc);
+      constexpr int J = paced<PACE, NDMA - PART>(M);
+      if constexpr (REST && J >= 0) dma.template issue<PART + (J >= 0 ? J : 0)>(kt - 1 + NB, prv);
+      constexpr int I = big_read_slot(M);
+      if constexpr (FRAG && I >= 0 && I < NRB) big_read_b<G, SPARSE, F8, 1, (I >= 0 ? I : 0)>(cur, cur2, L, f);
+      FFN24_FENCE();
+    });
+    if constexpr (LEFT >= 0) {
+      wait_vmcnt<(LEFT > 0 ? LEFT : 0)>();
+      wait_lgkmcnt0();
+      __builtin_amdgcn_s_barrier();
+    }
+    FFN24_FENCE();
+    static_for<32>([&](auto M) {
+      if constexpr (MATH) big_op<SPARSE, F8, 1, M>(f, acc);
+      constexpr int J = paced<PACE, H1>(M);
+      if constexpr (ISSUE && J >= 0) dma.template issue<(J >= 0 ? J : 0)>(kt + NB, cur);
+      if constexpr (FRAG && LEFT >= 0) {
+        constexpr int I = big_read_slot(M);
+        if constexpr (I >= 0 && I < NRB) big_read_b<G, SPARSE, F8, 0, (I >= 0 ? I : 0)>(nxt, nxt2, L, f);
+        if constexpr (M % 4 == 3) big_read_a<G, SPARSE, F8, M / 4>(nxt, nxt2, L, f);
+      }
+      FFN24_FENCE();
+    });
+    slot += STEP;
+    if (slot >= NB) slot -= NB;
+  };
+  using None = std::integral_constant<int, -1>;
+  using Steady = std::integral_constant<int, STEP == 1 ? (NB - 2) * NDMA : NDMA>;
+  int kt = 0;
+  if (ring_full) {
+    // (dense fp8: the number of stages is even, K is a multiple of 128, and stages kt + 4 and kt + 5 are there or not together)
+    for (; kt < nk - NB; kt += STEP) step(kt, I1{}, I1{}, Steady{});
+    if constexpr (STEP == 1) { step(kt, I1{}, I0{}, I0{}); kt++; }
+  }
+  for (; kt < nk - STEP; kt += STEP) step(kt, I0{}, I0{}, I0{});
+  step(kt, I0{}, I0{}, None{});
+
+  // let the last ops (8 passes each at most) drain before the epilogue reads the accumulators
+  asm volatile("s_nop 15\n s_nop 15\n s_nop 15" ::: "memory");
+  // and tie the accumulators to a point after the wait (volatile statements keep their order), so that no read of
+  // them can be scheduled above it
+#pragma unroll
+  for (int i = 0; i < 8; i++)
+#pragma unroll
+    for (int j = 0; j < 8; j++) asm volatile("" : "+a"(acc[i][j]));
+  // 16 rows of a lane are four M-tiles' registers.  (Single floats: as vectors of 16 they would each take 16 registers of the other file from the first
+  // element read to the last one used, all 256, and spill what else an epilogue holds.)
+  float out[2][8][16];
+#pragma unroll
+  for (int i = 0; i < 2; i++)
+#pragma unroll
+    for (int j = 0; j < 8; j++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) out[i][j][v] = acc[4 * i + v / 4][j][v % 4];
+  const int at = fresh_lane();
+  const int m_lane = m0 + wy * 128 + 32 * (at >> 4), n_lane = n0 + wx * 128 + 8 * (at & 15);
   if constexpr (PERSIST) {
     pid += pid_step;
     const bool more = pid < pid_end;
@@ -817,27 +962,25 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
       // every wave has read its last fragments: the ring is free for the next tile's first stages, which then land while
       // the epilogue runs
       __builtin_amdgcn_s_barrier();
-      tile_coords<PROBE, MI == 2 * NI>(g.M / G::BM, g.N / G::BN, pid, tm, tn);
+      tile_coords<PROBE>(g.M / G::BM, g.N / G::BN, pid, tm, tn);
       m0 = tm * G::BM; n0 = tn * G::BN;
       dma.init(g, m0, n0, tid);
-      for (int s = 0; s < npro; s++) static_for<NDMA>([&](auto J) { dma.template issue<J>(s, smem + s * G::STAGE); });
+      prologue();
     }
-    Epi::template run<MI, NI>(ea, acc, m_lane, n_lane);
+    Epi::template run<2, 8>(ea, out, m_lane, n_lane);
     if (!more) break;
     first = false;
   } else {
-    if constexpr (epi_is_staged<Epi>::value) {
-      // the epilogue stages its stores through the operand ring: every wave must have read its last fragments first
-      constexpr int WAVE_BYTES = (32 * NI) * (64 * MI);   // the wave's part of the result in bf16
-      static_assert(G::LDS_TOTAL >= GEMM_THREADS / 64 * WAVE_BYTES, "a staging area per wave");
-      __builtin_amdgcn_s_barrier();
-      Epi::template run<MI, NI>(ea, acc, m_lane, n_lane, smem + wave * WAVE_BYTES);
-    } else {
-      Epi::template run<MI, NI>(ea, acc, m_lane, n_lane);
-    }
+    run_epilogue<G, Epi, 2, 8>(ea, out, m_lane, n_lane, smem, wave);
     break;
   }
   }   // tiles
+}
+
+template <bool SPARSE, class Epi, bool F8 = false, int PROBE = 0, int MI = 4, int NI = 4>
+__device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi::Args& ea, char* smem, int pid, int pid_end = 0, int pid_step = 0) {
+  if constexpr (MI * NI == 16) gemm_tile_big<SPARSE, Epi, F8, PROBE>(g, ea, smem, pid, pid_end, pid_step);
+  else gemm_tile_small<SPARSE, Epi, F8, MI, NI>(g, ea, smem, pid);
 }
 
 // Clock sample of a workgroup (profiling only): ticks of the shader clock and of the constant 100 MHz clock between its
@@ -845,13 +988,15 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi:
 // under matrix load).
 struct ClkSample {
   unsigned long long t0, r0;
+  int wave;
   __device__ __forceinline__ void begin(const GemmArgs& g) {
+    wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     if (g.clk) { t0 = __builtin_amdgcn_s_memtime(); r0 = __builtin_amdgcn_s_memrealtime(); }
   }
   __device__ __forceinline__ void end(const GemmArgs& g) {
     if (g.clk && blockIdx.x < CLK_SLOTS) {
       unsigned long long t1 = __builtin_amdgcn_s_memtime(), r1 = __builtin_amdgcn_s_memrealtime();
-      if (threadIdx.x == 0) { g.clk[2 * blockIdx.x] = t1 - t0; g.clk[2 * blockIdx.x + 1] = r1 - r0; }
+      if (wave == 0 && fresh_lane() == 0) { g.clk[2 * blockIdx.x] = t1 - t0; g.clk[2 * blockIdx.x + 1] = r1 - r0; }
     }
   }
 };
@@ -903,8 +1048,8 @@ template <class EpiA, class EpiB>
 struct EpiDuo {
   static constexpr bool STAGED = true;
   struct Args { typename EpiA::Args a; typename EpiB::Args b; bool second; };
-  template <int MI, int NI>
-  static __device__ __forceinline__ void run(const Args& e, f32x16 (&acc)[MI][NI], int m_lane, int n_lane, char* wbuf) {
+  template <int MI, int NI, class Acc>
+  static __device__ __forceinline__ void run(const Args& e, Acc& acc, int m_lane, int n_lane, char* wbuf) {
     if (e.second) EpiB::template run<MI, NI>(e.b, acc, m_lane, n_lane, wbuf);
     else EpiA::template run<MI, NI>(e.a, acc, m_lane, n_lane);
   }

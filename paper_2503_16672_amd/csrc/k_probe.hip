@@ -22,63 +22,58 @@ struct DevBuf {
 
 __device__ __forceinline__ uint32_t xorshift(uint32_t& x) { x ^= x << 13; x ^= x >> 17; x ^= x << 5; return x; }
 
-// KIND 0 dense bf16 32x32x16, 1 sparse bf16 32x32x32, 2 dense fp8 32x32x64, 3 sparse fp8 32x32x64.
-// 16 independent accumulators per wave, exactly the GEMM core's register tile; operands are pseudo-random finite values
-// (the clock the chip settles at under matrix load depends on how much the operand bits toggle).
+// KIND 0 dense bf16 16x16x32, 1 sparse bf16 16x16x64, 2 dense fp8 16x16x128, 3 sparse fp8 16x16x128.
+// 64 independent accumulators of 4 registers per wave, exactly the GEMM core's register tile (256 x 256), with its ops; operands are pseudo-random
+// finite values (the clock the chip settles at under matrix load depends on how much the operand bits toggle).
 template <int KIND>
 __global__ void __launch_bounds__(256) mfma_rate_kernel(int iters, unsigned long long* out, float* sink, uint32_t seed) {
+  constexpr bool SPARSE = (KIND & 1) != 0, F8 = KIND >= 2;
   uint32_t x = (threadIdx.x + blockIdx.x * 256u) * 2654435761u + seed;
-  bf16x8 a[4], b[4], b2[4];
-  i32x8 a8[4], b8[4];
-  int idx[4];
-  for (int i = 0; i < 4; i++) {
-    for (int j = 0; j < 4; j++) {
-      // bf16 pairs in (-2, 2) without zeros, infinities or NaNs; fp8 bytes with the NaN codes masked out
-      reinterpret_cast<uint32_t*>(&a[i])[j] = 0x3C003C00u | (xorshift(x) & 0x83FF83FFu);
-      reinterpret_cast<uint32_t*>(&b[i])[j] = 0x3C003C00u | (xorshift(x) & 0x83FF83FFu);
-      reinterpret_cast<uint32_t*>(&b2[i])[j] = 0x3C003C00u | (xorshift(x) & 0x83FF83FFu);
-    }
-    for (int j = 0; j < 8; j++) { a8[i][j] = (int)(xorshift(x) & 0x77777777u); b8[i][j] = (int)(xorshift(x) & 0x77777777u); }
-    const uint32_t codes[6] = {0x4, 0x8, 0xC, 0x9, 0xD, 0xE};   // the six legal 2:4 index nibbles
+  // bf16 pairs in (-2, 2) without zeros, infinities or NaNs; fp8 bytes with the NaN codes masked out
+  auto operand = [&](bf16x8& v) {
+#pragma unroll
+    for (int j = 0; j < 4; j++) reinterpret_cast<uint32_t*>(&v)[j] = F8 ? xorshift(x) & 0x77777777u : 0x3C003C00u | (xorshift(x) & 0x83FF83FFu);
+  };
+  BigFrags<SPARSE, F8> f;
+#pragma unroll
+  for (int i = 0; i < 8; i++) {
+    for (auto& v : f.a[i]) operand(v);
+    for (auto& v : f.b[i / 4][i % 4]) operand(v);
     uint32_t w = 0;
-    for (int q = 0; q < 8; q++) w |= codes[xorshift(x) % 6] << (4 * q);
-    idx[i] = (int)w;
+#pragma unroll
+    for (int q = 0; q < 8; q++) {     // the six legal 2:4 index nibbles
+      const uint32_t code = (0xED9C84u >> (4 * (xorshift(x) % 6))) & 15u;
+      w |= code << (4 * q);
+    }
+    if constexpr (SPARSE) f.idx[i] = w;
   }
-  f32x16 acc[4][4];
-  for (int i = 0; i < 4; i++)
-    for (int j = 0; j < 4; j++)
-      for (int v = 0; v < 16; v++) acc[i][j][v] = 0.f;
-  // (the dense fp8 op is inline assembly on the accumulation registers, as in the GEMM core; the builtins place their
-  // accumulators themselves)
+  f32x4 acc[8][8];
+#pragma unroll
+  for (int i = 0; i < 8; i++)
+#pragma unroll
+    for (int j = 0; j < 8; j++) {
+      acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      asm volatile("" : "+a"(acc[i][j]));
+    }
   __syncthreads();
   unsigned long long t0 = __builtin_amdgcn_s_memtime(), r0 = __builtin_amdgcn_s_memrealtime();
   for (int it = 0; it < iters; it++) {
-#pragma unroll
-    for (int mi = 0; mi < 4; mi++)
-#pragma unroll
-      for (int ni = 0; ni < 4; ni++) {
-        if constexpr (KIND == 0) acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mi], b[ni], acc[mi][ni], 0, 0, 0);
-        if constexpr (KIND == 1) {
-          bf16x16 bb = __builtin_shufflevector(b[ni], b2[ni], 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
-          acc[mi][ni] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(a[mi], bb, acc[mi][ni], idx[mi], 0, 0);
-        }
-        if constexpr (KIND == 2) asm volatile("v_mfma_f32_32x32x64_f8f6f4 %0, %1, %2, %0" : "+a"(acc[mi][ni]) : "v"(a8[mi]), "v"(b8[ni]));
-        if constexpr (KIND == 3)
-          acc[mi][ni] = __builtin_amdgcn_smfmac_f32_32x32x64_fp8_fp8(__builtin_bit_cast(i32x4, a[mi]), b8[ni], acc[mi][ni], idx[mi], 0, 0);
-      }
+    static_for<32>([&](auto M) { big_op<SPARSE, F8, 0, M>(f, acc); });
+    static_for<32>([&](auto M) { big_op<SPARSE, F8, 1, M>(f, acc); });
   }
-  if constexpr (KIND == 2) {
-    asm volatile("s_nop 15\n s_nop 15\n s_nop 15\n s_nop 15\n s_nop 15" ::: "memory");
+  asm volatile("s_nop 15\n s_nop 15\n s_nop 15" ::: "memory");
 #pragma unroll
-    for (int i = 0; i < 4; i++)
+  for (int i = 0; i < 8; i++)
 #pragma unroll
-      for (int j = 0; j < 4; j++) asm volatile("" : "+a"(acc[i][j]));
-  }
+    for (int j = 0; j < 8; j++) asm volatile("" : "+a"(acc[i][j]));
   unsigned long long t1 = __builtin_amdgcn_s_memtime(), r1 = __builtin_amdgcn_s_memrealtime();
   float s = 0.f;
-  for (int i = 0; i < 4; i++)
-    for (int j = 0; j < 4; j++)
-      for (int v = 0; v < 16; v++) s += acc[i][j][v];
+#pragma unroll
+  for (int i = 0; i < 8; i++)
+#pragma unroll
+    for (int j = 0; j < 8; j++)
+#pragma unroll
+      for (int v = 0; v < 4; v++) s += acc[i][j][v];
   if (s == 12345.678f) sink[0] = s;   // keeps the loop alive
   if ((threadIdx.x & 63) == 0) {
     int w = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -182,10 +177,10 @@ int probe_mfma_rate(int kind, int iters, double* cycles_per_op, double* mhz, dou
   if (rc) return 1;
   double t = 0, r = 0;
   for (size_t i = 0; i < h.size(); i += 2) { t += (double)h[i]; r += (double)h[i + 1]; }
-  const double ops = (double)iters * 16;
+  const double ops = (double)iters * 64;
   *cycles_per_op = t / (h.size() / 2) / ops;
   *mhz = 100.0 * t / r;
-  const double flops_per_op = kind == 0 ? 2.0 * 32 * 32 * 16 : (kind == 1 ? 2.0 * 32 * 32 * 32 : 2.0 * 32 * 32 * 64);
+  const double flops_per_op = 2.0 * 16 * 16 * (kind == 0 ? 32 : kind == 1 ? 64 : 128);
   *tflops_dense_equivalent = flops_per_op * ops * blocks * 4 / (ms * 1e-3) / 1e12;
   return 0;
 }
