@@ -239,8 +239,9 @@ FFN24_API int ffn24_prepare_weights(ffn24_ctx* ctx, const void* W1, const void* 
  * the hidden features of each token;  Y = H24 W2.
  *   X [T][D], W1 [D][F], b1 [F] fp32 or NULL (the paper's FFN has no bias; b1 only dials the sparsity of synthetic
  *   inputs), W2 [F][D], Y [T][D].  W1 and W2 both NULL: the weights of ffn24_prepare_weights (FFN24_ERR_STATE if none).
- * Kernels: two weight transposes (every GEMM operand is consumed K-contiguous), the dense-MFMA up-projection with
- * the activation and the pruning fused into its epilogue (H is never written densely), the sparse-MFMA
+ * Kernels: one pass over the weights (fp8: transposes, every fp8 GEMM operand is consumed K-contiguous; bf16: the copies that a
+ * context with FFN24_TRAINING keeps for the backward, the forward itself reads W1 and W2 where they lie), the dense-MFMA
+ * up-projection with the activation and the pruning fused into its epilogue (H is never written densely), the sparse-MFMA
  * down-projection.  The context keeps (Hc, meta), its own re-arranged copies of W1 and W2 and the X pointer for
  * ffn24_bwd; the caller keeps X alive and unchanged until then. */
 FFN24_API int ffn24_fwd(ffn24_ctx* ctx, const void* X, const void* W1, const float* b1, const void* W2, void* Y, void* stream);
@@ -250,7 +251,8 @@ FFN24_API int ffn24_fwd(ffn24_ctx* ctx, const void* X, const void* W1, const flo
  * intermediate tensors -- the compressed activation and the two re-arranged weights, T F + T F / 8 + 4 D F bytes, which
  * ffn24_ctx_create would allocate -- live in a static device array of FFN24_STATIC_SCRATCH_BYTES inside the library, of
  * which every GPU that loads the library holds one copy until the process ends.  The call allocates and frees nothing
- * and calls no allocating routine; it only enqueues four kernels on `stream`.
+ * and calls no allocating routine; it only enqueues two kernels on `stream` (three where Y lies over W2: only then are the
+ * weights re-arranged, otherwise they are read where they lie).
  *   X [T][D], W1 [D][F], b1 [F] fp32 or NULL, W2 [F][D], Y [T][D]: device pointers, bf16, caller-owned as everywhere.
  *   T, D, F multiples of 256.  FFN24_ERR_SCRATCH if ffn24_static_scratch_needed(T, D, F) exceeds the buffer (use a
  *   context then); the other error codes as for ffn24_fwd.

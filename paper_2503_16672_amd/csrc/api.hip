@@ -141,7 +141,50 @@ int weight_pass(ffn24_ctx* c, const void* W1, const void* W2, hipStream_t s) {
   return t.done((c->f8 ? launch_transpose8_weights : launch_transpose_weights)(W1, W2, D, F, c->W1t, c->W1p, c->W2t, c->W2p, s)) ? FFN24_ERR_HIP : FFN24_OK;
 }
 
-// Weights of a forward call: both given (run the weight pass; prepared copies are gone after it), or both NULL (use
+struct WgradActs { const void *dY, *X; int form; };
+
+// Do na bytes at a and nb at b share any?  (A caller's matrix is read in place only where no output of the launches that read it lies over it.)
+bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y + nb && y < x + na;
+}
+
+// What the two GEMMs of a bf16 forward read the weights from: the copies of the weight pass, or the caller's matrices as they stand (k-major: W1 [D][F]
+// as the up-projection's A, W2 [F][D] as the down-projection's B), which saves the pass (T 1024 D 1024 F 4096: 9.7 of 39 us).
+struct Weights { const void *up, *down; int up_form, down_form; };
+
+// Weights of a bf16 forward call: both given (prepared copies are gone after it), or both NULL (use the copies ffn24_prepare_weights left).  Given,
+// they are read where they lie; a context that trains keeps them for the backward, W2 in panel form (A operand of the dH GEMM) and W1 in B panel
+// form (B operand of the dX GEMM), and the words of zero / zero2 are cleared, all in one launch.  Y is what the call will write.
+int resolve_weights16(ffn24_ctx* c, const void* W1, const void* W2, const void* Y, uint32_t* zero, int zero_n, uint32_t* zero2, int zero2_n, Weights* w, hipStream_t s) {
+  const int D = (int)c->D, F = (int)c->F;
+  PaneliseJobs pre;
+  if (zero) pre.add_zero(zero, zero_n);
+  if (zero2) pre.add_zero(zero2, zero2_n);
+  *w = Weights{c->W1t, c->W2t, FORM_PANEL, FORM_PANEL};
+  if (W1 || W2) {
+    if (!W1 || !W2) return FFN24_ERR_NULL;
+    if (misaligned(W1) || misaligned(W2)) return FFN24_ERR_ALIGN;
+    c->prepared = 0;
+    if (fits_k_major(D, F) && !overlap(Y, 2 * (size_t)c->T * D, W2, 2 * (size_t)D * F)) {
+      *w = Weights{W1, W2, FORM_K_MAJOR, FORM_K_MAJOR};
+      if (c->W1p) {
+        pre.add_copy(W1, D, 2 * F, c->W1p, 1, nullptr, true);
+        pre.add_copy(W2, F, 2 * D, c->W2p, 0, nullptr, true);
+      }
+    } else if (int rc = weight_pass(c, W1, W2, s)) {
+      return rc;
+    }
+  } else if (!c->prepared) {
+    return FFN24_ERR_STATE;
+  }
+  const bool any = pre.copies || pre.zeros;
+  if (w->up_form != FORM_K_MAJOR) return any && launch_panelise8(pre, s) ? FFN24_ERR_HIP : FFN24_OK;
+  Timed t(c, K_TR_W, s);
+  return t.done(any ? launch_panelise8(pre, s) : 0) ? FFN24_ERR_HIP : FFN24_OK;
+}
+
+// Weights of an fp8 forward call: both given (run the weight pass; prepared copies are gone after it), or both NULL (use
 // the copies ffn24_prepare_weights left).
 int resolve_weights(ffn24_ctx* c, const void* W1, const void* W2, hipStream_t s) {
   if (!W1 && !W2) return c->prepared ? FFN24_OK : FFN24_ERR_STATE;
@@ -149,6 +192,21 @@ int resolve_weights(ffn24_ctx* c, const void* W1, const void* W2, hipStream_t s)
   if (misaligned(W1) || misaligned(W2)) return FFN24_ERR_ALIGN;
   c->prepared = 0;
   return weight_pass(c, W1, W2, s);
+}
+
+// dY and X as the weight gradients' B operands: as they lie, k-major, or (token permutation, whose rows the transposes gather; sizes without 32-bit
+// offsets; a gradient that lies over one of them) transposed, in B panel form.  act_pass makes the copies where
+// they are needed.
+WgradActs wgrad_acts(const ffn24_ctx* c, const void* dY, const int* perm, const void* dW1, const void* dW2) {
+  const size_t td = 2 * (size_t)c->T * c->D, df = 2 * (size_t)c->D * c->F;
+  bool direct = !perm && fits_k_major((int)c->T, (int)c->D);
+  for (const void* in : {dY, c->X})
+    for (const void* out : {dW1, dW2}) direct = direct && !overlap(out, df, in, td);
+  return direct ? WgradActs{dY, c->X, FORM_K_MAJOR} : WgradActs{c->dYt, c->Xt, FORM_PANEL};
+}
+int act_pass(ffn24_ctx* c, const WgradActs& w, const void* dY, const int* perm, hipStream_t s) {
+  Timed t(c, K_TR_ACT, s);   // (a pass that is not needed is timed as nothing)
+  return t.done(w.form == FORM_K_MAJOR ? 0 : launch_transpose_acts(dY, c->X, (int)c->T, (int)c->D, c->dYt, c->Xt, perm, s));
 }
 
 int check_ptrs(std::initializer_list<const void*> ps) {
@@ -555,7 +613,7 @@ int ffn24_fwd(ffn24_ctx* c, const void* X, const void* W1, const float* b1, cons
   int T = (int)c->T, D = (int)c->D, F = (int)c->F;
   c->have_fwd24 = c->have_fwd_dense = 0;
   if (c->f8 && (c->flags & FFN24_ROWWISE) && !c->rsx) return FFN24_ERR_STATE;
-  if ((rc = resolve_weights(c, W1, W2, s))) return rc;
+  if (c->f8 && (rc = resolve_weights(c, W1, W2, s))) return rc;
   if (c->f8 && (c->flags & FFN24_ROWWISE)) {
     // row-wise scaling: up-projection (bf16 kept values + row maxima), row-wise quantisation, scaled sparse GEMM
     uint32_t* nnz = (c->flags & FFN24_SPLIT) && c->n_dense > 0 ? c->nnz : nullptr;
@@ -594,12 +652,13 @@ int ffn24_fwd(ffn24_ctx* c, const void* X, const void* W1, const float* b1, cons
     return FFN24_OK;
   }
   uint32_t* nnz = (c->flags & FFN24_SPLIT) && c->n_dense > 0 ? c->nnz : nullptr;
-  if (nnz && launch_zero32(nnz, (size_t)F, s)) return FFN24_ERR_HIP;
-  if (c->tele && launch_zero32(reinterpret_cast<uint32_t*>(c->tele), 2 * TELE_WORDS, s)) return FFN24_ERR_HIP;
+  Weights w;
+  if ((rc = resolve_weights16(c, W1, W2, Y, nnz, F, reinterpret_cast<uint32_t*>(c->tele), 2 * TELE_WORDS, &w, s))) return rc;
   const int* perm = c->perm_on ? c->perm : nullptr;   // position p inside the FFN holds token perm[p]
-  { Timed t(c, K_UP, s);   if (t.done(launch_up_prune24(c->W1t, X, b1, T, D, F, c->Hc, c->meta, c->Hdbg, nnz, c->tele, perm, s))) return FFN24_ERR_HIP; }
+  { Timed t(c, K_UP, s);   if (t.done(launch_up_prune24(w.up, w.up_form, X, b1, T, D, F, c->Hc, c->meta, c->Hdbg, nnz, c->tele, perm, s))) return FFN24_ERR_HIP; }
   { Timed t(c, K_DOWN, s);
-    int rc1 = perm ? launch_sp_rowmajor_mapped(c->Hc, c->meta, 1, c->W2t, 1, T, D, F, Y, perm, s) : launch_sp_rowmajor(c->Hc, c->meta, 1, c->W2t, 1, T, D, F, Y, s);
+    int rc1 = perm ? launch_sp_rowmajor_mapped(c->Hc, c->meta, 1, w.down, w.down_form, T, D, F, Y, perm, s)
+                   : launch_sp_rowmajor(c->Hc, c->meta, 1, w.down, w.down_form, T, D, F, Y, s);
     if (t.done(rc1)) return FFN24_ERR_HIP; }
   if (c->tele && (rc = tele_snapshot(c, 1, s))) return rc;
   c->X = X; c->have_fwd24 = 1;
@@ -620,19 +679,23 @@ int ffn24_fwd_static(const void* X, const void* W1, const float* b1, const void*
   if (b1 && misaligned(b1)) return FFN24_ERR_ALIGN;
   unsigned char* base = nullptr;
   if ((rc = scratch_base(&base))) return rc;
-  // carve-up of the scratch buffer: Hc [T][F/2] bf16 | meta [T][F/8] | W1^T [F][D] bf16 | W2^T [D][F] bf16 (panel forms).
+  // carve-up of the scratch buffer: Hc [T][F/2] bf16 | meta [T][F/8] | W1^T [F][D] bf16 | W2^T [D][F] bf16 (panel forms).  The weights are read where
+  // they lie, though (what fits the scratch fits_k_major too), and re-arranged only where Y lies over W2.
   // Every byte a kernel below reads from it has been written by an earlier kernel of this same call, so nothing has to
   // start at zero and what a previous call left behind is never seen.
   const size_t tf = (size_t)T * (size_t)F, df = (size_t)D * (size_t)F;
   unsigned char* Hc = base;
   uint8_t* meta = base + tf;
-  unsigned char* W1t = base + tf + tf / 8;
-  unsigned char* W2t = W1t + 2 * df;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int Ti = (int)T, Di = (int)D, Fi = (int)F;
-  if (launch_transpose_weights(W1, W2, Di, Fi, W1t, nullptr, W2t, nullptr, s)) return FFN24_ERR_HIP;
-  if (launch_up_prune24(W1t, X, b1, Ti, Di, Fi, Hc, meta, nullptr, nullptr, nullptr, nullptr, s)) return FFN24_ERR_HIP;
-  if (launch_sp_rowmajor(Hc, meta, 1, W2t, 1, Ti, Di, Fi, Y, s)) return FFN24_ERR_HIP;
+  if (overlap(Y, 2 * (size_t)T * (size_t)D, W2, 2 * df)) {
+    unsigned char *W1t = base + tf + tf / 8, *W2t = W1t + 2 * df;
+    if (launch_transpose_weights(W1, W2, Di, Fi, W1t, nullptr, W2t, nullptr, s)) return FFN24_ERR_HIP;
+    if (launch_up_prune24(W1t, FORM_PANEL, X, b1, Ti, Di, Fi, Hc, meta, nullptr, nullptr, nullptr, nullptr, s)) return FFN24_ERR_HIP;
+    return launch_sp_rowmajor(Hc, meta, 1, W2t, FORM_PANEL, Ti, Di, Fi, Y, s) ? FFN24_ERR_HIP : FFN24_OK;
+  }
+  if (launch_up_prune24(W1, FORM_K_MAJOR, X, b1, Ti, Di, Fi, Hc, meta, nullptr, nullptr, nullptr, nullptr, s)) return FFN24_ERR_HIP;
+  if (launch_sp_rowmajor(Hc, meta, 1, W2, FORM_K_MAJOR, Ti, Di, Fi, Y, s)) return FFN24_ERR_HIP;
   return FFN24_OK;
 }
 
@@ -736,6 +799,7 @@ int ffn24_bwd(ffn24_ctx* c, const void* dY, void* dX, void* dW1, void* dW2, void
     return FFN24_OK;
   }
   const int* perm = c->perm_on ? c->perm : nullptr;   // position p inside the FFN holds token perm[p]
+  const WgradActs w = wgrad_acts(c, dY, perm, dW1, dW2);
   // the forward's two counts stay; the feature-wise one belongs to this backward
   if (c->tele && launch_zero32(reinterpret_cast<uint32_t*>(c->tele + tele_index(TELE_KEPT_FEAT, 0)), 2 * TELE_SLOTS * TELE_STRIDE, s)) return FFN24_ERR_HIP;
   { Timed t(c, K_DH, s);  if (t.done(launch_dh_gather(c->W2p, dY, c->Hc, c->meta, T, D, F, c->dZc, perm, s))) return FFN24_ERR_HIP; }
@@ -752,24 +816,22 @@ int ffn24_bwd(ffn24_ctx* c, const void* dY, void* dX, void* dW1, void* dW2, void
       if (t.done(launch_featurewise24_split(c->Hc, c->meta, c->dZc, T, F, c->row_of_feat, ns, c->Hc_t, c->meta_t, c->dZc_t, c->Hdn_t, c->dZdn_t, c->tele, nullptr, nullptr, s)))
         return FFN24_ERR_HIP; }
     if (c->tele && (rc = tele_snapshot(c, 1, s))) return rc;
-    { Timed t(c, K_TR_ACT, s);
-      if (t.done(launch_transpose_acts(dY, c->X, T, D, c->dYt, c->Xt, perm, s))) return FFN24_ERR_HIP; }
+    if (act_pass(c, w, dY, perm, s)) return FFN24_ERR_HIP;
     if (!c->profiling) {
-      if (launch_split_wgrads(c->Hc_t, c->dZc_t, c->meta_t, ns, c->Hdn_t, c->dZdn_t, nd, c->dYt, c->Xt, D, T, dW2, c->dW1t, D, c->feat_of_row, s)) return FFN24_ERR_HIP;
+      if (launch_split_wgrads(c->Hc_t, c->dZc_t, c->meta_t, ns, c->Hdn_t, c->dZdn_t, nd, w.dY, w.X, w.form, D, T, dW2, c->dW1t, D, c->feat_of_row, s)) return FFN24_ERR_HIP;
     } else {
-    { Timed t(c, K_DW2, s); if (t.done(launch_split_wgrad(c->Hc_t, c->meta_t, ns, c->Hdn_t, nd, c->dYt, D, T, dW2, D, c->feat_of_row, s))) return FFN24_ERR_HIP; }
-    { Timed t(c, K_DW1, s); if (t.done(launch_split_wgrad(c->dZc_t, c->meta_t, ns, c->dZdn_t, nd, c->Xt, D, T, c->dW1t, D, c->feat_of_row, s))) return FFN24_ERR_HIP; }
+    { Timed t(c, K_DW2, s); if (t.done(launch_split_wgrad(c->Hc_t, c->meta_t, ns, c->Hdn_t, nd, w.dY, w.form, D, T, dW2, D, c->feat_of_row, s))) return FFN24_ERR_HIP; }
+    { Timed t(c, K_DW1, s); if (t.done(launch_split_wgrad(c->dZc_t, c->meta_t, ns, c->dZdn_t, nd, w.X, w.form, D, T, c->dW1t, D, c->feat_of_row, s))) return FFN24_ERR_HIP; }
     }
     { Timed t(c, K_TR_DW1, s); if (t.done(launch_transpose(c->dW1t, F, D, dW1, s))) return FFN24_ERR_HIP; }
     return FFN24_OK;
   }
   { Timed t(c, K_FW, s);  if (t.done(launch_featurewise24(c->Hc, c->meta, c->dZc, T, F, c->Hc_t, c->meta_t, c->dZc_t, c->tele, s))) return FFN24_ERR_HIP; }
   if (c->tele && (rc = tele_snapshot(c, 1, s))) return rc;
-  { Timed t(c, K_TR_ACT, s);
-    if (t.done(launch_transpose_acts(dY, c->X, T, D, c->dYt, c->Xt, perm, s))) return FFN24_ERR_HIP; }
-  if (!c->profiling) return launch_wgrad(c->Hc_t, c->dZc_t, c->meta_t, c->dYt, c->Xt, F, D, T, dW2, dW1, s) ? FFN24_ERR_HIP : FFN24_OK;   // (profiling times the two by themselves)
-  { Timed t(c, K_DW2, s); if (t.done(launch_sp_rowmajor(c->Hc_t, c->meta_t, 1, c->dYt, 1, F, D, T, dW2, s))) return FFN24_ERR_HIP; }
-  { Timed t(c, K_DW1, s); if (t.done(launch_sp_colmajor(c->dZc_t, c->meta_t, 1, c->Xt, 1, F, D, T, dW1, s))) return FFN24_ERR_HIP; }
+  if (act_pass(c, w, dY, perm, s)) return FFN24_ERR_HIP;
+  if (!c->profiling) return launch_wgrad(c->Hc_t, c->dZc_t, c->meta_t, w.dY, w.X, w.form, F, D, T, dW2, dW1, s) ? FFN24_ERR_HIP : FFN24_OK;   // (profiling times the two by themselves)
+  { Timed t(c, K_DW2, s); if (t.done(launch_sp_rowmajor(c->Hc_t, c->meta_t, 1, w.dY, w.form, F, D, T, dW2, s))) return FFN24_ERR_HIP; }
+  { Timed t(c, K_DW1, s); if (t.done(launch_sp_colmajor(c->dZc_t, c->meta_t, 1, w.X, w.form, F, D, T, dW1, s))) return FFN24_ERR_HIP; }
   return FFN24_OK;
 }
 
@@ -785,7 +847,7 @@ int ffn_fwd(ffn24_ctx* c, const void* X, const void* W1, const float* b1, const 
   int T = (int)c->T, D = (int)c->D, F = (int)c->F;
   c->have_fwd24 = c->have_fwd_dense = 0;
   if (c->f8 && (c->flags & FFN24_ROWWISE) && !c->rsx) return FFN24_ERR_STATE;
-  if ((rc = resolve_weights(c, W1, W2, s))) return rc;
+  if (c->f8 && (rc = resolve_weights(c, W1, W2, s))) return rc;
   if (c->f8 && (c->flags & FFN24_ROWWISE)) {
     // dense baseline with row-wise scales: up-projection (bf16 activations + row maxima), row-wise quantisation, dense GEMM
     PaneliseJobs pre;
@@ -814,9 +876,10 @@ int ffn_fwd(ffn24_ctx* c, const void* X, const void* W1, const float* b1, const 
     if (train) { c->X = X; c->have_fwd_dense = 1; }
     return FFN24_OK;
   }
-  if (c->tele && launch_zero32(reinterpret_cast<uint32_t*>(c->tele), 2 * TELE_WORDS, s)) return FFN24_ERR_HIP;
-  { Timed t(c, KD_UP, s);   if (t.done(launch_up_relu2(c->W1t, X, b1, T, D, F, c->Hd, c->Hd_t, c->tele, s))) return FFN24_ERR_HIP; }
-  { Timed t(c, KD_DOWN, s); if (t.done(launch_dense_rowmajor(c->Hd, 1, c->W2t, 1, T, D, F, Y, s))) return FFN24_ERR_HIP; }
+  Weights w;
+  if ((rc = resolve_weights16(c, W1, W2, Y, nullptr, 0, reinterpret_cast<uint32_t*>(c->tele), 2 * TELE_WORDS, &w, s))) return rc;
+  { Timed t(c, KD_UP, s);   if (t.done(launch_up_relu2(w.up, w.up_form, X, b1, T, D, F, c->Hd, c->Hd_t, c->tele, s))) return FFN24_ERR_HIP; }
+  { Timed t(c, KD_DOWN, s); if (t.done(launch_dense_rowmajor(c->Hd, 1, w.down, w.down_form, T, D, F, Y, s))) return FFN24_ERR_HIP; }
   if (c->tele && (rc = tele_snapshot(c, 0, s))) return rc;
   c->X = X; c->have_fwd_dense = 1;
   return FFN24_OK;
@@ -884,11 +947,11 @@ int ffn_bwd(ffn24_ctx* c, const void* dY, void* dX, void* dW1, void* dW2, void* 
   }
   { Timed t(c, KD_DH, s);  if (t.done(launch_dh_drelu(c->W2p, dY, c->Hd, T, D, F, c->dZd, c->dZd_t, s))) return FFN24_ERR_HIP; }
   { Timed t(c, KD_DX, s);  if (t.done(launch_dense_rowmajor(c->dZd, 1, c->W1p, 1, T, D, F, dX, s))) return FFN24_ERR_HIP; }
-  { Timed t(c, K_TR_ACT, s);
-    if (t.done(launch_transpose_acts(dY, c->X, T, D, c->dYt, c->Xt, nullptr, s))) return FFN24_ERR_HIP; }
-  if (!c->profiling) return launch_wgrad(c->Hd_t, c->dZd_t, nullptr, c->dYt, c->Xt, F, D, T, dW2, dW1, s) ? FFN24_ERR_HIP : FFN24_OK;   // (profiling times the two by themselves)
-  { Timed t(c, KD_DW2, s); if (t.done(launch_dense_rowmajor(c->Hd_t, 1, c->dYt, 1, F, D, T, dW2, s))) return FFN24_ERR_HIP; }
-  { Timed t(c, KD_DW1, s); if (t.done(launch_dense_colmajor(c->dZd_t, 1, c->Xt, 1, F, D, T, dW1, s))) return FFN24_ERR_HIP; }
+  const WgradActs w = wgrad_acts(c, dY, nullptr, dW1, dW2);
+  if (act_pass(c, w, dY, nullptr, s)) return FFN24_ERR_HIP;
+  if (!c->profiling) return launch_wgrad(c->Hd_t, c->dZd_t, nullptr, w.dY, w.X, w.form, F, D, T, dW2, dW1, s) ? FFN24_ERR_HIP : FFN24_OK;   // (profiling times the two by themselves)
+  { Timed t(c, KD_DW2, s); if (t.done(launch_dense_rowmajor(c->Hd_t, 1, w.dY, w.form, F, D, T, dW2, s))) return FFN24_ERR_HIP; }
+  { Timed t(c, KD_DW1, s); if (t.done(launch_dense_colmajor(c->dZd_t, 1, w.X, w.form, F, D, T, dW1, s))) return FFN24_ERR_HIP; }
   return FFN24_OK;
 }
 

@@ -1,7 +1,7 @@
 // MFMA / sparse-MFMA GEMM core for gfx950 (CDNA4), bf16 operands, fp32 accumulation.
 //
-// One kernel template computes C[m][n] = sum_k A[m][k] * B[n][k]; both operands are K-contiguous in memory
-// (operands that are not are transposed once by a streaming kernel, see k_stream.hip).  Four wavefronts (2x2), each owning a
+// One kernel template computes C[m][n] = sum_k A[m][k] * B[n][k]; both operands are K-contiguous in memory, or (bf16: a dense A, B) k-major,
+// k the slow dimension, as W1, W2, X and dY come (fp8 operands that are not K-contiguous are transposed once by a streaming kernel, k_stream.hip).  Four wavefronts (2x2), each owning a
 // wave tile of 32 MI x 32 NI, so a block tile is 64 MI x 64 NI.  Block tile 256x256 (MI = NI = 4: 256 accumulator
 // registers per lane, pinned to the AGPR file) is the one that streams the fewest operand bytes per matrix op and carries the
 // large problems; 256x128, 128x128, 128x64 and 64x64 take the shapes whose 256x256 tiles would leave CUs idle (pick_tile in
@@ -181,6 +181,43 @@ __device__ __forceinline__ int swz4(int p) { return ((p >> 2) & 1) | ((((p >> 1)
 template <bool SPARSE> __device__ __forceinline__ int swz4_big(int i) { return SPARSE ? (i >> 3) & 1 : ((i >> 3) & 1) << 1; }
 __device__ __forceinline__ int swz8_big(int i) { return (i & 2) | (((i >> 3) & 1) << 2); }
 
+// k-major operands (TR): a caller's matrix with k as its slow dimension -- A [K][M] dense, B [K][N] -- read as it stands, bf16 only, under 4 GiB.  A
+// stage's k rows lie in LDS as they come, 512 (256 x 256 tile) to 128 bytes of 16-byte pieces, and a fragment is read with the transposing LDS
+// reads: the 16 lanes of a group hand in 8 bytes each, four consecutive rows (columns) of the tile at four k, and lane i gets the four k of
+// row (column) i (measured: result lane i, element j = element i % 4 of the bytes lane 4 j + i / 4 points at).  So lanes 4 c .. 4 c + 3 always
+// hold neighbours in memory.  For A that is the row order of the tiles anyway (four accumulators of a lane are four rows); of B every lane
+// wants neighbouring columns, which the lanes of a quad exchange after the main loop (unquad).
+// Against a pass that transposed them first: forward at T 1024 D 1024 F 4096 39.4 -> 25.6 us, bf16 step at T 1280 D 768 F 3072 78.7 -> 67.5, dense
+// step at T 4096 D 2048 F 8192 732 -> 709; GEMM by GEMM (panel form -> k-major) T 8192 D 2048 F 8192 up-projection 222 -> 215, down-projection 121 -> 114,
+// dW2 122 -> 116, T = F = 16384 D 4096 within 1 %, sparse 128 x 64 at T 2048 D 1024 F 4096 17.2 -> 19.0.
+// Swizzles: what 32 lanes (16 where only one half of each piece is used) read at a time lies in different banks.  The rate of such reads is that of
+// 16-byte reads then (221 against 256 B/clk in a loop of nothing else; 32 without the swizzle).
+constexpr int TR_A = 1, TR_B = 2;
+template <int MI, int NI> __device__ __forceinline__ int tr_swz_a(int k) {
+  if constexpr (MI * NI == 16) return (k & 3) | ((k >> 3) & 1) << 2;
+  else if constexpr (MI == 4) return (k & 3) << 1;
+  else if constexpr (MI == 2) return (k & 1) << 1 | (k & 2) << 2;
+  else return (k & 2) << 1;
+}
+template <int MI, int NI> __device__ __forceinline__ int tr_swz_b(int k) {
+  if constexpr (MI * NI == 16) return (k & 3) | ((k >> 3) & 1) << 2;
+  else if constexpr (NI == 2) return (k & 3) << 2;
+  else return (k & 2) << 1;
+}
+// a fragment of 8 k: the lane's 8 bytes of k .. k + 3 at p, of k + 4 .. k + 7 four rows on.  (__restrict__: without the alias scope it brings the compiler
+// takes the read for one of what any DMA in flight writes and waits for all of them; the loops wait for the stage they read themselves.)
+template <int KROW>
+__device__ __forceinline__ bf16x8 tr_read(const char* __restrict__ p) {
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p), hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * KROW));
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+// lane i of a quad gets a value of lane P(i) of it, P packed two bits a lane
+template <int P>
+__device__ __forceinline__ float quad(float x) { return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), P, 0xF, 0xF, true)); }
+constexpr int quad_perm(int a, int b, int c, int d) { return a | b << 2 | c << 4 | d << 6; }
+
 // compile-time loop: f(std::integral_constant<int, 0>) ... f(std::integral_constant<int, N-1>)
 template <class F, int... Is>
 __device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, Is...>) { (f(std::integral_constant<int, Is>{}), ...); }
@@ -209,10 +246,11 @@ __device__ __forceinline__ void wait_lgkmcnt0() { __builtin_amdgcn_s_waitcnt(0xC
 // ------------------------------------------------------------------------------------------------
 // global -> LDS DMA plan of one wave
 // ------------------------------------------------------------------------------------------------
-template <bool SPARSE, bool F8 = false, int PROBE = 0, int MI = 4, int NI = 4>
+template <bool SPARSE, bool F8 = false, int PROBE = 0, int MI = 4, int NI = 4, int TR = 0>
 struct Dma {
   using G = Geo<SPARSE, F8, MI, NI>;
   static constexpr int NA = G::NA, NVB = G::NVB;
+  static constexpr bool TRA = (TR & TR_A) != 0, TRB = (TR & TR_B) != 0;
   __amdgpu_buffer_rsrc_t a;      // from the block's first A row on (uniform)
   __amdgpu_buffer_rsrc_t am;     // metadata
   __amdgpu_buffer_rsrc_t b;
@@ -230,14 +268,18 @@ struct Dma {
     const bool panel = g.a_panel != 0, bp = g.b_panel != 0;
     const uint32_t a_pitch = panel ? 64u : a_row, m_pitch = panel ? (uint32_t)G::META_ROW : (uint32_t)(g.K / 8);
     const int ma = MI == 4 ? 0 : m0 & 255, mb = m0 - ma, na = NI == 4 || !bp ? 0 : n0 & 255, nb = n0 - na;
-    a = from(static_cast<const char*>(g.A) + (size_t)mb * a_row + (size_t)ma * a_pitch);
+    if constexpr (TRA) a = from(static_cast<const char*>(g.A) + (size_t)m0 * G::ESIZE);
+    else a = from(static_cast<const char*>(g.A) + (size_t)mb * a_row + (size_t)ma * a_pitch);
     if constexpr (SPARSE) am = from(reinterpret_cast<const char*>(g.Ameta) + (size_t)mb * (g.K / 8) + (size_t)ma * m_pitch);
-    b = from(static_cast<const char*>(g.B) + (g.b_rowmap ? (size_t)0 : (size_t)nb * b_row));
-    a_stage = panel ? 256u * (uint32_t)G::A_ROW : (uint32_t)G::A_ROW;
+    if constexpr (TRB) b = from(static_cast<const char*>(g.B) + (size_t)n0 * G::ESIZE);
+    else b = from(static_cast<const char*>(g.B) + (g.b_rowmap ? (size_t)0 : (size_t)nb * b_row));
+    const uint32_t a_krow = (uint32_t)g.M * G::ESIZE, b_krow = (uint32_t)g.N * G::ESIZE;   // bytes per k of a k-major operand
+    a_stage = TRA ? (uint32_t)G::BK * a_krow : panel ? 256u * (uint32_t)G::A_ROW : (uint32_t)G::A_ROW;
     m_stage = panel ? 256u * G::META_ROW : (uint32_t)G::META_ROW;
-    b_stage = bp ? 256u * (uint32_t)G::B_ROW : (uint32_t)G::B_ROW;
+    b_stage = TRB ? (uint32_t)G::BK * b_krow : bp ? 256u * (uint32_t)G::B_ROW : (uint32_t)G::B_ROW;
 #pragma unroll
     for (int j = 0; j < NA; j++) {
+      if constexpr (TRA) { va[j] = k_major<MI>(NA * wave + j, lane, a_krow, [](int k) { return tr_swz_a<MI, NI>(k); }); continue; }
       // 64-byte rows, 16 an instruction; 128-byte rows, 8 an instruction, of which the panel form has two 64-byte pieces in
       // consecutive 16 KiB runs
       const int p = G::WIDE ? 8 * (NA * wave + j) + (lane >> 3) : 16 * (NA * wave + j) + (lane >> 2);
@@ -246,6 +288,7 @@ struct Dma {
     }
 #pragma unroll
     for (int j = 0; j < NVB; j++) {
+      if constexpr (TRB) { vb[j] = k_major<NI>(NVB * wave + j, lane, b_krow, [](int k) { return tr_swz_b<MI, NI>(k); }); continue; }
       int p = G::B_ROW == 128 ? 8 * (NVB * wave + j) + (lane >> 3) : 16 * (NVB * wave + j) + (lane >> 2);
       int c = G::B_ROW == 128 ? (lane & 7) ^ (G::BIG ? swz8_big(big_n_col<SPARSE>(p)) : swz8(p)) : (lane & 3) ^ (G::BIG ? swz4_big<false>(big_n_col<SPARSE>(p)) : swz4(p));
       const int n = G::BIG ? big_unperm_n<SPARSE>(p) : unperm_n<NI>(p);
@@ -266,6 +309,14 @@ struct Dma {
         }
       }
     }
+  }
+
+  // What a lane of instruction j fetches of a k-major operand: 8 / W rows of 128 W bytes of LDS an instruction, the 16-byte pieces of row k at
+  // places XORed with the swizzle of k.
+  template <int W, class Swz>
+  static __device__ __forceinline__ uint32_t k_major(int j, int lane, uint32_t krow, Swz swz) {
+    const int k = (8 / W) * j + lane / (8 * W);
+    return (uint32_t)k * krow + (uint32_t)(((lane & (8 * W - 1)) ^ swz(k)) * 16);
   }
 
   // DMA instruction J of stage kt into the stage buffer at `buf` (uniform LDS pointer)
@@ -309,6 +360,16 @@ struct LaneCtx {
   int sw4;          // swz4 of the lane's row (the same for every 32-row tile)
   int sw8;          // swz8 of the lane's B row for even ni (odd ni: ^4)
   int sw8a;         // swz8 of the lane's A row for even mi (odd mi: ^4)
+  int a_tr, b_tr;   // k-major operands: the lane's first 8 bytes of the stage's A, of its B
+  template <int MI, int NI>
+  __device__ __forceinline__ void set_tr(int lane) {
+    const int i = lane & 15, odd = (lane >> 4) & 1, k = 8 * h + (i >> 2);
+    // quad 4 odd + i % 4 of the 32 rows is lane half hc's vh-th group of four
+    const int quad = 4 * odd + (i & 3), hc = quad & 1, vh = quad >> 1;
+    a_tr = k * (128 * MI) + (((4 * MI * wy + 2 * MI * hc + (vh >> 1)) ^ tr_swz_a<MI, NI>(k)) << 4) + 8 * (vh & 1);
+    // NI = 2: N-tile ni has the ni-th half of every 16-byte piece
+    b_tr = NI == 2 ? k * 256 + (((8 * wx + quad) ^ tr_swz_b<MI, NI>(k)) << 4) : k * 128 + (((4 * wx + (quad >> 1)) ^ tr_swz_b<MI, NI>(k)) << 4) + 8 * (quad & 1);
+  }
 };
 
 // Dense: K step S (0,1) of the 64-byte stage rows; fragment I < MI -> a[I], else b[I-MI]
@@ -316,9 +377,11 @@ template <int MI, int NI>
 struct FragD {
   bf16x8 a[MI], b[NI];
 };
-template <class G, int S, int I, int PROBE, int MI, int NI>
+template <class G, int S, int I, int PROBE, int TR = 0, int MI, int NI>
 __device__ __forceinline__ void load_frag_dense1(const char* buf, const LaneCtx& L, FragD<MI, NI>& f) {
   if constexpr ((PROBE & PROBE_NO_FRAG) != 0) return;
+  if constexpr (I < MI && (TR & TR_A)) { f.a[I] = tr_read<128 * MI>(buf + (L.a_tr ^ (I << 5)) + S * (16 * 128 * MI)); return; }
+  if constexpr (I >= MI && (TR & TR_B)) { f.b[I - MI] = tr_read<128 * NI>(buf + G::B_OFF + L.b_tr + 8 * (I - MI) + S * (16 * 128 * NI)); return; }
   if constexpr (G::WIDE) {
     constexpr int i = I < MI ? I : I - MI;
     const int c = ((2 * S + L.h) ^ (I < MI ? L.sw8a : L.sw8) ^ ((i & 1) << 2)) << 4;
@@ -380,10 +443,15 @@ __device__ __forceinline__ void load_idx_sparse1(const char* buf, const LaneCtx&
   }
 }
 // fragment I of instruction S: I < MI -> a[I]; the next NI -> low halves of b; the last NI -> high halves of b
-template <class G, int S, int I, int PROBE, int MI, int NI>
+template <class G, int S, int I, int PROBE, int TR = 0, int MI, int NI>
 __device__ __forceinline__ void load_frag_sparse1(const char* buf, const LaneCtx& L, FragS<MI, NI>& f) {
   if constexpr ((PROBE & PROBE_NO_FRAG) != 0) return;
-  if constexpr (I < MI) {
+  if constexpr (I >= MI && (TR & TR_B)) {
+    constexpr int i = (I - MI) % NI;
+    const char* p = buf + G::B_OFF + L.b_tr + 8 * i + S * (16 * 128 * NI);
+    if constexpr (I < MI + NI) f.blo[i] = tr_read<128 * NI>(p);
+    else f.bhi[i] = tr_read<128 * NI>(p + 32 * 128 * NI);
+  } else if constexpr (I < MI) {
     f.a[I] = *reinterpret_cast<const bf16x8*>(buf + L.a_row64 + I * (32 * 64) + (((2 * L.h + S) ^ L.sw4) << 4));
   } else {
     constexpr int i = (I - MI) % NI;
@@ -410,21 +478,21 @@ __device__ __forceinline__ void mfma_sparse1(const FragS<MI, NI>& f, const IdxWo
 
 // What a wave of the smaller tiles holds of one whole stage: the fragments (and metadata) as READS LDS reads, consumed by OPS matrix ops
 // that come in the order of k.
-template <bool SPARSE, bool F8, int MI, int NI>
+template <bool SPARSE, bool F8, int MI, int NI, int TR = 0>
 struct StageRegs {                           // dense: chunk pairs q of 32 bytes of k, one K step each (fp8: two a step)
   static constexpr int PAIRS = wide_stage(MI, NI) ? 4 : 2, NF = MI + NI;
   static constexpr int READS = PAIRS * NF, OPS = MI * NI * PAIRS / (F8 ? 2 : 1);
   static constexpr int READ_SLOTS = OPS > 1 ? OPS / 2 : 1;
   FragD<MI, NI> f[PAIRS];
-  template <class G, int I, int PROBE> __device__ __forceinline__ void read(const char* buf, const LaneCtx& L) { load_frag_dense1<G, I / NF, I % NF, PROBE>(buf, L, f[I / NF]); }
+  template <class G, int I, int PROBE> __device__ __forceinline__ void read(const char* buf, const LaneCtx& L) { load_frag_dense1<G, I / NF, I % NF, PROBE, TR>(buf, L, f[I / NF]); }
   template <int M, int PROBE> __device__ __forceinline__ void op(f32x16 (&acc)[MI][NI]) const {
     constexpr int s = M / (MI * NI), m = M % (MI * NI);
     if constexpr (F8) mfma_dense_f8<m, PROBE>(f[2 * s], f[2 * s + 1], acc);
     else mfma_dense1<m, PROBE>(f[s], acc);
   }
 };
-template <bool F8, int MI, int NI>
-struct StageRegs<true, F8, MI, NI> {
+template <bool F8, int MI, int NI, int TR>
+struct StageRegs<true, F8, MI, NI, TR> {
   static constexpr int NF = MI + 2 * NI;
   static constexpr int READS = MI + 2 * NF, OPS = 2 * MI * NI;
   static constexpr int READ_SLOTS = OPS / 2;
@@ -432,7 +500,7 @@ struct StageRegs<true, F8, MI, NI> {
   IdxWords<F8> idx[MI];
   template <class G, int I, int PROBE> __device__ __forceinline__ void read(const char* buf, const LaneCtx& L) {
     if constexpr (I < MI) load_idx_sparse1<G, F8, I>(buf, L, idx);
-    else load_frag_sparse1<G, (I - MI) / NF, (I - MI) % NF, PROBE>(buf, L, f[(I - MI) / NF]);
+    else load_frag_sparse1<G, (I - MI) / NF, (I - MI) % NF, PROBE, TR>(buf, L, f[(I - MI) / NF]);
   }
   template <int M, int PROBE> __device__ __forceinline__ void op(f32x16 (&acc)[MI][NI]) const {
     mfma_sparse1<F8, M / (MI * NI), M % (MI * NI), PROBE>(f[M / (MI * NI)], idx, acc);
@@ -514,7 +582,23 @@ __device__ __forceinline__ void ride(F&& f) {
   static_for<hi - lo>([&](auto i) { f(std::integral_constant<int, lo + decltype(i)::value>{}); });
 }
 
-template <bool SPARSE, class Epi, bool F8, int MI, int NI>
+// NI = 2, B k-major: lane i of a quad has columns 8 g + i and 8 g + 4 + i and wants 8 g + 2 i and 8 g + 2 i + 1
+template <int MI>
+__device__ __forceinline__ void unquad(f32x16 (&acc)[MI][2]) {
+  const bool upper = (fresh_lane() & 2) != 0;
+#pragma unroll
+  for (int i = 0; i < MI; i++)
+#pragma unroll
+    for (int v = 0; v < 16; v++) {
+      const float x = acc[i][0][v], y = acc[i][1][v];
+      constexpr int EVEN = quad_perm(0, 2, 0, 2), ODD = quad_perm(1, 3, 1, 3);
+      const float x0 = quad<EVEN>(x), y0 = quad<EVEN>(y), x1 = quad<ODD>(x), y1 = quad<ODD>(y);
+      acc[i][0][v] = upper ? y0 : x0;
+      acc[i][1][v] = upper ? y1 : x1;
+    }
+}
+
+template <bool SPARSE, class Epi, bool F8, int MI, int NI, int TR>
 __device__ __forceinline__ void gemm_tile_small(const GemmArgs& g, const typename Epi::Args& ea, char* smem, int pid) {
   using G = Geo<SPARSE, F8, MI, NI>;
   constexpr int NMF = MI * NI;              // matrix ops (slots) per K step
@@ -540,7 +624,9 @@ __device__ __forceinline__ void gemm_tile_small(const GemmArgs& g, const typenam
   L.sw8 = NI == 1 ? swz8(L.wx * 32 + L.rho) : swz8(L.rho);
   L.sw8a = MI == 1 ? swz8(L.wy * 32 + L.rho) : swz8(L.rho);
 
-  Dma<SPARSE, F8, PROBE, MI, NI> dma;
+  if constexpr (TR != 0) L.set_tr<MI, NI>(lane);
+
+  Dma<SPARSE, F8, PROBE, MI, NI, TR> dma;
   dma.init(g, m0, n0, tid);
 
   const int nk = g.K / G::BK;
@@ -569,8 +655,8 @@ __device__ __forceinline__ void gemm_tile_small(const GemmArgs& g, const typenam
     // stage's ops run (two register sets), with one wait and one barrier a stage, and the DMA of the stage that reuses this
     // stage's buffer, whose fragments are in registers, rides along.  One tile a CU, K 4096: sparse 64 x 64 15.0 -> 13.0 us, 128 x 64 16.6
     // -> 15.2, 256 x 128 37.0 -> 35.8; dense 64 x 64 see wide_stage, 128 x 128 29.8 -> 29.6.  What bounds them now is the operand stream.
-    StageRegs<SPARSE, F8, MI, NI> r0, r1;
-    using SR = StageRegs<SPARSE, F8, MI, NI>;
+    StageRegs<SPARSE, F8, MI, NI, TR> r0, r1;
+    using SR = StageRegs<SPARSE, F8, MI, NI, TR>;
     auto stage = [&](int kt, char* cur, char* nxt, const SR& now, SR& next, auto mode, auto left) {
       constexpr int MODE = decltype(mode)::value, LEFT = decltype(left)::value;
       FFN24_FENCE();
@@ -622,14 +708,14 @@ __device__ __forceinline__ void gemm_tile_small(const GemmArgs& g, const typenam
     constexpr int NF = MI + 2 * NI;
     IdxWords<F8> idx[MI];
     static_for<MI>([&](auto I) { load_idx_sparse1<G, F8, I>(smem, L, idx); });
-    static_for<NF>([&](auto I) { load_frag_sparse1<G, 0, I, PROBE>(smem, L, f0); });
+    static_for<NF>([&](auto I) { load_frag_sparse1<G, 0, I, PROBE, TR>(smem, L, f0); });
     auto stage = [&](int kt, char* cur, char* nxt, auto mode) {
       constexpr int MODE = decltype(mode)::value;
       IdxWords<F8> idx_n[MI] = {};
       FFN24_FENCE();
       static_for<NMF>([&](auto M) {
         mfma_sparse1<F8, 0, M, PROBE>(f0, idx, acc);
-        ride<NF, FRAG_SLOTS, M>([&](auto I) { load_frag_sparse1<G, 1, I, PROBE>(cur, L, f1); });
+        ride<NF, FRAG_SLOTS, M>([&](auto I) { load_frag_sparse1<G, 1, I, PROBE, TR>(cur, L, f1); });
         FFN24_FENCE();
       });
       if constexpr (MODE != 2) {
@@ -644,7 +730,7 @@ __device__ __forceinline__ void gemm_tile_small(const GemmArgs& g, const typenam
         if constexpr (MODE == 0) ride<NDMA, NMF, M>([&](auto J) { dma.template issue<J>(kt + NB, cur); });
         if constexpr (MODE != 2) {
           if constexpr (M < MI) load_idx_sparse1<G, F8, M>(nxt, L, idx_n);
-          ride<NF, FRAG_SLOTS, M>([&](auto I) { load_frag_sparse1<G, 0, I, PROBE>(nxt, L, f0); });
+          ride<NF, FRAG_SLOTS, M>([&](auto I) { load_frag_sparse1<G, 0, I, PROBE, TR>(nxt, L, f0); });
         }
         FFN24_FENCE();
       });
@@ -667,8 +753,8 @@ __device__ __forceinline__ void gemm_tile_small(const GemmArgs& g, const typenam
     // one barrier at the end of the stage.  Two fragment sets alternate.
     FragD<MI, NI> fr[2][2];
     constexpr int NF = MI + NI;
-    static_for<NF>([&](auto I) { load_frag_dense1<G, 0, I, PROBE>(smem, L, fr[0][0]); });
-    static_for<NF>([&](auto I) { load_frag_dense1<G, 1, I, PROBE>(smem, L, fr[0][1]); });
+    static_for<NF>([&](auto I) { load_frag_dense1<G, 0, I, PROBE, TR>(smem, L, fr[0][0]); });
+    static_for<NF>([&](auto I) { load_frag_dense1<G, 1, I, PROBE, TR>(smem, L, fr[0][1]); });
     auto stage = [&](int kt, char* cur, char* nxt, auto par, auto mode) {
       constexpr int P = decltype(par)::value, MODE = decltype(mode)::value;
       FFN24_FENCE();
@@ -676,8 +762,8 @@ __device__ __forceinline__ void gemm_tile_small(const GemmArgs& g, const typenam
         mfma_dense_f8<M, PROBE>(fr[P][0], fr[P][1], acc);
         if constexpr (MODE == 0) ride<NDMA, NMF, M>([&](auto J) { dma.template issue<J>(kt + NB, cur); });
         if constexpr (MODE != 2) ride<2 * NF, NMF, M>([&](auto I) {
-          if constexpr (I < NF) load_frag_dense1<G, 0, I, PROBE>(nxt, L, fr[P ^ 1][0]);
-          else load_frag_dense1<G, 1, I - NF, PROBE>(nxt, L, fr[P ^ 1][1]);
+          if constexpr (I < NF) load_frag_dense1<G, 0, I, PROBE, TR>(nxt, L, fr[P ^ 1][0]);
+          else load_frag_dense1<G, 1, I - NF, PROBE, TR>(nxt, L, fr[P ^ 1][1]);
         });
         FFN24_FENCE();
       });
@@ -714,13 +800,13 @@ __device__ __forceinline__ void gemm_tile_small(const GemmArgs& g, const typenam
   } else {
     FragD<MI, NI> f0, f1;
     constexpr int NF = MI + NI;
-    static_for<NF>([&](auto I) { load_frag_dense1<G, 0, I, PROBE>(smem, L, f0); });
+    static_for<NF>([&](auto I) { load_frag_dense1<G, 0, I, PROBE, TR>(smem, L, f0); });
     auto stage = [&](int kt, char* cur, char* nxt, auto mode) {
       constexpr int MODE = decltype(mode)::value;
       FFN24_FENCE();
       static_for<NMF>([&](auto M) {
         mfma_dense1<M, PROBE>(f0, acc);
-        ride<NF, FRAG_SLOTS, M>([&](auto I) { load_frag_dense1<G, 1, I, PROBE>(cur, L, f1); });
+        ride<NF, FRAG_SLOTS, M>([&](auto I) { load_frag_dense1<G, 1, I, PROBE, TR>(cur, L, f1); });
         FFN24_FENCE();
       });
       if constexpr (MODE != 2) {
@@ -732,7 +818,7 @@ __device__ __forceinline__ void gemm_tile_small(const GemmArgs& g, const typenam
       static_for<NMF>([&](auto M) {
         mfma_dense1<M, PROBE>(f1, acc);
         if constexpr (MODE == 0) ride<NDMA, NMF, M>([&](auto J) { dma.template issue<J>(kt + NB, cur); });
-        if constexpr (MODE != 2) ride<NF, FRAG_SLOTS, M>([&](auto I) { load_frag_dense1<G, 0, I, PROBE>(nxt, L, f0); });
+        if constexpr (MODE != 2) ride<NF, FRAG_SLOTS, M>([&](auto I) { load_frag_dense1<G, 0, I, PROBE, TR>(nxt, L, f0); });
         FFN24_FENCE();
       });
     };
@@ -748,6 +834,7 @@ __device__ __forceinline__ void gemm_tile_small(const GemmArgs& g, const typenam
     advance(kt, std::integral_constant<int, 2>{});
   }
 
+  if constexpr ((TR & TR_B) && NI == 2) unquad(acc);
   int m_lane = m0 + L.wy * (32 * MI) + (16 * MI) * L.h;
   int n_lane = n0 + L.wx * (32 * NI) + NI * L.rho;
   run_epilogue<G, Epi, MI, NI>(ea, acc, m_lane, n_lane, smem, wave);
@@ -800,16 +887,22 @@ __device__ __forceinline__ void big_op(const BigFrags<SPARSE, F8>& f, f32x4 (&ac
   else op16_sp_f8(f.a[mi][0], cat16(f.b[H][n][0], f.b[H][n][1]), f.idx[mi], acc[mi][ni]);
 }
 // fragment reads of A tile T (with its metadata) and of read I of B half H; buf: the stage's buffer, buf2: the second stage's (dense fp8)
-template <class G, bool SPARSE, bool F8, int T>
+template <class G, bool SPARSE, bool F8, int T, int TR = 0>
 __device__ __forceinline__ void big_read_a(const char* buf, const char* buf2, const BigLane& L, BigFrags<SPARSE, F8>& f) {
+  if constexpr ((TR & TR_A) != 0) { f.a[T][0] = tr_read<512>(buf + (L.a ^ ((T / 2) << 4)) + 8 * (T % 2)); return; }
   f.a[T][0] = *reinterpret_cast<const bf16x8*>(buf + L.a + T * (4 * 64));
   if constexpr (F8 && !SPARSE) f.a[T][1] = *reinterpret_cast<const bf16x8*>(buf2 + L.a + T * (4 * 64));
   if constexpr (SPARSE && F8) f.idx[T] = *reinterpret_cast<const uint32_t*>(buf + L.m + T * (8 * 16));
   if constexpr (SPARSE && !F8) f.idx[T] = *reinterpret_cast<const uint16_t*>(buf + L.m + T * (4 * 8));
 }
-template <class G, bool SPARSE, bool F8, int H, int I>
+template <class G, bool SPARSE, bool F8, int H, int I, int TR = 0>
 __device__ __forceinline__ void big_read_b(const char* buf, const char* buf2, const BigLane& L, BigFrags<SPARSE, F8>& f) {
   // N-tile 4 H + n
+  if constexpr ((TR & TR_B) != 0) {
+    constexpr int n = SPARSE ? I / 2 : I, hi = SPARSE ? I % 2 : 0;
+    f.b[H][n][hi] = tr_read<512>(buf + (L.b ^ (n << 4 | H << 3)) + hi * (16 * 512));
+    return;
+  }
   if constexpr (SPARSE) f.b[H][I / 2][I % 2] = *reinterpret_cast<const bf16x8*>(buf + (L.b ^ ((I % 2) << 5)) + (32 * (I / 2) + 4 * H) * 128);
   else if constexpr (F8) f.b[H][I / 2][I % 2] = *reinterpret_cast<const bf16x8*>((I % 2 ? buf2 : buf) + L.b + (32 * (I / 2) + 8 * H) * 64);
   else f.b[H][I][0] = *reinterpret_cast<const bf16x8*>(buf + L.b + (32 * I + 8 * H) * 64);
@@ -826,7 +919,35 @@ __device__ __forceinline__ void big_read_b(const char* buf, const char* buf2, co
 constexpr int big_read_slot(int M) { return M % 4 == 1 ? M / 4 * 2 : M % 4 == 2 ? M / 4 * 2 + 1 : -1; }
 template <int SLOTS, int N> constexpr int paced(int M) { return M % SLOTS == 0 && M / SLOTS < N ? M / SLOTS : -1; }
 
-template <bool SPARSE, class Epi, bool F8, int PROBE>
+// B k-major: N-tile 4 H + n of lane 4 g + i has column 32 g + 8 n + 4 (H ^ g % 2) + i (both halves of the 16-byte pieces are then read at a time,
+// by neighbouring quads).  Of the eight columns in x, lane 4 g + i gets 32 g + 8 i + 0 .. 7.
+__device__ __forceinline__ void unquad(float (&x)[8], int lane) {
+  const bool swap = (lane & 4) != 0, odd = (lane & 1) != 0, upper = (lane & 2) != 0;
+  constexpr int XOR1 = quad_perm(1, 0, 3, 2), XOR2 = quad_perm(2, 3, 0, 1);
+#pragma unroll
+  for (int n = 0; n < 4; n++) {
+    const float a = x[n], b = x[4 + n];
+    x[n] = swap ? b : a;
+    x[4 + n] = swap ? a : b;
+  }
+#pragma unroll
+  for (int h = 0; h < 8; h += 4) {
+#pragma unroll
+    for (int n = 0; n < 4; n += 2) {
+      const float a = x[h + n], b = x[h + n + 1], qa = quad<XOR1>(a), qb = quad<XOR1>(b);
+      x[h + n] = odd ? qb : a;
+      x[h + n + 1] = odd ? b : qa;
+    }
+#pragma unroll
+    for (int n = 0; n < 2; n++) {
+      const float a = x[h + n], b = x[h + n + 2], qa = quad<XOR2>(a), qb = quad<XOR2>(b);
+      x[h + n] = upper ? qb : a;
+      x[h + n + 2] = upper ? b : qa;
+    }
+  }
+}
+
+template <bool SPARSE, class Epi, bool F8, int PROBE, int TR>
 __device__ __forceinline__ void gemm_tile_big(const GemmArgs& g, const typename Epi::Args& ea, char* smem, int pid, int pid_end, int pid_step) {
   using G = Geo<SPARSE, F8, 4, 4>;
   constexpr int NB = G::NB, NDMA = G::NDMA - ((SPARSE && (PROBE & PROBE_FILL_LESS)) ? 3 : 0);
@@ -845,9 +966,17 @@ __device__ __forceinline__ void gemm_tile_big(const GemmArgs& g, const typename 
   L.a = (wy * 128 + 32 * (c >> 2) + (c & 3)) * 64 + ((win ^ swz4_big<SPARSE>(c)) << 4);
   L.b = SPARSE ? G::B_OFF + (wx * 128 + 8 * (c >> 2) + (c & 3)) * 128 + ((((q & 1) | ((q >> 1) << 2)) ^ swz8_big(c)) << 4)
                : G::B_OFF + (wx * 128 + 16 * (c >> 3) + (c & 7)) * 64 + ((q ^ swz4_big<false>(c)) << 4);
+  if constexpr ((TR & TR_A) != 0) {
+    const int k = 8 * q + (c >> 2);
+    L.a = k * 512 + (((16 * wy + 4 * (c & 3)) ^ tr_swz_a<4, 4>(k)) << 4);
+  }
+  if constexpr ((TR & TR_B) != 0) {
+    const int k = 8 * (SPARSE ? (q & 1) | (q >> 1) << 2 : q) + (c >> 2);
+    L.b = G::B_OFF + k * 512 + (((16 * wx + 4 * (c & 3)) ^ tr_swz_b<4, 4>(k)) << 4) + 8 * (c & 1);
+  }
   L.m = G::META_OFF + (F8 ? (2 * wy + (c >> 3)) * (1024 + 128) + ((c >> 2) & 1) * 64 + (c & 3) * 16 + 4 * win : (4 * wy + (c >> 2)) * (256 + 32) + (c & 3) * 8 + 2 * win);
 
-  Dma<SPARSE, F8, PROBE, 4, 4> dma;
+  Dma<SPARSE, F8, PROBE, 4, 4, TR> dma;
   dma.init(g, m0, n0, tid);
   const int nk = g.K / G::BK;
   constexpr int STEP = F8 && !SPARSE ? 2 : 1;                  // stages a K step
@@ -883,8 +1012,8 @@ __device__ __forceinline__ void gemm_tile_big(const GemmArgs& g, const typename 
   __builtin_amdgcn_s_barrier();
   FFN24_FENCE();
   if constexpr (FRAG) {
-    static_for<8>([&](auto T) { big_read_a<G, SPARSE, F8, T>(smem, smem + G::STAGE, L, f); });
-    static_for<NRB>([&](auto I) { big_read_b<G, SPARSE, F8, 0, I>(smem, smem + G::STAGE, L, f); });
+    static_for<8>([&](auto T) { big_read_a<G, SPARSE, F8, T, TR>(smem, smem + G::STAGE, L, f); });
+    static_for<NRB>([&](auto I) { big_read_b<G, SPARSE, F8, 0, I, TR>(smem, smem + G::STAGE, L, f); });
   }
 
   int slot = 0;
@@ -902,7 +1031,7 @@ __device__ __forceinline__ void gemm_tile_big(const GemmArgs& g, const typename 
       constexpr int J = paced<PACE, NDMA - PART>(M);
       if constexpr (REST && J >= 0) dma.template issue<PART + (J >= 0 ? J : 0)>(kt - 1 + NB, prv);
       constexpr int I = big_read_slot(M);
-      if constexpr (FRAG && I >= 0 && I < NRB) big_read_b<G, SPARSE, F8, 1, (I >= 0 ? I : 0)>(cur, cur2, L, f);
+      if constexpr (FRAG && I >= 0 && I < NRB) big_read_b<G, SPARSE, F8, 1, (I >= 0 ? I : 0), TR>(cur, cur2, L, f);
       FFN24_FENCE();
     });
     if constexpr (LEFT >= 0) {
@@ -917,8 +1046,8 @@ __device__ __forceinline__ void gemm_tile_big(const GemmArgs& g, const typename 
       if constexpr (ISSUE && J >= 0) dma.template issue<(J >= 0 ? J : 0)>(kt + NB, cur);
       if constexpr (FRAG && LEFT >= 0) {
         constexpr int I = big_read_slot(M);
-        if constexpr (I >= 0 && I < NRB) big_read_b<G, SPARSE, F8, 0, (I >= 0 ? I : 0)>(nxt, nxt2, L, f);
-        if constexpr (M % 4 == 3) big_read_a<G, SPARSE, F8, M / 4>(nxt, nxt2, L, f);
+        if constexpr (I >= 0 && I < NRB) big_read_b<G, SPARSE, F8, 0, (I >= 0 ? I : 0), TR>(nxt, nxt2, L, f);
+        if constexpr (M % 4 == 3) big_read_a<G, SPARSE, F8, M / 4, TR>(nxt, nxt2, L, f);
       }
       FFN24_FENCE();
     });
@@ -954,6 +1083,19 @@ __device__ __forceinline__ void gemm_tile_big(const GemmArgs& g, const typename 
 #pragma unroll
       for (int v = 0; v < 16; v++) out[i][j][v] = acc[4 * i + v / 4][j][v % 4];
   const int at = fresh_lane();
+  if constexpr ((TR & TR_B) != 0) {
+#pragma unroll
+    for (int i = 0; i < 2; i++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) {
+        float x[8];
+#pragma unroll
+        for (int j = 0; j < 8; j++) x[j] = out[i][j][v];
+        unquad(x, at);
+#pragma unroll
+        for (int j = 0; j < 8; j++) out[i][j][v] = x[j];
+      }
+  }
   const int m_lane = m0 + wy * 128 + 32 * (at >> 4), n_lane = n0 + wx * 128 + 8 * (at & 15);
   if constexpr (PERSIST) {
     pid += pid_step;
@@ -977,10 +1119,11 @@ __device__ __forceinline__ void gemm_tile_big(const GemmArgs& g, const typename 
   }   // tiles
 }
 
-template <bool SPARSE, class Epi, bool F8 = false, int PROBE = 0, int MI = 4, int NI = 4>
+template <bool SPARSE, class Epi, bool F8 = false, int PROBE = 0, int MI = 4, int NI = 4, int TR = 0>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const typename Epi::Args& ea, char* smem, int pid, int pid_end = 0, int pid_step = 0) {
-  if constexpr (MI * NI == 16) gemm_tile_big<SPARSE, Epi, F8, PROBE>(g, ea, smem, pid, pid_end, pid_step);
-  else gemm_tile_small<SPARSE, Epi, F8, MI, NI>(g, ea, smem, pid);
+  static_assert(TR == 0 || (!F8 && !(SPARSE && (TR & TR_A))), "k-major operands: bf16, and a 2:4 operand has its own form");
+  if constexpr (MI * NI == 16) gemm_tile_big<SPARSE, Epi, F8, PROBE, TR>(g, ea, smem, pid, pid_end, pid_step);
+  else gemm_tile_small<SPARSE, Epi, F8, MI, NI, TR>(g, ea, smem, pid);
 }
 
 // Clock sample of a workgroup (profiling only): ticks of the shader clock and of the constant 100 MHz clock between its
@@ -1010,6 +1153,16 @@ __global__ void __launch_bounds__(GEMM_THREADS, (Geo<SPARSE, F8, MI, NI>::PER_CU
   cs.end(g);
 }
 
+// The same with a k-major operand.
+template <bool SPARSE, class Epi, int TR, int MI, int NI>
+__global__ void __launch_bounds__(GEMM_THREADS, (Geo<SPARSE, false, MI, NI>::PER_CU)) gemm_k_major_kernel(GemmArgs g, typename Epi::Args ea) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  ClkSample cs;
+  cs.begin(g);
+  gemm_tile<SPARSE, Epi, false, 0, MI, NI, TR>(g, ea, smem, blockIdx.x);
+  cs.end(g);
+}
+
 // A dense and a sparse GEMM (same epilogue type, separate arguments, same N and K) in one launch, for one weight gradient or for both
 // (`sets` = 2).  The split weight-gradient GEMMs use it (Sec. 2, "Optimization 1": a 2:4 GEMM over most hidden features plus a dense one
 // over the few that are not sparse enough): alone, the small dense GEMM would occupy a fraction of the CUs for as long as a full round
@@ -1019,7 +1172,7 @@ __global__ void __launch_bounds__(GEMM_THREADS, (Geo<SPARSE, F8, MI, NI>::PER_CU
 template <class Epi>
 struct PairSet { GemmArgs gd; typename Epi::Args ed; GemmArgs gs; typename Epi::Args es; };
 
-template <class Epi, bool F8 = false, int MI = 4, int NI = 4>
+template <class Epi, bool F8 = false, int MI = 4, int NI = 4, int TR = 0>
 __global__ void __launch_bounds__(GEMM_THREADS, (Geo<true, F8, MI, NI>::PER_CU)) gemm_pair_kernel(PairSet<Epi> a, PairSet<Epi> b, int sets, int nd_tiles,
                                                                                                  int ns_tiles) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -1030,13 +1183,13 @@ __global__ void __launch_bounds__(GEMM_THREADS, (Geo<true, F8, MI, NI>::PER_CU))
     GemmArgs g = a.gd;                   // (the sets differ in their operands only)
     typename Epi::Args e = a.ed;
     if (pid >= nd_tiles) { pid -= nd_tiles; g.A = b.gd.A; g.B = b.gd.B; e = b.ed; }
-    gemm_tile<false, Epi, F8, 0, MI, NI>(g, e, smem, pid);
+    gemm_tile<false, Epi, F8, 0, MI, NI, TR>(g, e, smem, pid);
   } else {
     pid -= sets * nd_tiles;
     GemmArgs g = a.gs;
     typename Epi::Args e = a.es;
     if (pid >= ns_tiles) { pid -= ns_tiles; g.A = b.gs.A; g.Ameta = b.gs.Ameta; g.B = b.gs.B; e = b.es; }
-    gemm_tile<true, Epi, F8, 0, MI, NI>(g, e, smem, pid);
+    gemm_tile<true, Epi, F8, 0, MI, NI, TR>(g, e, smem, pid);
   }
   cs.end(a.gs);
 }
@@ -1054,7 +1207,7 @@ struct EpiDuo {
     else EpiA::template run<MI, NI>(e.a, acc, m_lane, n_lane);
   }
 };
-template <bool SPARSE, class EpiA, class EpiB, bool F8, int MI, int NI>
+template <bool SPARSE, class EpiA, class EpiB, bool F8, int MI, int NI, int TR>
 __global__ void __launch_bounds__(GEMM_THREADS, (Geo<SPARSE, F8, MI, NI>::PER_CU)) gemm_duo_kernel(GemmArgs ga, typename EpiA::Args ea, int n_first,
                                                                                                   GemmArgs gb, typename EpiB::Args eb) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -1063,7 +1216,7 @@ __global__ void __launch_bounds__(GEMM_THREADS, (Geo<SPARSE, F8, MI, NI>::PER_CU
   GemmArgs g = ga;                       // (same M, N, K and operand forms)
   if (second) { g.A = gb.A; g.Ameta = gb.Ameta; g.B = gb.B; }
   const typename EpiDuo<EpiA, EpiB>::Args e{ea, eb, second};
-  gemm_tile<SPARSE, EpiDuo<EpiA, EpiB>, F8, 0, MI, NI>(g, e, smem, second ? bid - n_first : bid);
+  gemm_tile<SPARSE, EpiDuo<EpiA, EpiB>, F8, 0, MI, NI, TR>(g, e, smem, second ? bid - n_first : bid);
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -3,14 +3,14 @@
 
 namespace ffn24 {
 
-int launch_up_relu2(const void* W1t, const void* X, const float* b1, int T, int D, int F, void* H, void* Ht, unsigned long long* tele, hipStream_t s) {
-  GemmArgs g{W1t, nullptr, X, F, T, D, 1};
+int launch_up_relu2(const void* W1, int w1_form, const void* X, const float* b1, int T, int D, int F, void* H, void* Ht, unsigned long long* tele, hipStream_t s) {
+  GemmArgs g{W1, nullptr, X, F, T, D, w1_form == FORM_PANEL};
   if (tele) {
     EpiRelu2T<true>::Args eas{static_cast<__bf16*>(H), static_cast<__bf16*>(Ht), b1, F, T, tele};
-    return launch_gemm<false, EpiRelu2T<true>>(g, eas, s);
+    return w1_form == FORM_K_MAJOR ? launch_gemm<false, EpiRelu2T<true>, false, TR_A>(g, eas, s) : launch_gemm<false, EpiRelu2T<true>>(g, eas, s);
   }
   EpiRelu2::Args ea{static_cast<__bf16*>(H), static_cast<__bf16*>(Ht), b1, F, T, nullptr};
-  return launch_gemm<false, EpiRelu2>(g, ea, s);
+  return w1_form == FORM_K_MAJOR ? launch_gemm<false, EpiRelu2, false, TR_A>(g, ea, s) : launch_gemm<false, EpiRelu2>(g, ea, s);
 }
 
 int launch_dh_drelu(const void* W2, const void* dY, const void* H, int T, int D, int F, void* dZ, void* dZt, hipStream_t s) {

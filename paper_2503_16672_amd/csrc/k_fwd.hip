@@ -4,29 +4,30 @@
 
 namespace ffn24 {
 
-int launch_up_prune24(const void* W1t, const void* X, const float* b1, int T, int D, int F,
+int launch_up_prune24(const void* W1, int w1_form, const void* X, const float* b1, int T, int D, int F,
                       void* Hc, uint8_t* meta, void* Hdbg, uint32_t* nnz, unsigned long long* tele, const int* token_map, hipStream_t s) {
-  GemmArgs g{W1t, nullptr, X, F, T, D, 1, token_map};
+  GemmArgs g{W1, nullptr, X, F, T, D, w1_form == FORM_PANEL, token_map};
   EpiPrune24::Args ea{static_cast<__bf16*>(Hc), meta, static_cast<__bf16*>(Hdbg), b1, F, nullptr, nullptr};
   if (nnz || tele) {
     EpiPrune24T<true>::Args eas{static_cast<__bf16*>(Hc), meta, static_cast<__bf16*>(Hdbg), b1, F, nnz, tele};
-    return launch_gemm<false, EpiPrune24T<true>>(g, eas, s);
+    return w1_form == FORM_K_MAJOR ? launch_gemm<false, EpiPrune24T<true>, false, TR_A>(g, eas, s) : launch_gemm<false, EpiPrune24T<true>>(g, eas, s);
   }
-  return launch_gemm<false, EpiPrune24>(g, ea, s);
+  return w1_form == FORM_K_MAJOR ? launch_gemm<false, EpiPrune24, false, TR_A>(g, ea, s) : launch_gemm<false, EpiPrune24>(g, ea, s);
 }
 
-int launch_sp_rowmajor(const void* vals, const uint8_t* meta, int a_panel, const void* B, int b_panel, int M, int N, int K, void* C, hipStream_t s) {
-  GemmArgs g{vals, meta, B, M, N, K, a_panel, nullptr, b_panel};
+int launch_sp_rowmajor(const void* vals, const uint8_t* meta, int a_panel, const void* B, int b_form, int M, int N, int K, void* C, hipStream_t s) {
+  GemmArgs g{vals, meta, B, M, N, K, a_panel, nullptr, b_form == FORM_PANEL};
   EpiRowMajor::Args ea{static_cast<__bf16*>(C), N};
-  if (!a_panel && !b_panel && K >= ROWS_MIN_K) return launch_gemm_rows<EpiRowMajor>(g, ea, s);
+  if (b_form == FORM_K_MAJOR) return launch_gemm<true, EpiRowMajor, false, TR_B>(g, ea, s);
+  if (!a_panel && b_form == FORM_ROWS && K >= ROWS_MIN_K) return launch_gemm_rows<EpiRowMajor>(g, ea, s);
   return launch_gemm<true, EpiRowMajor>(g, ea, s);
 }
 
-int launch_sp_rowmajor_mapped(const void* vals, const uint8_t* meta, int a_panel, const void* B, int b_panel, int M, int N, int K, void* C,
+int launch_sp_rowmajor_mapped(const void* vals, const uint8_t* meta, int a_panel, const void* B, int b_form, int M, int N, int K, void* C,
                               const int* rowmap, hipStream_t s) {
-  GemmArgs g{vals, meta, B, M, N, K, a_panel, nullptr, b_panel};
+  GemmArgs g{vals, meta, B, M, N, K, a_panel, nullptr, b_form == FORM_PANEL};
   EpiRowMajorMapped::Args ea{static_cast<__bf16*>(C), N, rowmap};
-  return launch_gemm<true, EpiRowMajorMapped>(g, ea, s);
+  return b_form == FORM_K_MAJOR ? launch_gemm<true, EpiRowMajorMapped, false, TR_B>(g, ea, s) : launch_gemm<true, EpiRowMajorMapped>(g, ea, s);
 }
 
 }  // namespace ffn24

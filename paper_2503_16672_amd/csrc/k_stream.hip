@@ -840,8 +840,10 @@ __global__ void __launch_bounds__(256) panelise8_kernel(PaneliseJobs jobs) {
       const int r = (int)(i / per_row), cq = (int)(i % per_row), c = cq << 4;
       const int prow = cp.b_form ? b_panel_pos(r) : r;
       const size_t src = cp.rowmap ? (size_t)cp.rowmap[r] * per_row + cq : i;
-      st_stream(reinterpret_cast<u32x4*>(static_cast<uint8_t*>(cp.out) + a24_piece(prow, c >> 6, cp.C >> 6) * 64 + (c & 63)),
-                ld_stream(static_cast<const u32x4*>(cp.in) + src));
+      u32x4* out = reinterpret_cast<u32x4*>(static_cast<uint8_t*>(cp.out) + a24_piece(prow, c >> 6, cp.C >> 6) * 64 + (c & 63));
+      const u32x4* in = static_cast<const u32x4*>(cp.in) + src;
+      if (cp.keep) *out = *in;
+      else st_stream(out, ld_stream(in));
       return;
     }
     bid -= cp.blocks;

@@ -4,12 +4,18 @@
 
 namespace ffn24 {
 
-static GemmArgs wgrad_args(const void* A, const uint8_t* meta, const void* B, int F, int D, int T) { return GemmArgs{A, meta, B, F, D, T, 1, nullptr, 1}; }
+static GemmArgs wgrad_args(const void* A, const uint8_t* meta, const void* B, int F, int D, int T, int b_form = FORM_PANEL) {
+  return GemmArgs{A, meta, B, F, D, T, 1, nullptr, b_form == FORM_PANEL};
+}
 
-int launch_wgrad(const void* H, const void* Z, const uint8_t* meta, const void* dYt, const void* Xt, int F, int D, int T, void* dW2, void* dW1, hipStream_t s) {
-  const GemmArgs g2 = wgrad_args(H, meta, dYt, F, D, T), g1 = wgrad_args(Z, meta, Xt, F, D, T);
+int launch_wgrad(const void* H, const void* Z, const uint8_t* meta, const void* dYt, const void* Xt, int b_form, int F, int D, int T, void* dW2, void* dW1,
+                 hipStream_t s) {
+  const GemmArgs g2 = wgrad_args(H, meta, dYt, F, D, T, b_form), g1 = wgrad_args(Z, meta, Xt, F, D, T, b_form);
   const EpiRowMajor::Args e2{static_cast<__bf16*>(dW2), D};
   const EpiColMajor::Args e1{static_cast<__bf16*>(dW1), F};
+  if (b_form == FORM_K_MAJOR)
+    return meta ? launch_gemm_duo<true, EpiRowMajor, EpiColMajor, false, TR_B>(g2, e2, g1, e1, s)
+                : launch_gemm_duo<false, EpiRowMajor, EpiColMajor, false, TR_B>(g2, e2, g1, e1, s);
   return meta ? launch_gemm_duo<true, EpiRowMajor, EpiColMajor>(g2, e2, g1, e1, s) : launch_gemm_duo<false, EpiRowMajor, EpiColMajor>(g2, e2, g1, e1, s);
 }
 

@@ -40,33 +40,38 @@ __host__ __device__ constexpr int tele_index(int kind, int slot) { return (kind 
 // All return a hipError_t cast to int (0 = success); shapes must already be validated by the caller:
 // M % 256 == 0, N % 256 == 0, K % 64 == 0, 16-byte aligned pointers.  Every GEMM operand is K-contiguous.
 
-// up-projection with rows = hidden features: A = W1^T [F][D] in dense panel form, B = X [T][D]
+// Forms of a dense operand: row-major K-contiguous; the panel form (of A or of B) of gemm_core.hpp; k-major, a caller's [K][M] or [K][N] matrix as it
+// stands (bf16, read with the transposing LDS reads; 32-bit offsets inside it: see fits_k_major).  "b_panel" below: the first two, 0 or 1.
+enum { FORM_ROWS = 0, FORM_PANEL = 1, FORM_K_MAJOR = 2 };
+inline bool fits_k_major(int K, int cols) { return 2ull * (unsigned)K * (unsigned)cols < (1ull << 32); }
+
+// up-projection with rows = hidden features: A = W1^T [F][D] in dense panel form or W1 [D][F] k-major, B = X [T][D]
 // nnz (may be NULL): [F] per-feature non-zero counts, accumulated with atomics (zeroed by the caller)
 // token_map (may be NULL, also below): column n of the GEMM (position n inside the FFN) is token token_map[n] of X / dY
 // tele (may be NULL, also below): the telemetry slots (TELE_KINDS x TELE_SLOTS 64-bit counters, epilogues.hpp) the
 // launch adds its counts to
-int launch_up_prune24(const void* W1t, const void* X, const float* b1, int T, int D, int F,
+int launch_up_prune24(const void* W1, int w1_form, const void* X, const float* b1, int T, int D, int F,
                       void* Hc, uint8_t* meta, void* Hdbg, uint32_t* nnz, unsigned long long* tele, const int* token_map, hipStream_t s);
-int launch_up_relu2(const void* W1t, const void* X, const float* b1, int T, int D, int F, void* H, void* Ht, unsigned long long* tele, hipStream_t s);
+int launch_up_relu2(const void* W1, int w1_form, const void* X, const float* b1, int T, int D, int F, void* H, void* Ht, unsigned long long* tele, hipStream_t s);
 // C[M][N] = A24[M][K] * B[N][K]^T; a_panel: (vals, meta) are in panel form instead of row-major;
-// b_panel (also below): B is in the B panel form of gemm_core.hpp instead of row-major
-int launch_sp_rowmajor(const void* vals, const uint8_t* meta, int a_panel, const void* B, int b_panel, int M, int N, int K, void* C, hipStream_t s);
+// b_form (also below): the form of B
+int launch_sp_rowmajor(const void* vals, const uint8_t* meta, int a_panel, const void* B, int b_form, int M, int N, int K, void* C, hipStream_t s);
 // out[N][M] = (A24[M][K] * B[N][K]^T)^T
-int launch_sp_colmajor(const void* vals, const uint8_t* meta, int a_panel, const void* B, int b_panel, int M, int N, int K, void* Ct, hipStream_t s);
+int launch_sp_colmajor(const void* vals, const uint8_t* meta, int a_panel, const void* B, int b_form, int M, int N, int K, void* Ct, hipStream_t s);
 // dH = dY W2^T with rows = hidden features: A = W2 [F][D] in dense panel form, B = dY [T][D]; pointwise part fused
 int launch_dh_gather(const void* W2, const void* dY, const void* Hc, const uint8_t* meta, int T, int D, int F, void* dZc,
                      const int* token_map, hipStream_t s);
 // C[rowmap[m]][N] = (A24 * B^T)[m][N]: the result rows go back to their tokens
-int launch_sp_rowmajor_mapped(const void* vals, const uint8_t* meta, int a_panel, const void* B, int b_panel, int M, int N, int K, void* C,
+int launch_sp_rowmajor_mapped(const void* vals, const uint8_t* meta, int a_panel, const void* B, int b_form, int M, int N, int K, void* C,
                               const int* rowmap, hipStream_t s);
 int launch_dh_drelu(const void* W2, const void* dY, const void* H, int T, int D, int F, void* dZ, void* dZt, hipStream_t s);
 // split weight gradient (operands in panel form): rows [0, ns) from the sparse GEMM over (vals, meta) [ns][K], rows
-// [ns, ns + nd) from the dense GEMM over Ad [nd][K], both against B [N][K] (B panel form), one launch; row m goes to C[rowmap[m]][*]
-int launch_split_wgrad(const void* vals, const uint8_t* meta, int ns, const void* Ad, int nd, const void* B, int N, int K,
+// [ns, ns + nd) from the dense GEMM over Ad [nd][K], both against B [N][K] (b_form: B panel form or k-major), one launch; row m goes to C[rowmap[m]][*]
+int launch_split_wgrad(const void* vals, const uint8_t* meta, int ns, const void* Ad, int nd, const void* B, int b_form, int N, int K,
                        void* C, int ldc, const int* rowmap, hipStream_t s);
 // both weight gradients of a split step in one launch: dW2 from (H, Hd) and dYt, dW1 (as [F][D] rows, dW1t) from (Z, Zd) and Xt
-int launch_split_wgrads(const void* H, const void* Z, const uint8_t* meta, int ns, const void* Hd, const void* Zd, int nd, const void* dYt, const void* Xt, int N,
-                        int K, void* dW2, void* dW1t, int ldc, const int* rowmap, hipStream_t s);
+int launch_split_wgrads(const void* H, const void* Z, const uint8_t* meta, int ns, const void* Hd, const void* Zd, int nd, const void* dYt, const void* Xt, int b_form,
+                        int N, int K, void* dW2, void* dW1t, int ldc, const int* rowmap, hipStream_t s);
 int launch_split_wgrads_f8_rowwise(const void* H, const void* Z, const uint8_t* meta, int ns, const void* Hd, const void* Zd, int nd, const void* dYt,
                                    const void* Xt, int N, int K, const float* rs2, const float* cs2, const float* rs1, const float* cs1, void* dW2, void* dW1t,
                                    int ldc, const int* rowmap, hipStream_t s);
@@ -81,16 +86,17 @@ int launch_featurewise24_split(const void* Hc, const uint8_t* meta, const void* 
                                void* Hc_t, uint8_t* meta_t, void* dZc_t, void* Hdn_t, void* dZdn_t, unsigned long long* tele,
                                uint32_t* hmax, uint32_t* zmax, hipStream_t s);
 // both weight gradients of a step, in one launch where that helps: dW2 [F][D] and dW1 [D][F] from the transposed activation H and dZ Z
-// (2:4 along tokens with one metadata tensor, or dense: meta NULL), dYt and Xt; everything in panel form; fp8: a scale each, or
+// (2:4 along tokens with one metadata tensor, or dense: meta NULL), dYt and Xt; everything in panel form, or (b_form) dY and X themselves k-major; fp8: a scale each, or
 // a scale per row and per column each
-int launch_wgrad(const void* H, const void* Z, const uint8_t* meta, const void* dYt, const void* Xt, int F, int D, int T, void* dW2, void* dW1, hipStream_t s);
+int launch_wgrad(const void* H, const void* Z, const uint8_t* meta, const void* dYt, const void* Xt, int b_form, int F, int D, int T, void* dW2, void* dW1,
+                 hipStream_t s);
 int launch_wgrad_f8(const void* H, const void* Z, const uint8_t* meta, const void* dYt, const void* Xt, int F, int D, int T, float scale2, float scale1,
                     void* dW2, void* dW1, hipStream_t s);
 int launch_wgrad_f8_rowwise(const void* H, const void* Z, const uint8_t* meta, const void* dYt, const void* Xt, int F, int D, int T, const float* rs2,
                             const float* cs2, const float* rs1, const float* cs1, void* dW2, void* dW1, hipStream_t s);
 // dense GEMMs: A [M][K] (a_panel: in dense panel form), B [N][K]
-int launch_dense_rowmajor(const void* A, int a_panel, const void* B, int b_panel, int M, int N, int K, void* C, hipStream_t s);
-int launch_dense_colmajor(const void* A, int a_panel, const void* B, int b_panel, int M, int N, int K, void* Ct, hipStream_t s);
+int launch_dense_rowmajor(const void* A, int a_panel, const void* B, int b_form, int M, int N, int K, void* C, hipStream_t s);
+int launch_dense_colmajor(const void* A, int a_panel, const void* B, int b_form, int M, int N, int K, void* Ct, hipStream_t s);
 // fp8 e4m3 forward (per-tensor scales).  W1t8 [F][D] in dense panel form (64-byte pieces = 64 k), X8 [T][D];
 // compressed activation in the fp8 panel form (64 stored bytes + 16 metadata bytes per 128 k); bf16 results.
 // Hc16, meta16 (may be NULL): also the kept values before quantisation (bf16) and their metadata, in the bf16 panel form
@@ -177,14 +183,15 @@ int launch_unpanel(const void* src, int rows, int npanels, int piece_bytes, void
 // form, up to three word arrays cleared, one scale vector gathered
 struct PaneliseJobs {
   static constexpr int COPIES = 3, ZEROS = 3;
-  struct Copy { const void* in; int R, C; void* out; int b_form; const int* rowmap; unsigned blocks; } copy[COPIES] = {};
+  struct Copy { const void* in; int R, C; void* out; int b_form; const int* rowmap; unsigned blocks; bool keep; } copy[COPIES] = {};
   uint32_t* zero[ZEROS] = {};
   int zero_n[ZEROS] = {};
   const float* gather_src = nullptr; const int* gather_map = nullptr; float* gather_dst = nullptr; int gather_n = 0;
   int copies = 0, zeros = 0;   // (host side: slots in use)
-  // R x C bytes, C % 64 == 0, R % 256 == 0
-  void add_copy(const void* in, int R, int C, void* out, int b_form, const int* rowmap) {
-    copy[copies++] = Copy{in, R, C, out, b_form, rowmap, (unsigned)(((size_t)R * (C >> 4) + 255) / 256)};
+  // R x C bytes, C % 64 == 0, R % 256 == 0; keep: no streaming hints, the input is read again right away (the weights' copies: with the hints the
+  // GEMMs behind them took longer, T 1024 D 1024 F 4096 down-projection 20.8 us against 15.2, and at T = F = 16384 D 4096 the copies, 100 against 83)
+  void add_copy(const void* in, int R, int C, void* out, int b_form, const int* rowmap, bool keep = false) {
+    copy[copies++] = Copy{in, R, C, out, b_form, rowmap, (unsigned)(((size_t)R * (C >> 4) + 255) / 256), keep};
   }
   void add_zero(uint32_t* p, int n) { zero[zeros] = p; zero_n[zeros++] = n; }
   void set_gather(const float* src, const int* map, int n, float* dst) { gather_src = src; gather_map = map; gather_n = n; gather_dst = dst; }

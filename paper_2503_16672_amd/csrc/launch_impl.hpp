@@ -10,10 +10,12 @@ namespace ffn24 {
 template <class E, class = void> struct epi_cost { static constexpr EpiCost value = EPI_PLAIN; };
 template <class E> struct epi_cost<E, std::void_t<decltype(E::COST)>> { static constexpr EpiCost value = E::COST; };
 
-template <bool SPARSE, class Epi, bool F8, int PROBE, int MI, int NI>
+template <bool SPARSE, class Epi, bool F8, int PROBE, int MI, int NI, int TR = 0>
 static int launch_tile(const GemmArgs& g, const typename Epi::Args& ea, hipStream_t s) {
   using G = Geo<SPARSE, F8, MI, NI>;
-  auto kern = gemm_kernel<SPARSE, Epi, F8, PROBE, MI, NI>;
+  void (*kern)(GemmArgs, typename Epi::Args);
+  if constexpr (TR != 0) kern = gemm_k_major_kernel<SPARSE, Epi, TR, MI, NI>;
+  else kern = gemm_kernel<SPARSE, Epi, F8, PROBE, MI, NI>;
   static std::atomic<bool> configured[MAX_DEVICES] = {};
   if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), G::LDS_TOTAL, configured)) return rc;
   int nblocks = (g.M / G::BM) * (g.N / G::BN);
@@ -22,16 +24,16 @@ static int launch_tile(const GemmArgs& g, const typename Epi::Args& ea, hipStrea
   return (int)hipGetLastError();
 }
 
-template <bool SPARSE, class Epi, bool F8 = false>
+template <bool SPARSE, class Epi, bool F8 = false, int TR = 0>
 static int launch_gemm(const GemmArgs& g_in, const typename Epi::Args& ea, hipStream_t s) {
   GemmArgs g = g_in;
   g.clk = tl_gemm_clk;
   switch (pick_tile(SPARSE, F8, epi_cost<Epi>::value, g.M, g.N, g.K)) {
-    case 0: return launch_tile<SPARSE, Epi, F8, 0, 4, 4>(g, ea, s);
-    case 1: return launch_tile<SPARSE, Epi, F8, 0, 4, 2>(g, ea, s);
-    case 2: return launch_tile<SPARSE, Epi, F8, 0, 2, 2>(g, ea, s);
-    case 3: return launch_tile<SPARSE, Epi, F8, 0, 2, 1>(g, ea, s);
-    default: return launch_tile<SPARSE, Epi, F8, 0, 1, 1>(g, ea, s);
+    case 0: return launch_tile<SPARSE, Epi, F8, 0, 4, 4, TR>(g, ea, s);
+    case 1: return launch_tile<SPARSE, Epi, F8, 0, 4, 2, TR>(g, ea, s);
+    case 2: return launch_tile<SPARSE, Epi, F8, 0, 2, 2, TR>(g, ea, s);
+    case 3: return launch_tile<SPARSE, Epi, F8, 0, 2, 1, TR>(g, ea, s);
+    default: return launch_tile<SPARSE, Epi, F8, 0, 1, 1, TR>(g, ea, s);
   }
 }
 
@@ -58,10 +60,10 @@ static int launch_gemm_rows(const GemmArgs& g, const typename Epi::Args& ea, hip
   }
 }
 
-template <bool SPARSE, class EpiA, class EpiB, bool F8, int MI, int NI>
+template <bool SPARSE, class EpiA, class EpiB, bool F8, int MI, int NI, int TR>
 static int launch_duo_tile(const GemmArgs& ga, const typename EpiA::Args& ea, const GemmArgs& gb, const typename EpiB::Args& eb, hipStream_t s) {
   using G = Geo<SPARSE, F8, MI, NI>;
-  auto kern = gemm_duo_kernel<SPARSE, EpiA, EpiB, F8, MI, NI>;
+  auto kern = gemm_duo_kernel<SPARSE, EpiA, EpiB, F8, MI, NI, TR>;
   static std::atomic<bool> configured[MAX_DEVICES] = {};
   if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), G::LDS_TOTAL, configured)) return rc;
   const int n = (ga.M / G::BM) * (ga.N / G::BN);
@@ -70,28 +72,28 @@ static int launch_duo_tile(const GemmArgs& ga, const typename EpiA::Args& ea, co
 }
 
 // Two GEMMs of the same M, N, K and operand forms (gemm_duo_kernel), with the tile that suits both together.
-template <bool SPARSE, class EpiA, class EpiB, bool F8 = false>
+template <bool SPARSE, class EpiA, class EpiB, bool F8 = false, int TR = 0>
 static int launch_gemm_duo(const GemmArgs& ga, const typename EpiA::Args& ea, const GemmArgs& gb, const typename EpiB::Args& eb, hipStream_t s) {
   const int tile = pick_tile(SPARSE, F8, EPI_PLAIN, ga.M, ga.N, ga.K, 2);
   const long long n = tile_count(TILES_SPARSE[0], ga.M, ga.N);
   if (tile == 0 && (n % CHIP_CUS == 0 || apart_is_better(F8, n, ga.K, 1))) {   // (whole rounds each: nothing to share)
-    const int rc = launch_tile<SPARSE, EpiA, F8, 0, 4, 4>(ga, ea, s);   // (the tile one of them takes alone, too)
-    return rc ? rc : launch_tile<SPARSE, EpiB, F8, 0, 4, 4>(gb, eb, s);
+    const int rc = launch_tile<SPARSE, EpiA, F8, 0, 4, 4, TR>(ga, ea, s);   // (the tile one of them takes alone, too)
+    return rc ? rc : launch_tile<SPARSE, EpiB, F8, 0, 4, 4, TR>(gb, eb, s);
   }
   switch (tile) {
-    case 0: return launch_duo_tile<SPARSE, EpiA, EpiB, F8, 4, 4>(ga, ea, gb, eb, s);
-    case 1: return launch_duo_tile<SPARSE, EpiA, EpiB, F8, 4, 2>(ga, ea, gb, eb, s);
-    case 2: return launch_duo_tile<SPARSE, EpiA, EpiB, F8, 2, 2>(ga, ea, gb, eb, s);
-    case 3: return launch_duo_tile<SPARSE, EpiA, EpiB, F8, 2, 1>(ga, ea, gb, eb, s);
-    default: return launch_duo_tile<SPARSE, EpiA, EpiB, F8, 1, 1>(ga, ea, gb, eb, s);
+    case 0: return launch_duo_tile<SPARSE, EpiA, EpiB, F8, 4, 4, TR>(ga, ea, gb, eb, s);
+    case 1: return launch_duo_tile<SPARSE, EpiA, EpiB, F8, 4, 2, TR>(ga, ea, gb, eb, s);
+    case 2: return launch_duo_tile<SPARSE, EpiA, EpiB, F8, 2, 2, TR>(ga, ea, gb, eb, s);
+    case 3: return launch_duo_tile<SPARSE, EpiA, EpiB, F8, 2, 1, TR>(ga, ea, gb, eb, s);
+    default: return launch_duo_tile<SPARSE, EpiA, EpiB, F8, 1, 1, TR>(ga, ea, gb, eb, s);
   }
 }
 
-template <class Epi, bool F8, int MI, int NI>
+template <class Epi, bool F8, int MI, int NI, int TR>
 static int launch_pair_tile(const PairSet<Epi>& a, const PairSet<Epi>& b, int sets, hipStream_t s) {
   using GS = Geo<true, F8, MI, NI>;
   using GD = Geo<false, F8, MI, NI>;
-  auto kern = gemm_pair_kernel<Epi, F8, MI, NI>;
+  auto kern = gemm_pair_kernel<Epi, F8, MI, NI, TR>;
   constexpr int lds = GS::LDS_TOTAL > GD::LDS_TOTAL ? GS::LDS_TOTAL : GD::LDS_TOTAL;
   static std::atomic<bool> configured[MAX_DEVICES] = {};
   if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds, configured)) return rc;
@@ -101,20 +103,20 @@ static int launch_pair_tile(const PairSet<Epi>& a, const PairSet<Epi>& b, int se
 }
 
 // a dense and a sparse GEMM in one launch (gemm_pair_kernel), or two such sets of the same sizes; b is read with sets == 2 only
-template <class Epi, bool F8 = false>
+template <class Epi, bool F8 = false, int TR = 0>
 static int launch_gemm_pair(const PairSet<Epi>& a_in, const PairSet<Epi>& b, int sets, hipStream_t s) {
   if (sets == 2 && apart_is_better(F8, tile_count(TILES_DENSE[0], a_in.gd.M + a_in.gs.M, a_in.gs.N), a_in.gs.K, 2)) {
-    const int rc = launch_gemm_pair<Epi, F8>(a_in, a_in, 1, s);
-    return rc ? rc : launch_gemm_pair<Epi, F8>(b, b, 1, s);
+    const int rc = launch_gemm_pair<Epi, F8, TR>(a_in, a_in, 1, s);
+    return rc ? rc : launch_gemm_pair<Epi, F8, TR>(b, b, 1, s);
   }
   PairSet<Epi> a = a_in;
   a.gs.clk = tl_gemm_clk;
   switch (pick_pair_tile(F8, a.gd.M, a.gs.M, a.gs.N, a.gs.K, sets)) {
-    case 0: return launch_pair_tile<Epi, F8, 4, 4>(a, b, sets, s);
-    case 1: return launch_pair_tile<Epi, F8, 4, 2>(a, b, sets, s);
-    case 2: return launch_pair_tile<Epi, F8, 2, 2>(a, b, sets, s);
-    case 3: return launch_pair_tile<Epi, F8, 2, 1>(a, b, sets, s);
-    default: return launch_pair_tile<Epi, F8, 1, 1>(a, b, sets, s);
+    case 0: return launch_pair_tile<Epi, F8, 4, 4, TR>(a, b, sets, s);
+    case 1: return launch_pair_tile<Epi, F8, 4, 2, TR>(a, b, sets, s);
+    case 2: return launch_pair_tile<Epi, F8, 2, 2, TR>(a, b, sets, s);
+    case 3: return launch_pair_tile<Epi, F8, 2, 1, TR>(a, b, sets, s);
+    default: return launch_pair_tile<Epi, F8, 1, 1, TR>(a, b, sets, s);
   }
 }
 

@@ -1,0 +1,84 @@
+"""bf16 GEMMs that read a caller's matrix with k as its slow dimension (W1, W2, X, dY where they lie): the same products in the same order as from
+the re-arranged copies, so the results are equal bit for bit.  Sizes: every block tile in the up-projection, the down-projection and the weight
+gradients, with one to many stages of the ring."""
+from contextlib import closing
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2503_16672_amd import ffn24
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [(256, 256, 512), (256, 512, 2048), (768, 512, 2048), (1280, 768, 3072), (2048, 1024, 4096), (2048, 1280, 5120), (4096, 2048, 8192), (8192, 2048, 8192)]
+
+
+def _inputs(T, D, F):
+    g = torch.Generator(device="cuda").manual_seed(T + D + F)
+    new = lambda *s, scale=1.0: torch.empty(s, device="cuda").normal_(generator=g).mul_(scale).to(torch.bfloat16)
+    return new(T, D), new(D, F, scale=D ** -0.5), torch.full((F,), -1.2, device="cuda"), new(F, D, scale=F ** -0.5), new(T, D)
+
+
+def _equal(a, b):
+    return all(torch.equal(x.view(torch.int16), y.view(torch.int16)) for x, y in zip(a, b, strict=True))
+
+
+def _over(a, shape):
+    """A matrix of `shape` and a copy of `a` that share their first bytes."""
+    n = shape[0] * shape[1]
+    buf = torch.zeros(max(a.numel(), n), dtype=torch.bfloat16, device="cuda")
+    buf[:a.numel()] = a.reshape(-1)
+    return buf[:n].view(shape), buf[:a.numel()].view(a.shape)
+
+
+@pytest.mark.parametrize("T,D,F", SIZES)
+@pytest.mark.parametrize("split", [0, 256])
+def test_block(T, D, F, split):
+    if split and (F < 1024 or T > 2048):
+        pytest.skip("a quarter of the features at most; the pair's tiles are covered by the smaller sizes")
+    X, W1, b1, W2, dY = _inputs(T, D, F)
+    with closing(ffn24.Context(T, D, F, ffn24.FFN24_TRAINING | ffn24.FFN24_PERMUTE | (ffn24.FFN24_SPLIT if split else 0), ffn24.FFN24_BF16)) as c:
+        if split:
+            c.set_split(split)
+        c.set_token_permutation(np.arange(T, dtype=np.int32))       # gathers nothing, but takes the transposed copies
+        c.prepare_weights(W1, W2)
+        want = [c.ffn24_fwd(X, None, b1, None).clone(), *c.ffn24_bwd(dY)]
+        c.set_token_permutation(None)
+        for profiling in (False, True):                             # with it the weight gradients are launches of their own
+            c.set_profiling(profiling)
+            got = [c.ffn24_fwd(X, W1, b1, W2), *c.ffn24_bwd(dY)]
+            torch.cuda.synchronize()
+            assert _equal(want, got), profiling
+        c.set_profiling(False)
+        # an output over an input takes the copies
+        Y, W2o = _over(W2, (T, D))
+        assert _equal(want[:1], [c.ffn24_fwd(X, W1, b1, W2o, Y)])
+        c.ffn24_fwd(X, W1, b1, W2)
+        dW1, dYo = _over(dY, (D, F))
+        assert _equal(want[1:], c.ffn24_bwd(dYo, out=(torch.empty_like(X), dW1, torch.empty_like(W2))))
+
+
+@pytest.mark.parametrize("T,D,F", SIZES)
+def test_dense(T, D, F):
+    X, W1, b1, W2, dY = _inputs(T, D, F)
+    with closing(ffn24.Context(T, D, F, ffn24.FFN24_TRAINING | ffn24.FFN24_DENSE, ffn24.FFN24_BF16)) as c:
+        c.prepare_weights(W1, W2)
+        dW1, dYo = _over(dY, (D, F))
+        want = [c.ffn_fwd(X, None, b1, None).clone(), *c.ffn_bwd(dYo, out=(torch.empty_like(X), dW1, torch.empty_like(W2)))]
+        for profiling in (False, True):
+            c.set_profiling(profiling)
+            got = [c.ffn_fwd(X, W1, b1, W2), *c.ffn_bwd(dY)]
+            torch.cuda.synchronize()
+            assert _equal(want, got), profiling
+
+
+@pytest.mark.parametrize("T,D,F", SIZES[:5])
+def test_static(T, D, F):
+    X, W1, b1, W2, _ = _inputs(T, D, F)
+    with closing(ffn24.Context(T, D, F, 0, ffn24.FFN24_BF16)) as c:
+        c.prepare_weights(W1, W2)
+        want = [c.ffn24_fwd(X, None, b1, None)]
+        assert _equal(want, [ffn24.ffn24_fwd_static(X, W1, b1, W2, torch.empty_like(X))])
+        Y, W2o = _over(W2, (T, D))
+        assert _equal(want, [ffn24.ffn24_fwd_static(X, W1, b1, W2o, Y)])
