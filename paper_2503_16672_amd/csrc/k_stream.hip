@@ -11,6 +11,9 @@ namespace ffn24 {
 // hint (measured on a plain copy: 6.0-6.5 TB/s with it, 5.6-6.1 without).
 template <class T> __device__ __forceinline__ T ld_stream(const T* p) { return __builtin_nontemporal_load(p); }
 template <class T> __device__ __forceinline__ void st_stream(T* p, T v) { __builtin_nontemporal_store(v, p); }
+// What the next kernels read again is stored without it: the caches then still hold some of it (operands brought into another form: row-wise fp8
+// step at T = F = 8192, D = 2048 773 -> 765 us, T = F = 16384, D = 4096 in bf16 the same).
+template <class T> __device__ __forceinline__ void st_keep(T* p, T v) { *p = v; }
 
 // key of a bf16 storage word at position i of its group: ((magnitude << 2) | (3 - i)) << 1 | sign.
 // The sign rides in the lowest bit, below the position, so it never takes part in the ordering.
@@ -188,6 +191,9 @@ __global__ void __launch_bounds__(256) featurewise24_kernel(const uint16_t* __re
   const int f0 = blockIdx.x * FW_FEAT, t_first = blockIdx.y * FW_TOK * tiles;
   const int tid = threadIdx.x;
   const bool has_z = dZc != nullptr;
+  // small operands stay in the caches for the weight gradients (T 1280 D 768 F 3072: step 68.1 -> 66.9 us); large ones would push out what else is
+  // there (T = F = 16384, D 4096: 7346 -> 7397; T = F = 8192 772 -> 774)
+  const bool keep = PANEL && (size_t)T * F <= 1 << 24;
   const int tok = tid >> 2, ch = tid & 3;            // in: 16 features of a token
   const int oct = tid & 7, word = tid >> 3;          // out: 8 tokens of features fa and fa + 8
   const int fa = ((word >> 3) << 4) | (word & 7);
@@ -286,9 +292,17 @@ __global__ void __launch_bounds__(256) featurewise24_kernel(const uint16_t* __re
       }
       const size_t piece = PANEL ? a24_piece(orow[b], t >> 6, T >> 6) : (size_t)orow[b] * (T >> 6) + (t >> 6);
       const size_t vo = piece * 32 + 4 * oct, mo = piece * 8 + oct;
-      st_stream(reinterpret_cast<u32x2*>(Hc_t + vo), u32x2{hp[b][0], hp[b][1]});
-      if (has_z) st_stream(reinterpret_cast<u32x2*>(dZc_t + vo), u32x2{zp[b][0], zp[b][1]});
-      st_stream(meta_t + mo, (uint8_t)(b ? nib >> 16 : nib));
+      const u32x2 hv2 = {hp[b][0], hp[b][1]}, zv2 = {zp[b][0], zp[b][1]};
+      const uint8_t mv2 = (uint8_t)(b ? nib >> 16 : nib);
+      if (keep) {
+        st_keep(reinterpret_cast<u32x2*>(Hc_t + vo), hv2);
+        if (has_z) st_keep(reinterpret_cast<u32x2*>(dZc_t + vo), zv2);
+        st_keep(meta_t + mo, mv2);
+      } else {
+        st_stream(reinterpret_cast<u32x2*>(Hc_t + vo), hv2);
+        if (has_z) st_stream(reinterpret_cast<u32x2*>(dZc_t + vo), zv2);
+        st_stream(meta_t + mo, mv2);
+      }
     }
   }
   if (hmax) {
@@ -682,7 +696,7 @@ __device__ __forceinline__ void transpose_tile(const TransposeJob& job, int tile
       for (int i = 0; i < 2; i++) {
         const int r = r0 + 2 * rp + i;
         const int prow = in_panel_b ? b_panel_pos(r) : r;
-        st_stream(reinterpret_cast<u32x4*>(in_panel + a24_piece(prow, c >> 5, C >> 5) * 32 + (c & 31)), v[pass][i]);
+        st_keep(reinterpret_cast<u32x4*>(in_panel + a24_piece(prow, c >> 5, C >> 5) * 32 + (c & 31)), v[pass][i]);
       }
     }
     uint32_t* dst = sT + ((rp + 4 * rot) & 31);
@@ -701,8 +715,8 @@ __device__ __forceinline__ void transpose_tile(const TransposeJob& job, int tile
     const uint32_t* src = sT + c * TR_LDW + 4 * ((q + (c >> 6)) & 7);
     u32x4 o = {src[0], src[1], src[2], src[3]};
     const int r = r0 + 8 * q;
-    if constexpr (OUT_FORM == 1) st_stream(reinterpret_cast<u32x4*>(out + a24_piece(c0 + c, r >> 5, R >> 5) * 32 + (r & 31)), o);
-    else if constexpr (OUT_FORM == 2) st_stream(reinterpret_cast<u32x4*>(out + a24_piece(b_panel_pos(c0 + c), r >> 5, R >> 5) * 32 + (r & 31)), o);
+    if constexpr (OUT_FORM == 1) st_keep(reinterpret_cast<u32x4*>(out + a24_piece(c0 + c, r >> 5, R >> 5) * 32 + (r & 31)), o);
+    else if constexpr (OUT_FORM == 2) st_keep(reinterpret_cast<u32x4*>(out + a24_piece(b_panel_pos(c0 + c), r >> 5, R >> 5) * 32 + (r & 31)), o);
     else st_stream(reinterpret_cast<u32x4*>(out + (size_t)(c0 + c) * R + r), o);
   }
 }
@@ -769,7 +783,7 @@ __device__ __forceinline__ void transpose8_tile(const TransposeJob& job, int til
     for (int i = 0; i < 4; i++) {
       const int r = r0 + 4 * rq + i;
       const int prow = in_panel_b ? b_panel_pos(r) : r;
-      st_stream(reinterpret_cast<u32x4*>(in_panel + a24_piece(prow, c >> 6, C >> 6) * 64 + (c & 63)), v[i]);
+      st_keep(reinterpret_cast<u32x4*>(in_panel + a24_piece(prow, c >> 6, C >> 6) * 64 + (c & 63)), v[i]);
     }
   }
   const int rot = ch >> 2;                   // (c >> 6) & 3 of every column this work item holds
@@ -793,8 +807,8 @@ __device__ __forceinline__ void transpose8_tile(const TransposeJob& job, int til
     const uint32_t* src = reinterpret_cast<const uint32_t*>(sT) + c * (T8_LD / 4) + 4 * ((q + p) & 3);
     u32x4 o = {src[0], src[1], src[2], src[3]};
     const int r = r0 + 16 * q;
-    if constexpr (OUT_FORM == 1) st_stream(reinterpret_cast<u32x4*>(out + a24_piece(c0 + c, r >> 6, R >> 6) * 64 + (r & 63)), o);
-    else if constexpr (OUT_FORM == 2) st_stream(reinterpret_cast<u32x4*>(out + a24_piece(b_panel_pos(c0 + c), r >> 6, R >> 6) * 64 + (r & 63)), o);
+    if constexpr (OUT_FORM == 1) st_keep(reinterpret_cast<u32x4*>(out + a24_piece(c0 + c, r >> 6, R >> 6) * 64 + (r & 63)), o);
+    else if constexpr (OUT_FORM == 2) st_keep(reinterpret_cast<u32x4*>(out + a24_piece(b_panel_pos(c0 + c), r >> 6, R >> 6) * 64 + (r & 63)), o);
     else st_stream(reinterpret_cast<u32x4*>(out + (size_t)(c0 + c) * R + r), o);
   }
 }
@@ -843,7 +857,7 @@ __global__ void __launch_bounds__(256) panelise8_kernel(PaneliseJobs jobs) {
       u32x4* out = reinterpret_cast<u32x4*>(static_cast<uint8_t*>(cp.out) + a24_piece(prow, c >> 6, cp.C >> 6) * 64 + (c & 63));
       const u32x4* in = static_cast<const u32x4*>(cp.in) + src;
       if (cp.keep) *out = *in;
-      else st_stream(out, ld_stream(in));
+      else st_keep(out, ld_stream(in));
       return;
     }
     bid -= cp.blocks;
