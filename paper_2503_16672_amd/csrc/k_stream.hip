@@ -1042,8 +1042,11 @@ int launch_quantise_rows(const void* Hc16, const uint8_t* meta16, const uint32_t
 // zero; codes = e4m3(x / scale), row-major [R][C].
 
 // Per row, the whole row held in registers between the maximum and the quantisation: LANES work items per row (a wave, or the workgroup
-// for rows beyond 4096 values), up to NV 16-byte pieces each, all requested before the first is used.
-template <int LANES, int NV>
+// for rows beyond 4096 values), up to NV 16-byte pieces each, all requested before the first is used.  KEEP: without the streaming hint, for a matrix
+// that the caches hold and that is quantised per column as well (one call after the other, 8192 x 4096: 55.5 -> 52.6 us, and the rows alone
+// 18.8 -> 17.9; larger ones lose, 16384 x 4096 35.3 -> 37.8, 16384 x 16384 129 -> 144).
+constexpr int64_t KEEP_VALUES = 1 << 25;
+template <int LANES, int NV, bool KEEP>
 __global__ void __launch_bounds__(256) quantise_bf16_rows_kernel(const u32x4* __restrict__ X, int64_t R, int C8, u32x2* __restrict__ codes,
                                                                  float* __restrict__ scales) {
   const int t = threadIdx.x & (LANES - 1);
@@ -1054,7 +1057,7 @@ __global__ void __launch_bounds__(256) quantise_bf16_rows_kernel(const u32x4* __
 #pragma unroll
   for (int i = 0; i < NV; i++) {
     const int c = t + LANES * i;
-    v[i] = c < C8 ? ld_stream(row + c) : u32x4{0u, 0u, 0u, 0u};
+    v[i] = c < C8 ? (KEEP ? row[c] : ld_stream(row + c)) : u32x4{0u, 0u, 0u, 0u};
   }
   u16x8 mv = {};
 #pragma unroll
@@ -1102,14 +1105,13 @@ __global__ void __launch_bounds__(256) quantise_bf16_long_rows_kernel(const u32x
   for (int c = lane; c < C8; c += 64) st_stream(out + c, quantise8(row[c], d));
 }
 
-// Per column, three kernels: (1) the largest magnitude words of every column over slabs of rows, (2) their maximum over the slabs and the
+// Per column of a matrix of more than HELD_ROWS rows, three kernels: (1) the largest magnitude words of every column over slabs of rows, (2) their maximum over the slabs and the
 // scale, (3) the codes.  A workgroup of (1) and (3) covers 64 pieces of 8 columns x 4 interleaved row groups, so that a wave's load is
 // 1024 contiguous bytes of a row and QC_UNROLL rows are in flight per work item.  The slab maxima [slab][C] (16-bit words) stand in the
-// codes buffer, which (3) overwrites afterwards: 2 C ceil(R / QC_ROWS) bytes of its R C.  With a single slab (1) writes the scales.
+// codes buffer, which (3) overwrites afterwards: 2 C ceil(R / QC_ROWS) bytes of its R C.
 constexpr int QC_UNROLL = 16, QC_ROWS = 4 * QC_UNROLL, QC_SLABS = 256;
 
-__global__ void __launch_bounds__(256) colmax_bf16_kernel(const u32x4* __restrict__ X, int64_t R, int C8, int64_t slab_rows, u16x8* __restrict__ part,
-                                                          float* __restrict__ scales) {
+__global__ void __launch_bounds__(256) colmax_bf16_kernel(const u32x4* __restrict__ X, int64_t R, int C8, int64_t slab_rows, u16x8* __restrict__ part) {
   __shared__ u16x8 sm[4][64];
   const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
   const int c = blockIdx.x * 64 + lane;
@@ -1131,11 +1133,7 @@ __global__ void __launch_bounds__(256) colmax_bf16_kernel(const u32x4* __restric
   __syncthreads();
   if (grp != 0 || c >= C8) return;
   m = __builtin_elementwise_max(__builtin_elementwise_max(m, sm[1][lane]), __builtin_elementwise_max(sm[2][lane], sm[3][lane]));
-  if (part) part[(size_t)blockIdx.y * C8 + c] = m;
-  else {
-#pragma unroll
-    for (int j = 0; j < 8; j++) scales[8 * c + j] = scale_of_max(m[j]);
-  }
+  part[(size_t)blockIdx.y * C8 + c] = m;
 }
 
 // (2): 16 pieces of 8 columns x 16 groups of slabs per workgroup
@@ -1178,26 +1176,88 @@ __global__ void __launch_bounds__(256) quantise_bf16_cols_kernel(const u32x4* __
   }
 }
 
+// Per column, the whole strip of W pieces of 8 columns held in registers between the maximum and the quantisation (one launch, X read once): a
+// workgroup of 1024, W neighbouring work items a row, NV rows each.  A strip's rows are parts of lines; strips next to each other go to the same
+// XCD, whose L2 puts the lines together.  Short matrices, whose launches cost as much as their bytes (a call, three launches -> one, us): 300 x 256
+// 12.7 -> 8.0, 1024 x 1024 12.2 -> 7.6, 1397 x 544 19.4 -> 8.6, 1536 x 16384 25.6 -> 21.4.  A tall one has fewer workgroups than the chip
+// has CUs, or too many registers: 2048 x 4096 13.4 -> 14.4, 4096 x 1024 12.1 -> 15.8, 8192 x 12896 93 -> 130.
+constexpr int HELD_ROWS = 1536;
+template <int W, int NV>
+__global__ void __launch_bounds__(1024) quantise_bf16_held_cols_kernel(const u32x4* __restrict__ X, int R, int C8, u32x2* __restrict__ codes,
+                                                                       float* __restrict__ scales) {
+  constexpr int GROUPS = 1024 / W;
+  __shared__ u16x8 sm[16][W];
+  const int per_xcd = (int)gridDim.x >> 3, strip = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+  const int ci = threadIdx.x & (W - 1), c = strip * W + ci, r0 = threadIdx.x / W;
+  const bool in = c < C8;
+  const u32x4* col = X + c;
+  u32x4 v[NV];
+#pragma unroll
+  for (int i = 0; i < NV; i++) {
+    const int r = r0 + GROUPS * i;
+    v[i] = in && r < R ? col[(size_t)r * C8] : u32x4{0u, 0u, 0u, 0u};
+  }
+  u16x8 m = {};
+#pragma unroll
+  for (int i = 0; i < NV; i++) m = max_mag(m, v[i]);
+#pragma unroll
+  for (int sft = W; sft < 64; sft <<= 1) {
+    u32x4 o, w = __builtin_bit_cast(u32x4, m);
+#pragma unroll
+    for (int d = 0; d < 4; d++) o[d] = (uint32_t)__shfl_xor((int)w[d], sft, 64);
+    m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x8, o));
+  }
+  if ((threadIdx.x & 63) < W) sm[threadIdx.x >> 6][ci] = m;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 16; k++) m = __builtin_elementwise_max(m, sm[k][ci]);
+  if (!in) return;
+  ExactDiv d[8];
+#pragma unroll
+  for (int j = 0; j < 8; j++) {
+    const float s = scale_of_max(m[j]);
+    if (r0 == 0) scales[8 * c + j] = s;
+    d[j] = ExactDiv(s);
+  }
+  u32x2* out = codes + c;
+#pragma unroll
+  for (int i = 0; i < NV; i++) {
+    const int r = r0 + GROUPS * i;
+    if (r < R) st_keep(out + (size_t)r * C8, quantise8(v[i], d));
+  }
+}
+
+template <int W, int NV>
+static int launch_held_cols(const u32x4* X, int64_t R, int C8, u32x2* codes, float* scales, hipStream_t s) {
+  const unsigned per_xcd = (unsigned)(((C8 + W - 1) / W + 7) / 8);
+  hipLaunchKernelGGL((quantise_bf16_held_cols_kernel<W, NV>), dim3(8 * per_xcd), dim3(1024), 0, s, X, (int)R, C8, codes, scales);
+  return (int)hipGetLastError();
+}
+
 int launch_quantise_bf16(const void* X, int64_t R, int64_t C, int axis, void* codes, float* scales, hipStream_t s) {
   const int C8 = (int)(C / 8);
   const u32x4* x = static_cast<const u32x4*>(X);
   u32x2* out = static_cast<u32x2*>(codes);
   if (axis == 1) {
-    auto kern = C8 <= 64 * 2 ? quantise_bf16_rows_kernel<64, 2> : C8 <= 64 * 8 ? quantise_bf16_rows_kernel<64, 8>
-              : C8 <= 256 * 8 ? quantise_bf16_rows_kernel<256, 8> : quantise_bf16_long_rows_kernel;
+    const bool keep = R * C <= KEEP_VALUES;
+    auto kern = C8 <= 64 * 2 ? (keep ? quantise_bf16_rows_kernel<64, 2, true> : quantise_bf16_rows_kernel<64, 2, false>)
+              : C8 <= 64 * 8 ? (keep ? quantise_bf16_rows_kernel<64, 8, true> : quantise_bf16_rows_kernel<64, 8, false>)
+              : C8 <= 256 * 8 ? (keep ? quantise_bf16_rows_kernel<256, 8, true> : quantise_bf16_rows_kernel<256, 8, false>) : quantise_bf16_long_rows_kernel;
     const int per = C8 > 64 * 8 && C8 <= 256 * 8 ? 1 : 4;   // rows per workgroup
     // 2^24 rows, the most there can be, of a workgroup each are 2^32 work items, one more than a grid dimension may have: two halves then
     const int64_t groups = (R + per - 1) / per, most = 1 << 23;
     hipLaunchKernelGGL(kern, dim3((unsigned)(groups < most ? groups : most), (unsigned)((groups + most - 1) / most)), dim3(256), 0, s, x, R, C8, out, scales);
     return (int)hipGetLastError();
   }
+  if (R <= 512) return launch_held_cols<4, 2>(x, R, C8, out, scales, s);
+  if (R <= HELD_ROWS) return launch_held_cols<4, 6>(x, R, C8, out, scales, s);
   // at most QC_SLABS slabs, each a whole number of QC_ROWS rows
   const int64_t slab_rows = ((R + QC_SLABS - 1) / QC_SLABS + QC_ROWS - 1) / QC_ROWS * QC_ROWS;
   const int slabs = (int)((R + slab_rows - 1) / slab_rows);
-  u16x8* part = slabs > 1 ? static_cast<u16x8*>(codes) : nullptr;
+  u16x8* part = static_cast<u16x8*>(codes);
   const unsigned nc = (unsigned)((C8 + 63) / 64);
-  hipLaunchKernelGGL(colmax_bf16_kernel, dim3(nc, (unsigned)slabs), dim3(256), 0, s, x, R, C8, slab_rows, part, scales);
-  if (part) hipLaunchKernelGGL(col_scales_kernel, dim3((unsigned)((C8 + 15) / 16)), dim3(256), 0, s, part, C8, slabs, scales);
+  hipLaunchKernelGGL(colmax_bf16_kernel, dim3(nc, (unsigned)slabs), dim3(256), 0, s, x, R, C8, slab_rows, part);
+  hipLaunchKernelGGL(col_scales_kernel, dim3((unsigned)((C8 + 15) / 16)), dim3(256), 0, s, part, C8, slabs, scales);
   hipLaunchKernelGGL(quantise_bf16_cols_kernel, dim3(nc * (unsigned)((R + QC_ROWS - 1) / QC_ROWS)), dim3(256), 0, s, x, R, C8, scales, out);
   return (int)hipGetLastError();
 }
