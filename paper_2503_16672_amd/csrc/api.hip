@@ -803,10 +803,15 @@ int ffn24_bwd(ffn24_ctx* c, const void* dY, void* dX, void* dW1, void* dW2, void
   // the forward's two counts stay; the feature-wise one belongs to this backward
   if (c->tele && launch_zero32(reinterpret_cast<uint32_t*>(c->tele + tele_index(TELE_KEPT_FEAT, 0)), 2 * TELE_SLOTS * TELE_STRIDE, s)) return FFN24_ERR_HIP;
   { Timed t(c, K_DH, s);  if (t.done(launch_dh_gather(c->W2p, dY, c->Hc, c->meta, T, D, F, c->dZc, perm, s))) return FFN24_ERR_HIP; }
-  { Timed t(c, K_DX, s);
-    int rc1 = perm ? launch_sp_rowmajor_mapped(c->dZc, c->meta, 1, c->W1p, 1, T, D, F, dX, perm, s) : launch_sp_rowmajor(c->dZc, c->meta, 1, c->W1p, 1, T, D, F, dX, s);
-    if (t.done(rc1)) return FFN24_ERR_HIP; }
   const bool split = (c->flags & FFN24_SPLIT) && c->n_dense > 0;
+  const bool together = !perm && !split && !c->tele && !c->profiling;   // dX and the feature-wise re-compression (below)
+  if (together) {
+    if (launch_dx_featurewise(c->Hc, c->meta, c->dZc, c->W1p, T, D, F, dX, c->Hc_t, c->meta_t, c->dZc_t, s)) return FFN24_ERR_HIP;
+  } else {
+    Timed t(c, K_DX, s);
+    int rc1 = perm ? launch_sp_rowmajor_mapped(c->dZc, c->meta, 1, c->W1p, 1, T, D, F, dX, perm, s) : launch_sp_rowmajor(c->dZc, c->meta, 1, c->W1p, 1, T, D, F, dX, s);
+    if (t.done(rc1)) return FFN24_ERR_HIP;
+  }
   if (split) {
     // Sec. 2, "Optimization 1": the n_dense least sparse features are kept out of the feature-wise 2:4; their rows
     // of both weight gradients come from dense GEMMs, all others from the sparse ones
@@ -826,7 +831,7 @@ int ffn24_bwd(ffn24_ctx* c, const void* dY, void* dX, void* dW1, void* dW2, void
     { Timed t(c, K_TR_DW1, s); if (t.done(launch_transpose(c->dW1t, F, D, dW1, s))) return FFN24_ERR_HIP; }
     return FFN24_OK;
   }
-  { Timed t(c, K_FW, s);  if (t.done(launch_featurewise24(c->Hc, c->meta, c->dZc, T, F, c->Hc_t, c->meta_t, c->dZc_t, c->tele, s))) return FFN24_ERR_HIP; }
+  if (!together) { Timed t(c, K_FW, s);  if (t.done(launch_featurewise24(c->Hc, c->meta, c->dZc, T, F, c->Hc_t, c->meta_t, c->dZc_t, c->tele, s))) return FFN24_ERR_HIP; }
   if (c->tele && (rc = tele_snapshot(c, 1, s))) return rc;
   if (act_pass(c, w, dY, perm, s)) return FFN24_ERR_HIP;
   if (!c->profiling) return launch_wgrad(c->Hc_t, c->dZc_t, c->meta_t, w.dY, w.X, w.form, F, D, T, dW2, dW1, s) ? FFN24_ERR_HIP : FFN24_OK;   // (profiling times the two by themselves)

@@ -1163,6 +1163,15 @@ __global__ void __launch_bounds__(GEMM_THREADS, (Geo<SPARSE, false, MI, NI>::PER
   cs.end(g);
 }
 
+// A GEMM and other work that neither waits for it nor it for: the workgroups from n_tiles on run Side (stream_core.hpp), on what the tiles leave of the chip.
+template <bool SPARSE, class Epi, int TR, int MI, int NI, class Side>
+__global__ void __launch_bounds__(GEMM_THREADS, (Geo<SPARSE, false, MI, NI>::PER_CU)) gemm_side_kernel(GemmArgs g, typename Epi::Args ea, int n_tiles,
+                                                                                                        typename Side::Args sa) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  if ((int)blockIdx.x < n_tiles) gemm_tile<SPARSE, Epi, false, 0, MI, NI, TR>(g, ea, smem, blockIdx.x);
+  else Side::run(sa, blockIdx.x - n_tiles, smem);
+}
+
 // A dense and a sparse GEMM (same epilogue type, separate arguments, same N and K) in one launch, for one weight gradient or for both
 // (`sets` = 2).  The split weight-gradient GEMMs use it (Sec. 2, "Optimization 1": a 2:4 GEMM over most hidden features plus a dense one
 // over the few that are not sparse enough): alone, the small dense GEMM would occupy a fraction of the CUs for as long as a full round

@@ -23,6 +23,19 @@ int launch_sp_rowmajor(const void* vals, const uint8_t* meta, int a_panel, const
   return launch_gemm<true, EpiRowMajor>(g, ea, s);
 }
 
+int launch_dx_featurewise(const void* Hc, const uint8_t* meta, const void* dZc, const void* W1p, int T, int D, int F, void* dX, void* Hc_t, uint8_t* meta_t, void* dZc_t,
+                          hipStream_t s) {
+  const GemmArgs g{dZc, meta, W1p, T, D, F, 1, nullptr, 1};
+  const EpiRowMajor::Args ea{static_cast<__bf16*>(dX), D};
+  const SideFeaturewise::Args sa{static_cast<const uint16_t*>(Hc), meta, static_cast<const uint16_t*>(dZc), T, F, static_cast<uint16_t*>(Hc_t), meta_t,
+                                 static_cast<uint16_t*>(dZc_t)};
+  bool rode = false;
+  int rc = launch_gemm_side<true, EpiRowMajor, 0, SideFeaturewise>(g, ea, sa, (unsigned)(F / FW_FEAT) * (unsigned)(T / FW_TOK), &rode, s);
+  if (rode) return rc;
+  rc = launch_gemm<true, EpiRowMajor>(g, ea, s);
+  return rc ? rc : launch_featurewise24(Hc, meta, dZc, T, F, Hc_t, meta_t, dZc_t, nullptr, s);
+}
+
 int launch_sp_rowmajor_mapped(const void* vals, const uint8_t* meta, int a_panel, const void* B, int b_form, int M, int N, int K, void* C,
                               const int* rowmap, hipStream_t s) {
   GemmArgs g{vals, meta, B, M, N, K, a_panel, nullptr, b_form == FORM_PANEL};

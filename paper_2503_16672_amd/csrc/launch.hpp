@@ -174,6 +174,9 @@ int launch_sparsify24_bytes(const void* H8, int64_t rows, int64_t cols, void* va
 // inputs and outputs in panel form (the library's own buffers); _rows: row-major (a caller's), T % 128 == 0, F % 64 == 0
 int launch_featurewise24(const void* Hc, const uint8_t* meta, const void* dZc, int T, int F,
                          void* Hc_t, uint8_t* meta_t, void* dZc_t, unsigned long long* tele, hipStream_t s);
+// the dX GEMM (W1p in B panel form) and then the feature-wise re-compression (launch_featurewise24), or both in one launch where that helps
+int launch_dx_featurewise(const void* Hc, const uint8_t* meta, const void* dZc, const void* W1p, int T, int D, int F, void* dX, void* Hc_t, uint8_t* meta_t, void* dZc_t,
+                          hipStream_t s);
 int launch_featurewise24_rows(const void* Hc, const uint8_t* meta, const void* dZc, int T, int F, void* Hc_t, uint8_t* meta_t, void* dZc_t, hipStream_t s);
 // out[0] = elements, out[1..3] = the sums of the telemetry slots (non-zero, kept token-wise, kept feature-wise), out[4] = path
 int launch_tele_sum(const unsigned long long* tele, long long elements, long long path, long long* out, hipStream_t s);

@@ -2,6 +2,7 @@
 #pragma once
 #include "epilogues.hpp"
 #include "launch.hpp"
+#include "stream_core.hpp"
 #include "tile_rule.hpp"
 
 namespace ffn24 {
@@ -37,6 +38,30 @@ static int launch_gemm(const GemmArgs& g_in, const typename Epi::Args& ea, hipSt
   }
 }
 
+template <bool SPARSE, class Epi, int TR, int MI, int NI, class Side>
+static int launch_side_tile(const GemmArgs& g, const typename Epi::Args& ea, const typename Side::Args& sa, unsigned side_blocks, hipStream_t s) {
+  using G = Geo<SPARSE, false, MI, NI>;
+  static_assert(G::LDS_TOTAL >= FW_LDS, "what a side job needs");
+  auto kern = gemm_side_kernel<SPARSE, Epi, TR, MI, NI, Side>;
+  static std::atomic<bool> configured[MAX_DEVICES] = {};
+  if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), G::LDS_TOTAL, configured)) return rc;
+  const int n = (g.M / G::BM) * (g.N / G::BN);
+  hipLaunchKernelGGL(kern, dim3((unsigned)n + side_blocks), dim3(GEMM_THREADS), G::LDS_TOTAL, s, g, ea, n, sa);
+  return (int)hipGetLastError();
+}
+
+// A bf16 GEMM with other work in the same launch (gemm_side_kernel) where side_rides says so; *rode tells.
+template <bool SPARSE, class Epi, int TR, class Side>
+static int launch_gemm_side(const GemmArgs& g, const typename Epi::Args& ea, const typename Side::Args& sa, unsigned side_blocks, bool* rode, hipStream_t s) {
+  const int tile = pick_tile(SPARSE, false, epi_cost<Epi>::value, g.M, g.N, g.K);
+  *rode = side_rides(SPARSE, tile, g.M, g.N, g.K);
+  if (!*rode) return 0;
+  switch (tile) {
+    case 2: return launch_side_tile<SPARSE, Epi, TR, 2, 2, Side>(g, ea, sa, side_blocks, s);
+    case 3: return launch_side_tile<SPARSE, Epi, TR, 2, 1, Side>(g, ea, sa, side_blocks, s);
+    default: return launch_side_tile<SPARSE, Epi, TR, 1, 1, Side>(g, ea, sa, side_blocks, s);
+  }
+}
 template <class Epi, int MI, int NI, bool SHIFT>
 static int launch_rows_tile(const GemmArgs& g, const typename Epi::Args& ea, hipStream_t s) {
   using G = GeoRows<MI, NI>;

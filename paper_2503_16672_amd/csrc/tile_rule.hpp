@@ -67,6 +67,14 @@ inline bool apart_is_better(bool f8, long long n, int K, int min_rounds) {
   return n >= min_rounds * CHIP_CUS && n % CHIP_CUS != 0 && both == 2 * one && (f8 ? K : 2 * K) >= 6144;
 }
 
+// The feature-wise re-compression in one launch with the dX GEMM (M x N, reduction K; the re-compression goes over M x K): where the tiles, of a kind that
+// shares a CU, leave places free from the start, and the GEMM is short.  Apart, together, whole steps (us, T D F): 256 512 2048 35.6, 33.9; 1536 512
+// 2048 46.7, 45.0; 4096 512 1024 51.0, 49.5; 768 768 3072 59.3, 58.1; 1280 768 3072 65.9, 65.4; 1024 1024 4096 77.8, 77.8; beyond the line 1024 2048 4096
+// 115.8, 119.9; 2048 1024 4096 115, 119; 256 2048 8192 130, 134.
+inline bool side_rides(bool sparse, int tile, int M, int N, int K) {
+  return tile >= 2 && tile_count(sparse ? TILES_SPARSE[tile] : TILES_DENSE[tile], M, N) <= CHIP_CUS && (long long)M * K <= 1 << 22 && N <= 1024;
+}
+
 // The tile of a dense and a sparse GEMM in one launch (same N and K, the dense tiles first), `sets` times: all tiles over the CUs, but no
 // less than the dense ones take by themselves (their epilogue is a plain store, and their tiles share CUs with sparse ones instead of
 // running in full rounds: the time per k of single launches).  The two parts make the estimate rougher, so a
