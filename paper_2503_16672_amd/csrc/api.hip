@@ -630,7 +630,7 @@ int ffn24_fwd(ffn24_ctx* c, const void* X, const void* W1, const float* b1, cons
     { Timed t(c, K_UP, s);
       if (t.done(launch_up_prune24_f8_rowwise(c->W1t, c->Xp8, b1, T, D, F, sx, c->rsw1, c->Hc16, c->meta16, c->Hdbg, c->rowmax, nnz, s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_QUANT, s);
-      if (t.done(launch_quantise_rows(c->Hc16, c->meta16, c->rowmax, T, F, c->Hc, c->meta, c->rsh, s))) return FFN24_ERR_HIP; }
+      if (t.done(launch_quantise_rows(QuantJobs().add(c->Hc16, c->meta16, c->rowmax, T, F, c->Hc, c->meta, c->rsh), s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_DOWN, s);
       int rc1 = perm ? launch_sp_rowmajor_f8_rowwise_mapped(c->Hc, c->meta, c->W2t, 1, T, D, F, c->rsh, c->rsw2, Y, perm, s)
                      : launch_sp_rowmajor_f8_rowwise(c->Hc, c->meta, c->W2t, 1, T, D, F, c->rsh, c->rsw2, Y, s);
@@ -722,26 +722,29 @@ int ffn24_bwd_rowwise(ffn24_ctx* c, const ffn24_rowwise_bwd_operands* op, void* 
   { Timed t(c, K_PANEL_W, s); if (t.done(launch_panelise8(pre, s))) return FFN24_ERR_HIP; }
   { Timed t(c, K_DH, s);
     if (t.done(launch_dh_gather_f8_rowwise(c->W2rp, c->dYp8, c->Hc16, c->meta16, T, D, F, op->sw2_f, sdy_t, c->dZc16, c->rowmax_dz, s))) return FFN24_ERR_HIP; }
+  const bool split = (c->flags & FFN24_SPLIT) && c->n_dense > 0;
+  const int nd = split ? c->n_dense : 0, ns = F - nd;
   { Timed t(c, K_QUANT_DZ, s);
-    if (t.done(launch_quantise_rows(c->dZc16, c->meta16, c->rowmax_dz, T, F, c->dZc, c->meta, c->sdz_t, s))) return FFN24_ERR_HIP; }
+    const QuantJobs dz = QuantJobs().add(c->dZc16, c->meta16, c->rowmax_dz, T, F, c->dZc, c->meta, c->sdz_t);
+    if (t.done(split && !c->profiling ? launch_quantise_rows_partition(dz, c->nnz, F, nd, T, c->row_of_feat, c->feat_of_row, s)
+                                      : launch_quantise_rows(dz, s))) return FFN24_ERR_HIP; }
   { Timed t(c, K_DX, s);
     int rc1 = perm ? launch_sp_rowmajor_f8_rowwise_mapped(c->dZc, c->meta, op->W1_8c, 0, T, D, F, c->sdz_t, op->sw1_d, dX, perm, s)
                    : launch_sp_rowmajor_f8_rowwise(c->dZc, c->meta, op->W1_8c, 0, T, D, F, c->sdz_t, op->sw1_d, dX, s);
     if (t.done(rc1)) return FFN24_ERR_HIP; }
-  if ((c->flags & FFN24_SPLIT) && c->n_dense > 0) {
+  if (split) {
     // Sec. 2, "Optimization 1" on the row-wise recipe: the n_dense least sparse features keep the token-wise mask only; every
     // row of the permuted feature space (sparse rows first) gets its own scale, the sparse rows are quantised in compressed form,
     // the dense ones as plain rows, and each weight gradient is one launch of a sparse and a dense fp8 GEMM
-    const int nd = c->n_dense, ns = F - nd;
-    { Timed t(c, K_PART, s); if (t.done(launch_split_partition(c->nnz, F, nd, T, c->row_of_feat, c->feat_of_row, s))) return FFN24_ERR_HIP; }
+    if (c->profiling) { Timed t(c, K_PART, s); if (t.done(launch_split_partition(c->nnz, F, nd, T, c->row_of_feat, c->feat_of_row, s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_FW, s);
       if (t.done(launch_featurewise24_split(c->Hc16, c->meta16, c->dZc16, T, F, c->row_of_feat, ns, c->Hct16, c->meta_t16, c->dZct16, c->Hdn_t, c->dZdn_t,
                                             nullptr, c->hmax, c->zmax, s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_QUANT_T, s);
-      int rc1 = launch_quantise_rows(c->Hct16, c->meta_t16, c->hmax, ns, T, c->Hc_t, c->meta_t, c->sh_f, s);
-      if (!rc1) rc1 = launch_quantise_rows(c->dZct16, c->meta_t16, c->zmax, ns, T, c->dZc_t, c->meta_t, c->sdz_f, s);
-      if (!rc1) rc1 = launch_quantise_rows_dense(c->Hdn_t, c->hmax + ns, nd, T, c->Hdn8_t, c->sh_f + ns, s);
-      if (t.done(rc1 ? rc1 : launch_quantise_rows_dense(c->dZdn_t, c->zmax + ns, nd, T, c->dZdn8_t, c->sdz_f + ns, s))) return FFN24_ERR_HIP; }
+      QuantJobs q;
+      q.add(c->Hct16, c->meta_t16, c->hmax, ns, T, c->Hc_t, c->meta_t, c->sh_f).add(c->dZct16, c->meta_t16, c->zmax, ns, T, c->dZc_t, c->meta_t, c->sdz_f);
+      q.add_dense(c->Hdn_t, c->hmax + ns, nd, T, c->Hdn8_t, c->sh_f + ns).add_dense(c->dZdn_t, c->zmax + ns, nd, T, c->dZdn8_t, c->sdz_f + ns);
+      if (t.done(launch_quantise_rows(q, s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_TR_ACT, s);
       if (t.done(launch_transpose8_acts(op->dY8c, op->X8c, T, D, c->dYt, nullptr, c->Xt, perm, s))) return FFN24_ERR_HIP; }
     if (!c->profiling) {   // (profiling times the two by themselves)
@@ -759,8 +762,8 @@ int ffn24_bwd_rowwise(ffn24_ctx* c, const ffn24_rowwise_bwd_operands* op, void* 
   { Timed t(c, K_FW, s);
     if (t.done(launch_featurewise24_rowmax(c->Hc16, c->meta16, c->dZc16, T, F, c->Hct16, c->meta_t16, c->dZct16, c->hmax, c->zmax, s))) return FFN24_ERR_HIP; }
   { Timed t(c, K_QUANT_T, s);
-    int rc1 = launch_quantise_rows(c->Hct16, c->meta_t16, c->hmax, F, T, c->Hc_t, c->meta_t, c->sh_f, s);
-    if (t.done(rc1 ? rc1 : launch_quantise_rows(c->dZct16, c->meta_t16, c->zmax, F, T, c->dZc_t, c->meta_t, c->sdz_f, s))) return FFN24_ERR_HIP; }
+    if (t.done(launch_quantise_rows(QuantJobs().add(c->Hct16, c->meta_t16, c->hmax, F, T, c->Hc_t, c->meta_t, c->sh_f)
+                                        .add(c->dZct16, c->meta_t16, c->zmax, F, T, c->dZc_t, c->meta_t, c->sdz_f), s))) return FFN24_ERR_HIP; }
   { Timed t(c, K_TR_ACT, s);
     if (t.done(launch_transpose8_acts(op->dY8c, op->X8c, T, D, c->dYt, nullptr, c->Xt, perm, s))) return FFN24_ERR_HIP; }
   if (!c->profiling) return launch_wgrad_f8_rowwise(c->Hc_t, c->dZc_t, c->meta_t, c->dYt, c->Xt, F, D, T, c->sh_f, op->sdy_d, c->sdz_f, op->sx_d, dW2, dW1, s) ? FFN24_ERR_HIP : FFN24_OK;   // (profiling times the two by themselves)
@@ -862,7 +865,7 @@ int ffn_fwd(ffn24_ctx* c, const void* X, const void* W1, const float* b1, const 
     { Timed t(c, KD_UP, s);
       if (t.done(launch_up_relu2_f8_rowwise(c->W1t, c->Xp8, b1, T, D, F, c->rsx, c->rsw1, c->Hd16, c->rowmax, c->Hdt16, s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_QUANT, s);
-      if (t.done(launch_quantise_rows_dense(c->Hd16, c->rowmax, T, F, c->Hd, c->rsh, s))) return FFN24_ERR_HIP; }
+      if (t.done(launch_quantise_rows(QuantJobs().add_dense(c->Hd16, c->rowmax, T, F, c->Hd, c->rsh), s))) return FFN24_ERR_HIP; }
     { Timed t(c, KD_DOWN, s);
       if (t.done(launch_dense_rowmajor_f8_rowwise(c->Hd, c->W2t, 1, T, D, F, c->rsh, c->rsw2, Y, s))) return FFN24_ERR_HIP; }
     if (c->flags & FFN24_TRAINING) { c->X = X; c->have_fwd_dense = 1; }
@@ -908,14 +911,14 @@ int ffn_bwd_rowwise(ffn24_ctx* c, const ffn24_rowwise_bwd_operands* op, void* dX
   { Timed t(c, KD_DH, s);
     if (t.done(launch_dh_drelu_f8_rowwise(c->W2rp, c->dYp8, c->Hd16, T, D, F, op->sw2_f, op->sdy_t, c->dZd16, c->dZdt16, c->rowmax_dz, s))) return FFN24_ERR_HIP; }
   { Timed t(c, K_QUANT_DZ, s);
-    if (t.done(launch_quantise_rows_dense(c->dZd16, c->rowmax_dz, T, F, c->dZd, c->sdz_t, s))) return FFN24_ERR_HIP; }
+    if (t.done(launch_quantise_rows(QuantJobs().add_dense(c->dZd16, c->rowmax_dz, T, F, c->dZd, c->sdz_t), s))) return FFN24_ERR_HIP; }
   { Timed t(c, KD_DX, s);
     if (t.done(launch_dense_rowmajor_f8_rowwise(c->dZd, c->W1cp, 1, T, D, F, c->sdz_t, op->sw1_d, dX, s))) return FFN24_ERR_HIP; }
   { Timed t(c, K_QUANT_T, s);      // per-feature maxima of the two transposed bf16 operands, then their quantisation
     int rc1 = launch_rowmax_dense(c->Hdt16, F, T, c->hmax, s);
     if (!rc1) rc1 = launch_rowmax_dense(c->dZdt16, F, T, c->zmax, s);
-    if (!rc1) rc1 = launch_quantise_rows_dense(c->Hdt16, c->hmax, F, T, c->Hd_t, c->sh_f, s);
-    if (t.done(rc1 ? rc1 : launch_quantise_rows_dense(c->dZdt16, c->zmax, F, T, c->dZd_t, c->sdz_f, s))) return FFN24_ERR_HIP; }
+    if (t.done(rc1 ? rc1 : launch_quantise_rows(QuantJobs().add_dense(c->Hdt16, c->hmax, F, T, c->Hd_t, c->sh_f).add_dense(c->dZdt16, c->zmax, F, T, c->dZd_t, c->sdz_f), s)))
+      return FFN24_ERR_HIP; }
   { Timed t(c, K_TR_ACT, s);
     if (t.done(launch_transpose8_acts(op->dY8c, op->X8c, T, D, c->dYt, nullptr, c->Xt, nullptr, s))) return FFN24_ERR_HIP; }
   if (!c->profiling) return launch_wgrad_f8_rowwise(c->Hd_t, c->dZd_t, nullptr, c->dYt, c->Xt, F, D, T, c->sh_f, op->sdy_d, c->sdz_f, op->sx_d, dW2, dW1, s) ? FFN24_ERR_HIP : FFN24_OK;   // (profiling times the two by themselves)

@@ -328,12 +328,13 @@ int launch_featurewise24_split(const void* Hc, const uint8_t* meta, const void* 
 // padding the lanes' runs would start a multiple of 32 words apart, all in two banks.  The rows are first written over the counts
 // in LDS and leave in feature order, so that the stores to row_of_feat are whole lines and those to feat_of_row nearly so.
 constexpr int PART_LDS_FEATS = 32768, PART_BINS = 2048;   // one workgroup of 1024: two bins a thread
+constexpr int PART_SHARED_FEATS = 16384;                   // in a launch with other work: two workgroups a CU
 __device__ __forceinline__ int part_slot(int f) { return f + (f >> 5); }
 
+// (a workgroup of 1024; s_nnz: F counts if they fit)
 template <bool IN_LDS>
-__global__ void __launch_bounds__(1024) split_partition_kernel(const uint32_t* __restrict__ nnz_g, int F, int n_dense, uint32_t max_count,
-                                                               int* __restrict__ row_of_feat, int* __restrict__ feat_of_row) {
-  extern __shared__ uint32_t s_nnz[];                // F counts if they fit
+__device__ __forceinline__ void split_partition(uint32_t* s_nnz, const uint32_t* __restrict__ nnz_g, int F, int n_dense, uint32_t max_count,
+                                                int* __restrict__ row_of_feat, int* __restrict__ feat_of_row) {
   __shared__ uint32_t s_part[16];
   __shared__ int s_bin, s_above;
   __shared__ uint32_t s_hist[PART_BINS];
@@ -418,6 +419,13 @@ __global__ void __launch_bounds__(1024) split_partition_kernel(const uint32_t* _
       feat_of_row[row] = f;
     }
   }
+}
+
+template <bool IN_LDS>
+__global__ void __launch_bounds__(1024) split_partition_kernel(const uint32_t* __restrict__ nnz, int F, int n_dense, uint32_t max_count,
+                                                               int* __restrict__ row_of_feat, int* __restrict__ feat_of_row) {
+  extern __shared__ uint32_t s_nnz[];
+  split_partition<IN_LDS>(s_nnz, nnz, F, n_dense, max_count, row_of_feat, feat_of_row);
 }
 
 int launch_split_partition(const uint32_t* nnz, int F, int n_dense, int max_count, int* row_of_feat, int* feat_of_row, hipStream_t s) {
@@ -794,22 +802,69 @@ int launch_featurewise24_f8(const void* Hc8, const uint8_t* meta, const void* dZ
 // a wave reads whole contiguous kilobytes; a lane's 8 codes of either input piece are exchanged with its neighbour's, so that each
 // stores 16 bytes and the wave a contiguous kilobyte again.  One output piece per lane and workgroups in memory order (a
 // quarter of a block of 256 rows each, then the next panel).  The stores are plain: the next kernel reads the codes.
+// A launch takes up to four matrices (QuantJobs): the operands of one stage of a step, whose launches by themselves end one after the other.
 template <bool META>
-__global__ void __launch_bounds__(256) quantise_rows_kernel(const u32x4* __restrict__ H16, const u32x2* __restrict__ meta16,
-                                                            const uint32_t* __restrict__ rowmax, int np8, u32x4* __restrict__ H8,
-                                                            u32x2* __restrict__ meta8, float* __restrict__ sh) {
-  const int c = threadIdx.x & 3, j = blockIdx.x >> 2, t = blockIdx.y * 256 + 64 * (blockIdx.x & 3) + (threadIdx.x >> 2);
+__device__ __forceinline__ void quantise_rows_block(const QuantJobs::Job& job, unsigned bid, int tid) {
+  const u32x4* __restrict__ H16 = static_cast<const u32x4*>(job.H16);
+  u32x4* __restrict__ H8 = static_cast<u32x4*>(job.H8);
+  const int np8 = job.np8;
+  const unsigned bx = bid % (4u * (unsigned)np8), by = bid / (4u * (unsigned)np8);
+  const int c = tid & 3, j = (int)(bx >> 2), t = (int)by * 256 + 64 * (int)(bx & 3) + (tid >> 2);
   const size_t pin = a24_piece(t, 2 * j, 2 * np8), pout = a24_piece(t, j, np8);
   const u32x4 v0 = ld_stream(H16 + pin * 4 + c), v1 = ld_stream(H16 + (pin + 256) * 4 + c);
-  if (META && c < 2) meta8[pout * 2 + c] = ld_stream(meta16 + pin + 256 * c);
-  const float s = scale_of_max(rowmax[t]);
-  if (j == 0 && c == 0) sh[t] = s;
+  if (META && c < 2) reinterpret_cast<u32x2*>(job.meta8)[pout * 2 + c] = ld_stream(reinterpret_cast<const u32x2*>(job.meta16) + pin + 256 * c);
+  const float s = scale_of_max(job.rowmax[t]);
+  if (j == 0 && c == 0) job.sh[t] = s;
   const ExactDiv d[1] = {ExactDiv(s)};
   const u32x2 q0 = quantise8(v0, d), q1 = quantise8(v1, d);
   const bool odd = c & 1;                              // even lanes store of the first input piece, odd ones of the second
   const u32x2 keep = odd ? q1 : q0, send = odd ? q0 : q1;
   const uint32_t r0 = (uint32_t)__shfl_xor((int)send[0], 1, 64), r1 = (uint32_t)__shfl_xor((int)send[1], 1, 64);
   H8[pout * 4 + 2 * odd + (c >> 1)] = odd ? u32x4{r0, r1, keep[0], keep[1]} : u32x4{keep[0], keep[1], r0, r1};
+}
+__device__ __forceinline__ void quantise_rows_at(const QuantJobs& jobs, unsigned bid, int tid) {
+#pragma unroll
+  for (int k = 0; k < QuantJobs::JOBS; k++) {
+    const QuantJobs::Job& job = jobs.job[k];
+    if (bid < job.blocks) {
+      if (job.meta16) quantise_rows_block<true>(job, bid, tid);
+      else quantise_rows_block<false>(job, bid, tid);
+      return;
+    }
+    bid -= job.blocks;
+  }
+}
+__global__ void __launch_bounds__(256) quantise_rows_kernel(QuantJobs jobs) { quantise_rows_at(jobs, blockIdx.x, threadIdx.x); }
+
+int launch_quantise_rows(const QuantJobs& jobs, hipStream_t s) {
+  unsigned blocks = 0;
+  for (const auto& job : jobs.job) blocks += job.blocks;
+  hipLaunchKernelGGL(quantise_rows_kernel, dim3(blocks), dim3(256), 0, s, jobs);
+  return (int)hipGetLastError();
+}
+
+// The same with the feature partition of the split, which everything after it waits for and which keeps one workgroup busy: it runs beside the
+// quantisation of dZ instead of after it (T = F = 8192, D = 2048: 10.6 us of a step).  Workgroups of 1024, as the partition's is: four of the
+// quantisation's 256 each.
+__global__ void __launch_bounds__(1024) quantise_rows_partition_kernel(QuantJobs jobs, const uint32_t* __restrict__ nnz, int F, int n_dense, uint32_t max_count,
+                                                                       int* __restrict__ row_of_feat, int* __restrict__ feat_of_row) {
+  extern __shared__ uint32_t s_nnz[];
+  if (blockIdx.x == 0) split_partition<true>(s_nnz, nnz, F, n_dense, max_count, row_of_feat, feat_of_row);
+  else quantise_rows_at(jobs, 4 * (blockIdx.x - 1) + (threadIdx.x >> 8), threadIdx.x & 255);
+}
+
+int launch_quantise_rows_partition(const QuantJobs& jobs, const uint32_t* nnz, int F, int n_dense, int max_count, int* row_of_feat, int* feat_of_row, hipStream_t s) {
+  if (F > PART_SHARED_FEATS) {
+    const int rc = launch_quantise_rows(jobs, s);
+    return rc ? rc : launch_split_partition(nnz, F, n_dense, max_count, row_of_feat, feat_of_row, s);
+  }
+  static std::atomic<bool> configured[MAX_DEVICES] = {};
+  if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(quantise_rows_partition_kernel), 4 * (PART_SHARED_FEATS + PART_SHARED_FEATS / 32), configured)) return rc;
+  unsigned blocks = 0;
+  for (const auto& job : jobs.job) blocks += job.blocks;
+  hipLaunchKernelGGL(quantise_rows_partition_kernel, dim3(1 + (blocks + 3) / 4), dim3(1024), 4 * ((size_t)F + (size_t)F / 32), s, jobs, nnz, F, n_dense,
+                     (uint32_t)max_count, row_of_feat, feat_of_row);
+  return (int)hipGetLastError();
 }
 
 // Largest magnitude word of every row of a bf16 matrix [R][C] in dense panel form (64-byte pieces of 32 k): rmax[r] is raised
@@ -836,23 +891,6 @@ __global__ void __launch_bounds__(256) rowmax_dense_kernel(const u32x4* __restri
 
 int launch_rowmax_dense(const void* X16, int R, int C, uint32_t* rmax, hipStream_t s) {
   hipLaunchKernelGGL(rowmax_dense_kernel, dim3(R / 256, ROWMAX_SLICES), dim3(256), 0, s, static_cast<const u32x4*>(X16), R, C, rmax);
-  return (int)hipGetLastError();
-}
-
-int launch_quantise_rows_dense(const void* H16, const uint32_t* rowmax, int T, int F, void* H8, float* sh, hipStream_t s) {
-  const int np8 = F >> 6;
-  hipLaunchKernelGGL(quantise_rows_kernel<false>, dim3((unsigned)(4 * np8), (unsigned)(T / 256)), dim3(256), 0, s,
-                     static_cast<const u32x4*>(H16), static_cast<const u32x2*>(nullptr), rowmax, np8, static_cast<u32x4*>(H8),
-                     static_cast<u32x2*>(nullptr), sh);
-  return (int)hipGetLastError();
-}
-
-int launch_quantise_rows(const void* Hc16, const uint8_t* meta16, const uint32_t* rowmax, int T, int F, void* Hc8, uint8_t* meta8, float* sh,
-                         hipStream_t s) {
-  const int np8 = F >> 7;
-  hipLaunchKernelGGL(quantise_rows_kernel<true>, dim3((unsigned)(4 * np8), (unsigned)(T / 256)), dim3(256), 0, s,
-                     static_cast<const u32x4*>(Hc16), reinterpret_cast<const u32x2*>(meta16), rowmax, np8, static_cast<u32x4*>(Hc8),
-                     reinterpret_cast<u32x2*>(meta8), sh);
   return (int)hipGetLastError();
 }
 

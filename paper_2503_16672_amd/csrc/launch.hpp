@@ -141,9 +141,23 @@ int launch_dh_drelu_f8_rowwise(const void* W2rp8, const void* dY8r, const void* 
                                void* dZ16, void* dZt16, uint32_t* rowmax, hipStream_t s);
 int launch_rowmax_dense(const void* X16, int R, int C, uint32_t* rmax, hipStream_t s);
 int launch_dense_colmajor_f8_rowwise(const void* A8, const void* B8, int M, int N, int K, const float* rs, const float* cs, void* Ct, hipStream_t s);
-int launch_quantise_rows_dense(const void* H16, const uint32_t* rowmax, int T, int F, void* H8, float* sh, hipStream_t s);
 int launch_dense_rowmajor_f8_rowwise(const void* A8, const void* B8, int b_panel, int M, int N, int K, const float* rs, const float* cs, void* C, hipStream_t s);
-int launch_quantise_rows(const void* Hc16, const uint8_t* meta16, const uint32_t* rowmax, int T, int F, void* Hc8, uint8_t* meta8, float* sh, hipStream_t s);
+// row-wise quantisation of up to four matrices in one launch: rows of F values, compressed (add: kept values and metadata) or plain (add_dense),
+// bf16 panel form to fp8 panel form; sh [T] is written
+struct QuantJobs {
+  static constexpr int JOBS = 4;
+  struct Job { const void* H16; const uint8_t* meta16; const uint32_t* rowmax; int np8; void* H8; uint8_t* meta8; float* sh; unsigned blocks; } job[JOBS] = {};
+  int jobs = 0;   // (host side: slots in use)
+  QuantJobs& add(const void* Hc16, const uint8_t* meta16, const uint32_t* rowmax, int T, int F, void* Hc8, uint8_t* meta8, float* sh) {
+    const int np8 = F >> (meta16 ? 7 : 6);
+    job[jobs++] = Job{Hc16, meta16, rowmax, np8, Hc8, meta8, sh, 4u * (unsigned)np8 * (unsigned)(T / 256)};
+    return *this;
+  }
+  QuantJobs& add_dense(const void* H16, const uint32_t* rowmax, int T, int F, void* H8, float* sh) { return add(H16, nullptr, rowmax, T, F, H8, nullptr, sh); }
+};
+int launch_quantise_rows(const QuantJobs& jobs, hipStream_t s);
+// ... and launch_split_partition, beside it where F is small enough
+int launch_quantise_rows_partition(const QuantJobs& jobs, const uint32_t* nnz, int F, int n_dense, int max_count, int* row_of_feat, int* feat_of_row, hipStream_t s);
 int launch_sp_rowmajor_f8_rowwise(const void* vals8, const uint8_t* meta, const void* B8, int b_panel, int M, int N, int K, const float* rs, const float* cs,
                                   void* C, hipStream_t s);
 // the same with result row m stored as row rowmap[m] (token permutation: the rows go back to their tokens; rs stays in row order)
