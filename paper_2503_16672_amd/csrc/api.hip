@@ -135,10 +135,11 @@ int tele_snapshot(ffn24_ctx* c, long long path, hipStream_t s) {
 // operand of the down-projection) and, when the context trains, W2 itself in panel form (A operand of the dH GEMM)
 // and W1 itself in B panel form (B operand of the dX GEMM) -- not in a row-wise fp8 context, whose backward takes the
 // caller's differently quantised weight codes instead (W1p, W2p are NULL there).
-int weight_pass(ffn24_ctx* c, const void* W1, const void* W2, hipStream_t s) {
+int weight_pass(ffn24_ctx* c, const void* W1, const void* W2, const PaneliseJobs* jobs, hipStream_t s) {   // jobs (may be NULL): fp8, in the same launch
   int D = (int)c->D, F = (int)c->F;
   Timed t(c, K_TR_W, s);
-  return t.done((c->f8 ? launch_transpose8_weights : launch_transpose_weights)(W1, W2, D, F, c->W1t, c->W1p, c->W2t, c->W2p, s)) ? FFN24_ERR_HIP : FFN24_OK;
+  return t.done(c->f8 ? launch_transpose8_weights(W1, W2, D, F, c->W1t, c->W1p, c->W2t, c->W2p, jobs, s)
+                      : launch_transpose_weights(W1, W2, D, F, c->W1t, c->W1p, c->W2t, c->W2p, s)) ? FFN24_ERR_HIP : FFN24_OK;
 }
 
 struct WgradActs { const void *dY, *X; int form; };
@@ -172,7 +173,7 @@ int resolve_weights16(ffn24_ctx* c, const void* W1, const void* W2, const void* 
         pre.add_copy(W1, D, 2 * F, c->W1p, 1, nullptr, true);
         pre.add_copy(W2, F, 2 * D, c->W2p, 0, nullptr, true);
       }
-    } else if (int rc = weight_pass(c, W1, W2, s)) {
+    } else if (int rc = weight_pass(c, W1, W2, nullptr, s)) {
       return rc;
     }
   } else if (!c->prepared) {
@@ -184,14 +185,22 @@ int resolve_weights16(ffn24_ctx* c, const void* W1, const void* W2, const void* 
   return t.done(any ? launch_panelise8(pre, s) : 0) ? FFN24_ERR_HIP : FFN24_OK;
 }
 
-// Weights of an fp8 forward call: both given (run the weight pass; prepared copies are gone after it), or both NULL (use
-// the copies ffn24_prepare_weights left).
-int resolve_weights(ffn24_ctx* c, const void* W1, const void* W2, hipStream_t s) {
-  if (!W1 && !W2) return c->prepared ? FFN24_OK : FFN24_ERR_STATE;
-  if (!W1 || !W2) return FFN24_ERR_NULL;
-  if (misaligned(W1) || misaligned(W2)) return FFN24_ERR_ALIGN;
-  c->prepared = 0;
-  return weight_pass(c, W1, W2, s);
+constexpr int64_t EARLY_VALUES = 1 << 22;
+
+// What an fp8 forward call needs before its first GEMM: the weights, both given (run the weight pass; prepared copies are gone after it) or both NULL
+// (use the copies ffn24_prepare_weights left), and jobs, in one launch (profiling times the two by themselves).
+int fp8_prologue(ffn24_ctx* c, const void* W1, const void* W2, const PaneliseJobs& jobs, hipStream_t s) {
+  if (W1 || W2) {
+    if (!W1 || !W2) return FFN24_ERR_NULL;
+    if (misaligned(W1) || misaligned(W2)) return FFN24_ERR_ALIGN;
+    c->prepared = 0;
+    const int rc = weight_pass(c, W1, W2, c->profiling ? nullptr : &jobs, s);
+    if (rc || !c->profiling) return rc;
+  } else if (!c->prepared) {
+    return FFN24_ERR_STATE;
+  }
+  Timed t(c, K_PANEL_X, s);
+  return t.done(launch_panelise8(jobs, s)) ? FFN24_ERR_HIP : FFN24_OK;
 }
 
 // dY and X as the weight gradients' B operands: as they lie, k-major, or (token permutation, whose rows the transposes gather; sizes without 32-bit
@@ -386,7 +395,7 @@ int ffn24_prepare_weights(ffn24_ctx* c, const void* W1, const void* W2, void* st
   if (rc) return rc;
   c->prepared = 0;
   c->have_fwd24 = c->have_fwd_dense = 0;
-  if ((rc = weight_pass(c, W1, W2, static_cast<hipStream_t>(stream)))) return rc;
+  if ((rc = weight_pass(c, W1, W2, nullptr, static_cast<hipStream_t>(stream)))) return rc;
   c->prepared = 1;
   return FFN24_OK;
 }
@@ -613,7 +622,6 @@ int ffn24_fwd(ffn24_ctx* c, const void* X, const void* W1, const float* b1, cons
   int T = (int)c->T, D = (int)c->D, F = (int)c->F;
   c->have_fwd24 = c->have_fwd_dense = 0;
   if (c->f8 && (c->flags & FFN24_ROWWISE) && !c->rsx) return FFN24_ERR_STATE;
-  if (c->f8 && (rc = resolve_weights(c, W1, W2, s))) return rc;
   if (c->f8 && (c->flags & FFN24_ROWWISE)) {
     // row-wise scaling: up-projection (bf16 kept values + row maxima), row-wise quantisation, scaled sparse GEMM
     uint32_t* nnz = (c->flags & FFN24_SPLIT) && c->n_dense > 0 ? c->nnz : nullptr;
@@ -626,7 +634,7 @@ int ffn24_fwd(ffn24_ctx* c, const void* X, const void* W1, const float* b1, cons
     const float* sx = c->rsx;
     if (perm) { pre.set_gather(c->rsx, perm, T, c->sx_p); sx = c->sx_p; }
     pre.add_copy(X, T, D, c->Xp8, 1, perm);
-    { Timed t(c, K_PANEL_X, s); if (t.done(launch_panelise8(pre, s))) return FFN24_ERR_HIP; }
+    if ((rc = fp8_prologue(c, W1, W2, pre, s))) return rc;
     { Timed t(c, K_UP, s);
       if (t.done(launch_up_prune24_f8_rowwise(c->W1t, c->Xp8, b1, T, D, F, sx, c->rsw1, c->Hc16, c->meta16, c->Hdbg, c->rowmax, nnz, s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_QUANT, s);
@@ -642,7 +650,7 @@ int ffn24_fwd(ffn24_ctx* c, const void* X, const void* W1, const float* b1, cons
     const bool train = (c->flags & FFN24_TRAINING) != 0;
     PaneliseJobs pre;
     pre.add_copy(X, T, D, c->Xp8, 1, nullptr);
-    { Timed t(c, K_PANEL_X, s); if (t.done(launch_panelise8(pre, s))) return FFN24_ERR_HIP; }
+    if ((rc = fp8_prologue(c, W1, W2, pre, s))) return rc;
     { Timed t(c, K_UP, s);
       if (t.done(launch_up_prune24_f8(c->W1t, c->Xp8, b1, T, D, F, c->sx * c->sw1, c->sh, c->Hc, c->meta, c->Hdbg, train ? c->Hc16 : nullptr,
                                       train ? c->meta16 : nullptr, s))) return FFN24_ERR_HIP; }
@@ -719,7 +727,15 @@ int ffn24_bwd_rowwise(ffn24_ctx* c, const ffn24_rowwise_bwd_operands* op, void* 
   pre.add_zero(c->rowmax_dz, T); pre.add_zero(c->hmax, F); pre.add_zero(c->zmax, F);
   const float* sdy_t = op->sdy_t;                     // as in the forward: the scales of the gathered rows, and dX's rows scattered back
   if (perm) { pre.set_gather(op->sdy_t, perm, T, c->sdy_p); sdy_t = c->sdy_p; }
-  { Timed t(c, K_PANEL_W, s); if (t.done(launch_panelise8(pre, s))) return FFN24_ERR_HIP; }
+  // small activations are transposed in the same launch (profiling times it by itself); large ones later, when the caches keep them for the weight gradients: step
+  // at T 1280 D 768 F 3072 76.0 -> 73.6 us, 2048 1024 4096 115 -> 111, 4096 2048 8192 400 -> 399, but 8192 2048 8192 713 -> 717, 4096 4096 16384 1185 -> 1200
+  const bool early = !c->profiling && c->T * c->D <= EARLY_VALUES;
+  if (early) {
+    if (launch_transpose8_acts(op->dY8c, op->X8c, T, D, c->dYt, nullptr, c->Xt, perm, &pre, s)) return FFN24_ERR_HIP;
+  } else {
+    Timed t(c, K_PANEL_W, s);
+    if (t.done(launch_panelise8(pre, s))) return FFN24_ERR_HIP;
+  }
   { Timed t(c, K_DH, s);
     if (t.done(launch_dh_gather_f8_rowwise(c->W2rp, c->dYp8, c->Hc16, c->meta16, T, D, F, op->sw2_f, sdy_t, c->dZc16, c->rowmax_dz, s))) return FFN24_ERR_HIP; }
   const bool split = (c->flags & FFN24_SPLIT) && c->n_dense > 0;
@@ -745,8 +761,8 @@ int ffn24_bwd_rowwise(ffn24_ctx* c, const ffn24_rowwise_bwd_operands* op, void* 
       q.add(c->Hct16, c->meta_t16, c->hmax, ns, T, c->Hc_t, c->meta_t, c->sh_f).add(c->dZct16, c->meta_t16, c->zmax, ns, T, c->dZc_t, c->meta_t, c->sdz_f);
       q.add_dense(c->Hdn_t, c->hmax + ns, nd, T, c->Hdn8_t, c->sh_f + ns).add_dense(c->dZdn_t, c->zmax + ns, nd, T, c->dZdn8_t, c->sdz_f + ns);
       if (t.done(launch_quantise_rows(q, s))) return FFN24_ERR_HIP; }
-    { Timed t(c, K_TR_ACT, s);
-      if (t.done(launch_transpose8_acts(op->dY8c, op->X8c, T, D, c->dYt, nullptr, c->Xt, perm, s))) return FFN24_ERR_HIP; }
+    if (!early) { Timed t(c, K_TR_ACT, s);
+      if (t.done(launch_transpose8_acts(op->dY8c, op->X8c, T, D, c->dYt, nullptr, c->Xt, perm, nullptr, s))) return FFN24_ERR_HIP; }
     if (!c->profiling) {   // (profiling times the two by themselves)
       if (launch_split_wgrads_f8_rowwise(c->Hc_t, c->dZc_t, c->meta_t, ns, c->Hdn8_t, c->dZdn8_t, nd, c->dYt, c->Xt, D, T, c->sh_f, op->sdy_d, c->sdz_f, op->sx_d,
                                          dW2, c->dW1t, D, c->feat_of_row, s)) return FFN24_ERR_HIP;
@@ -764,8 +780,8 @@ int ffn24_bwd_rowwise(ffn24_ctx* c, const ffn24_rowwise_bwd_operands* op, void* 
   { Timed t(c, K_QUANT_T, s);
     if (t.done(launch_quantise_rows(QuantJobs().add(c->Hct16, c->meta_t16, c->hmax, F, T, c->Hc_t, c->meta_t, c->sh_f)
                                         .add(c->dZct16, c->meta_t16, c->zmax, F, T, c->dZc_t, c->meta_t, c->sdz_f), s))) return FFN24_ERR_HIP; }
-  { Timed t(c, K_TR_ACT, s);
-    if (t.done(launch_transpose8_acts(op->dY8c, op->X8c, T, D, c->dYt, nullptr, c->Xt, perm, s))) return FFN24_ERR_HIP; }
+  if (!early) { Timed t(c, K_TR_ACT, s);
+    if (t.done(launch_transpose8_acts(op->dY8c, op->X8c, T, D, c->dYt, nullptr, c->Xt, perm, nullptr, s))) return FFN24_ERR_HIP; }
   if (!c->profiling) return launch_wgrad_f8_rowwise(c->Hc_t, c->dZc_t, c->meta_t, c->dYt, c->Xt, F, D, T, c->sh_f, op->sdy_d, c->sdz_f, op->sx_d, dW2, dW1, s) ? FFN24_ERR_HIP : FFN24_OK;   // (profiling times the two by themselves)
   { Timed t(c, K_DW2, s);
     if (t.done(launch_sp_rowmajor_f8_rowwise(c->Hc_t, c->meta_t, c->dYt, 1, F, D, T, c->sh_f, op->sdy_d, dW2, s))) return FFN24_ERR_HIP; }
@@ -787,7 +803,7 @@ int ffn24_bwd(ffn24_ctx* c, const void* dY, void* dX, void* dW1, void* dW2, void
   if (c->f8) {
     // fp8 backward (per-tensor scales): every GEMM operand is e4m3, the gradients come out in bf16
     { Timed t(c, K_TR_ACT, s);   // dY^T for the dW2 GEMM first: the same pass leaves dY8 in panel form for the dH GEMM
-      if (t.done(launch_transpose8_acts(dY, c->X, T, D, c->dYt, c->dYp8, c->Xt, nullptr, s))) return FFN24_ERR_HIP; }
+      if (t.done(launch_transpose8_acts(dY, c->X, T, D, c->dYt, c->dYp8, c->Xt, nullptr, nullptr, s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_DH, s);
       if (t.done(launch_dh_gather_f8(c->W2p, c->dYp8, c->Hc16, c->meta16, T, D, F, c->sdy * c->sw2, c->sdz, c->dZc, s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_DX, s);
@@ -855,13 +871,12 @@ int ffn_fwd(ffn24_ctx* c, const void* X, const void* W1, const float* b1, const 
   int T = (int)c->T, D = (int)c->D, F = (int)c->F;
   c->have_fwd24 = c->have_fwd_dense = 0;
   if (c->f8 && (c->flags & FFN24_ROWWISE) && !c->rsx) return FFN24_ERR_STATE;
-  if (c->f8 && (rc = resolve_weights(c, W1, W2, s))) return rc;
   if (c->f8 && (c->flags & FFN24_ROWWISE)) {
     // dense baseline with row-wise scales: up-projection (bf16 activations + row maxima), row-wise quantisation, dense GEMM
     PaneliseJobs pre;
     pre.add_zero(c->rowmax, T);
     pre.add_copy(X, T, D, c->Xp8, 1, nullptr);
-    { Timed t(c, K_PANEL_X, s); if (t.done(launch_panelise8(pre, s))) return FFN24_ERR_HIP; }
+    if ((rc = fp8_prologue(c, W1, W2, pre, s))) return rc;
     { Timed t(c, KD_UP, s);
       if (t.done(launch_up_relu2_f8_rowwise(c->W1t, c->Xp8, b1, T, D, F, c->rsx, c->rsw1, c->Hd16, c->rowmax, c->Hdt16, s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_QUANT, s);
@@ -875,7 +890,7 @@ int ffn_fwd(ffn24_ctx* c, const void* X, const void* W1, const float* b1, const 
     const bool train = (c->flags & FFN24_TRAINING) != 0;
     PaneliseJobs pre;
     pre.add_copy(X, T, D, c->Xp8, 1, nullptr);
-    { Timed t(c, K_PANEL_X, s); if (t.done(launch_panelise8(pre, s))) return FFN24_ERR_HIP; }
+    if ((rc = fp8_prologue(c, W1, W2, pre, s))) return rc;
     { Timed t(c, KD_UP, s);
       if (t.done(launch_up_relu2_f8(c->W1t, c->Xp8, b1, T, D, F, c->sx * c->sw1, c->sh, c->Hd, train ? c->Hd16 : nullptr, train ? c->Hd_t : nullptr, s)))
         return FFN24_ERR_HIP; }
@@ -907,7 +922,13 @@ int ffn_bwd_rowwise(ffn24_ctx* c, const ffn24_rowwise_bwd_operands* op, void* dX
   pre.add_copy(op->W1_8c, D, F, c->W1cp, 1, nullptr);      // (the dense dX GEMM does lose with its B operand row-major: 1.28 -> 1.43 ms)
   pre.add_copy(op->dY8r, T, D, c->dYp8, 1, nullptr);
   pre.add_zero(c->rowmax_dz, T); pre.add_zero(c->hmax, F); pre.add_zero(c->zmax, F);
-  { Timed t(c, K_PANEL_W, s); if (t.done(launch_panelise8(pre, s))) return FFN24_ERR_HIP; }
+  const bool early = !c->profiling && c->T * c->D <= EARLY_VALUES;   // (as in ffn24_bwd_rowwise)
+  if (early) {
+    if (launch_transpose8_acts(op->dY8c, op->X8c, T, D, c->dYt, nullptr, c->Xt, nullptr, &pre, s)) return FFN24_ERR_HIP;
+  } else {
+    Timed t(c, K_PANEL_W, s);
+    if (t.done(launch_panelise8(pre, s))) return FFN24_ERR_HIP;
+  }
   { Timed t(c, KD_DH, s);
     if (t.done(launch_dh_drelu_f8_rowwise(c->W2rp, c->dYp8, c->Hd16, T, D, F, op->sw2_f, op->sdy_t, c->dZd16, c->dZdt16, c->rowmax_dz, s))) return FFN24_ERR_HIP; }
   { Timed t(c, K_QUANT_DZ, s);
@@ -919,8 +940,8 @@ int ffn_bwd_rowwise(ffn24_ctx* c, const ffn24_rowwise_bwd_operands* op, void* dX
     if (!rc1) rc1 = launch_rowmax_dense(c->dZdt16, F, T, c->zmax, s);
     if (t.done(rc1 ? rc1 : launch_quantise_rows(QuantJobs().add_dense(c->Hdt16, c->hmax, F, T, c->Hd_t, c->sh_f).add_dense(c->dZdt16, c->zmax, F, T, c->dZd_t, c->sdz_f), s)))
       return FFN24_ERR_HIP; }
-  { Timed t(c, K_TR_ACT, s);
-    if (t.done(launch_transpose8_acts(op->dY8c, op->X8c, T, D, c->dYt, nullptr, c->Xt, nullptr, s))) return FFN24_ERR_HIP; }
+  if (!early) { Timed t(c, K_TR_ACT, s);
+    if (t.done(launch_transpose8_acts(op->dY8c, op->X8c, T, D, c->dYt, nullptr, c->Xt, nullptr, nullptr, s))) return FFN24_ERR_HIP; }
   if (!c->profiling) return launch_wgrad_f8_rowwise(c->Hd_t, c->dZd_t, nullptr, c->dYt, c->Xt, F, D, T, c->sh_f, op->sdy_d, c->sdz_f, op->sx_d, dW2, dW1, s) ? FFN24_ERR_HIP : FFN24_OK;   // (profiling times the two by themselves)
   { Timed t(c, KD_DW2, s);
     if (t.done(launch_dense_rowmajor_f8_rowwise(c->Hd_t, c->dYt, 1, F, D, T, c->sh_f, op->sdy_d, dW2, s))) return FFN24_ERR_HIP; }
@@ -941,7 +962,7 @@ int ffn_bwd(ffn24_ctx* c, const void* dY, void* dX, void* dW1, void* dW2, void* 
   int T = (int)c->T, D = (int)c->D, F = (int)c->F;
   if (c->f8) {
     { Timed t(c, K_TR_ACT, s);
-      if (t.done(launch_transpose8_acts(dY, c->X, T, D, c->dYt, c->dYp8, c->Xt, nullptr, s))) return FFN24_ERR_HIP; }
+      if (t.done(launch_transpose8_acts(dY, c->X, T, D, c->dYt, c->dYp8, c->Xt, nullptr, nullptr, s))) return FFN24_ERR_HIP; }
     { Timed t(c, KD_DH, s);
       if (t.done(launch_dh_drelu_f8(c->W2p, c->dYp8, c->Hd16, T, D, F, c->sdy * c->sw2, c->sdz, c->dZd, c->dZd_t, s))) return FFN24_ERR_HIP; }
     { Timed t(c, KD_DX, s);

@@ -640,45 +640,23 @@ __device__ __forceinline__ void transpose8_tile(const TransposeJob& job, int til
   }
 }
 
-template <int FORM_A, int FORM_B>
-__global__ void __launch_bounds__(256) transpose8_kernel(TransposeJob a, int n_first, TransposeJob b) {
-  __shared__ __attribute__((aligned(16))) uint8_t sT[T8_COLS * T8_LD];
-  const int bid = blockIdx.x;
-  if (bid < n_first) transpose8_tile<FORM_A>(a, bid, sT);
-  else transpose8_tile<FORM_B>(b, bid - n_first, sT);
-}
-
-static int transpose8_tiles(const TransposeJob& j) { return (j.C / T8_COLS) * (j.R / 64); }
-
-int launch_transpose8_weights(const void* W1, const void* W2, int D, int F, void* W1t, void* W1p, void* W2t, void* W2p, hipStream_t s) {
-  const TransposeJob a{W1, D, F, W1t, W1p, 1, nullptr}, b{W2, F, D, W2t, W2p, 0, nullptr};
-  hipLaunchKernelGGL((transpose8_kernel<1, 2>), dim3((unsigned)(transpose8_tiles(a) + transpose8_tiles(b))), dim3(256), 0, s, a, transpose8_tiles(a), b);
-  return (int)hipGetLastError();
-}
-
-int launch_transpose8_acts(const void* dY, const void* X, int T, int D, void* dYt, void* dYp, void* Xt, const int* rowmap, hipStream_t s) {
-  const TransposeJob a{dY, T, D, dYt, dYp, 1, rowmap}, b{X, T, D, Xt, nullptr, 0, rowmap};
-  hipLaunchKernelGGL((transpose8_kernel<2, 2>), dim3((unsigned)(transpose8_tiles(a) + transpose8_tiles(b))), dim3(256), 0, s, a, transpose8_tiles(a), b);
-  return (int)hipGetLastError();
-}
-
-// What an fp8 forward or backward needs done before its first GEMM, in one launch (each of these passes by itself is about as long as its
+// What a forward or backward needs done before its first GEMM, in one launch (each of these passes by itself is about as long as its
 // launch: T = 8192 D = 2048 F = 8192, token permutation and split, 4 + 6 launches of 4.7-9 us became 2):
 //   copies: byte matrices [R][C] (row-major, C a multiple of 64) into the dense fp8 panel form (64-byte pieces of 64 k, K = C) as A
 //     operands take it, or, b_form, into the B panel form (rows of every block of 256 in LDS order); row r is taken from memory row
 //     rowmap[r] if one is given (token permutation); 16 bytes per work item;
 //   zero: 32-bit words cleared (row maxima, counts);
 //   gather: dst[i] = src[map[i]], a per-token scale vector brought into the order of a token permutation.
-__global__ void __launch_bounds__(256) panelise8_kernel(PaneliseJobs jobs) {
-  unsigned bid = blockIdx.x;
+__device__ __forceinline__ void panelise8_block(const PaneliseJobs& jobs, unsigned bid) {
 #pragma unroll
   for (int j = 0; j < PaneliseJobs::COPIES; j++) {
     const PaneliseJobs::Copy& cp = jobs.copy[j];
     if (bid < cp.blocks) {
-      const int per_row = cp.C >> 4;
-      const size_t i = (size_t)bid * 256 + threadIdx.x;
-      if (i >= (size_t)cp.R * per_row) return;
-      const int r = (int)(i / per_row), cq = (int)(i % per_row), c = cq << 4;
+      const unsigned per_row = (unsigned)cp.C >> 4;
+      const size_t i = (size_t)bid * 256 + threadIdx.x, n = (size_t)cp.R * per_row;
+      if (i >= n) return;
+      const unsigned rq = n >> 32 ? (unsigned)(i / per_row) : (unsigned)i / per_row;   // (the long division only where it has to be)
+      const int r = (int)rq, cq = (int)((unsigned)i - rq * per_row), c = cq << 4;
       const int prow = cp.b_form ? b_panel_pos(r) : r;
       const size_t src = cp.rowmap ? (size_t)cp.rowmap[r] * per_row + cq : i;
       u32x4* out = reinterpret_cast<u32x4*>(static_cast<uint8_t*>(cp.out) + a24_piece(prow, c >> 6, cp.C >> 6) * 64 + (c & 63));
@@ -697,13 +675,47 @@ __global__ void __launch_bounds__(256) panelise8_kernel(PaneliseJobs jobs) {
   }
   if (i < jobs.gather_n) jobs.gather_dst[i] = jobs.gather_src[jobs.gather_map[i]];
 }
+__global__ void __launch_bounds__(256) panelise8_kernel(PaneliseJobs jobs) { panelise8_block(jobs, blockIdx.x); }
 
-int launch_panelise8(const PaneliseJobs& jobs, hipStream_t s) {
+struct NoJobs {};
+template <int FORM_A, int FORM_B, class Jobs>
+__global__ void __launch_bounds__(256) transpose8_kernel(TransposeJob a, int n_first, TransposeJob b, int n_tiles, Jobs jobs) {
+  __shared__ __attribute__((aligned(16))) uint8_t sT[T8_COLS * T8_LD];
+  const int bid = blockIdx.x;
+  if constexpr (std::is_same_v<Jobs, PaneliseJobs>) {
+    if (bid >= n_tiles) { panelise8_block(jobs, (unsigned)(bid - n_tiles)); return; }
+  }
+  if (bid < n_first) transpose8_tile<FORM_A>(a, bid, sT);
+  else transpose8_tile<FORM_B>(b, bid - n_first, sT);
+}
+
+static int transpose8_tiles(const TransposeJob& j) { return (j.C / T8_COLS) * (j.R / 64); }
+
+static unsigned panelise8_blocks(const PaneliseJobs& jobs) {
   unsigned blocks = 0;
   int side = jobs.gather_n;
   for (const auto& c : jobs.copy) blocks += c.blocks;
   for (int n : jobs.zero_n) side += n;
-  hipLaunchKernelGGL(panelise8_kernel, dim3(blocks + (unsigned)((side + 255) / 256)), dim3(256), 0, s, jobs);
+  return blocks + (unsigned)((side + 255) / 256);
+}
+template <int FORM_A, int FORM_B>
+static int launch_transpose8(const TransposeJob& a, const TransposeJob& b, const PaneliseJobs* jobs, hipStream_t s) {
+  const int na = transpose8_tiles(a), n = na + transpose8_tiles(b);
+  if (jobs) hipLaunchKernelGGL((transpose8_kernel<FORM_A, FORM_B, PaneliseJobs>), dim3((unsigned)n + panelise8_blocks(*jobs)), dim3(256), 0, s, a, na, b, n, *jobs);
+  else hipLaunchKernelGGL((transpose8_kernel<FORM_A, FORM_B, NoJobs>), dim3((unsigned)n), dim3(256), 0, s, a, na, b, n, NoJobs());
+  return (int)hipGetLastError();
+}
+
+int launch_transpose8_weights(const void* W1, const void* W2, int D, int F, void* W1t, void* W1p, void* W2t, void* W2p, const PaneliseJobs* jobs, hipStream_t s) {
+  return launch_transpose8<1, 2>({W1, D, F, W1t, W1p, 1, nullptr}, {W2, F, D, W2t, W2p, 0, nullptr}, jobs, s);
+}
+
+int launch_transpose8_acts(const void* dY, const void* X, int T, int D, void* dYt, void* dYp, void* Xt, const int* rowmap, const PaneliseJobs* jobs, hipStream_t s) {
+  return launch_transpose8<2, 2>({dY, T, D, dYt, dYp, 1, rowmap}, {X, T, D, Xt, nullptr, 0, rowmap}, jobs, s);
+}
+
+int launch_panelise8(const PaneliseJobs& jobs, hipStream_t s) {
+  hipLaunchKernelGGL(panelise8_kernel, dim3(panelise8_blocks(jobs)), dim3(256), 0, s, jobs);
   return (int)hipGetLastError();
 }
 

@@ -220,11 +220,12 @@ int launch_panelise8(const PaneliseJobs& jobs, hipStream_t s);
 //   form and, W2p given, W2 itself in dense panel form (all sizes multiples of 256)
 //   acts: dY, X [T][D] -> dYt, Xt in B panel form, row r taken from memory row rowmap[r] (may be NULL); bytes: dYp given, also dY
 //   itself in B panel form
+//   jobs (may be NULL; bytes): those of launch_panelise8 as well
 int launch_transpose(const void* in, int R, int C, void* out, hipStream_t s);
 int launch_transpose_weights(const void* W1, const void* W2, int D, int F, void* W1t, void* W1p, void* W2t, void* W2p, hipStream_t s);
 int launch_transpose_acts(const void* dY, const void* X, int T, int D, void* dYt, void* Xt, const int* rowmap, hipStream_t s);
-int launch_transpose8_weights(const void* W1, const void* W2, int D, int F, void* W1t, void* W1p, void* W2t, void* W2p, hipStream_t s);
-int launch_transpose8_acts(const void* dY, const void* X, int T, int D, void* dYt, void* dYp, void* Xt, const int* rowmap, hipStream_t s);
+int launch_transpose8_weights(const void* W1, const void* W2, int D, int F, void* W1t, void* W1p, void* W2t, void* W2p, const PaneliseJobs* jobs, hipStream_t s);
+int launch_transpose8_acts(const void* dY, const void* X, int T, int D, void* dYt, void* dYp, void* Xt, const int* rowmap, const PaneliseJobs* jobs, hipStream_t s);
 
 // ------------------------------------------------------------------------------------------------
 // measurement probes (k_probe.hip); they allocate their own buffers and wait for their own work
