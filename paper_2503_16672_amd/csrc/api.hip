@@ -638,7 +638,7 @@ int ffn24_fwd(ffn24_ctx* c, const void* X, const void* W1, const float* b1, cons
     { Timed t(c, K_UP, s);
       if (t.done(launch_up_prune24_f8_rowwise(c->W1t, c->Xp8, b1, T, D, F, sx, c->rsw1, c->Hc16, c->meta16, c->Hdbg, c->rowmax, nnz, s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_QUANT, s);
-      if (t.done(launch_quantise_rows(QuantJobs().add(c->Hc16, c->meta16, c->rowmax, T, F, c->Hc, c->meta, c->rsh), s))) return FFN24_ERR_HIP; }
+      if (t.done(launch_quantise_rows(QuantJobs(T, F, true).add(c->Hc16, c->meta16, c->rowmax, c->Hc, c->meta, c->rsh), s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_DOWN, s);
       int rc1 = perm ? launch_sp_rowmajor_f8_rowwise_mapped(c->Hc, c->meta, c->W2t, 1, T, D, F, c->rsh, c->rsw2, Y, perm, s)
                      : launch_sp_rowmajor_f8_rowwise(c->Hc, c->meta, c->W2t, 1, T, D, F, c->rsh, c->rsw2, Y, s);
@@ -741,7 +741,7 @@ int ffn24_bwd_rowwise(ffn24_ctx* c, const ffn24_rowwise_bwd_operands* op, void* 
   const bool split = (c->flags & FFN24_SPLIT) && c->n_dense > 0;
   const int nd = split ? c->n_dense : 0, ns = F - nd;
   { Timed t(c, K_QUANT_DZ, s);
-    const QuantJobs dz = QuantJobs().add(c->dZc16, c->meta16, c->rowmax_dz, T, F, c->dZc, c->meta, c->sdz_t);
+    const QuantJobs dz = QuantJobs(T, F, true).add(c->dZc16, c->meta16, c->rowmax_dz, c->dZc, c->meta, c->sdz_t);
     if (t.done(split && !c->profiling ? launch_quantise_rows_partition(dz, c->nnz, F, nd, T, c->row_of_feat, c->feat_of_row, s)
                                       : launch_quantise_rows(dz, s))) return FFN24_ERR_HIP; }
   { Timed t(c, K_DX, s);
@@ -757,10 +757,11 @@ int ffn24_bwd_rowwise(ffn24_ctx* c, const ffn24_rowwise_bwd_operands* op, void* 
       if (t.done(launch_featurewise24_split(c->Hc16, c->meta16, c->dZc16, T, F, c->row_of_feat, ns, c->Hct16, c->meta_t16, c->dZct16, c->Hdn_t, c->dZdn_t,
                                             nullptr, c->hmax, c->zmax, s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_QUANT_T, s);
-      QuantJobs q;
-      q.add(c->Hct16, c->meta_t16, c->hmax, ns, T, c->Hc_t, c->meta_t, c->sh_f).add(c->dZct16, c->meta_t16, c->zmax, ns, T, c->dZc_t, c->meta_t, c->sdz_f);
-      q.add_dense(c->Hdn_t, c->hmax + ns, nd, T, c->Hdn8_t, c->sh_f + ns).add_dense(c->dZdn_t, c->zmax + ns, nd, T, c->dZdn8_t, c->sdz_f + ns);
-      if (t.done(launch_quantise_rows(q, s))) return FFN24_ERR_HIP; }
+      QuantJobs sparse(ns, T, true), dense(nd, T, false);
+      sparse.add(c->Hct16, c->meta_t16, c->hmax, c->Hc_t, c->meta_t, c->sh_f).add(c->dZct16, c->meta_t16, c->zmax, c->dZc_t, c->meta_t, c->sdz_f);
+      dense.add_dense(c->Hdn_t, c->hmax + ns, c->Hdn8_t, c->sh_f + ns).add_dense(c->dZdn_t, c->zmax + ns, c->dZdn8_t, c->sdz_f + ns);
+      const int rc1 = launch_quantise_rows(sparse, s);
+      if (t.done(rc1 ? rc1 : launch_quantise_rows(dense, s))) return FFN24_ERR_HIP; }
     if (!early) { Timed t(c, K_TR_ACT, s);
       if (t.done(launch_transpose8_acts(op->dY8c, op->X8c, T, D, c->dYt, nullptr, c->Xt, perm, nullptr, s))) return FFN24_ERR_HIP; }
     if (!c->profiling) {   // (profiling times the two by themselves)
@@ -778,8 +779,8 @@ int ffn24_bwd_rowwise(ffn24_ctx* c, const ffn24_rowwise_bwd_operands* op, void* 
   { Timed t(c, K_FW, s);
     if (t.done(launch_featurewise24_rowmax(c->Hc16, c->meta16, c->dZc16, T, F, c->Hct16, c->meta_t16, c->dZct16, c->hmax, c->zmax, s))) return FFN24_ERR_HIP; }
   { Timed t(c, K_QUANT_T, s);
-    if (t.done(launch_quantise_rows(QuantJobs().add(c->Hct16, c->meta_t16, c->hmax, F, T, c->Hc_t, c->meta_t, c->sh_f)
-                                        .add(c->dZct16, c->meta_t16, c->zmax, F, T, c->dZc_t, c->meta_t, c->sdz_f), s))) return FFN24_ERR_HIP; }
+    if (t.done(launch_quantise_rows(QuantJobs(F, T, true).add(c->Hct16, c->meta_t16, c->hmax, c->Hc_t, c->meta_t, c->sh_f)
+                                        .add(c->dZct16, c->meta_t16, c->zmax, c->dZc_t, c->meta_t, c->sdz_f), s))) return FFN24_ERR_HIP; }
   if (!early) { Timed t(c, K_TR_ACT, s);
     if (t.done(launch_transpose8_acts(op->dY8c, op->X8c, T, D, c->dYt, nullptr, c->Xt, perm, nullptr, s))) return FFN24_ERR_HIP; }
   if (!c->profiling) return launch_wgrad_f8_rowwise(c->Hc_t, c->dZc_t, c->meta_t, c->dYt, c->Xt, F, D, T, c->sh_f, op->sdy_d, c->sdz_f, op->sx_d, dW2, dW1, s) ? FFN24_ERR_HIP : FFN24_OK;   // (profiling times the two by themselves)
@@ -880,7 +881,7 @@ int ffn_fwd(ffn24_ctx* c, const void* X, const void* W1, const float* b1, const 
     { Timed t(c, KD_UP, s);
       if (t.done(launch_up_relu2_f8_rowwise(c->W1t, c->Xp8, b1, T, D, F, c->rsx, c->rsw1, c->Hd16, c->rowmax, c->Hdt16, s))) return FFN24_ERR_HIP; }
     { Timed t(c, K_QUANT, s);
-      if (t.done(launch_quantise_rows(QuantJobs().add_dense(c->Hd16, c->rowmax, T, F, c->Hd, c->rsh), s))) return FFN24_ERR_HIP; }
+      if (t.done(launch_quantise_rows(QuantJobs(T, F, false).add_dense(c->Hd16, c->rowmax, c->Hd, c->rsh), s))) return FFN24_ERR_HIP; }
     { Timed t(c, KD_DOWN, s);
       if (t.done(launch_dense_rowmajor_f8_rowwise(c->Hd, c->W2t, 1, T, D, F, c->rsh, c->rsw2, Y, s))) return FFN24_ERR_HIP; }
     if (c->flags & FFN24_TRAINING) { c->X = X; c->have_fwd_dense = 1; }
@@ -932,13 +933,13 @@ int ffn_bwd_rowwise(ffn24_ctx* c, const ffn24_rowwise_bwd_operands* op, void* dX
   { Timed t(c, KD_DH, s);
     if (t.done(launch_dh_drelu_f8_rowwise(c->W2rp, c->dYp8, c->Hd16, T, D, F, op->sw2_f, op->sdy_t, c->dZd16, c->dZdt16, c->rowmax_dz, s))) return FFN24_ERR_HIP; }
   { Timed t(c, K_QUANT_DZ, s);
-    if (t.done(launch_quantise_rows(QuantJobs().add_dense(c->dZd16, c->rowmax_dz, T, F, c->dZd, c->sdz_t), s))) return FFN24_ERR_HIP; }
+    if (t.done(launch_quantise_rows(QuantJobs(T, F, false).add_dense(c->dZd16, c->rowmax_dz, c->dZd, c->sdz_t), s))) return FFN24_ERR_HIP; }
   { Timed t(c, KD_DX, s);
     if (t.done(launch_dense_rowmajor_f8_rowwise(c->dZd, c->W1cp, 1, T, D, F, c->sdz_t, op->sw1_d, dX, s))) return FFN24_ERR_HIP; }
   { Timed t(c, K_QUANT_T, s);      // per-feature maxima of the two transposed bf16 operands, then their quantisation
     int rc1 = launch_rowmax_dense(c->Hdt16, F, T, c->hmax, s);
     if (!rc1) rc1 = launch_rowmax_dense(c->dZdt16, F, T, c->zmax, s);
-    if (t.done(rc1 ? rc1 : launch_quantise_rows(QuantJobs().add_dense(c->Hdt16, c->hmax, F, T, c->Hd_t, c->sh_f).add_dense(c->dZdt16, c->zmax, F, T, c->dZd_t, c->sdz_f), s)))
+    if (t.done(rc1 ? rc1 : launch_quantise_rows(QuantJobs(F, T, false).add_dense(c->Hdt16, c->hmax, c->Hd_t, c->sh_f).add_dense(c->dZdt16, c->zmax, c->dZd_t, c->sdz_f), s)))
       return FFN24_ERR_HIP; }
   if (!early) { Timed t(c, K_TR_ACT, s);
     if (t.done(launch_transpose8_acts(op->dY8c, op->X8c, T, D, c->dYt, nullptr, c->Xt, nullptr, nullptr, s))) return FFN24_ERR_HIP; }

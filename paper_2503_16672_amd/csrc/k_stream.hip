@@ -814,14 +814,13 @@ int launch_featurewise24_f8(const void* Hc8, const uint8_t* meta, const void* dZ
 // a wave reads whole contiguous kilobytes; a lane's 8 codes of either input piece are exchanged with its neighbour's, so that each
 // stores 16 bytes and the wave a contiguous kilobyte again.  One output piece per lane and workgroups in memory order (a
 // quarter of a block of 256 rows each, then the next panel).  The stores are plain: the next kernel reads the codes.
-// A launch takes up to four matrices (QuantJobs): the operands of one stage of a step, whose launches by themselves end one after the other.
+// A launch takes one matrix or two of one kind and size (QuantJobs): the operands of one stage of a step, whose launches by themselves end one after the
+// other.  The kind and the place come from the grid: found by division and a walk over the jobs they cost a workgroup that lives this short 4 us of a
+// launch's 21 (T = F = 8192).
 template <bool META>
-__device__ __forceinline__ void quantise_rows_block(const QuantJobs::Job& job, unsigned bid, int tid) {
+__device__ __forceinline__ void quantise_rows_piece(const QuantJobs::Job& job, int np8, int j, int t, int c) {
   const u32x4* __restrict__ H16 = static_cast<const u32x4*>(job.H16);
   u32x4* __restrict__ H8 = static_cast<u32x4*>(job.H8);
-  const int np8 = job.np8;
-  const unsigned bx = bid % (4u * (unsigned)np8), by = bid / (4u * (unsigned)np8);
-  const int c = tid & 3, j = (int)(bx >> 2), t = (int)by * 256 + 64 * (int)(bx & 3) + (tid >> 2);
   const size_t pin = a24_piece(t, 2 * j, 2 * np8), pout = a24_piece(t, j, np8);
   const u32x4 v0 = ld_stream(H16 + pin * 4 + c), v1 = ld_stream(H16 + (pin + 256) * 4 + c);
   if (META && c < 2) reinterpret_cast<u32x2*>(job.meta8)[pout * 2 + c] = ld_stream(reinterpret_cast<const u32x2*>(job.meta16) + pin + 256 * c);
@@ -834,35 +833,30 @@ __device__ __forceinline__ void quantise_rows_block(const QuantJobs::Job& job, u
   const uint32_t r0 = (uint32_t)__shfl_xor((int)send[0], 1, 64), r1 = (uint32_t)__shfl_xor((int)send[1], 1, 64);
   H8[pout * 4 + 2 * odd + (c >> 1)] = odd ? u32x4{r0, r1, keep[0], keep[1]} : u32x4{keep[0], keep[1], r0, r1};
 }
-__device__ __forceinline__ void quantise_rows_at(const QuantJobs& jobs, unsigned bid, int tid) {
-#pragma unroll
-  for (int k = 0; k < QuantJobs::JOBS; k++) {
-    const QuantJobs::Job& job = jobs.job[k];
-    if (bid < job.blocks) {
-      if (job.meta16) quantise_rows_block<true>(job, bid, tid);
-      else quantise_rows_block<false>(job, bid, tid);
-      return;
-    }
-    bid -= job.blocks;
-  }
+template <bool META>
+__global__ void __launch_bounds__(256) quantise_rows_kernel(QuantJobs jobs) {
+  quantise_rows_piece<META>(blockIdx.z ? jobs.job[1] : jobs.job[0], jobs.np8, (int)(blockIdx.x >> 2), (int)(blockIdx.y * 256 + 64 * (blockIdx.x & 3) + (threadIdx.x >> 2)),
+                            threadIdx.x & 3);
 }
-__global__ void __launch_bounds__(256) quantise_rows_kernel(QuantJobs jobs) { quantise_rows_at(jobs, blockIdx.x, threadIdx.x); }
 
 int launch_quantise_rows(const QuantJobs& jobs, hipStream_t s) {
-  unsigned blocks = 0;
-  for (const auto& job : jobs.job) blocks += job.blocks;
-  hipLaunchKernelGGL(quantise_rows_kernel, dim3(blocks), dim3(256), 0, s, jobs);
+  const dim3 grid(4u * (unsigned)jobs.np8, (unsigned)(jobs.rows / 256), (unsigned)jobs.jobs);
+  if (jobs.job[0].meta16) hipLaunchKernelGGL(quantise_rows_kernel<true>, grid, dim3(256), 0, s, jobs);
+  else hipLaunchKernelGGL(quantise_rows_kernel<false>, grid, dim3(256), 0, s, jobs);
   return (int)hipGetLastError();
 }
 
-// The same with the feature partition of the split, which everything after it waits for and which keeps one workgroup busy: it runs beside the
-// quantisation of dZ instead of after it (T = F = 8192, D = 2048: 10.6 us of a step).  Workgroups of 1024, as the partition's is: four of the
-// quantisation's 256 each.
+// One compressed matrix, with the feature partition of the split, which everything after it waits for and which keeps one workgroup busy: it runs beside the
+// quantisation of dZ instead of after it (T = F = 8192, D = 2048: 10.6 us of a step).  Workgroups of 1024, as the partition's is: a whole block of 256 rows
+// each; the first row of the grid is the partition's.
 __global__ void __launch_bounds__(1024) quantise_rows_partition_kernel(QuantJobs jobs, const uint32_t* __restrict__ nnz, int F, int n_dense, uint32_t max_count,
                                                                        int* __restrict__ row_of_feat, int* __restrict__ feat_of_row) {
   extern __shared__ uint32_t s_nnz[];
-  if (blockIdx.x == 0) split_partition<true>(s_nnz, nnz, F, n_dense, max_count, row_of_feat, feat_of_row);
-  else quantise_rows_at(jobs, 4 * (blockIdx.x - 1) + (threadIdx.x >> 8), threadIdx.x & 255);
+  if (blockIdx.y == 0) {
+    if (blockIdx.x == 0) split_partition<true>(s_nnz, nnz, F, n_dense, max_count, row_of_feat, feat_of_row);
+    return;
+  }
+  quantise_rows_piece<true>(jobs.job[0], jobs.np8, (int)blockIdx.x, (int)((blockIdx.y - 1) * 256 + (threadIdx.x >> 2)), threadIdx.x & 3);
 }
 
 int launch_quantise_rows_partition(const QuantJobs& jobs, const uint32_t* nnz, int F, int n_dense, int max_count, int* row_of_feat, int* feat_of_row, hipStream_t s) {
@@ -872,10 +866,8 @@ int launch_quantise_rows_partition(const QuantJobs& jobs, const uint32_t* nnz, i
   }
   static std::atomic<bool> configured[MAX_DEVICES] = {};
   if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(quantise_rows_partition_kernel), 4 * (PART_SHARED_FEATS + PART_SHARED_FEATS / 32), configured)) return rc;
-  unsigned blocks = 0;
-  for (const auto& job : jobs.job) blocks += job.blocks;
-  hipLaunchKernelGGL(quantise_rows_partition_kernel, dim3(1 + (blocks + 3) / 4), dim3(1024), 4 * ((size_t)F + (size_t)F / 32), s, jobs, nnz, F, n_dense,
-                     (uint32_t)max_count, row_of_feat, feat_of_row);
+  hipLaunchKernelGGL(quantise_rows_partition_kernel, dim3((unsigned)jobs.np8, 1u + (unsigned)(jobs.rows / 256)), dim3(1024), 4 * ((size_t)F + (size_t)F / 32), s, jobs, nnz,
+                     F, n_dense, (uint32_t)max_count, row_of_feat, feat_of_row);
   return (int)hipGetLastError();
 }
 

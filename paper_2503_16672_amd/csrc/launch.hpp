@@ -142,18 +142,17 @@ int launch_dh_drelu_f8_rowwise(const void* W2rp8, const void* dY8r, const void* 
 int launch_rowmax_dense(const void* X16, int R, int C, uint32_t* rmax, hipStream_t s);
 int launch_dense_colmajor_f8_rowwise(const void* A8, const void* B8, int M, int N, int K, const float* rs, const float* cs, void* Ct, hipStream_t s);
 int launch_dense_rowmajor_f8_rowwise(const void* A8, const void* B8, int b_panel, int M, int N, int K, const float* rs, const float* cs, void* C, hipStream_t s);
-// row-wise quantisation of up to four matrices in one launch: rows of F values, compressed (add: kept values and metadata) or plain (add_dense),
-// bf16 panel form to fp8 panel form; sh [T] is written
+// row-wise quantisation of one matrix, or of two of one kind and size, in one launch: rows of F values, compressed (kept values and metadata) or plain
+// (meta16 NULL), bf16 panel form to fp8 panel form; sh [T] is written
 struct QuantJobs {
-  static constexpr int JOBS = 4;
-  struct Job { const void* H16; const uint8_t* meta16; const uint32_t* rowmax; int np8; void* H8; uint8_t* meta8; float* sh; unsigned blocks; } job[JOBS] = {};
-  int jobs = 0;   // (host side: slots in use)
-  QuantJobs& add(const void* Hc16, const uint8_t* meta16, const uint32_t* rowmax, int T, int F, void* Hc8, uint8_t* meta8, float* sh) {
-    const int np8 = F >> (meta16 ? 7 : 6);
-    job[jobs++] = Job{Hc16, meta16, rowmax, np8, Hc8, meta8, sh, 4u * (unsigned)np8 * (unsigned)(T / 256)};
+  struct Job { const void* H16; const uint8_t* meta16; const uint32_t* rowmax; void* H8; uint8_t* meta8; float* sh; } job[2] = {};
+  int rows, np8, jobs = 0;
+  QuantJobs(int T, int F, bool compressed) : rows(T), np8(F >> (compressed ? 7 : 6)) {}
+  QuantJobs& add(const void* Hc16, const uint8_t* meta16, const uint32_t* rowmax, void* Hc8, uint8_t* meta8, float* sh) {
+    job[jobs++] = Job{Hc16, meta16, rowmax, Hc8, meta8, sh};
     return *this;
   }
-  QuantJobs& add_dense(const void* H16, const uint32_t* rowmax, int T, int F, void* H8, float* sh) { return add(H16, nullptr, rowmax, T, F, H8, nullptr, sh); }
+  QuantJobs& add_dense(const void* H16, const uint32_t* rowmax, void* H8, float* sh) { return add(H16, nullptr, rowmax, H8, nullptr, sh); }
 };
 int launch_quantise_rows(const QuantJobs& jobs, hipStream_t s);
 // ... and launch_split_partition, beside it where F is small enough
