@@ -517,9 +517,12 @@ def main() -> int:
             if name in SPARSE:
                 kernels[name]["tflops_dense_equivalent"] = round(2 * tf, 1)
         else:
+            if name == "transpose_acts" and not fp8 and not args.permute:
+                kernels[name] = {"ms": round(ms, 4), "what": "no pass: dY and X are read where they lie"}
+                continue
             # streaming kernels: feature-wise re-compression moves 4.25 bytes per element of [T, F]; a transpose pair
             # reads and writes 2 x 2 bytes per element of its two matrices
-            # (the weight pass also writes panel-form copies of W1 and W2 when the context trains: 12 D F bytes then)
+            # (the per-tensor fp8 weight pass also writes panel-form copies of W1 and W2 when the context trains; the bf16 one only copies: 8 D F bytes)
             es = 1.0 if fp8 else 2.0
             if name in ("quantise_rows", "quantise_dz_rows", "quantise_transposed"):
                 # reads the bf16 kept values + metadata, writes codes + metadata (+ one scale per row); the transposed pair runs twice
@@ -529,7 +532,7 @@ def main() -> int:
             if name == "split_partition":
                 kernels[name] = {"ms": round(ms, 4)}
                 continue
-            nbytes = {"panelise_bwd_weights": 2.0 * D * F + 2.0 * T * D, "panelise_x": 2.0 * T * D, "featurewise24": (2.0 * (2.0 if rowwise_bwd else es) + 0.25) * T * F, "transpose_weights": (6.0 if bwd and not rowwise_bwd else 4.0) * es * D * F,
+            nbytes = {"panelise_bwd_weights": 2.0 * D * F + 2.0 * T * D, "panelise_x": 2.0 * T * D, "featurewise24": (2.0 * (2.0 if rowwise_bwd else es) + 0.25) * T * F, "transpose_weights": (6.0 if bwd and fp8 and not rowwise_bwd else 4.0) * es * D * F,
                       # (per-tensor fp8: the pass over dY8 also leaves its panel-form copy)
                       "transpose_acts": (5.0 if fp8 and not rowwise_bwd else 4.0) * es * T * D, "transpose_dw1": 4.0 * D * F}[name]
             gbs = nbytes / (ms * 1e-3) / 1e9

@@ -38,7 +38,7 @@ constexpr int TELE_WORDS = TELE_KINDS * TELE_SLOTS * TELE_STRIDE;   // 64-bit wo
 __host__ __device__ constexpr int tele_index(int kind, int slot) { return (kind * TELE_SLOTS + (slot & (TELE_SLOTS - 1))) * TELE_STRIDE; }
 
 // All return a hipError_t cast to int (0 = success); shapes must already be validated by the caller:
-// M % 256 == 0, N % 256 == 0, K % 64 == 0, 16-byte aligned pointers.  Every GEMM operand is K-contiguous.
+// M % 256 == 0, N % 256 == 0, K % 64 == 0, 16-byte aligned pointers.  Every GEMM operand is K-contiguous unless its form says otherwise (FORM_K_MAJOR).
 
 // Forms of a dense operand: row-major K-contiguous; the panel form (of A or of B) of gemm_core.hpp; k-major, a caller's [K][M] or [K][N] matrix as it
 // stands (bf16, read with the transposing LDS reads; 32-bit offsets inside it: see fits_k_major).  "b_panel" below: the first two, 0 or 1.
@@ -130,7 +130,7 @@ int launch_up_prune24_f8_rowwise(const void* W1t8, const void* X8, const float* 
 int launch_split_wgrad_f8_rowwise(const void* vals8, const uint8_t* meta, int ns, const void* Ad8, int nd, const void* B8, int N, int K,
                                   const float* rs, const float* cs, void* C, int ldc, const int* rowmap, hipStream_t s);
 // the dense row-wise-scaled baseline: up-projection writing every activation as bf16 (dense panel form) and raising rowmax;
-// quantise_rows_dense turns them into e4m3 (dense fp8 panel form) with sh[t] = rowmax[t] / 448; dense GEMM with sh[t] sw2[n]
+// quantise_rows turns them into e4m3 (dense fp8 panel form) with sh[t] = rowmax[t] / 448; dense GEMM with sh[t] sw2[n]
 // (Ht16, may be NULL: the activation once more as the bf16 [F][T] operand, dense panel form)
 int launch_up_relu2_f8_rowwise(const void* W1t8, const void* X8, const float* b1, int T, int D, int F, const float* sx, const float* sw1,
                                void* H16, uint32_t* rowmax, void* Ht16, hipStream_t s);
