@@ -1,17 +1,10 @@
 """Register use of the GEMM kernels, from the compiler's own report (no GPU): these keep everything in registers.  One spilled register gives a
 kernel a scratch segment, which cost every tile of the sparse store kernels 0.15-0.2 us."""
-import os
 import re
-import subprocess
-from concurrent.futures import ThreadPoolExecutor
-from pathlib import Path
 
 import pytest
 
-from paper_2503_16672_amd import build
-
-SRC = Path(build.CSRC)
-UNITS = ["k_fwd", "k_bwd", "k_fp8_rowwise"]
+UNITS = ["k_fwd", "k_bwd", "k_wgrad", "k_dense_a", "k_dense_b", "k_fp8", "k_fp8_rowwise"]
 
 
 # translation unit, 2:4 operand, epilogue as the mangled name has it, wave tiles (4 x 4: 256 x 256, 4 x 2: 256 x 128)
@@ -32,20 +25,30 @@ def test_kernels_do_not_spill(report, unit, sparse, epilogue, tiles):
         assert report[unit][found[0]] == (0, 0), (found[0], report[unit][found[0]])
 
 
+# The dense row-wise fp8 epilogues hold a scale a column, a scale a row and the row maxima beside the accumulators: registers that may be spilled.
+KNOWN = {("EpiRelu2Rw", 4, 4): 10, ("EpiRelu2Rw", 4, 2): 42, ("EpiDReluRw", 4, 4): 8, ("EpiDReluRw", 4, 2): 8}
+
+
+@pytest.mark.parametrize("unit", UNITS)
+def test_no_other_kernel_spills(report, unit):
+    """Every kernel of the unit: also those that read k-major operands, that take two GEMMs or other work into one launch, and every tile."""
+    kinds = {"k_fwd": ["gemm_kernel", "gemm_k_major_kernel", "gemm_side_kernel", "gemm_rows_kernel"], "k_bwd": ["gemm_kernel", "gemm_k_major_kernel", "gemm_pair_kernel"],
+             "k_wgrad": ["gemm_k_major_kernel", "gemm_duo_kernel"], "k_dense_a": ["gemm_k_major_kernel"], "k_dense_b": ["gemm_k_major_kernel"]}
+    for kind in kinds.get(unit, ["gemm_kernel"]):
+        assert any(kind in k for k in report[unit]), kind
+    bad = {}
+    for name, (spilled, scratch) in report[unit].items():
+        known = [n for (epilogue, mi, ni), n in KNOWN.items() if "gemm_kernelILb0E" in name and f"{len(epilogue)}{epilogue}E" in name and f"Li0ELi{mi}ELi{ni}E" in name]
+        if (spilled or scratch) and not (known and spilled <= known[0]):
+            bad[name] = (spilled, scratch)
+    assert not bad, bad
+
+
 @pytest.fixture(scope="module")
-def report(tmp_path_factory):
+def report(assembly):
     """translation unit -> kernel name -> (spilled registers, bytes of scratch a work item)"""
-    if not os.path.exists(build.HIPCC):
-        pytest.skip("no hipcc")
-    d = tmp_path_factory.mktemp("asm")
-
-    def one(unit):
-        out = d / f"{unit}.s"
-        subprocess.run([build.HIPCC, *build.FLAGS, "-w", "--cuda-device-only", "-S", str(SRC / f"{unit}.hip"), "-o", str(out)], check=True)
-        kernels = {}
-        for m in re.finditer(r"\.name:\s+(_Z\S+)\n(.*?)\.vgpr_spill_count:\s+(\d+)", out.read_text(), re.S):
-            kernels[m[1]] = (int(m[3]), int(re.search(r"\.private_segment_fixed_size:\s+(\d+)", m[2])[1]))
-        return kernels
-
-    with ThreadPoolExecutor(len(UNITS)) as ex:
-        return dict(zip(UNITS, ex.map(one, UNITS)))
+    kernels = {}
+    for unit in UNITS:
+        kernels[unit] = {m[1]: (int(m[3]), int(re.search(r"\.private_segment_fixed_size:\s+(\d+)", m[2])[1]))
+                         for m in re.finditer(r"\.name:\s+(_Z\S+)\n(.*?)\.vgpr_spill_count:\s+(\d+)", assembly[unit], re.S)}
+    return kernels
