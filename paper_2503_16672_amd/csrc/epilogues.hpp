@@ -761,22 +761,48 @@ struct EpiColMajorScaled {
 
 // Row maxima of a launch: rowmax[t] is raised to the largest bf16 magnitude word of row t.  A token row spans F / (16 MI) lanes of the
 // launch, and one atomic for each of them was the larger part of the row-wise epilogues (T = F = 8192: a million atomics, 15 us of the
-// dH GEMM's 157 with 256 x 256 tiles and 40 of 167 with 256 x 128).  So the two lane halves, which hold the same tokens, are
-// combined first, which halves them, and what is already there is looked at before: the values are requested when the epilogue starts,
+// dH GEMM's 157 with 256 x 256 tiles and 40 of 167 with 256 x 128).  So the lane groups, which hold the same tokens, are
+// combined first, and what is already there is looked at before: the values are requested before they are needed,
 // and an atomic goes out only where it would raise one.  That spares the later rounds of a launch and most of a tile that starts late;
 // tiles of one round that finish together all see the cleared value and all send theirs.  A value that is out of date is lower and
 // only costs an atomic.
+// What bounds those that do go out is how many lines each touches and how many tiles raise the same ones.  The 256 x 256 tile's four lane
+// groups therefore exchange halves of what they hold instead of each adding up all of it, and every lane raises two neighbouring tokens:
+// a wave's 128 tokens are two instructions of 64 lanes over four lines each.  Eight instructions of the 16 lanes of one group, four lines
+// each again, took longer the fewer the tokens and the more the tiles (row-wise fp8, up-projection and dH, us: T 512 D 4096 F 32768 106 -> 76
+// and 93 -> 73; T 512 D 8192 F 32768 157 -> 129 and 128 -> 114; T 4096 D 4096 F 16384 218 -> 208 and 215 -> 211; T = F = 8192, D 2048
+// 117 -> 116 and 121 -> 119).
 template <int MI, int NI>
 struct RowMax {
-  uint32_t seen[NI];
+  using LT = LaneTile<MI, NI>;
+  static constexpr bool SCATTER = LT::GROUPS == 4;
+  static constexpr int OWN = SCATTER ? NI / 4 : NI;   // tokens a lane raises
+  uint32_t seen[OWN];
+  static __device__ __forceinline__ int first(int n_lane) { return SCATTER ? n_lane + OWN * LT::h() : n_lane; }
   __device__ __forceinline__ void load(const uint32_t* rowmax, int n_lane) {
 #pragma unroll
-    for (int ni = 0; ni < NI; ni++) seen[ni] = __hip_atomic_load(rowmax + n_lane + ni, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int i = 0; i < OWN; i++) seen[i] = __hip_atomic_load(rowmax + first(n_lane) + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  __device__ __forceinline__ void raise(uint32_t* rowmax, int n_lane, int ni, uint32_t mx) const {
+  // mx: the lane's maxima of its tokens, two to a word (NI = 1: both halves are of its one token)
+  __device__ __forceinline__ void raise(uint32_t* rowmax, int n_lane, const uint32_t (&mx)[(NI + 1) / 2]) const {
+    if constexpr (SCATTER) {
+      const bool up = (LT::h() & 2) != 0, odd = (LT::h() & 1) != 0;
+      uint32_t k[2];
 #pragma unroll
-    for (int sft = LaneTile<MI, NI>::LANES; sft < 64; sft <<= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, sft, 64));
-    if (LaneTile<MI, NI>::h() == 0 && mx > seen[ni]) atomicMax(rowmax + n_lane + ni, mx);
+      for (int i = 0; i < 2; i++) k[i] = pk_max16(up ? mx[2 + i] : mx[i], (uint32_t)__shfl_xor((int)(up ? mx[i] : mx[2 + i]), 32, 64));
+      const uint32_t m = pk_max16(odd ? k[1] : k[0], (uint32_t)__shfl_xor((int)(odd ? k[0] : k[1]), 16, 64));
+      int at = first(n_lane);
+      asm volatile("" : "+v"(at));                   // (counted anew: the address kept since the load is two registers more)
+      if ((m & 0xFFFFu) > seen[0]) atomicMax(rowmax + at, m & 0xFFFFu);
+      if ((m >> 16) > seen[1]) atomicMax(rowmax + at + 1, m >> 16);
+    } else {
+#pragma unroll
+      for (int ni = 0; ni < NI; ni++) {
+        uint32_t m = NI == 1 ? max(mx[0] & 0xFFFFu, mx[0] >> 16) : ni & 1 ? mx[0] >> 16 : mx[0] & 0xFFFFu;
+        m = max(m, (uint32_t)__shfl_xor((int)m, 32, 64));
+        if (LT::h() == 0 && m > seen[ni]) atomicMax(rowmax + n_lane + ni, m);
+      }
+    }
   }
 };
 
@@ -840,9 +866,8 @@ struct EpiPrune24RwT {
 #pragma unroll
     for (int ni = 0; ni < NI; ni++) {
       st_nibbles<MI>(e.meta + a24_piece(n_lane + ni, m_lane >> 6, e.F >> 6) * 8 + ((m_lane & 63) >> 3), nib[ni]);
-      if constexpr (NI > 1) rm.raise(e.rowmax, n_lane, ni, ni & 1 ? mx[ni / 2] >> 16 : mx[ni / 2] & 0xFFFFu);
-      else rm.raise(e.rowmax, n_lane, ni, max(mx[0] & 0xFFFFu, mx[0] >> 16));
     }
+    rm.raise(e.rowmax, n_lane, mx);
     if constexpr (STATS) {
       uint32_t cnt[4 * MI];
       nz.fold(cnt);
@@ -905,8 +930,10 @@ struct EpiRelu2Rw {
         }
       }
     }
+    uint32_t two[(NI + 1) / 2] = {};
 #pragma unroll
-    for (int ni = 0; ni < NI; ni++) rm.raise(e.rowmax, n_lane, ni, mx[ni]);
+    for (int ni = 0; ni < NI; ni++) two[ni / 2] |= mx[ni] << (16 * (ni & 1));
+    rm.raise(e.rowmax, n_lane, two);
   }
 };
 
@@ -960,8 +987,10 @@ struct EpiDReluRw {
         st_cols<NI>(e.dZt16 + a24_piece(m_lane + 16 * mi + v, n_lane >> 5, e.T >> 5) * 32 + (n_lane & 31), o);
       }
     }
+    uint32_t two[(NI + 1) / 2] = {};
 #pragma unroll
-    for (int ni = 0; ni < NI; ni++) rm.raise(e.rowmax, n_lane, ni, mx[ni]);
+    for (int ni = 0; ni < NI; ni++) two[ni / 2] |= mx[ni] << (16 * (ni & 1));
+    rm.raise(e.rowmax, n_lane, two);
   }
 };
 
@@ -1057,7 +1086,7 @@ struct EpiDGatherRw {
   template <int MI, int NI, class Acc>
   static __device__ __forceinline__ void run(const Args& e, Acc& acc, int m_lane, int n_lane, char* wbuf) {
     RowMax<MI, NI> rm;
-    rm.load(e.rowmax, n_lane);
+    if constexpr (NI < 8) rm.load(e.rowmax, n_lane);
     LaneVec<MI> lr;
     lr.load(e.rs, m_lane, 1.f);
     LaneSaved24<MI, NI> sv;
@@ -1065,14 +1094,16 @@ struct EpiDGatherRw {
     float csv[NI];
 #pragma unroll
     for (int ni = 0; ni < NI; ni++) csv[ni] = e.cs[n_lane + ni];
+    uint32_t mx[(NI + 1) / 2] = {};
 #pragma unroll
     for (int ni = 0; ni < NI; ni++) {
+      if (NI == 8 && ni == NI / 2) rm.load(e.rowmax, n_lane);   // (from the start on it is two registers too many)
       size_t t = (size_t)(n_lane + ni);
       const float cs = csv[ni];
       size_t piece = a24_piece((int)t, m_lane >> 6, e.F >> 6);
       const u32x2 mt = sv.mt[ni];
       __bf16* zrow = e.dZc16 + piece * 32 + ((m_lane & 63) >> 1);
-      uint32_t mx = 0u;
+      uint32_t m = 0u;
 #pragma unroll
       for (int mi = 0; mi < MI; mi++) {
         const u32x4 h = sv.kept(ni, mi);
@@ -1089,13 +1120,15 @@ struct EpiDGatherRw {
           float g0 = 2.f * __builtin_amdgcn_sqrtf(bf16_lo_to_f32(h[a]));
           float g1 = 2.f * __builtin_amdgcn_sqrtf(bf16_hi_to_f32(h[a]));
           z[a] = pack_bf16x2(s0 * g0, s1 * g1);
-          mx = max(mx, max(z[a] & 0x7FFFu, (z[a] >> 16) & 0x7FFFu));
+          m = max(m, max(z[a] & 0x7FFFu, (z[a] >> 16) & 0x7FFFu));
         }
         if constexpr (LaneTile<MI, NI>::STAGED) *reinterpret_cast<u32x4*>(PanelStage<MI, NI>::at(wbuf, ni, mi)) = z;
         else *reinterpret_cast<u32x4*>(zrow + 8 * mi) = z;
       }
-      rm.raise(e.rowmax, n_lane, ni, mx);
+      mx[ni / 2] |= m << (16 * (ni & 1));
+      keep_here<NI == 8>(mx[ni / 2]);
     }
+    rm.raise(e.rowmax, n_lane, mx);
     if constexpr (LaneTile<MI, NI>::STAGED) PanelStage<MI, NI>::flush(wbuf, reinterpret_cast<char*>(e.dZc16) + PanelStage<MI, NI>::first(m_lane, n_lane, e.F));
   }
 };

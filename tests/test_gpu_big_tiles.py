@@ -39,10 +39,15 @@ def _bf16_step(F24, dev, b1, dense, ts, fs):
     return (Y, *g)
 
 
+# (T, D, F): 256 x 256 tiles in every GEMM of every kind (test_tile_rule.py), less than a round of them; in all but the dense and the fp8 up- and
+# down-projections and the dense fp8 weight gradients, an odd multiple of 256 as the short reduction and more than a round
+SIZES = [(3584, 3584, 3584), (8192, 2304, 8192)]
+
+
+@pytest.mark.parametrize("T,D,Fh", SIZES)
 @pytest.mark.parametrize("kind", ["bf16", "fp8", "fp8_rowwise"])
 @pytest.mark.parametrize("dense", [False, True])
-def test_steps_have_the_bits_of_smaller_tiles(F24, kind, dense):
-    T, D, Fh = 8192, 2304, 8192                       # 256 x 256 tiles in every GEMM; an odd multiple of 256 as the short reduction
+def test_steps_have_the_bits_of_smaller_tiles(F24, kind, dense, T, D, Fh):
     g = torch.Generator(device="cuda").manual_seed(11)
     dev = {k: torch.randn(*s, generator=g, device="cuda") for k, s in (("X", (T, D)), ("W1", (D, Fh)), ("W2", (Fh, D)), ("dY", (T, D)))}
     b1 = torch.full((Fh,), -0.05, device="cuda")
@@ -55,7 +60,7 @@ def test_steps_have_the_bits_of_smaller_tiles(F24, kind, dense):
         dev = {k: (v * 64).clamp(-448, 448).to(torch.float8_e4m3fn).view(torch.uint8) for k, v in dev.items()}
         q = {k: v for k, v in dev.items()}
         step = lambda ts, fs: _fp8_step(F24, q, dev, b1, kind == "fp8_rowwise", dense, ts, fs)
-    print(f"256 x 256 tiles {kind} dense={dense}", flush=True)
+    print(f"256 x 256 tiles {kind} dense={dense} T={T} D={D} F={Fh}", flush=True)
     full = step(T, Fh)
     assert float(full[0].float().abs().max()) > 0 and all(bool(torch.isfinite(x.float()).all()) for x in full)
     got = step(512, Fh)

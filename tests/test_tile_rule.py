@@ -7,6 +7,7 @@ from pathlib import Path
 
 import pytest
 
+from test_gpu_big_tiles import SIZES as BIG_SIZES
 from test_gpu_pick import SHAPES as PICK_SHAPES
 
 RULE = Path(__file__).resolve().parents[1] / "paper_2503_16672_amd" / "csrc" / "tile_rule.hpp"
@@ -77,6 +78,17 @@ def test_shapes_of_the_pick_tests_take_every_tile(picks):
     for f8, epilogue in ((0, "p"), (1, "f")):
         assert picks([(0, f8, epilogue, Fh, T, D, 1) for T, D, Fh, _ in PICK_SHAPES]) == [tile for *_, tile in PICK_SHAPES]
     assert {tile for *_, tile in PICK_SHAPES} == set(range(5))
+
+
+def test_shape_of_the_big_tile_tests_takes_them_everywhere(picks):
+    """The first size of the GPU test of the 256 x 256 tile runs every GEMM of every kind of step with it, and its slices of 512 tokens (Y, dX) and
+    256 features (dW1, dW2) run with smaller tiles."""
+    T, D, F = BIG_SIZES[0]
+    products = lambda t, f: [(0, 0, "p", f, t, D, 1), (0, 1, "p", f, t, D, 1), (0, 1, "f", f, t, D, 1), (0, 1, "s", f, t, D, 1),
+                             *((sp, f8, "p", t, D, f, 1) for sp in (0, 1) for f8 in (0, 1))]
+    gradients = lambda t, f: [(sp, f8, "p", f, D, t, 2) for sp in (0, 1) for f8 in (0, 1)]
+    assert set(picks(products(T, F) + gradients(T, F))) == {0}
+    assert 0 not in picks(products(512, F)) and 0 not in picks(gradients(T, 256))
 
 
 def test_two_full_gemms_take_the_large_tile_alone_too(tmp_path):
