@@ -966,13 +966,14 @@ __global__ void __launch_bounds__(256) quantise_bf16_long_rows_kernel(const u32x
   for (int c = lane; c < C8; c += 64) st_stream(out + c, quantise8(row[c], d));
 }
 
-// Per column of a matrix of more than HELD_ROWS rows, three kernels: (1) the largest magnitude words of every column over slabs of rows, (2) their maximum over the slabs and the
-// scale, (3) the codes.  A workgroup of (1) and (3) covers 64 pieces of 8 columns x 4 interleaved row groups, so that a wave's load is
+// Per column (matrices that held_columns leaves), three kernels: (1) the largest magnitude words of every column over slabs of rows, (2) their
+// maximum over the slabs and the scale, (3) the codes.  A workgroup of (1) and (3) covers 64 pieces of 8 columns x 4 interleaved row groups, so that a wave's load is
 // 1024 contiguous bytes of a row and QC_UNROLL rows are in flight per work item.  The slab maxima [slab][C] (16-bit words) stand in the
-// codes buffer, which (3) overwrites afterwards: 2 C ceil(R / QC_ROWS) bytes of its R C.
+// codes buffer, which (3) overwrites afterwards: 2 C ceil(R / QC_ROWS) bytes of its R C.  With a single slab (1) writes the scales.
 constexpr int QC_UNROLL = 16, QC_ROWS = 4 * QC_UNROLL, QC_SLABS = 256;
 
-__global__ void __launch_bounds__(256) colmax_bf16_kernel(const u32x4* __restrict__ X, int64_t R, int C8, int64_t slab_rows, u16x8* __restrict__ part) {
+__global__ void __launch_bounds__(256) colmax_bf16_kernel(const u32x4* __restrict__ X, int64_t R, int C8, int64_t slab_rows, u16x8* __restrict__ part,
+                                                          float* __restrict__ scales) {
   __shared__ u16x8 sm[4][64];
   const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
   const int c = blockIdx.x * 64 + lane;
@@ -994,7 +995,11 @@ __global__ void __launch_bounds__(256) colmax_bf16_kernel(const u32x4* __restric
   __syncthreads();
   if (grp != 0 || c >= C8) return;
   m = __builtin_elementwise_max(__builtin_elementwise_max(m, sm[1][lane]), __builtin_elementwise_max(sm[2][lane], sm[3][lane]));
-  part[(size_t)blockIdx.y * C8 + c] = m;
+  if (part) part[(size_t)blockIdx.y * C8 + c] = m;
+  else {
+#pragma unroll
+    for (int j = 0; j < 8; j++) scales[8 * c + j] = scale_of_max(m[j]);
+  }
 }
 
 // (2): 16 pieces of 8 columns x 16 groups of slabs per workgroup
@@ -1039,10 +1044,7 @@ __global__ void __launch_bounds__(256) quantise_bf16_cols_kernel(const u32x4* __
 
 // Per column, the whole strip of W pieces of 8 columns held in registers between the maximum and the quantisation (one launch, X read once): a
 // workgroup of 1024, W neighbouring work items a row, NV rows each.  A strip's rows are parts of lines; strips next to each other go to the same
-// XCD, whose L2 puts the lines together.  Short matrices, whose launches cost as much as their bytes (a call, three launches -> one, us): 300 x 256
-// 12.7 -> 8.0, 1024 x 1024 12.2 -> 7.6, 1397 x 544 19.4 -> 8.6, 1536 x 16384 25.6 -> 21.4.  A tall one has fewer workgroups than the chip
-// has CUs, or too many registers: 2048 x 4096 13.4 -> 14.4, 4096 x 1024 12.1 -> 15.8, 8192 x 12896 93 -> 130.
-constexpr int HELD_ROWS = 1536;
+// XCD, whose L2 puts the lines together.  For which matrices, and what it measured beside the three launches: held_columns (tile_rule.hpp).
 template <int W, int NV>
 __global__ void __launch_bounds__(1024) quantise_bf16_held_cols_kernel(const u32x4* __restrict__ X, int R, int C8, u32x2* __restrict__ codes,
                                                                        float* __restrict__ scales) {
@@ -1110,15 +1112,14 @@ int launch_quantise_bf16(const void* X, int64_t R, int64_t C, int axis, void* co
     hipLaunchKernelGGL(kern, dim3((unsigned)(groups < most ? groups : most), (unsigned)((groups + most - 1) / most)), dim3(256), 0, s, x, R, C8, out, scales);
     return (int)hipGetLastError();
   }
-  if (R <= 512) return launch_held_cols<4, 2>(x, R, C8, out, scales, s);
-  if (R <= HELD_ROWS) return launch_held_cols<4, 6>(x, R, C8, out, scales, s);
+  if (held_columns(R, C)) return R <= 512 ? launch_held_cols<4, 2>(x, R, C8, out, scales, s) : launch_held_cols<4, 6>(x, R, C8, out, scales, s);
   // at most QC_SLABS slabs, each a whole number of QC_ROWS rows
   const int64_t slab_rows = ((R + QC_SLABS - 1) / QC_SLABS + QC_ROWS - 1) / QC_ROWS * QC_ROWS;
   const int slabs = (int)((R + slab_rows - 1) / slab_rows);
-  u16x8* part = static_cast<u16x8*>(codes);
+  u16x8* part = slabs > 1 ? static_cast<u16x8*>(codes) : nullptr;
   const unsigned nc = (unsigned)((C8 + 63) / 64);
-  hipLaunchKernelGGL(colmax_bf16_kernel, dim3(nc, (unsigned)slabs), dim3(256), 0, s, x, R, C8, slab_rows, part);
-  hipLaunchKernelGGL(col_scales_kernel, dim3((unsigned)((C8 + 15) / 16)), dim3(256), 0, s, part, C8, slabs, scales);
+  hipLaunchKernelGGL(colmax_bf16_kernel, dim3(nc, (unsigned)slabs), dim3(256), 0, s, x, R, C8, slab_rows, part, scales);
+  if (part) hipLaunchKernelGGL(col_scales_kernel, dim3((unsigned)((C8 + 15) / 16)), dim3(256), 0, s, part, C8, slabs, scales);
   hipLaunchKernelGGL(quantise_bf16_cols_kernel, dim3(nc * (unsigned)((R + QC_ROWS - 1) / QC_ROWS)), dim3(256), 0, s, x, R, C8, scales, out);
   return (int)hipGetLastError();
 }

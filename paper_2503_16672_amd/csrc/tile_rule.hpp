@@ -96,6 +96,19 @@ inline int pick_pair_tile(bool f8, int Md, int Ms, int N, int K, int sets) {
   return best;
 }
 
+// quantise_e4m3 per column (k_stream.hip): in one launch that holds strips of 32 columns in registers, or in three that read the matrix twice.
+// Three launches cost 5 us more to begin with; a strip keeps a workgroup of 1024 for 5 us and more whatever it holds, and its rows are half
+// lines.  So the strips win while they are few: one round of two workgroups a CU (16384 columns) up to 640 rows, whose registers that allows, one
+// workgroup a CU (8192 columns) up to 1536.  From 1024 rows on they win again where the matrix is larger than the caches and the second
+// reading costs, until the strips' partial lines do.  Three launches / one (R x C): 1 x 16384 1.34, 1 x 32768 0.78, 8 x 2^20 0.05, 512 x 8192 1.70, 512 x
+// 16384 1.22, 512 x 20480 0.88, 512 x 131072 0.85; 640 x 16384 1.05, 640 x 32768 0.96; 1024 x 8192 1.49, 1024 x 9216 0.93, 1024 x 24576 1.08, 1024 x 65536
+// 1.16, 1024 x 98304 0.94; 1536 x 8192 1.20, 1536 x 10240 0.78, 1536 x 14336 1.07, 1536 x 32768 1.35, 1536 x 65536 0.98.  Beyond 1536 rows the registers run out
+// (8192 x 12896 93 -> 130 us) or the CUs idle (2048 x 4096 13.4 -> 14.4, 4096 x 1024 12.1 -> 15.8).
+inline bool held_columns(long long R, long long C) {
+  if (R <= 640 && C <= 16384) return true;
+  return R <= 1536 && (C <= 8192 || (R >= 768 && R * C >= 5 << 22 && R * C <= 1 << 26));
+}
+
 // Row-major feature-wise re-compression (k_stream.hip): 64 x 64 tiles, 3-4 us whatever there is to do, up to 2^22 elements; above, tiles of
 // 128 tokens x 256 features, which move whole lines but keep a workgroup busy for 7.5 us.  Measured, 64 x 64 against 128 x 256, with
 // dZ: 128 x 64 2.8 / 7.4 us, 128 x 16384 4.6 / 9.3, 1280 x 3200 9.1 / 10.0, 2048 x 2048 7.8 / 9.8; 5248 x 896 10.7 / 9.8, 1792 x 3712 13.1 / 10.3.

@@ -144,3 +144,16 @@ def test_featurewise_tile_of_measured_shapes(tmp_path):
     (tmp_path / "main.cpp").write_text('#include "%s"\nusing namespace ffn24;\nint main() { return %s ? 0 : 1; }\n' % (RULE, checks))
     subprocess.run(["g++", "-std=c++17", "-o", str(tmp_path / "main"), str(tmp_path / "main.cpp")], check=True)
     assert subprocess.run([str(tmp_path / "main")]).returncode == 0
+
+
+def test_held_columns_of_measured_shapes(tmp_path):
+    """quantise_e4m3 per column: one launch where it was the faster one, three launches where they were (by 4 % and more)."""
+    held = [(1, 8), (1, 16384), (64, 16384), (512, 8192), (512, 16384), (640, 16384), (1024, 8192), (1024, 24576), (1024, 65536), (1280, 16384), (1536, 512), (1536, 8192), (1536, 16384), (1536, 32768)]
+    not_held = [(1, 32768), (1, 1 << 24), (8, 1 << 20), (64, 1 << 20), (256, 32768), (256, 1 << 18), (512, 20480), (512, 1 << 17), (640, 32768), (768, 20480), (896, 16384), (1024, 9216),
+                (1024, 98304), (1152, 12288), (1536, 10240), (1536, 98304), (1536, 1 << 17), (1537, 512), (2048, 4096), (4096, 1024), (8192, 12896), (1 << 24, 8), (1 << 24, 1 << 24)]
+    if not shutil.which("g++"):
+        pytest.skip("no host compiler")
+    checks = " && ".join([f"held_columns({r}, {c})" for r, c in held] + [f"!held_columns({r}, {c})" for r, c in not_held])
+    (tmp_path / "main.cpp").write_text('#include "%s"\nusing namespace ffn24;\nint main() { return %s ? 0 : 1; }\n' % (RULE, checks))
+    subprocess.run(["g++", "-std=c++17", "-o", str(tmp_path / "main"), str(tmp_path / "main.cpp")], check=True)
+    assert subprocess.run([str(tmp_path / "main")]).returncode == 0
