@@ -3,6 +3,7 @@
 #include <new>
 #include "../../include/ffn24.h"
 #include "launch.hpp"
+#include "tile_rule.hpp"
 
 using namespace ffn24;
 
@@ -155,7 +156,7 @@ bool overlap(const void* a, size_t na, const void* b, size_t nb) {
 struct Weights { const void *up, *down; int up_form, down_form; };
 
 // Weights of a bf16 forward call: both given (prepared copies are gone after it), or both NULL (use the copies ffn24_prepare_weights left).  Given,
-// they are read where they lie; a context that trains keeps them for the backward, W2 in panel form (A operand of the dH GEMM) and W1 in B panel
+// they are read where they lie (where copies are faster, weights_in_place, or Y lies over W2: re-arranged); a context that trains keeps them for the backward, W2 in panel form (A operand of the dH GEMM) and W1 in B panel
 // form (B operand of the dX GEMM), and the words of zero / zero2 are cleared, all in one launch.  Y is what the call will write.
 int resolve_weights16(ffn24_ctx* c, const void* W1, const void* W2, const void* Y, uint32_t* zero, int zero_n, uint32_t* zero2, int zero2_n, Weights* w, hipStream_t s) {
   const int D = (int)c->D, F = (int)c->F;
@@ -167,7 +168,7 @@ int resolve_weights16(ffn24_ctx* c, const void* W1, const void* W2, const void* 
     if (!W1 || !W2) return FFN24_ERR_NULL;
     if (misaligned(W1) || misaligned(W2)) return FFN24_ERR_ALIGN;
     c->prepared = 0;
-    if (fits_k_major(D, F) && !overlap(Y, 2 * (size_t)c->T * D, W2, 2 * (size_t)D * F)) {
+    if (fits_k_major(D, F) && weights_in_place(c->T, D, F, c->W1p != nullptr) && !overlap(Y, 2 * (size_t)c->T * D, W2, 2 * (size_t)D * F)) {
       *w = Weights{W1, W2, FORM_K_MAJOR, FORM_K_MAJOR};
       if (c->W1p) {
         pre.add_copy(W1, D, 2 * F, c->W1p, 1, nullptr, true);
@@ -204,11 +205,11 @@ int fp8_prologue(ffn24_ctx* c, const void* W1, const void* W2, const PaneliseJob
 }
 
 // dY and X as the weight gradients' B operands: as they lie, k-major, or (token permutation, whose rows the transposes gather; sizes without 32-bit
-// offsets; a gradient that lies over one of them) transposed, in B panel form.  act_pass makes the copies where
+// offsets; where copies are faster, acts_in_place; a gradient that lies over one of them) transposed, in B panel form.  act_pass makes the copies where
 // they are needed.
-WgradActs wgrad_acts(const ffn24_ctx* c, const void* dY, const int* perm, const void* dW1, const void* dW2) {
+WgradActs wgrad_acts(const ffn24_ctx* c, bool dense, const void* dY, const int* perm, const void* dW1, const void* dW2) {
   const size_t td = 2 * (size_t)c->T * c->D, df = 2 * (size_t)c->D * c->F;
-  bool direct = !perm && fits_k_major((int)c->T, (int)c->D);
+  bool direct = !perm && fits_k_major((int)c->T, (int)c->D) && acts_in_place(c->T, c->D, c->F, dense);
   for (const void* in : {dY, c->X})
     for (const void* out : {dW1, dW2}) direct = direct && !overlap(out, df, in, td);
   return direct ? WgradActs{dY, c->X, FORM_K_MAJOR} : WgradActs{c->dYt, c->Xt, FORM_PANEL};
@@ -688,7 +689,7 @@ int ffn24_fwd_static(const void* X, const void* W1, const float* b1, const void*
   unsigned char* base = nullptr;
   if ((rc = scratch_base(&base))) return rc;
   // carve-up of the scratch buffer: Hc [T][F/2] bf16 | meta [T][F/8] | W1^T [F][D] bf16 | W2^T [D][F] bf16 (panel forms).  The weights are read where
-  // they lie, though (what fits the scratch fits_k_major too), and re-arranged only where Y lies over W2.
+  // they lie, though (what fits the scratch fits_k_major too), and re-arranged only where that is faster (weights_in_place) or Y lies over W2.
   // Every byte a kernel below reads from it has been written by an earlier kernel of this same call, so nothing has to
   // start at zero and what a previous call left behind is never seen.
   const size_t tf = (size_t)T * (size_t)F, df = (size_t)D * (size_t)F;
@@ -696,7 +697,7 @@ int ffn24_fwd_static(const void* X, const void* W1, const float* b1, const void*
   uint8_t* meta = base + tf;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int Ti = (int)T, Di = (int)D, Fi = (int)F;
-  if (overlap(Y, 2 * (size_t)T * (size_t)D, W2, 2 * df)) {
+  if (overlap(Y, 2 * (size_t)T * (size_t)D, W2, 2 * df) || !weights_in_place(T, D, F, false)) {
     unsigned char *W1t = base + tf + tf / 8, *W2t = W1t + 2 * df;
     if (launch_transpose_weights(W1, W2, Di, Fi, W1t, nullptr, W2t, nullptr, s)) return FFN24_ERR_HIP;
     if (launch_up_prune24(W1t, FORM_PANEL, X, b1, Ti, Di, Fi, Hc, meta, nullptr, nullptr, nullptr, nullptr, s)) return FFN24_ERR_HIP;
@@ -819,7 +820,7 @@ int ffn24_bwd(ffn24_ctx* c, const void* dY, void* dX, void* dW1, void* dW2, void
     return FFN24_OK;
   }
   const int* perm = c->perm_on ? c->perm : nullptr;   // position p inside the FFN holds token perm[p]
-  const WgradActs w = wgrad_acts(c, dY, perm, dW1, dW2);
+  const WgradActs w = wgrad_acts(c, false, dY, perm, dW1, dW2);
   // the forward's two counts stay; the feature-wise one belongs to this backward
   if (c->tele && launch_zero32(reinterpret_cast<uint32_t*>(c->tele + tele_index(TELE_KEPT_FEAT, 0)), 2 * TELE_SLOTS * TELE_STRIDE, s)) return FFN24_ERR_HIP;
   { Timed t(c, K_DH, s);  if (t.done(launch_dh_gather(c->W2p, dY, c->Hc, c->meta, T, D, F, c->dZc, perm, s))) return FFN24_ERR_HIP; }
@@ -977,7 +978,7 @@ int ffn_bwd(ffn24_ctx* c, const void* dY, void* dX, void* dW1, void* dW2, void* 
   }
   { Timed t(c, KD_DH, s);  if (t.done(launch_dh_drelu(c->W2p, dY, c->Hd, T, D, F, c->dZd, c->dZd_t, s))) return FFN24_ERR_HIP; }
   { Timed t(c, KD_DX, s);  if (t.done(launch_dense_rowmajor(c->dZd, 1, c->W1p, 1, T, D, F, dX, s))) return FFN24_ERR_HIP; }
-  const WgradActs w = wgrad_acts(c, dY, nullptr, dW1, dW2);
+  const WgradActs w = wgrad_acts(c, true, dY, nullptr, dW1, dW2);
   if (act_pass(c, w, dY, nullptr, s)) return FFN24_ERR_HIP;
   if (!c->profiling) return launch_wgrad(c->Hd_t, c->dZd_t, nullptr, w.dY, w.X, w.form, F, D, T, dW2, dW1, s) ? FFN24_ERR_HIP : FFN24_OK;   // (profiling times the two by themselves)
   { Timed t(c, KD_DW2, s); if (t.done(launch_dense_rowmajor(c->Hd_t, 1, w.dY, w.form, F, D, T, dW2, s))) return FFN24_ERR_HIP; }

@@ -75,6 +75,27 @@ inline bool side_rides(bool sparse, int tile, int M, int N, int K) {
   return tile >= 2 && tile_count(sparse ? TILES_SPARSE[tile] : TILES_DENSE[tile], M, N) <= CHIP_CUS && (long long)M * K <= 1 << 22 && N <= 1024;
 }
 
+// A matrix read k-major as the B operand saves the pass that would re-arrange it, but the lanes of a 256 x 256 tile exchange their accumulators before they
+// are stored, 2.2-3.5 us for every round of the chip and GEMM, which a pass over a matrix that is small beside the result does not cost.
+// GEMMs: of that many results of `values` each; pass_ns: what the pass takes.
+inline bool in_place_is_better(long long values, int gemms, long long pass_ns) { return values < 2LL << 24 || gemms * 2900 * values >> 24 <= pass_ns; }
+
+// Weight gradients (D x F from T tokens; the pass goes over dY and X).  In place / copies, bf16 backwards (us, T D F): 256 4096 16384 238, 220; 1024
+// 4096 16384 435, 419; 2048 4096 16384 687, 670; 4096 4096 16384 1184, 1184; 256 8192 28672 703, 628; 2048 8192 28672 2204, 2131; 256 4096 8192 124, 118;
+// 512 8192 4096 164, 170; 3072 4096 8192 516, 513; 8192 4096 8192 1172, 1186; 16384 4096 8192 2275, 2353.  Below two rounds copies gain nothing that can be
+// told from noise and lose up to 20 % where launches count (512 512 2048 19.3, 23.4; 512 2048 12288 121, 122; dense 119, 133).
+// Few columns and a 2:4 operand: tiles of 64 columns read 128 bytes of a token's row at a time, which is slower than panels once the step's
+// tensors (6 T D + 4 1/4 T F bytes) no longer fit the last-level cache: 65536 512 512 349, 305; 65536 512 1024 451, 416; 65536 256 1024 352, 308; 131072 256 512
+// 627, 524; 262144 512 512 1460, 1364; still within it 32768 512 512 136, 154; 65536 256 256 188, 209; more columns 131072 768 768 971, 1047; 131072 512 2048
+// 1290, 1305; dense 65536 512 512 425, 420, 65536 512 1024 525, 538.
+inline bool acts_in_place(long long T, long long D, long long F, bool dense) {
+  if (!dense && D <= 512 && D * F <= 1 << 19 && T * (6 * D + 17 * F / 4) > 1 << 28) return false;
+  return in_place_is_better(D * F, 2, 5000 + T * D / 625);
+}
+// The weights in a forward, for W2 as the down-projection's B (keep: the context copies them in any case, for the backward).  In place / copies (us, T D F):
+// 65536 2048 512 262, 236; 131072 1024 512 281, 265; 16384 8192 1024 423, 375; 65536 4096 1024 767, 732; level 131072 1024 4096 1512, 1498.
+inline bool weights_in_place(long long T, long long D, long long F, bool keep) { return in_place_is_better(T * D, 1, keep ? D * F / 1150 : 5000 + D * F / 625); }
+
 // The tile of a dense and a sparse GEMM in one launch (same N and K, the dense tiles first), `sets` times: all tiles over the CUs, but no
 // less than the dense ones take by themselves (their epilogue is a plain store, and their tiles share CUs with sparse ones instead of
 // running in full rounds: the time per k of single launches).  The two parts make the estimate rougher, so a

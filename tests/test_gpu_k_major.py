@@ -82,3 +82,45 @@ def test_static(T, D, F):
         assert _equal(want, [ffn24.ffn24_fwd_static(X, W1, b1, W2, torch.empty_like(X))])
         Y, W2o = _over(W2, (T, D))
         assert _equal(want, [ffn24.ffn24_fwd_static(X, W1, b1, W2o, Y)])
+
+
+@pytest.mark.parametrize("T,D,F", [(256, 4096, 8192), (512, 8192, 4608)])
+@pytest.mark.parametrize("dense", [False, True])
+def test_gradients_from_copies(T, D, F, dense):
+    """Few tokens beside the gradients: dY and X are brought into panel form.  A feature's part of the gradients depends on no other feature, so a
+    step on 512 features, which reads them where they lie, has the same bits."""
+    X, W1, b1, W2, dY = _inputs(T, D, F)
+    got = []
+    for fs in (F, 512):
+        with closing(ffn24.Context(T, D, fs, ffn24.FFN24_TRAINING | (ffn24.FFN24_DENSE if dense else 0), ffn24.FFN24_BF16)) as c:
+            (c.ffn_fwd if dense else c.ffn24_fwd)(X, W1[:, :fs].contiguous(), b1[:fs].contiguous(), W2[:fs].contiguous())
+            got.append((c.ffn_bwd if dense else c.ffn24_bwd)(dY))
+    (_, dW1, dW2), (_, dW1s, dW2s) = got
+    assert _equal((dW1[:, :512].contiguous(), dW2[:512]), (dW1s, dW2s))
+
+
+@pytest.mark.parametrize("T,D,F", [(65536, 512, 512), (131072, 256, 512)])
+@pytest.mark.parametrize("dense", [False, True])
+def test_long_calls_from_copies(T, D, F, dense):
+    """Many tokens beside the weights: these are brought into panel form, and (2:4) the gradients take copies of dY and X.  A token's row of Y depends on no
+    other token: a forward on 1024 tokens, which reads the weights where they lie, and one with prepared weights have the same bits.  The gradients
+    are the sums of those of two halves of the tokens, which read dY and X where they lie, up to the rounding of three bf16 results."""
+    X, W1, b1, W2, dY = _inputs(T, D, F)
+
+    def step(lo, hi, weights=(W1, W2)):
+        with closing(ffn24.Context(hi - lo, D, F, ffn24.FFN24_TRAINING | (ffn24.FFN24_DENSE if dense else 0), ffn24.FFN24_BF16)) as c:
+            if weights[0] is None:
+                c.prepare_weights(W1, W2)
+            Y = (c.ffn_fwd if dense else c.ffn24_fwd)(X[lo:hi], weights[0], b1, weights[1])
+            return (Y, *(c.ffn_bwd if dense else c.ffn24_bwd)(dY[lo:hi]))
+
+    full = step(0, T)
+    assert _equal(full, step(0, T, (None, None)))
+    assert _equal([full[0][:1024]], step(0, 1024)[:1])
+    a, b = step(0, T // 2), step(T // 2, T)
+    for whole, x, y in zip(full[2:], a[2:], b[2:]):
+        whole, x, y = whole.double(), x.double(), y.double()
+        # a bf16 rounding is at most 2^-9 of the value; the fp32 sums of up to T terms in another order stay below 2^-12 of the 2-norm
+        bound = 2.0 ** -9 * (whole.norm() + x.norm() + y.norm()) + 2.0 ** -12 * whole.norm()
+        assert float((whole - x - y).norm()) <= float(bound)
+    assert _equal([full[1]], [torch.cat([a[1], b[1]])])
