@@ -171,8 +171,8 @@ int resolve_weights16(ffn24_ctx* c, const void* W1, const void* W2, const void* 
     if (fits_k_major(D, F) && weights_in_place(c->T, D, F, c->W1p != nullptr) && !overlap(Y, 2 * (size_t)c->T * D, W2, 2 * (size_t)D * F)) {
       *w = Weights{W1, W2, FORM_K_MAJOR, FORM_K_MAJOR};
       if (c->W1p) {
-        pre.add_copy(W1, D, 2 * F, c->W1p, 1, nullptr, true);
-        pre.add_copy(W2, F, 2 * D, c->W2p, 0, nullptr, true);
+        pre.add_copy(W1, D, 2 * F, c->W1p, 1, nullptr);
+        pre.add_copy(W2, F, 2 * D, c->W2p, 0, nullptr);
       }
     } else if (int rc = weight_pass(c, W1, W2, nullptr, s)) {
       return rc;

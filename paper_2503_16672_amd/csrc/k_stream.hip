@@ -140,7 +140,7 @@ int launch_sparsify24(const void* H, int64_t rows, int64_t cols, void* vals, uin
   return (int)hipGetLastError();
 }
 
-template <bool PANEL, bool SPLIT = false>
+template <bool PANEL, bool SPLIT = false, bool KEEP = false>
 __global__ void __launch_bounds__(256) featurewise24_kernel(const uint16_t* __restrict__ Hc, const uint8_t* __restrict__ meta,
                                                             const uint16_t* __restrict__ dZc, int T, int F, int tiles,
                                                             uint16_t* __restrict__ Hc_t, uint8_t* __restrict__ meta_t,
@@ -149,7 +149,7 @@ __global__ void __launch_bounds__(256) featurewise24_kernel(const uint16_t* __re
                                                             unsigned long long* __restrict__ tele, uint32_t* __restrict__ hmax,
                                                             uint32_t* __restrict__ zmax) {
   __shared__ uint32_t lds[FW_LDS / 4];
-  featurewise24_tiles<PANEL, SPLIT>(Hc, meta, dZc, T, F, tiles, Hc_t, meta_t, dZc_t, row_of_feat, n_sparse, Hdn_t, dZdn_t, tele, hmax, zmax, blockIdx.x,
+  featurewise24_tiles<PANEL, SPLIT, KEEP>(Hc, meta, dZc, T, F, tiles, Hc_t, meta_t, dZc_t, row_of_feat, n_sparse, Hdn_t, dZdn_t, tele, hmax, zmax, blockIdx.x,
                                     blockIdx.y, lds);
 }
 
@@ -289,7 +289,8 @@ int launch_featurewise24_rows(const void* Hc, const uint8_t* meta, const void* d
 int launch_featurewise24(const void* Hc, const uint8_t* meta, const void* dZc, int T, int F,
                          void* Hc_t, uint8_t* meta_t, void* dZc_t, unsigned long long* tele, hipStream_t s) {
   dim3 grid(F / FW_FEAT, T / FW_TOK);
-  hipLaunchKernelGGL(featurewise24_kernel<true>, grid, dim3(256), 0, s, static_cast<const uint16_t*>(Hc), meta,
+  auto kern = fw_keep(T, F) ? featurewise24_kernel<true, false, true> : featurewise24_kernel<true>;
+  hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, static_cast<const uint16_t*>(Hc), meta,
                      static_cast<const uint16_t*>(dZc), T, F, 1, static_cast<uint16_t*>(Hc_t), meta_t, static_cast<uint16_t*>(dZc_t),
                      nullptr, 0, nullptr, nullptr, tele, nullptr, nullptr);
   return (int)hipGetLastError();
@@ -299,7 +300,8 @@ int launch_featurewise24(const void* Hc, const uint8_t* meta, const void* dZc, i
 int launch_featurewise24_rowmax(const void* Hc, const uint8_t* meta, const void* dZc, int T, int F, void* Hc_t, uint8_t* meta_t, void* dZc_t,
                                 uint32_t* hmax, uint32_t* zmax, hipStream_t s) {
   dim3 grid(F / FW_FEAT, T / FW_TOK);
-  hipLaunchKernelGGL(featurewise24_kernel<true>, grid, dim3(256), 0, s, static_cast<const uint16_t*>(Hc), meta,
+  auto kern = fw_keep(T, F) ? featurewise24_kernel<true, false, true> : featurewise24_kernel<true>;
+  hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, static_cast<const uint16_t*>(Hc), meta,
                      static_cast<const uint16_t*>(dZc), T, F, 1, static_cast<uint16_t*>(Hc_t), meta_t, static_cast<uint16_t*>(dZc_t),
                      nullptr, 0, nullptr, nullptr, nullptr, hmax, zmax);
   return (int)hipGetLastError();
@@ -310,7 +312,8 @@ int launch_featurewise24_split(const void* Hc, const uint8_t* meta, const void* 
                                uint32_t* hmax, uint32_t* zmax, hipStream_t s) {
   const int tiles = fw_tiles(T, F, hmax != nullptr);
   dim3 grid(F / FW_FEAT, T / (FW_TOK * tiles));
-  hipLaunchKernelGGL((featurewise24_kernel<true, true>), grid, dim3(256), 0, s, static_cast<const uint16_t*>(Hc), meta,
+  auto kern = fw_keep(T, F) ? featurewise24_kernel<true, true, true> : featurewise24_kernel<true, true>;
+  hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, static_cast<const uint16_t*>(Hc), meta,
                      static_cast<const uint16_t*>(dZc), T, F, tiles, static_cast<uint16_t*>(Hc_t), meta_t, static_cast<uint16_t*>(dZc_t),
                      row_of_feat, n_sparse, static_cast<uint16_t*>(Hdn_t), static_cast<uint16_t*>(dZdn_t), tele, hmax, zmax);
   return (int)hipGetLastError();
@@ -647,6 +650,9 @@ __device__ __forceinline__ void transpose8_tile(const TransposeJob& job, int til
 //     rowmap[r] if one is given (token permutation); 16 bytes per work item;
 //   zero: 32-bit words cleared (row maxima, counts);
 //   gather: dst[i] = src[map[i]], a per-token scale vector brought into the order of a token permutation.
+// No streaming hints: what is copied here is read again, the copy right away and the input by a later pass of the step (weights with the hints on loads and
+// stores: the down-projection behind them at T 1024 D 1024 F 4096 20.8 us against 15.2, the copies at T = F = 16384 D 4096 100 against 83; X with the
+// hint on its loads alone: fp8 step at T 4096 D 2048 F 8192 325 against 322.6).
 __device__ __forceinline__ void panelise8_block(const PaneliseJobs& jobs, unsigned bid) {
 #pragma unroll
   for (int j = 0; j < PaneliseJobs::COPIES; j++) {
@@ -661,8 +667,7 @@ __device__ __forceinline__ void panelise8_block(const PaneliseJobs& jobs, unsign
       const size_t src = cp.rowmap ? (size_t)cp.rowmap[r] * per_row + cq : i;
       u32x4* out = reinterpret_cast<u32x4*>(static_cast<uint8_t*>(cp.out) + a24_piece(prow, c >> 6, cp.C >> 6) * 64 + (c & 63));
       const u32x4* in = static_cast<const u32x4*>(cp.in) + src;
-      if (cp.keep) *out = *in;
-      else st_keep(out, ld_stream(in));
+      *out = *in;
       return;
     }
     bid -= cp.blocks;

@@ -199,15 +199,14 @@ int launch_unpanel(const void* src, int rows, int npanels, int piece_bytes, void
 // form, up to three word arrays cleared, one scale vector gathered
 struct PaneliseJobs {
   static constexpr int COPIES = 3, ZEROS = 3;
-  struct Copy { const void* in; int R, C; void* out; int b_form; const int* rowmap; unsigned blocks; bool keep; } copy[COPIES] = {};
+  struct Copy { const void* in; int R, C; void* out; int b_form; const int* rowmap; unsigned blocks; } copy[COPIES] = {};
   uint32_t* zero[ZEROS] = {};
   int zero_n[ZEROS] = {};
   const float* gather_src = nullptr; const int* gather_map = nullptr; float* gather_dst = nullptr; int gather_n = 0;
   int copies = 0, zeros = 0;   // (host side: slots in use)
-  // R x C bytes, C % 64 == 0, R % 256 == 0; keep: no streaming hints, the input is read again right away (the weights' copies: with the hints the
-  // GEMMs behind them took longer, T 1024 D 1024 F 4096 down-projection 20.8 us against 15.2, and at T = F = 16384 D 4096 the copies, 100 against 83)
-  void add_copy(const void* in, int R, int C, void* out, int b_form, const int* rowmap, bool keep = false) {
-    copy[copies++] = Copy{in, R, C, out, b_form, rowmap, (unsigned)(((size_t)R * (C >> 4) + 255) / 256), keep};
+  // R x C bytes, C % 64 == 0, R % 256 == 0
+  void add_copy(const void* in, int R, int C, void* out, int b_form, const int* rowmap) {
+    copy[copies++] = Copy{in, R, C, out, b_form, rowmap, (unsigned)(((size_t)R * (C >> 4) + 255) / 256)};
   }
   void add_zero(uint32_t* p, int n) { zero[zeros] = p; zero_n[zeros++] = n; }
   void set_gather(const float* src, const int* map, int n, float* dst) { gather_src = src; gather_map = map; gather_n = n; gather_dst = dst; }

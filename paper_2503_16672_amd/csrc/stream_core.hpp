@@ -9,8 +9,7 @@ namespace ffn24 {
 // hint (measured on a plain copy: 6.0-6.5 TB/s with it, 5.6-6.1 without).
 template <class T> __device__ __forceinline__ T ld_stream(const T* p) { return __builtin_nontemporal_load(p); }
 template <class T> __device__ __forceinline__ void st_stream(T* p, T v) { __builtin_nontemporal_store(v, p); }
-// What the next kernels read again is stored without it: the caches then still hold some of it (operands brought into another form: row-wise fp8
-// step at T = F = 8192, D = 2048 773 -> 765 us, T = F = 16384, D = 4096 in bf16 the same).
+// What the next kernels read again is stored without it (operands brought into another form, small transposed ones): the caches then still hold some of it.
 template <class T> __device__ __forceinline__ void st_keep(T* p, T v) { *p = v; }
 
 // Feature-wise 2:4 on top of the token-wise mask (Sec. 2, last paragraph; Fig. 2c).
@@ -45,8 +44,10 @@ __device__ __forceinline__ uint32_t halves_hi(uint32_t a, uint32_t b) { return _
 // SPLIT (Sec. 2, "Optimization 1"; panel form only): feature f becomes row row_of_feat[f] of the outputs; rows below
 // n_sparse are 2:4-compressed along tokens as above, the others -- the least sparse features -- are written out
 // uncompressed, as rows [row - n_sparse] of the dense operands Hdn_t, dZdn_t [n_dense][T] (dense panel form).
+// KEEP (compressed outputs in the panel form; fw_keep): stored without the streaming hint.  A template argument: where only a value tells two such
+// stores apart the compiler makes one store of them, without the hint.
 // (bx, by): which workgroup of a grid of F / FW_FEAT by T / (FW_TOK tiles); sH: FW_LDS bytes
-template <bool PANEL, bool SPLIT = false>
+template <bool PANEL, bool SPLIT = false, bool KEEP = false>
 __device__ __forceinline__ void featurewise24_tiles(const uint16_t* __restrict__ Hc, const uint8_t* __restrict__ meta, const uint16_t* __restrict__ dZc, int T,
                                                     int F, int tiles, uint16_t* __restrict__ Hc_t, uint8_t* __restrict__ meta_t,
                                                     uint16_t* __restrict__ dZc_t, const int* __restrict__ row_of_feat, int n_sparse,
@@ -57,9 +58,6 @@ __device__ __forceinline__ void featurewise24_tiles(const uint16_t* __restrict__
   const int f0 = bx * FW_FEAT, t_first = by * FW_TOK * tiles;
   const int tid = threadIdx.x;
   const bool has_z = dZc != nullptr;
-  // small operands stay in the caches for the weight gradients (T 1280 D 768 F 3072: step 68.1 -> 66.9 us); large ones would push out what else is
-  // there (T = F = 16384, D 4096: 7346 -> 7397; T = F = 8192 772 -> 774)
-  const bool keep = PANEL && (size_t)T * F <= 1 << 24;
   const int tok = tid >> 2, ch = tid & 3;            // in: 16 features of a token
   const int oct = tid & 7, word = tid >> 3;          // out: 8 tokens of features fa and fa + 8
   const int fa = ((word >> 3) << 4) | (word & 7);
@@ -160,7 +158,7 @@ __device__ __forceinline__ void featurewise24_tiles(const uint16_t* __restrict__
       const size_t vo = piece * 32 + 4 * oct, mo = piece * 8 + oct;
       const u32x2 hv2 = {hp[b][0], hp[b][1]}, zv2 = {zp[b][0], zp[b][1]};
       const uint8_t mv2 = (uint8_t)(b ? nib >> 16 : nib);
-      if (keep) {
+      if constexpr (KEEP) {
         st_keep(reinterpret_cast<u32x2*>(Hc_t + vo), hv2);
         if (has_z) st_keep(reinterpret_cast<u32x2*>(dZc_t + vo), zv2);
         st_keep(meta_t + mo, mv2);
@@ -200,13 +198,19 @@ __device__ __forceinline__ void featurewise24_tiles(const uint16_t* __restrict__
   }
 }
 
+// Operands that the last-level cache (256 MB) can hold beside what else the weight gradients read stay there for them; larger ones would push that out.
+// With the hint / without, whole steps (us, T D F): bf16 8192 512 4096 204, 192; 8192 1024 4096 323, 313; 4096 1024 5120 228, 222; 8192 1024 6144 level;
+// 16384 512 4096 375, 394; 8192 2048 8192 982, 991; 10240 2048 8192 1283, 1314; 131072 512 1024 1063, 1164; 16384 4096 16384 7067, 7088; the other way round at
+// 16384 1024 4096 599, 581 and 12288 1024 8192 864, 853; with a split or row maxima within 1 %.
+inline bool fw_keep(int T, int F) { return (size_t)T * F < 1 << 26; }
+
 // Work that rides beside a GEMM's tiles in one launch (gemm_side_kernel): run(args, workgroup, LDS).
 // The feature-wise re-compression (panel form, one tile of tokens a workgroup), beside the dX GEMM, which needs nothing of it.
 struct SideFeaturewise {
   struct Args { const uint16_t* Hc; const uint8_t* meta; const uint16_t* dZc; int T, F; uint16_t* Hc_t; uint8_t* meta_t; uint16_t* dZc_t; };
   static __device__ __forceinline__ void run(const Args& a, unsigned bid, char* smem) {
     const unsigned nx = (unsigned)a.F / FW_FEAT;
-    featurewise24_tiles<true>(a.Hc, a.meta, a.dZc, a.T, a.F, 1, a.Hc_t, a.meta_t, a.dZc_t, nullptr, 0, nullptr, nullptr, nullptr, nullptr, nullptr, (int)(bid % nx),
+    featurewise24_tiles<true, false, true>(a.Hc, a.meta, a.dZc, a.T, a.F, 1, a.Hc_t, a.meta_t, a.dZc_t, nullptr, 0, nullptr, nullptr, nullptr, nullptr, nullptr, (int)(bid % nx),
                               (int)(bid / nx), reinterpret_cast<uint32_t*>(smem));
   }
 };

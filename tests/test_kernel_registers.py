@@ -53,6 +53,20 @@ def test_row_maxima_leave_in_whole_waves(assembly, epilogue):
     assert body.count("global_atomic_umax") == 2
 
 
+def _body(text, name):
+    name = re.search(rf"^(_ZN5ffn24{name}\S*):", text, re.M)[1]
+    return text[text.index(f"\n{name}:"):text.index(f".size\t{name},")]
+
+
+@pytest.mark.parametrize("split", [0, 1])
+@pytest.mark.parametrize("keep", [0, 1])
+def test_transposed_operands_keep_their_hints(assembly, split, keep):
+    """The feature-wise re-compression of the panel form in its two variants: without the streaming hint on the compressed outputs (KEEP), and with it on
+    every one (of two features: values, dZ values and metadata each).  Told apart by a value alone, the compiler makes one store of the two."""
+    stores = re.findall(r"^\s*global_store_\S+ .*", _body(assembly["k_stream"], f"20featurewise24_kernelILb1ELb{split}ELb{keep}E"), re.M)
+    assert sum(" nt" in s for s in stores) == (0 if keep else 6) and len(stores) >= 6
+
+
 @pytest.fixture(scope="module")
 def report(assembly):
     """translation unit -> kernel name -> (spilled registers, bytes of scratch a work item)"""
