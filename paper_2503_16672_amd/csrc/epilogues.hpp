@@ -235,7 +235,8 @@ struct ColMajorStage {
   static __device__ __forceinline__ void put(char* wbuf, int ni, int c, u32x4 v) { *reinterpret_cast<u32x4*>(wbuf + at(NI * LT::rho() + ni, 2 * MI * LT::h() + c)) = v; }
   // C, ldc: the whole result; m_lane, n_lane: the lane's
   static __device__ __forceinline__ void flush(const char* wbuf, __bf16* C, int ldc, int m_lane, int n_lane) {
-    asm volatile("" : "+s"(C));   // (uniform up to here: copied to vector registers ahead of the main loop's tail, with k-major operands, it was spilled)
+    // (256 x 256: uniform up to here; copied to vector registers ahead of the main loop's tail, with k-major operands, it was spilled)
+    if constexpr (LT::LANES == 16) asm volatile("" : "+s"(C));
     __bf16* out = C + (size_t)(n_lane - NI * LT::rho()) * ldc + (m_lane - 16 * MI * LT::h());
     const int lane = lane_id(), c = lane & (PIECES - 1), sub = lane / PIECES;
     constexpr int PER = 64 / PIECES;   // rows per store instruction
