@@ -68,11 +68,13 @@ inline bool apart_is_better(bool f8, long long n, int K, int min_rounds) {
 }
 
 // The feature-wise re-compression in one launch with the dX GEMM (M x N, reduction K; the re-compression goes over M x K): where the tiles, of a kind that
-// shares a CU, leave places free from the start, and the GEMM is short.  Apart, together, whole steps (us, T D F): 256 512 2048 35.6, 33.9; 1536 512
-// 2048 46.7, 45.0; 4096 512 1024 51.0, 49.5; 768 768 3072 59.3, 58.1; 1280 768 3072 65.9, 65.4; 1024 1024 4096 77.8, 77.8; beyond the line 1024 2048 4096
-// 115.8, 119.9; 2048 1024 4096 115, 119; 256 2048 8192 130, 134.
+// shares a CU, leave places free from the start, and the GEMM is short.  Apart, together, whole steps (us, T D F).  64 x 64 tiles: 256 512 2048 35.7, 33.5; 1536
+// 512 2048 46.7, 45.4; 768 768 3072 59.3, 58.5; 1280 768 3072 65.9, 65.4; 512 1024 4096 62.5, 62.2.  128 x 64: 4096 512 1024 50.3, 48.9; 8192 256 512 52.2, 50.7.
+// 128 x 128: 8192 512 512 61.4, 59.8; 2304 1024 1280 65.3, 64.9; 4096 1024 1024 69.3, 67.9; 3072 1024 1280 71.8, 70.9.  Beyond the lines 1024 1024 4096 78.0, 78.8; 2048 1024
+// 2048 69.0, 70.1; 1536 1024 2560 74.4, 75.5; 2048 768 3072 83.8, 86.1; 2048 512 4096 79.7, 80.6; 1024 1536 2048 64.9, 65.9; 1280 1280 5120 121.5, 126.3.
 inline bool side_rides(bool sparse, int tile, int M, int N, int K) {
-  return tile >= 2 && tile_count(sparse ? TILES_SPARSE[tile] : TILES_DENSE[tile], M, N) <= CHIP_CUS && (long long)M * K <= 1 << 22 && N <= 1024;
+  return tile >= 2 && tile_count(sparse ? TILES_SPARSE[tile] : TILES_DENSE[tile], M, N) <= CHIP_CUS && (long long)M * K <= 1 << 22 && N <= 1024 &&
+         (K <= 1280 || (long long)M * N * K <= 3LL << 30);
 }
 
 // A matrix read k-major as the B operand saves the pass that would re-arrange it, but the lanes of a 256 x 256 tile exchange their accumulators before they

@@ -1,6 +1,6 @@
 """bf16 GEMMs that read a caller's matrix with k as its slow dimension (W1, W2, X, dY where they lie): the same products in the same order as from
 the re-arranged copies, so the results are equal bit for bit.  Sizes: every block tile in the up-projection, the down-projection and the weight
-gradients, with one to many stages of the ring."""
+gradients, together, alone and with a split, and beside the feature-wise re-compression in dX (test_tile_rule.py), with one to many stages of the ring."""
 from contextlib import closing
 
 import numpy as np
@@ -11,7 +11,8 @@ from paper_2503_16672_amd import ffn24
 
 pytestmark = pytest.mark.gpu
 
-SIZES = [(256, 256, 512), (256, 512, 2048), (768, 512, 2048), (1280, 768, 3072), (2048, 1024, 4096), (2048, 1280, 5120), (4096, 2048, 8192), (8192, 2048, 8192)]
+SIZES = [(256, 256, 512), (256, 512, 2048), (768, 512, 2048), (1280, 768, 3072), (2048, 1024, 4096), (2048, 1280, 5120), (4096, 2048, 8192), (8192, 2048, 8192),
+         (4096, 512, 1024), (2304, 1024, 1280)]
 
 
 def _inputs(T, D, F):
@@ -35,7 +36,7 @@ def _over(a, shape):
 @pytest.mark.parametrize("T,D,F", SIZES)
 @pytest.mark.parametrize("split", [0, 256])
 def test_block(T, D, F, split):
-    if split and (F < 1024 or T > 2048):
+    if split and (F < 1024 or (T > 2048 and F > 1280)):
         pytest.skip("a quarter of the features at most; the pair's tiles are covered by the smaller sizes")
     X, W1, b1, W2, dY = _inputs(T, D, F)
     with closing(ffn24.Context(T, D, F, ffn24.FFN24_TRAINING | ffn24.FFN24_PERMUTE | (ffn24.FFN24_SPLIT if split else 0), ffn24.FFN24_BF16)) as c:

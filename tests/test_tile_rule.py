@@ -8,6 +8,7 @@ from pathlib import Path
 import pytest
 
 from test_gpu_big_tiles import SIZES as BIG_SIZES
+from test_gpu_k_major import SIZES as K_MAJOR_SIZES
 from test_gpu_pick import SHAPES as PICK_SHAPES
 
 RULE = Path(__file__).resolve().parents[1] / "paper_2503_16672_amd" / "csrc" / "tile_rule.hpp"
@@ -91,6 +92,34 @@ def test_shape_of_the_big_tile_tests_takes_them_everywhere(picks):
     assert 0 not in picks(products(512, F)) and 0 not in picks(gradients(T, 256))
 
 
+def test_sizes_of_the_k_major_tests_take_every_tile(picks, tmp_path):
+    """... in each of the GEMMs that they name; and those beside which the re-compression rides take the three tiles that it may."""
+    every = set(range(5))
+    assert set(picks([(0, 0, "p", F, T, D, 1) for T, D, F in K_MAJOR_SIZES])) == every                     # up-projection
+    for sparse in (0, 1):
+        assert set(picks([(sparse, 0, "p", T, D, F, 1) for T, D, F in K_MAJOR_SIZES])) == every            # down-projection, dX
+        assert set(picks([(sparse, 0, "p", F, D, T, 2) for T, D, F in K_MAJOR_SIZES])) == every            # weight gradients together
+        assert set(picks([(sparse, 0, "p", F, D, T, 1) for T, D, F in K_MAJOR_SIZES])) == every            # ... alone
+    split = [s for s in K_MAJOR_SIZES if s[2] >= 1024 and not (s[0] > 2048 and s[2] > 1280)]
+    (tmp_path / "main.cpp").write_text("""
+#include "%s"
+#include <cstdio>
+using namespace ffn24;
+int main() {
+  int T, D, F;
+  while (std::scanf("%%d %%d %%d", &T, &D, &F) == 3) {
+    const int dx = pick_tile(true, false, EPI_PLAIN, T, D, F);
+    std::printf("%%d %%d\\n", pick_pair_tile(false, 256, F - 256, D, T, 2), side_rides(true, dx, T, D, F) ? dx : -1);
+  }
+}
+""" % RULE)
+    subprocess.run(["g++", "-std=c++17", "-o", str(tmp_path / "main"), str(tmp_path / "main.cpp")], check=True)
+    run = lambda sizes: [tuple(map(int, line.split())) for line in
+                         subprocess.run([str(tmp_path / "main")], input="\n".join(" ".join(map(str, s)) for s in sizes), capture_output=True, text=True, check=True).stdout.splitlines()]
+    assert {pair for pair, _ in run(split)} == every
+    assert {rides for _, rides in run(K_MAJOR_SIZES)} == {-1, 2, 3, 4}
+
+
 def test_two_full_gemms_take_the_large_tile_alone_too(tmp_path):
     """Where two GEMMs together take the 256 x 256 tile and each fills whole rounds with it, they are launched apart with that tile: one of
     them by itself has to pick it as well."""
@@ -133,6 +162,32 @@ def test_launches_apart(tmp_path):
     text = "\n".join(" ".join(str(x) for x in q) for q, _ in TOGETHER)
     got = subprocess.run([str(tmp_path / "main")], input=text, capture_output=True, text=True, check=True).stdout.split()
     assert [int(x) for x in got] == [a for _, a in TOGETHER]
+
+
+def test_rides_beside_dx_at_measured_shapes(tmp_path):
+    """The feature-wise re-compression beside the dX GEMM: where whole steps were faster so, with each of the three tiles, and not where they were
+    slower by 1 % and more."""
+    if not shutil.which("g++"):
+        pytest.skip("no host compiler")
+    rides = [((256, 512, 2048), 4), ((1536, 512, 2048), 4), ((768, 768, 3072), 4), ((1280, 768, 3072), 4), ((512, 1024, 4096), 4), ((4096, 512, 1024), 3), ((8192, 256, 512), 3),
+             ((8192, 512, 512), 2), ((2304, 1024, 1280), 2), ((4096, 1024, 1024), 2), ((3072, 1024, 1280), 2)]
+    apart = [(1024, 1024, 4096), (2048, 1024, 2048), (1536, 1024, 2560), (2048, 768, 3072), (2048, 512, 4096), (1024, 1536, 2048), (1280, 1280, 5120)]
+    (tmp_path / "main.cpp").write_text("""
+#include "%s"
+#include <cstdio>
+using namespace ffn24;
+int main() {
+  int T, D, F;
+  while (std::scanf("%%d %%d %%d", &T, &D, &F) == 3) {
+    const int tile = pick_tile(true, false, EPI_PLAIN, T, D, F);
+    std::printf("%%d\\n", side_rides(true, tile, T, D, F) ? tile : -1);
+  }
+}
+""" % RULE)
+    subprocess.run(["g++", "-std=c++17", "-o", str(tmp_path / "main"), str(tmp_path / "main.cpp")], check=True)
+    text = "\n".join(" ".join(map(str, x)) for x in [s for s, _ in rides] + apart)
+    got = [int(x) for x in subprocess.run([str(tmp_path / "main")], input=text, capture_output=True, text=True, check=True).stdout.split()]
+    assert got == [tile for _, tile in rides] + [-1] * len(apart)
 
 
 def test_in_place_or_copied_at_measured_shapes(tmp_path):
