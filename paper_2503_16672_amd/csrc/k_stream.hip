@@ -909,9 +909,10 @@ int launch_rowmax_dense(const void* X16, int R, int C, uint32_t* rmax, hipStream
 
 // Per row, the whole row held in registers between the maximum and the quantisation: LANES work items per row (a wave, or the workgroup
 // for rows beyond 4096 values), up to NV 16-byte pieces each, all requested before the first is used.  KEEP: without the streaming hint, for a matrix
-// that the caches hold and that is quantised per column as well (one call after the other, 8192 x 4096: 55.5 -> 52.6 us, and the rows alone
-// 18.8 -> 17.9; larger ones lose, 16384 x 4096 35.3 -> 37.8, 16384 x 16384 129 -> 144).
-constexpr int64_t KEEP_VALUES = 1 << 25;
+// that the last-level cache (256 MB) holds and that is quantised per column as well (rows and columns in either order, with the hint / without: 8192 x
+// 2048 34.5, 33.2 us; 8192 x 4096 55.4, 52.7; 8192 x 6144 73.9, 70.1; 12288 x 4096 78.3, 76.3; 16384 x 4096 99.2, 98.5; 8192 x 16384 182, 186; 16384 x 16384 356, 368; the
+// rows alone 3 % either way up to 2^27 values, 16384 x 16384 129, 143).
+constexpr int64_t KEEP_VALUES = 1 << 26;
 template <int LANES, int NV, bool KEEP>
 __global__ void __launch_bounds__(256) quantise_bf16_rows_kernel(const u32x4* __restrict__ X, int64_t R, int C8, u32x2* __restrict__ codes,
                                                                  float* __restrict__ scales) {
