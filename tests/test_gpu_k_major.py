@@ -33,6 +33,18 @@ def _over(a, shape):
     return buf[:n].view(shape), buf[:a.numel()].view(a.shape)
 
 
+def _needs(gib):
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < gib << 30:
+        pytest.skip(f"needs {gib} GiB of device memory")
+
+
+def _sum_of_parts(whole, *parts):
+    """The parts' sum up to the bf16 rounding of each (2^-9 of a value) and fp32 sums in another order (below 2^-12 of the 2-norm)."""
+    w, p = whole.double(), [x.double() for x in parts]
+    return float((w - sum(p)).norm()) <= 2.0 ** -9 * float(w.norm() + sum(x.norm() for x in p)) + 2.0 ** -12 * float(w.norm())
+
+
 @pytest.mark.parametrize("T,D,F", SIZES)
 @pytest.mark.parametrize("split", [0, 256])
 def test_block(T, D, F, split):
@@ -119,9 +131,61 @@ def test_long_calls_from_copies(T, D, F, dense):
     assert _equal(full, step(0, T, (None, None)))
     assert _equal([full[0][:1024]], step(0, 1024)[:1])
     a, b = step(0, T // 2), step(T // 2, T)
-    for whole, x, y in zip(full[2:], a[2:], b[2:]):
-        whole, x, y = whole.double(), x.double(), y.double()
-        # a bf16 rounding is at most 2^-9 of the value; the fp32 sums of up to T terms in another order stay below 2^-12 of the 2-norm
-        bound = 2.0 ** -9 * (whole.norm() + x.norm() + y.norm()) + 2.0 ** -12 * whole.norm()
-        assert float((whole - x - y).norm()) <= float(bound)
+    assert all(_sum_of_parts(*parts) for parts in zip(full[2:], a[2:], b[2:]))
     assert _equal([full[1]], [torch.cat([a[1], b[1]])])
+
+
+def test_weights_beyond_2_gib():
+    """Offsets inside a k-major operand are 32-bit: weights of 3 GiB each, both as A and as B, against the re-arranged copies, whose offsets are small."""
+    T, D, F = 256, 1536, 1 << 20
+    _needs(40)
+    print(f"weights of 3 GiB T={T} D={D} F={F}", flush=True)
+    X, W1, b1, W2, _ = _inputs(T, D, F)
+    with closing(ffn24.Context(T, D, F, 0, ffn24.FFN24_BF16)) as c:
+        Y = c.ffn24_fwd(X, W1, b1, W2).clone()
+        c.prepare_weights(W1, W2)
+        assert float(Y.float().abs().max()) > 0 and _equal([Y], [c.ffn24_fwd(X, None, b1, None)])
+
+
+def test_activations_beyond_2_gib():
+    """X and dY of 3 GiB: k-major in the weight gradients, and gathered by a token permutation with 32-bit offsets from their first row (the identity, against
+    the rows as they stand, whose offsets are small)."""
+    T, D, F = 98304, 16384, 512
+    _needs(64)
+    print(f"activations of 3 GiB T={T} D={D} F={F}", flush=True)
+    X, W1, b1, W2, dY = _inputs(T, D, F)
+    with closing(ffn24.Context(T, D, F, ffn24.FFN24_TRAINING | ffn24.FFN24_PERMUTE, ffn24.FFN24_BF16)) as c:
+        got = [c.ffn24_fwd(X, W1, b1, W2).clone(), *c.ffn24_bwd(dY)]
+        c.set_token_permutation(np.arange(T, dtype=np.int32))
+        assert _equal(got, [c.ffn24_fwd(X, W1, b1, W2), *c.ffn24_bwd(dY)])
+
+
+def test_weights_of_4_gib_take_copies():
+    """Beyond 32-bit offsets the weights are re-arranged.  Y is the sum over the two halves of the features, whose weights (2 GiB) are read where they lie."""
+    T, D, F = 256, 2048, 1 << 20
+    _needs(48)
+    print(f"weights of 4 GiB T={T} D={D} F={F}", flush=True)
+    X, W1, b1, W2, _ = _inputs(T, D, F)
+
+    def forward(lo, hi):
+        with closing(ffn24.Context(T, D, hi - lo, 0, ffn24.FFN24_BF16)) as c:
+            return c.ffn24_fwd(X, W1[:, lo:hi].contiguous(), b1[lo:hi].contiguous(), W2[lo:hi].contiguous())
+
+    assert _sum_of_parts(forward(0, F), forward(0, F // 2), forward(F // 2, F))
+
+
+def test_activations_of_4_gib_take_copies():
+    """The same for X and dY of the weight gradients, over the two halves of the tokens; Y and dX row for row."""
+    T, D, F = 1 << 20, 2048, 256
+    _needs(64)
+    print(f"activations of 4 GiB T={T} D={D} F={F}", flush=True)
+    X, W1, b1, W2, dY = _inputs(T, D, F)
+
+    def step(lo, hi):
+        with closing(ffn24.Context(hi - lo, D, F, ffn24.FFN24_TRAINING, ffn24.FFN24_BF16)) as c:
+            return c.ffn24_fwd(X[lo:hi], W1, b1, W2), *c.ffn24_bwd(dY[lo:hi])
+
+    full, a, b = step(0, T), step(0, T // 2), step(T // 2, T)
+    for i in (0, 1):
+        assert _equal([full[i][:T // 2], full[i][T // 2:]], [a[i], b[i]])
+    assert _sum_of_parts(full[2], a[2], b[2]) and _sum_of_parts(full[3], a[3], b[3])
