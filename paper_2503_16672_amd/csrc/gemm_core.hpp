@@ -377,9 +377,8 @@ template <int MI, int NI>
 struct FragD {
   bf16x8 a[MI], b[NI];
 };
-template <class G, int S, int I, int PROBE, int TR = 0, int MI, int NI>
+template <class G, int S, int I, int TR = 0, int MI, int NI>
 __device__ __forceinline__ void load_frag_dense1(const char* buf, const LaneCtx& L, FragD<MI, NI>& f) {
-  if constexpr ((PROBE & PROBE_NO_FRAG) != 0) return;
   if constexpr (I < MI && (TR & TR_A)) { f.a[I] = tr_read<128 * MI>(buf + (L.a_tr ^ (I << 5)) + S * (16 * 128 * MI)); return; }
   if constexpr (I >= MI && (TR & TR_B)) { f.b[I - MI] = tr_read<128 * NI>(buf + G::B_OFF + L.b_tr + 8 * (I - MI) + S * (16 * 128 * NI)); return; }
   if constexpr (G::WIDE) {
@@ -393,9 +392,8 @@ __device__ __forceinline__ void load_frag_dense1(const char* buf, const LaneCtx&
   if constexpr (I < MI) f.a[I] = *reinterpret_cast<const bf16x8*>(buf + L.a_row64 + I * (32 * 64) + c);
   else f.b[I - MI] = *reinterpret_cast<const bf16x8*>(buf + G::B_OFF + L.b_row64 + (I - MI) * (32 * 64) + c);
 }
-template <int M, int PROBE, int MI, int NI>
+template <int M, int MI, int NI>
 __device__ __forceinline__ void mfma_dense1(const FragD<MI, NI>& f, f32x16 (&acc)[MI][NI]) {
-  if constexpr ((PROBE & PROBE_NO_MFMA) != 0) return;
   constexpr int mi = M / NI, ni = M % NI;
   acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[mi], f.b[ni], acc[mi][ni], 0, 0, 0);
 }
@@ -413,9 +411,8 @@ __device__ __forceinline__ i32x8 cat16(const bf16x8& lo, const bf16x8& hi) {
 __device__ __forceinline__ void mfma_f8(const i32x8& a, const i32x8& b, f32x16& c) {
   c = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, 0, 0, 0);
 }
-template <int M, int PROBE, int MI, int NI>
+template <int M, int MI, int NI>
 __device__ __forceinline__ void mfma_dense_f8(const FragD<MI, NI>& f0, const FragD<MI, NI>& f1, f32x16 (&acc)[MI][NI]) {
-  if constexpr ((PROBE & PROBE_NO_MFMA) != 0) return;
   constexpr int mi = M / NI, ni = M % NI;
   mfma_f8(cat16(f0.a[mi], f1.a[mi]), cat16(f0.b[ni], f1.b[ni]), acc[mi][ni]);
 }
@@ -443,9 +440,8 @@ __device__ __forceinline__ void load_idx_sparse1(const char* buf, const LaneCtx&
   }
 }
 // fragment I of instruction S: I < MI -> a[I]; the next NI -> low halves of b; the last NI -> high halves of b
-template <class G, int S, int I, int PROBE, int TR = 0, int MI, int NI>
+template <class G, int S, int I, int TR = 0, int MI, int NI>
 __device__ __forceinline__ void load_frag_sparse1(const char* buf, const LaneCtx& L, FragS<MI, NI>& f) {
-  if constexpr ((PROBE & PROBE_NO_FRAG) != 0) return;
   if constexpr (I >= MI && (TR & TR_B)) {
     constexpr int i = (I - MI) % NI;
     const char* p = buf + G::B_OFF + L.b_tr + 8 * i + S * (16 * 128 * NI);
@@ -463,9 +459,8 @@ __device__ __forceinline__ void load_frag_sparse1(const char* buf, const LaneCtx
 }
 // fp8: v_smfmac_f32_32x32x64_fp8_fp8 has, byte for byte, the operand layout of the bf16 instruction (measured): A 16
 // stored bytes of the lane half's window, B the two 16-byte chunks, and a full 32-bit index word per instruction.
-template <bool F8, int S, int M, int PROBE, int MI, int NI>
+template <bool F8, int S, int M, int MI, int NI>
 __device__ __forceinline__ void mfma_sparse1(const FragS<MI, NI>& f, const IdxWords<F8> (&idx)[MI], f32x16 (&acc)[MI][NI]) {
-  if constexpr ((PROBE & PROBE_NO_MFMA) != 0) return;
   constexpr int mi = M / NI, ni = M % NI;
   if constexpr (F8) {
     acc[mi][ni] = __builtin_amdgcn_smfmac_f32_32x32x64_fp8_fp8(__builtin_bit_cast(i32x4, f.a[mi]), cat16(f.blo[ni], f.bhi[ni]), acc[mi][ni],
@@ -484,11 +479,11 @@ struct StageRegs {                           // dense: chunk pairs q of 32 bytes
   static constexpr int READS = PAIRS * NF, OPS = MI * NI * PAIRS / (F8 ? 2 : 1);
   static constexpr int READ_SLOTS = OPS > 1 ? OPS / 2 : 1;
   FragD<MI, NI> f[PAIRS];
-  template <class G, int I, int PROBE> __device__ __forceinline__ void read(const char* buf, const LaneCtx& L) { load_frag_dense1<G, I / NF, I % NF, PROBE, TR>(buf, L, f[I / NF]); }
-  template <int M, int PROBE> __device__ __forceinline__ void op(f32x16 (&acc)[MI][NI]) const {
+  template <class G, int I> __device__ __forceinline__ void read(const char* buf, const LaneCtx& L) { load_frag_dense1<G, I / NF, I % NF, TR>(buf, L, f[I / NF]); }
+  template <int M> __device__ __forceinline__ void op(f32x16 (&acc)[MI][NI]) const {
     constexpr int s = M / (MI * NI), m = M % (MI * NI);
-    if constexpr (F8) mfma_dense_f8<m, PROBE>(f[2 * s], f[2 * s + 1], acc);
-    else mfma_dense1<m, PROBE>(f[s], acc);
+    if constexpr (F8) mfma_dense_f8<m>(f[2 * s], f[2 * s + 1], acc);
+    else mfma_dense1<m>(f[s], acc);
   }
 };
 template <bool F8, int MI, int NI, int TR>
@@ -498,12 +493,12 @@ struct StageRegs<true, F8, MI, NI, TR> {
   static constexpr int READ_SLOTS = OPS / 2;
   FragS<MI, NI> f[2];
   IdxWords<F8> idx[MI];
-  template <class G, int I, int PROBE> __device__ __forceinline__ void read(const char* buf, const LaneCtx& L) {
+  template <class G, int I> __device__ __forceinline__ void read(const char* buf, const LaneCtx& L) {
     if constexpr (I < MI) load_idx_sparse1<G, F8, I>(buf, L, idx);
-    else load_frag_sparse1<G, (I - MI) / NF, (I - MI) % NF, PROBE, TR>(buf, L, f[(I - MI) / NF]);
+    else load_frag_sparse1<G, (I - MI) / NF, (I - MI) % NF, TR>(buf, L, f[(I - MI) / NF]);
   }
-  template <int M, int PROBE> __device__ __forceinline__ void op(f32x16 (&acc)[MI][NI]) const {
-    mfma_sparse1<F8, M / (MI * NI), M % (MI * NI), PROBE>(f[M / (MI * NI)], idx, acc);
+  template <int M> __device__ __forceinline__ void op(f32x16 (&acc)[MI][NI]) const {
+    mfma_sparse1<F8, M / (MI * NI), M % (MI * NI)>(f[M / (MI * NI)], idx, acc);
   }
 };
 
@@ -603,12 +598,12 @@ __device__ __forceinline__ void gemm_tile_small(const GemmArgs& g, const typenam
   using G = Geo<SPARSE, F8, MI, NI>;
   constexpr int NMF = MI * NI;              // matrix ops (slots) per K step
   constexpr int FRAG_SLOTS = (NMF + 1) / 2; // slots of a K step that carry fragment reads
-  constexpr int NB = G::NB, NDMA = G::NDMA, PROBE = 0;
+  constexpr int NB = G::NB, NDMA = G::NDMA;
 
   int tid = threadIdx.x;
   int lane = tid & 63, wave = tid >> 6;
   int tm, tn;
-  tile_coords<PROBE, MI == 2 * NI>(g.M / G::BM, g.N / G::BN, pid, tm, tn);
+  tile_coords<0, MI == 2 * NI>(g.M / G::BM, g.N / G::BN, pid, tm, tn);
   int m0 = tm * G::BM, n0 = tn * G::BN;
 
   // (written out here and in gemm_rows_kernel: from a function, returned or by reference, it costs the sparse 256 x 256 store kernels 1-4
@@ -626,7 +621,7 @@ __device__ __forceinline__ void gemm_tile_small(const GemmArgs& g, const typenam
 
   if constexpr (TR != 0) L.set_tr<MI, NI>(lane);
 
-  Dma<SPARSE, F8, PROBE, MI, NI, TR> dma;
+  Dma<SPARSE, F8, 0, MI, NI, TR> dma;
   dma.init(g, m0, n0, tid);
 
   const int nk = g.K / G::BK;
@@ -661,8 +656,8 @@ __device__ __forceinline__ void gemm_tile_small(const GemmArgs& g, const typenam
       constexpr int MODE = decltype(mode)::value, LEFT = decltype(left)::value;
       FFN24_FENCE();
       static_for<SR::OPS>([&](auto M) {
-        now.template op<M, PROBE>(acc);
-        if constexpr (MODE != 2) ride<SR::READS, SR::READ_SLOTS, M>([&](auto I) { next.template read<G, I, PROBE>(nxt, L); });
+        now.template op<M>(acc);
+        if constexpr (MODE != 2) ride<SR::READS, SR::READ_SLOTS, M>([&](auto I) { next.template read<G, I>(nxt, L); });
         // (from 4 matrix ops a K step on, behind the fragment reads: 256 x 128 36.5 -> 35.8 us, dense 128 x 128 11.2 -> 10.6; 128 x 64 15.2 -> 15.7)
         constexpr int FIRST = NMF >= 4 ? SR::OPS / 2 : 0;
         if constexpr (MODE == 0 && M >= FIRST) ride<NDMA, SR::OPS - FIRST, M - FIRST>([&](auto J) { dma.template issue<J>(kt + NB, cur); });
@@ -682,7 +677,7 @@ __device__ __forceinline__ void gemm_tile_small(const GemmArgs& g, const typenam
       stage(kt, smem + slot * G::STAGE, smem + ns * G::STAGE, now, next, mode, left);
       slot = ns;
     };
-    static_for<SR::READS>([&](auto I) { r0.template read<G, I, PROBE>(smem, L); });
+    static_for<SR::READS>([&](auto I) { r0.template read<G, I>(smem, L); });
     if (npro == NB) wait_vmcnt<(NB - 2) * NDMA>(); else wait_vmcnt<0>();   // stage 1, which stage 0 reads
     wait_lgkmcnt0();
     __builtin_amdgcn_s_barrier();
@@ -708,14 +703,14 @@ __device__ __forceinline__ void gemm_tile_small(const GemmArgs& g, const typenam
     constexpr int NF = MI + 2 * NI;
     IdxWords<F8> idx[MI];
     static_for<MI>([&](auto I) { load_idx_sparse1<G, F8, I>(smem, L, idx); });
-    static_for<NF>([&](auto I) { load_frag_sparse1<G, 0, I, PROBE, TR>(smem, L, f0); });
+    static_for<NF>([&](auto I) { load_frag_sparse1<G, 0, I, TR>(smem, L, f0); });
     auto stage = [&](int kt, char* cur, char* nxt, auto mode) {
       constexpr int MODE = decltype(mode)::value;
       IdxWords<F8> idx_n[MI] = {};
       FFN24_FENCE();
       static_for<NMF>([&](auto M) {
-        mfma_sparse1<F8, 0, M, PROBE>(f0, idx, acc);
-        ride<NF, FRAG_SLOTS, M>([&](auto I) { load_frag_sparse1<G, 1, I, PROBE, TR>(cur, L, f1); });
+        mfma_sparse1<F8, 0, M>(f0, idx, acc);
+        ride<NF, FRAG_SLOTS, M>([&](auto I) { load_frag_sparse1<G, 1, I, TR>(cur, L, f1); });
         FFN24_FENCE();
       });
       if constexpr (MODE != 2) {
@@ -726,11 +721,11 @@ __device__ __forceinline__ void gemm_tile_small(const GemmArgs& g, const typenam
       }
       FFN24_FENCE();
       static_for<NMF>([&](auto M) {
-        mfma_sparse1<F8, 1, M, PROBE>(f1, idx, acc);
+        mfma_sparse1<F8, 1, M>(f1, idx, acc);
         if constexpr (MODE == 0) ride<NDMA, NMF, M>([&](auto J) { dma.template issue<J>(kt + NB, cur); });
         if constexpr (MODE != 2) {
           if constexpr (M < MI) load_idx_sparse1<G, F8, M>(nxt, L, idx_n);
-          ride<NF, FRAG_SLOTS, M>([&](auto I) { load_frag_sparse1<G, 0, I, PROBE, TR>(nxt, L, f0); });
+          ride<NF, FRAG_SLOTS, M>([&](auto I) { load_frag_sparse1<G, 0, I, TR>(nxt, L, f0); });
         }
         FFN24_FENCE();
       });
@@ -753,17 +748,17 @@ __device__ __forceinline__ void gemm_tile_small(const GemmArgs& g, const typenam
     // one barrier at the end of the stage.  Two fragment sets alternate.
     FragD<MI, NI> fr[2][2];
     constexpr int NF = MI + NI;
-    static_for<NF>([&](auto I) { load_frag_dense1<G, 0, I, PROBE, TR>(smem, L, fr[0][0]); });
-    static_for<NF>([&](auto I) { load_frag_dense1<G, 1, I, PROBE, TR>(smem, L, fr[0][1]); });
+    static_for<NF>([&](auto I) { load_frag_dense1<G, 0, I, TR>(smem, L, fr[0][0]); });
+    static_for<NF>([&](auto I) { load_frag_dense1<G, 1, I, TR>(smem, L, fr[0][1]); });
     auto stage = [&](int kt, char* cur, char* nxt, auto par, auto mode) {
       constexpr int P = decltype(par)::value, MODE = decltype(mode)::value;
       FFN24_FENCE();
       static_for<NMF>([&](auto M) {
-        mfma_dense_f8<M, PROBE>(fr[P][0], fr[P][1], acc);
+        mfma_dense_f8<M>(fr[P][0], fr[P][1], acc);
         if constexpr (MODE == 0) ride<NDMA, NMF, M>([&](auto J) { dma.template issue<J>(kt + NB, cur); });
         if constexpr (MODE != 2) ride<2 * NF, NMF, M>([&](auto I) {
-          if constexpr (I < NF) load_frag_dense1<G, 0, I, PROBE, TR>(nxt, L, fr[P ^ 1][0]);
-          else load_frag_dense1<G, 1, I - NF, PROBE, TR>(nxt, L, fr[P ^ 1][1]);
+          if constexpr (I < NF) load_frag_dense1<G, 0, I, TR>(nxt, L, fr[P ^ 1][0]);
+          else load_frag_dense1<G, 1, I - NF, TR>(nxt, L, fr[P ^ 1][1]);
         });
         FFN24_FENCE();
       });
@@ -800,13 +795,13 @@ __device__ __forceinline__ void gemm_tile_small(const GemmArgs& g, const typenam
   } else {
     FragD<MI, NI> f0, f1;
     constexpr int NF = MI + NI;
-    static_for<NF>([&](auto I) { load_frag_dense1<G, 0, I, PROBE, TR>(smem, L, f0); });
+    static_for<NF>([&](auto I) { load_frag_dense1<G, 0, I, TR>(smem, L, f0); });
     auto stage = [&](int kt, char* cur, char* nxt, auto mode) {
       constexpr int MODE = decltype(mode)::value;
       FFN24_FENCE();
       static_for<NMF>([&](auto M) {
-        mfma_dense1<M, PROBE>(f0, acc);
-        ride<NF, FRAG_SLOTS, M>([&](auto I) { load_frag_dense1<G, 1, I, PROBE, TR>(cur, L, f1); });
+        mfma_dense1<M>(f0, acc);
+        ride<NF, FRAG_SLOTS, M>([&](auto I) { load_frag_dense1<G, 1, I, TR>(cur, L, f1); });
         FFN24_FENCE();
       });
       if constexpr (MODE != 2) {
@@ -816,9 +811,9 @@ __device__ __forceinline__ void gemm_tile_small(const GemmArgs& g, const typenam
       }
       FFN24_FENCE();
       static_for<NMF>([&](auto M) {
-        mfma_dense1<M, PROBE>(f1, acc);
+        mfma_dense1<M>(f1, acc);
         if constexpr (MODE == 0) ride<NDMA, NMF, M>([&](auto J) { dma.template issue<J>(kt + NB, cur); });
-        if constexpr (MODE != 2) ride<NF, FRAG_SLOTS, M>([&](auto I) { load_frag_dense1<G, 0, I, PROBE, TR>(nxt, L, f0); });
+        if constexpr (MODE != 2) ride<NF, FRAG_SLOTS, M>([&](auto I) { load_frag_dense1<G, 0, I, TR>(nxt, L, f0); });
         FFN24_FENCE();
       });
     };
@@ -1362,7 +1357,7 @@ __global__ void __launch_bounds__(GEMM_THREADS, (GeoRows<MI, NI>::PER_CU)) gemm_
   auto first = [&](const char* cur, const char* nxt) {
     const char* abuf = shifted ? nxt : cur;
     static_for<SR::OPS>([&](auto M) {
-      r0.template op<M, 0>(acc);
+      r0.template op<M>(acc);
       ride<SR::READS, SR::READ_SLOTS, M>([&](auto I) { read_rows<MI, NI, 1, I>(cur, abuf, L, r1); });
       FFN24_FENCE();
     });
@@ -1371,7 +1366,7 @@ __global__ void __launch_bounds__(GEMM_THREADS, (GeoRows<MI, NI>::PER_CU)) gemm_
   auto second = [&](int kt, char* cur, const char* nxt, auto issue, auto more) {
     constexpr bool ISSUE = decltype(issue)::value, MORE = decltype(more)::value;
     static_for<SR::OPS>([&](auto M) {
-      r1.template op<M, 0>(acc);
+      r1.template op<M>(acc);
       if constexpr (MORE) ride<SR::READS, SR::READ_SLOTS, M>([&](auto I) { read_rows<MI, NI, 0, I>(nxt, nxt, L, r0); });
       if constexpr (ISSUE) ride<NDMA, SR::OPS, M>([&](auto J) { dma.template issue<J>(kt + NB, cur); });
       FFN24_FENCE();
