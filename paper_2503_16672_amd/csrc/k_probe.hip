@@ -164,7 +164,9 @@ int probe_mfma_rate(int kind, int iters, double* cycles_per_op, double* mhz, dou
   };
   hipEvent_t e0, e1;
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) return 1;
-  launch(200, 1u);   // warm-up: clocks and code in place
+  // 20 ms of the same first: when matrix load sets in the power controller holds the clock down for some milliseconds, and a loop that starts with them
+  // shows less than what it sustains (dense bf16, 4 ms from idle 1.67-1.95 PFLOP/s, after this 2.08)
+  launch(kind < 2 ? 40000 : 20000, 1u);
   (void)hipEventRecord(e0, nullptr);
   launch(iters, 7u);
   (void)hipEventRecord(e1, nullptr);
