@@ -122,7 +122,7 @@ FFN24_API int ffn24_set_row_scales(ffn24_ctx* ctx, const float* sx, const float*
  * memory, cols a multiple of 8.  axis 1: one scale per row, scales[r] = max_c |X[r][c]| / 448 (1 if the row is all zero);
  * axis 0: one scale per column, scales[c] = max_r |X[r][c]| / 448.  codes[r][c] = e4m3(X[r][c] / scale), round to nearest even
  * (nothing saturates: the largest entry of every row / column maps to 448).  codes: rows x cols bytes, row-major; scales: fp32,
- * [rows] or [cols] (with axis 0 the codes buffer holds intermediate values until the call's last kernel has run).  These are the
+ * [rows] or [cols] (with axis 0 the codes buffer may hold intermediate values until the call's last kernel has run).  These are the
  * (codes, scales) pairs that ffn24_set_row_scales / ffn24_fwd and ffn24_bwd_rowwise take, made from the caller's bf16 tensors:
  * X per row, W1 and W2 per column for the forward; dY per row and per column, X per column, W2 and W1 per row for the backward.
  * Empty matrices are a no-op.  FFN24_ERR_SHAPE for another axis or cols % 8 != 0. */
@@ -240,7 +240,8 @@ FFN24_API int ffn24_prepare_weights(ffn24_ctx* ctx, const void* W1, const void* 
  *   X [T][D], W1 [D][F], b1 [F] fp32 or NULL (the paper's FFN has no bias; b1 only dials the sparsity of synthetic
  *   inputs), W2 [F][D], Y [T][D].  W1 and W2 both NULL: the weights of ffn24_prepare_weights (FFN24_ERR_STATE if none).
  * Kernels: one pass over the weights (fp8: transposes, every fp8 GEMM operand is consumed K-contiguous; bf16: the copies that a
- * context with FFN24_TRAINING keeps for the backward, the forward itself reads W1 and W2 where they lie), the dense-MFMA
+ * context with FFN24_TRAINING keeps for the backward; the forward itself reads W1 and W2 where they lie, or, with many tokens beside small weights,
+ * re-arranged where that is faster), the dense-MFMA
  * up-projection with the activation and the pruning fused into its epilogue (H is never written densely), the sparse-MFMA
  * down-projection.  The context keeps (Hc, meta), its own re-arranged copies of W1 and W2 and the X pointer for
  * ffn24_bwd; the caller keeps X alive and unchanged until then. */
@@ -251,8 +252,8 @@ FFN24_API int ffn24_fwd(ffn24_ctx* ctx, const void* X, const void* W1, const flo
  * intermediate tensors -- the compressed activation and the two re-arranged weights, T F + T F / 8 + 4 D F bytes, which
  * ffn24_ctx_create would allocate -- live in a static device array of FFN24_STATIC_SCRATCH_BYTES inside the library, of
  * which every GPU that loads the library holds one copy until the process ends.  The call allocates and frees nothing
- * and calls no allocating routine; it only enqueues two kernels on `stream` (three where Y lies over W2: only then are the
- * weights re-arranged, otherwise they are read where they lie).
+ * and calls no allocating routine; it only enqueues two kernels on `stream`, which read the weights where they lie (three where Y lies
+ * over W2, and with many tokens beside small weights, where re-arranging them first is faster).
  *   X [T][D], W1 [D][F], b1 [F] fp32 or NULL, W2 [F][D], Y [T][D]: device pointers, bf16, caller-owned as everywhere.
  *   T, D, F multiples of 256.  FFN24_ERR_SCRATCH if ffn24_static_scratch_needed(T, D, F) exceeds the buffer (use a
  *   context then); the other error codes as for ffn24_fwd.
@@ -347,7 +348,7 @@ FFN24_API int ffn24_kernel_mhz(ffn24_ctx* ctx, int kernel, float* mhz);
  * device buffers, runs on the default stream and waits for its own work; not for serving code.
  *   ffn24_probe_mfma_rate: a register-resident loop of matrix instructions with no memory traffic, one wave per SIMD on
  *     every CU, pseudo-random operands.  kind 0 dense bf16 16x16x32, 1 sparse bf16 16x16x64, 2 dense fp8 16x16x128,
- *     3 sparse fp8 16x16x128; iters x 64 ops per wave.  Returns shader-clock cycles per op and wave, the clock (MHz) the
+ *     3 sparse fp8 16x16x128; iters x 64 ops per wave, after 20 ms of the same loop (under new load the clock is held down at first).  Returns shader-clock cycles per op and wave, the clock (MHz) the
  *     loop ran at, and the chip-wide rate in dense-equivalent TFLOP/s (a sparse op counts its dense equivalent).
  *   ffn24_probe_gemm: the library's GEMM core (dense bf16 if sparse == 0, else 2:4 bf16; plain row-major epilogue) on
  *     pseudo-random operands, M, N multiples of 256, K a multiple of 128 and >= 512, with ingredients of its main loop
@@ -355,7 +356,7 @@ FFN24_API int ffn24_kernel_mhz(ffn24_ctx* ctx, int kernel, float* mhz);
  *     5 matrix ops only, 8 every K stage re-reads the first 8 stages (all L2 hits), 14 = 8 + 6; or the whole loop with
  *     another tile walk: 16 bands of 8 tile-rows per XCD, 32 the 8 per-XCD patches of a round side by side along M,
  *     64 patches of 4 x 8 tiles, 128 patches of 16 x 2 tiles (the product: a 4 x 2 grid of 8 x 4 patches); or, 256, with a
- *     stage's DMA instructions on consecutive matrix-op slots (the product issues them on every other slot); or, 512 (sparse only),
+ *     stage's DMA instructions on consecutive matrix-op slots (the product issues one on every 64 cycles, 128 in the dense loop); or, 512 (sparse only),
  *     with a quarter of every stage's operand bytes not fetched; or, 1024, as 256 persistent workgroups that walk the tiles and ask
  *     for a tile's first stages before the epilogue of the tile before.  Returns the median
  *     kernel duration over `reps` launches and the clock it ran at.  Variants other than 0 compute nothing meaningful.

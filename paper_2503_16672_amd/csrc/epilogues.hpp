@@ -201,7 +201,7 @@ struct LaneSavedDense {
   }
 };
 
-// C[m][n], n contiguous: 4 consecutive columns per lane and row -> one 8-byte store per row.
+// C[m][n], n contiguous: a lane's neighbouring columns of a row leave in one store, 16 bytes (8 columns) with the 256 x 256 tile, 2 NI bytes with the others.
 struct EpiRowMajor {
   struct Args { __bf16* C; int ldc; };
   template <int MI, int NI, class Acc>

@@ -27,7 +27,7 @@
 // A dense A operand can be in panel form too: piece (r, kp) = the 32 k (64 bytes) [32 kp, 32 kp + 32) of row r,
 // same piece index with K / 32 panels per row (the weight copies the library makes for itself).
 //
-// Data movement.  Global memory goes straight to LDS (global_load_lds_dwordx4: no VGPR staging, no LDS store
+// Data movement.  Global memory goes straight to LDS (buffer loads with LDS as their destination: no VGPR staging, no LDS store
 // instructions) into a ring of stage buffers, 2-3 stages ahead of the math, so that L2/HBM latency is covered:
 //   dense : stage = 32 k  (A 16 KiB + B 16 KiB), ring of 4  -> 128 KiB of the CU's 160 KiB LDS (fp8: 64 k, ring of 5, all of it)
 //   sparse: stage = 64 k  (A 16 KiB stored values + 2 KiB metadata + B 32 KiB), ring of 3 -> 151 KiB
@@ -190,8 +190,9 @@ __device__ __forceinline__ int swz8_big(int i) { return (i & 2) | (((i >> 3) & 1
 // Against a pass that transposed them first: forward at T 1024 D 1024 F 4096 39.4 -> 25.6 us, bf16 step at T 1280 D 768 F 3072 78.7 -> 67.5, dense
 // step at T 4096 D 2048 F 8192 732 -> 709; GEMM by GEMM (panel form -> k-major) T 8192 D 2048 F 8192 up-projection 222 -> 215, down-projection 121 -> 114,
 // dW2 122 -> 116, T = F = 16384 D 4096 within 1 %, sparse 128 x 64 at T 2048 D 1024 F 4096 17.2 -> 19.0.
-// Swizzles: what 32 lanes (16 where only one half of each piece is used) read at a time lies in different banks.  The rate of such reads is that of
-// 16-byte reads then (221 against 256 B/clk in a loop of nothing else; 32 without the swizzle).
+// Swizzles: what 32 lanes (16 where only one half of each piece is used) read at a time lies in different banks.  The rate of such reads is near that of
+// 16-byte reads then (221 against 256 B/clk in a loop of nothing else; 32 without the swizzle).  Inside the 256 x 256 loops, beside the DMA's writes, the counters
+// see conflicts in 0-1 % of the LDS-active cycles with B k-major, but in a third of them with A k-major (panels: none), T = F = 16384, D 4096.
 constexpr int TR_A = 1, TR_B = 2;
 template <int MI, int NI> __device__ __forceinline__ int tr_swz_a(int k) {
   if constexpr (MI * NI == 16) return (k & 3) | ((k >> 3) & 1) << 2;
@@ -606,8 +607,6 @@ __device__ __forceinline__ void gemm_tile_small(const GemmArgs& g, const typenam
   tile_coords<0, MI == 2 * NI>(g.M / G::BM, g.N / G::BN, pid, tm, tn);
   int m0 = tm * G::BM, n0 = tn * G::BN;
 
-  // (written out here and in gemm_rows_kernel: from a function, returned or by reference, it costs the sparse 256 x 256 store kernels 1-4
-  // spilled registers)
   LaneCtx L;
   L.rho = lane & 31; L.h = lane >> 5; L.wy = wave >> 1; L.wx = wave & 1;
   L.a_row64 = (L.wy * (32 * MI) + L.rho) * 64;
@@ -743,7 +742,7 @@ __device__ __forceinline__ void gemm_tile_small(const GemmArgs& g, const typenam
     for (; kt < nk - 1; kt++) advance(kt, std::integral_constant<int, 1>{});
     advance(kt, std::integral_constant<int, 2>{});
   } else if constexpr (F8) {
-    // Dense fp8: a stage is ONE K step of 16 matrix ops (64 cycles each).  The fragments of the whole next stage and
+    // Dense fp8, 256 x 128: a stage is ONE K step of 8 matrix ops (64 cycles each).  The fragments of the whole next stage and
     // the DMA of the stage that reuses this stage's buffer (its fragments are already in registers) ride on them;
     // one barrier at the end of the stage.  Two fragment sets alternate.
     FragD<MI, NI> fr[2][2];
@@ -838,7 +837,8 @@ __device__ __forceinline__ void gemm_tile_small(const GemmArgs& g, const typenam
 // The 256 x 256 block tile: four waves of 128 x 128, one a SIMD, 256 accumulators a lane pinned to the AGPR file.  Its matrix ops are the
 // 16 x 16 ones: under matrix load the chip is bound by its power limit, and a 16 x 16 op moves fewer accumulator bytes a flop through the
 // register file than a 32 x 32 one.  Register-resident loops at the power limit, N(0, 1) operands, 32 x 32 -> 16 x 16 (PFLOP/s dense equivalent):
-// dense bf16 1.83 -> 2.09, 2:4 bf16 3.37 -> 3.55, dense fp8 4.11 -> 4.47, 2:4 fp8 6.49 -> 6.89.  The whole loop, pseudo-random operands, M 16384
+// dense bf16 1.83 -> 2.09, 2:4 bf16 3.37 -> 3.55, dense fp8 4.11 -> 4.47, 2:4 fp8 6.49 -> 6.89 (the rates depend on the operands: with the
+// uniform ones of probe_mfma_rate the 16 x 16 loops give 2.01, 3.41, 4.66 and 7.07).  The whole loop, pseudo-random operands, M 16384
 // N 4096: dense bf16 K 16384 1.59 -> 1.53 ms, K 4096 0.495 -> 0.467, 2:4 1.02 -> 0.98, 0.262 -> 0.256; the steps of the block at T = F = 16384, D 4096
 // 7.45 -> 7.09 ms, fp8 forward at T = D = 8192, F 32768 2.48 -> 2.33 ms.  What bounds it is energy: the clock settles 15 % higher than with the
 // 32 x 32 ops (1.75 against 1.52 GHz) and a stage takes 10 % more cycles (1290 against 1180 of 1024), and whatever saves cycles alone (B fragments read two
@@ -909,7 +909,7 @@ __device__ __forceinline__ void big_read_b(const char* buf, const char* buf2, co
 // pipes idle: measured per 512 cycles of matrix ops, the ones that carried 14 DMA instructions took 1200 cycles.  So they are spread over
 // the whole step from its barrier to the next one: half of them in half 1, the rest in half 0 of the NEXT step, still into the buffer that the stage
 // before freed -- one stage buffer is therefore half filled across a stage boundary, which costs nothing because the ring keeps NB - 2 whole
-// stages in flight anyway.  One instruction on every 64 cycles (2:4, 13 or 14 a stage) or 128 (dense).  Fragment reads take the slots between.
+// stages in flight anyway.  One instruction on every 64 cycles (2:4, 13 or 14 a stage) or 128 (dense, 8 a stage).  Fragment reads take the slots between.
 // which fragment read of B rides on op M of a half: two on every four ops
 constexpr int big_read_slot(int M) { return M % 4 == 1 ? M / 4 * 2 : M % 4 == 2 ? M / 4 * 2 + 1 : -1; }
 template <int SLOTS, int N> constexpr int paced(int M) { return M % SLOTS == 0 && M / SLOTS < N ? M / SLOTS : -1; }

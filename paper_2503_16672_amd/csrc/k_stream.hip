@@ -331,7 +331,10 @@ int launch_featurewise24_split(const void* Hc, const uint8_t* meta, const void* 
 // padding the lanes' runs would start a multiple of 32 words apart, all in two banks.  The rows are first written over the counts
 // in LDS and leave in feature order, so that the stores to row_of_feat are whole lines and those to feat_of_row nearly so.
 constexpr int PART_LDS_FEATS = 32768, PART_BINS = 2048;   // one workgroup of 1024: two bins a thread
-constexpr int PART_SHARED_FEATS = 16384;                   // in a launch with other work: two workgroups a CU
+// In a launch with the quantisation of dZ, whose workgroups get the LDS of the counts too: two of them a CU up to here, one beyond it (not tried).  Apart, together,
+// whole row-wise steps (us, T D F): 256 512 2048 60.1, 57.8; 1280 768 3072 90.0, 86.6; 8192 2048 8192 720, 711; 512 3072 12288 277, 274; 4096 3072 12288 813, 803;
+// 512 4096 16384 421, 417; 4096 4096 16384 1221, 1211; 16384 4096 16384 4215, 4210.
+constexpr int PART_SHARED_FEATS = 16384;
 __device__ __forceinline__ int part_slot(int f) { return f + (f >> 5); }
 
 // (a workgroup of 1024; s_nnz: F counts if they fit)
@@ -487,7 +490,7 @@ int launch_unpanel(const void* src, int rows, int npanels, int piece_bytes, void
 // writes over all banks); then 16 bytes of a transposed row per work item go out: 128 rows x 128 bytes.  (One 64 x 64 tile per
 // workgroup with element-wise LDS scatter, the first version, moved 4.3-4.9 TB/s.)
 // OUT_FORM: 0 row-major; 1 the dense panel form of gemm_core.hpp (64-byte pieces of 32 k, K = R), as A operands take it;
-// 2 the B panel form (the same with the rows of every block of 256 in LDS order).
+// 2 the B panel form (the same with row n of every block of 256 at b_panel_pos(n)).
 // in_panel (optional): a copy of the input itself in panel form (K = C), made in the same pass; in_panel_b: in the B form.
 // in_rowmap (optional): input row r is read from memory row in_rowmap[r] (token permutation).
 // Two transposes may share a launch (a step needs them in pairs, both weights or both activations: at small sizes a launch costs as much
@@ -646,7 +649,7 @@ __device__ __forceinline__ void transpose8_tile(const TransposeJob& job, int til
 // What a forward or backward needs done before its first GEMM, in one launch (each of these passes by itself is about as long as its
 // launch: T = 8192 D = 2048 F = 8192, token permutation and split, 4 + 6 launches of 4.7-9 us became 2):
 //   copies: byte matrices [R][C] (row-major, C a multiple of 64) into the dense fp8 panel form (64-byte pieces of 64 k, K = C) as A
-//     operands take it, or, b_form, into the B panel form (rows of every block of 256 in LDS order); row r is taken from memory row
+//     operands take it, or, b_form, into the B panel form (row n of every block of 256 at b_panel_pos(n)); row r is taken from memory row
 //     rowmap[r] if one is given (token permutation); 16 bytes per work item;
 //   zero: 32-bit words cleared (row maxima, counts);
 //   gather: dst[i] = src[map[i]], a per-token scale vector brought into the order of a token permutation.

@@ -16,7 +16,7 @@ template <class T> __device__ __forceinline__ void st_keep(T* p, T v) { *p = v; 
 // Input: token-wise compressed Hc [T][F/2] + meta [T][F/8], and optionally dZc [T][F/2] with the same metadata.
 // Output: for every feature, groups of 4 consecutive tokens of the pruned activation keep their top-2:
 //   Hc_t [F][T/2], meta_t [F][T/8], and dZc_t [F][T/2] = dZ at the positions picked for H.
-// Inputs and outputs in the panel form of gemm_core.hpp (a caller's row-major tensors: PANEL = false and featurewise24_rows_kernel below).
+// Inputs and outputs in the panel form of gemm_core.hpp (a caller's row-major tensors: PANEL = false, and featurewise24_rows_kernel in k_stream.hip).
 // One workgroup handles 64 tokens x 64 features at a time: decompress into LDS, then each work item takes two features and 8 consecutive
 // tokens (two groups each).  A tile's input is one contiguous 4 KiB run per tensor and it writes one contiguous 4 KiB run; 128-token
 // tiles, with twice the LDS per workgroup and half the workgroups per CU, ran at 5.0 instead of 5.9 TB/s.  Words are pairs of features

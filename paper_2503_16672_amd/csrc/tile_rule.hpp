@@ -16,6 +16,10 @@ namespace ffn24 {
 // faster.  GEMM by GEMM, each of the five tiles in whole steps: 78 % of 480 choices cost at most 0.4 % of a step over the best one, 90 % at most
 // 2 %; the worst are 7.2 and 6.0 % (T 1792 D 2304 F 6400, dense and bf16 step: 128 x 128 where 256 x 256 is the better), the others
 // above 3 % mostly small shapes that take a tile one size too large and weight gradients of half a round that are faster on 128 x 128.
+// The 256 x 256 tile has since been given the 16 x 16 matrix ops (gemm_core.hpp) and gained 2-6 % on the others.  Looked at again, 88 training steps (four kinds,
+// T 256-16384, D 512-4864, F 1024-16384), with every GEMM one tile smaller, one larger, or 256 x 256: 76 are within 0.5 % of the best of the four, the worst 3.5 % from it
+// (row-wise fp8, 768 768 3072: 65.7 us, 63.5 with the smaller tiles), the worst that would gain from 256 x 256 2.0 % (dense 12288 2048 6144: 1549, 1518); the
+// mean against 256 x 256 throughout is 1.31 x, the least 0.98.
 // What the rule avoids: a bf16 step at T 2304 D 4864 F 15616 (2.1 rounds) is 1.8 % longer with 256 x 128 up-projection and dH than with 256 x 256.
 struct TileCost { int mi, ni, per_k, fixed; };   // 0.1 ns per (bf16) k; ns per tile
 constexpr TileCost TILES_SPARSE[] = {{4, 4, 140, 6000}, {4, 2, 92, 5000}, {2, 2, 57, 3000}, {2, 1, 39, 2000}, {1, 1, 26, 1500}};
@@ -24,8 +28,8 @@ constexpr int NUM_TILES = 5;   // the tables list the same tiles
 constexpr long long CHIP_CUS = 256;
 
 // What an epilogue adds to the fill and store of the two largest dense tiles (ns).  The fp8 epilogues scale or quantise every value beside
-// 256 accumulators, and half the reduction time covers it less.  The dense row-wise one spills 44 registers on the 256 x 128 tile and 22 on the
-// 256 x 256: the two are equal at 1.8-2.6 rounds (544 us either way at T 5888 D 2304 F 5120, 690 and 691 at T 7168 D 2048 F 6144), where
+// 256 accumulators, and half the reduction time covers it less.  The dense row-wise one spills 42 registers on the 256 x 128 tile and 6 on the
+// 256 x 256 (44 and 22 when these were fitted): the two were equal at 1.8-2.6 rounds (544 us either way at T 5888 D 2304 F 5120, 690 and 691 at T 7168 D 2048 F 6144), where
 // the accumulators alone would make 256 x 128 the better.
 struct EpiCost { int t256x256, t256x128; };
 constexpr EpiCost EPI_PLAIN = {0, 0}, EPI_FP8 = {3000, 0}, EPI_FP8_SPILLS = {3000, 8000};
